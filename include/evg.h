@@ -137,7 +137,10 @@ typedef struct {
    * before a first message arrives).  evg_init asks the runtime about each pointer:
    * host memory, memory of another device, or an allocation that ends before the
    * stated size gives EVG_ERR_INVALID (the same holds for evg_step's grad and
-   * evg_average's out). */
+   * evg_average's out).  Between evg_init and evg_destroy xhat, the mailboxes and vel are
+   * the library's to write: a mailbox that has received equals its sender's xhat (unless
+   * delivery is delayed or xhat_reset moves xhat without a message), and evg_step reads
+   * whichever copy is nearer. */
   float* x;      /* current parameters                                   */
   float* xhat;   /* values last sent (Section 4, X-hat)                   */
   float* mbox_l; /* last received from the left neighbour (r-1)           */

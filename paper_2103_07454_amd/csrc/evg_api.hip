@@ -706,6 +706,9 @@ static evg_status fixed_args(evg_ctx* c, const float* grad, StepArgs* out) {
   a.hist_fused = (g.topk_ppm && g.norm_mode == EVG_NORM_FUSED) ? 1u : 0u;
   a.cached = c->cached ? 1u : 0u;
   a.pull = c->t.xsnap ? 1u : 0u;
+  // a mailbox equals its sender's xhat wherever a message has arrived, unless messages are under way
+  // (delay) or xhat moves without a message (reset)
+  a.share = (!c->cached && !g.delivery_delay && !(g.xhat_reset && g.topk_ppm)) ? 1u : 0u;
   a.xhat_reset = (g.xhat_reset && g.topk_ppm) ? 1u : 0u;
   const bool norm_diff = g.trigger_kind == EVG_TRIGGER_NORM_DIFF;
   // fused + whole-tensor sends: xhat's norm is a scalar per tensor and xhat is never read

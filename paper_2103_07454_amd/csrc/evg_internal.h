@@ -8,6 +8,8 @@ namespace evg {
 constexpr int kThreads = 256;          // 4 wavefronts of 64 lanes
 constexpr int kLaneElems = 4;          // one float4 per lane and sweep
 constexpr int kSweep = kThreads * kLaneElems;   // elements one workgroup covers per sweep
+constexpr uint32_t kXcds = 8;          // compute dies, each with an L2 of its own
+constexpr uint32_t kSegTiles = 128;    // 1024-element tiles of one worker that an XCD takes before the next worker's
 constexpr int kHistBins = 2048;        // 11 key bits per selection pass (passes A, B); pass C uses 512
 constexpr uint32_t kStageCap = 2048;   // staged entries / in-bin keys of a chunk that the staging kernel
 constexpr uint32_t kStageCapBin = 1024;   // gathers in LDS before writing them out (more: direct stores)
@@ -115,6 +117,8 @@ struct StepArgs {
   uint32_t from_device;    // take k and decay^k from IterState instead of the two fields here
   uint32_t xhat_reset;     // a Top-K event resets the whole tensor's xhat to x
   uint32_t cached;         // the arenas fit the last-level cache: ordinary instead of streaming accesses
+  uint32_t share;          // streaming ring whose mailboxes equal the senders' xhat: the update pass reads it there
+  uint32_t xcd_tiles;      // share: tiles per XCD (set by launch_update)
   uint32_t pull;           // whole-tensor sends are fetched by the receivers inside the update pass
   uint32_t one_launch;     // ... and the update pass also runs the trigger tests (no other kernel in the step)
   uint32_t step_no;        // one_launch: steps completed before this one (picks the copy of x to read)

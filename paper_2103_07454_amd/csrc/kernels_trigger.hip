@@ -7,6 +7,7 @@
 //   k_expand   writes the compact lists of chunks to copy / to Top-K select.
 //   k_copy     x -> left neighbour's right mailbox, right neighbour's left mailbox for
 //              every listed chunk: the stand-in for the one-sided puts of Section 6.
+//              Rings whose update pass reads the neighbours' xhat: x -> xhat.
 #include "trigger_device.h"
 
 namespace evg {
@@ -104,8 +105,10 @@ __global__ __launch_bounds__(kThreads) void k_expand(Tables T) {
   for (uint32_t i = lane_id(); i < ld.nchunks; i += 64) dst[i] = first + i;
 }
 
-// (xhat takes the sent values in the update pass, which has them in registers.)
-template <int SWEEPS, bool STREAM>
+// HAT = false: the two mailboxes (xhat takes the sent values in the update pass, which has them
+// in registers).  HAT = true: xhat alone -- the receivers read it there in the update pass and
+// store it into their mailboxes.
+template <int SWEEPS, bool STREAM, bool HAT>
 __global__ __launch_bounds__(kThreads) void k_copy(Tables T) {
   const uint32_t n = T.counts[0];
   for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
@@ -114,7 +117,7 @@ __global__ __launch_bounds__(kThreads) void k_copy(Tables T) {
     const ChunkDesc cd = T.chunks[c];
     const uint32_t left = (r + T.P - 1) % T.P, right = (r + 1) % T.P;
     const float* src = T.x + (size_t)r * T.Npad + cd.off;
-    float* d1 = T.mbox_r + (size_t)left * T.Npad + cd.off;
+    float* d1 = HAT ? T.xhat + (size_t)r * T.Npad + cd.off : T.mbox_r + (size_t)left * T.Npad + cd.off;
     float* d2 = T.mbox_l + (size_t)right * T.Npad + cd.off;
 #pragma unroll
     for (int it = 0; it < SWEEPS; ++it) {
@@ -122,7 +125,7 @@ __global__ __launch_bounds__(kThreads) void k_copy(Tables T) {
       if (e < cd.len) {
         const float4 v = ld4t<STREAM>(src + e);
         st4t<STREAM>(d1 + e, v);
-        st4t<STREAM>(d2 + e, v);
+        if (!HAT) st4t<STREAM>(d2 + e, v);
       }
     }
   }
@@ -193,21 +196,22 @@ __global__ __launch_bounds__(kThreads) void k_deliver(Tables T) {
   }
 }
 
-template <bool STREAM>
+template <bool STREAM, bool HAT>
 static hipError_t launch_copy_v(const Tables& t, uint32_t chunk_elems, uint32_t grid, hipStream_t s) {
   const dim3 g(grid), b(kThreads);
   switch (chunk_elems / kSweep) {
-    case 1: k_copy<1, STREAM><<<g, b, 0, s>>>(t); break;
-    case 2: k_copy<2, STREAM><<<g, b, 0, s>>>(t); break;
-    case 4: k_copy<4, STREAM><<<g, b, 0, s>>>(t); break;
-    case 8: k_copy<8, STREAM><<<g, b, 0, s>>>(t); break;
+    case 1: k_copy<1, STREAM, HAT><<<g, b, 0, s>>>(t); break;
+    case 2: k_copy<2, STREAM, HAT><<<g, b, 0, s>>>(t); break;
+    case 4: k_copy<4, STREAM, HAT><<<g, b, 0, s>>>(t); break;
+    case 8: k_copy<8, STREAM, HAT><<<g, b, 0, s>>>(t); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 hipError_t launch_copy(const Tables& t, const StepArgs& a, uint32_t chunk_elems, uint32_t grid, hipStream_t s) {
-  return a.cached ? launch_copy_v<false>(t, chunk_elems, grid, s) : launch_copy_v<true>(t, chunk_elems, grid, s);
+  if (a.share) return launch_copy_v<true, true>(t, chunk_elems, grid, s);
+  return a.cached ? launch_copy_v<false, false>(t, chunk_elems, grid, s) : launch_copy_v<true, false>(t, chunk_elems, grid, s);
 }
 
 hipError_t launch_deliver(const Tables& t, uint32_t chunk_elems, uint32_t grid, hipStream_t s) {

@@ -6,7 +6,8 @@
 // One workgroup (256 threads, one float4 per thread) owns one 1024-element sweep of
 // one chunk of one worker: the launch shape that streams best on MI355X; with Top-K
 // messages to apply it owns two consecutive sweeps, which halves the per-workgroup
-// cost of that work.  HBM-bound: 5 reads + 2 writes of 4 bytes per element.
+// cost of that work.  HBM-bound: 3 reads + 2 writes of 4 bytes per element where the
+// neighbours' last sent values are read through the L2 (SHARE below), 5 + 2 elsewhere.
 //
 // Top-K messages are applied here, where the dense arrays pass through registers
 // anyway: the sender's own message patches xhat (only the sent entries count as
@@ -138,6 +139,17 @@ __device__ __forceinline__ void block_sums(const double v[SPW], double* ws, doub
   __syncthreads();
 }
 
+// Which tile a workgroup of a SHARE pass owns.  Workgroups go to the eight XCDs in turn by their
+// linear number; each XCD gets a contiguous eighth of the tiles, walks it in segments of `w` tiles,
+// and goes through all workers (blockIdx.y) of a segment before the next segment.  A worker's piece
+// of xhat is then read by the worker before, itself and the worker after within 2 w tiles' worth of
+// work on one L2.  w: see launch_update.
+__device__ __forceinline__ bool shared_tile(const StepArgs& A, uint32_t tiles, uint32_t* tile) {
+  const uint32_t w = gridDim.x / kXcds, i = blockIdx.z * w + blockIdx.x / kXcds;   // i: inside the XCD's eighth
+  *tile = (blockIdx.x % kXcds) * A.xcd_tiles + i;
+  return i < A.xcd_tiles && *tile < tiles;
+}
+
 // DIST: 0 normal (one Philox block per float4), 1 Student-t(3) (two blocks per float4).
 // GRADBUF: gradients come from a caller buffer.
 // NORM: what the pass accumulates for the next trigger test: 0 nothing, 1 the sweep's squared
@@ -155,6 +167,15 @@ __device__ __forceinline__ void block_sums(const double v[SPW], double* ws, doub
 // mailbox here; and the new x is also written to the other of the two copies for the next
 // iteration (two copies in turn: the one read now is written by nobody in this launch).  Fewer
 // launches per iteration for rings that live in the cache, where launches are what costs.
+// SHARE: what a worker last received from a neighbour IS that neighbour's xhat (same-iteration
+// delivery, only sent entries count as communicated): it is read from there, not from the mailbox
+// arena.  Three workers then read each piece of xhat, and the order of the workgroups (tile_of)
+// has two of the three reads hit the L2: 20 instead of 28 bytes of memory traffic per element and
+// step (12 instead of 20 read).  Measured, pass + copy kernel of whole sends: 16 ResNet-18 workers 855 + 233
+// -> 790 + 153 us; pass alone, 64 workers with Top-K 10 %: 4.85 -> 3.99 ms.  The owner may patch its xhat with its own message while its
+// neighbours read it: they apply the same message to what they read, so an entry of the message
+// ends as the sent value either way and every other entry is not changed by anyone.  A tensor
+// that was sent whole has had its xhat written by k_copy; the receiver stores it into its mailbox.
 // TESTS (with PULL): no kernel has run the trigger tests of this iteration.  Every workgroup
 // runs the three it depends on itself (its own tensor's and that tensor's of the two
 // neighbours: three wavefronts, one each, from the sweep sums the previous pass left), and the
@@ -162,7 +183,7 @@ __device__ __forceinline__ void block_sums(const double v[SPW], double* ws, doub
 // written by this launch (Tables: the _out arrays), so every workgroup decides alike.  One
 // launch per iteration.
 template <int DIST, bool GRADBUF, int NORM, bool TOPK, bool HISTA, int SPW, bool STREAM, bool PULL = false,
-          bool TESTS = false>
+          bool TESTS = false, bool SHARE = false>
 __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
   static_assert(!TESTS || (PULL && !TOPK && SPW == 1), "the tests ride in the pass of rings whose receivers fetch the sends");
   __shared__ double ws[4 * SPW];
@@ -177,8 +198,11 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
   uint32_t* hA = reinterpret_cast<uint32_t*>(pv);
   static_assert(!HISTA || TOPK, "the histogram shares the patch windows' storage");
   static_assert(NWIN >= 1 && NWIN <= 3, "EVG_PATCH_WINDOWS is 1, 2 or 3");
+  static_assert(!SHARE || !PULL, "two ways to get at the neighbours' values");
   const uint32_t groups = T.SW / SPW;      // workgroups per chunk (SW is a multiple of SPW)
-  const uint32_t c = blockIdx.x / groups, sub0 = (blockIdx.x % groups) * SPW, r = blockIdx.y;
+  uint32_t tile = blockIdx.x;
+  if (SHARE && !shared_tile(A, T.C * groups, &tile)) return;    // uniform
+  const uint32_t c = tile / groups, sub0 = (tile % groups) * SPW, r = blockIdx.y;
   const ChunkDesc cd = T.chunks[c];
   const uint32_t seg = r * T.L + cd.layer;
   bool vl = T.valid_l[seg] != 0, vr = T.valid_r[seg] != 0;
@@ -212,9 +236,9 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) close_step(T, A);
   } else {
     my_event = T.fired[seg];
-    // PULL: did my neighbours send this tensor whole in this iteration? (then vl / vr are set)
-    from_l = PULL && T.fired[lw * T.L + cd.layer] == 1;
-    from_r = PULL && T.fired[rw * T.L + cd.layer] == 1;
+    // did my neighbours send this tensor whole in this iteration? (then vl / vr are set)
+    from_l = (PULL || SHARE) && T.fired[lw * T.L + cd.layer] == 1;
+    from_r = (PULL || SHARE) && T.fired[rw * T.L + cd.layer] == 1;
   }
   // step n reads copy (n-1) & 1 of x and writes copy n & 1; where a kernel ahead of this one ran
   // the tests it has counted this step already
@@ -250,12 +274,25 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
         if (!A.plain_sgd) v4 = ld4t<STREAM>(T.vel + base + e[u]);   // uniform
         xa[u][0] = x4.x; xa[u][1] = x4.y; xa[u][2] = x4.z; xa[u][3] = x4.w;
         va[u][0] = v4.x; va[u][1] = v4.y; va[u][2] = v4.z; va[u][3] = v4.w;
-        if (from_l) {        // the put of my left neighbour, carried out by its receiver
+        if (SHARE) {
+          // ordinary loads: the line is wanted twice more by this XCD
+          if (vl) {
+            const float4 t = ld4t<false>(T.xhat + (size_t)lw * T.Npad + cd.off + e[u]);
+            la[u][0] = t.x; la[u][1] = t.y; la[u][2] = t.z; la[u][3] = t.w;
+            if (from_l) st4t<STREAM>(T.mbox_l + base + e[u], t);
+          }
+        } else if (from_l) {        // the put of my left neighbour, carried out by its receiver
           const float4 t = ld4t<STREAM>(snap_in + (size_t)lw * T.Npad + cd.off + e[u]);
           la[u][0] = t.x; la[u][1] = t.y; la[u][2] = t.z; la[u][3] = t.w;
           st4t<STREAM>(T.mbox_l + base + e[u], t);
         } else if (vl) { const float4 t = ld4t<STREAM>(T.mbox_l + base + e[u]); la[u][0] = t.x; la[u][1] = t.y; la[u][2] = t.z; la[u][3] = t.w; }
-        if (from_r) {
+        if (SHARE) {
+          if (vr) {
+            const float4 t = ld4t<false>(T.xhat + (size_t)rw * T.Npad + cd.off + e[u]);
+            ra[u][0] = t.x; ra[u][1] = t.y; ra[u][2] = t.z; ra[u][3] = t.w;
+            if (from_r) st4t<STREAM>(T.mbox_r + base + e[u], t);
+          }
+        } else if (from_r) {
           const float4 t = ld4t<STREAM>(snap_in + (size_t)rw * T.Npad + cd.off + e[u]);
           ra[u][0] = t.x; ra[u][1] = t.y; ra[u][2] = t.z; ra[u][3] = t.w;
           st4t<STREAM>(T.mbox_r + base + e[u], t);
@@ -263,9 +300,9 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
         if (sent_whole) {
           // the whole tensor was sent in this iteration: xhat becomes the x just read
           ha[u][0] = xa[u][0]; ha[u][1] = xa[u][1]; ha[u][2] = xa[u][2]; ha[u][3] = xa[u][3];
-          st4t<STREAM>(T.xhat + base + e[u], x4);
+          if (!SHARE) st4t<STREAM>(T.xhat + base + e[u], x4);
         } else if (NORM == 1 || NORM == 3 || TOPK) {
-          const float4 t = ld4t<STREAM>(T.xhat + base + e[u]); ha[u][0] = t.x; ha[u][1] = t.y; ha[u][2] = t.z; ha[u][3] = t.w;
+          const float4 t = ld4t<STREAM && !SHARE>(T.xhat + base + e[u]); ha[u][0] = t.x; ha[u][1] = t.y; ha[u][2] = t.z; ha[u][3] = t.w;
         }
         if (GRADBUF) { const float4 t = ld4t<STREAM>(A.grad + base + e[u]); g[u][0] = t.x; g[u][1] = t.y; g[u][2] = t.z; g[u][3] = t.w; }
       }
@@ -456,6 +493,22 @@ static void launch_update_w(const Tables& t, const StepArgs& a, uint32_t dist, u
     if (grad_mode == 1) k_update<0, true, NORM, NT, NH, 1, false, true><<<grid, block, 0, s>>>(t, a);
     else if (dist == 0) k_update<0, false, NORM, NT, NH, 1, false, true><<<grid, block, 0, s>>>(t, a);
     else k_update<1, false, NORM, NT, NH, 1, false, true><<<grid, block, 0, s>>>(t, a);
+    return;
+  }
+  if (a.share) {             // the host sets share only for streaming rings
+    // Segments of about kSegTiles tiles, all of one length.  Shorter ones keep less traffic between two
+    // reads of a piece of xhat, longer ones keep the memory streaming in longer runs.  The pass at
+    // 16 / 32 / 64 / 128 / 256 tiles: 858 / 828 / 801 / 790 / 786 us (16 ResNet-18 workers, whole sends),
+    // 1286 / 1270 / 1260 / 1249 / 1259 us (32, no momentum), 4.09 / 4.05 / 4.02 / 3.99 / 3.98 ms (64, Top-K 10 %).
+    StepArgs b = a;
+    const uint32_t tiles = t.C * (t.SW / SPW);
+    b.xcd_tiles = (tiles + kXcds - 1) / kXcds;
+    const uint32_t want = kSegTiles / SPW;
+    const uint32_t nseg = (b.xcd_tiles + want / 2) / want ? (b.xcd_tiles + want / 2) / want : 1u;
+    const dim3 sgrid(kXcds * ((b.xcd_tiles + nseg - 1) / nseg), t.P, nseg);
+    if (grad_mode == 1) k_update<0, true, NORM, TOPK, HISTA, SPW, true, false, false, true><<<sgrid, block, 0, s>>>(t, b);
+    else if (dist == 0) k_update<0, false, NORM, TOPK, HISTA, SPW, true, false, false, true><<<sgrid, block, 0, s>>>(t, b);
+    else k_update<1, false, NORM, TOPK, HISTA, SPW, true, false, false, true><<<sgrid, block, 0, s>>>(t, b);
     return;
   }
   if (a.cached) {

@@ -15,8 +15,9 @@ Writes, for the configuration's workload name W:
                                         VALU instruction count, with the run they were measured on
 
 FETCH_SIZE and WRITE_SIZE are in KiB per dispatch and are calibrated on the library's own plain
-copy kernel: at iteration 0 `k_copy` copies every chunk of x into both mailboxes, so it reads
-P * sum(pad4(n_l)) * 4 bytes and writes twice that; true bytes = counter * 1024 * factor.
+copy kernel: at iteration 0 `k_copy` copies every chunk of x, into xhat (rings whose update pass
+reads the neighbours' xhat) or into both mailboxes, so it reads P * sum(pad4(n_l)) * 4 bytes and
+writes once or twice that; true bytes = counter * 1024 * factor.
 """
 from __future__ import annotations
 
@@ -123,8 +124,9 @@ def main():
         fetch, write = counter_rows(a.fetch, "FETCH_SIZE"), counter_rows(a.write, "WRITE_SIZE")
         npad4 = sum((int(n) + 3) // 4 * 4 for n in w.layer_numel)
         copy_read = w.P * npad4 * 4
-        copy_write = 2 * copy_read
         kc = [k for k in fetch if "k_copy" in k][0]
+        to_xhat = short(kc).rstrip(">").endswith("true")          # k_copy<SWEEPS, STREAM, HAT>
+        copy_write = copy_read if to_xhat else 2 * copy_read
         f_fetch = copy_read / (max(fetch[kc]) * KIB)
         f_write = copy_write / (max(write[kc]) * KIB)
         record["calibration"] = {"kernel": short(kc), "read_bytes": copy_read, "write_bytes": copy_write,
@@ -134,7 +136,7 @@ def main():
                f"    rocprofv3 --pmc FETCH_SIZE --kernel-trace --output-format csv -d <out> -o cfg{c} -- {bench_cmd}",
                f"    rocprofv3 --pmc WRITE_SIZE --kernel-trace --output-format csv -d <out> -o cfg{c} -- {bench_cmd}", "",
                f"Counters are in KiB per dispatch. Calibration on the library's plain copy kernel `k_copy` at iteration 0, where it",
-               f"copies every chunk of x into both mailboxes (reads {copy_read} B, writes {copy_write} B): FETCH_SIZE factor "
+               f"copies every chunk of x into {'xhat' if to_xhat else 'both mailboxes'} (reads {copy_read} B, writes {copy_write} B): FETCH_SIZE factor "
                f"{f_fetch:.4f}, WRITE_SIZE factor {f_write:.4f}", "(true bytes = counter x 1024 x factor).", "",
                f"Averages over the timed and the instrumented run of the {a.steps} iterations (warm-up launches dropped), GB per launch:", "",
                "| kernel | launches | fetch GB | write GB | total GB |", "|---|---|---|---|---|"]
