@@ -166,7 +166,7 @@ typedef struct {
                                slot and were selected straight from x and xhat instead (slower,
                                same result): massive ties or winners crowded into a few granules */
   uint64_t library_bytes;   /* device memory the library holds for this context besides the
-                               caller's five arenas (tables, work lists, Top-K histograms,
+                               caller's five arenas (tables, Top-K histograms,
                                staging and message buffers); for evg_init_static the part
                                of the static block in use                           */
   /* optional per-(worker, tensor) outputs, HOST arrays of P*L entries or NULL  */
@@ -182,12 +182,13 @@ typedef struct {
 /* Phases reported by evg_timing_read. */
 enum {
   EVG_PH_NORM = 0,       /* separate drift-norm pass (EVG_NORM_SEPARATE only)        */
-  EVG_PH_TRIGGER = 1,    /* norm finalisation, trigger test, thresholds, work lists
+  EVG_PH_TRIGGER = 1,    /* norm finalisation, trigger test, thresholds
                             (no samples where the update pass runs the tests itself:
                             cache-resident rings that send whole tensors, norms fused,
                             no tensor above 131 072 elements, evg_step only)          */
-  EVG_PH_SEND_FULL = 2,  /* whole-tensor copies into both mailboxes (no samples where
-                            the receivers fetch the sends inside the update pass)     */
+  EVG_PH_SEND_FULL = 2,  /* whole-tensor copies (no samples where the receivers fetch the
+                            sends inside the update pass, nor in Top-K rings, whose few
+                            whole sends are part of the selection's first kernel)     */
   EVG_PH_TOPK_SELECT = 3,/* threshold-key search for the Top-K set                   */
   EVG_PH_TOPK_SEND = 4,  /* pack (index, value) messages, put them                   */
   EVG_PH_UPDATE = 5,     /* fused averaging + momentum SGD (+ next drift norms)      */
@@ -205,7 +206,7 @@ evg_status evg_layer_offsets(uint32_t L, const uint64_t* layer_numel, uint64_t* 
 /* Validates cfg, builds the device tables, initialises xhat, vel and the
  * thresholds (Section 4: nothing has been sent yet, so xhat = x).  hip_stream
  * is a hipStream_t (NULL = the default stream); all work of this context is
- * enqueued on it.  Allocates library-owned device memory (tables, work lists,
+ * enqueued on it.  Allocates library-owned device memory (tables,
  * Top-K histograms and message staging). */
 evg_status evg_init(evg_ctx** out, const evg_config* cfg, void* hip_stream);
 
@@ -213,7 +214,7 @@ evg_status evg_init(evg_ctx** out, const evg_config* cfg, void* hip_stream);
  * hipMalloc, tight serving loops that create and drop rings, code that is later captured
  * into a HIP graph): identical to evg_init in arguments, results and in every later call on
  * the context, except that all library-owned device tables (norm partial sums, decisions,
- * counters, work lists, Top-K histograms, staging and message buffers) are carved out of one
+ * counters, Top-K histograms, staging and message buffers) are carved out of one
  * block of EVG_STATIC_SCRATCH_BYTES that is part of the library image on every GPU, instead
  * of coming from hipMalloc.  Calls no hipMalloc / hipFree and no allocating library routine;
  * evg_destroy on such a context frees no device memory either.  A configuration whose

@@ -66,7 +66,6 @@ struct evg_ctx {
   hipStream_t stream = nullptr;
   Tables t{};
   uint32_t chunk_elems = 8192;
-  uint32_t work_grid = 1;
   std::vector<uint64_t> numel;      // per tensor
   std::vector<uint32_t> K;          // per tensor Top-K message length
   std::vector<uint32_t> msg_off;
@@ -288,16 +287,15 @@ static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uin
   add(S, 4); add(S, 4); add(S, 4); add(S, 4);            // delta, last_norm, delta_before, last_event
   add(S, 1); add(S, 1); add(S, 1); add(S, 1);            // valid_l, valid_r, fired, near_tie
   add(S, 4); add(S, 4); add(S, 4); add(S, 4);            // ev_full, ev_topk, near_cnt, nonfinite_cnt
-  add(S * hist_len, 4); add(S, 4); add(S, 4); add(S, 4); // slope_hist, slope_cnt, seg_woff_full/topk
-  add(4, 4); add(1, sizeof(IterState)); add(kDecayTable, 8);
-  add(PC, 4);                                            // work_full
+  add(S * hist_len, 4); add(S, 4);                       // slope_hist, slope_cnt
+  add(1, 4); add(1, sizeof(IterState)); add(kDecayTable, 8);
   if (pull) add(2 * P * Npad, 4);                        // xsnap
   if (one_launch) {                                      // the second set of what the trigger tests read
     add(PC * SW, 8); add(S, 4); add(S, 4);
     if (norm_diff) add(S, 8);
   }
   if (topk) {
-    add(PC, 4); add(S * kHistBins, 4); add(S, 4); add(S, 4); add(PC, 8);
+    add(S * kHistBins, 4); add(S, 4); add(S, 4); add(PC, 8);
     const uint64_t stage = P * (Npad / 16 * stage_num);
     add(stage, 4); add(stage, 4); add(stage, 4);
     add(PC, 8); add(PC, 8); add(PC * (SW + 1), 4);
@@ -440,7 +438,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   for (const LayerDesc& d : layers) most_sweeps = std::max(most_sweeps, d.nchunks * t.SW);
   const bool one_launch = c->cached && !cfg->topk_ppm && !cfg->delivery_delay &&
                           cfg->norm_mode == EVG_NORM_FUSED && most_sweeps <= 128;
-  int dev = 0, cus = 256;
+  int dev = 0;
   ChunkDesc* d_chunks = nullptr;
   LayerDesc* d_layers = nullptr;
 #define TRY_OR_FREE(expr)              \
@@ -460,7 +458,6 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     }                                                                                \
   } while (0)
   HIP_OR_FREE(hipGetDevice(&dev));
-  HIP_OR_FREE(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   if (use_scratch) {
     const uint64_t need = table_bytes(P, L, C, t.SW, t.hist_len, Npad, ktot, t.stage_num, cfg->topk_ppm != 0,
                                       cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF,
@@ -494,8 +491,6 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     c->arena_base = g_scratch_base[dev];
     c->arena_dev = dev;
   }
-  const uint64_t full_grid = (uint64_t)P * C;
-  c->work_grid = (uint32_t)(full_grid < (uint64_t)cus * 8 ? full_grid : (uint64_t)cus * 8);
   TRY_OR_FREE(c->dalloc(&d_chunks, C, false));
   TRY_OR_FREE(c->dalloc(&d_layers, L, false));
   HIP_OR_FREE(hipMemcpyAsync(d_chunks, chunks.data(), C * sizeof(ChunkDesc), hipMemcpyHostToDevice, c->stream));
@@ -521,9 +516,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   TRY_OR_FREE(c->dalloc(&t.nonfinite_cnt, S, true));
   TRY_OR_FREE(c->dalloc(&t.slope_hist, S * t.hist_len, true));
   TRY_OR_FREE(c->dalloc(&t.slope_cnt, S, true));
-  TRY_OR_FREE(c->dalloc(&t.seg_woff_full, S, true));
-  TRY_OR_FREE(c->dalloc(&t.seg_woff_topk, S, true));
-  TRY_OR_FREE(c->dalloc(&t.counts, 4, true));
+  TRY_OR_FREE(c->dalloc(&t.not_staged, 1, true));
   TRY_OR_FREE(c->dalloc(&t.it, 1, true));
   {
     // decay^k as evg_step computes it, for the steps that take k from the device
@@ -535,7 +528,6 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     t.decay_tab = d_tab;
     t.decay_len = kDecayTable;
   }
-  TRY_OR_FREE(c->dalloc(&t.work_full, P * C, true));
   // cache-resident ring, whole tensors, same-iteration delivery: the update pass fetches the sends
   // itself from a copy of x it keeps (one more array of the ring's size, library-owned)
   const bool pull = c->cached && !cfg->topk_ppm && !cfg->delivery_delay;
@@ -551,7 +543,6 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   t.partials_out = t.partials; t.partials_hat_out = t.partials_hat; t.xhat_sq_out = t.xhat_sq;
   t.delta_out = t.delta; t.last_event_out = t.last_event;
   if (cfg->topk_ppm) {
-    TRY_OR_FREE(c->dalloc(&t.work_topk, P * C, true));
     TRY_OR_FREE(c->dalloc(&t.hist, S * kHistBins, true));
     TRY_OR_FREE(c->dalloc(&t.sel_prefix, S, true));
     TRY_OR_FREE(c->dalloc(&t.sel_krem, S, true));
@@ -566,8 +557,6 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     TRY_OR_FREE(c->dalloc(&t.msg_val, (uint64_t)P * ktot, true));
     TRY_OR_FREE(c->dalloc(&t.idx_hash, S, true));
     TRY_OR_FREE(c->dalloc(&t.msg_hash, S, true));
-  } else {
-    t.work_topk = t.work_full;   // never listed: k_expand only writes it for Top-K events
   }
   // nothing sent yet: xhat = x, khat = -1, delta = its starting value, v = 0
   const float d0 = cfg->thr_mode == EVG_THR_FIXED ? cfg->thr_fixed : cfg->delta_init;
@@ -638,26 +627,25 @@ static evg_status enqueue_step(evg_ctx* c, const StepArgs& args, bool timed) {
   }
   if (!single) {
     Phase ph(c, EVG_PH_TRIGGER);
-    HIP_TRY(launch_trigger(t, a, c->stream));
-    HIP_TRY(launch_scan(t, a, c->stream));
-    HIP_TRY(launch_expand(t, a, c->stream));
+    HIP_TRY(a.hist_fused ? launch_topk_decide(t, a, c->stream) : launch_trigger(t, a, c->stream));
     if ((st = ph.end()) != EVG_OK) return st;
   }
-  if (!a.delay && !a.pull) {      // with delayed delivery the mailboxes are written after the update;
-                                  // a cache-resident ring's receivers fetch the sends in the update pass
+  if (!a.delay && !a.pull && !a.topk_on) {   // with delayed delivery the mailboxes are written after the update;
+                                  // a cache-resident ring's receivers fetch the sends in the update pass;
+                                  // a Top-K ring's few whole sends ride in the selection's first kernel
     Phase ph(c, EVG_PH_SEND_FULL);
-    HIP_TRY(launch_copy(t, a, c->chunk_elems, c->work_grid, c->stream));
+    HIP_TRY(launch_copy(t, a, c->chunk_elems, c->stream));
     if ((st = ph.end()) != EVG_OK) return st;
   }
   if (a.topk_on) {
     {
       Phase ph(c, EVG_PH_TOPK_SELECT);
-      HIP_TRY(launch_topk_select(t, a, c->chunk_elems, c->work_grid, c->stream));
+      HIP_TRY(launch_topk_select(t, a, c->chunk_elems, c->stream));
       if ((st = ph.end()) != EVG_OK) return st;
     }
     {
       Phase ph(c, EVG_PH_TOPK_SEND);
-      HIP_TRY(launch_topk_send(t, a, c->chunk_elems, c->work_grid, c->stream));
+      HIP_TRY(launch_topk_send(t, a, c->stream));
       if ((st = ph.end()) != EVG_OK) return st;
     }
   }
@@ -677,7 +665,7 @@ static evg_status enqueue_step(evg_ctx* c, const StepArgs& args, bool timed) {
   }
   if (a.delay) {
     Phase ph(c, EVG_PH_DELIVER);
-    HIP_TRY(launch_deliver(t, c->chunk_elems, c->work_grid, c->stream));
+    HIP_TRY(launch_deliver(t, c->chunk_elems, c->stream));
     if ((st = ph.end()) != EVG_OK) return st;
   }
   c->messages_live = true;
@@ -794,7 +782,7 @@ evg_status evg_stats(evg_ctx* c, evg_stats_t* out) {
   out->near_tie_flags = near;
   out->nonfinite_norms = nonf;
   uint32_t not_staged = 0;
-  HIP_TRY(hipMemcpy(&not_staged, t.counts + 3, 4, hipMemcpyDeviceToHost));
+  HIP_TRY(hipMemcpy(&not_staged, t.not_staged, 4, hipMemcpyDeviceToHost));
   out->chunks_not_staged = not_staged;
   out->library_bytes = c->owned_bytes;
   return EVG_OK;
@@ -879,7 +867,7 @@ std::vector<Piece> state_pieces(evg_ctx* c) {
       {t.valid_l, S}, {t.valid_r, S}, {t.fired, S}, {t.near_tie, S},
       {t.ev_full, S * 4}, {t.ev_topk, S * 4}, {t.near_cnt, S * 4}, {t.nonfinite_cnt, S * 4},
       {t.slope_hist, S * t.hist_len * 4}, {t.slope_cnt, S * 4}, {t.partials, sweeps * 8},
-      {t.it, sizeof(IterState)}, {t.counts, 4 * sizeof(uint32_t)}};   // counts[3] is a running counter
+      {t.it, sizeof(IterState)}, {t.not_staged, sizeof(uint32_t)}};
   if (t.partials_hat) { v.push_back({t.partials_hat, sweeps * 8}); v.push_back({t.xhat_sq, S * 8}); }
   if (t.hist) v.push_back({t.hist, S * kHistBins * 4});
   return v;
@@ -888,7 +876,7 @@ std::vector<Piece> state_pieces(evg_ctx* c) {
 StateHeader state_header(evg_ctx* c) {
   StateHeader h{};
   std::memcpy(h.magic, "EVGSTATE", 8);
-  h.version = 3;
+  h.version = 4;
   h.P = c->t.P; h.L = c->t.L; h.C = c->t.C; h.SW = c->t.SW; h.S = c->t.S;
   h.hist_len = c->t.hist_len;
   h.topk_ppm = c->cfg.topk_ppm;

@@ -119,6 +119,27 @@ __device__ __forceinline__ void st4t(float* p, float4 a) {
   else *reinterpret_cast<float4*>(p) = a;
 }
 
+// The whole-tensor send of one chunk, by one workgroup.
+// HAT = false: the two mailboxes (xhat takes the sent values in the update pass, which has them
+// in registers).  HAT = true: xhat alone -- the receivers read it there in the update pass and
+// store it into their mailboxes.
+template <int SWEEPS, bool STREAM, bool HAT>
+__device__ __forceinline__ void copy_chunk(const Tables& T, uint32_t r, const ChunkDesc& cd) {
+  const uint32_t left = (r + T.P - 1) % T.P, right = (r + 1) % T.P;
+  const float* src = T.x + (size_t)r * T.Npad + cd.off;
+  float* d1 = HAT ? T.xhat + (size_t)r * T.Npad + cd.off : T.mbox_r + (size_t)left * T.Npad + cd.off;
+  float* d2 = T.mbox_l + (size_t)right * T.Npad + cd.off;
+#pragma unroll
+  for (int it = 0; it < SWEEPS; ++it) {
+    const uint32_t e = it * kSweep + threadIdx.x * kLaneElems;
+    if (e < cd.len) {
+      const float4 v = ld4t<STREAM>(src + e);
+      st4t<STREAM>(d1 + e, v);
+      if (!HAT) st4t<STREAM>(d2 + e, v);
+    }
+  }
+}
+
 // ----------------------------------------------------------------------------
 // Synthetic gradients.  Philox4x32-10 (Salmon et al., SC'11): ten rounds, each
 // two 32x32->64 multiplies by fixed odd constants followed by xors with the

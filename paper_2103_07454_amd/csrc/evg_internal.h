@@ -68,10 +68,7 @@ struct Tables {
   uint8_t* valid_l; uint8_t* valid_r; uint8_t* fired; uint8_t* near_tie;
   uint32_t* ev_full; uint32_t* ev_topk; uint32_t* near_cnt; uint32_t* nonfinite_cnt;
   float* slope_hist; uint32_t* slope_cnt;   // [S*hist_len], [S]
-  uint32_t* seg_woff_full; uint32_t* seg_woff_topk;   // [S] exclusive scans
-  uint32_t* counts;        // [0] chunks to copy whole, [1] chunks of Top-K tensors, [2] Top-K tensors,
-                           // [3] chunks so far whose possible winners did not fit their staging slot
-  uint32_t* work_full; uint32_t* work_topk;   // [P*C] compact chunk lists (r*C + c)
+  uint32_t* not_staged;    // [1] chunks so far whose possible winners did not fit their staging slot
   uint32_t* hist;          // [S*kHistBins]
   uint32_t* sel_prefix; uint32_t* sel_krem;   // [S]
   uint2* stage_n;          // [P*C] per chunk: staged entries (bin >= the threshold bin), and how many
@@ -135,14 +132,11 @@ hipError_t launch_update(const Tables& t, const StepArgs& a, uint32_t dist, uint
                          int norm, hipStream_t s);
 hipError_t launch_trigger(const Tables& t, const StepArgs& a, hipStream_t s);
 hipError_t launch_begin(const Tables& t, hipStream_t s);
-hipError_t launch_scan(const Tables& t, const StepArgs& a, hipStream_t s);
-hipError_t launch_expand(const Tables& t, const StepArgs& a, hipStream_t s);
-hipError_t launch_copy(const Tables& t, const StepArgs& a, uint32_t chunk_elems, uint32_t grid, hipStream_t s);
-hipError_t launch_deliver(const Tables& t, uint32_t chunk_elems, uint32_t grid, hipStream_t s);
-hipError_t launch_topk_select(const Tables& t, const StepArgs& a, uint32_t chunk_elems, uint32_t grid,
-                              hipStream_t s);
-hipError_t launch_topk_send(const Tables& t, const StepArgs& a, uint32_t chunk_elems, uint32_t grid,
-                            hipStream_t s);
+hipError_t launch_copy(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
+hipError_t launch_deliver(const Tables& t, uint32_t chunk_elems, hipStream_t s);
+hipError_t launch_topk_decide(const Tables& t, const StepArgs& a, hipStream_t s);
+hipError_t launch_topk_select(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
+hipError_t launch_topk_send(const Tables& t, const StepArgs& a, hipStream_t s);
 hipError_t launch_average(const Tables& t, float* out, hipStream_t s);
 hipError_t launch_message_hashes(const Tables& t, hipStream_t s);
 

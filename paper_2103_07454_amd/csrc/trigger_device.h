@@ -1,5 +1,5 @@
 // The trigger test of one (worker, tensor) as device functions, shared by the kernels that
-// run it: k_trigger / k_front (one wavefront per tensor, ahead of the update pass) and the
+// run it: k_trigger / k_topk_decide (one wavefront per tensor, ahead of the update pass) and the
 // update pass of rings that take a single launch per iteration (every workgroup repeats the
 // tests it depends on; the tensor's first workgroup records the outcome).
 //
@@ -16,20 +16,32 @@ namespace evg {
 // Sums of the tensor's sweep partials in a fixed order, by one whole wavefront; valid in every lane.
 // *hat_sums: the squared norm of xhat comes from the arena sums (norm-difference trigger with
 // Top-K, or before the tensor's first event) rather than from the scalar kept at its last event.
+// Eight loads are in flight at a time (the sums stay in order): a tensor of 2.4 M elements has 36 partials
+// per lane, and waiting for each of them made the kernel 13 us; batched, 5.
+__device__ __forceinline__ double ordered_lane_sum(const double* part, uint32_t np) {
+  double acc = 0.0;
+  for (uint32_t i = lane_id(); i < np; i += 64 * 8) {
+    double v[8];
+#pragma unroll
+    for (uint32_t u = 0; u < 8; ++u) v[u] = i + 64 * u < np ? part[i + 64 * u] : 0.0;
+#pragma unroll
+    for (uint32_t u = 0; u < 8; ++u) acc += v[u];
+  }
+  return acc;
+}
+
 __device__ __forceinline__ void segment_sums(const Tables& T, const StepArgs& A, uint32_t seg, double* acc_out,
                                              double* acc_hat_out, bool* hat_sums_out) {
   const uint32_t r = seg / T.L, l = seg % T.L;
   const LayerDesc ld = T.layers[l];
   const double* part = T.partials + ((size_t)r * T.C + ld.chunk0) * T.SW;
   const uint32_t np = ld.nchunks * T.SW;
-  double acc = 0.0, acc_hat = 0.0;
-  for (uint32_t i = lane_id(); i < np; i += 64) acc += part[i];
-  acc = wave_sum(acc);
+  double acc_hat = 0.0;
+  const double acc = wave_sum(ordered_lane_sum(part, np));
   const bool hat_sums = A.norm_src == 2 || (A.norm_src == 1 && T.last_event[seg] < 0);
   if (hat_sums) {
     const double* ph = T.partials_hat + ((size_t)r * T.C + ld.chunk0) * T.SW;
-    for (uint32_t i = lane_id(); i < np; i += 64) acc_hat += ph[i];
-    acc_hat = wave_sum(acc_hat);
+    acc_hat = wave_sum(ordered_lane_sum(ph, np));
   }
   *acc_out = acc;
   *acc_hat_out = acc_hat;
