@@ -2,6 +2,7 @@
 // launch sequence and the counters.  See include/evg.h for the contract.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -387,8 +388,6 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     LayerDesc& d = layers[l];
     d.off = (uint32_t)off;
     d.numel = (uint32_t)n;
-    d.chunk0 = (uint32_t)chunks.size();
-    d.nchunks = (uint32_t)((n + ce - 1) / ce);
     uint64_t k = 0;
     if (cfg->topk_ppm) {
       k = (n * (uint64_t)cfg->topk_ppm + 999999ull) / 1000000ull;
@@ -401,22 +400,51 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     d.sig_base = cfg->synth.sigma0;
     if (cfg->grad_mode == EVG_GRAD_SYNTH && cfg->synth.fan_in_scaling)
       d.sig_base = cfg->synth.sigma0 / std::sqrt((double)cfg->layer_fan_in[l]);
-    for (uint32_t i = 0; i < d.nchunks; ++i) {
-      ChunkDesc cd;
-      cd.j0 = i * ce;
-      cd.off = d.off + cd.j0;
-      cd.len = (uint32_t)(n - cd.j0 < ce ? n - cd.j0 : ce);
-      cd.layer = l;
-      chunks.push_back(cd);
-    }
     c->numel.push_back(n);
     c->K.push_back(d.K);
     c->msg_off.push_back(d.msg_off);
     c->N += n;
     off += pad_to(n, 4);
   }
+  // Streaming rings: sweeps begin on cache lines.  A network whose widths are no multiples of 32 has its
+  // tensors anywhere on multiples of 16 bytes; wavefronts then share the lines where they meet and write
+  // parts of them.  Step times without -> with, whole sends: ResNet-18 of width 62, 16 workers 1031 -> 945 us;
+  // width 28, 60 workers 843 -> 771 us; width 40, 30 workers 871 -> 796 us.  Not where the additional chunks
+  // would take the tables past a limit.
+  const uint32_t hist_len = cfg->thr_mode == EVG_THR_ADAPTIVE ? cfg->hist_len : 1, SW = ce / (uint32_t)kSweep;
+  const bool pull = c->cached && !cfg->topk_ppm && !cfg->delivery_delay;
+  bool one_launch = false;
+  uint64_t need = 0;
+  auto cut_chunks = [&](bool on_lines) {
+    chunks.clear();
+    uint32_t most_sweeps = 0;
+    for (uint32_t l = 0; l < L; ++l) {
+      LayerDesc& d = layers[l];
+      const uint32_t lead = on_lines ? d.off % kLineElems : 0u;
+      d.chunk0 = (uint32_t)chunks.size();
+      d.nchunks = (uint32_t)(((uint64_t)d.numel + lead + ce - 1) / ce);
+      for (uint32_t i = 0; i < d.nchunks; ++i) {
+        ChunkDesc cd;
+        cd.lead = i == 0 ? lead : 0u;
+        cd.j0 = i == 0 ? 0u : i * ce - lead;
+        cd.off = d.off + cd.j0;
+        cd.len = std::min(d.numel - cd.j0, ce - cd.lead);
+        cd.layer = l;
+        chunks.push_back(cd);
+      }
+      most_sweeps = std::max(most_sweeps, d.nchunks * SW);
+    }
+    // one launch per iteration: the ring's receivers fetch the sends (see `pull` below), the update pass
+    // accumulates the norms, and one wavefront sums a tensor's sweep partials with two loads per lane
+    one_launch = pull && cfg->norm_mode == EVG_NORM_FUSED && most_sweeps <= 128;
+    need = table_bytes(P, L, chunks.size(), SW, hist_len, Npad, ktot, stage_num_for(cfg->topk_ppm), cfg->topk_ppm != 0,
+                       cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF, pull, one_launch);
+    return (uint64_t)P * chunks.size() * (SW + 1) <= 0xFFFFFFF0ull && (uint64_t)P * ktot <= 0xFFFFFFF0ull &&
+           !(use_scratch && need > kScratchBytes);
+  };
+  if (c->cached || !cut_chunks(true)) (void)cut_chunks(false);
   const uint64_t C = chunks.size();
-  if ((uint64_t)P * C * (ce / 1024 + 1) > 0xFFFFFFF0ull || (uint64_t)P * ktot > 0xFFFFFFF0ull) {
+  if ((uint64_t)P * C * (SW + 1) > 0xFFFFFFF0ull || (uint64_t)P * ktot > 0xFFFFFFF0ull) {
     delete c;
     return fail(EVG_ERR_INVALID, "configuration too large: work lists and message slots are indexed with 32 bits");
   }
@@ -425,19 +453,13 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   // ---- device tables ------------------------------------------------------
   Tables& t = c->t;
   t.P = P; t.L = L; t.C = (uint32_t)C; t.S = (uint32_t)S;
-  t.SW = ce / (uint32_t)kSweep;
-  t.hist_len = cfg->thr_mode == EVG_THR_ADAPTIVE ? cfg->hist_len : 1;
+  t.SW = SW;
+  t.hist_len = hist_len;
   t.Ktot = (uint32_t)ktot;
   t.Npad = Npad;
   t.stage_num = stage_num_for(cfg->topk_ppm);
   t.stage_stride = Npad / 16 * t.stage_num;
   t.x = cfg->x; t.xhat = cfg->xhat; t.mbox_l = cfg->mbox_l; t.mbox_r = cfg->mbox_r; t.vel = cfg->vel;
-  // one launch per iteration: the ring's receivers fetch the sends (see `pull` below), the update pass
-  // accumulates the norms, and one wavefront sums a tensor's sweep partials with two loads per lane
-  uint32_t most_sweeps = 0;
-  for (const LayerDesc& d : layers) most_sweeps = std::max(most_sweeps, d.nchunks * t.SW);
-  const bool one_launch = c->cached && !cfg->topk_ppm && !cfg->delivery_delay &&
-                          cfg->norm_mode == EVG_NORM_FUSED && most_sweeps <= 128;
   int dev = 0;
   ChunkDesc* d_chunks = nullptr;
   LayerDesc* d_layers = nullptr;
@@ -459,9 +481,6 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   } while (0)
   HIP_OR_FREE(hipGetDevice(&dev));
   if (use_scratch) {
-    const uint64_t need = table_bytes(P, L, C, t.SW, t.hist_len, Npad, ktot, t.stage_num, cfg->topk_ppm != 0,
-                                      cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF,
-                                      c->cached && !cfg->topk_ppm && !cfg->delivery_delay, one_launch);
     if (need > kScratchBytes) {
       evg_destroy(c);
       return fail(EVG_ERR_INVALID, "this configuration needs %llu bytes of tables; the static scratch block "
@@ -530,7 +549,6 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   }
   // cache-resident ring, whole tensors, same-iteration delivery: the update pass fetches the sends
   // itself from a copy of x it keeps (one more array of the ring's size, library-owned)
-  const bool pull = c->cached && !cfg->topk_ppm && !cfg->delivery_delay;
   if (pull) TRY_OR_FREE(c->dalloc(&t.xsnap, 2 * (uint64_t)P * Npad, false));
   if (one_launch) {
     TRY_OR_FREE(c->dalloc(&c->second.partials, P * C * t.SW, true));

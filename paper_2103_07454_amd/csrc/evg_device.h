@@ -131,7 +131,7 @@ __device__ __forceinline__ void copy_chunk(const Tables& T, uint32_t r, const Ch
   float* d2 = T.mbox_l + (size_t)right * T.Npad + cd.off;
 #pragma unroll
   for (int it = 0; it < SWEEPS; ++it) {
-    const uint32_t e = it * kSweep + threadIdx.x * kLaneElems;
+    const uint32_t e = it * kSweep + threadIdx.x * kLaneElems - cd.lead;   // positions before the lead wrap around
     if (e < cd.len) {
       const float4 v = ld4t<STREAM>(src + e);
       st4t<STREAM>(d1 + e, v);

@@ -8,6 +8,7 @@ namespace evg {
 constexpr int kThreads = 256;          // 4 wavefronts of 64 lanes
 constexpr int kLaneElems = 4;          // one float4 per lane and sweep
 constexpr int kSweep = kThreads * kLaneElems;   // elements one workgroup covers per sweep
+constexpr uint32_t kLineElems = 32;    // floats of a 128-byte cache line
 constexpr uint32_t kXcds = 8;          // compute dies, each with an L2 of its own
 constexpr uint32_t kSegTiles = 128;    // 1024-element tiles of one worker that an XCD takes before the next worker's
 constexpr int kHistBins = 2048;        // 11 key bits per selection pass (passes A, B); pass C uses 512
@@ -16,11 +17,14 @@ constexpr uint32_t kStageCapBin = 1024;   // gathers in LDS before writing them 
 
 // A chunk is a run of one tensor's elements that one workgroup handles; it never
 // straddles tensors, starts at a multiple of 4 elements and is at most chunk_elems long.
+// In rings that stream from memory a tensor's first chunk leaves out its first `lead` positions, so that the
+// sweeps of all its chunks begin on cache lines (tensors begin on multiples of 16 bytes only).
 struct ChunkDesc {
   uint32_t off;    // start inside a worker's arena slice (floats, multiple of 4)
   uint32_t len;    // elements (multiple of 4 except a tensor's last chunk)
   uint32_t layer;  // tensor index
   uint32_t j0;     // start inside the tensor (multiple of 4)
+  uint32_t lead;   // multiple of 4: the chunk's elements are positions lead .. lead + len - 1 of its workgroup's sweeps
 };
 
 struct LayerDesc {

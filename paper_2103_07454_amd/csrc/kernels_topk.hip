@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_hist(Tables T, StepArgs A) {
   __syncthreads();
 #pragma unroll
   for (int it = 0; it < SWEEPS; ++it) {
-    const uint32_t e = it * kSweep + threadIdx.x * kLaneElems;
+    const uint32_t e = it * kSweep + threadIdx.x * kLaneElems - wi.cd.lead;   // positions before the lead wrap around
     if (e < wi.cd.len) {
       const float4 x4 = ld4s(T.x + wi.base + e);
       float4 h4 = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_stage(Tables T, StepArgs A) {
     float4 x4[STEP], h4[STEP];
 #pragma unroll
     for (int u = 0; u < STEP; ++u) {
-      e[u] = (it + u) * kSweep + threadIdx.x * kLaneElems;
+      e[u] = (it + u) * kSweep + threadIdx.x * kLaneElems - wi.cd.lead;
       x4[u] = make_float4(0.f, 0.f, 0.f, 0.f);
       h4[u] = x4[u];
       if (e[u] < wi.cd.len) {
@@ -494,7 +494,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_pack(Tables T, StepArgs A) {
       }
       // entries ascend, so a group of 64 touches only the sweeps between its first and its last
       // entry's (all three values below are wave-uniform)
-      const uint32_t sw = (j[u] - wi.cd.j0) / (uint32_t)kSweep;
+      const uint32_t sw = (j[u] - wi.cd.j0 + wi.cd.lead) / (uint32_t)kSweep;
       const uint64_t mi = __ballot(in[u]);
       const uint32_t last = mi ? 63u - (uint32_t)__builtin_clzll(mi) : 0u;
       const uint32_t sw_lo = __shfl(sw, 0, 64), sw_hi = __shfl(sw, last, 64);

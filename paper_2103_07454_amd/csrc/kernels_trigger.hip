@@ -71,7 +71,7 @@ __global__ __launch_bounds__(kThreads) void k_deliver(Tables T) {
   float* d2 = T.mbox_l + (size_t)right * T.Npad + cd.off;
 #pragma unroll
   for (int it = 0; it < SWEEPS; ++it) {
-    const uint32_t e = it * kSweep + threadIdx.x * kLaneElems;
+    const uint32_t e = it * kSweep + threadIdx.x * kLaneElems - cd.lead;
     if (e < cd.len) {
       const float4 v = ld4s(src + e);
       st4s(d1 + e, v);

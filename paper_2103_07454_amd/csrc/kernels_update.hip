@@ -60,7 +60,7 @@ __global__ __launch_bounds__(kThreads) void k_norm(Tables T) {
   const uint32_t c = blockIdx.x / T.SW, sub = blockIdx.x % T.SW, r = blockIdx.y;
   const ChunkDesc cd = T.chunks[c];
   const size_t base = (size_t)r * T.Npad + cd.off;
-  const uint32_t e = sub * kSweep + threadIdx.x * kLaneElems;
+  const uint32_t e = sub * kSweep + threadIdx.x * kLaneElems - cd.lead;   // positions before the lead wrap around
   double acc = 0.0, acc_hat = 0.0;
   if (e < cd.len) {
     const float4 x4 = ld4(T.x + base + e), h4 = ld4(T.xhat + base + e);
@@ -256,13 +256,13 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
   bool live[SPW];
 #pragma unroll
   for (int u = 0; u < SPW; ++u) {
-    e[u] = (sub0 + u) * kSweep + threadIdx.x * kLaneElems;
+    e[u] = (sub0 + u) * kSweep + threadIdx.x * kLaneElems - cd.lead;
     live[u] = e[u] < cd.len;
   }
   double acc[SPW], acc_hat[SPW];
 #pragma unroll
   for (int u = 0; u < SPW; ++u) { acc[u] = 0.0; acc_hat[u] = 0.0; }
-  if (sub0 * kSweep < cd.len) {        // uniform: the window holds elements
+  if (sub0 * kSweep < cd.len + cd.lead) {        // uniform: the window holds elements
     float xa[SPW][4], va[SPW][4], la[SPW][4], ra[SPW][4], ha[SPW][4], g[SPW][4];
 #pragma unroll
     for (int u = 0; u < SPW; ++u) {
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
       // three sparse patches of this iteration: my own message (what xhat must now
       // hold) and the two messages that arrive in my mailboxes
       const uint32_t left = (r + T.P - 1) % T.P, right = (r + 1) % T.P;
-      const uint32_t moff = T.layers[cd.layer].msg_off, j_lo = cd.j0 + sub0 * kSweep;
+      const uint32_t moff = T.layers[cd.layer].msg_off, j_lo = cd.j0 + sub0 * kSweep - cd.lead;
       const Slice s0m = message_slice<SPW>(T, r, cd.layer, c, sub0, moff);
       Slice s1 = message_slice<SPW>(T, left, cd.layer, c, sub0, moff);
       Slice s2 = message_slice<SPW>(T, right, cd.layer, c, sub0, moff);
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
       }
     }
   }
-  if (HISTA && sub0 * kSweep < cd.len) {     // uniform
+  if (HISTA && sub0 * kSweep < cd.len + cd.lead) {     // uniform
     __syncthreads();
     uint32_t* gh = T.hist + (size_t)seg * kHistBins;
     for (uint32_t b = threadIdx.x; b < (uint32_t)kHistBins; b += kThreads) {
