@@ -75,6 +75,7 @@ struct evg_ctx {
   uint64_t iters = 0;
   int64_t last_iter = -1;
   bool messages_live = false;       // the message buffers hold the last step's messages
+  uint32_t part = 0;                // workers of the ring that one workgroup of a walking pass goes through
   bool cached = false;              // the five arenas together fit the last-level cache
   bool device_ahead = false;        // evg_step_next has been used: replays of a captured graph
                                     // advance the device's iteration without the host seeing
@@ -296,7 +297,7 @@ static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uin
     if (norm_diff) add(S, 8);
   }
   if (topk) {
-    add(S * kHistBins, 4); add(S, 4); add(S, 4); add(PC, 8);
+    add(S * kHistBins, 4); add(S, 4); add(S, 4); add(S, 4); add(PC, 8);
     const uint64_t stage = P * (Npad / 16 * stage_num);
     add(stage, 4); add(stage, 4); add(stage, 4);
     add(PC, 8); add(PC, 8); add(PC * (SW + 1), 4);
@@ -443,6 +444,17 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
            !(use_scratch && need > kScratchBytes);
   };
   if (c->cached || !cut_chunks(true)) (void)cut_chunks(false);
+  // One workgroup per window and the whole ring, if that is enough of them for the 256 CUs; few windows (and then
+  // many workers) are better walked in parts, although the sends of the workers at their ends need a pass of
+  // their own.  1 / 2 / 4 / 8 parts: ResNet-20 of width 20 (414 windows) on 64 workers 216 / 202 / 186 / 184 us,
+  // ResNet-18 of width 10 (268) on 50 123 / 116 / 108 / 107, of width 14 (524) on 40 154 / 149 / 143 / 145, of width
+  // 20 (1069) on 20 131 / 138 / 140 / 149; a perceptron of 116 windows on 64 workers 70 / 68 / 61 / 57, of 388
+  // 140 / 156 / 148 / 145.
+  uint64_t windows = 0;
+  for (const ChunkDesc& cd : chunks) windows += (cd.lead + cd.len + kSweep - 1) / kSweep;
+  const uint64_t parts = windows < 600 ? (2048 + windows - 1) / windows : 1;
+  c->part = P < 16 ? P : std::max<uint32_t>(8u, (uint32_t)((P + parts - 1) / parts));
+  if (c->part > P) c->part = P;
   const uint64_t C = chunks.size();
   if ((uint64_t)P * C * (SW + 1) > 0xFFFFFFF0ull || (uint64_t)P * ktot > 0xFFFFFFF0ull) {
     delete c;
@@ -564,6 +576,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     TRY_OR_FREE(c->dalloc(&t.hist, S * kHistBins, true));
     TRY_OR_FREE(c->dalloc(&t.sel_prefix, S, true));
     TRY_OR_FREE(c->dalloc(&t.sel_krem, S, true));
+    TRY_OR_FREE(c->dalloc(&t.sel_cut, S, true));
     TRY_OR_FREE(c->dalloc(&t.stage_n, P * C, true));
     TRY_OR_FREE(c->dalloc(&t.stage_key, (uint64_t)P * t.stage_stride, false));
     TRY_OR_FREE(c->dalloc(&t.stage_idx, (uint64_t)P * t.stage_stride, false));
@@ -648,9 +661,10 @@ static evg_status enqueue_step(evg_ctx* c, const StepArgs& args, bool timed) {
     HIP_TRY(a.hist_fused ? launch_topk_decide(t, a, c->stream) : launch_trigger(t, a, c->stream));
     if ((st = ph.end()) != EVG_OK) return st;
   }
-  if (!a.delay && !a.pull && !a.topk_on) {   // with delayed delivery the mailboxes are written after the update;
-                                  // a cache-resident ring's receivers fetch the sends in the update pass;
-                                  // a Top-K ring's few whole sends ride in the selection's first kernel
+  // Whole sends: with delayed delivery the mailboxes are written after the update, a cache-resident ring's receivers
+  // fetch them in the update pass, a Top-K ring's few ride in the selection's first kernel, and a walking pass has
+  // them in registers -- but for the workers at the ends of the parts it is walked in.
+  if (!a.topk_on && a.walk && a.part < t.P) {
     Phase ph(c, EVG_PH_SEND_FULL);
     HIP_TRY(launch_copy(t, a, c->chunk_elems, c->stream));
     if ((st = ph.end()) != EVG_OK) return st;
@@ -670,7 +684,8 @@ static evg_status enqueue_step(evg_ctx* c, const StepArgs& args, bool timed) {
   {
     Phase ph(c, EVG_PH_UPDATE);
     const int norm = !fused ? 0 : !norm_diff ? 1 : g.topk_ppm ? 3 : 2;
-    HIP_TRY(launch_update(t, a, g.synth.dist, g.grad_mode, norm, c->stream));
+    HIP_TRY(a.walk ? launch_walk(t, a, g.synth.dist, g.grad_mode, norm, c->stream)
+                   : launch_update(t, a, g.synth.dist, g.grad_mode, norm, c->stream));
     if ((st = ph.end()) != EVG_OK) return st;
   }
   if (single) {
@@ -714,7 +729,8 @@ static evg_status fixed_args(evg_ctx* c, const float* grad, StepArgs* out) {
   a.pull = c->t.xsnap ? 1u : 0u;
   // a mailbox equals its sender's xhat wherever a message has arrived, unless messages are under way
   // (delay) or xhat moves without a message (reset)
-  a.share = (!c->cached && !g.delivery_delay && !(g.xhat_reset && g.topk_ppm)) ? 1u : 0u;
+  a.walk = (!c->cached && !g.delivery_delay && !(g.xhat_reset && g.topk_ppm)) ? 1u : 0u;
+  a.part = c->part;
   a.xhat_reset = (g.xhat_reset && g.topk_ppm) ? 1u : 0u;
   const bool norm_diff = g.trigger_kind == EVG_TRIGGER_NORM_DIFF;
   // fused + whole-tensor sends: xhat's norm is a scalar per tensor and xhat is never read

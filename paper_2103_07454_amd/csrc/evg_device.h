@@ -119,6 +119,11 @@ __device__ __forceinline__ void st4t(float* p, float4 a) {
   else *reinterpret_cast<float4*>(p) = a;
 }
 
+// Workers at the ends of a part of the ring (parts of A.part workers; one part: none).
+__device__ __forceinline__ bool is_led(const Tables& T, const StepArgs& A, uint32_t s) {
+  return A.part < T.P && (s % A.part == 0 || s % A.part == A.part - 1 || s == T.P - 1);
+}
+
 // The whole-tensor send of one chunk, by one workgroup.
 // HAT = false: the two mailboxes (xhat takes the sent values in the update pass, which has them
 // in registers).  HAT = true: xhat alone -- the receivers read it there in the update pass and
@@ -274,6 +279,56 @@ __device__ __forceinline__ float student_t3(uint32_t wr, uint32_t wa) {
   float c, s;
   turn_cos_sin(wa, c, s);
   return rad * c;
+}
+
+// The gradient of four consecutive elements, the first of them element j of its tensor: variates
+// times sg (sigma of the tensor at this iteration), times the gain where the worker has a spike.
+// DIST 0: normal, one Philox block per four elements.  DIST 1: Student-t(3), two blocks: variate i takes
+// words 2i (radius) and 2i+1 (angle) of the eight.
+template <int DIST>
+__device__ __forceinline__ void draw_gradient(const StepArgs& A, uint32_t j, uint32_t layer, uint32_t k, uint32_t r,
+                                              float sg, bool spike, float g[4]) {
+  if (DIST == 0) {
+    float z[4];
+    normals4(philox(j >> 2, layer, k, r, A.key0, A.key1), z);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) g[i] = sg * z[i];
+  } else {
+    const uint32_t b0 = (j >> 2) << 1;
+    const Rand4 ra = philox(b0, layer, k, r, A.key0, A.key1);
+    const Rand4 rb = philox(b0 + 1u, layer, k, r, A.key0, A.key1);
+    g[0] = sg * student_t3(ra.w[0], ra.w[1]);
+    g[1] = sg * student_t3(ra.w[2], ra.w[3]);
+    g[2] = sg * student_t3(rb.w[0], rb.w[1]);
+    g[3] = sg * student_t3(rb.w[2], rb.w[3]);
+  }
+  if (spike) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) g[i] = g[i] * A.spike_gain;
+  }
+}
+
+// Does worker r have a spike in iteration k?
+__device__ __forceinline__ bool has_spike(const StepArgs& A, uint32_t k, uint32_t r) {
+  return A.spike_prob > 0.0f && unit_open(philox(0u, 0xFFFFFFFFu, k, r, A.key0, A.key1).w[0]) < A.spike_prob;
+}
+
+// Squared drift of the first nv lanes of a float4 pair, added in lane order.
+__device__ __forceinline__ void drift_acc(double& acc, const float x[4], const float h[4], uint32_t nv) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if ((uint32_t)i < nv) {
+      const float e = x[i] - h[i];
+      acc += (double)e * (double)e;
+    }
+  }
+}
+
+// Sum of squares of the first nv lanes, added in lane order.
+__device__ __forceinline__ void square_acc(double& acc, const float x[4], uint32_t nv) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if ((uint32_t)i < nv) acc += (double)x[i] * (double)x[i];
 }
 
 // Key that ranks elements for Top-K: the bit pattern of a non-negative float is

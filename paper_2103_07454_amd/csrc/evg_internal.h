@@ -9,8 +9,6 @@ constexpr int kThreads = 256;          // 4 wavefronts of 64 lanes
 constexpr int kLaneElems = 4;          // one float4 per lane and sweep
 constexpr int kSweep = kThreads * kLaneElems;   // elements one workgroup covers per sweep
 constexpr uint32_t kLineElems = 32;    // floats of a 128-byte cache line
-constexpr uint32_t kXcds = 8;          // compute dies, each with an L2 of its own
-constexpr uint32_t kSegTiles = 128;    // 1024-element tiles of one worker that an XCD takes before the next worker's
 constexpr int kHistBins = 2048;        // 11 key bits per selection pass (passes A, B); pass C uses 512
 constexpr uint32_t kStageCap = 2048;   // staged entries / in-bin keys of a chunk that the staging kernel
 constexpr uint32_t kStageCapBin = 1024;   // gathers in LDS before writing them out (more: direct stores)
@@ -74,7 +72,8 @@ struct Tables {
   float* slope_hist; uint32_t* slope_cnt;   // [S*hist_len], [S]
   uint32_t* not_staged;    // [1] chunks so far whose possible winners did not fit their staging slot
   uint32_t* hist;          // [S*kHistBins]
-  uint32_t* sel_prefix; uint32_t* sel_krem;   // [S]
+  uint32_t* sel_prefix; uint32_t* sel_krem;   // [S] in the end the threshold key, and how many of the keys equal to it win
+  uint32_t* sel_cut;       // [S] the last element of the tensor that wins with a key equal to the threshold
   uint2* stage_n;          // [P*C] per chunk: staged entries (bin >= the threshold bin), and how many
                            // of them lie IN the threshold bin; x = 0xFFFFFFFF: more than the chunk's
                            // slot holds, nothing staged (its elements are then read from the arenas)
@@ -118,8 +117,8 @@ struct StepArgs {
   uint32_t from_device;    // take k and decay^k from IterState instead of the two fields here
   uint32_t xhat_reset;     // a Top-K event resets the whole tensor's xhat to x
   uint32_t cached;         // the arenas fit the last-level cache: ordinary instead of streaming accesses
-  uint32_t share;          // streaming ring whose mailboxes equal the senders' xhat: the update pass reads it there
-  uint32_t xcd_tiles;      // share: tiles per XCD (set by launch_update)
+  uint32_t walk;           // streaming ring whose mailboxes equal the senders' xhat: update pass of kernels_walk.hip
+  uint32_t part;           // walk: workers of the ring that a workgroup goes through (P: all)
   uint32_t pull;           // whole-tensor sends are fetched by the receivers inside the update pass
   uint32_t one_launch;     // ... and the update pass also runs the trigger tests (no other kernel in the step)
   uint32_t step_no;        // one_launch: steps completed before this one (picks the copy of x to read)
@@ -134,6 +133,8 @@ hipError_t launch_norm(const Tables& t, bool norm_diff, hipStream_t s);
 // norm: 0 no norm work, 1 squared drift, 2 squared x, 3 squared x and squared xhat
 hipError_t launch_update(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t grad_mode,
                          int norm, hipStream_t s);
+// norm as above; rings for which the host sets StepArgs::walk
+hipError_t launch_walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t grad_mode, int norm, hipStream_t s);
 hipError_t launch_trigger(const Tables& t, const StepArgs& a, hipStream_t s);
 hipError_t launch_begin(const Tables& t, hipStream_t s);
 hipError_t launch_copy(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);

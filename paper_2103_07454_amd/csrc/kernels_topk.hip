@@ -163,8 +163,8 @@ __global__ __launch_bounds__(kThreads) void k_topk_decide(Tables T, StepArgs A) 
 //   key                                     for those of them whose bin IS b (flag set): only they
 //                                           still have to be compared with the exact threshold,
 //                                           everything above bin b wins whatever the threshold is.
-// COPY: 0 nothing to do for a tensor sent whole (messages land later), 1 its chunk goes into the
-// two mailboxes, 2 into xhat (see copy_chunk): a Top-K tensor's first send takes no launch of its own.
+// COPY: 0 nothing to do for a tensor sent whole (it lands later, or the walk sends it), 1 its chunk goes into
+// the two mailboxes, 2 into xhat, if its worker is at the end of a part of the ring (see copy_chunk): a Top-K tensor's first send takes no launch of its own.
 template <int SWEEPS, int COPY, bool STREAM>
 __global__ __launch_bounds__(kThreads) void k_topk_stage(Tables T, StepArgs A) {
   constexpr int STEP = SWEEPS >= 4 ? 4 : SWEEPS;
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_stage(Tables T, StepArgs A) {
   __shared__ __attribute__((aligned(16))) float lv[kCap];
   const WorkItem wi = work_item(T, blockIdx.y, blockIdx.x);
   const uint32_t code = T.fired[wi.seg];      // uniform
-  if (COPY && code == 1) copy_chunk<SWEEPS, STREAM, COPY == 2>(T, wi.r, wi.cd);
+  if (COPY && code == 1 && (COPY == 1 || is_led(T, A, wi.r))) copy_chunk<SWEEPS, STREAM, COPY == 2>(T, wi.r, wi.cd);
   if (code != 2) return;
   const uint32_t bin = T.sel_prefix[wi.seg];
   for (uint32_t b = threadIdx.x; b < (uint32_t)kHistBins; b += kThreads) h[b] = 0;
@@ -491,6 +491,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_pack(Tables T, StepArgs A) {
         const uint32_t pos = g + (eq < ties ? eq : ties);
         T.msg_idx[mbase + pos] = j[u];
         T.msg_val[mbase + pos] = val[u];
+        if (ise && eq == ties - 1) T.sel_cut[wi.seg] = j[u];      // the last tie that wins
       }
       // entries ascend, so a group of 64 touches only the sweeps between its first and its last
       // entry's (all three values below are wave-uniform)
@@ -559,8 +560,8 @@ static void select_s(const Tables& t, const StepArgs& a, hipStream_t s) {
     k_topk_hist<SWEEPS><<<g, b, 0, s>>>(t, a);
     k_topk_pick<0><<<segs, b, 0, s>>>(t);
   }
-  if (a.delay) k_topk_stage<SWEEPS, 0, false><<<g, b, 0, s>>>(t, a);
-  else if (a.share) k_topk_stage<SWEEPS, 2, true><<<g, b, 0, s>>>(t, a);
+  if (a.delay || (a.walk && a.part == t.P)) k_topk_stage<SWEEPS, 0, false><<<g, b, 0, s>>>(t, a);
+  else if (a.walk) k_topk_stage<SWEEPS, 2, true><<<g, b, 0, s>>>(t, a);
   else if (a.cached) k_topk_stage<SWEEPS, 1, false><<<g, b, 0, s>>>(t, a);
   else k_topk_stage<SWEEPS, 1, true><<<g, b, 0, s>>>(t, a);
   k_topk_pick<1><<<segs, b, 0, s>>>(t);

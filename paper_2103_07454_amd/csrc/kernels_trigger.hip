@@ -3,9 +3,8 @@
 //              per-chunk partial sums in a fixed order, applies the event condition
 //              || xhat - x || >= delta (Section 4), recomputes the adaptive threshold
 //              at events (Eq. 3), marks the neighbours' mailbox slots as filled.
-//   k_copy     x -> left neighbour's right mailbox, right neighbour's left mailbox for
-//              every chunk of a tensor that fired: the stand-in for the one-sided puts of
-//              Section 6.  Rings whose update pass reads the neighbours' xhat: x -> xhat.
+//   k_copy     x -> xhat for every chunk of a tensor that fired, where the update pass walks the ring
+//              in parts: for the workers at their ends.
 // The kernels that act on fired tensors have one workgroup per chunk of the ring, which leaves
 // at once if its tensor stayed silent.  (Compact lists of the fired chunks, made by two more
 // kernels, cost a dependent launch each, 5 + 5 us, and saved nothing in the kernels that read them.)
@@ -37,12 +36,12 @@ __global__ void k_begin(Tables T) {
   T.it->decay_pow = T.decay_tab[k < T.decay_len ? k : T.decay_len - 1];
 }
 
-template <int SWEEPS, bool STREAM, bool HAT>
-__global__ __launch_bounds__(kThreads) void k_copy(Tables T) {
+template <int SWEEPS>
+__global__ __launch_bounds__(kThreads) void k_copy(Tables T, StepArgs A) {
   const uint32_t c = blockIdx.x, r = blockIdx.y;
   const ChunkDesc cd = T.chunks[c];
-  if (T.fired[r * T.L + cd.layer] != 1) return;
-  copy_chunk<SWEEPS, STREAM, HAT>(T, r, cd);
+  if (T.fired[r * T.L + cd.layer] != 1 || !is_led(T, A, r)) return;
+  copy_chunk<SWEEPS, true, true>(T, r, cd);
 }
 
 hipError_t launch_trigger(const Tables& t, const StepArgs& a, hipStream_t s) {
@@ -84,22 +83,16 @@ __global__ __launch_bounds__(kThreads) void k_deliver(Tables T) {
   }
 }
 
-template <bool STREAM, bool HAT>
-static hipError_t launch_copy_v(const Tables& t, uint32_t chunk_elems, hipStream_t s) {
+hipError_t launch_copy(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s) {
   const dim3 g(t.C, t.P), b(kThreads);
   switch (chunk_elems / kSweep) {
-    case 1: k_copy<1, STREAM, HAT><<<g, b, 0, s>>>(t); break;
-    case 2: k_copy<2, STREAM, HAT><<<g, b, 0, s>>>(t); break;
-    case 4: k_copy<4, STREAM, HAT><<<g, b, 0, s>>>(t); break;
-    case 8: k_copy<8, STREAM, HAT><<<g, b, 0, s>>>(t); break;
+    case 1: k_copy<1><<<g, b, 0, s>>>(t, a); break;
+    case 2: k_copy<2><<<g, b, 0, s>>>(t, a); break;
+    case 4: k_copy<4><<<g, b, 0, s>>>(t, a); break;
+    case 8: k_copy<8><<<g, b, 0, s>>>(t, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
-}
-
-hipError_t launch_copy(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s) {
-  if (a.share) return launch_copy_v<true, true>(t, chunk_elems, s);
-  return a.cached ? launch_copy_v<false, false>(t, chunk_elems, s) : launch_copy_v<true, false>(t, chunk_elems, s);
 }
 
 hipError_t launch_deliver(const Tables& t, uint32_t chunk_elems, hipStream_t s) {

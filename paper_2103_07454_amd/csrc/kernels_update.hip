@@ -35,24 +35,6 @@ namespace evg {
 
 __device__ __forceinline__ float4 ld4(const float* p) { return ld4s(p); }
 
-// Squared drift of the first nv lanes of a float4 pair, added in lane order.
-__device__ __forceinline__ void drift_acc(double& acc, const float x[4], const float h[4], uint32_t nv) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if ((uint32_t)i < nv) {
-      const float e = x[i] - h[i];
-      acc += (double)e * (double)e;
-    }
-  }
-}
-
-// Sum of squares of the first nv lanes, added in lane order.
-__device__ __forceinline__ void square_acc(double& acc, const float x[4], uint32_t nv) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if ((uint32_t)i < nv) acc += (double)x[i] * (double)x[i];
-}
-
 // NORMDIFF: the trigger compares ||x|| with ||xhat||: two sums instead of the drift's.
 template <bool NORMDIFF>
 __global__ __launch_bounds__(kThreads) void k_norm(Tables T) {
@@ -139,17 +121,6 @@ __device__ __forceinline__ void block_sums(const double v[SPW], double* ws, doub
   __syncthreads();
 }
 
-// Which tile a workgroup of a SHARE pass owns.  Workgroups go to the eight XCDs in turn by their
-// linear number; each XCD gets a contiguous eighth of the tiles, walks it in segments of `w` tiles,
-// and goes through all workers (blockIdx.y) of a segment before the next segment.  A worker's piece
-// of xhat is then read by the worker before, itself and the worker after within 2 w tiles' worth of
-// work on one L2.  w: see launch_update.
-__device__ __forceinline__ bool shared_tile(const StepArgs& A, uint32_t tiles, uint32_t* tile) {
-  const uint32_t w = gridDim.x / kXcds, i = blockIdx.z * w + blockIdx.x / kXcds;   // i: inside the XCD's eighth
-  *tile = (blockIdx.x % kXcds) * A.xcd_tiles + i;
-  return i < A.xcd_tiles && *tile < tiles;
-}
-
 // DIST: 0 normal (one Philox block per float4), 1 Student-t(3) (two blocks per float4).
 // GRADBUF: gradients come from a caller buffer.
 // NORM: what the pass accumulates for the next trigger test: 0 nothing, 1 the sweep's squared
@@ -167,15 +138,6 @@ __device__ __forceinline__ bool shared_tile(const StepArgs& A, uint32_t tiles, u
 // mailbox here; and the new x is also written to the other of the two copies for the next
 // iteration (two copies in turn: the one read now is written by nobody in this launch).  Fewer
 // launches per iteration for rings that live in the cache, where launches are what costs.
-// SHARE: what a worker last received from a neighbour IS that neighbour's xhat (same-iteration
-// delivery, only sent entries count as communicated): it is read from there, not from the mailbox
-// arena.  Three workers then read each piece of xhat, and the order of the workgroups (tile_of)
-// has two of the three reads hit the L2: 20 instead of 28 bytes of memory traffic per element and
-// step (12 instead of 20 read).  Measured, pass + copy kernel of whole sends: 16 ResNet-18 workers 855 + 233
-// -> 790 + 153 us; pass alone, 64 workers with Top-K 10 %: 4.85 -> 3.99 ms.  The owner may patch its xhat with its own message while its
-// neighbours read it: they apply the same message to what they read, so an entry of the message
-// ends as the sent value either way and every other entry is not changed by anyone.  A tensor
-// that was sent whole has had its xhat written by k_copy; the receiver stores it into its mailbox.
 // TESTS (with PULL): no kernel has run the trigger tests of this iteration.  Every workgroup
 // runs the three it depends on itself (its own tensor's and that tensor's of the two
 // neighbours: three wavefronts, one each, from the sweep sums the previous pass left), and the
@@ -183,7 +145,7 @@ __device__ __forceinline__ bool shared_tile(const StepArgs& A, uint32_t tiles, u
 // written by this launch (Tables: the _out arrays), so every workgroup decides alike.  One
 // launch per iteration.
 template <int DIST, bool GRADBUF, int NORM, bool TOPK, bool HISTA, int SPW, bool STREAM, bool PULL = false,
-          bool TESTS = false, bool SHARE = false>
+          bool TESTS = false>
 __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
   static_assert(!TESTS || (PULL && !TOPK && SPW == 1), "the tests ride in the pass of rings whose receivers fetch the sends");
   __shared__ double ws[4 * SPW];
@@ -198,11 +160,8 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
   uint32_t* hA = reinterpret_cast<uint32_t*>(pv);
   static_assert(!HISTA || TOPK, "the histogram shares the patch windows' storage");
   static_assert(NWIN >= 1 && NWIN <= 3, "EVG_PATCH_WINDOWS is 1, 2 or 3");
-  static_assert(!SHARE || !PULL, "two ways to get at the neighbours' values");
   const uint32_t groups = T.SW / SPW;      // workgroups per chunk (SW is a multiple of SPW)
-  uint32_t tile = blockIdx.x;
-  if (SHARE && !shared_tile(A, T.C * groups, &tile)) return;    // uniform
-  const uint32_t c = tile / groups, sub0 = (tile % groups) * SPW, r = blockIdx.y;
+  const uint32_t c = blockIdx.x / groups, sub0 = (blockIdx.x % groups) * SPW, r = blockIdx.y;
   const ChunkDesc cd = T.chunks[c];
   const uint32_t seg = r * T.L + cd.layer;
   bool vl = T.valid_l[seg] != 0, vr = T.valid_r[seg] != 0;
@@ -237,8 +196,8 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
   } else {
     my_event = T.fired[seg];
     // did my neighbours send this tensor whole in this iteration? (then vl / vr are set)
-    from_l = (PULL || SHARE) && T.fired[lw * T.L + cd.layer] == 1;
-    from_r = (PULL || SHARE) && T.fired[rw * T.L + cd.layer] == 1;
+    from_l = PULL && T.fired[lw * T.L + cd.layer] == 1;
+    from_r = PULL && T.fired[rw * T.L + cd.layer] == 1;
   }
   // step n reads copy (n-1) & 1 of x and writes copy n & 1; where a kernel ahead of this one ran
   // the tests it has counted this step already
@@ -274,25 +233,12 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
         if (!A.plain_sgd) v4 = ld4t<STREAM>(T.vel + base + e[u]);   // uniform
         xa[u][0] = x4.x; xa[u][1] = x4.y; xa[u][2] = x4.z; xa[u][3] = x4.w;
         va[u][0] = v4.x; va[u][1] = v4.y; va[u][2] = v4.z; va[u][3] = v4.w;
-        if (SHARE) {
-          // ordinary loads: the line is wanted twice more by this XCD
-          if (vl) {
-            const float4 t = ld4t<false>(T.xhat + (size_t)lw * T.Npad + cd.off + e[u]);
-            la[u][0] = t.x; la[u][1] = t.y; la[u][2] = t.z; la[u][3] = t.w;
-            if (from_l) st4t<STREAM>(T.mbox_l + base + e[u], t);
-          }
-        } else if (from_l) {        // the put of my left neighbour, carried out by its receiver
+        if (from_l) {        // the put of my left neighbour, carried out by its receiver
           const float4 t = ld4t<STREAM>(snap_in + (size_t)lw * T.Npad + cd.off + e[u]);
           la[u][0] = t.x; la[u][1] = t.y; la[u][2] = t.z; la[u][3] = t.w;
           st4t<STREAM>(T.mbox_l + base + e[u], t);
         } else if (vl) { const float4 t = ld4t<STREAM>(T.mbox_l + base + e[u]); la[u][0] = t.x; la[u][1] = t.y; la[u][2] = t.z; la[u][3] = t.w; }
-        if (SHARE) {
-          if (vr) {
-            const float4 t = ld4t<false>(T.xhat + (size_t)rw * T.Npad + cd.off + e[u]);
-            ra[u][0] = t.x; ra[u][1] = t.y; ra[u][2] = t.z; ra[u][3] = t.w;
-            if (from_r) st4t<STREAM>(T.mbox_r + base + e[u], t);
-          }
-        } else if (from_r) {
+        if (from_r) {
           const float4 t = ld4t<STREAM>(snap_in + (size_t)rw * T.Npad + cd.off + e[u]);
           ra[u][0] = t.x; ra[u][1] = t.y; ra[u][2] = t.z; ra[u][3] = t.w;
           st4t<STREAM>(T.mbox_r + base + e[u], t);
@@ -300,9 +246,9 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
         if (sent_whole) {
           // the whole tensor was sent in this iteration: xhat becomes the x just read
           ha[u][0] = xa[u][0]; ha[u][1] = xa[u][1]; ha[u][2] = xa[u][2]; ha[u][3] = xa[u][3];
-          if (!SHARE) st4t<STREAM>(T.xhat + base + e[u], x4);
+          st4t<STREAM>(T.xhat + base + e[u], x4);
         } else if (NORM == 1 || NORM == 3 || TOPK) {
-          const float4 t = ld4t<STREAM && !SHARE>(T.xhat + base + e[u]); ha[u][0] = t.x; ha[u][1] = t.y; ha[u][2] = t.z; ha[u][3] = t.w;
+          const float4 t = ld4t<STREAM>(T.xhat + base + e[u]); ha[u][0] = t.x; ha[u][1] = t.y; ha[u][2] = t.z; ha[u][3] = t.w;
         }
         if (GRADBUF) { const float4 t = ld4t<STREAM>(A.grad + base + e[u]); g[u][0] = t.x; g[u][1] = t.y; g[u][2] = t.z; g[u][3] = t.w; }
       }
@@ -380,29 +326,7 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
       if (live[u]) {
         if (!GRADBUF) {
           const float sg = (float)(T.layers[cd.layer].sig_base * step_decay(T, A));
-          if (DIST == 0) {
-            float z[4];
-            normals4(philox((cd.j0 + e[u]) >> 2, cd.layer, k_iter, r, A.key0, A.key1), z);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) g[u][i] = sg * z[i];
-          } else {
-            // four variates from the two Philox blocks 2g, 2g+1 of this float4 (g = index / 4):
-            // variate i takes words 2i (radius) and 2i+1 (angle) of the eight
-            const uint32_t b0 = ((cd.j0 + e[u]) >> 2) << 1;
-            const Rand4 ra = philox(b0, cd.layer, k_iter, r, A.key0, A.key1);
-            const Rand4 rb = philox(b0 + 1u, cd.layer, k_iter, r, A.key0, A.key1);
-            g[u][0] = sg * student_t3(ra.w[0], ra.w[1]);
-            g[u][1] = sg * student_t3(ra.w[2], ra.w[3]);
-            g[u][2] = sg * student_t3(rb.w[0], rb.w[1]);
-            g[u][3] = sg * student_t3(rb.w[2], rb.w[3]);
-          }
-          if (A.spike_prob > 0.0f) {
-            const Rand4 sp = philox(0u, 0xFFFFFFFFu, k_iter, r, A.key0, A.key1);
-            if (unit_open(sp.w[0]) < A.spike_prob) {
-#pragma unroll
-              for (int i = 0; i < 4; ++i) g[u][i] = g[u][i] * A.spike_gain;
-            }
-          }
+          draw_gradient<DIST>(A, cd.j0 + e[u], cd.layer, k_iter, r, sg, has_spike(A, k_iter, r), g[u]);
         }
         const uint32_t nv = cd.len - e[u] < 4u ? cd.len - e[u] : 4u;
 #pragma unroll
@@ -493,22 +417,6 @@ static void launch_update_w(const Tables& t, const StepArgs& a, uint32_t dist, u
     if (grad_mode == 1) k_update<0, true, NORM, NT, NH, 1, false, true><<<grid, block, 0, s>>>(t, a);
     else if (dist == 0) k_update<0, false, NORM, NT, NH, 1, false, true><<<grid, block, 0, s>>>(t, a);
     else k_update<1, false, NORM, NT, NH, 1, false, true><<<grid, block, 0, s>>>(t, a);
-    return;
-  }
-  if (a.share) {             // the host sets share only for streaming rings
-    // Segments of about kSegTiles tiles, all of one length.  Shorter ones keep less traffic between two
-    // reads of a piece of xhat, longer ones keep the memory streaming in longer runs.  The pass at
-    // 16 / 32 / 64 / 128 / 256 tiles: 858 / 828 / 801 / 790 / 786 us (16 ResNet-18 workers, whole sends),
-    // 1286 / 1270 / 1260 / 1249 / 1259 us (32, no momentum), 4.09 / 4.05 / 4.02 / 3.99 / 3.98 ms (64, Top-K 10 %).
-    StepArgs b = a;
-    const uint32_t tiles = t.C * (t.SW / SPW);
-    b.xcd_tiles = (tiles + kXcds - 1) / kXcds;
-    const uint32_t want = kSegTiles / SPW;
-    const uint32_t nseg = (b.xcd_tiles + want / 2) / want ? (b.xcd_tiles + want / 2) / want : 1u;
-    const dim3 sgrid(kXcds * ((b.xcd_tiles + nseg - 1) / nseg), t.P, nseg);
-    if (grad_mode == 1) k_update<0, true, NORM, TOPK, HISTA, SPW, true, false, false, true><<<sgrid, block, 0, s>>>(t, b);
-    else if (dist == 0) k_update<0, false, NORM, TOPK, HISTA, SPW, true, false, false, true><<<sgrid, block, 0, s>>>(t, b);
-    else k_update<1, false, NORM, TOPK, HISTA, SPW, true, false, false, true><<<sgrid, block, 0, s>>>(t, b);
     return;
   }
   if (a.cached) {

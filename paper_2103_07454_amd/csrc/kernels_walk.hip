@@ -1,0 +1,348 @@
+// The update pass of rings that stream from memory (same work and results as k_update): one
+// workgroup owns a window of one tensor and walks it around the whole ring, worker by worker.
+#include "trigger_device.h"
+
+namespace evg {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// A window of one worker's slice as a buffer of `bytes` bytes: lanes past them read zeros and write
+// nothing, so a window's ragged end, an array that is not wanted in this iteration (bytes = 0) and a
+// lane that has nothing to write all take the same instructions, without a branch around a memory access.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t window(const float* at, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(at), 0, (int)bytes, 0x00027000);
+}
+constexpr int kNt = 2;                        // non-temporal: every line is touched once
+constexpr uint32_t kNowhere = 0xFFFFFFF0u;    // an offset past every window
+
+struct Quad { float v[4]; };
+
+// Is `any` set in one of the four lanes whose float4s make up an aligned 64 bytes?  Those are written
+// together: scattered 16-byte writes cost far more in HBM than the unchanged bytes.
+__device__ __forceinline__ bool any_of_line_part(uint32_t any) {
+  any |= (uint32_t)__builtin_amdgcn_mov_dpp((int)any, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
+  any |= (uint32_t)__builtin_amdgcn_mov_dpp((int)any, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+  return any != 0;
+}
+
+__device__ __forceinline__ Quad load_quad(const float* at, uint32_t bytes, uint32_t byte) {
+  const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(window(at, bytes), (int)byte, 0, kNt);
+  Quad q;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) q.v[i] = __uint_as_float(t[i]);
+  return q;
+}
+__device__ __forceinline__ void store_quad(float* at, uint32_t bytes, uint32_t byte, const Quad& q) {
+  u32x4 t;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) t[i] = __float_as_uint(q.v[i]);
+  __builtin_amdgcn_raw_buffer_store_b128(t, window(at, bytes), (int)byte, 0, kNt);
+}
+
+// A copy that stays where it is written: the registers of the original are free for the next load from
+// here on (left to itself the compiler loads elsewhere and moves the values at the loop's end, which
+// waits there for loads that are wanted an iteration later).
+__device__ __forceinline__ Quad taken(const Quad& q) {
+  Quad c;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) asm volatile("v_mov_b32 %0, %1" : "=v"(c.v[i]) : "v"(q.v[i]));
+  return c;
+}
+
+// The sum of wave_sum, in its order of additions, without LDS: halves and rows change places for the
+// first two steps; from then on a row's values repeat with the step's period, so that a rotation
+// brings the same value as the exchange.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_sum_dpp(double v) {
+  uint64_t b = (uint64_t)__double_as_longlong(v);
+  const auto l32 = __builtin_amdgcn_permlane32_swap((uint32_t)b, (uint32_t)b, false, false);
+  const auto h32 = __builtin_amdgcn_permlane32_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+  v = __longlong_as_double((long long)(((uint64_t)h32[0] << 32) | l32[0])) +
+      __longlong_as_double((long long)(((uint64_t)h32[1] << 32) | l32[1]));
+  b = (uint64_t)__double_as_longlong(v);
+  const auto l16 = __builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false);
+  const auto h16 = __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+  v = __longlong_as_double((long long)(((uint64_t)h16[0] << 32) | l16[0])) +
+      __longlong_as_double((long long)(((uint64_t)h16[1] << 32) | l16[1]));
+  v += dpp_f64<0x128>(v);   // row_ror:8
+  v += dpp_f64<0x124>(v);   // row_ror:4
+  v += dpp_f64<0x122>(v);   // row_ror:2
+  v += dpp_f64<0x121>(v);   // row_ror:1
+  return v;
+}
+
+// What the walk has to know of a worker; lane i of a wavefront holds the i-th worker's.
+struct Marks { uint32_t f, thr, cut; };   // f: see below; Top-K: the threshold key, and the last element that wins a tie
+constexpr uint32_t kCode = 3u, kLeftFilled = 4u, kRightFilled = 8u, kSpike = 16u, kLed = 32u;
+
+template <int DIST, bool GRADBUF, int NORM, bool TOPK, bool HISTA, int W>
+__global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
+  constexpr uint32_t kElems = 256 * W, SPW = W / 4;
+  __shared__ double ws[NORM ? 64 * W : 1], ws_hat[NORM == 3 ? 64 * W : 1];
+  __shared__ __attribute__((aligned(16))) uint32_t hist[HISTA ? 2 * kHistBins + 4 : 4];
+  const uint32_t groups = T.SW / SPW;
+  const uint32_t c = blockIdx.x / groups, sub0 = (blockIdx.x % groups) * SPW;
+  const ChunkDesc cd = T.chunks[c];
+  if (sub0 * kSweep >= cd.len + cd.lead) return;                   // uniform (its sums are zero for good)
+  const uint32_t P = T.P, layer = cd.layer, k_iter = step_k(T, A);
+  const uint32_t r0 = blockIdx.y * A.part, n = P - r0 < A.part ? P - r0 : A.part;   // workers r0 .. r0 + n - 1
+  const bool closed = n == P;                            // the part is the whole ring
+  const uint32_t skip = sub0 == 0 ? cd.lead : 0u, first = sub0 * kSweep + skip - cd.lead;   // first element of the window
+  const uint32_t left_over = cd.len - first;
+  const uint32_t here = left_over < kElems - skip ? left_over : kElems - skip;   // elements of the window
+  const uint32_t nb = (here + 3) / 4 * 16;               // its bytes (tensors are padded to 4 elements)
+  const size_t off = (size_t)cd.off + first;
+  const uint32_t e = threadIdx.x * kLaneElems - skip;    // positions before the first element wrap around: past the end
+  const uint32_t byte = e < here ? e * 4 : kNowhere;
+  const uint32_t nv = e >= here ? 0u : here - e < 4u ? here - e : 4u;
+  const uint32_t j = cd.j0 + first + e;
+  const float third = 0.333333343f;   // (float)(1/3): the ring's mixing weight
+  const float sg = GRADBUF ? 0.0f : (float)(T.layers[layer].sig_base * step_decay(T, A));
+  const uint32_t nb_vel = A.plain_sgd ? 0u : nb;
+  auto at = [&](float* arena, uint32_t s) { return arena + (size_t)s * T.Npad + off; };
+  auto worker = [&](uint32_t i) { return r0 + i < P ? r0 + i : r0 + i - P; };   // i <= n
+
+  // the i-th worker of the part, i = n: the one after it
+  auto marks_of = [&](uint32_t i) {
+    Marks m{0u, 0xFFFFFFFFu, 0u};
+    if (i <= n) {
+      const uint32_t s = worker(i), seg = s * T.L + layer, code = T.fired[seg];
+      m.f = code | (T.valid_l[seg] ? kLeftFilled : 0u) | (T.valid_r[seg] ? kRightFilled : 0u);
+      if (!GRADBUF && has_spike(A, k_iter, s)) m.f |= kSpike;
+      if (is_led(T, A, s)) m.f |= kLed;
+      else if (TOPK && code == 2) { m.thr = T.sel_prefix[seg]; m.cut = T.sel_cut[seg]; }
+    }
+    return m;
+  };
+  uint32_t base = 0;
+  Marks cur = marks_of(lane_id()), nxt = cur;
+  if (n >= 64) nxt = marks_of(64 + lane_id());
+  auto read_mark = [&](uint32_t a, uint32_t b, uint32_t i) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)(i - base < 64 ? a : b), (int)((i - base) & 63u));
+  };
+
+  // What worker s's neighbours hold of it from this iteration on, written to its xhat (to_hat bytes) and its
+  // neighbours' mailboxes (to_right, to_left bytes) if it sends.
+  auto send = [&](uint32_t s, uint32_t f, uint32_t thr, uint32_t cut, uint32_t to_hat, uint32_t to_left, uint32_t to_right,
+                  const Quad& x, const Quad& h) {
+    Quad q;
+    uint32_t where = byte;
+    const bool led = (f & kLed) != 0, whole = (f & kCode) == 1 && !led;
+    if (TOPK) {
+      uint32_t any = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t key = rank_key(x.v[i], h.v[i], A.topk_key);
+        const bool win = key > thr || (key == thr && j + i <= cut);
+        q.v[i] = whole || win ? x.v[i] : h.v[i];
+        any |= win ? 1u : 0u;
+      }
+      if (!whole && !led && !any_of_line_part(any)) where = kNowhere;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) q.v[i] = whole ? x.v[i] : h.v[i];
+    }
+    const bool sends = (f & kCode) != 0;
+    store_quad(at(T.xhat, s), sends && !led ? to_hat : 0u, where, q);
+    store_quad(at(T.mbox_l, s + 1 == P ? 0u : s + 1), sends ? to_right : 0u, where, q);
+    store_quad(at(T.mbox_r, s == 0 ? P - 1 : s - 1), sends ? to_left : 0u, where, q);
+    return q;
+  };
+  // does the walk need xhat from memory?  (not where the whole tensor has just been sent)
+  auto reads_hat = [](uint32_t f) { return (f & kCode) != 1 || (f & kLed) != 0; };
+
+  if (HISTA) {
+    for (uint32_t b = threadIdx.x; b < 2 * kHistBins + 4; b += 64 * W) hist[b] = 0;
+    __syncthreads();
+  }
+  const bool dead = !HISTA && wave_id() * 256u >= here + skip;      // wave-uniform
+  if (NORM && dead) {
+    ws[lane_id() * W + wave_id()] = 0.0;
+    if (NORM == 3) ws_hat[lane_id() * W + wave_id()] = 0.0;
+  }
+
+  // The last worker whose x / xhat the loop below loads.  A closed ring's last worker is among the
+  // first two that are loaded and stays in registers, an open part ends with the xhat of the worker after it.
+  const uint32_t last_x = closed ? n - 2 : n - 1, last_h = closed ? n - 2 : n;
+  Quad x1{}, h1{}, v1{}, g1{}, xc{}, ec{}, el{}, x_last{}, e_last{}, e_first{};
+  if (!dead) {
+    const uint32_t before = r0 == 0 ? P - 1 : r0 - 1;
+    x_last = load_quad(at(T.x, before), closed ? nb : 0u, byte);
+    xc = load_quad(at(T.x, r0), nb, byte);
+    x1 = load_quad(at(T.x, worker(1)), 1 <= last_x ? nb : 0u, byte);
+    v1 = load_quad(at(T.vel, r0), nb_vel, byte);
+    if (GRADBUF) g1 = load_quad(A.grad + (size_t)r0 * T.Npad + off, nb, byte);
+    const uint32_t seg_b = before * T.L + layer;
+    uint32_t f_b = __builtin_amdgcn_readfirstlane((int)T.fired[seg_b]);
+    if (is_led(T, A, before)) f_b |= kLed;
+    uint32_t thr_b = 0xFFFFFFFFu, cut_b = 0u;
+    if (TOPK && f_b == 2) {
+      thr_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)T.sel_prefix[seg_b]);
+      cut_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)T.sel_cut[seg_b]);
+    }
+    const uint32_t f0 = read_mark(cur.f, nxt.f, 0);
+    const Quad h_last = load_quad(at(T.xhat, before), reads_hat(f_b) ? nb : 0u, byte);
+    const Quad h0 = load_quad(at(T.xhat, r0), reads_hat(f0) ? nb : 0u, byte);
+    h1 = load_quad(at(T.xhat, worker(1)), 1 <= last_h && reads_hat(read_mark(cur.f, nxt.f, 1)) ? nb : 0u, byte);
+    e_last = send(before, f_b, thr_b, cut_b, closed ? nb : 0u, closed ? nb : 0u, nb, x_last, h_last);
+    e_first = send(r0, f0, read_mark(cur.thr, nxt.thr, 0), read_mark(cur.cut, nxt.cut, 0), nb, closed ? nb : 0u,
+                   closed || n > 1 ? nb : 0u, xc, h0);
+    el = e_last;
+    ec = e_first;
+  }
+  for (uint32_t i = 0; i < n; ++i) {
+    const uint32_t r = r0 + i;
+    if (i == base + 64) {
+      base += 64;
+      cur = nxt;
+      nxt = marks_of(base + 64 + lane_id());
+    }
+    if (!dead) {
+      // the next worker's values have arrived: take them, and ask for those of the one after it
+      Quad xn = taken(x1), hn = taken(h1), vel = taken(v1), g = GRADBUF ? taken(g1) : g1;
+      const uint32_t f = read_mark(cur.f, nxt.f, i), fn = read_mark(cur.f, nxt.f, i + 1);
+      const uint32_t f2 = read_mark(cur.f, nxt.f, i + 2);
+      const uint32_t s1 = worker(i + 1), s2 = i + 2 <= n ? worker(i + 2) : 0u;
+      const bool another = i + 1 < n;
+      x1 = load_quad(at(T.x, s2), i + 2 <= last_x ? nb : 0u, byte);
+      h1 = load_quad(at(T.xhat, s2), i + 2 <= last_h && reads_hat(f2) ? nb : 0u, byte);
+      v1 = load_quad(at(T.vel, another ? r + 1 : 0), another ? nb_vel : 0u, byte);
+      if (GRADBUF) g1 = load_quad(A.grad + (size_t)(another ? r + 1 : 0) * T.Npad + off, another ? nb : 0u, byte);
+      Quad en = send(s1, fn, read_mark(cur.thr, nxt.thr, i + 1), read_mark(cur.cut, nxt.cut, i + 1),
+                     i + 1 <= last_x ? nb : 0u, i + 1 <= last_h ? nb : 0u, i + 1 <= last_x && (closed || i + 2 < n) ? nb : 0u,
+                     xn, hn);
+      if (closed && i + 1 > last_x) {
+        en = i + 1 == n ? e_first : e_last;
+        xn = x_last;
+      }
+      if (!GRADBUF) draw_gradient<DIST>(A, j, layer, k_iter, r, sg, (f & kSpike) != 0, g.v);
+      const bool vl = (f & kLeftFilled) != 0, vr = (f & kRightFilled) != 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool in = (uint32_t)i < nv;      // lanes past the tensor's end are padding: left as they are
+        const float vn = A.plain_sgd ? g.v[i] : __builtin_fmaf(A.mu, vel.v[i], g.v[i]);
+        const float a = (vl ? (el.v[i] - xc.v[i]) : 0.0f) + (vr ? (en.v[i] - xc.v[i]) : 0.0f);
+        const float cns = __builtin_fmaf(a, third, xc.v[i]);
+        const float xnew = __builtin_fmaf(-A.lr, vn, cns);
+        xc.v[i] = in ? xnew : xc.v[i];
+        vel.v[i] = in ? vn : vel.v[i];
+      }
+      store_quad(at(T.x, r), nb, byte, xc);
+      store_quad(at(T.vel, r), nb_vel, byte, vel);
+      if (NORM) {
+        double acc = 0.0, acc_hat = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {          // in lane order, padding adds zero
+          const bool in = (uint32_t)i < nv;
+          const float d = in ? (NORM == 1 ? xc.v[i] - ec.v[i] : xc.v[i]) : 0.0f, h = in ? ec.v[i] : 0.0f;
+          acc += (double)d * (double)d;
+          if (NORM == 3) acc_hat += (double)h * (double)h;
+        }
+        acc = wave_sum_dpp(acc);
+        if (NORM == 3) acc_hat = wave_sum_dpp(acc_hat);
+        if (lane_id() == 0) {
+          ws[(i & 63u) * W + wave_id()] = acc;
+          if (NORM == 3) ws_hat[(i & 63u) * W + wave_id()] = acc_hat;
+        }
+      }
+      if (HISTA) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const uint32_t bin = rank_key(xc.v[q], ec.v[q], A.topk_key) >> 20;
+          atomicAdd(&hist[(uint32_t)q < nv ? (i & 1u) * kHistBins + bin : 2 * kHistBins], 1u);
+        }
+      }
+      el = ec;
+      ec = en;
+      xc = xn;
+    }
+    if (HISTA) {
+      // two histograms in turn: this barrier ends worker r's counting, and the clearing of the other one
+      __syncthreads();
+      uint32_t* gh = T.hist + (size_t)(r * T.L + layer) * kHistBins;
+      for (uint32_t b = threadIdx.x * 4; b < (uint32_t)kHistBins; b += 256 * W) {
+        u32x4* p = reinterpret_cast<u32x4*>(hist + (i & 1u) * kHistBins + b);
+        const u32x4 n = *p;
+        if (n.x | n.y | n.z | n.w) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (n[i]) atomicAdd(gh + b + i, n[i]);
+          *p = u32x4{0u, 0u, 0u, 0u};
+        }
+      }
+    }
+    if (NORM && ((i & 63u) == 63u || i == n - 1)) {          // uniform
+      __syncthreads();
+      const uint32_t done = (i & 63u) + 1;
+      for (uint32_t q = threadIdx.x; q < done * SPW; q += 64 * W) {
+        const uint32_t rr = q / SPW, u = q % SPW;
+        const size_t slot = ((size_t)(r0 + (i & ~63u) + rr) * T.C + c) * T.SW + sub0 + u;
+        const double* p = ws + rr * W + 4 * u;
+        T.partials_out[slot] = ((p[0] + p[1]) + p[2]) + p[3];
+        if (NORM == 3) {
+          const double* ph = ws_hat + rr * W + 4 * u;
+          T.partials_hat_out[slot] = ((ph[0] + ph[1]) + ph[2]) + ph[3];
+        }
+      }
+      __syncthreads();
+    }
+  }
+}
+
+// A ring walked in parts: the Top-K messages of the workers at the ends of parts go into their xhat ahead
+// of the walk, where both parts then find what they sent (whole tensors: copy_chunk).
+__global__ __launch_bounds__(kThreads) void k_lead(Tables T, StepArgs A) {
+  const uint32_t c = blockIdx.x / T.SW, sub = blockIdx.x % T.SW, r = blockIdx.y;
+  const ChunkDesc cd = T.chunks[c];
+  const uint32_t seg = r * T.L + cd.layer;
+  if (!is_led(T, A, r) || T.fired[seg] != 2) return;           // uniform
+  const uint32_t e = sub * kSweep + threadIdx.x * kLaneElems - cd.lead;   // positions before the lead wrap around
+  const bool live = e < cd.len;
+  float* at = T.xhat + (size_t)r * T.Npad + cd.off + e;
+  float4 x4 = make_float4(0.f, 0.f, 0.f, 0.f), h4 = x4;
+  if (live) { x4 = ld4s(T.x + (size_t)r * T.Npad + cd.off + e); h4 = ld4s(at); }
+  const uint32_t thr = T.sel_prefix[seg], cut = T.sel_cut[seg];
+  const float xa[4] = {x4.x, x4.y, x4.z, x4.w};
+  float ha[4] = {h4.x, h4.y, h4.z, h4.w};
+  uint32_t any = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t key = rank_key(xa[i], ha[i], A.topk_key);
+    const bool win = key > thr || (key == thr && cd.j0 + e + i <= cut);
+    ha[i] = win ? xa[i] : ha[i];
+    any |= win ? 1u : 0u;
+  }
+  if (live && any_of_line_part(any)) st4s(at, make_float4(ha[0], ha[1], ha[2], ha[3]));
+}
+
+template <int NORM, bool TOPK, bool HISTA, int W>
+static void walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t grad_mode, hipStream_t s) {
+  const dim3 grid(t.C * (t.SW / (W / 4)), (t.P + a.part - 1) / a.part), block(64 * W);
+  if (grad_mode == 1) k_update_walk<0, true, NORM, TOPK, HISTA, W><<<grid, block, 0, s>>>(t, a);
+  else if (dist == 0) k_update_walk<0, false, NORM, TOPK, HISTA, W><<<grid, block, 0, s>>>(t, a);
+  else k_update_walk<1, false, NORM, TOPK, HISTA, W><<<grid, block, 0, s>>>(t, a);
+}
+
+hipError_t launch_walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t grad_mode, int norm, hipStream_t s) {
+  if (a.topk_on) {
+    if (a.part < t.P) k_lead<<<dim3(t.C * t.SW, t.P), dim3(kThreads), 0, s>>>(t, a);
+    // eight wavefronts share a histogram where chunks are long enough
+    const bool wide = t.SW % 2 == 0;
+    if (norm == 0) walk<0, true, false, 4>(t, a, dist, grad_mode, s);
+    else if (norm == 1 && a.hist_fused) wide ? walk<1, true, true, 8>(t, a, dist, grad_mode, s) : walk<1, true, true, 4>(t, a, dist, grad_mode, s);
+    else if (norm == 3 && a.hist_fused) wide ? walk<3, true, true, 8>(t, a, dist, grad_mode, s) : walk<3, true, true, 4>(t, a, dist, grad_mode, s);
+    else return hipErrorInvalidValue;
+  } else if (norm == 0) walk<0, false, false, 4>(t, a, dist, grad_mode, s);
+  else if (norm == 1) walk<1, false, false, 4>(t, a, dist, grad_mode, s);
+  else if (norm == 2) walk<2, false, false, 4>(t, a, dist, grad_mode, s);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+}  // namespace evg

@@ -1,0 +1,53 @@
+"""Streaming rings are updated by workgroups that walk a window around the ring, in parts where a
+network has few windows and many workers.  Checked against the oracle at the ring sizes where the walk
+can go wrong: the smallest, around the 64 workers whose marks a wavefront holds at a time, and rings
+whose last part is of one worker or a few."""
+import pytest
+
+from paper_2103_07454_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def evg():
+    from paper_2103_07454_amd import evg as m
+    m.lib()
+    return m
+
+
+def _run(evg, oracle_mod, P, numels, *, norm_mode=0, iters=7, **kw):
+    from helpers import lockstep
+    both = {k: kw.pop(k) for k in ("trigger_kind", "topk_key") if k in kw}
+    tensors = [inputs.TensorSpec(f"t{i}", (n,), 16 + i, "weight") for i, n in enumerate(numels)]
+    w = inputs.Workload("walk", P, tensors, iters, sigma0=0.05, decay=0.9, seed=P, **kw)
+    x0 = inputs.replicate(w.x0(), P)
+    ring = evg.Ring.from_workload(w, x0, mailbox_fill=float("nan"), access_mode=evg.ACCESS_STREAM, norm_mode=norm_mode, **both)
+    orc = oracle_mod.Oracle.from_workload(w, x0, **both)
+    differ = "trigger_kind" in both
+    rep = lockstep(ring, orc, w.iters, sample_messages=8, norm_rtol=None if differ else 2e-7,
+                   norm_abs_of_x=2.5e-7 if differ else None)
+    assert rep["rel"]["x"] <= 1e-5 and (differ or all(rep["bitwise"].values())), rep
+
+
+# 3 .. 15 workers: one part; from 16 on parts of 8: 16 = 8 + 8, 17 = 8 + 8 + 1, 23 = 8 + 8 + 7
+@pytest.mark.parametrize("P", [3, 4, 15, 16, 17, 23, 63, 64, 65, 66, 130])
+@pytest.mark.parametrize("kw", [dict(), dict(momentum=0.0, spike_prob=0.3, spike_gain=4.0), dict(topk_ppm=100_000),
+                                dict(topk_ppm=20_000, dist=1, topk_key=1)], ids=["whole", "plain", "topk", "topk_value"])
+def test_ring_sizes(evg, oracle_mod, P, kw):
+    _run(evg, oracle_mod, P, [1300, 7, 2048, 515], **kw)
+
+
+# more than 600 windows: one part whatever the number of workers
+@pytest.mark.parametrize("P", [16, 64, 65])
+@pytest.mark.parametrize("topk", [0, 100_000])
+def test_whole_ring(evg, oracle_mod, P, topk):
+    _run(evg, oracle_mod, P, [3] * 640 + [1029], topk_ppm=topk, iters=4)
+
+
+@pytest.mark.parametrize("P", [5, 18])
+@pytest.mark.parametrize("topk", [0, 100_000])
+@pytest.mark.parametrize("norm_mode,trigger_kind", [(1, 0), (0, 1), (1, 1)])
+def test_norms(evg, oracle_mod, P, topk, norm_mode, trigger_kind):
+    kw = dict(trigger_kind=1) if trigger_kind else {}
+    _run(evg, oracle_mod, P, [9000, 33, 1024], topk_ppm=topk, norm_mode=norm_mode, **kw)
