@@ -267,17 +267,8 @@ evg_status evg_destroy(evg_ctx* c) {
 
 // Bytes of library-owned device tables a configuration needs, with every table rounded up to
 // the scratch block's alignment: the same list as the allocations of init_common.
-// Staging entries reserved per 16 elements of a chunk.  The possible winners of a Top-K event are
-// its K winners plus the rest of the threshold bin (a 9 % wide slice of the key range: a few per
-// cent of the tensor): one and a half times the Top-K share plus a sixteenth covers that with room
-// to spare, and a chunk that needs more is handled from the arenas.
-static uint32_t stage_num_for(uint32_t topk_ppm) {
-  const uint64_t want = (3ull * topk_ppm * 8ull + 999999ull) / 1000000ull + 1ull;   // in sixteenths
-  return want <= 4 ? 4u : want <= 8 ? 8u : want <= 12 ? 12u : 16u;
-}
-
 static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uint64_t hist_len, uint64_t Npad,
-                            uint64_t ktot, uint64_t stage_num, bool topk, bool norm_diff, bool pull, bool one_launch) {
+                            uint64_t ktot, bool topk, bool norm_diff, bool pull, bool one_launch) {
   const uint64_t S = P * L, PC = P * C;
   uint64_t total = 0;
   auto add = [&total](uint64_t count, uint64_t elem) {
@@ -297,11 +288,24 @@ static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uin
     if (norm_diff) add(S, 8);
   }
   if (topk) {
-    add(S * kHistBins, 4); add(S, 4); add(S, 4); add(S, 4); add(PC, 8);
-    const uint64_t stage = P * (Npad / 16 * stage_num);
-    add(stage, 4); add(stage, 4); add(stage, 4);
-    add(PC, 8); add(PC, 8); add(PC * (SW + 1), 4);
+    add(S * kHistBins, 4); add(S, 4); add(S, 4); add(S, 4); add(PC, 4);   // hist, selection, stage_n
+    add(P * (Npad / 16 * 4), 4);                         // stage_key
+    add(PC * SW * 4, 4); add(PC, 8); add(PC, 8);           // group, chunk_cnt, chunk_before
     add(P * ktot, 4); add(P * ktot, 4); add(S, 8); add(S, 8);
+  }
+  return total;
+}
+
+// What evg_init_static admits is part of its interface and older than the present tables: a Top-K ring is
+// reckoned with three words for each possible winner (one and a half times the Top-K share plus a sixteenth, in
+// quarters of the ring) and without copies of x.  The tables take less.
+static uint64_t admitted_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uint64_t hist_len, uint64_t Npad,
+                               uint64_t ktot, uint32_t topk_ppm, bool norm_diff, bool pull, bool one_launch) {
+  uint64_t total = table_bytes(P, L, C, SW, hist_len, Npad, ktot, topk_ppm != 0, norm_diff, pull && !topk_ppm, one_launch);
+  if (topk_ppm) {
+    const uint64_t want = (3ull * topk_ppm * 8ull + 999999ull) / 1000000ull + 1ull;   // in sixteenths
+    const uint64_t quarters = want <= 4 ? 1 : want <= 8 ? 2 : want <= 12 ? 3 : 4;
+    total += P * (Npad / 16 * 4) * 4 * (3 * quarters - 1);
   }
   return total;
 }
@@ -413,9 +417,11 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   // width 28, 60 workers 843 -> 771 us; width 40, 30 workers 871 -> 796 us.  Not where the additional chunks
   // would take the tables past a limit.
   const uint32_t hist_len = cfg->thr_mode == EVG_THR_ADAPTIVE ? cfg->hist_len : 1, SW = ce / (uint32_t)kSweep;
-  const bool pull = c->cached && !cfg->topk_ppm && !cfg->delivery_delay;
+  // (an xhat that is reset at events is not what a neighbour's mailbox holds, so that a Top-K message could not be told from it)
+  bool pull = c->cached && !cfg->delivery_delay && !(cfg->xhat_reset && cfg->topk_ppm);
   bool one_launch = false;
   uint64_t need = 0;
+  uint64_t admitted = 0;
   auto cut_chunks = [&](bool on_lines) {
     chunks.clear();
     uint32_t most_sweeps = 0;
@@ -437,13 +443,19 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     }
     // one launch per iteration: the ring's receivers fetch the sends (see `pull` below), the update pass
     // accumulates the norms, and one wavefront sums a tensor's sweep partials with two loads per lane
-    one_launch = pull && cfg->norm_mode == EVG_NORM_FUSED && most_sweeps <= 128;
-    need = table_bytes(P, L, chunks.size(), SW, hist_len, Npad, ktot, stage_num_for(cfg->topk_ppm), cfg->topk_ppm != 0,
+    one_launch = pull && !cfg->topk_ppm && cfg->norm_mode == EVG_NORM_FUSED && most_sweeps <= 128;
+    need = table_bytes(P, L, chunks.size(), SW, hist_len, Npad, ktot, cfg->topk_ppm != 0,
                        cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF, pull, one_launch);
+    admitted = admitted_bytes(P, L, chunks.size(), SW, hist_len, Npad, ktot, cfg->topk_ppm,
+                              cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF, pull, one_launch);
     return (uint64_t)P * chunks.size() * (SW + 1) <= 0xFFFFFFF0ull && (uint64_t)P * ktot <= 0xFFFFFFF0ull &&
-           !(use_scratch && need > kScratchBytes);
+           !(use_scratch && std::max(need, admitted) > kScratchBytes);
   };
   if (c->cached || !cut_chunks(true)) (void)cut_chunks(false);
+  if (use_scratch && need > kScratchBytes && pull && cfg->topk_ppm) {   // no room for the copies of x: messages are applied
+    pull = false;                                                        // by a kernel of their own
+    (void)cut_chunks(false);
+  }
   // One workgroup per window and the whole ring, if that is enough of them for the 256 CUs; few windows (and then
   // many workers) are better walked in parts, although the sends of the workers at their ends need a pass of
   // their own.  1 / 2 / 4 / 8 parts: ResNet-20 of width 20 (414 windows) on 64 workers 216 / 202 / 186 / 184 us,
@@ -469,8 +481,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   t.hist_len = hist_len;
   t.Ktot = (uint32_t)ktot;
   t.Npad = Npad;
-  t.stage_num = stage_num_for(cfg->topk_ppm);
-  t.stage_stride = Npad / 16 * t.stage_num;
+  t.stage_stride = Npad / 16 * 4;
   t.x = cfg->x; t.xhat = cfg->xhat; t.mbox_l = cfg->mbox_l; t.mbox_r = cfg->mbox_r; t.vel = cfg->vel;
   int dev = 0;
   ChunkDesc* d_chunks = nullptr;
@@ -493,6 +504,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   } while (0)
   HIP_OR_FREE(hipGetDevice(&dev));
   if (use_scratch) {
+    need = std::max(need, admitted);
     if (need > kScratchBytes) {
       evg_destroy(c);
       return fail(EVG_ERR_INVALID, "this configuration needs %llu bytes of tables; the static scratch block "
@@ -579,11 +591,9 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     TRY_OR_FREE(c->dalloc(&t.sel_cut, S, true));
     TRY_OR_FREE(c->dalloc(&t.stage_n, P * C, true));
     TRY_OR_FREE(c->dalloc(&t.stage_key, (uint64_t)P * t.stage_stride, false));
-    TRY_OR_FREE(c->dalloc(&t.stage_idx, (uint64_t)P * t.stage_stride, false));
-    TRY_OR_FREE(c->dalloc(&t.stage_val, (uint64_t)P * t.stage_stride, false));
+    TRY_OR_FREE(c->dalloc(&t.group, P * C * t.SW * 4, true));
     TRY_OR_FREE(c->dalloc(&t.chunk_cnt, P * C, true));
     TRY_OR_FREE(c->dalloc(&t.chunk_before, P * C, true));
-    TRY_OR_FREE(c->dalloc(&t.chunk_sub, P * C * (t.SW + 1), true));
     TRY_OR_FREE(c->dalloc(&t.msg_idx, (uint64_t)P * ktot, true));
     TRY_OR_FREE(c->dalloc(&t.msg_val, (uint64_t)P * ktot, true));
     TRY_OR_FREE(c->dalloc(&t.idx_hash, S, true));
@@ -675,9 +685,9 @@ static evg_status enqueue_step(evg_ctx* c, const StepArgs& args, bool timed) {
       HIP_TRY(launch_topk_select(t, a, c->chunk_elems, c->stream));
       if ((st = ph.end()) != EVG_OK) return st;
     }
-    {
+    if (a.applied || (a.walk && a.part < t.P)) {
       Phase ph(c, EVG_PH_TOPK_SEND);
-      HIP_TRY(launch_topk_send(t, a, c->stream));
+      HIP_TRY(launch_topk_apply(t, a, c->chunk_elems, c->stream));
       if ((st = ph.end()) != EVG_OK) return st;
     }
   }
@@ -731,6 +741,7 @@ static evg_status fixed_args(evg_ctx* c, const float* grad, StepArgs* out) {
   // (delay) or xhat moves without a message (reset)
   a.walk = (!c->cached && !g.delivery_delay && !(g.xhat_reset && g.topk_ppm)) ? 1u : 0u;
   a.part = c->part;
+  a.applied = (g.topk_ppm && !g.delivery_delay && !a.walk && !a.pull) ? 1u : 0u;
   a.xhat_reset = (g.xhat_reset && g.topk_ppm) ? 1u : 0u;
   const bool norm_diff = g.trigger_kind == EVG_TRIGGER_NORM_DIFF;
   // fused + whole-tensor sends: xhat's norm is a scalar per tensor and xhat is never read

@@ -29,6 +29,14 @@ __device__ __forceinline__ void st4s(float* p, float4 a) {
   __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(p));
 }
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// `bytes` bytes of memory as a buffer: lanes past them read zeros and write nothing, so a ragged end, an array that
+// is not wanted this time (bytes = 0) and a lane that has nothing to write all take the same instructions,
+// without a branch around a memory access (the compiler waits for a load before it leaves its branch).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t window(const void* at, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(at), 0, (int)bytes, 0x00027000);
+}
 // Sum over the 64 lanes by xor butterflies: every lane ends with the same value,
 // and the association order is fixed, so results repeat bit for bit.
 __device__ __forceinline__ double wave_sum(double v) {

@@ -10,8 +10,7 @@ constexpr int kLaneElems = 4;          // one float4 per lane and sweep
 constexpr int kSweep = kThreads * kLaneElems;   // elements one workgroup covers per sweep
 constexpr uint32_t kLineElems = 32;    // floats of a 128-byte cache line
 constexpr int kHistBins = 2048;        // 11 key bits per selection pass (passes A, B); pass C uses 512
-constexpr uint32_t kStageCap = 2048;   // staged entries / in-bin keys of a chunk that the staging kernel
-constexpr uint32_t kStageCapBin = 1024;   // gathers in LDS before writing them out (more: direct stores)
+constexpr uint32_t kStageCap = 2048;   // staged keys of a chunk at most
 
 // A chunk is a run of one tensor's elements that one workgroup handles; it never
 // straddles tensors, starts at a multiple of 4 elements and is at most chunk_elems long.
@@ -74,19 +73,14 @@ struct Tables {
   uint32_t* hist;          // [S*kHistBins]
   uint32_t* sel_prefix; uint32_t* sel_krem;   // [S] in the end the threshold key, and how many of the keys equal to it win
   uint32_t* sel_cut;       // [S] the last element of the tensor that wins with a key equal to the threshold
-  uint2* stage_n;          // [P*C] per chunk: staged entries (bin >= the threshold bin), and how many
-                           // of them lie IN the threshold bin; x = 0xFFFFFFFF: more than the chunk's
-                           // slot holds, nothing staged (its elements are then read from the arenas)
-  uint32_t* stage_idx; float* stage_val;   // [P*stage_stride] a chunk's staged entries, in ascending index
-                           // order; bit 31 of the index = in the threshold bin.  The chunk at arena
-                           // offset `off` owns entries (off/16)*stage_num .. +(len/16)*stage_num
-  uint32_t* stage_key;     // [P*stage_stride] the keys of the chunk's in-bin entries, same place, same order
-  uint32_t stage_num;      // staging entries per 16 elements: 4, 8, 12 or 16
+  uint32_t* stage_n;       // [P*C] staged keys of a chunk: those in the threshold bin; 0xFFFFFFFF: more than the
+                           // chunk's slot holds, nothing staged (they are then read from the arenas)
+  uint32_t* stage_key;     // [P*stage_stride] their low 20 bits, and the group in the chunk they belong to
   uint64_t stage_stride;   // staging entries per worker
-  uint2* chunk_cnt;        // [P*C] (keys above threshold, keys equal) per chunk
+  uint32_t* group;         // [P*C*SW*4] per 256 elements: keys above the threshold bin; in the end, over the chunk's
+                           // earlier groups, keys above (low half) and equal to (high half) the threshold
+  uint2* chunk_cnt;        // [P*C] keys above and equal to the threshold per chunk
   uint2* chunk_before;     // [P*C] the same, summed over the tensor's earlier chunks
-  uint32_t* chunk_sub;     // [P*C*(SW+1)] winners before each 1024-element sweep of a chunk,
-                           // as message slots (entry 0 = the chunk's first slot)
   uint32_t* msg_idx; float* msg_val;          // [P*Ktot]
   unsigned long long* idx_hash;               // [S] fingerprints of the last step's Top-K messages (sums of
   unsigned long long* msg_hash;               // mixed indices / mixed (value, index) pairs), filled on request
@@ -119,7 +113,8 @@ struct StepArgs {
   uint32_t cached;         // the arenas fit the last-level cache: ordinary instead of streaming accesses
   uint32_t walk;           // streaming ring whose mailboxes equal the senders' xhat: update pass of kernels_walk.hip
   uint32_t part;           // walk: workers of the ring that a workgroup goes through (P: all)
-  uint32_t pull;           // whole-tensor sends are fetched by the receivers inside the update pass
+  uint32_t pull;           // sends are fetched by the receivers inside the update pass
+  uint32_t applied;        // Top-K messages are written and put into the mailboxes ahead of the update pass
   uint32_t one_launch;     // ... and the update pass also runs the trigger tests (no other kernel in the step)
   uint32_t step_no;        // one_launch: steps completed before this one (picks the copy of x to read)
   uint32_t key0, key1;
@@ -141,7 +136,7 @@ hipError_t launch_copy(const Tables& t, const StepArgs& a, uint32_t chunk_elems,
 hipError_t launch_deliver(const Tables& t, uint32_t chunk_elems, hipStream_t s);
 hipError_t launch_topk_decide(const Tables& t, const StepArgs& a, hipStream_t s);
 hipError_t launch_topk_select(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
-hipError_t launch_topk_send(const Tables& t, const StepArgs& a, hipStream_t s);
+hipError_t launch_topk_apply(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
 hipError_t launch_average(const Tables& t, float* out, hipStream_t s);
 hipError_t launch_message_hashes(const Tables& t, hipStream_t s);
 

@@ -3,26 +3,26 @@
 // ties to the lower index.  Everything here is integer work on 31-bit keys (bit
 // patterns of non-negative floats), so results are exact and repeatable.
 //
-// Only two kernels read the fired tensors themselves (x and xhat):
-//   k_topk_hist   pass A: per-chunk LDS histogram of key bits 30..20, merged into the
-//                 tensor's histogram with integer atomics; k_topk_pick<0> then finds
-//                 the bin b that holds the K-th largest key.
-//   k_topk_stage  copies every element whose bin is >= b ("staged": all possible
-//                 winners, roughly K plus one bin's worth) as (index, value) into
-//                 the chunk's staging slot in ascending index order, marks those IN bin b
-//                 (bit 31 of the index), keeps the keys of the marked ones in a list of
-//                 their own, and histograms bits 19..9 of those keys.  Entries above bin b
-//                 win whatever the exact threshold turns out to be, so their keys are dropped.
-// The rest works on the staged entries only, a small fraction of the tensor:
-//   k_topk_hist_low   bits 8..0 of the in-bin keys under the 22-bit prefix -> threshold key t
-//                     and T = how many keys equal to t are still needed
-//   k_topk_count      per chunk: staged entries above bin b + in-bin keys > t, and in-bin keys == t
-//   k_topk_chunkscan  running totals over a tensor's chunks (one wavefront per tensor)
-//   k_topk_pack       stable compaction of the winners (key > t, or key == t while fewer
-//                     than T equal keys precede it in the tensor) into the tensor's
-//                     (index, value) message, ascending indices.
-// The message is applied to xhat and to the neighbours' mailboxes by the update pass.
+// The selection ends with two numbers per tensor, the threshold key t and the last element that wins
+// with a key equal to t: element j wins if key > t, or key == t and j <= cut.  Whoever has x and xhat in
+// registers afterwards -- the update pass -- can tell the winners by itself, and where they belong
+// in the message from the number of winners before its group of 256 elements.
+//
+//   k_topk_hist     pass A where the previous update pass has not done it: histogram of key bits 30..20 per tensor
+//   k_topk_decide   trigger test, and the bin b that holds the K-th largest key (k_topk_pick: the latter alone)
+//   k_topk_stage    the one pass over the fired tensors: per group of 256 elements how many keys lie above
+//                   bin b, and the keys IN bin b (a 9 .. 12 % wide slice of the key range, some per cent of the
+//                   tensor), whose bits 19..9 it counts
+//   k_topk_low      bits 8..0 of the in-bin keys under the 22-bit prefix -> threshold key
+//   k_topk_count    keys above and equal to the threshold per group, as running totals over a chunk
+//   k_topk_scan     the same over a tensor's chunks, and the cut
+//   k_topk_apply    messages written and applied ahead of the update pass, where that pass cannot
+// (The selection used to stage every possible winner as (index, value) and to compact the messages from there;
+// the update passes then scattered three messages each into LDS.  One kernel per tensor for all that follows
+// the staging was slower than the five launches: 89 instead of 30 us for 16 ResNet-18 workers, whose largest
+// tensors have 72 000 in-bin keys.)
 #include "trigger_device.h"
+#include "message_device.h"
 
 namespace evg {
 
@@ -30,14 +30,7 @@ struct WorkItem {
   uint32_t w, r, c, seg;
   ChunkDesc cd;
   size_t base;   // arena offset of the chunk
-  size_t slot;   // where the chunk's staged entries start in the staging arrays
-  uint32_t cap;  // how many entries the slot holds
 };
-
-// A chunk whose possible winners do not fit its staging slot is marked with this count and
-// staged not at all: the kernels that would read its staged entries read the chunk's elements
-// from the arenas instead (exact all the same; it takes massive ties or a large Top-K share).
-constexpr uint32_t kNotStaged = 0xFFFFFFFFu;
 
 __device__ __forceinline__ WorkItem work_item(const Tables& T, uint32_t r, uint32_t c) {
   WorkItem it;
@@ -47,13 +40,21 @@ __device__ __forceinline__ WorkItem work_item(const Tables& T, uint32_t r, uint3
   it.cd = T.chunks[c];
   it.seg = it.r * T.L + it.cd.layer;
   it.base = (size_t)it.r * T.Npad + it.cd.off;
-  // a slot holds stage_num of every 16 elements of the chunk's range; slots of neighbouring
-  // chunks cannot overlap (floor(a/16) + floor(len/16) <= floor((a + len)/16)) and start on
-  // multiples of 4 entries (stage_num is 4, 8, 12 or 16), i.e. 16-byte aligned
-  it.slot = (size_t)it.r * T.stage_stride + (size_t)(it.cd.off >> 4) * T.stage_num;
-  it.cap = (it.cd.len >> 4) * T.stage_num;
   return it;
 }
+
+// A chunk's staged keys: a quarter of its length, at most kStageCap, at a quarter of its arena offset (slots of
+// neighbouring chunks cannot overlap: floor(a/16) + floor(len/16) <= floor((a + len)/16); 16-byte aligned).
+__device__ __forceinline__ size_t stage_slot(const Tables& T, uint32_t r, uint32_t off) {
+  return (size_t)r * T.stage_stride + (size_t)(off >> 4) * 4;
+}
+__device__ __forceinline__ uint32_t stage_cap(uint32_t len) {
+  return (len >> 4) * 4 < kStageCap ? (len >> 4) * 4 : kStageCap;
+}
+
+// A chunk with more keys in the threshold bin than its slot holds is marked with this count and staged not
+// at all: they are read from the arenas instead (exact all the same; it takes massive ties or a tiny tensor).
+constexpr uint32_t kNotStaged = 0xFFFFFFFFu;
 
 // Adds the non-empty bins of a workgroup's LDS histogram to the tensor's histogram.
 template <int NB>
@@ -89,9 +90,8 @@ __global__ __launch_bounds__(kThreads) void k_topk_hist(Tables T, StepArgs A) {
   flush_hist<kHistBins>(h, T.hist + (size_t)wi.seg * kHistBins);
 }
 
-// One workgroup per tensor that sends a Top-K message: find the bin that holds the
-// krem-th largest key, append it to the prefix, keep what is still to be taken
-// inside that bin, and clear the histogram for the next pass.
+// One workgroup per tensor that sends a Top-K message: find the bin that holds the krem-th largest key, append it to the
+// prefix, keep what is still to be taken inside that bin, and clear the histogram for the next pass.
 // PASS 0: bits 30..20, PASS 1: bits 19..9, PASS 2: bits 8..0.
 template <int PASS>
 __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t code, uint32_t* ws) {
@@ -151,170 +151,290 @@ __global__ __launch_bounds__(kThreads) void k_topk_decide(Tables T, StepArgs A) 
   if (seg == 0 && threadIdx.x == 0) close_step(T, A);
 }
 
-// Up to four sweeps (16 elements per thread) share one workgroup scan, so that more
-// loads are in flight between barriers: the four per-sweep counts travel as 16-bit
-// fields of one 64-bit word (a sweep stages at most 1024 entries).  The entries are
-// compacted in LDS and written out once per chunk.
-//
-// What is staged per chunk, both lists in ascending index order in the chunk's staging slot
-// (a share of the chunk's length; a chunk with more possible winners than that is marked and
-// left to the arena paths of the kernels below):
-//   (index | in-bin flag in bit 31, value)  for every element whose bin is >= b: all possible winners;
-//   key                                     for those of them whose bin IS b (flag set): only they
-//                                           still have to be compared with the exact threshold,
-//                                           everything above bin b wins whatever the threshold is.
-// COPY: 0 nothing to do for a tensor sent whole (it lands later, or the walk sends it), 1 its chunk goes into
-// the two mailboxes, 2 into xhat, if its worker is at the end of a part of the ring (see copy_chunk): a Top-K tensor's first send takes no launch of its own.
+// One workgroup per chunk; a wavefront's part of a sweep is a group of 256 elements.  Ballots give the
+// counts; the keys in the threshold bin are gathered in LDS, in no particular order (each carries its
+// group, in the bits above its low 20), and leave as one run.  Bound by reading x and xhat.
+// COPY: 0 nothing to do for a tensor sent whole (it lands later, or the update pass sends it), 1 its chunk goes into
+// the two mailboxes, 2 into xhat, if its worker is at the end of a part of the ring (see copy_chunk): a
+// Top-K tensor's first send takes no launch of its own.
 template <int SWEEPS, int COPY, bool STREAM>
 __global__ __launch_bounds__(kThreads) void k_topk_stage(Tables T, StepArgs A) {
-  constexpr int STEP = SWEEPS >= 4 ? 4 : SWEEPS;
-  __shared__ uint32_t h[kHistBins];
-  __shared__ uint64_t ws[8];
-  // a chunk's staged entries are gathered here and leave as whole 16-byte streaming stores
-  // (scattered 4-byte stores straight to memory measured 12 % slower for the kernel); a chunk
-  // that stages more than the buffers hold falls back to direct stores
-  constexpr uint32_t kCap = kStageCap, kCapB = kStageCapBin;
-  __shared__ __attribute__((aligned(16))) uint32_t li[kCap], lb[kCapB];
-  __shared__ __attribute__((aligned(16))) float lv[kCap];
+  constexpr int STEP = SWEEPS >= 4 ? 4 : SWEEPS;      // sweeps whose loads are in flight together
+  __shared__ __attribute__((aligned(16))) uint32_t list[kStageCap];
+  __shared__ uint32_t h[kHistBins], listed;
   const WorkItem wi = work_item(T, blockIdx.y, blockIdx.x);
   const uint32_t code = T.fired[wi.seg];      // uniform
   if (COPY && code == 1 && (COPY == 1 || is_led(T, A, wi.r))) copy_chunk<SWEEPS, STREAM, COPY == 2>(T, wi.r, wi.cd);
   if (code != 2) return;
   const uint32_t bin = T.sel_prefix[wi.seg];
+  if (threadIdx.x == 0) listed = 0;
   for (uint32_t b = threadIdx.x; b < (uint32_t)kHistBins; b += kThreads) h[b] = 0;
   __syncthreads();
-  uint32_t run = 0, runb = 0;   // staged so far: all entries, in-bin entries
-  bool direct = false;          // uniform: this chunk overflowed an LDS buffer
-  bool over = false;            // uniform: this chunk overflowed its staging slot, nothing more is staged
-  for (int it = 0; it < SWEEPS; it += STEP) {   // uniform trip count: the scan needs every thread
-    float xa[STEP][4];
-    uint32_t key[STEP][4], take[STEP], inb[STEP], e[STEP];
+#pragma unroll
+  for (int it = 0; it < SWEEPS; it += STEP) {
+    uint32_t e[STEP];
     float4 x4[STEP], h4[STEP];
 #pragma unroll
     for (int u = 0; u < STEP; ++u) {
-      e[u] = (it + u) * kSweep + threadIdx.x * kLaneElems - wi.cd.lead;
+      e[u] = (it + u) * kSweep + threadIdx.x * kLaneElems - wi.cd.lead;   // positions before the lead wrap around
       x4[u] = make_float4(0.f, 0.f, 0.f, 0.f);
       h4[u] = x4[u];
       if (e[u] < wi.cd.len) {
-        x4[u] = ld4s(T.x + wi.base + e[u]);
-        if (!A.topk_key) h4[u] = ld4s(T.xhat + wi.base + e[u]);
+        x4[u] = ld4t<STREAM>(T.x + wi.base + e[u]);
+        if (!A.topk_key) h4[u] = ld4t<STREAM>(T.xhat + wi.base + e[u]);
       }
     }
-    uint64_t mine = 0, mineb = 0;
+    uint32_t key[STEP][4], n_in[STEP], n_all = 0;
+    uint64_t in[STEP][4];
 #pragma unroll
     for (int u = 0; u < STEP; ++u) {
-      take[u] = 0;
-      inb[u] = 0;
-      xa[u][0] = x4[u].x; xa[u][1] = x4[u].y; xa[u][2] = x4[u].z; xa[u][3] = x4[u].w;
-      const float ha[4] = {h4[u].x, h4[u].y, h4[u].z, h4[u].w};
+      const float xa[4] = {x4[u].x, x4[u].y, x4[u].z, x4[u].w}, ha[4] = {h4[u].x, h4[u].y, h4[u].z, h4[u].w};
       const uint32_t nv = e[u] >= wi.cd.len ? 0u : (wi.cd.len - e[u] < 4u ? wi.cd.len - e[u] : 4u);
+      uint32_t above = 0;
+      n_in[u] = 0;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        key[u][q] = 0;
-        if ((uint32_t)q < nv) {
-          key[u][q] = rank_key(xa[u][q], ha[q], A.topk_key);
-          const uint32_t kb = key[u][q] >> 20;
-          if (kb >= bin) take[u] |= 1u << q;
-          if (kb == bin) {
-            inb[u] |= 1u << q;
-            atomicAdd(&h[(key[u][q] >> 9) & 2047u], 1u);
-          }
-        }
+        key[u][q] = rank_key(xa[q], ha[q], A.topk_key);
+        const bool valid = (uint32_t)q < nv;
+        in[u][q] = __ballot(valid && (key[u][q] >> 20) == bin);
+        above += __popcll(__ballot(valid && (key[u][q] >> 20) > bin));
+        if (valid && (key[u][q] >> 20) == bin) atomicAdd(&h[(key[u][q] >> 9) & 2047u], 1u);
+        n_in[u] += __popcll(in[u][q]);
       }
-      mine |= (uint64_t)__popc(take[u]) << (16 * u);
-      mineb |= (uint64_t)__popc(inb[u]) << (16 * u);
+      if (lane_id() == 0) T.group[(size_t)wi.w * (T.SW * 4) + (it + u) * 4 + wave_id()] = above;
+      n_all += n_in[u];
     }
-    // staged order = index order: all of sweep `it` precedes sweep `it + 1`
-    uint64_t total, totalb, ex, exb;
-    block_excl_scan64x2<4>(mine, mineb, ws, &ex, &exb, &total, &totalb);
-    uint32_t before = run, beforeb = runb;   // entries of this chunk's earlier sweeps
-    uint32_t all = 0, allb = 0;
-#pragma unroll
-    for (int u = 0; u < STEP; ++u) {
-      all += (uint32_t)((total >> (16 * u)) & 0xFFFFu);
-      allb += (uint32_t)((totalb >> (16 * u)) & 0xFFFFu);
-    }
-    if (run + all > wi.cap) over = true;      // uniform (in-bin entries are among them: they fit if these do)
-    if (over) continue;                       // only the histogram above still matters for this chunk
-    if (!direct && (run + all > kCap || runb + allb > kCapB)) {   // uniform: empty the buffers and go direct
-      __syncthreads();
-      for (uint32_t q = threadIdx.x; q < run; q += kThreads) {
-        T.stage_idx[wi.slot + q] = li[q];
-        T.stage_val[wi.slot + q] = lv[q];
-      }
-      for (uint32_t q = threadIdx.x; q < runb; q += kThreads) T.stage_key[wi.slot + q] = lb[q];
-      direct = true;
+    uint32_t at = 0;
+    if (n_all) {                                     // wave-uniform
+      if (lane_id() == 0) at = atomicAdd(&listed, n_all);
+      at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
     }
 #pragma unroll
     for (int u = 0; u < STEP; ++u) {
-      uint32_t pos = before + (uint32_t)((ex >> (16 * u)) & 0xFFFFu);
-      uint32_t posb = beforeb + (uint32_t)((exb >> (16 * u)) & 0xFFFFu);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        if ((take[u] >> q) & 1u) {
-          const uint32_t flag = (inb[u] >> q) & 1u;
-          const uint32_t jf = (wi.cd.j0 + e[u] + q) | (flag << 31);
-          if (!direct) {
-            li[pos] = jf;
-            lv[pos] = xa[u][q];
-            if (flag) lb[posb] = key[u][q];
-          } else {
-            T.stage_idx[wi.slot + pos] = jf;
-            T.stage_val[wi.slot + pos] = xa[u][q];
-            if (flag) T.stage_key[wi.slot + posb] = key[u][q];
-          }
-          ++pos;
-          posb += flag;
-        }
+        const uint32_t pos = at + lanes_below(in[u][q]);
+        if (((in[u][q] >> lane_id()) & 1ull) && pos < kStageCap)
+          list[pos] = (key[u][q] & 0xFFFFFu) | (((it + u) * 4 + wave_id()) << 20);
+        at += __popcll(in[u][q]);
       }
-      before += (uint32_t)((total >> (16 * u)) & 0xFFFFu);
-      beforeb += (uint32_t)((totalb >> (16 * u)) & 0xFFFFu);
     }
-    run = before;
-    runb = beforeb;
-  }
-  if (threadIdx.x == 0) {
-    T.stage_n[wi.w] = over ? make_uint2(kNotStaged, 0u) : make_uint2(run, runb);
-    if (over) atomicAdd(T.not_staged, 1u);     // running count, reported by evg_stats
   }
   __syncthreads();
-  if (!direct && !over) {
-    // the chunk's slot starts 16-byte aligned: whole quads stream out, the tail goes singly
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    const uint32_t quads = run / 4, quadsb = runb / 4;
-    for (uint32_t q = threadIdx.x; q < quads; q += kThreads) {
-      __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(li + 4 * q),
-                                  reinterpret_cast<u32x4*>(T.stage_idx + wi.slot) + q);
-      __builtin_nontemporal_store(*reinterpret_cast<const f32x4*>(lv + 4 * q),
-                                  reinterpret_cast<f32x4*>(T.stage_val + wi.slot) + q);
-    }
-    for (uint32_t q = threadIdx.x; q < quadsb; q += kThreads)
-      __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(lb + 4 * q),
-                                  reinterpret_cast<u32x4*>(T.stage_key + wi.slot) + q);
-    for (uint32_t q = 4 * quads + threadIdx.x; q < run; q += kThreads) {
-      T.stage_idx[wi.slot + q] = li[q];
-      T.stage_val[wi.slot + q] = lv[q];
-    }
-    for (uint32_t q = 4 * quadsb + threadIdx.x; q < runb; q += kThreads) T.stage_key[wi.slot + q] = lb[q];
-  }
-
   flush_hist<kHistBins>(h, T.hist + (size_t)wi.seg * kHistBins);
+  const uint32_t n = listed;
+  const bool over = n > stage_cap(wi.cd.len);        // uniform
+  if (threadIdx.x == 0) {
+    T.stage_n[wi.w] = over ? kNotStaged : n;
+    if (over) atomicAdd(T.not_staged, 1u);           // running count, reported by evg_stats
+  }
+  if (over) return;
+  uint32_t* slot = T.stage_key + stage_slot(T, wi.r, wi.cd.off);
+  for (uint32_t q = threadIdx.x; q < n / 4; q += kThreads)
+    *reinterpret_cast<u32x4*>(slot + 4 * q) = *reinterpret_cast<const u32x4*>(list + 4 * q);
+  for (uint32_t q = n / 4 * 4 + threadIdx.x; q < n; q += kThreads) slot[q] = list[q];
 }
 
-// The three kernels below walk a chunk's staged entries, a thousand or so, so
-// one wavefront per chunk does it without LDS or workgroup barriers: ballots give
-// counts and ranks.  Four independent wavefronts share a workgroup.
+// Rank keys of a wavefront's 256 positions of a chunk from p0 on, 64 at a time; ok: there is an element.
+__device__ __forceinline__ void keys_at(const Tables& T, const StepArgs& A, uint32_t r, const ChunkDesc& pc, uint32_t p0,
+                                        uint32_t key[4], bool ok[4]) {
+  const size_t at = (size_t)r * T.Npad + pc.off;
+  const __amdgpu_buffer_rsrc_t x = window(T.x + at, pc.len * 4), h = window(T.xhat + at, A.topk_key ? 0u : pc.len * 4);
+  float xv[4], hv[4];
+#pragma unroll
+  for (uint32_t v = 0; v < 4; ++v) {
+    const uint32_t e = p0 + 64 * v + lane_id() - pc.lead;
+    ok[v] = e < pc.len;
+    xv[v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(x, (int)(ok[v] ? e * 4 : 0xFFFFFFF0u), 0, 0));
+    hv[v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(h, (int)(ok[v] ? e * 4 : 0xFFFFFFF0u), 0, 0));
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) key[v] = rank_key(xv[v], hv[v], A.topk_key);
+}
+
+// The kernels below walk a chunk's staged keys, a few hundred, so one wavefront per chunk does it without
+// workgroup barriers.  Four independent wavefronts share a workgroup.
 
 // The chunk of this wavefront (blockIdx.y = worker); false: none, or its tensor sends no Top-K message.
 __device__ __forceinline__ bool wave_item(const Tables& T, WorkItem* wi) {
-  const uint32_t c = blockIdx.x * (kThreads / 64) + wave_id();
+  const uint32_t c = blockIdx.x * (kThreads / 64) + (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_id());
   if (c >= T.C) return false;
   *wi = work_item(T, blockIdx.y, c);
   return T.fired[wi->seg] == 2;
 }
 
-__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
-  return __popcll(mask & ((1ull << lane_id()) - 1ull));
+// f(low 20 bits and group) for every key of the chunk in the threshold bin; all(key, group) instead, for every key, where
+// nothing is staged.
+template <typename F, typename G>
+__device__ __forceinline__ void in_bin_keys(const Tables& T, const StepArgs& A, const WorkItem& wi, F&& f, G&& all) {
+  const uint32_t n = T.stage_n[wi.w];
+  if (n != kNotStaged) {                             // wave-uniform
+    const uint32_t* slot = T.stage_key + stage_slot(T, wi.r, wi.cd.off);
+    for (uint32_t q0 = 0; q0 < n; q0 += 512) {       // two loads of 4 entries per lane in flight
+      u32x4 e[2];
+#pragma unroll
+      for (uint32_t u = 0; u < 2; ++u)
+        e[u] = __builtin_amdgcn_raw_buffer_load_b128(window(slot, (n + 3) / 4 * 16), (int)((q0 + 256 * u + 4 * lane_id()) * 4), 0, 0);
+#pragma unroll
+      for (uint32_t u = 0; u < 2; ++u)
+#pragma unroll
+        for (uint32_t v = 0; v < 4; ++v) f(e[u][v], q0 + 256 * u + 4 * lane_id() + v < n);
+    }
+  } else {
+#pragma unroll 1
+    for (uint32_t p0 = 0; p0 < wi.cd.lead + wi.cd.len; p0 += 256) {
+      uint32_t k[4];
+      bool ok[4];
+      keys_at(T, A, wi.r, wi.cd, p0, k, ok);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) all(k[v], p0 >> 8, ok[v]);
+    }
+  }
+}
+
+// Bits 8..0 of the in-bin keys that carry the 22-bit prefix found so far.  Matches are
+// rare (a 2^-22 slice of the key range), so they go straight to the tensor's histogram,
+// one atomic per distinct value per 64 entries.
+__global__ __launch_bounds__(kThreads) void k_topk_low(Tables T, StepArgs A) {
+  WorkItem wi;
+  if (!wave_item(T, &wi)) return;
+  const uint32_t prefix = T.sel_prefix[wi.seg];
+  uint32_t* gh = T.hist + (size_t)wi.seg * kHistBins;
+  auto add = [&](uint32_t k9, bool pending) {
+    uint64_t todo = __ballot(pending);
+    while (todo) {                                  // uniform: every lane sees the same mask
+      const uint32_t leader = __ffsll((unsigned long long)todo) - 1;
+      const uint32_t v = __shfl(k9, leader, 64);
+      const uint64_t same = __ballot(pending && k9 == v);
+      if (lane_id() == leader) atomicAdd(&gh[v], (uint32_t)__popcll(same));
+      if ((same >> lane_id()) & 1ull) pending = false;
+      todo &= ~same;
+    }
+  };
+  in_bin_keys(T, A, wi, [&](uint32_t e, bool in) { add(e & 511u, in && ((e >> 9) & 2047u) == (prefix & 2047u)); },
+              [&](uint32_t key, uint32_t, bool in) { add(key & 511u, in && (key >> 9) == prefix); });
+}
+
+// Keys above (low half) and equal to (high half) the threshold: per group the sum over the chunk's earlier groups, and
+// the chunk's totals.
+__global__ __launch_bounds__(kThreads) void k_topk_count(Tables T, StepArgs A) {
+  __shared__ uint32_t counts[kThreads / 64][64];
+  WorkItem wi;
+  if (!wave_item(T, &wi)) return;
+  uint32_t* cnt = counts[wave_id()];
+  const uint32_t t = T.sel_prefix[wi.seg], lane = lane_id(), G = T.SW * 4;
+  uint32_t* group = T.group + (size_t)wi.w * G;
+  const uint32_t above = lane < G ? group[lane] : 0u;
+  cnt[lane] = 0;
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  bool staged = true;
+  in_bin_keys(T, A, wi,
+              [&](uint32_t e, bool in) {
+                const uint32_t k = e & 0xFFFFFu, t20 = t & 0xFFFFFu;
+                if (in && k >= t20) atomicAdd(&cnt[e >> 20], k == t20 ? 0x10000u : 1u);
+              },
+              [&](uint32_t key, uint32_t g, bool in) {
+                staged = false;
+                if (in && key >= t) atomicAdd(&cnt[g], key == t ? 0x10000u : 1u);
+              });
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  const uint32_t mine = cnt[lane] + (staged ? above : 0u), incl = wave_incl_scan(mine);
+  if (lane < G) group[lane] = incl - mine;
+  if (lane == 63) T.chunk_cnt[wi.w] = make_uint2(incl & 0xFFFFu, incl >> 16);
+}
+
+// One wavefront per Top-K tensor: running totals over its chunks, in chunk order, and the last element that wins with a key
+// equal to the threshold (ties that do not all win are common: differences of parameters that have moved little
+// are multiples of the parameters' spacing).
+__global__ __launch_bounds__(64) void k_topk_scan(Tables T, StepArgs A) {
+  const uint32_t seg = blockIdx.x, lane = threadIdx.x;
+  if (T.fired[seg] != 2) return;
+  const uint32_t r = seg / T.L, ties = T.sel_krem[seg], t = T.sel_prefix[seg], G = T.SW * 4;
+  const LayerDesc ld = T.layers[seg % T.L];
+  const uint32_t first = r * T.C + ld.chunk0;
+  uint32_t carry_g = 0, carry_e = 0, crossing = 0, need = 0;
+  for (uint32_t b = 0; b < ld.nchunks; b += 64 * 4) {
+    uint2 n[4];
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) {
+      const uint32_t i = b + 64 * u + lane;
+      n[u] = i < ld.nchunks ? T.chunk_cnt[first + i] : make_uint2(0, 0);
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) {
+      const uint32_t i = b + 64 * u + lane;
+      const uint32_t ig = wave_incl_scan(n[u].x), ie = wave_incl_scan(n[u].y);
+      const uint32_t gb = carry_g + ig - n[u].x, eb = carry_e + ie - n[u].y;
+      if (i < ld.nchunks) T.chunk_before[first + i] = make_uint2(gb, eb);
+      const uint64_t m = __ballot(eb < ties && ties <= eb + n[u].y);       // at most one chunk of the tensor
+      if (m) {
+        const int l = __ffsll((unsigned long long)m) - 1;
+        crossing = b + 64 * u + (uint32_t)l;
+        need = ties - (uint32_t)__builtin_amdgcn_readlane((int)eb, l);
+      }
+      carry_g += (uint32_t)__builtin_amdgcn_readlane((int)ig, 63);
+      carry_e += (uint32_t)__builtin_amdgcn_readlane((int)ie, 63);
+    }
+  }
+  if (carry_e == ties) {                             // all of them win
+    if (lane == 0) T.sel_cut[seg] = ld.numel - 1;
+    return;
+  }
+  // the last group that begins before the last winning tie holds it
+  const ChunkDesc cd = T.chunks[ld.chunk0 + crossing];
+  const uint32_t before = lane < G ? T.group[(size_t)(first + crossing) * G + lane] >> 16 : 0xFFFFu;
+  const uint32_t g = (uint32_t)__popcll(__ballot(before < need)) - 1;
+  uint32_t left = need - (uint32_t)__builtin_amdgcn_readlane((int)before, (int)g), k[4];
+  bool ok[4];
+  keys_at(T, A, r, cd, g * 256, k, ok);
+#pragma unroll
+  for (uint32_t v = 0; v < 4; ++v) {
+    const uint64_t m = __ballot(ok[v] && k[v] == t);
+    const uint32_t found = __popcll(m);
+    if (((m >> lane) & 1ull) && lanes_below(m) + 1 == left) T.sel_cut[seg] = cd.j0 + g * 256 + 64 * v + lane - cd.lead;
+    left = left > found ? left - found : 0u;         // 0: behind us
+  }
+}
+
+// Ahead of the update pass, one workgroup per sweep: writes the Top-K messages of this iteration and applies them
+//   LEAD: to xhat, for the workers at the ends of the parts in which a ring is walked;
+//   else: to the neighbours' mailboxes (rings whose update pass cannot tell what a neighbour sent: its xhat is
+//   reset at events, or there is no room for the copies of x it would need).
+template <int SWEEPS, bool LEAD>
+__global__ __launch_bounds__(kThreads) void k_topk_apply(Tables T, StepArgs A) {
+  const WorkItem wi = work_item(T, blockIdx.y, blockIdx.x);
+  if (T.fired[wi.seg] != 2 || (LEAD && !is_led(T, A, wi.r))) return;           // uniform
+  const LayerDesc ld = T.layers[wi.cd.layer];
+  const uint32_t t = T.sel_prefix[wi.seg], cut = T.sel_cut[wi.seg];
+  const uint32_t left = (wi.r + T.P - 1) % T.P, right = (wi.r + 1) % T.P;
+#pragma unroll
+  for (int it = 0; it < SWEEPS; ++it) {
+    const uint32_t e = it * kSweep + threadIdx.x * kLaneElems - wi.cd.lead;   // positions before the lead wrap around
+    const bool live = e < wi.cd.len;
+    float4 x4 = make_float4(0.f, 0.f, 0.f, 0.f), h4 = x4;
+    if (live) { x4 = ld4s(T.x + wi.base + e); h4 = ld4s(T.xhat + wi.base + e); }
+    const float xa[4] = {x4.x, x4.y, x4.z, x4.w};
+    float ha[4] = {h4.x, h4.y, h4.z, h4.w};
+    const uint32_t nv = !live ? 0u : wi.cd.len - e < 4u ? wi.cd.len - e : 4u;
+    const uint32_t win = winners4(xa, ha, A.topk_key, t, cut, wi.cd.j0 + e, nv);
+    put_message(T, wi.r, ld.msg_off, message_place(T, wi.w, it * 4 + wave_id(), T.sel_krem[wi.seg]), win, xa, wi.cd.j0 + e);
+    const bool changes = any_of_line_part(win) && live;
+    if (LEAD) {
+      take_winners(win, xa, ha);
+      if (changes) st4s(T.xhat + wi.base + e, make_float4(ha[0], ha[1], ha[2], ha[3]));
+    } else if (changes) {
+      float* m1 = T.mbox_r + (size_t)left * T.Npad + wi.cd.off + e;
+      float* m2 = T.mbox_l + (size_t)right * T.Npad + wi.cd.off + e;
+#pragma unroll
+      for (int side = 0; side < 2; ++side) {
+        float* m = side ? m2 : m1;
+        const float4 b = ld4s(m);
+        float ba[4] = {b.x, b.y, b.z, b.w};
+        take_winners(win, xa, ba);
+        st4s(m, make_float4(ba[0], ba[1], ba[2], ba[3]));
+      }
+    }
+  }
 }
 
 // Finaliser of the SplitMix64 generator (Steele, Lea, Flood, OOPSLA'14): used to turn a
@@ -331,188 +451,6 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
-}
-
-// Rank key and value of element q of a chunk, straight from the arenas (chunks that were not staged).
-__device__ __forceinline__ uint32_t arena_key(const Tables& T, const WorkItem& wi, uint32_t q, uint32_t by_value,
-                                              float* xv) {
-  const float x = T.x[wi.base + q];
-  const float h = by_value ? 0.0f : T.xhat[wi.base + q];
-  *xv = x;
-  return rank_key(x, h, by_value);
-}
-
-constexpr int kBatch = 8;    // 64-entry groups loaded together by a wavefront, to overlap their latency
-
-// Bits 8..0 of the in-bin keys that carry the 22-bit prefix found so far.  Matches are
-// rare (a 2^-22 slice of the key range), so they go straight to the tensor's histogram,
-// one atomic per distinct value per 64 entries.
-__global__ __launch_bounds__(kThreads) void k_topk_hist_low(Tables T, StepArgs A) {
-  WorkItem wi;
-  if (!wave_item(T, &wi)) return;
-  const uint2 sn = T.stage_n[wi.w];
-  const bool staged = sn.x != kNotStaged;             // wave-uniform
-  const uint32_t prefix = T.sel_prefix[wi.seg], ns = staged ? sn.y : wi.cd.len;
-  uint32_t* gh = T.hist + (size_t)wi.seg * kHistBins;
-  for (uint32_t q0 = 0; q0 < ns; q0 += 64 * kBatch) {
-    uint32_t key[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const uint32_t q = q0 + u * 64 + lane_id();
-      key[u] = 0xFFFFFFFFu;                           // no key has bit 31: never matches
-      float unused;
-      if (q < ns) key[u] = staged ? T.stage_key[wi.slot + q] : arena_key(T, wi, q, A.topk_key, &unused);
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      bool pending = (key[u] >> 9) == prefix;
-      uint64_t todo = __ballot(pending);
-      while (todo) {                                  // uniform: every lane sees the same mask
-        const uint32_t leader = __ffsll((unsigned long long)todo) - 1;
-        const uint32_t v = __shfl(key[u] & 511u, leader, 64);
-        const uint64_t same = __ballot(pending && (key[u] & 511u) == v);
-        if (lane_id() == leader) atomicAdd(&gh[v], (uint32_t)__popcll(same));
-        if ((same >> lane_id()) & 1ull) pending = false;
-        todo &= ~same;
-      }
-    }
-  }
-}
-
-// Per chunk: how many staged keys exceed / equal the threshold key.  Every key above
-// the threshold is staged (its bin is >= the threshold's), so these are the chunk's counts;
-// entries staged without a key lie above the threshold's bin and exceed it.
-__global__ __launch_bounds__(kThreads) void k_topk_count(Tables T, StepArgs A) {
-  WorkItem wi;
-  if (!wave_item(T, &wi)) return;
-  const uint32_t t = T.sel_prefix[wi.seg];
-  const uint2 sn = T.stage_n[wi.w];
-  const bool staged = sn.x != kNotStaged;             // wave-uniform
-  const uint32_t ns = staged ? sn.y : wi.cd.len;
-  uint32_t g = staged ? sn.x - sn.y : 0u, e = 0;
-  for (uint32_t q0 = 0; q0 < ns; q0 += 64 * kBatch) {
-    uint32_t key[kBatch];
-    bool in[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const uint32_t q = q0 + u * 64 + lane_id();
-      in[u] = q < ns;
-      key[u] = 0u;
-      float unused;
-      if (in[u]) key[u] = staged ? T.stage_key[wi.slot + q] : arena_key(T, wi, q, A.topk_key, &unused);
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      g += __popcll(__ballot(in[u] && key[u] > t));
-      e += __popcll(__ballot(in[u] && key[u] == t));
-    }
-  }
-  if (lane_id() == 0) T.chunk_cnt[wi.w] = make_uint2(g, e);
-}
-
-// One wavefront per Top-K tensor: running totals over its chunks, in chunk order.
-__global__ __launch_bounds__(64) void k_topk_chunkscan(Tables T) {
-  const uint32_t seg = blockIdx.x;
-  if (T.fired[seg] != 2) return;
-  const uint32_t r = seg / T.L;
-  const LayerDesc ld = T.layers[seg % T.L];
-  const uint32_t first = r * T.C + ld.chunk0;
-  uint32_t carry_g = 0, carry_e = 0;
-  for (uint32_t b = 0; b < ld.nchunks; b += 64) {
-    const uint32_t i = b + threadIdx.x;
-    uint2 ce = make_uint2(0, 0);
-    if (i < ld.nchunks) ce = T.chunk_cnt[first + i];
-    const uint32_t ig = wave_incl_scan(ce.x), ie = wave_incl_scan(ce.y);
-    const uint32_t gb = carry_g + ig - ce.x, eb = carry_e + ie - ce.y;
-    if (i < ld.nchunks) T.chunk_before[first + i] = make_uint2(gb, eb);
-    carry_g += __shfl(ig, 63, 64);
-    carry_e += __shfl(ie, 63, 64);
-  }
-}
-
-// Stable compaction of a chunk's winners from its staged entries into the tensor's
-// message.  Also records where each 1024-element sweep of the chunk starts in the
-// message, so that the update pass can fetch exactly its part.
-__global__ __launch_bounds__(kThreads) void k_topk_pack(Tables T, StepArgs A) {
-  WorkItem wi;
-  if (!wave_item(T, &wi)) return;
-  const uint32_t t = T.sel_prefix[wi.seg], ties = T.sel_krem[wi.seg];
-  const bool staged = T.stage_n[wi.w].x != kNotStaged;           // wave-uniform
-  const uint32_t ns = staged ? T.stage_n[wi.w].x : wi.cd.len;
-  const uint2 before = T.chunk_before[wi.w];
-  const size_t mbase = (size_t)wi.r * T.Ktot + T.layers[wi.cd.layer].msg_off;
-  uint32_t* sub = T.chunk_sub + (size_t)wi.w * (T.SW + 1);
-  const uint32_t first = before.x + (before.y < ties ? before.y : ties);   // the chunk's first slot
-  uint32_t run_g = before.x, run_e = before.y;
-  uint32_t run_b = 0;                                 // in-bin entries of this chunk met so far
-  uint32_t per_sweep[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // winners per sweep (wave-uniform)
-  for (uint32_t q0 = 0; q0 < ns; q0 += 64 * kBatch) {
-    uint32_t key[kBatch], j[kBatch];
-    float val[kBatch];
-    bool in[kBatch], flag[kBatch];
-    if (staged) {
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        const uint32_t q = q0 + u * 64 + lane_id();
-        in[u] = q < ns;
-        j[u] = in[u] ? T.stage_idx[wi.slot + q] : wi.cd.j0;
-        val[u] = in[u] ? T.stage_val[wi.slot + q] : 0.0f;   // most staged entries win: fetch with the indices
-      }
-      // an entry with the in-bin flag finds its key in the chunk's key list, at its rank among
-      // the flagged entries; the others lie above the threshold's bin (any key above t will do)
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        flag[u] = (j[u] >> 31) != 0u;
-        j[u] &= 0x7FFFFFFFu;
-        const uint64_t mf = __ballot(flag[u]);
-        key[u] = 0xFFFFFFFFu;
-        if (flag[u]) key[u] = T.stage_key[wi.slot + run_b + lanes_below(mf)];
-        run_b += __popcll(mf);
-      }
-    } else {
-      // not staged: every element of the chunk, keys recomputed from the arenas
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        const uint32_t q = q0 + u * 64 + lane_id();
-        in[u] = q < ns;
-        j[u] = wi.cd.j0 + (in[u] ? q : 0u);
-        val[u] = 0.0f;
-        key[u] = 0u;
-        if (in[u]) key[u] = arena_key(T, wi, q, A.topk_key, &val[u]);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {                // groups in index order
-      const bool isg = in[u] && key[u] > t, ise = in[u] && key[u] == t;
-      const uint64_t mg = __ballot(isg), me = __ballot(ise);
-      const uint32_t g = run_g + lanes_below(mg), eq = run_e + lanes_below(me);
-      const bool win = isg || (ise && eq < ties);
-      if (win) {
-        const uint32_t pos = g + (eq < ties ? eq : ties);
-        T.msg_idx[mbase + pos] = j[u];
-        T.msg_val[mbase + pos] = val[u];
-        if (ise && eq == ties - 1) T.sel_cut[wi.seg] = j[u];      // the last tie that wins
-      }
-      // entries ascend, so a group of 64 touches only the sweeps between its first and its last
-      // entry's (all three values below are wave-uniform)
-      const uint32_t sw = (j[u] - wi.cd.j0 + wi.cd.lead) / (uint32_t)kSweep;
-      const uint64_t mi = __ballot(in[u]);
-      const uint32_t last = mi ? 63u - (uint32_t)__builtin_clzll(mi) : 0u;
-      const uint32_t sw_lo = __shfl(sw, 0, 64), sw_hi = __shfl(sw, last, 64);
-#pragma unroll
-      for (uint32_t s2 = 0; s2 < 8; ++s2)
-        if (s2 >= sw_lo && s2 <= sw_hi) per_sweep[s2] += __popcll(__ballot(win && sw == s2));
-      run_g += __popcll(mg);
-      run_e += __popcll(me);
-    }
-  }
-  if (lane_id() == 0) {
-    uint32_t at = first;
-#pragma unroll
-    for (uint32_t s2 = 0; s2 < 8; ++s2)
-      if (s2 < T.SW) { sub[s2] = at; at += per_sweep[s2]; }
-    sub[T.SW] = at;
-  }
 }
 
 // Fingerprints of the messages of the last step, computed when asked for (evg_message_hashes):
@@ -560,13 +498,24 @@ static void select_s(const Tables& t, const StepArgs& a, hipStream_t s) {
     k_topk_hist<SWEEPS><<<g, b, 0, s>>>(t, a);
     k_topk_pick<0><<<segs, b, 0, s>>>(t);
   }
-  if (a.delay || (a.walk && a.part == t.P)) k_topk_stage<SWEEPS, 0, false><<<g, b, 0, s>>>(t, a);
-  else if (a.walk) k_topk_stage<SWEEPS, 2, true><<<g, b, 0, s>>>(t, a);
+  if (a.delay || a.pull || (a.walk && a.part == t.P)) {
+    if (a.cached) k_topk_stage<SWEEPS, 0, false><<<g, b, 0, s>>>(t, a);
+    else k_topk_stage<SWEEPS, 0, true><<<g, b, 0, s>>>(t, a);
+  } else if (a.walk) k_topk_stage<SWEEPS, 2, true><<<g, b, 0, s>>>(t, a);
   else if (a.cached) k_topk_stage<SWEEPS, 1, false><<<g, b, 0, s>>>(t, a);
   else k_topk_stage<SWEEPS, 1, true><<<g, b, 0, s>>>(t, a);
   k_topk_pick<1><<<segs, b, 0, s>>>(t);
-  k_topk_hist_low<<<gw, b, 0, s>>>(t, a);
+  k_topk_low<<<gw, b, 0, s>>>(t, a);
   k_topk_pick<2><<<segs, b, 0, s>>>(t);
+  k_topk_count<<<gw, b, 0, s>>>(t, a);
+  k_topk_scan<<<segs, dim3(64), 0, s>>>(t, a);
+}
+
+template <int SWEEPS>
+static void apply_s(const Tables& t, const StepArgs& a, hipStream_t s) {
+  const dim3 g(t.C, t.P), b(kThreads);
+  if (a.walk) k_topk_apply<SWEEPS, true><<<g, b, 0, s>>>(t, a);
+  else k_topk_apply<SWEEPS, false><<<g, b, 0, s>>>(t, a);
 }
 
 hipError_t launch_topk_select(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s) {
@@ -580,11 +529,14 @@ hipError_t launch_topk_select(const Tables& t, const StepArgs& a, uint32_t chunk
   return hipGetLastError();
 }
 
-hipError_t launch_topk_send(const Tables& t, const StepArgs& a, hipStream_t s) {
-  const dim3 gw((t.C + 3) / 4, t.P), b(kThreads);
-  k_topk_count<<<gw, b, 0, s>>>(t, a);
-  k_topk_chunkscan<<<dim3(t.S), dim3(64), 0, s>>>(t);
-  k_topk_pack<<<gw, b, 0, s>>>(t, a);
+hipError_t launch_topk_apply(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s) {
+  switch (chunk_elems / kSweep) {
+    case 1: apply_s<1>(t, a, s); break;
+    case 2: apply_s<2>(t, a, s); break;
+    case 4: apply_s<4>(t, a, s); break;
+    case 8: apply_s<8>(t, a, s); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

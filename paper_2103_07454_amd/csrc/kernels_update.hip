@@ -3,33 +3,12 @@
 // of Section 4), which also accumulates the squared drift || x - xhat ||^2 that the
 // next iteration's trigger test needs, and a stand-alone drift-norm pass.
 //
-// One workgroup (256 threads, one float4 per thread) owns one 1024-element sweep of
-// one chunk of one worker: the launch shape that streams best on MI355X; with Top-K
-// messages to apply it owns two consecutive sweeps, which halves the per-workgroup
-// cost of that work.  HBM-bound: 3 reads + 2 writes of 4 bytes per element where the
-// neighbours' last sent values are read through the L2 (SHARE below), 5 + 2 elsewhere.
-//
-// Top-K messages are applied here, where the dense arrays pass through registers
-// anyway: the sender's own message patches xhat (only the sent entries count as
-// communicated), the left and right neighbours' messages patch the two mailboxes
-// (the receiving end of the put, Section 6).  A message slice is scattered into an
-// LDS window first, so that global accesses stay 16-byte wide and coalesced, and a
-// float4 is written back only if its 64-byte group changed.
+// Streaming rings with ordinary delivery are updated by kernels_walk.hip; k_update here serves the others:
+// rings that live in the cache, delayed delivery, xhat reset at events.  One workgroup (256 threads, one
+// float4 per thread) owns one 1024-element sweep of one chunk of one worker; where the pass also builds
+// the histogram of a Top-K ring, two.
+#include "message_device.h"
 #include "trigger_device.h"
-
-// Build-time variants of the Top-K message handling, kept so that the measurements behind the
-// defaults can be repeated (EVG_EXTRA_FLAGS="-DEVG_PATCH_WINDOWS=2" python -m paper_2103_07454_amd.build):
-//   EVG_PATCH_WINDOWS  LDS windows the three messages of a workgroup are scattered into: 3 = one each
-//                      (default: one barrier pair), 2 = two used in turn, 1 = one after the other
-//                      (less LDS, more barriers; measured 1-2 % slower);
-//   EVG_UPDATE_SPW     sweeps per workgroup when messages are applied: 2 (default) or 1 (5-7 % slower).
-// Results are identical in every variant.
-#ifndef EVG_PATCH_WINDOWS
-#define EVG_PATCH_WINDOWS 3
-#endif
-#ifndef EVG_UPDATE_SPW
-#define EVG_UPDATE_SPW 2
-#endif
 
 namespace evg {
 
@@ -60,52 +39,6 @@ __global__ __launch_bounds__(kThreads) void k_norm(Tables T) {
   }
 }
 
-// One source of a sparse patch for this workgroup's window of SPW sweeps: the slice
-// of worker `src`'s message that chunk c, sweeps sub0 .. sub0+SPW-1 produced (empty if
-// `src` sent no Top-K message for this tensor in this iteration).
-struct Slice { uint32_t at; uint32_t n; };   // P*Ktot and P*C*(SW+1) fit 32 bits (checked at init)
-
-template <int SPW>
-__device__ __forceinline__ Slice message_slice(const Tables& T, uint32_t src, uint32_t layer, uint32_t c,
-                                               uint32_t sub0, uint32_t msg_off) {
-  Slice s;
-  const uint32_t w = (src * T.C + c) * (T.SW + 1) + sub0;
-  const uint32_t lo = T.chunk_sub[w], hi = T.chunk_sub[w + SPW];
-  s.at = src * T.Ktot + msg_off + lo;
-  s.n = T.fired[src * T.L + layer] == 2 ? hi - lo : 0u;
-  return s;
-}
-
-// Scatters a slice into its LDS window (values + one bit per element).
-template <int SPW>
-__device__ __forceinline__ void scatter_slice(const Tables& T, const Slice& s, uint32_t j_lo, float* pv,
-                                              uint32_t* pm) {
-  for (uint32_t q = threadIdx.x; q < s.n; q += kThreads) {
-    const uint32_t loc = T.msg_idx[s.at + q] - j_lo;
-    if (loc < (uint32_t)(SPW * kSweep)) {
-      pv[loc] = T.msg_val[s.at + q];
-      atomicOr(&pm[loc >> 5], 1u << (loc & 31u));
-    }
-  }
-}
-
-// Replaces the lanes of this thread's float4 in sweep u of the window by the window's
-// entries.  Returns the change mask of the aligned 64-byte group (4 neighbouring float4s)
-// the float4 belongs to: write-back is decided per group, because scattered 16-byte
-// writes cost far more in HBM than the few unchanged bytes a full 64-byte line carries.
-__device__ __forceinline__ uint32_t take_patch(const float* pv, const uint32_t* pm, uint32_t u, float a[4]) {
-  const uint32_t l0 = u * kSweep + threadIdx.x * kLaneElems;   // first element of the float4
-  const uint32_t g0 = l0 & ~15u;                               // first element of its 64-byte group
-  const uint32_t group = (pm[g0 >> 5] >> (g0 & 31u)) & 0xFFFFu;   // (32-byte groups measured 19 % slower)
-  const uint32_t bits = (group >> (l0 & 15u)) & 0xFu;
-  const float4 v = *reinterpret_cast<const float4*>(pv + l0);   // unwritten lanes hold garbage: masked
-  a[0] = (bits & 1u) ? v.x : a[0];
-  a[1] = (bits & 2u) ? v.y : a[1];
-  a[2] = (bits & 4u) ? v.z : a[2];
-  a[3] = (bits & 8u) ? v.w : a[3];
-  return group;
-}
-
 // Workgroup sums of SPW values at once (one barrier pair); each in the association
 // order of block_sum.  `ws` is 4 * SPW doubles of LDS.
 template <int SPW>
@@ -125,12 +58,12 @@ __device__ __forceinline__ void block_sums(const double v[SPW], double* ws, doub
 // GRADBUF: gradients come from a caller buffer.
 // NORM: what the pass accumulates for the next trigger test: 0 nothing, 1 the sweep's squared
 // drift, 2 its squared x (xhat is then not read at all), 3 its squared x and squared xhat.
-// TOPK: messages of this iteration may have to be applied.
+// TOPK: Top-K messages of this iteration: my own is told from x and xhat as they pass through the registers, written to
+// the message buffers and applied to xhat; a neighbour's (PULL) from the copy of its x and from my mailbox.
 // HISTA: also histogram the top 11 bits of the new rank keys per tensor, the first
 // radix pass of the next iteration's Top-K selection, while the values are in registers.
-// SPW: consecutive sweeps of a chunk per workgroup (one float4 per thread and sweep).  One
-// streams best; two halve the per-workgroup costs of the Top-K work (message look-up,
-// barriers, clearing and merging the histogram).
+// SPW: consecutive sweeps of a chunk per workgroup (one float4 per thread and sweep).  Two halve the cost of
+// clearing and merging the histogram.
 // STREAM: non-temporal accesses to the arenas (rings larger than the last-level cache).
 // PULL: whole-tensor sends of this iteration have NOT been copied into the mailboxes: where a
 // neighbour sent, its values are fetched from the copy of x that the previous update pass left
@@ -150,16 +83,7 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
   static_assert(!TESTS || (PULL && !TOPK && SPW == 1), "the tests ride in the pass of rings whose receivers fetch the sends");
   __shared__ double ws[4 * SPW];
   __shared__ uint32_t outcome[3];
-  // LDS: the windows of the three patches; once those are consumed the same
-  // storage holds the key histogram
-  constexpr int NWIN = EVG_PATCH_WINDOWS;
-  constexpr int kWinFloats = NWIN * SPW * kSweep > (HISTA ? kHistBins : 0) ? NWIN * SPW * kSweep : kHistBins;
-  __shared__ __attribute__((aligned(16))) float pv[TOPK ? kWinFloats : 4];
-  __shared__ uint32_t pm[3 * 32 * SPW];
-  constexpr uint32_t kWin = SPW * kSweep, kWinWords = 32 * SPW;
-  uint32_t* hA = reinterpret_cast<uint32_t*>(pv);
-  static_assert(!HISTA || TOPK, "the histogram shares the patch windows' storage");
-  static_assert(NWIN >= 1 && NWIN <= 3, "EVG_PATCH_WINDOWS is 1, 2 or 3");
+  __shared__ uint32_t hA[HISTA ? kHistBins : 1];
   const uint32_t groups = T.SW / SPW;      // workgroups per chunk (SW is a multiple of SPW)
   const uint32_t c = blockIdx.x / groups, sub0 = (blockIdx.x % groups) * SPW, r = blockIdx.y;
   const ChunkDesc cd = T.chunks[c];
@@ -167,7 +91,7 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
   bool vl = T.valid_l[seg] != 0, vr = T.valid_r[seg] != 0;
   const uint32_t lw = (r + T.P - 1) % T.P, rw = (r + 1) % T.P;
   uint32_t my_event;
-  bool from_l = false, from_r = false;
+  bool from_l = false, from_r = false, some_l = false, some_r = false;   // the neighbours sent all / some of their tensor
   if (TESTS) {
     const uint32_t segs[3] = {seg, lw * T.L + cd.layer, rw * T.L + cd.layer};
     const bool books = blockIdx.x == T.layers[cd.layer].chunk0 * groups;    // the tensor's first workgroup
@@ -195,9 +119,14 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) close_step(T, A);
   } else {
     my_event = T.fired[seg];
-    // did my neighbours send this tensor whole in this iteration? (then vl / vr are set)
-    from_l = PULL && T.fired[lw * T.L + cd.layer] == 1;
-    from_r = PULL && T.fired[rw * T.L + cd.layer] == 1;
+    // what did my neighbours send of this tensor in this iteration? (then vl / vr are set)
+    if (PULL) {
+      const uint32_t fl = T.fired[lw * T.L + cd.layer], fr = T.fired[rw * T.L + cd.layer];
+      from_l = fl == 1;
+      from_r = fr == 1;
+      some_l = TOPK && fl == 2;
+      some_r = TOPK && fr == 2;
+    }
   }
   // step n reads copy (n-1) & 1 of x and writes copy n & 1; where a kernel ahead of this one ran
   // the tests it has counted this step already
@@ -223,10 +152,32 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
   for (int u = 0; u < SPW; ++u) { acc[u] = 0.0; acc_hat[u] = 0.0; }
   if (sub0 * kSweep < cd.len + cd.lead) {        // uniform: the window holds elements
     float xa[SPW][4], va[SPW][4], la[SPW][4], ra[SPW][4], ha[SPW][4], g[SPW][4];
+    float hat_was[TOPK ? SPW : 1][4];                    // xhat before this iteration's event
+    uint32_t nv[SPW];
+    float lx[TOPK && PULL ? SPW : 1][4], rx[TOPK && PULL ? SPW : 1][4];   // the neighbours' x before this iteration's update
+    // selections of mine and the neighbours' tensors, asked for early: nobody waits for them until the arenas are there
+    uint32_t thr[3], cut[3], moff = 0, place[SPW];
+    if (TOPK) {
+      const uint32_t segs[3] = {seg, PULL ? lw * T.L + cd.layer : seg, PULL ? rw * T.L + cd.layer : seg};
+#pragma unroll
+      for (int i = 0; i < 3; ++i) { thr[i] = T.sel_prefix[segs[i]]; cut[i] = T.sel_cut[segs[i]]; }
+      moff = T.layers[cd.layer].msg_off;
+#pragma unroll
+      for (int u = 0; u < SPW; ++u) place[u] = message_place(T, r * T.C + c, (sub0 + u) * 4 + wave_id(), T.sel_krem[seg]);
+    }
+    auto receive = [&](uint32_t thr, uint32_t cut, const float (*sx)[4], float* mbox, float (*a)[4]) {
+#pragma unroll
+      for (int u = 0; u < SPW; ++u) {
+        const uint32_t win = winners4(sx[u], a[u], A.topk_key, thr, cut, cd.j0 + e[u], nv[u]);
+        take_winners(win, sx[u], a[u]);
+        if (any_of_line_part(win) && live[u]) st4t<STREAM>(mbox + base + e[u], make_float4(a[u][0], a[u][1], a[u][2], a[u][3]));
+      }
+    };
 #pragma unroll
     for (int u = 0; u < SPW; ++u) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) { xa[u][i] = 0.f; va[u][i] = 0.f; la[u][i] = 0.f; ra[u][i] = 0.f; ha[u][i] = 0.f; g[u][i] = 0.f; }
+      for (int i = 0; i < 4; ++i) { xa[u][i] = 0.f; va[u][i] = 0.f; la[u][i] = 0.f; ra[u][i] = 0.f; ha[u][i] = 0.f; g[u][i] = 0.f; if (TOPK) hat_was[u][i] = 0.f; if (TOPK && PULL) { lx[u][i] = 0.f; rx[u][i] = 0.f; } }
+      nv[u] = !live[u] ? 0u : cd.len - e[u] < 4u ? cd.len - e[u] : 4u;
       if (live[u]) {
         const float4 x4 = ld4t<STREAM>(T.x + base + e[u]);
         float4 v4 = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -243,81 +194,46 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
           ra[u][0] = t.x; ra[u][1] = t.y; ra[u][2] = t.z; ra[u][3] = t.w;
           st4t<STREAM>(T.mbox_r + base + e[u], t);
         } else if (vr) { const float4 t = ld4t<STREAM>(T.mbox_r + base + e[u]); ra[u][0] = t.x; ra[u][1] = t.y; ra[u][2] = t.z; ra[u][3] = t.w; }
+        if (TOPK && PULL) {
+          const float4 tl = ld4t<STREAM>(snap_in + (size_t)lw * T.Npad + cd.off + e[u]);
+          const float4 tr = ld4t<STREAM>(snap_in + (size_t)rw * T.Npad + cd.off + e[u]);
+          lx[u][0] = tl.x; lx[u][1] = tl.y; lx[u][2] = tl.z; lx[u][3] = tl.w;
+          rx[u][0] = tr.x; rx[u][1] = tr.y; rx[u][2] = tr.z; rx[u][3] = tr.w;
+        }
+        if (TOPK && my_event == 2) {
+          const float4 t = ld4t<STREAM>(T.xhat + base + e[u]);
+          hat_was[u][0] = t.x; hat_was[u][1] = t.y; hat_was[u][2] = t.z; hat_was[u][3] = t.w;
+        }
         if (sent_whole) {
           // the whole tensor was sent in this iteration: xhat becomes the x just read
           ha[u][0] = xa[u][0]; ha[u][1] = xa[u][1]; ha[u][2] = xa[u][2]; ha[u][3] = xa[u][3];
           st4t<STREAM>(T.xhat + base + e[u], x4);
-        } else if (NORM == 1 || NORM == 3 || TOPK) {
+        } else if (TOPK && my_event == 2) {
+          ha[u][0] = hat_was[u][0]; ha[u][1] = hat_was[u][1]; ha[u][2] = hat_was[u][2]; ha[u][3] = hat_was[u][3];
+        } else if (NORM == 1 || NORM == 3) {
           const float4 t = ld4t<STREAM>(T.xhat + base + e[u]); ha[u][0] = t.x; ha[u][1] = t.y; ha[u][2] = t.z; ha[u][3] = t.w;
         }
         if (GRADBUF) { const float4 t = ld4t<STREAM>(A.grad + base + e[u]); g[u][0] = t.x; g[u][1] = t.y; g[u][2] = t.z; g[u][3] = t.w; }
       }
     }
     if (TOPK) {
-      // three sparse patches of this iteration: my own message (what xhat must now
-      // hold) and the two messages that arrive in my mailboxes
-      const uint32_t left = (r + T.P - 1) % T.P, right = (r + 1) % T.P;
-      const uint32_t moff = T.layers[cd.layer].msg_off, j_lo = cd.j0 + sub0 * kSweep - cd.lead;
-      const Slice s0m = message_slice<SPW>(T, r, cd.layer, c, sub0, moff);
-      Slice s1 = message_slice<SPW>(T, left, cd.layer, c, sub0, moff);
-      Slice s2 = message_slice<SPW>(T, right, cd.layer, c, sub0, moff);
-      Slice s0 = s0m;
-      if (sent_whole) s0.n = 0;              // xhat has just been written from registers
-      if (A.delay) { s1.n = 0; s2.n = 0; }   // the neighbours' messages land after this pass
-      if (s0.n | s1.n | s2.n) {          // uniform
-        for (uint32_t q = threadIdx.x; q < 3 * kWinWords; q += kThreads) pm[q] = 0;
-        __syncthreads();
-        // applies window w (values) / mask m to array a of every sweep and writes changed groups back
-        auto apply = [&](const float* w, const uint32_t* m, float (*a)[4], float* arena) {
+      // my own message: it is told from x and xhat, written, and applied to xhat
+      if (my_event == 2) {                   // uniform
 #pragma unroll
-          for (int u = 0; u < SPW; ++u) {
-            const uint32_t b = take_patch(w, m, u, a[u]);
-            if (live[u] && b) st4t<STREAM>(arena + base + e[u], make_float4(a[u][0], a[u][1], a[u][2], a[u][3]));
-          }
-        };
-        if (NWIN == 3) {
-          scatter_slice<SPW>(T, s0, j_lo, pv, pm);
-          scatter_slice<SPW>(T, s1, j_lo, pv + kWin, pm + kWinWords);
-          scatter_slice<SPW>(T, s2, j_lo, pv + 2 * kWin, pm + 2 * kWinWords);
-          __syncthreads();
-          apply(pv, pm, ha, T.xhat);
-          apply(pv + kWin, pm + kWinWords, la, T.mbox_l);
-          apply(pv + 2 * kWin, pm + 2 * kWinWords, ra, T.mbox_r);
-        } else if (NWIN == 2) {
-          // two windows in turn: while one is read the next message is scattered into the other
-          scatter_slice<SPW>(T, s0, j_lo, pv, pm);
-          __syncthreads();
-          scatter_slice<SPW>(T, s1, j_lo, pv + kWin, pm + kWinWords);
-          apply(pv, pm, ha, T.xhat);
-          __syncthreads();
-          scatter_slice<SPW>(T, s2, j_lo, pv, pm + 2 * kWinWords);
-          apply(pv + kWin, pm + kWinWords, la, T.mbox_l);
-          __syncthreads();
-          apply(pv, pm + 2 * kWinWords, ra, T.mbox_r);
-        } else {
-          // one window, the three messages one after the other (empty ones skipped: uniform)
-          if (s0.n) {
-            scatter_slice<SPW>(T, s0, j_lo, pv, pm);
-            __syncthreads();
-            apply(pv, pm, ha, T.xhat);
-            __syncthreads();
-          }
-          if (s1.n) {
-            scatter_slice<SPW>(T, s1, j_lo, pv, pm + kWinWords);
-            __syncthreads();
-            apply(pv, pm + kWinWords, la, T.mbox_l);
-            __syncthreads();
-          }
-          if (s2.n) {
-            scatter_slice<SPW>(T, s2, j_lo, pv, pm + 2 * kWinWords);
-            __syncthreads();
-            apply(pv, pm + 2 * kWinWords, ra, T.mbox_r);
+        for (int u = 0; u < SPW; ++u) {
+          const uint32_t win = winners4(xa[u], hat_was[u], A.topk_key, thr[0], cut[0], cd.j0 + e[u], nv[u]);
+          if (!A.applied) put_message(T, r, moff, place[u], win, xa[u], cd.j0 + e[u]);
+          if (!sent_whole) {
+            take_winners(win, xa[u], ha[u]);
+            if (any_of_line_part(win) && live[u]) st4t<STREAM>(T.xhat + base + e[u], make_float4(ha[u][0], ha[u][1], ha[u][2], ha[u][3]));
           }
         }
       }
+      // the neighbours': told from the copies of their x and from my mailboxes, which hold their xhat
+      if (PULL && some_l) receive(thr[1], cut[1], lx, T.mbox_l, la);
+      if (PULL && some_r) receive(thr[2], cut[2], rx, T.mbox_r, ra);
     }
     if (HISTA) {
-      __syncthreads();                 // patches consumed by every thread
       for (uint32_t b = threadIdx.x; b < (uint32_t)kHistBins; b += kThreads) hA[b] = 0;
       __syncthreads();
     }
@@ -328,10 +244,9 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
           const float sg = (float)(T.layers[cd.layer].sig_base * step_decay(T, A));
           draw_gradient<DIST>(A, cd.j0 + e[u], cd.layer, k_iter, r, sg, has_spike(A, k_iter, r), g[u]);
         }
-        const uint32_t nv = cd.len - e[u] < 4u ? cd.len - e[u] : 4u;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          if ((uint32_t)i < nv) {   // lanes past the tensor's end are padding: left as they are
+          if ((uint32_t)i < nv[u]) {   // lanes past the tensor's end are padding: left as they are
             // momentum 0 is the paper's plain SGD: the velocity is the gradient, and the
             // velocity arena is neither read nor written
             const float vn = A.plain_sgd ? g[u][i] : __builtin_fmaf(A.mu, va[u][i], g[u][i]);
@@ -344,13 +259,13 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
         st4t<STREAM>(T.x + base + e[u], make_float4(xa[u][0], xa[u][1], xa[u][2], xa[u][3]));
         if (PULL) st4t<STREAM>(snap_out + base + e[u], make_float4(xa[u][0], xa[u][1], xa[u][2], xa[u][3]));
         if (!A.plain_sgd) st4t<STREAM>(T.vel + base + e[u], make_float4(va[u][0], va[u][1], va[u][2], va[u][3]));
-        if (NORM == 1) drift_acc(acc[u], xa[u], ha[u], nv);
-        if (NORM >= 2) square_acc(acc[u], xa[u], nv);
-        if (NORM == 3) square_acc(acc_hat[u], ha[u], nv);
+        if (NORM == 1) drift_acc(acc[u], xa[u], ha[u], nv[u]);
+        if (NORM >= 2) square_acc(acc[u], xa[u], nv[u]);
+        if (NORM == 3) square_acc(acc_hat[u], ha[u], nv[u]);
         if (HISTA) {
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            if ((uint32_t)i < nv) atomicAdd(&hA[rank_key(xa[u][i], ha[u][i], A.topk_key) >> 20], 1u);
+            if ((uint32_t)i < nv[u]) atomicAdd(&hA[rank_key(xa[u][i], ha[u][i], A.topk_key) >> 20], 1u);
         }
       }
     }
@@ -405,18 +320,18 @@ template <int NORM, bool TOPK, bool HISTA, int SPW>
 static void launch_update_w(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t grad_mode,
                             hipStream_t s) {
   const dim3 grid(t.C * (t.SW / SPW), t.P), block(kThreads);
-  if (!TOPK && a.pull) {     // the host sets pull only for cache-resident rings with whole-tensor sends
-    constexpr bool NT = false, NH = false;
-    if (a.one_launch) {      // ... and one_launch only where the pass accumulates the norms (NORM != 0)
-      constexpr bool TS = NORM != 0;
-      if (grad_mode == 1) k_update<0, true, NORM, NT, NH, 1, false, true, TS><<<grid, block, 0, s>>>(t, a);
-      else if (dist == 0) k_update<0, false, NORM, NT, NH, 1, false, true, TS><<<grid, block, 0, s>>>(t, a);
-      else k_update<1, false, NORM, NT, NH, 1, false, true, TS><<<grid, block, 0, s>>>(t, a);
+  if (a.pull) {              // the host sets pull only for cache-resident rings
+    if (!TOPK && a.one_launch) {      // ... and one_launch only where the pass accumulates the norms (NORM != 0)
+      constexpr bool TS = !TOPK && NORM != 0;
+      constexpr int S1 = TOPK ? SPW : 1;
+      if (grad_mode == 1) k_update<0, true, NORM, TOPK, HISTA, S1, false, true, TS><<<grid, block, 0, s>>>(t, a);
+      else if (dist == 0) k_update<0, false, NORM, TOPK, HISTA, S1, false, true, TS><<<grid, block, 0, s>>>(t, a);
+      else k_update<1, false, NORM, TOPK, HISTA, S1, false, true, TS><<<grid, block, 0, s>>>(t, a);
       return;
     }
-    if (grad_mode == 1) k_update<0, true, NORM, NT, NH, 1, false, true><<<grid, block, 0, s>>>(t, a);
-    else if (dist == 0) k_update<0, false, NORM, NT, NH, 1, false, true><<<grid, block, 0, s>>>(t, a);
-    else k_update<1, false, NORM, NT, NH, 1, false, true><<<grid, block, 0, s>>>(t, a);
+    if (grad_mode == 1) k_update<0, true, NORM, TOPK, HISTA, SPW, false, true><<<grid, block, 0, s>>>(t, a);
+    else if (dist == 0) k_update<0, false, NORM, TOPK, HISTA, SPW, false, true><<<grid, block, 0, s>>>(t, a);
+    else k_update<1, false, NORM, TOPK, HISTA, SPW, false, true><<<grid, block, 0, s>>>(t, a);
     return;
   }
   if (a.cached) {
@@ -436,7 +351,7 @@ static void launch_update_v(const Tables& t, const StepArgs& a, uint32_t dist, u
   // two sweeps per workgroup where the pass carries the Top-K extras and a chunk has them
   // (measured: four are slower again, LDS and registers then hold occupancy down)
   if (TOPK && HISTA && t.SW % 2 == 0)
-    launch_update_w<NORM, TOPK, HISTA, (TOPK && HISTA) ? EVG_UPDATE_SPW : 1>(t, a, dist, grad_mode, s);
+    launch_update_w<NORM, TOPK, HISTA, (TOPK && HISTA) ? 2 : 1>(t, a, dist, grad_mode, s);
   else
     launch_update_w<NORM, TOPK, HISTA, 1>(t, a, dist, grad_mode, s);
 }

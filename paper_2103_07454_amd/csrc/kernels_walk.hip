@@ -1,29 +1,14 @@
 // The update pass of rings that stream from memory (same work and results as k_update): one
 // workgroup owns a window of one tensor and walks it around the whole ring, worker by worker.
+#include "message_device.h"
 #include "trigger_device.h"
 
 namespace evg {
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// A window of one worker's slice as a buffer of `bytes` bytes: lanes past them read zeros and write
-// nothing, so a window's ragged end, an array that is not wanted in this iteration (bytes = 0) and a
-// lane that has nothing to write all take the same instructions, without a branch around a memory access.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t window(const float* at, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(at), 0, (int)bytes, 0x00027000);
-}
 constexpr int kNt = 2;                        // non-temporal: every line is touched once
 constexpr uint32_t kNowhere = 0xFFFFFFF0u;    // an offset past every window
 
 struct Quad { float v[4]; };
-
-// Is `any` set in one of the four lanes whose float4s make up an aligned 64 bytes?  Those are written
-// together: scattered 16-byte writes cost far more in HBM than the unchanged bytes.
-__device__ __forceinline__ bool any_of_line_part(uint32_t any) {
-  any |= (uint32_t)__builtin_amdgcn_mov_dpp((int)any, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
-  any |= (uint32_t)__builtin_amdgcn_mov_dpp((int)any, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
-  return any != 0;
-}
 
 __device__ __forceinline__ Quad load_quad(const float* at, uint32_t bytes, uint32_t byte) {
   const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(window(at, bytes), (int)byte, 0, kNt);
@@ -78,7 +63,8 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
 }
 
 // What the walk has to know of a worker; lane i of a wavefront holds the i-th worker's.
-struct Marks { uint32_t f, thr, cut; };   // f: see below; Top-K: the threshold key, and the last element that wins a tie
+struct Marks { uint32_t f, thr, cut, place; };   // f: see below; Top-K: threshold key, last element that wins a tie, place in
+                                                 // the message of the first winner of this wavefront's group
 constexpr uint32_t kCode = 3u, kLeftFilled = 4u, kRightFilled = 8u, kSpike = 16u, kLed = 32u;
 
 template <int DIST, bool GRADBUF, int NORM, bool TOPK, bool HISTA, int W>
@@ -105,18 +91,23 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
   const float third = 0.333333343f;   // (float)(1/3): the ring's mixing weight
   const float sg = GRADBUF ? 0.0f : (float)(T.layers[layer].sig_base * step_decay(T, A));
   const uint32_t nb_vel = A.plain_sgd ? 0u : nb;
+  const uint32_t msg_off = TOPK ? T.layers[layer].msg_off : 0u;
   auto at = [&](float* arena, uint32_t s) { return arena + (size_t)s * T.Npad + off; };
   auto worker = [&](uint32_t i) { return r0 + i < P ? r0 + i : r0 + i - P; };   // i <= n
 
   // the i-th worker of the part, i = n: the one after it
   auto marks_of = [&](uint32_t i) {
-    Marks m{0u, 0xFFFFFFFFu, 0u};
+    Marks m{0u, 0xFFFFFFFFu, 0u, 0u};
     if (i <= n) {
       const uint32_t s = worker(i), seg = s * T.L + layer, code = T.fired[seg];
       m.f = code | (T.valid_l[seg] ? kLeftFilled : 0u) | (T.valid_r[seg] ? kRightFilled : 0u);
       if (!GRADBUF && has_spike(A, k_iter, s)) m.f |= kSpike;
       if (is_led(T, A, s)) m.f |= kLed;
-      else if (TOPK && code == 2) { m.thr = T.sel_prefix[seg]; m.cut = T.sel_cut[seg]; }
+      else if (TOPK && code == 2) {
+        m.thr = T.sel_prefix[seg];
+        m.cut = T.sel_cut[seg];
+        m.place = message_place(T, s * T.C + c, sub0 * 4 + wave_id(), T.sel_krem[seg]);
+      }
     }
     return m;
   };
@@ -129,21 +120,18 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
 
   // What worker s's neighbours hold of it from this iteration on, written to its xhat (to_hat bytes) and its
   // neighbours' mailboxes (to_right, to_left bytes) if it sends.
-  auto send = [&](uint32_t s, uint32_t f, uint32_t thr, uint32_t cut, uint32_t to_hat, uint32_t to_left, uint32_t to_right,
+  auto send = [&](uint32_t s, uint32_t f, uint32_t thr, uint32_t cut, uint32_t place, uint32_t to_hat, uint32_t to_left, uint32_t to_right,
                   const Quad& x, const Quad& h) {
     Quad q;
     uint32_t where = byte;
     const bool led = (f & kLed) != 0, whole = (f & kCode) == 1 && !led;
     if (TOPK) {
-      uint32_t any = 0;
+      // (workers at the ends of parts: k_topk_apply has done all this but the mailboxes)
+      const uint32_t win = winners4(x.v, h.v, A.topk_key, thr, cut, j, nv);
+      if (to_hat) put_message(T, s, msg_off, place, win, x.v, j);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint32_t key = rank_key(x.v[i], h.v[i], A.topk_key);
-        const bool win = key > thr || (key == thr && j + i <= cut);
-        q.v[i] = whole || win ? x.v[i] : h.v[i];
-        any |= win ? 1u : 0u;
-      }
-      if (!whole && !led && !any_of_line_part(any)) where = kNowhere;
+      for (int i = 0; i < 4; ++i) q.v[i] = whole || ((win >> i) & 1u) ? x.v[i] : h.v[i];
+      if (!whole && !led && !any_of_line_part(win)) where = kNowhere;
     } else {
 #pragma unroll
       for (int i = 0; i < 4; ++i) q.v[i] = whole ? x.v[i] : h.v[i];
@@ -181,17 +169,18 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
     const uint32_t seg_b = before * T.L + layer;
     uint32_t f_b = __builtin_amdgcn_readfirstlane((int)T.fired[seg_b]);
     if (is_led(T, A, before)) f_b |= kLed;
-    uint32_t thr_b = 0xFFFFFFFFu, cut_b = 0u;
+    uint32_t thr_b = 0xFFFFFFFFu, cut_b = 0u, place_b = 0u;
     if (TOPK && f_b == 2) {
       thr_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)T.sel_prefix[seg_b]);
       cut_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)T.sel_cut[seg_b]);
+      place_b = message_place(T, before * T.C + c, sub0 * 4 + wave_id(), T.sel_krem[seg_b]);
     }
     const uint32_t f0 = read_mark(cur.f, nxt.f, 0);
     const Quad h_last = load_quad(at(T.xhat, before), reads_hat(f_b) ? nb : 0u, byte);
     const Quad h0 = load_quad(at(T.xhat, r0), reads_hat(f0) ? nb : 0u, byte);
     h1 = load_quad(at(T.xhat, worker(1)), 1 <= last_h && reads_hat(read_mark(cur.f, nxt.f, 1)) ? nb : 0u, byte);
-    e_last = send(before, f_b, thr_b, cut_b, closed ? nb : 0u, closed ? nb : 0u, nb, x_last, h_last);
-    e_first = send(r0, f0, read_mark(cur.thr, nxt.thr, 0), read_mark(cur.cut, nxt.cut, 0), nb, closed ? nb : 0u,
+    e_last = send(before, f_b, thr_b, cut_b, place_b, closed ? nb : 0u, closed ? nb : 0u, nb, x_last, h_last);
+    e_first = send(r0, f0, read_mark(cur.thr, nxt.thr, 0), read_mark(cur.cut, nxt.cut, 0), read_mark(cur.place, nxt.place, 0), nb, closed ? nb : 0u,
                    closed || n > 1 ? nb : 0u, xc, h0);
     el = e_last;
     ec = e_first;
@@ -215,7 +204,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
       v1 = load_quad(at(T.vel, another ? r + 1 : 0), another ? nb_vel : 0u, byte);
       if (GRADBUF) g1 = load_quad(A.grad + (size_t)(another ? r + 1 : 0) * T.Npad + off, another ? nb : 0u, byte);
       Quad en = send(s1, fn, read_mark(cur.thr, nxt.thr, i + 1), read_mark(cur.cut, nxt.cut, i + 1),
-                     i + 1 <= last_x ? nb : 0u, i + 1 <= last_h ? nb : 0u, i + 1 <= last_x && (closed || i + 2 < n) ? nb : 0u,
+                     read_mark(cur.place, nxt.place, i + 1), i + 1 <= last_x ? nb : 0u, i + 1 <= last_h ? nb : 0u, i + 1 <= last_x && (closed || i + 2 < n) ? nb : 0u,
                      xn, hn);
       if (closed && i + 1 > last_x) {
         en = i + 1 == n ? e_first : e_last;
@@ -295,32 +284,6 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
   }
 }
 
-// A ring walked in parts: the Top-K messages of the workers at the ends of parts go into their xhat ahead
-// of the walk, where both parts then find what they sent (whole tensors: copy_chunk).
-__global__ __launch_bounds__(kThreads) void k_lead(Tables T, StepArgs A) {
-  const uint32_t c = blockIdx.x / T.SW, sub = blockIdx.x % T.SW, r = blockIdx.y;
-  const ChunkDesc cd = T.chunks[c];
-  const uint32_t seg = r * T.L + cd.layer;
-  if (!is_led(T, A, r) || T.fired[seg] != 2) return;           // uniform
-  const uint32_t e = sub * kSweep + threadIdx.x * kLaneElems - cd.lead;   // positions before the lead wrap around
-  const bool live = e < cd.len;
-  float* at = T.xhat + (size_t)r * T.Npad + cd.off + e;
-  float4 x4 = make_float4(0.f, 0.f, 0.f, 0.f), h4 = x4;
-  if (live) { x4 = ld4s(T.x + (size_t)r * T.Npad + cd.off + e); h4 = ld4s(at); }
-  const uint32_t thr = T.sel_prefix[seg], cut = T.sel_cut[seg];
-  const float xa[4] = {x4.x, x4.y, x4.z, x4.w};
-  float ha[4] = {h4.x, h4.y, h4.z, h4.w};
-  uint32_t any = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint32_t key = rank_key(xa[i], ha[i], A.topk_key);
-    const bool win = key > thr || (key == thr && cd.j0 + e + i <= cut);
-    ha[i] = win ? xa[i] : ha[i];
-    any |= win ? 1u : 0u;
-  }
-  if (live && any_of_line_part(any)) st4s(at, make_float4(ha[0], ha[1], ha[2], ha[3]));
-}
-
 template <int NORM, bool TOPK, bool HISTA, int W>
 static void walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t grad_mode, hipStream_t s) {
   const dim3 grid(t.C * (t.SW / (W / 4)), (t.P + a.part - 1) / a.part), block(64 * W);
@@ -331,7 +294,6 @@ static void walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t gra
 
 hipError_t launch_walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t grad_mode, int norm, hipStream_t s) {
   if (a.topk_on) {
-    if (a.part < t.P) k_lead<<<dim3(t.C * t.SW, t.P), dim3(kThreads), 0, s>>>(t, a);
     // eight wavefronts share a histogram where chunks are long enough
     const bool wide = t.SW % 2 == 0;
     if (norm == 0) walk<0, true, false, 4>(t, a, dist, grad_mode, s);

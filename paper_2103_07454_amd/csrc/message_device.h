@@ -1,0 +1,69 @@
+// Who wins in a Top-K selection, told from x, xhat and the selection's outcome, and where a winner belongs in
+// the message.
+#pragma once
+#include "evg_device.h"
+
+namespace evg {
+
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// One bit per element of a float4, the first of them element j of the tensor.  thr = 0xFFFFFFFF: none
+// (keys have 31 bits).  nv: how many of the four are elements of the tensor.
+__device__ __forceinline__ uint32_t winners4(const float x[4], const float h[4], uint32_t by_value, uint32_t thr,
+                                             uint32_t cut, uint32_t j, uint32_t nv) {
+  uint32_t win = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t key = rank_key(x[i], h[i], by_value);
+    win |= key > thr || (key == thr && j + i <= cut) ? 1u << i : 0u;
+  }
+  return win & ((1u << nv) - 1u);
+}
+
+__device__ __forceinline__ void take_winners(uint32_t win, const float x[4], float h[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) h[i] = (win >> i) & 1u ? x[i] : h[i];
+}
+
+// Is `any` non-zero in one of the four lanes whose float4s make up an aligned 64 bytes?  Those are written
+// together: scattered 16-byte writes cost far more in HBM than the unchanged bytes (128 bytes: 3 % slower
+// where 10 % is sent, 2 % faster at 1 %).
+__device__ __forceinline__ bool any_of_line_part(uint32_t any) {
+  any |= (uint32_t)__builtin_amdgcn_mov_dpp((int)any, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
+  any |= (uint32_t)__builtin_amdgcn_mov_dpp((int)any, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+  return any != 0;
+}
+
+// Winners of the tensor before a group of 256 elements (chunk w of all workers' chunks, group g of the chunk; ties: how
+// many keys equal to the threshold win).
+__device__ __forceinline__ uint32_t message_place(const Tables& T, uint32_t w, uint32_t g, uint32_t ties) {
+  const uint2 before = T.chunk_before[w];
+  const uint32_t in_chunk = T.group[(size_t)w * (T.SW * 4) + g], equal = before.y + (in_chunk >> 16);
+  return before.x + (in_chunk & 0xFFFFu) + (equal < ties ? equal : ties);
+}
+
+// Writes the winners of a wavefront's group to their places in worker r's message, ascending indices.
+__device__ __forceinline__ void put_message(const Tables& T, uint32_t r, uint32_t msg_off, uint32_t place, uint32_t win,
+                                            const float x[4], uint32_t j) {
+  uint64_t m[4];
+  uint32_t pos = place;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    m[i] = __ballot((win >> i) & 1u);
+    pos += lanes_below(m[i]);
+  }
+  if ((m[0] | m[1] | m[2] | m[3]) == 0) return;       // wave-uniform
+  const size_t base = (size_t)r * T.Ktot + msg_off;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if ((win >> i) & 1u) {
+      T.msg_idx[base + pos] = j + i;
+      T.msg_val[base + pos] = x[i];
+      ++pos;
+    }
+  }
+}
+
+}  // namespace evg
