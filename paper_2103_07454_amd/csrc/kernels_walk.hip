@@ -73,7 +73,13 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
   __shared__ double ws[NORM ? 64 * W : 1], ws_hat[NORM == 3 ? 64 * W : 1];
   __shared__ __attribute__((aligned(16))) uint32_t hist[HISTA ? 2 * kHistBins + 4 : 4];
   const uint32_t groups = T.SW / SPW;
-  const uint32_t c = blockIdx.x / groups, sub0 = (blockIdx.x % groups) * SPW;
+  // Workgroups go to the eight XCDs in turn by their number.  Where the pass counts keys, each XCD takes a contiguous
+  // eighth of the windows, so that the counts of a tensor are added in one L2 (8 ResNet-50 workers 1019 -> 944 us;
+  // without that work consecutive windows are better left in turn, 1249 against 1300 us).
+  const uint32_t all = T.C * groups, each = (all + 7) / 8;
+  const uint32_t window_no = HISTA ? (blockIdx.x & 7u) * each + (blockIdx.x >> 3) : blockIdx.x;
+  if (window_no >= all || (HISTA && (blockIdx.x >> 3) >= each)) return;         // uniform
+  const uint32_t c = window_no / groups, sub0 = (window_no % groups) * SPW;
   const ChunkDesc cd = T.chunks[c];
   if (sub0 * kSweep >= cd.len + cd.lead) return;                   // uniform (its sums are zero for good)
   const uint32_t P = T.P, layer = cd.layer, k_iter = step_k(T, A);
@@ -185,6 +191,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
     el = e_last;
     ec = e_first;
   }
+  uint32_t f = read_mark(cur.f, nxt.f, 0), fn = read_mark(cur.f, nxt.f, 1);     // the marks of workers i and i + 1
   for (uint32_t i = 0; i < n; ++i) {
     const uint32_t r = r0 + i;
     if (i == base + 64) {
@@ -195,7 +202,6 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
     if (!dead) {
       // the next worker's values have arrived: take them, and ask for those of the one after it
       Quad xn = taken(x1), hn = taken(h1), vel = taken(v1), g = GRADBUF ? taken(g1) : g1;
-      const uint32_t f = read_mark(cur.f, nxt.f, i), fn = read_mark(cur.f, nxt.f, i + 1);
       const uint32_t f2 = read_mark(cur.f, nxt.f, i + 2);
       const uint32_t s1 = worker(i + 1), s2 = i + 2 <= n ? worker(i + 2) : 0u;
       const bool another = i + 1 < n;
@@ -250,6 +256,8 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
       el = ec;
       ec = en;
       xc = xn;
+      f = fn;
+      fn = f2;
     }
     if (HISTA) {
       // two histograms in turn: this barrier ends worker r's counting, and the clearing of the other one
@@ -286,7 +294,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
 
 template <int NORM, bool TOPK, bool HISTA, int W>
 static void walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t grad_mode, hipStream_t s) {
-  const dim3 grid(t.C * (t.SW / (W / 4)), (t.P + a.part - 1) / a.part), block(64 * W);
+  const dim3 grid((t.C * (t.SW / (W / 4)) + 7) / 8 * 8, (t.P + a.part - 1) / a.part), block(64 * W);
   if (grad_mode == 1) k_update_walk<0, true, NORM, TOPK, HISTA, W><<<grid, block, 0, s>>>(t, a);
   else if (dist == 0) k_update_walk<0, false, NORM, TOPK, HISTA, W><<<grid, block, 0, s>>>(t, a);
   else k_update_walk<1, false, NORM, TOPK, HISTA, W><<<grid, block, 0, s>>>(t, a);

@@ -44,25 +44,28 @@ __device__ __forceinline__ uint32_t message_place(const Tables& T, uint32_t w, u
   return before.x + (in_chunk & 0xFFFFu) + (equal < ties ? equal : ties);
 }
 
-// Writes the winners of a wavefront's group to their places in worker r's message, ascending indices.
+// Writes the winners of a wavefront's group to their places in worker r's message, ascending indices: `place` is the first
+// one's (the same in all lanes).  The stretch that they fill is a buffer of just their number, past which the
+// other lanes' stores fall.
 __device__ __forceinline__ void put_message(const Tables& T, uint32_t r, uint32_t msg_off, uint32_t place, uint32_t win,
                                             const float x[4], uint32_t j) {
-  uint64_t m[4];
-  uint32_t pos = place;
+  uint32_t n = 0, rank = 0;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    m[i] = __ballot((win >> i) & 1u);
-    pos += lanes_below(m[i]);
+    const uint64_t m = __ballot((win >> i) & 1u);
+    n += (uint32_t)__popcll(m);
+    rank += lanes_below(m);
   }
-  if ((m[0] | m[1] | m[2] | m[3]) == 0) return;       // wave-uniform
-  const size_t base = (size_t)r * T.Ktot + msg_off;
+  if (n == 0) return;                                 // wave-uniform
+  const size_t at = (size_t)r * T.Ktot + msg_off + (uint32_t)__builtin_amdgcn_readfirstlane((int)place);
+  const __amdgpu_buffer_rsrc_t idx = window(T.msg_idx + at, n * 4), val = window(T.msg_val + at, n * 4);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    if ((win >> i) & 1u) {
-      T.msg_idx[base + pos] = j + i;
-      T.msg_val[base + pos] = x[i];
-      ++pos;
-    }
+    const bool w = (win >> i) & 1u;
+    const int byte = (int)(w ? rank * 4 : 0xFFFFFFF0u);
+    __builtin_amdgcn_raw_buffer_store_b32(j + i, idx, byte, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[i]), val, byte, 0, 0);
+    rank += w ? 1u : 0u;
   }
 }
 
