@@ -660,7 +660,6 @@ static evg_status enqueue_step(evg_ctx* c, const StepArgs& args, bool timed) {
     t.partials_out = c->second.partials;
     t.xhat_sq_out = c->second.xhat_sq; t.delta_out = c->second.delta; t.last_event_out = c->second.last_event;
   }
-  if (a.from_device) HIP_TRY(launch_begin(t, c->stream));
   if (!fused) {
     Phase ph(c, EVG_PH_NORM);
     HIP_TRY(launch_norm(t, norm_diff, c->stream));

@@ -37,7 +37,7 @@ struct LayerDesc {
 // The iteration as the device knows it.  evg_step passes the iteration by value; a step
 // that must be replayable from a captured graph (evg_step_next) reads it from here instead.
 struct IterState {
-  uint32_t k;          // iteration of the step in flight (set by k_begin in replayable steps)
+  uint32_t k;          // iteration of the step in flight (set with the trigger tests of replayable steps)
   uint32_t k_next;     // the iteration after the last completed step
   uint64_t iters;      // steps completed
   double decay_pow;    // decay^k for the step in flight (replayable steps)
@@ -131,7 +131,6 @@ hipError_t launch_update(const Tables& t, const StepArgs& a, uint32_t dist, uint
 // norm as above; rings for which the host sets StepArgs::walk
 hipError_t launch_walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t grad_mode, int norm, hipStream_t s);
 hipError_t launch_trigger(const Tables& t, const StepArgs& a, hipStream_t s);
-hipError_t launch_begin(const Tables& t, hipStream_t s);
 hipError_t launch_copy(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
 hipError_t launch_deliver(const Tables& t, uint32_t chunk_elems, hipStream_t s);
 hipError_t launch_topk_decide(const Tables& t, const StepArgs& a, hipStream_t s);

@@ -17,7 +17,7 @@ __device__ __forceinline__ void trigger_segment(const Tables& T, const StepArgs&
   double acc, acc_hat;
   bool hat_sums;
   segment_sums(T, A, seg, &acc, &acc_hat, &hat_sums);
-  if (lane_id() == 0) (void)segment_test<true, true>(T, A, seg, acc, acc_hat, hat_sums);
+  if (lane_id() == 0) (void)segment_test<true, true>(T, A, seg, acc, acc_hat, hat_sums, tested_k(T, A));
 }
 
 __global__ __launch_bounds__(kThreads) void k_trigger(Tables T, StepArgs A) {
@@ -25,15 +25,6 @@ __global__ __launch_bounds__(kThreads) void k_trigger(Tables T, StepArgs A) {
   if (seg >= T.S) return;           // whole wavefront leaves; no workgroup barrier below
   trigger_segment(T, A, seg);
   if (seg == 0 && lane_id() == 0) close_step(T, A);
-}
-
-// First kernel of a replayable step: one thread moves the device's iteration on.
-__global__ void k_begin(Tables T) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  const uint32_t k = T.it->k_next;
-  T.it->k = k;
-  if (k >= T.decay_len) T.it->overflow = 1;
-  T.it->decay_pow = T.decay_tab[k < T.decay_len ? k : T.decay_len - 1];
 }
 
 template <int SWEEPS>
@@ -47,11 +38,6 @@ __global__ __launch_bounds__(kThreads) void k_copy(Tables T, StepArgs A) {
 hipError_t launch_trigger(const Tables& t, const StepArgs& a, hipStream_t s) {
   const uint32_t grid = (t.S + 3) / 4;
   k_trigger<<<dim3(grid), dim3(kThreads), 0, s>>>(t, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_begin(const Tables& t, hipStream_t s) {
-  k_begin<<<dim3(1), dim3(64), 0, s>>>(t);
   return hipGetLastError();
 }
 

@@ -101,8 +101,8 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
       bool hat_sums;
       segment_sums(T, A, sg, &acc, &acc_hat, &hat_sums);
       if (lane_id() == 0)
-        outcome[wave_id()] = (books && wave_id() == 0) ? segment_test<true, false>(T, A, sg, acc, acc_hat, hat_sums)
-                                                       : segment_test<false, false>(T, A, sg, acc, acc_hat, hat_sums);
+        outcome[wave_id()] = (books && wave_id() == 0) ? segment_test<true, false>(T, A, sg, acc, acc_hat, hat_sums, A.k)
+                                                       : segment_test<false, false>(T, A, sg, acc, acc_hat, hat_sums, A.k);
     }
     __syncthreads();
     my_event = outcome[0];
@@ -140,6 +140,7 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
   const size_t base = (size_t)r * T.Npad + cd.off;
   const float third = 0.333333343f;   // (float)(1/3): the ring's mixing weight
   const uint32_t k_iter = step_k(T, A);
+  end_replayable(T, A);
   uint32_t e[SPW];
   bool live[SPW];
 #pragma unroll

@@ -83,6 +83,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
   const ChunkDesc cd = T.chunks[c];
   if (sub0 * kSweep >= cd.len + cd.lead) return;                   // uniform (its sums are zero for good)
   const uint32_t P = T.P, layer = cd.layer, k_iter = step_k(T, A);
+  end_replayable(T, A);
   const uint32_t r0 = blockIdx.y * A.part, n = P - r0 < A.part ? P - r0 : A.part;   // workers r0 .. r0 + n - 1
   const bool closed = n == P;                            // the part is the whole ring
   const uint32_t skip = sub0 == 0 ? cd.lead : 0u, first = sub0 * kSweep + skip - cd.lead;   // first element of the window
