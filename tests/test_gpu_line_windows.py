@@ -52,3 +52,41 @@ def test_tensors_off_the_lines(evg, oracle_mod, options, chunk):
     rep = lockstep(ring, orc, w.iters, sample_messages=4, norm_rtol=None if differ else 2e-7,
                    norm_abs_of_x=2.5e-7 if differ else None)
     assert rep["rel"]["x"] <= 1e-5 and (differ or all(rep["bitwise"].values())), rep
+
+
+@pytest.mark.parametrize("topk", [0, 100_000])
+def test_saved_state_of_tensors_cut_at_their_start(evg, topk):
+    """A blob with fewer sums per tensor, as written where every tensor was cut at its own start, continues alike."""
+    import numpy as np
+    sizes, chunk, P = [5, 1024, 1020, 3000, 2048, 70], 1024, 3
+    tensors = [inputs.TensorSpec(f"t{i}", (n,), 16, "weight") for i, n in enumerate(sizes)]
+    w = inputs.Workload("blob", P, tensors, 8, sigma0=0.05, decay=0.9, seed=3, topk_ppm=topk)
+
+    def ring():
+        return evg.Ring.from_workload(w, mailbox_fill=0.0, chunk_elems=chunk, access_mode=evg.ACCESS_STREAM)
+
+    a, b = ring(), ring()
+    for k in range(4):
+        a.step(k)
+    ck = a.export_state()
+    blob = np.array(ck["blob"], dtype=np.uint8)
+    offs = np.concatenate([[0], np.cumsum([(n + 3) // 4 * 4 for n in sizes])])[:-1]
+    now = [-(-(n + int(o) % 32) // chunk) for n, o in zip(sizes, offs)]
+    plain = [-(-n // chunk) for n in sizes]
+    assert sum(now) > sum(plain)
+    S = P * len(sizes)
+    at = 80 + S * (40 + 4 * 1)          # header, then the per-tensor arrays, then the sums of the sweeps
+    sums = blob[at:at + 8 * P * sum(now)].view(np.float64).reshape(P, sum(now))
+    old, i = np.zeros((P, sum(plain))), 0
+    for n, m, j in zip(now, plain, np.concatenate([[0], np.cumsum(plain)])):
+        old[:, j] = sums[:, i:i + n].sum(axis=1)
+        i += n
+    head = blob[:at].copy()
+    head[20:24] = np.array([sum(plain)], dtype=np.uint32).view(np.uint8)      # the number of chunks
+    rest = blob[at + 8 * P * sum(now):]
+    b.import_state(dict(ck, blob=np.concatenate([head, old.reshape(-1).view(np.uint8), rest])))
+    for k in range(4, 8):
+        a.step(k)
+        b.step(k)
+    for name in ("x", "xhat", "mbox_l", "mbox_r", "vel"):
+        assert np.array_equal(a.state(name), b.state(name)), name
