@@ -27,9 +27,11 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X published peak, GB/s
-# Algorithmic bytes of the update pass per element: reads x, mbox_l, mbox_r, vel,
-# xhat and writes x, vel (fp32) = 28; with Top-K it also reads the three messages
-# (8 rho per fired element) and scatters them into xhat and both mailboxes (12 rho).
+# Algorithmic bytes of the update pass per element.  Walking the ring: reads x, vel, xhat and writes x,
+# vel (fp32) = 20, a whole send writes both mailboxes (8) and writes xhat instead of reading it; elsewhere
+# the mailboxes are read: 28.  With Top-K it also writes the messages (8 rho per fired element) and
+# scatters them into xhat and both mailboxes (12 rho).
+UPDATE_BYTES_PER_ELEM_WALK = 20
 UPDATE_BYTES_PER_ELEM = 28
 UPDATE_TOPK_BYTES_PER_FIRED_ELEM_PER_RHO = 20
 
@@ -203,7 +205,12 @@ def main():
     rho = w.topk_ppm / 1e6
     f_full = float((st["events_full_rl"].astype(np.float64) * numel[None, :]).sum() / (elems * args.steps))
     f_topk = float((st["events_topk_rl"].astype(np.float64) * numel[None, :]).sum() / (elems * args.steps))
-    step_bytes_per_elem = (28 if w.momentum != 0.0 else 20) + 16 * f_full + 8 * f_topk + 28 * rho * f_topk
+    # rings that stream from memory, with ordinary delivery: the update pass walks the ring
+    walks = 20 * w.P * evg.padded_numel(w.layer_numel) > (128 << 20) and not args.delivery_delay and not args.xhat_reset
+    if walks:
+        step_bytes_per_elem = (20 if w.momentum != 0.0 else 12) + 8 * f_full + 8 * f_topk + 20 * rho * f_topk
+    else:
+        step_bytes_per_elem = (28 if w.momentum != 0.0 else 20) + 16 * f_full + 8 * f_topk + 28 * rho * f_topk
     out = {
         "metric": "param_elements_per_s_fused_trigger_consensus_update",
         "value": elems * args.steps / dt,
@@ -234,17 +241,17 @@ def main():
     if phases:
         ms_upd, n_upd = phases["update"]
         avg_ms = ms_upd / max(1, n_upd)
-        per_elem = UPDATE_BYTES_PER_ELEM + UPDATE_TOPK_BYTES_PER_FIRED_ELEM_PER_RHO * rho * f_topk
+        per_elem = (UPDATE_BYTES_PER_ELEM_WALK + 8 * f_full if walks else UPDATE_BYTES_PER_ELEM) \
+            + UPDATE_TOPK_BYTES_PER_FIRED_ELEM_PER_RHO * rho * f_topk
         if w.momentum == 0.0:
             per_elem -= 8          # plain SGD: no velocity read or write
-        if args.trigger_kind == 1 and not w.topk_ppm:
+        if args.trigger_kind == 1 and not w.topk_ppm and not walks:
             per_elem -= 4          # xhat is not read: its norm is a scalar per tensor
         upd_bytes = per_elem * elems
         achieved = upd_bytes / (avg_ms * 1e-3) / 1e9
         # What the dense-mailbox semantics cost at the granularity memory is written in: the dense
-        # 28 (or fewer) bytes per element (a tensor that was sent whole has its xhat written instead
-        # of read: the same 4 bytes), each message read by its sender and both receivers (3 x 8 bytes
-        # per entry), and the write-back of every aligned 64-byte group of xhat and of the two
+        # bytes per element (a tensor that was sent whole has its xhat written instead of read: the same
+        # 4 bytes), each message written (8 bytes per entry), and the write-back of every aligned 64-byte group of xhat and of the two
         # mailboxes that holds a sent entry.  With K of n entries sent, spread evenly, a 16-float
         # group holds one with probability 1 - (1 - K/n)^16.
         dense = per_elem - UPDATE_TOPK_BYTES_PER_FIRED_ELEM_PER_RHO * rho * f_topk
@@ -253,7 +260,7 @@ def main():
                       for n in w.layer_numel], np.float64)
         share = K / numel
         dirty = 1.0 - (1.0 - share) ** 16
-        floor = dense * elems + float((ev_topk * numel * (12 * dirty + 24 * share)).sum()) / args.steps
+        floor = dense * elems + float((ev_topk * numel * (12 * dirty + 8 * share)).sum()) / args.steps
         counters = measured_counters(w.name) if not (args.diag_grad_buffer or args.trigger_kind or args.delivery_delay
                                                      or args.xhat_reset or args.plain_sgd or args.seed is not None
                                                      or args.topk_ppm is not None) else None
@@ -286,9 +293,8 @@ def main():
                                "hbm_achieved_GBps": achieved, "hbm_frac": achieved / HBM_PEAK_GBS}
         out["phase_ms_per_step"] = {p: ms / max(1, args.steps) for p, (ms, n) in phases.items()}
         # the other HBM-bound phases against the same peak, on their share of the lower-bound bytes:
-        # whole sends move 12 B per fired element here (xhat := x rides in the update pass), the
-        # Top-K selection one key pass over x and xhat (8 B), packing writes the 8 rho message
-        alg = {"send_full": 12 * f_full, "topk_select": 8 * f_topk, "topk_send": 8 * rho * f_topk}
+        # the Top-K selection makes one key pass over x and xhat (8 B)
+        alg = {"topk_select": 8 * f_topk}
         out["phase_frac_of_hbm_peak"] = {
             p: b * elems / (phases[p][0] / max(1, args.steps) * 1e-3) / 1e9 / HBM_PEAK_GBS
             for p, b in alg.items() if phases[p][0] > 0 and b > 0}

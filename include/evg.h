@@ -186,11 +186,15 @@ enum {
                             (no samples where the update pass runs the tests itself:
                             cache-resident rings that send whole tensors, norms fused,
                             no tensor above 131 072 elements, evg_step only)          */
-  EVG_PH_SEND_FULL = 2,  /* whole-tensor copies (no samples where the receivers fetch the
-                            sends inside the update pass, nor in Top-K rings, whose few
-                            whole sends are part of the selection's first kernel)     */
+  EVG_PH_SEND_FULL = 2,  /* whole-tensor copies: only for the few workers whose values two
+                            workgroups need, where a streaming ring of many workers and a
+                            small network is walked in parts; elsewhere whole sends are part
+                            of the update pass, of the selection's first kernel or of the
+                            delivery                                                  */
   EVG_PH_TOPK_SELECT = 3,/* threshold-key search for the Top-K set                   */
-  EVG_PH_TOPK_SEND = 4,  /* pack (index, value) messages, put them                   */
+  EVG_PH_TOPK_SEND = 4,  /* (index, value) messages, where a kernel ahead of the update
+                            pass writes and applies them (xhat reset at events, rings
+                            walked in parts); elsewhere the update pass does          */
   EVG_PH_UPDATE = 5,     /* fused averaging + momentum SGD (+ next drift norms)      */
   EVG_PH_DELIVER = 6,    /* delivery_delay = 1 only: the iteration's puts land       */
   EVG_PH_COUNT = 7

@@ -88,31 +88,6 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* ws, ui
   return before + incl - v;
 }
 
-// The same over 64-bit words that pack four 16-bit counters none of which can overflow its
-// field (so the two 32-bit halves scan independently), two such words at once: one barrier pair
-// serves both.  `ws` is 2 * W uint64 of LDS.
-template <int W>
-__device__ __forceinline__ void block_excl_scan64x2(uint64_t a, uint64_t b, uint64_t* ws, uint64_t* ex_a,
-                                                    uint64_t* ex_b, uint64_t* total_a, uint64_t* total_b) {
-  const uint64_t ia = ((uint64_t)wave_incl_scan((uint32_t)(a >> 32)) << 32) | wave_incl_scan((uint32_t)a);
-  const uint64_t ib = ((uint64_t)wave_incl_scan((uint32_t)(b >> 32)) << 32) | wave_incl_scan((uint32_t)b);
-  if (lane_id() == 63) { ws[wave_id()] = ia; ws[W + wave_id()] = ib; }
-  __syncthreads();
-  uint64_t before_a = 0, all_a = 0, before_b = 0, all_b = 0;
-#pragma unroll
-  for (int w = 0; w < W; ++w) {
-    const uint64_t sa = ws[w], sb = ws[W + w];
-    if ((uint32_t)w < wave_id()) { before_a += sa; before_b += sb; }
-    all_a += sa;
-    all_b += sb;
-  }
-  __syncthreads();
-  *total_a = all_a;
-  *total_b = all_b;
-  *ex_a = before_a + ia - a;
-  *ex_b = before_b + ib - b;
-}
-
 // The same accesses with the choice left to the caller: a ring whose arenas fit the
 // last-level cache is better served by ordinary cached accesses (measured 10 % per step
 // on an 8-worker ResNet-20-sized ring).

@@ -14,10 +14,9 @@ Writes, for the configuration's workload name W:
   profiles/counters_W.json              the figures bench.py prints as roofline.traffic and as the
                                         VALU instruction count, with the run they were measured on
 
-FETCH_SIZE and WRITE_SIZE are in KiB per dispatch and are calibrated on the library's own plain
-copy kernel: at iteration 0 `k_copy` copies every chunk of x, into xhat (rings whose update pass
-reads the neighbours' xhat) or into both mailboxes, so it reads P * sum(pad4(n_l)) * 4 bytes and
-writes once or twice that; true bytes = counter * 1024 * factor.
+FETCH_SIZE and WRITE_SIZE are in KiB per dispatch and are calibrated on the library's own averaging
+kernel `k_average`, which reads every worker's padded slice of x once and writes one such slice;
+true bytes = counter * 1024 * factor.
 """
 from __future__ import annotations
 
@@ -115,18 +114,14 @@ def main():
               "fraction_fired_full": b["config"]["fraction_fired_full"], "kernels": {}}
 
     # ---- HBM traffic --------------------------------------------------------------------
-    if a.fetch and a.write and not any("k_copy" in k for k in counter_rows(a.fetch, "FETCH_SIZE")):
-        # cache-resident rings that send whole tensors never launch the copy kernel, and their
-        # counters would mostly show cache hits anyway
-        print(f"no k_copy launch in {a.fetch}: the counters cannot be calibrated, no traffic summary is written")
+    if a.fetch and a.write and elems * 20 <= 128 << 20:
+        print("the ring lives in the cache: its counters would mostly show cache hits, no traffic summary is written")
         a.fetch = a.write = None
     if a.fetch and a.write:
         fetch, write = counter_rows(a.fetch, "FETCH_SIZE"), counter_rows(a.write, "WRITE_SIZE")
-        npad4 = sum((int(n) + 3) // 4 * 4 for n in w.layer_numel)
-        copy_read = w.P * npad4 * 4
-        kc = [k for k in fetch if "k_copy" in k][0]
-        to_xhat = short(kc).rstrip(">").endswith("true")          # k_copy<SWEEPS, STREAM, HAT>
-        copy_write = copy_read if to_xhat else 2 * copy_read
+        npad = (sum((int(n) + 3) // 4 * 4 for n in w.layer_numel) + 63) // 64 * 64
+        copy_read, copy_write = w.P * npad * 4, npad * 4
+        kc = [k for k in fetch if "k_average" in k][0]
         f_fetch = copy_read / (max(fetch[kc]) * KIB)
         f_write = copy_write / (max(write[kc]) * KIB)
         record["calibration"] = {"kernel": short(kc), "read_bytes": copy_read, "write_bytes": copy_write,
@@ -135,8 +130,8 @@ def main():
                "Commands (two runs, one counter each; on the MI355X box after `cd /tmp && export TMPDIR=/tmp`):", "",
                f"    rocprofv3 --pmc FETCH_SIZE --kernel-trace --output-format csv -d <out> -o cfg{c} -- {bench_cmd}",
                f"    rocprofv3 --pmc WRITE_SIZE --kernel-trace --output-format csv -d <out> -o cfg{c} -- {bench_cmd}", "",
-               f"Counters are in KiB per dispatch. Calibration on the library's plain copy kernel `k_copy` at iteration 0, where it",
-               f"copies every chunk of x into {'xhat' if to_xhat else 'both mailboxes'} (reads {copy_read} B, writes {copy_write} B): FETCH_SIZE factor "
+               f"Counters are in KiB per dispatch. Calibration on the library's averaging kernel `k_average`, which reads every worker's",
+               f"slice of x and writes one (reads {copy_read} B, writes {copy_write} B): FETCH_SIZE factor "
                f"{f_fetch:.4f}, WRITE_SIZE factor {f_write:.4f}", "(true bytes = counter x 1024 x factor).", "",
                f"Averages over the timed and the instrumented run of the {a.steps} iterations (warm-up launches dropped), GB per launch:", "",
                "| kernel | launches | fetch GB | write GB | total GB |", "|---|---|---|---|---|"]
@@ -149,7 +144,7 @@ def main():
             af = sum(fv) / len(fv) * KIB * f_fetch
             aw = sum(wv) / len(wv) * KIB * f_write
             out.append(f"| {short(k)} | {len(fv)} | {af / 1e9:.3f} | {aw / 1e9:.3f} | {(af + aw) / 1e9:.3f} |")
-            record["kernels"].setdefault(short(k).replace("evg::", "").split("<")[0], {}).update(
+            record["kernels"].setdefault(short(k).replace("evg::", "").split("<")[0].replace("k_update_walk", "k_update"), {}).update(
                 fetch_bytes=af, write_bytes=aw, traffic_bytes=af + aw, launches=len(fv))
         upd = record["kernels"].get("k_update")
         if upd and rf["bound"] == "hbm":
