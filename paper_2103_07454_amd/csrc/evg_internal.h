@@ -51,8 +51,8 @@ struct Tables {
   const LayerDesc* layers;
   float* x; float* xhat; float* mbox_l; float* mbox_r; float* vel;
   float* xsnap;            // [2][P*Npad] or null: copies of x that the update pass of one iteration leaves
-                           // for the next one, two in turn (cache-resident rings with whole-tensor
-                           // sends: the receivers then fetch what a neighbour sends, no copy kernel)
+                           // for the next one, two in turn (cache-resident rings with ordinary
+                           // delivery: the receivers then fetch what a neighbour sends, no copy kernel)
   double* partials;        // [P*C*SW] per 1024-element sweep of a chunk: sum of squared drift, or
                            // of squared x when the trigger compares norms
   double* partials_hat;    // [P*C*SW] sum of squared xhat (norm-difference trigger only)
