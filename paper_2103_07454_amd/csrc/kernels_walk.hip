@@ -315,7 +315,9 @@ static void walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t gra
 
 hipError_t launch_walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t grad_mode, int norm, hipStream_t s) {
   if (a.topk_on) {
-    // eight wavefronts share a histogram where chunks are long enough
+    // Eight wavefronts share a histogram where chunks are long enough.  4 / 8 / 16, steps in us: 64 ResNet-18 workers - / 4923 /
+    // 4762, 60 of width 28 978 / 950 / 1051, 20 of width 20 219 / 220 / 262, 8 ResNet-50 workers of half width 369 / 364 / 406, with
+    // Student-t gradients 390 / 404 / 451, 12 perceptrons with given gradients 188 / 138 / 119.
     const bool wide = t.SW % 2 == 0;
     if (norm == 0) walk<0, true, false, 4>(t, a, dist, grad_mode, s);
     else if (norm == 1 && a.hist_fused) wide ? walk<1, true, true, 8>(t, a, dist, grad_mode, s) : walk<1, true, true, 4>(t, a, dist, grad_mode, s);
