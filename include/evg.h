@@ -293,8 +293,8 @@ evg_status evg_average(evg_ctx* c, float* out);
  * depends on (thresholds, last-event iterations, mailbox flags, slope histories, counters,
  * the norm partial sums and radix histograms carried from the last update pass, the
  * iteration count) goes into one opaque HOST blob.  evg_state_export waits for the stream.
- * evg_state_import expects a context created with the same configuration whose arenas
- * already hold the saved contents; a blob from a different configuration is rejected with
+ * evg_state_import expects a context created with the same configuration (access_mode may
+ * differ, and evg_init or evg_init_static) whose arenas already hold the saved contents; a blob from a different configuration is rejected with
  * EVG_ERR_INVALID.  After import, evg_step continues exactly (bit for bit) where the
  * exporting context stopped. */
 uint64_t evg_state_size(evg_ctx* c); /* bytes needed for the blob; 0 if c is NULL */

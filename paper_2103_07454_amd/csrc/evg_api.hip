@@ -7,6 +7,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -70,12 +71,12 @@ struct evg_ctx {
   std::vector<uint64_t> numel;      // per tensor
   std::vector<uint32_t> K;          // per tensor Top-K message length
   std::vector<uint32_t> msg_off;
-  std::vector<uint32_t> nchunks;    // per tensor
   std::vector<void*> owned;         // device allocations to free
   uint64_t N = 0;                   // unpadded elements per worker
   uint64_t iters = 0;
   int64_t last_iter = -1;
   bool messages_live = false;       // the message buffers hold the last step's messages
+  bool on_lines = false;            // sweeps begin on cache lines (streaming rings)
   uint32_t part = 0;                // workers of the ring that one workgroup of a walking pass goes through
   bool cached = false;              // the five arenas together fit the last-level cache
   bool device_ahead = false;        // evg_step_next has been used: replays of a captured graph
@@ -452,7 +453,8 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     return (uint64_t)P * chunks.size() * (SW + 1) <= 0xFFFFFFF0ull && (uint64_t)P * ktot <= 0xFFFFFFF0ull &&
            !(use_scratch && std::max(need, admitted) > kScratchBytes);
   };
-  if (c->cached || !cut_chunks(true)) (void)cut_chunks(false);
+  c->on_lines = !c->cached && cut_chunks(true);
+  if (!c->on_lines) (void)cut_chunks(false);
   if (use_scratch && need > kScratchBytes && pull && cfg->topk_ppm) {   // no room for the copies of x: messages are applied
     pull = false;                                                        // by a kernel of their own
     (void)cut_chunks(false);
@@ -468,7 +470,6 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   const uint64_t parts = windows < 600 ? (2048 + windows - 1) / windows : 1;
   c->part = P < 16 ? P : std::max<uint32_t>(8u, (uint32_t)((P + parts - 1) / parts));
   if (c->part > P) c->part = P;
-  for (const LayerDesc& d : layers) c->nchunks.push_back(d.nchunks);
   const uint64_t C = chunks.size();
   if ((uint64_t)P * C * (SW + 1) > 0xFFFFFFF0ull || (uint64_t)P * ktot > 0xFFFFFFF0ull) {
     delete c;
@@ -902,6 +903,8 @@ struct StateHeader {
   int64_t last_iter;
 };
 
+constexpr uint32_t kCutOnLines = 1u << 16;   // StateHeader::pad, from version 5 on
+
 struct Piece { void* dev; size_t bytes; };
 
 // Every library-owned array a later step reads before writing it.
@@ -922,14 +925,14 @@ std::vector<Piece> state_pieces(evg_ctx* c) {
 StateHeader state_header(evg_ctx* c) {
   StateHeader h{};
   std::memcpy(h.magic, "EVGSTATE", 8);
-  h.version = 4;
+  h.version = 5;
   h.P = c->t.P; h.L = c->t.L; h.C = c->t.C; h.SW = c->t.SW; h.S = c->t.S;
   h.hist_len = c->t.hist_len;
   h.topk_ppm = c->cfg.topk_ppm;
   h.trigger_kind = c->cfg.trigger_kind;
   h.norm_mode = c->cfg.norm_mode;
   h.thr_mode = c->cfg.thr_mode;
-  h.pad = c->cfg.delivery_delay | (c->cfg.xhat_reset << 8);
+  h.pad = c->cfg.delivery_delay | (c->cfg.xhat_reset << 8) | (c->on_lines ? kCutOnLines : 0u);
   h.Npad = c->t.Npad;
   h.iters = c->iters;
   h.last_iter = c->last_iter;
@@ -968,37 +971,65 @@ evg_status evg_state_export(evg_ctx* c, void* blob, uint64_t capacity) {
 
 evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
   if (!c || !blob) return fail(EVG_ERR_INVALID, "context and blob must be non-NULL");
-  // A blob may also come from a library that cut every tensor at its own start instead of on cache lines: fewer
-  // sweeps, whose sums serve all the same, since a tensor's are only ever added up.
+  // A tensor's sums are only ever added up, so a blob serves whether its ring cut the tensors at their own starts or on cache
+  // lines; how this configuration's tensors are cut either way, in chunks per tensor:
   const Tables& t = c->t;
   const uint64_t granule = (uint64_t)t.SW * kSweep;
-  uint64_t plain_C = 0;
-  for (uint64_t n : c->numel) plain_C += (n + granule - 1) / granule;
-  const uint64_t sums = t.partials_hat ? 2 : 1, fewer = (uint64_t)t.P * (t.C - plain_C) * t.SW * 8 * sums;
-  const bool plain = fewer != 0 && size == evg_state_size(c) - fewer;
-  if (!plain && size != evg_state_size(c)) return fail(EVG_ERR_INVALID, "blob size does not match this configuration");
+  const size_t L = c->numel.size();
+  auto chunks_of = [&](size_t l, uint64_t off, bool on_lines) {
+    return (c->numel[l] + (on_lines ? off % kLineElems : 0) + granule - 1) / granule;
+  };
+  uint64_t C_plain = 0, C_lines = 0, off = 0;
+  for (size_t l = 0; l < L; ++l) {
+    C_plain += chunks_of(l, off, false);
+    C_lines += chunks_of(l, off, true);
+    off += pad_to(c->numel[l], 4);
+  }
   StateHeader got;
+  if (size < sizeof got) return fail(EVG_ERR_INVALID, "blob size does not match this configuration");
   std::memcpy(&got, blob, sizeof got);
+  const bool same_cut = got.C == t.C;
+  const bool maybe_lines = got.version == 4 || (got.pad & kCutOnLines);     // (version 4 does not say)
+  const uint64_t sums = t.partials_hat ? 2 : 1, per_chunk = (uint64_t)t.P * t.SW * 8 * sums;
+  if (got.C != C_plain && !(maybe_lines && got.C == C_lines))
+    return fail(EVG_ERR_INVALID, "blob was exported from a different configuration or version");
+  if (size != evg_state_size(c) - t.C * per_chunk + got.C * per_chunk)
+    return fail(EVG_ERR_INVALID, "blob size does not match this configuration");
   StateHeader want = state_header(c);
-  if (plain) want.C = (uint32_t)plain_C;
+  want.C = got.C;
+  if (got.version == 4) want.version = 4;
+  want.pad = (want.pad & ~kCutOnLines) | (got.version == 4 ? 0u : got.pad & kCutOnLines);
   want.iters = got.iters;
   want.last_iter = got.last_iter;
   if (std::memcmp(&got, &want, sizeof got) != 0)
     return fail(EVG_ERR_INVALID, "blob was exported from a different configuration or version");
+  const size_t sum_count = (size_t)t.P * t.C * t.SW;
+  std::unique_ptr<double[]> moved(same_cut ? nullptr : new (std::nothrow) double[sum_count]);
+  if (!same_cut && !moved) return fail(EVG_ERR_OOM, "host allocation failed");
   HIP_TRY(hipStreamSynchronize(c->stream));
   const char* in = static_cast<const char*>(blob) + sizeof got;
   for (const Piece& p : state_pieces(c)) {
-    if (plain && (p.dev == t.partials || p.dev == t.partials_hat)) {
-      std::vector<double> spread(p.bytes / 8, 0.0);
-      double* to = spread.data();
-      for (uint32_t r = 0; r < t.P; ++r)
-        for (size_t l = 0; l < c->numel.size(); ++l) {
-          const uint64_t n = (c->numel[l] + granule - 1) / granule * t.SW;
-          std::memcpy(to, in, n * 8);
-          in += n * 8;
-          to += (uint64_t)c->nchunks[l] * t.SW;
+    if (!same_cut && (p.dev == t.partials || p.dev == t.partials_hat)) {
+      // sums of the exporter's sweeps to the places of this ring's; what is beyond the last place in use here (a
+      // streaming ring's passes never write there) joins the sum before
+      double* to = moved.get();
+      std::fill_n(to, sum_count, 0.0);
+      for (uint32_t r = 0; r < t.P; ++r) {
+        off = 0;
+        for (size_t l = 0; l < L; ++l) {
+          const uint64_t from = chunks_of(l, off, !c->on_lines) * t.SW;
+          const uint64_t used = (c->numel[l] + (c->on_lines ? off % kLineElems : 0) + kSweep - 1) / kSweep;
+          for (uint64_t i = 0; i < from; ++i) {
+            double v;
+            std::memcpy(&v, in, 8);
+            in += 8;
+            to[std::min(i, used - 1)] += v;
+          }
+          to += chunks_of(l, off, c->on_lines) * t.SW;
+          off += pad_to(c->numel[l], 4);
         }
-      HIP_TRY(hipMemcpy(p.dev, spread.data(), p.bytes, hipMemcpyHostToDevice));
+      }
+      HIP_TRY(hipMemcpy(p.dev, moved.get(), p.bytes, hipMemcpyHostToDevice));
       continue;
     }
     HIP_TRY(hipMemcpy(p.dev, in, p.bytes, hipMemcpyHostToDevice));
