@@ -989,16 +989,18 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
   if (size < sizeof got) return fail(EVG_ERR_INVALID, "blob size does not match this configuration");
   std::memcpy(&got, blob, sizeof got);
   const bool same_cut = got.C == t.C;
-  const bool maybe_lines = got.version == 4 || (got.pad & kCutOnLines);     // (version 4 does not say)
+  const bool maybe_lines = got.version == 4 || (got.version > 4 && (got.pad & kCutOnLines));   // (version 4 does not say)
   const uint64_t sums = t.partials_hat ? 2 : 1, per_chunk = (uint64_t)t.P * t.SW * 8 * sums;
   if (got.C != C_plain && !(maybe_lines && got.C == C_lines))
     return fail(EVG_ERR_INVALID, "blob was exported from a different configuration or version");
-  if (size != evg_state_size(c) - t.C * per_chunk + got.C * per_chunk)
+  // version 3 has three more words, lengths of lists that are no longer kept, ahead of the count of chunks not staged
+  const uint64_t list_bytes = got.version == 3 ? 12 : 0;
+  if (size != evg_state_size(c) - t.C * per_chunk + got.C * per_chunk + list_bytes)
     return fail(EVG_ERR_INVALID, "blob size does not match this configuration");
   StateHeader want = state_header(c);
   want.C = got.C;
-  if (got.version == 4) want.version = 4;
-  want.pad = (want.pad & ~kCutOnLines) | (got.version == 4 ? 0u : got.pad & kCutOnLines);
+  if (got.version == 3 || got.version == 4) want.version = got.version;
+  want.pad = (want.pad & ~kCutOnLines) | (got.version <= 4 ? 0u : got.pad & kCutOnLines);
   want.iters = got.iters;
   want.last_iter = got.last_iter;
   if (std::memcmp(&got, &want, sizeof got) != 0)
@@ -1009,6 +1011,7 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
   HIP_TRY(hipStreamSynchronize(c->stream));
   const char* in = static_cast<const char*>(blob) + sizeof got;
   for (const Piece& p : state_pieces(c)) {
+    if (p.dev == t.not_staged) in += list_bytes;
     if (!same_cut && (p.dev == t.partials || p.dev == t.partials_hat)) {
       // sums of the exporter's sweeps to the places of this ring's; what is beyond the last place in use here (a
       // streaming ring's passes never write there) joins the sum before

@@ -71,3 +71,26 @@ def test_a_blob_of_other_tensors_is_refused(evg, sizes):
     with pytest.raises(evg.EvgError) as e:
         b.import_state(ck)
     assert e.value.status == 1
+
+
+# version 3: tensors cut at their own starts, and four words where later versions have one
+@pytest.mark.parametrize("access", ["stream", "cached"])
+@pytest.mark.parametrize("kw", [dict(), dict(topk_ppm=100_000), dict(trigger_kind=1, topk_ppm=100_000)], ids=["whole", "topk", "norms_topk"])
+def test_blobs_of_version_3_are_read(evg, kw, access):
+    sizes, chunk, P = [5, 1024, 1020, 3000, 2048, 70], 1024, 3
+    kw = dict(kw)
+    over = dict(trigger_kind=kw.pop("trigger_kind")) if "trigger_kind" in kw else {}
+    w = _workload(sizes, **kw)
+    a = evg.Ring.from_workload(w, mailbox_fill=0.0, chunk_elems=chunk, access_mode=evg.ACCESS_CACHED, **over)
+    b = evg.Ring.from_workload(w, mailbox_fill=0.0, chunk_elems=chunk,
+                               access_mode=evg.ACCESS_STREAM if access == "stream" else evg.ACCESS_CACHED, **over)
+    for k in range(4):
+        a.step(k)
+    ck = a.export_state()
+    # header, the per-tensor arrays, one sum per sweep, the iteration
+    at = 80 + P * len(sizes) * (40 + 4) + 8 * P * sum(_chunks(sizes, chunk, False)) + 32
+    old = np.insert(np.array(ck["blob"], dtype=np.uint8), at, np.full(12, 7, np.uint8))
+    old[8:12] = np.array([3], np.uint32).view(np.uint8)
+    b.import_state(dict(ck, blob=old))
+    assert a.stats()["chunks_not_staged"] == b.stats()["chunks_not_staged"]
+    _same_run(a, b, 4, 10)
