@@ -1008,7 +1008,8 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
   const size_t sum_count = (size_t)t.P * t.C * t.SW;
   std::unique_ptr<double[]> moved(same_cut ? nullptr : new (std::nothrow) double[sum_count]);
   if (!same_cut && !moved) return fail(EVG_ERR_OOM, "host allocation failed");
-  HIP_TRY(hipStreamSynchronize(c->stream));
+  // Everything goes through the context's stream, and is waited for: steps on a non-blocking stream do not wait for copies
+  // on the default stream, and a copy from device to device does not make the host wait.
   const char* in = static_cast<const char*>(blob) + sizeof got;
   for (const Piece& p : state_pieces(c)) {
     if (p.dev == t.not_staged) in += list_bytes;
@@ -1032,18 +1033,20 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
           off += pad_to(c->numel[l], 4);
         }
       }
-      HIP_TRY(hipMemcpy(p.dev, moved.get(), p.bytes, hipMemcpyHostToDevice));
+      HIP_TRY(hipMemcpyAsync(p.dev, moved.get(), p.bytes, hipMemcpyHostToDevice, c->stream));
+      HIP_TRY(hipStreamSynchronize(c->stream));        // `moved` is filled again
       continue;
     }
-    HIP_TRY(hipMemcpy(p.dev, in, p.bytes, hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpyAsync(p.dev, in, p.bytes, hipMemcpyHostToDevice, c->stream));
     in += p.bytes;
   }
   // the library's copy of x follows the caller's arena, which holds the saved parameters again
   if (c->t.xsnap) {
     const size_t arena = (size_t)c->t.P * c->t.Npad;
-    HIP_TRY(hipMemcpy(c->t.xsnap, c->t.x, arena * 4, hipMemcpyDeviceToDevice));
-    HIP_TRY(hipMemcpy(c->t.xsnap + arena, c->t.x, arena * 4, hipMemcpyDeviceToDevice));
+    HIP_TRY(hipMemcpyAsync(c->t.xsnap, c->t.x, arena * 4, hipMemcpyDeviceToDevice, c->stream));
+    HIP_TRY(hipMemcpyAsync(c->t.xsnap + arena, c->t.x, arena * 4, hipMemcpyDeviceToDevice, c->stream));
   }
+  HIP_TRY(hipStreamSynchronize(c->stream));
   c->iters = got.iters;
   c->last_iter = got.last_iter;
   c->messages_live = false;         // message buffers are scratch and are not part of the blob

@@ -94,3 +94,26 @@ def test_blobs_of_version_3_are_read(evg, kw, access):
     b.import_state(dict(ck, blob=old))
     assert a.stats()["chunks_not_staged"] == b.stats()["chunks_not_staged"]
     _same_run(a, b, 4, 10)
+
+
+@pytest.mark.parametrize("topk", [0, 100_000])
+def test_steps_on_a_stream_of_their_own_follow_an_import(evg, topk):
+    """The import is over when it returns, for a stream that waits for no other: the copies of x that cached rings
+    send from are those of the imported parameters."""
+    import torch
+    w = _workload([700_003, 60_000, 5], topk_ppm=topk)
+    a = evg.Ring.from_workload(w, mailbox_fill=0.0)
+    for k in range(4):
+        a.step(k)
+    ck = a.export_state()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        b = evg.Ring.from_workload(w, mailbox_fill=0.0, stream=s)
+        b.step(0)
+        b.import_state(ck)
+        b.step(4)
+        b.step_next()
+    s.synchronize()
+    a.step(4)
+    a.step(5)
+    _same_run(a, b, 6, 8)
