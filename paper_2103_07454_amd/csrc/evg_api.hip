@@ -854,7 +854,10 @@ evg_status evg_message(evg_ctx* c, uint32_t r, uint32_t l, uint32_t* idx, float*
   HIP_TRY(hipStreamSynchronize(c->stream));
   uint8_t code = 0;
   HIP_TRY(hipMemcpy(&code, t.fired + (size_t)r * t.L + l, 1, hipMemcpyDeviceToHost));
-  if (code != 2 || !c->cfg.topk_ppm || !c->messages_live) {
+  uint32_t threshold = 0;
+  if (code == 2 && c->cfg.topk_ppm)
+    HIP_TRY(hipMemcpy(&threshold, t.sel_prefix + (size_t)r * t.L + l, 4, hipMemcpyDeviceToHost));
+  if (code != 2 || !c->cfg.topk_ppm || !c->messages_live || threshold == kNoThreshold) {
     *count = 0;
     return EVG_OK;
   }

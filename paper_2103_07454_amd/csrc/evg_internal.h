@@ -11,6 +11,10 @@ constexpr int kSweep = kThreads * kLaneElems;   // elements one workgroup covers
 constexpr uint32_t kLineElems = 32;    // floats of a 128-byte cache line
 constexpr int kHistBins = 2048;        // 11 key bits per selection pass (passes A, B); pass C uses 512
 constexpr uint32_t kStageCap = 2048;   // staged keys of a chunk at most
+// Threshold key that no key reaches (they have 31 bits).  A selection ends with it where it would not find exactly K
+// winners: the histogram that the last update pass left does not fit x and xhat, which the caller has written since.
+// Nothing is sent then; the update passes write a message's winners without a look at its length.
+constexpr uint32_t kNoThreshold = 0xFFFFFFFFu;
 
 // A chunk is a run of one tensor's elements that one workgroup handles; it never
 // straddles tensors, starts at a multiple of 4 elements and is at most chunk_elems long.
@@ -71,7 +75,7 @@ struct Tables {
   float* slope_hist; uint32_t* slope_cnt;   // [S*hist_len], [S]
   uint32_t* not_staged;    // [1] chunks so far whose possible winners did not fit their staging slot
   uint32_t* hist;          // [S*kHistBins]
-  uint32_t* sel_prefix; uint32_t* sel_krem;   // [S] in the end the threshold key, and how many of the keys equal to it win
+  uint32_t* sel_prefix; uint32_t* sel_krem;   // [S] in the end the threshold key (or kNoThreshold), and how many of the keys equal to it win
   uint32_t* sel_cut;       // [S] the last element of the tensor that wins with a key equal to the threshold
   uint32_t* stage_n;       // [P*C] staged keys of a chunk: those in the threshold bin; 0xFFFFFFFF: more than the
                            // chunk's slot holds, nothing staged (they are then read from the arenas)

@@ -116,6 +116,7 @@ __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t
   }
   uint32_t total;
   const uint32_t above = block_excl_scan<4>(local, ws, &total);   // keys in higher bins
+  if (total < krem && threadIdx.x == 0) T.sel_prefix[seg] = kNoThreshold;   // (no later pass finds krem keys under this prefix either)
   if (above < krem && krem <= above + local) {    // exactly one thread
     uint32_t run = above, bin = top, rem = krem - above;
 #pragma unroll
@@ -376,6 +377,10 @@ __global__ __launch_bounds__(64) void k_topk_scan(Tables T, StepArgs A) {
       carry_e += (uint32_t)__builtin_amdgcn_readlane((int)ie, 63);
     }
   }
+  if (t == kNoThreshold || carry_g + ties != ld.K || carry_e < ties) {
+    if (lane == 0) T.sel_prefix[seg] = kNoThreshold;
+    return;
+  }
   if (carry_e == ties) {                             // all of them win
     if (lane == 0) T.sel_cut[seg] = ld.numel - 1;
     return;
@@ -460,7 +465,7 @@ __global__ __launch_bounds__(kThreads) void k_message_hashes(Tables T) {
   __shared__ unsigned long long ws[2 * (kThreads / 64)];
   const uint32_t seg = blockIdx.x;
   unsigned long long hi = 0ull, hm = 0ull;
-  if (T.fired[seg] == 2) {          // uniform for the workgroup
+  if (T.fired[seg] == 2 && T.sel_prefix[seg] != kNoThreshold) {          // uniform for the workgroup
     const LayerDesc ld = T.layers[seg % T.L];
     const size_t mbase = (size_t)(seg / T.L) * T.Ktot + ld.msg_off;
     for (uint32_t q = threadIdx.x; q < ld.K; q += kThreads) {

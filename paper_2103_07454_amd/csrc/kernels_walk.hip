@@ -116,7 +116,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
 
   // the i-th worker of the part, i = n: the one after it
   auto marks_of = [&](uint32_t i) {
-    Marks m{0u, 0xFFFFFFFFu, 0u, 0u};
+    Marks m{0u, kNoThreshold, 0u, 0u};
     if (i <= n) {
       const uint32_t s = worker(i), seg = s * T.L + layer, code = T.fired[seg];
       m.f = code | (T.valid_l[seg] ? kLeftFilled : 0u) | (T.valid_r[seg] ? kRightFilled : 0u);
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
     const uint32_t seg_b = before * T.L + layer;
     uint32_t f_b = __builtin_amdgcn_readfirstlane((int)T.fired[seg_b]);
     if (is_led(T, A, before)) f_b |= kLed;
-    uint32_t thr_b = 0xFFFFFFFFu, cut_b = 0u, place_b = 0u;
+    uint32_t thr_b = kNoThreshold, cut_b = 0u, place_b = 0u;
     if (TOPK && f_b == 2) {
       thr_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)T.sel_prefix[seg_b]);
       cut_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)T.sel_cut[seg_b]);

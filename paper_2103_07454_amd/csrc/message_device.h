@@ -9,8 +9,8 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// One bit per element of a float4, the first of them element j of the tensor.  thr = 0xFFFFFFFF: none
-// (keys have 31 bits).  nv: how many of the four are elements of the tensor.
+// One bit per element of a float4, the first of them element j of the tensor.  thr = kNoThreshold: none.
+// nv: how many of the four are elements of the tensor.
 __device__ __forceinline__ uint32_t winners4(const float x[4], const float h[4], uint32_t by_value, uint32_t thr,
                                              uint32_t cut, uint32_t j, uint32_t nv) {
   uint32_t win = 0;
