@@ -118,11 +118,12 @@ typedef struct {
                                    EVG_ACCESS_STREAM: non-temporal (rings far larger than the
                                    caches); EVG_ACCESS_CACHED: ordinary accesses (rings that fit
                                    the 256 MB last-level cache); EVG_ACCESS_AUTO: cached if the
-                                   five arenas together take at most 128 MB.  A cached ring that
-                                   sends whole tensors without delivery delay also skips the copy
-                                   kernel: each receiver fetches what its neighbours send inside
-                                   the update pass, from a copy of x the library keeps (two more
-                                   arrays of the ring's size, library-owned).  If its norms are
+                                   five arenas together take at most 128 MB.  In a cached ring
+                                   without delivery delay each receiver fetches what its neighbours
+                                   send inside the update pass, from a copy of x the library keeps
+                                   (two more arrays of the ring's size, library-owned); not where
+                                   Top-K messages are sent and xhat_reset or EVG_NORM_SEPARATE is
+                                   set.  If such a ring sends whole tensors, its norms are
                                    accumulated by the update pass (norm_mode) and no tensor is
                                    longer than 131 072 elements, evg_step is then ONE kernel launch:
                                    the update pass runs the trigger tests itself.  evg_step_next
@@ -137,10 +138,13 @@ typedef struct {
    * before a first message arrives).  evg_init asks the runtime about each pointer:
    * host memory, memory of another device, or an allocation that ends before the
    * stated size gives EVG_ERR_INVALID (the same holds for evg_step's grad and
-   * evg_average's out).  Between evg_init and evg_destroy xhat, the mailboxes and vel are
-   * the library's to write: a mailbox that has received equals its sender's xhat (unless
+   * evg_average's out).  Between evg_init and evg_destroy xhat and the mailboxes are the
+   * library's to write: a mailbox that has received equals its sender's xhat (unless
    * delivery is delayed or xhat_reset moves xhat without a message), and evg_step reads
-   * whichever copy is nearer. */
+   * whichever copy is nearer.  So is x, of which the update pass carries norms, histograms and
+   * copies on to the next step (a Top-K tensor whose histogram no longer fits it sends nothing);
+   * with EVG_NORM_SEPARATE nothing but a cached whole-tensor ring's copies is carried, and
+   * in every other ring the caller may write x between two steps. */
   float* x;      /* current parameters                                   */
   float* xhat;   /* values last sent (Section 4, X-hat)                   */
   float* mbox_l; /* last received from the left neighbour (r-1)           */

@@ -419,8 +419,11 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   // width 28, 60 workers 843 -> 771 us; width 40, 30 workers 871 -> 796 us.  Not where the additional chunks
   // would take the tables past a limit.
   const uint32_t hist_len = cfg->thr_mode == EVG_THR_ADAPTIVE ? cfg->hist_len : 1, SW = ce / (uint32_t)kSweep;
-  // (an xhat that is reset at events is not what a neighbour's mailbox holds, so that a Top-K message could not be told from it)
-  bool pull = c->cached && !cfg->delivery_delay && !(cfg->xhat_reset && cfg->topk_ppm);
+  // Receivers fetch the sends from copies of x.  Not Top-K sends of rings whose xhat is reset at events: a mailbox then does
+  // not hold what the message was told from.  Nor of rings with a norm pass of their own, in which nothing else is
+  // carried from step to step: a caller may have written x since the copies were made, and the sender goes by x.
+  bool pull = c->cached && !cfg->delivery_delay &&
+              !(cfg->topk_ppm && (cfg->xhat_reset || cfg->norm_mode == EVG_NORM_SEPARATE));
   bool one_launch = false;
   uint64_t need = 0;
   uint64_t admitted = 0;
