@@ -267,49 +267,74 @@ evg_status evg_destroy(evg_ctx* c) {
   return EVG_OK;
 }
 
-// Bytes of library-owned device tables a configuration needs, with every table rounded up to
-// the scratch block's alignment: the same list as the allocations of init_common.
+// Sizes of a list of tables, every one rounded up to the scratch block's alignment.
+struct TableSum {
+  uint64_t total = 0;
+  void add(uint64_t count, uint64_t elem) {
+    total = (total + kScratchAlign - 1) / kScratchAlign * kScratchAlign + (count ? count : 1) * elem;
+  }
+};
+
+// Bytes of library-owned device tables a configuration needs: the same list as the allocations of init_common.
 static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uint64_t hist_len, uint64_t Npad,
                             uint64_t ktot, bool topk, bool norm_diff, bool pull, bool one_launch) {
   const uint64_t S = P * L, PC = P * C;
-  uint64_t total = 0;
-  auto add = [&total](uint64_t count, uint64_t elem) {
-    total = (total + kScratchAlign - 1) / kScratchAlign * kScratchAlign + (count ? count : 1) * elem;
-  };
-  add(C, sizeof(ChunkDesc)); add(L, sizeof(LayerDesc));
-  add(PC * SW, 8);
-  if (norm_diff) { add(PC * SW, 8); add(S, 8); }
-  add(S, 4); add(S, 4); add(S, 4); add(S, 4);            // delta, last_norm, delta_before, last_event
-  add(S, 1); add(S, 1); add(S, 1); add(S, 1);            // valid_l, valid_r, fired, near_tie
-  add(S, 4); add(S, 4); add(S, 4); add(S, 4);            // ev_full, ev_topk, near_cnt, nonfinite_cnt
-  add(S * hist_len, 4); add(S, 4);                       // slope_hist, slope_cnt
-  add(1, 4); add(1, sizeof(IterState)); add(kDecayTable, 8);
-  if (pull) add(2 * P * Npad, 4);                        // xsnap
-  if (one_launch) {                                      // the second set of what the trigger tests read
-    add(PC * SW, 8); add(S, 4); add(S, 4);
-    if (norm_diff) add(S, 8);
+  TableSum t;
+  t.add(C, sizeof(ChunkDesc)); t.add(L, sizeof(LayerDesc));
+  t.add(PC * SW, 8);
+  if (norm_diff) { t.add(PC * SW, 8); t.add(S, 8); }
+  t.add(S, 4); t.add(S, 4); t.add(S, 4); t.add(S, 4);            // delta, last_norm, delta_before, last_event
+  t.add(S, 1); t.add(S, 1); t.add(S, 1); t.add(S, 1);            // valid_l, valid_r, fired, near_tie
+  t.add(S, 4); t.add(S, 4); t.add(S, 4); t.add(S, 4);            // ev_full, ev_topk, near_cnt, nonfinite_cnt
+  t.add(S * hist_len, 4); t.add(S, 4);                           // slope_hist, slope_cnt
+  t.add(1, 4); t.add(1, sizeof(IterState)); t.add(kDecayTable, 8);
+  if (pull) t.add(2 * P * Npad, 4);                              // xsnap
+  if (one_launch) {                                              // the second set of what the trigger tests read
+    t.add(PC * SW, 8); t.add(S, 4); t.add(S, 4);
+    if (norm_diff) t.add(S, 8);
   }
   if (topk) {
-    add(S * kHistBins, 4); add(S, 4); add(S, 4); add(S, 4); add(PC, 4);   // hist, selection, stage_n
-    add(P * (Npad / 16 * 4), 4);                         // stage_key
-    add(PC * SW * 4, 4); add(PC, 8); add(PC, 8);           // group, chunk_cnt, chunk_before
-    add(P * ktot, 4); add(P * ktot, 4); add(S, 8); add(S, 8);
+    t.add(S * kHistBins, 4); t.add(S, 4); t.add(S, 4); t.add(S, 4); t.add(PC, 4);   // hist, selection, stage_n
+    t.add(P * (Npad / 16 * 4), 4);                               // stage_key
+    t.add(group_entries(P, C, Npad), 4); t.add(PC, 8); t.add(PC, 8);                // group, chunk_cnt, chunk_before
+    t.add(P * ktot, 4); t.add(P * ktot, 4); t.add(S, 8); t.add(S, 8);
   }
-  return total;
+  return t.total;
 }
 
-// What evg_init_static admits is part of its interface and older than the present tables: a Top-K ring is
-// reckoned with three words for each possible winner (one and a half times the Top-K share plus a sixteenth, in
-// quarters of the ring) and without copies of x.  The tables take less.
+// What evg_init_static admits is part of its interface, and older than the present tables: it is reckoned with those of the
+// library's first version, whose tensors were cut at their own starts (C chunks a worker), with lists of fired
+// chunks, and for Top-K with three words for each possible winner (one and a half times the Top-K share plus a
+// sixteenth, in quarters of the ring), but without copies of x.  Whatever it admits has room: at most one word more
+// for each 256 elements and 28 bytes a chunk, where the old lists took 2 bytes for each element, or 36 and more a chunk.
 static uint64_t admitted_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uint64_t hist_len, uint64_t Npad,
-                               uint64_t ktot, uint32_t topk_ppm, bool norm_diff, bool pull, bool one_launch) {
-  uint64_t total = table_bytes(P, L, C, SW, hist_len, Npad, ktot, topk_ppm != 0, norm_diff, pull && !topk_ppm, one_launch);
-  if (topk_ppm) {
-    const uint64_t want = (3ull * topk_ppm * 8ull + 999999ull) / 1000000ull + 1ull;   // in sixteenths
-    const uint64_t quarters = want <= 4 ? 1 : want <= 8 ? 2 : want <= 12 ? 3 : 4;
-    total += P * (Npad / 16 * 4) * 4 * (3 * quarters - 1);
+                               uint64_t ktot, uint32_t topk_ppm, bool norm_diff, bool whole_copies, bool one_launch) {
+  const uint64_t S = P * L, PC = P * C;
+  TableSum t;
+  t.add(C, 16); t.add(L, sizeof(LayerDesc));
+  t.add(PC * SW, 8);
+  if (norm_diff) { t.add(PC * SW, 8); t.add(S, 8); }
+  for (int i = 0; i < 4; ++i) t.add(S, 4);
+  for (int i = 0; i < 4; ++i) t.add(S, 1);
+  for (int i = 0; i < 4; ++i) t.add(S, 4);
+  t.add(S * hist_len, 4);
+  for (int i = 0; i < 3; ++i) t.add(S, 4);
+  t.add(4, 4); t.add(1, sizeof(IterState)); t.add(kDecayTable, 8);
+  t.add(PC, 4);
+  if (whole_copies) t.add(2 * P * Npad, 4);
+  if (one_launch) {
+    t.add(PC * SW, 8); t.add(S, 4); t.add(S, 4);
+    if (norm_diff) t.add(S, 8);
   }
-  return total;
+  if (topk_ppm) {
+    t.add(PC, 4); t.add(S * kHistBins, 4); t.add(S, 4); t.add(S, 4); t.add(PC, 8);
+    const uint64_t want = (3ull * topk_ppm * 8ull + 999999ull) / 1000000ull + 1ull;   // in sixteenths
+    const uint64_t stage = P * (Npad / 16 * (want <= 4 ? 4 : want <= 8 ? 8 : want <= 12 ? 12 : 16));
+    t.add(stage, 4); t.add(stage, 4); t.add(stage, 4);
+    t.add(PC, 8); t.add(PC, 8); t.add(PC * (SW + 1), 4);
+    t.add(P * ktot, 4); t.add(P * ktot, 4); t.add(S, 8); t.add(S, 8);
+  }
+  return t.total;
 }
 
 static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_stream, bool use_scratch) {
@@ -426,7 +451,6 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
               !(cfg->topk_ppm && (cfg->xhat_reset || cfg->norm_mode == EVG_NORM_SEPARATE));
   bool one_launch = false;
   uint64_t need = 0;
-  uint64_t admitted = 0;
   auto cut_chunks = [&](bool on_lines) {
     chunks.clear();
     uint32_t most_sweeps = 0;
@@ -451,10 +475,8 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     one_launch = pull && !cfg->topk_ppm && cfg->norm_mode == EVG_NORM_FUSED && most_sweeps <= 128;
     need = table_bytes(P, L, chunks.size(), SW, hist_len, Npad, ktot, cfg->topk_ppm != 0,
                        cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF, pull, one_launch);
-    admitted = admitted_bytes(P, L, chunks.size(), SW, hist_len, Npad, ktot, cfg->topk_ppm,
-                              cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF, pull, one_launch);
     return (uint64_t)P * chunks.size() * (SW + 1) <= 0xFFFFFFF0ull && (uint64_t)P * ktot <= 0xFFFFFFF0ull &&
-           !(use_scratch && std::max(need, admitted) > kScratchBytes);
+           !(use_scratch && need > kScratchBytes);
   };
   c->on_lines = !c->cached && cut_chunks(true);
   if (!c->on_lines) (void)cut_chunks(false);
@@ -510,7 +532,10 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   } while (0)
   HIP_OR_FREE(hipGetDevice(&dev));
   if (use_scratch) {
-    need = std::max(need, admitted);
+    uint64_t plain_C = 0;
+    for (uint64_t n : c->numel) plain_C += (n + ce - 1) / ce;
+    need = std::max(need, admitted_bytes(P, L, plain_C, SW, hist_len, Npad, ktot, cfg->topk_ppm,
+                                         cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF, pull && !cfg->topk_ppm, one_launch));
     if (need > kScratchBytes) {
       evg_destroy(c);
       return fail(EVG_ERR_INVALID, "this configuration needs %llu bytes of tables; the static scratch block "
@@ -597,7 +622,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     TRY_OR_FREE(c->dalloc(&t.sel_cut, S, true));
     TRY_OR_FREE(c->dalloc(&t.stage_n, P * C, true));
     TRY_OR_FREE(c->dalloc(&t.stage_key, (uint64_t)P * t.stage_stride, false));
-    TRY_OR_FREE(c->dalloc(&t.group, P * C * t.SW * 4, true));
+    TRY_OR_FREE(c->dalloc(&t.group, group_entries(P, C, Npad), true));
     TRY_OR_FREE(c->dalloc(&t.chunk_cnt, P * C, true));
     TRY_OR_FREE(c->dalloc(&t.chunk_before, P * C, true));
     TRY_OR_FREE(c->dalloc(&t.msg_idx, (uint64_t)P * ktot, true));

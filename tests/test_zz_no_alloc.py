@@ -95,3 +95,16 @@ def test_configuration_beyond_the_block_is_rejected(evg):
     r.step(0)
     r.synchronize()
     r.close()
+
+
+# What is admitted does not change with the tables' present sizes: one long tensor, many tiny ones, whole sends of many
+# tensors, each at the last size that has always been admitted and at the first that never was.
+@pytest.mark.parametrize("P,most,more,kw,over", [
+    (8, [2_178_496], [2_178_560], dict(topk_ppm=100_000), dict(chunk_elems=8192)),
+    (3, [4] * 2630, [4] * 2631, dict(topk_ppm=100_000), dict(chunk_elems=8192)),
+    (16, [4] * 62_112, [4] * 62_113, dict(), dict(chunk_elems=1024, access_mode=1))], ids=["long", "tiny", "whole"])
+def test_the_largest_configurations_admitted(evg, P, most, more, kw, over):
+    with pytest.raises(evg.EvgError) as ei:
+        evg.Ring.from_workload(workload(P, more, **kw), static_tables=True, **over)
+    assert ei.value.status == 1 and "static scratch block" in str(ei.value)
+    run_pair(evg, workload(P, most, **kw), 5, **over).close()
