@@ -118,7 +118,9 @@ typedef struct {
                                    EVG_ACCESS_STREAM: non-temporal (rings far larger than the
                                    caches); EVG_ACCESS_CACHED: ordinary accesses (rings that fit
                                    the 256 MB last-level cache); EVG_ACCESS_AUTO: cached if the
-                                   five arenas together take at most 128 MB.  In a cached ring
+                                   five arenas together take at most 128 MB.  Top-K rings without
+                                   delivery delay are streamed, whatever is asked for, if seven
+                                   arenas take more than 256 MB.  In a cached ring
                                    without delivery delay each receiver fetches what its neighbours
                                    send inside the update pass, from a copy of x the library keeps
                                    (two more arrays of the ring's size, library-owned); not where

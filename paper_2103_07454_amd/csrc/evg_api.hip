@@ -408,9 +408,6 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   c->cfg.layer_fan_in = nullptr;
   c->stream = static_cast<hipStream_t>(hip_stream);
   c->chunk_elems = ce;
-  // 256 MB of last-level cache on MI355X; a ring whose arenas take at most half of it is
-  // served from there and does better with ordinary than with streaming accesses
-  c->cached = cfg->access_mode == EVG_ACCESS_CACHED || (cfg->access_mode == EVG_ACCESS_AUTO && small_ring);
   const uint32_t P = cfg->P, L = cfg->L;
   std::vector<LayerDesc> layers(L);
   std::vector<ChunkDesc> chunks;
@@ -438,6 +435,13 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     c->N += n;
     off += pad_to(n, 4);
   }
+  // 256 MB of last-level cache on MI355X; a ring whose arenas take at most half of it is served from there and does better
+  // with ordinary than with streaming accesses.  A Top-K ring with copies of x has seven arenas: asked for cached
+  // accesses beyond the cache's size it is streamed all the same (8 ResNet-18 workers of width 22, 240 MB: cached and with copies
+  // 153 us a step, streamed 119; of width 64 on 16 1092 instead of 2061).
+  const bool topk_now = cfg->topk_ppm && !cfg->delivery_delay;
+  const bool copies_fit = 7 * arena_bytes <= (256ull << 20);
+  c->cached = cfg->access_mode == EVG_ACCESS_AUTO ? small_ring : cfg->access_mode == EVG_ACCESS_CACHED && (!topk_now || copies_fit);
   // Streaming rings: sweeps begin on cache lines.  A network whose widths are no multiples of 32 has its
   // tensors anywhere on multiples of 16 bytes; wavefronts then share the lines where they meet and write
   // parts of them.  Step times without -> with, whole sends: ResNet-18 of width 62, 16 workers 1031 -> 945 us;
