@@ -118,14 +118,16 @@ typedef struct {
                                    EVG_ACCESS_STREAM: non-temporal (rings far larger than the
                                    caches); EVG_ACCESS_CACHED: ordinary accesses (rings that fit
                                    the 256 MB last-level cache); EVG_ACCESS_AUTO: cached if the
-                                   five arenas together take at most 128 MB.  Top-K rings without
-                                   delivery delay are streamed, whatever is asked for, if seven
-                                   arenas take more than 256 MB.  In a cached ring
+                                   five arenas together take at most 128 MB, or 220 MB for Top-K
+                                   rings without delivery delay whose tensors make fewer than 600
+                                   pieces of 1024 elements.  Larger ones of these rings are streamed
+                                   also where EVG_ACCESS_CACHED is asked for, if seven arenas take
+                                   more than 256 MB.  In a cached ring
                                    without delivery delay each receiver fetches what its neighbours
                                    send inside the update pass, from a copy of x the library keeps
                                    (two more arrays of the ring's size, library-owned); not where
                                    Top-K messages are sent and xhat_reset or EVG_NORM_SEPARATE is
-                                   set.  If such a ring sends whole tensors, its norms are
+                                   set or seven arenas exceed 256 MB.  If such a ring sends whole tensors, its norms are
                                    accumulated by the update pass (norm_mode) and no tensor is
                                    longer than 131 072 elements, evg_step is then ONE kernel launch:
                                    the update pass runs the trigger tests itself.  evg_step_next

@@ -439,9 +439,18 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   // with ordinary than with streaming accesses.  A Top-K ring with copies of x has seven arenas: asked for cached
   // accesses beyond the cache's size it is streamed all the same (8 ResNet-18 workers of width 22, 240 MB: cached and with copies
   // 153 us a step, streamed 119; of width 64 on 16 1092 instead of 2061).
+  // Few windows (1024 elements of a tensor) leave a walking pass, which goes from worker to worker, short of workgroups,
+  // and Top-K rings of up to 220 MB with fewer than 600 of them do better with cached accesses: 40 ResNet-18 workers of width 8 (134
+  // MB) 128 us a step against 194 streamed, with messages put into the mailboxes ahead of the update pass where the
+  // copies do not fit 64 of width 8 (215 MB) 197 against 262, 24 perceptrons of width 512 (186 MB) 110 against 132; but 24 of width
+  // 14 (246 MB) 180 against 172, 64 perceptrons of width 256 (248 MB) 157 against 151.
   const bool topk_now = cfg->topk_ppm && !cfg->delivery_delay;
   const bool copies_fit = 7 * arena_bytes <= (256ull << 20);
-  c->cached = cfg->access_mode == EVG_ACCESS_AUTO ? small_ring : cfg->access_mode == EVG_ACCESS_CACHED && (!topk_now || copies_fit);
+  uint64_t windows = 0;
+  for (const LayerDesc& d : layers) windows += ((uint64_t)d.numel + d.off % kLineElems + kSweep - 1) / kSweep;
+  const bool few = topk_now && windows < 600 && 5 * arena_bytes <= (220ull << 20);
+  c->cached = cfg->access_mode == EVG_ACCESS_AUTO ? small_ring || few
+                                                  : cfg->access_mode == EVG_ACCESS_CACHED && (!topk_now || copies_fit || few);
   // Streaming rings: sweeps begin on cache lines.  A network whose widths are no multiples of 32 has its
   // tensors anywhere on multiples of 16 bytes; wavefronts then share the lines where they meet and write
   // parts of them.  Step times without -> with, whole sends: ResNet-18 of width 62, 16 workers 1031 -> 945 us;
@@ -452,7 +461,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   // not hold what the message was told from.  Nor of rings with a norm pass of their own, in which nothing else is
   // carried from step to step: a caller may have written x since the copies were made, and the sender goes by x.
   bool pull = c->cached && !cfg->delivery_delay &&
-              !(cfg->topk_ppm && (cfg->xhat_reset || cfg->norm_mode == EVG_NORM_SEPARATE));
+              !(cfg->topk_ppm && (cfg->xhat_reset || cfg->norm_mode == EVG_NORM_SEPARATE || !copies_fit));
   bool one_launch = false;
   uint64_t need = 0;
   auto cut_chunks = [&](bool on_lines) {
@@ -494,8 +503,6 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   // ResNet-18 of width 10 (268) on 50 123 / 116 / 108 / 107, of width 14 (524) on 40 154 / 149 / 143 / 145, of width
   // 20 (1069) on 20 131 / 138 / 140 / 149; a perceptron of 116 windows on 64 workers 70 / 68 / 61 / 57, of 388
   // 140 / 156 / 148 / 145.
-  uint64_t windows = 0;
-  for (const ChunkDesc& cd : chunks) windows += (cd.lead + cd.len + kSweep - 1) / kSweep;
   const uint64_t parts = windows < 600 ? (2048 + windows - 1) / windows : 1;
   c->part = P < 16 ? P : std::max<uint32_t>(8u, (uint32_t)((P + parts - 1) / parts));
   if (c->part > P) c->part = P;
