@@ -68,6 +68,7 @@ struct evg_ctx {
   hipStream_t stream = nullptr;
   Tables t{};
   uint32_t chunk_elems = 8192;
+  uint32_t asked_SW = 8;            // sweeps of the chunks asked for (shorter ones if the static block has no room for them)
   std::vector<uint64_t> numel;      // per tensor
   std::vector<uint32_t> K;          // per tensor Top-K message length
   std::vector<uint32_t> msg_off;
@@ -296,7 +297,7 @@ static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uin
   if (topk) {
     t.add(S * kHistBins, 4); t.add(S, 4); t.add(S, 4); t.add(S, 4); t.add(PC, 4);   // hist, selection, stage_n
     t.add(P * (Npad / 16 * 4), 4);                               // stage_key
-    t.add(group_entries(P, C, Npad), 4); t.add(PC, 8); t.add(PC, 8);                // group, chunk_cnt, chunk_before
+    t.add(PC * SW * 4, 4); t.add(PC, 8); t.add(PC, 8);           // group, chunk_cnt, chunk_before
     t.add(P * ktot, 4); t.add(P * ktot, 4); t.add(S, 8); t.add(S, 8);
   }
   return t.total;
@@ -305,8 +306,9 @@ static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uin
 // What evg_init_static admits is part of its interface, and older than the present tables: it is reckoned with those of the
 // library's first version, whose tensors were cut at their own starts (C chunks a worker), with lists of fired
 // chunks, and for Top-K with three words for each possible winner (one and a half times the Top-K share plus a
-// sixteenth, in quarters of the ring), but without copies of x.  Whatever it admits has room: at most one word more
-// for each 256 elements and 28 bytes a chunk, where the old lists took 2 bytes for each element, or 36 and more a chunk.
+// sixteenth, in quarters of the ring), but without copies of x.  Whatever it admits has room, in chunks of 1024 elements if
+// need be: those take 44 bytes each besides a quarter of the staging words, where the old lists took at least 48 a
+// chunk and 2 more for each element (Top-K; whole sends need less than they did).
 static uint64_t admitted_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uint64_t hist_len, uint64_t Npad,
                                uint64_t ktot, uint32_t topk_ppm, bool norm_diff, bool whole_copies, bool one_launch) {
   const uint64_t S = P * L, PC = P * C;
@@ -383,7 +385,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   // rings that live in the last-level cache are bound by launch and workgroup counts, not by
   // HBM: small granules leave fewer empty sweeps behind their many short tensors (measured)
   const bool small_ring = 5 * arena_bytes <= (128ull << 20);
-  const uint32_t ce = cfg->chunk_elems ? cfg->chunk_elems : small_ring ? 2048u : 8192u;
+  uint32_t ce = cfg->chunk_elems ? cfg->chunk_elems : small_ring ? 2048u : 8192u;
   const float* arenas[5] = {cfg->x, cfg->xhat, cfg->mbox_l, cfg->mbox_r, cfg->vel};
   static const char* names[5] = {"x", "xhat", "mbox_l", "mbox_r", "vel"};
   for (int i = 0; i < 5; ++i) {
@@ -407,7 +409,6 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   c->cfg.layer_numel = nullptr;
   c->cfg.layer_fan_in = nullptr;
   c->stream = static_cast<hipStream_t>(hip_stream);
-  c->chunk_elems = ce;
   const uint32_t P = cfg->P, L = cfg->L;
   std::vector<LayerDesc> layers(L);
   std::vector<ChunkDesc> chunks;
@@ -456,7 +457,9 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   // parts of them.  Step times without -> with, whole sends: ResNet-18 of width 62, 16 workers 1031 -> 945 us;
   // width 28, 60 workers 843 -> 771 us; width 40, 30 workers 871 -> 796 us.  Not where the additional chunks
   // would take the tables past a limit.
-  const uint32_t hist_len = cfg->thr_mode == EVG_THR_ADAPTIVE ? cfg->hist_len : 1, SW = ce / (uint32_t)kSweep;
+  const uint32_t hist_len = cfg->thr_mode == EVG_THR_ADAPTIVE ? cfg->hist_len : 1;
+  const uint32_t ce_asked = ce;
+  uint32_t SW = ce / (uint32_t)kSweep;
   // Receivers fetch the sends from copies of x.  Not Top-K sends of rings whose xhat is reset at events: a mailbox then does
   // not hold what the message was told from.  Nor of rings with a norm pass of their own, in which nothing else is
   // carried from step to step: a caller may have written x since the copies were made, and the sender goes by x.
@@ -497,6 +500,13 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     pull = false;                                                        // by a kernel of their own
     (void)cut_chunks(false);
   }
+  if (use_scratch && need > kScratchBytes && cfg->topk_ppm && SW > 1) {   // thousands of short tensors: their chunks have as many
+    ce = kSweep;                                                          // counts as long ones
+    SW = 1;
+    (void)cut_chunks(false);
+  }
+  c->chunk_elems = ce;
+  c->asked_SW = ce_asked / (uint32_t)kSweep;
   // One workgroup per window and the whole ring, if that is enough of them for the 256 CUs; few windows (and then
   // many workers) are better walked in parts, although the sends of the workers at their ends need a pass of
   // their own.  1 / 2 / 4 / 8 parts: ResNet-20 of width 20 (414 windows) on 64 workers 216 / 202 / 186 / 184 us,
@@ -544,8 +554,8 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   HIP_OR_FREE(hipGetDevice(&dev));
   if (use_scratch) {
     uint64_t plain_C = 0;
-    for (uint64_t n : c->numel) plain_C += (n + ce - 1) / ce;
-    need = std::max(need, admitted_bytes(P, L, plain_C, SW, hist_len, Npad, ktot, cfg->topk_ppm,
+    for (uint64_t n : c->numel) plain_C += (n + ce_asked - 1) / ce_asked;
+    need = std::max(need, admitted_bytes(P, L, plain_C, c->asked_SW, hist_len, Npad, ktot, cfg->topk_ppm,
                                          cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF, pull && !cfg->topk_ppm, one_launch));
     if (need > kScratchBytes) {
       evg_destroy(c);
@@ -633,7 +643,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     TRY_OR_FREE(c->dalloc(&t.sel_cut, S, true));
     TRY_OR_FREE(c->dalloc(&t.stage_n, P * C, true));
     TRY_OR_FREE(c->dalloc(&t.stage_key, (uint64_t)P * t.stage_stride, false));
-    TRY_OR_FREE(c->dalloc(&t.group, group_entries(P, C, Npad), true));
+    TRY_OR_FREE(c->dalloc(&t.group, P * C * t.SW * 4, true));
     TRY_OR_FREE(c->dalloc(&t.chunk_cnt, P * C, true));
     TRY_OR_FREE(c->dalloc(&t.chunk_before, P * C, true));
     TRY_OR_FREE(c->dalloc(&t.msg_idx, (uint64_t)P * ktot, true));
@@ -945,7 +955,7 @@ struct StateHeader {
   int64_t last_iter;
 };
 
-constexpr uint32_t kCutOnLines = 1u << 16;   // StateHeader::pad, from version 5 on
+constexpr uint32_t kCutOnLines = 1u << 16, kCutFiner = 1u << 17;   // StateHeader::pad, from version 5 on
 
 struct Piece { void* dev; size_t bytes; };
 
@@ -974,7 +984,8 @@ StateHeader state_header(evg_ctx* c) {
   h.trigger_kind = c->cfg.trigger_kind;
   h.norm_mode = c->cfg.norm_mode;
   h.thr_mode = c->cfg.thr_mode;
-  h.pad = c->cfg.delivery_delay | (c->cfg.xhat_reset << 8) | (c->on_lines ? kCutOnLines : 0u);
+  h.pad = c->cfg.delivery_delay | (c->cfg.xhat_reset << 8) | (c->on_lines ? kCutOnLines : 0u) |
+          (c->t.SW != c->asked_SW ? kCutFiner : 0u);
   h.Npad = c->t.Npad;
   h.iters = c->iters;
   h.last_iter = c->last_iter;
@@ -1013,41 +1024,45 @@ evg_status evg_state_export(evg_ctx* c, void* blob, uint64_t capacity) {
 
 evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
   if (!c || !blob) return fail(EVG_ERR_INVALID, "context and blob must be non-NULL");
-  // A tensor's sums are only ever added up, so a blob serves whether its ring cut the tensors at their own starts or on cache
-  // lines; how this configuration's tensors are cut either way, in chunks per tensor:
+  // A tensor's sums are only ever added up, so a blob serves however its ring cut the tensors: at their own starts or on cache
+  // lines, or into shorter chunks than were asked for.  A tensor's sums in chunks of SW sweeps:
   const Tables& t = c->t;
-  const uint64_t granule = (uint64_t)t.SW * kSweep;
   const size_t L = c->numel.size();
-  auto chunks_of = [&](size_t l, uint64_t off, bool on_lines) {
-    return (c->numel[l] + (on_lines ? off % kLineElems : 0) + granule - 1) / granule;
+  auto sums_of = [&](size_t l, uint64_t off, uint64_t SW, bool on_lines) {
+    const uint64_t granule = SW * kSweep;
+    return (c->numel[l] + (on_lines ? off % kLineElems : 0) + granule - 1) / granule * SW;
   };
-  uint64_t C_plain = 0, C_lines = 0, off = 0;
-  for (size_t l = 0; l < L; ++l) {
-    C_plain += chunks_of(l, off, false);
-    C_lines += chunks_of(l, off, true);
-    off += pad_to(c->numel[l], 4);
-  }
   StateHeader got;
   if (size < sizeof got) return fail(EVG_ERR_INVALID, "blob size does not match this configuration");
   std::memcpy(&got, blob, sizeof got);
-  const bool same_cut = got.C == t.C;
-  const bool maybe_lines = got.version == 4 || (got.version > 4 && (got.pad & kCutOnLines));   // (version 4 does not say)
-  const uint64_t sums = t.partials_hat ? 2 : 1, per_chunk = (uint64_t)t.P * t.SW * 8 * sums;
-  if (got.C != C_plain && !(maybe_lines && got.C == C_lines))
+  const uint32_t flags = got.version > 4 ? got.pad & (kCutOnLines | kCutFiner) : 0u;
+  if (got.SW != t.SW && !(flags & kCutFiner && got.SW == 1) && got.SW != c->asked_SW)
+    return fail(EVG_ERR_INVALID, "blob was exported from a different configuration or version");
+  uint64_t plain = 0, lines = 0, off = 0;        // sums per worker
+  for (size_t l = 0; l < L; ++l) {
+    plain += sums_of(l, off, got.SW, false);
+    lines += sums_of(l, off, got.SW, true);
+    off += pad_to(c->numel[l], 4);
+  }
+  const uint64_t here = (uint64_t)t.C * t.SW, there = (uint64_t)got.C * got.SW;
+  const bool same_cut = got.C == t.C && got.SW == t.SW, from_lines = there != plain;
+  const bool maybe_lines = got.version == 4 || (flags & kCutOnLines);     // (version 4 does not say)
+  if (there != plain && !(maybe_lines && there == lines))
     return fail(EVG_ERR_INVALID, "blob was exported from a different configuration or version");
   // version 3 has three more words, lengths of lists that are no longer kept, ahead of the count of chunks not staged
-  const uint64_t list_bytes = got.version == 3 ? 12 : 0;
-  if (size != evg_state_size(c) - t.C * per_chunk + got.C * per_chunk + list_bytes)
+  const uint64_t list_bytes = got.version == 3 ? 12 : 0, per_sum = (uint64_t)t.P * 8 * (t.partials_hat ? 2 : 1);
+  if (size != evg_state_size(c) - here * per_sum + there * per_sum + list_bytes)
     return fail(EVG_ERR_INVALID, "blob size does not match this configuration");
   StateHeader want = state_header(c);
   want.C = got.C;
+  want.SW = got.SW;
   if (got.version == 3 || got.version == 4) want.version = got.version;
-  want.pad = (want.pad & ~kCutOnLines) | (got.version <= 4 ? 0u : got.pad & kCutOnLines);
+  want.pad = (want.pad & ~(kCutOnLines | kCutFiner)) | flags;
   want.iters = got.iters;
   want.last_iter = got.last_iter;
   if (std::memcmp(&got, &want, sizeof got) != 0)
     return fail(EVG_ERR_INVALID, "blob was exported from a different configuration or version");
-  const size_t sum_count = (size_t)t.P * t.C * t.SW;
+  const size_t sum_count = (size_t)t.P * here;
   std::unique_ptr<double[]> moved(same_cut ? nullptr : new (std::nothrow) double[sum_count]);
   if (!same_cut && !moved) return fail(EVG_ERR_OOM, "host allocation failed");
   // Everything goes through the context's stream, and is waited for: steps on a non-blocking stream do not wait for copies
@@ -1063,7 +1078,7 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
       for (uint32_t r = 0; r < t.P; ++r) {
         off = 0;
         for (size_t l = 0; l < L; ++l) {
-          const uint64_t from = chunks_of(l, off, !c->on_lines) * t.SW;
+          const uint64_t from = sums_of(l, off, got.SW, from_lines);
           const uint64_t used = (c->numel[l] + (c->on_lines ? off % kLineElems : 0) + kSweep - 1) / kSweep;
           for (uint64_t i = 0; i < from; ++i) {
             double v;
@@ -1071,7 +1086,7 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
             in += 8;
             to[std::min(i, used - 1)] += v;
           }
-          to += chunks_of(l, off, c->on_lines) * t.SW;
+          to += sums_of(l, off, t.SW, c->on_lines);
           off += pad_to(c->numel[l], 4);
         }
       }

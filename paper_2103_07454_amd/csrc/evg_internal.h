@@ -38,14 +38,6 @@ struct LayerDesc {
   double sig_base;   // sigma0 [/ sqrt(fan_in)]
 };
 
-// Counts per group of 256 positions of a chunk (Tables::group): a worker's chunks have theirs one after the other, chunk c from
-// offset / 256 + 2 c on.  They do not overlap: a chunk of n elements and a lead of at most 28 has at most n / 256 + 2 groups (rounded
-// down), and the next one begins at least n elements later.  Wavefronts past a chunk's end read what they don't use:
-// 32 entries more, a chunk's most groups.
-__host__ __device__ inline uint64_t group_stride(uint64_t C, uint64_t Npad) { return Npad / 256 + 2 * C; }
-__host__ __device__ inline uint64_t group_entries(uint64_t P, uint64_t C, uint64_t Npad) { return P * group_stride(C, Npad) + 32; }
-__host__ __device__ inline uint32_t group_count(const ChunkDesc& cd) { return (cd.lead + cd.len + 255) / 256; }
-
 // The iteration as the device knows it.  evg_step passes the iteration by value; a step
 // that must be replayable from a captured graph (evg_step_next) reads it from here instead.
 struct IterState {
@@ -89,7 +81,7 @@ struct Tables {
                            // chunk's slot holds, nothing staged (they are then read from the arenas)
   uint32_t* stage_key;     // [P*stage_stride] their low 20 bits, and the group in the chunk they belong to
   uint64_t stage_stride;   // staging entries per worker
-  uint32_t* group;         // [group_entries] per 256 positions of a chunk: keys above the threshold bin; in the end, over the chunk's
+  uint32_t* group;         // [P*C*SW*4] per 256 elements: keys above the threshold bin; in the end, over the chunk's
                            // earlier groups, keys above (low half) and equal to (high half) the threshold
   uint2* chunk_cnt;        // [P*C] keys above and equal to the threshold per chunk
   uint2* chunk_before;     // [P*C] the same, summed over the tensor's earlier chunks

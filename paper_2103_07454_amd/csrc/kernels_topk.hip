@@ -167,8 +167,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_stage(Tables T, StepArgs A) {
   const uint32_t code = T.fired[wi.seg];      // uniform
   if (COPY && code == 1 && (COPY == 1 || is_led(T, A, wi.r))) copy_chunk<SWEEPS, STREAM, COPY == 2>(T, wi.r, wi.cd);
   if (code != 2) return;
-  const uint32_t bin = T.sel_prefix[wi.seg], n_groups = group_count(wi.cd);
-  uint32_t* group = groups_of(T, wi.r, wi.c, wi.cd.off);
+  const uint32_t bin = T.sel_prefix[wi.seg];
   if (threadIdx.x == 0) listed = 0;
   for (uint32_t b = threadIdx.x; b < (uint32_t)kHistBins; b += kThreads) h[b] = 0;
   __syncthreads();
@@ -203,7 +202,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_stage(Tables T, StepArgs A) {
         if (valid && (key[u][q] >> 20) == bin) atomicAdd(&h[(key[u][q] >> 9) & 2047u], 1u);
         n_in[u] += __popcll(in[u][q]);
       }
-      if (lane_id() == 0 && (it + u) * 4 + wave_id() < n_groups) group[(it + u) * 4 + wave_id()] = above;
+      if (lane_id() == 0) T.group[(size_t)wi.w * (T.SW * 4) + (it + u) * 4 + wave_id()] = above;
       n_all += n_in[u];
     }
     uint32_t at = 0;
@@ -324,8 +323,8 @@ __global__ __launch_bounds__(kThreads) void k_topk_count(Tables T, StepArgs A) {
   WorkItem wi;
   if (!wave_item(T, &wi)) return;
   uint32_t* cnt = counts[wave_id()];
-  const uint32_t t = T.sel_prefix[wi.seg], lane = lane_id(), G = group_count(wi.cd);
-  uint32_t* group = groups_of(T, wi.r, wi.c, wi.cd.off);
+  const uint32_t t = T.sel_prefix[wi.seg], lane = lane_id(), G = T.SW * 4;
+  uint32_t* group = T.group + (size_t)wi.w * G;
   const uint32_t above = lane < G ? group[lane] : 0u;
   cnt[lane] = 0;
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -351,7 +350,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_count(Tables T, StepArgs A) {
 __global__ __launch_bounds__(64) void k_topk_scan(Tables T, StepArgs A) {
   const uint32_t seg = blockIdx.x, lane = threadIdx.x;
   if (T.fired[seg] != 2) return;
-  const uint32_t r = seg / T.L, ties = T.sel_krem[seg], t = T.sel_prefix[seg];
+  const uint32_t r = seg / T.L, ties = T.sel_krem[seg], t = T.sel_prefix[seg], G = T.SW * 4;
   const LayerDesc ld = T.layers[seg % T.L];
   const uint32_t first = r * T.C + ld.chunk0;
   uint32_t carry_g = 0, carry_e = 0, crossing = 0, need = 0;
@@ -388,7 +387,7 @@ __global__ __launch_bounds__(64) void k_topk_scan(Tables T, StepArgs A) {
   }
   // the last group that begins before the last winning tie holds it
   const ChunkDesc cd = T.chunks[ld.chunk0 + crossing];
-  const uint32_t before = lane < group_count(cd) ? groups_of(T, r, ld.chunk0 + crossing, cd.off)[lane] >> 16 : 0xFFFFu;
+  const uint32_t before = lane < G ? T.group[(size_t)(first + crossing) * G + lane] >> 16 : 0xFFFFu;
   const uint32_t g = (uint32_t)__popcll(__ballot(before < need)) - 1;
   uint32_t left = need - (uint32_t)__builtin_amdgcn_readlane((int)before, (int)g), k[4];
   bool ok[4];
@@ -423,7 +422,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_apply(Tables T, StepArgs A) {
     float ha[4] = {h4.x, h4.y, h4.z, h4.w};
     const uint32_t nv = !live ? 0u : wi.cd.len - e < 4u ? wi.cd.len - e : 4u;
     const uint32_t win = winners4(xa, ha, A.topk_key, t, cut, wi.cd.j0 + e, nv);
-    put_message(T, wi.r, ld.msg_off, message_place(T, wi.r, wi.c, wi.cd.off, it * 4 + wave_id(), T.sel_krem[wi.seg]), win, xa, wi.cd.j0 + e);
+    put_message(T, wi.r, ld.msg_off, message_place(T, wi.w, it * 4 + wave_id(), T.sel_krem[wi.seg]), win, xa, wi.cd.j0 + e);
     const bool changes = any_of_line_part(win) && live;
     if (LEAD) {
       take_winners(win, xa, ha);

@@ -164,7 +164,7 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
       for (int i = 0; i < 3; ++i) { thr[i] = T.sel_prefix[segs[i]]; cut[i] = T.sel_cut[segs[i]]; }
       moff = T.layers[cd.layer].msg_off;
 #pragma unroll
-      for (int u = 0; u < SPW; ++u) place[u] = message_place(T, r, c, cd.off, (sub0 + u) * 4 + wave_id(), T.sel_krem[seg]);
+      for (int u = 0; u < SPW; ++u) place[u] = message_place(T, r * T.C + c, (sub0 + u) * 4 + wave_id(), T.sel_krem[seg]);
     }
     auto receive = [&](uint32_t thr, uint32_t cut, const float (*sx)[4], float* mbox, float (*a)[4]) {
 #pragma unroll

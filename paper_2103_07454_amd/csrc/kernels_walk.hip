@@ -125,7 +125,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
       else if (TOPK && code == 2) {
         m.thr = T.sel_prefix[seg];
         m.cut = T.sel_cut[seg];
-        m.place = message_place(T, s, c, cd.off, sub0 * 4 + wave_id(), T.sel_krem[seg]);
+        m.place = message_place(T, s * T.C + c, sub0 * 4 + wave_id(), T.sel_krem[seg]);
       }
     }
     return m;
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
     if (TOPK && f_b == 2) {
       thr_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)T.sel_prefix[seg_b]);
       cut_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)T.sel_cut[seg_b]);
-      place_b = message_place(T, before, c, cd.off, sub0 * 4 + wave_id(), T.sel_krem[seg_b]);
+      place_b = message_place(T, before * T.C + c, sub0 * 4 + wave_id(), T.sel_krem[seg_b]);
     }
     const uint32_t f0 = read_mark(cur.f, nxt.f, 0);
     const Quad h_last = load_quad(at(T.xhat, before), reads_hat(f_b) ? nb : 0u, byte);

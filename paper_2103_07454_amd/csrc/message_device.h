@@ -36,16 +36,11 @@ __device__ __forceinline__ bool any_of_line_part(uint32_t any) {
   return any != 0;
 }
 
-// Worker r's counts per group of chunk c, which begins at off.
-__device__ __forceinline__ uint32_t* groups_of(const Tables& T, uint32_t r, uint32_t c, uint32_t off) {
-  return T.group + (size_t)r * group_stride(T.C, T.Npad) + (off >> 8) + 2 * (size_t)c;
-}
-
-// Winners of worker r's tensor before group g of chunk c, which begins at off (ties: how many keys equal to the
-// threshold win).
-__device__ __forceinline__ uint32_t message_place(const Tables& T, uint32_t r, uint32_t c, uint32_t off, uint32_t g, uint32_t ties) {
-  const uint2 before = T.chunk_before[(size_t)r * T.C + c];
-  const uint32_t in_chunk = groups_of(T, r, c, off)[g], equal = before.y + (in_chunk >> 16);
+// Winners of the tensor before a group of 256 elements (chunk w of all workers' chunks, group g of the chunk; ties: how
+// many keys equal to the threshold win).
+__device__ __forceinline__ uint32_t message_place(const Tables& T, uint32_t w, uint32_t g, uint32_t ties) {
+  const uint2 before = T.chunk_before[w];
+  const uint32_t in_chunk = T.group[(size_t)w * (T.SW * 4) + g], equal = before.y + (in_chunk >> 16);
   return before.x + (in_chunk & 0xFFFFu) + (equal < ties ? equal : ties);
 }
 

@@ -34,7 +34,7 @@ def workload(P, sizes, **kw):
     return inputs.Workload("static", P, tensors, 14, **base)
 
 
-def run_pair(evg, w, iters, **over):
+def run_pair(evg, w, iters, same_tables=True, **over):
     import torch
     x0 = inputs.replicate(w.x0(), w.P)
     a = evg.Ring.from_workload(w, x0, mailbox_fill=float("nan"), static_tables=True, **over)
@@ -52,7 +52,8 @@ def run_pair(evg, w, iters, **over):
             assert np.array_equal(ha[0], hb[0]) and np.array_equal(ha[1], hb[1]), k
     sa, sb = a.stats(arrays=True), b.stats(arrays=True)
     for key in sa:
-        assert np.array_equal(sa[key], sb[key]), key
+        if same_tables or key not in ("library_bytes", "chunks_not_staged"):
+            assert np.array_equal(sa[key], sb[key]), key
     assert sa["events_total"] > w.P * w.L
     for name in ARENAS:
         ta, tb = getattr(a, name), getattr(b, name)
@@ -98,7 +99,8 @@ def test_configuration_beyond_the_block_is_rejected(evg):
 
 
 # What is admitted does not change with the tables' present sizes: one long tensor, many tiny ones, whole sends of many
-# tensors, each at the last size that has always been admitted and at the first that never was.
+# tensors, each at the last size that has always been admitted and at the first that never was.  (The chunks may be shorter
+# than evg_init's; a state blob goes either way all the same.)
 @pytest.mark.parametrize("P,most,more,kw,over", [
     (8, [2_178_496], [2_178_560], dict(topk_ppm=100_000), dict(chunk_elems=8192)),
     (3, [4] * 2630, [4] * 2631, dict(topk_ppm=100_000), dict(chunk_elems=8192)),
@@ -107,4 +109,19 @@ def test_the_largest_configurations_admitted(evg, P, most, more, kw, over):
     with pytest.raises(evg.EvgError) as ei:
         evg.Ring.from_workload(workload(P, more, **kw), static_tables=True, **over)
     assert ei.value.status == 1 and "static scratch block" in str(ei.value)
-    run_pair(evg, workload(P, most, **kw), 5, **over).close()
+    w = workload(P, most, **kw)
+    a = run_pair(evg, w, 5, same_tables=False, **over)
+    b = evg.Ring.from_workload(w, mailbox_fill=0.0, **over)
+    b.import_state(a.export_state())
+    for k in range(5, 8):
+        a.step(k)
+        b.step(k)
+    a.import_state(b.export_state())
+    for k in range(8, 10):
+        a.step(k)
+        b.step(k)
+    assert np.array_equal(a.decisions()["fired"], b.decisions()["fired"])
+    for name in ARENAS:
+        assert np.array_equal(a.state(name), b.state(name)), name
+    a.close()
+    b.close()
