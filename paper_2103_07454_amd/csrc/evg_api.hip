@@ -507,15 +507,27 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   }
   c->chunk_elems = ce;
   c->asked_SW = ce_asked / (uint32_t)kSweep;
-  // One workgroup per window and the whole ring, if that is enough of them for the 256 CUs; few windows (and then
-  // many workers) are better walked in parts, although the sends of the workers at their ends need a pass of
-  // their own.  1 / 2 / 4 / 8 parts: ResNet-20 of width 20 (414 windows) on 64 workers 216 / 202 / 186 / 184 us,
-  // ResNet-18 of width 10 (268) on 50 123 / 116 / 108 / 107, of width 14 (524) on 40 154 / 149 / 143 / 145, of width
-  // 20 (1069) on 20 131 / 138 / 140 / 149; a perceptron of 116 windows on 64 workers 70 / 68 / 61 / 57, of 388
-  // 140 / 156 / 148 / 145.
-  const uint64_t parts = windows < 600 ? (2048 + windows - 1) / windows : 1;
-  c->part = P < 16 ? P : std::max<uint32_t>(8u, (uint32_t)((P + parts - 1) / parts));
-  if (c->part > P) c->part = P;
+  // One workgroup per window and the whole ring, if that is enough of them for the 256 CUs; few windows are better walked in
+  // parts, although the sends of the workers at their ends need a pass of their own.  What a part costs besides grows
+  // with the windows, so a part has at least `fewest` workers, and there are no more than give `aim` workgroups (Top-K: of two
+  // windows each).  Measured with parts of 1 to all workers, us a step, whole sends: perceptrons of 28 windows on 15 workers 16 in
+  // parts of one, 24 in one part; of 102 on 24 25 in parts of two or three, 28 of eight, 35 in one; of 300 on 64 118 in
+  // parts of 6, 8 or 11, 128 in one; ResNet-20 of 326 on 64 138 of 12, 161 in one, but on 15 36 in one part, 38 of eight.  Top-K
+  // 10 %: 28 windows on 15 workers 47 and 78, 102 on 24 63 of three, 111 in one; 326 on 64 266 of 12, 331 in one; ResNet-18 of 574
+  // windows on 24 157 in one part, 172 of eight, on 64 342 of 12, 350 in one.  A compromise: a perceptron of 399 windows would be
+  // walked in one part by 40 workers in 92 us (whole sends) where parts of eight take 100.
+  uint64_t fewest = 8, aim = 2048;
+  bool one_part = windows >= 600 || P <= 5;
+  if (!cfg->topk_ppm && windows < 250) {
+    fewest = std::min<uint64_t>(8, windows / 40);
+    aim = 1536;
+  } else if (cfg->topk_ppm && windows < 250 && (P < 20 || windows < 110)) {
+    fewest = windows / 50;
+    aim = 768;
+  }
+  one_part |= cfg->topk_ppm ? windows >= 390 && 16ull * P <= windows : windows >= 110 && P < 16;
+  const uint64_t parts = one_part ? 1 : std::min((aim + windows - 1) / windows, std::max<uint64_t>(1, P / std::max<uint64_t>(1, fewest)));
+  c->part = (uint32_t)((P + parts - 1) / parts);
   const uint64_t C = chunks.size();
   if ((uint64_t)P * C * (SW + 1) > 0xFFFFFFF0ull || (uint64_t)P * ktot > 0xFFFFFFF0ull) {
     delete c;

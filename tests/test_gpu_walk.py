@@ -1,7 +1,7 @@
 """Streaming rings are updated by workgroups that walk a window around the ring, in parts where a
 network has few windows and many workers.  Checked against the oracle at the ring sizes where the walk
-can go wrong: the smallest, around the 64 workers whose marks a wavefront holds at a time, and rings
-whose last part is of one worker or a few."""
+can go wrong: the smallest, around the 64 workers whose marks a wavefront holds at a time, parts of one
+worker, and rings whose last part is of one worker or a few."""
 import pytest
 
 from paper_2103_07454_amd import inputs
@@ -30,7 +30,7 @@ def _run(evg, oracle_mod, P, numels, *, norm_mode=0, iters=7, **kw):
     assert rep["rel"]["x"] <= 1e-5 and (differ or all(rep["bitwise"].values())), rep
 
 
-# 3 .. 15 workers: one part; from 16 on parts of 8: 16 = 8 + 8, 17 = 8 + 8 + 1, 23 = 8 + 8 + 7
+# so few windows: 3 and 4 workers in one part, more in parts of one worker
 @pytest.mark.parametrize("P", [3, 4, 15, 16, 17, 23, 63, 64, 65, 66, 130])
 @pytest.mark.parametrize("kw", [dict(), dict(momentum=0.0, spike_prob=0.3, spike_gain=4.0), dict(topk_ppm=100_000),
                                 dict(topk_ppm=20_000, dist=1, topk_key=1)], ids=["whole", "plain", "topk", "topk_value"])
@@ -51,3 +51,11 @@ def test_whole_ring(evg, oracle_mod, P, topk):
 def test_norms(evg, oracle_mod, P, topk, norm_mode, trigger_kind):
     kw = dict(trigger_kind=1) if trigger_kind else {}
     _run(evg, oracle_mod, P, [9000, 33, 1024], topk_ppm=topk, norm_mode=norm_mode, **kw)
+
+
+# Tensors of one window each, and a longer one.  Of about 100 windows whole sends and Top-K go in parts of 3 workers (19 = 6 * 3 + 1),
+# 5 and 9 (65), 9 and 17 (130); of 200 in parts of 4 (16), 5 and 12 (23), 9 (66); of 330 in one part (15), of 9 (17), 10 (65).
+@pytest.mark.parametrize("windows,P", [(100, 19), (100, 65), (100, 130), (200, 16), (200, 23), (200, 66), (330, 15), (330, 17), (330, 65)])
+@pytest.mark.parametrize("kw", [dict(), dict(topk_ppm=100_000)], ids=["whole", "topk"])
+def test_parts(evg, oracle_mod, windows, P, kw):
+    _run(evg, oracle_mod, P, [1, 3, 8, 2] * ((windows - 5) // 4) + [4097], iters=5, **kw)
