@@ -201,8 +201,9 @@ enum {
                             delivery                                                  */
   EVG_PH_TOPK_SELECT = 3,/* threshold-key search for the Top-K set                   */
   EVG_PH_TOPK_SEND = 4,  /* (index, value) messages, where a kernel ahead of the update
-                            pass writes and applies them (xhat reset at events, rings
-                            walked in parts); elsewhere the update pass does          */
+                            pass writes and applies them (rings walked in parts, cached
+                            rings without copies of x, xhat reset at events in rings of
+                            few pieces); elsewhere the update pass does               */
   EVG_PH_UPDATE = 5,     /* fused averaging + momentum SGD (+ next drift norms)      */
   EVG_PH_DELIVER = 6,    /* delivery_delay = 1 only: the iteration's puts land       */
   EVG_PH_COUNT = 7

@@ -78,6 +78,7 @@ struct evg_ctx {
   int64_t last_iter = -1;
   bool messages_live = false;       // the message buffers hold the last step's messages
   bool on_lines = false;            // sweeps begin on cache lines (streaming rings)
+  bool walk = false;                // the update pass walks the ring
   uint32_t part = 0;                // workers of the ring that one workgroup of a walking pass goes through
   bool cached = false;              // the five arenas together fit the last-level cache
   bool device_ahead = false;        // evg_step_next has been used: replays of a captured graph
@@ -528,6 +529,9 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   one_part |= cfg->topk_ppm ? windows >= 390 && 16ull * P <= windows : windows >= 110 && P < 16;
   const uint64_t parts = one_part ? 1 : std::min((aim + windows - 1) / windows, std::max<uint64_t>(1, P / std::max<uint64_t>(1, fewest)));
   c->part = (uint32_t)((P + parts - 1) / parts);
+  // A mailbox equals its sender's xhat wherever a message has arrived, unless messages are under way (delay).  Where xhat is
+  // reset at events the walk reads the mailboxes, and does not know of messages applied ahead at the ends of parts.
+  c->walk = !c->cached && !cfg->delivery_delay && !(cfg->xhat_reset && cfg->topk_ppm && parts > 1);
   const uint64_t C = chunks.size();
   if ((uint64_t)P * C * (SW + 1) > 0xFFFFFFF0ull || (uint64_t)P * ktot > 0xFFFFFFF0ull) {
     delete c;
@@ -800,9 +804,7 @@ static evg_status fixed_args(evg_ctx* c, const float* grad, StepArgs* out) {
   a.hist_fused = (g.topk_ppm && g.norm_mode == EVG_NORM_FUSED) ? 1u : 0u;
   a.cached = c->cached ? 1u : 0u;
   a.pull = c->t.xsnap ? 1u : 0u;
-  // a mailbox equals its sender's xhat wherever a message has arrived, unless messages are under way
-  // (delay) or xhat moves without a message (reset)
-  a.walk = (!c->cached && !g.delivery_delay && !(g.xhat_reset && g.topk_ppm)) ? 1u : 0u;
+  a.walk = c->walk ? 1u : 0u;
   a.part = c->part;
   a.applied = (g.topk_ppm && !g.delivery_delay && !a.walk && !a.pull) ? 1u : 0u;
   a.xhat_reset = (g.xhat_reset && g.topk_ppm) ? 1u : 0u;

@@ -79,7 +79,11 @@ struct Marks { uint32_t f, thr, cut, place; };   // f: see below; Top-K: thresho
                                                  // the message of the first winner of this wavefront's group
 constexpr uint32_t kCode = 3u, kLeftFilled = 4u, kRightFilled = 8u, kSpike = 16u, kLed = 32u;
 
-template <int DIST, bool GRADBUF, int NORM, bool TOPK, bool HISTA, int W>
+// RESET (with TOPK; the whole ring in one part): an event resets the sender's xhat to x while the mailboxes take the sent
+// entries only, so a mailbox is not its sender's xhat and is read, 8 bytes more per element: its winners are taken from the
+// sender's x, which the walk has at hand.  16 ResNet-18 workers with Top-K 1 % and 10 %: 1355 and 1521 us a step, where
+// a pass ahead that puts the messages into the mailboxes and an update pass per worker take 1517 and 1817.
+template <int DIST, bool GRADBUF, int NORM, bool TOPK, bool HISTA, int W, bool RESET = false>
 __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
   constexpr uint32_t kElems = 256 * W, SPW = W / 4;
   __shared__ double ws[NORM ? 64 * W : 1], ws_hat[NORM == 3 ? 64 * W : 1];
@@ -139,10 +143,22 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
 
   // What worker s's neighbours hold of it from this iteration on, written to its xhat (to_hat bytes) and its
   // neighbours' mailboxes (to_right, to_left bytes) if it sends.
+  // RESET: to its xhat only; `sent`, one bit per element, says what the neighbours take.
+  uint32_t sent = 0;
   auto send = [&](uint32_t s, uint32_t f, uint32_t thr, uint32_t cut, uint32_t place, uint32_t to_hat, uint32_t to_left, uint32_t to_right,
                   const Quad& x, const Quad& h) {
     Quad q;
     uint32_t where = byte;
+    if (RESET) {
+      const uint32_t win = winners4(x.v, h.v, A.topk_key, thr, cut, j, nv);
+      if (to_hat) put_message(T, s, msg_off, place, win, x.v, j);
+      const bool sends = (f & kCode) != 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) q.v[i] = sends ? x.v[i] : h.v[i];
+      store_quad(at(T.xhat, s), sends ? to_hat : 0u, byte, q);
+      sent = (f & kCode) == 1 ? (1u << nv) - 1u : win;
+      return q;
+    }
     const bool led = (f & kLed) != 0, whole = (f & kCode) == 1 && !led;
     if (TOPK) {
       // (workers at the ends of parts: k_topk_apply has done all this but the mailboxes)
@@ -178,6 +194,14 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
   // first two that are loaded and stays in registers, an open part ends with the xhat of the worker after it.
   const uint32_t last_x = closed ? n - 2 : n - 1, last_h = closed ? n - 2 : n;
   Quad x1{}, h1{}, v1{}, g1{}, xc{}, ec{}, el{}, x_last{}, e_last{}, e_first{};
+  // RESET: the next worker's mailboxes; x before its update, and what it sent, of the worker before, the first and the last
+  Quad ml1{}, mr1{}, xl{}, x_first{};
+  uint32_t sent_l = 0, sent_c = 0, sent_first = 0, sent_last = 0;
+  auto mailbox = [&](float* m, uint32_t s, uint32_t f, uint32_t filled) { return load_quad(at(m, s), f & filled ? nb : 0u, byte); };
+  auto receive = [&](float* m, uint32_t s, uint32_t sent, const Quad& from, Quad& held) {
+    take_winners(sent, from.v, held.v);
+    store_quad(at(m, s), nb, any_of_line_part(sent) ? byte : kNowhere, held);
+  };
   if (!dead) {
     const uint32_t before = r0 == 0 ? P - 1 : r0 - 1;
     x_last = load_quad(at(T.x, before), closed ? nb : 0u, byte);
@@ -198,9 +222,21 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
     const Quad h_last = load_quad(at(T.xhat, before), reads_hat(f_b) ? nb : 0u, byte);
     const Quad h0 = load_quad(at(T.xhat, r0), reads_hat(f0) ? nb : 0u, byte);
     h1 = load_quad(at(T.xhat, worker(1)), 1 <= last_h && reads_hat(read_mark(cur.f, nxt.f, 1)) ? nb : 0u, byte);
+    if (RESET) {
+      ml1 = mailbox(T.mbox_l, r0, f0, kLeftFilled);
+      mr1 = mailbox(T.mbox_r, r0, f0, kRightFilled);
+    }
     e_last = send(before, f_b, thr_b, cut_b, place_b, closed ? nb : 0u, closed ? nb : 0u, nb, x_last, h_last);
+    sent_last = sent;
     e_first = send(r0, f0, read_mark(cur.thr, nxt.thr, 0), read_mark(cur.cut, nxt.cut, 0), read_mark(cur.place, nxt.place, 0), nb, closed ? nb : 0u,
                    closed || n > 1 ? nb : 0u, xc, h0);
+    sent_first = sent;
+    if (RESET) {
+      xl = x_last;
+      x_first = xc;
+      sent_l = sent_last;
+      sent_c = sent_first;
+    }
     el = e_last;
     ec = e_first;
   }
@@ -215,6 +251,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
     if (!dead) {
       // the next worker's values have arrived: take them, and ask for those of the one after it
       Quad xn = taken(x1), hn = taken(h1), vel = taken(v1), g = GRADBUF ? taken(g1) : g1;
+      Quad ml = RESET ? taken(ml1) : ml1, mr = RESET ? taken(mr1) : mr1;
       const uint32_t f2 = read_mark(cur.f, nxt.f, i + 2);
       const uint32_t s1 = worker(i + 1), s2 = i + 2 <= n ? worker(i + 2) : 0u;
       const bool another = i + 1 < n;
@@ -222,12 +259,24 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
       h1 = load_quad(at(T.xhat, s2), i + 2 <= last_h && reads_hat(f2) ? nb : 0u, byte);
       v1 = load_quad(at(T.vel, another ? r + 1 : 0), another ? nb_vel : 0u, byte);
       if (GRADBUF) g1 = load_quad(A.grad + (size_t)(another ? r + 1 : 0) * T.Npad + off, another ? nb : 0u, byte);
+      if (RESET) {
+        ml1 = mailbox(T.mbox_l, another ? r + 1 : 0, another ? fn : 0u, kLeftFilled);
+        mr1 = mailbox(T.mbox_r, another ? r + 1 : 0, another ? fn : 0u, kRightFilled);
+      }
       Quad en = send(s1, fn, read_mark(cur.thr, nxt.thr, i + 1), read_mark(cur.cut, nxt.cut, i + 1),
                      read_mark(cur.place, nxt.place, i + 1), i + 1 <= last_x ? nb : 0u, i + 1 <= last_h ? nb : 0u, i + 1 <= last_x && (closed || i + 2 < n) ? nb : 0u,
                      xn, hn);
       if (closed && i + 1 > last_x) {
         en = i + 1 == n ? e_first : e_last;
-        xn = x_last;
+        xn = RESET && i + 1 == n ? x_first : x_last;
+        sent = i + 1 == n ? sent_first : sent_last;
+      }
+      if (RESET) {
+        receive(T.mbox_l, r, sent_l, xl, ml);
+        receive(T.mbox_r, r, sent, xn, mr);
+        xl = xc;
+        sent_l = sent_c;
+        sent_c = sent;
       }
       if (!GRADBUF) draw_gradient<DIST>(A, j, layer, k_iter, r, sg, (f & kSpike) != 0, g.v);
       const bool vl = (f & kLeftFilled) != 0, vr = (f & kRightFilled) != 0;
@@ -235,7 +284,8 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
       for (int i = 0; i < 4; ++i) {
         const bool in = (uint32_t)i < nv;      // lanes past the tensor's end are padding: left as they are
         const float vn = A.plain_sgd ? g.v[i] : __builtin_fmaf(A.mu, vel.v[i], g.v[i]);
-        const float a = (vl ? (el.v[i] - xc.v[i]) : 0.0f) + (vr ? (en.v[i] - xc.v[i]) : 0.0f);
+        const float lv = RESET ? ml.v[i] : el.v[i], rv = RESET ? mr.v[i] : en.v[i];
+        const float a = (vl ? (lv - xc.v[i]) : 0.0f) + (vr ? (rv - xc.v[i]) : 0.0f);
         const float cns = __builtin_fmaf(a, third, xc.v[i]);
         const float xnew = __builtin_fmaf(-A.lr, vn, cns);
         xc.v[i] = in ? xnew : xc.v[i];
@@ -266,7 +316,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
           atomicAdd(&hist[(uint32_t)q < nv ? (i & 1u) * kHistBins + bin : 2 * kHistBins], 1u);
         }
       }
-      el = ec;
+      if (!RESET) el = ec;
       ec = en;
       xc = xn;
       f = fn;
@@ -305,12 +355,12 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
   }
 }
 
-template <int NORM, bool TOPK, bool HISTA, int W>
+template <int NORM, bool TOPK, bool HISTA, int W, bool RESET = false>
 static void walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t grad_mode, hipStream_t s) {
   const dim3 grid((t.C * (t.SW / (W / 4)) + 7) / 8 * 8, (t.P + a.part - 1) / a.part), block(64 * W);
-  if (grad_mode == 1) k_update_walk<0, true, NORM, TOPK, HISTA, W><<<grid, block, 0, s>>>(t, a);
-  else if (dist == 0) k_update_walk<0, false, NORM, TOPK, HISTA, W><<<grid, block, 0, s>>>(t, a);
-  else k_update_walk<1, false, NORM, TOPK, HISTA, W><<<grid, block, 0, s>>>(t, a);
+  if (grad_mode == 1) k_update_walk<0, true, NORM, TOPK, HISTA, W, RESET><<<grid, block, 0, s>>>(t, a);
+  else if (dist == 0) k_update_walk<0, false, NORM, TOPK, HISTA, W, RESET><<<grid, block, 0, s>>>(t, a);
+  else k_update_walk<1, false, NORM, TOPK, HISTA, W, RESET><<<grid, block, 0, s>>>(t, a);
 }
 
 hipError_t launch_walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t grad_mode, int norm, hipStream_t s) {
@@ -319,7 +369,12 @@ hipError_t launch_walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32
     // 4762, 60 of width 28 978 / 950 / 1051, 20 of width 20 219 / 220 / 262, 8 ResNet-50 workers of half width 369 / 364 / 406, with
     // Student-t gradients 390 / 404 / 451, 12 perceptrons with given gradients 188 / 138 / 119.
     const bool wide = t.SW % 2 == 0;
-    if (norm == 0) walk<0, true, false, 4>(t, a, dist, grad_mode, s);
+    if (a.xhat_reset) {
+      if (norm == 0) walk<0, true, false, 4, true>(t, a, dist, grad_mode, s);
+      else if (norm == 1 && a.hist_fused) wide ? walk<1, true, true, 8, true>(t, a, dist, grad_mode, s) : walk<1, true, true, 4, true>(t, a, dist, grad_mode, s);
+      else if (norm == 3 && a.hist_fused) wide ? walk<3, true, true, 8, true>(t, a, dist, grad_mode, s) : walk<3, true, true, 4, true>(t, a, dist, grad_mode, s);
+      else return hipErrorInvalidValue;
+    } else if (norm == 0) walk<0, true, false, 4>(t, a, dist, grad_mode, s);
     else if (norm == 1 && a.hist_fused) wide ? walk<1, true, true, 8>(t, a, dist, grad_mode, s) : walk<1, true, true, 4>(t, a, dist, grad_mode, s);
     else if (norm == 3 && a.hist_fused) wide ? walk<3, true, true, 8>(t, a, dist, grad_mode, s) : walk<3, true, true, 4>(t, a, dist, grad_mode, s);
     else return hipErrorInvalidValue;

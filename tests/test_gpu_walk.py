@@ -18,7 +18,7 @@ def evg():
 
 def _run(evg, oracle_mod, P, numels, *, norm_mode=0, iters=7, **kw):
     from helpers import lockstep
-    both = {k: kw.pop(k) for k in ("trigger_kind", "topk_key") if k in kw}
+    both = {k: kw.pop(k) for k in ("trigger_kind", "topk_key", "xhat_reset") if k in kw}
     tensors = [inputs.TensorSpec(f"t{i}", (n,), 16 + i, "weight") for i, n in enumerate(numels)]
     w = inputs.Workload("walk", P, tensors, iters, sigma0=0.05, decay=0.9, seed=P, **kw)
     x0 = inputs.replicate(w.x0(), P)
@@ -59,3 +59,29 @@ def test_norms(evg, oracle_mod, P, topk, norm_mode, trigger_kind):
 @pytest.mark.parametrize("kw", [dict(), dict(topk_ppm=100_000)], ids=["whole", "topk"])
 def test_parts(evg, oracle_mod, windows, P, kw):
     _run(evg, oracle_mod, P, [1, 3, 8, 2] * ((windows - 5) // 4) + [4097], iters=5, **kw)
+
+
+# xhat reset at events: the walk reads the mailboxes (one part: up to 5 workers, or more than 600 windows; parts: no walk)
+@pytest.mark.parametrize("P,numels", [(3, [1300, 7, 2048, 515]), (5, [9000, 33, 1024]), (4, [20480, 3]), (16, [3] * 640 + [1029]),
+                                      (66, [2] * 620 + [700]), (17, [1300, 7])], ids=["3", "5", "chunks", "16", "66", "parts"])
+@pytest.mark.parametrize("kw", [dict(topk_ppm=100_000), dict(topk_ppm=20_000, dist=1, topk_key=1, momentum=0.0),
+                                dict(topk_ppm=300_000, trigger_kind=1, spike_prob=0.3, spike_gain=4.0), dict(topk_ppm=100_000, norm_mode=1)],
+                         ids=["drift", "value", "norms", "separate"])
+def test_xhat_reset(evg, oracle_mod, P, numels, kw):
+    _run(evg, oracle_mod, P, numels, iters=6, xhat_reset=1, **kw)
+
+
+@pytest.mark.parametrize("chunk", [1024, 8192])
+def test_xhat_reset_with_given_gradients(evg, oracle_mod, chunk):
+    import torch
+    from helpers import lockstep
+    tensors = [inputs.TensorSpec(f"t{i}", (n,), 16 + i, "weight") for i, n in enumerate([9000, 5, 4097])]
+    w = inputs.Workload("walk", 4, tensors, 7, seed=4, topk_ppm=100_000)
+    x0 = inputs.replicate(w.x0(), w.P)
+    ring = evg.Ring.from_workload(w, x0, mailbox_fill=float("nan"), access_mode=evg.ACCESS_STREAM, xhat_reset=1, grad_mode=1,
+                                  chunk_elems=chunk)
+    orc = oracle_mod.Oracle.from_workload(w, x0, xhat_reset=1, grad_mode=1)
+    given = {k: inputs.random_grads(w.P, w.N, 900 + k, 0.02) for k in range(w.iters)}
+    on_gpu = {k: torch.from_numpy(ring.layout.pad(g)).cuda() for k, g in given.items()}
+    rep = lockstep(ring, orc, w.iters, grads=given.get, gpu_grads=on_gpu.get, sample_messages=8)
+    assert all(rep["bitwise"].values()), rep
