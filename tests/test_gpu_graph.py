@@ -93,3 +93,55 @@ def test_captured_step_replays_as_successive_iterations(evg, topk, buffer):
     assert ring.stats()["iters"] == 12 and float(junk[0]) == 10.0
     ring.step(12, g); ref.step(12, g)         # back to the eager call
     same(ref, ring)
+
+
+# Rings whose update pass walks: in one part, in parts of one worker, and in parts of three whose last is of one.  The first
+# workgroup of that pass moves the iteration on.
+STREAMED = {"one_part": dict(P=4), "parts_of_1": dict(P=17),
+            "parts_of_3": dict(P=19, tensors=TENSORS + [inputs.TensorSpec(f"b{i}", (2,), 9, "bias") for i in range(3, 66)])}
+
+
+@pytest.mark.parametrize("over", [dict(), dict(topk_ppm=100_000), dict(topk_ppm=100_000, xhat_reset=1)],
+                         ids=["whole", "topk", "reset"])
+@pytest.mark.parametrize("shape", list(STREAMED))
+def test_replays_of_walking_passes(evg, shape, over):
+    import torch
+    over = dict(over)
+    w = workload(**STREAMED[shape], topk_ppm=over.pop("topk_ppm", 0))
+    over.update(access_mode=evg.ACCESS_STREAM)
+    ref = evg.Ring.from_workload(w, **over)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        ring = evg.Ring.from_workload(w, stream=s, **over)
+        ring.step_next()
+        ring.step(1)
+    s.synchronize()
+    ref.step(0)
+    ref.step(1)
+    same(ref, ring)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        ring.step_next()
+    same(ref, ring)                           # recorded, not run
+    junk = torch.zeros(1 << 20, device="cuda")
+    for k in range(2, 8):
+        graph.replay()
+        ref.step(k)
+        junk.add_(1.0)
+        torch.cuda.synchronize()
+        same(ref, ring)
+        assert ring.stats()["iters"] == k + 1
+    with pytest.raises(evg.EvgError) as e:
+        ring.step(7)
+    assert e.value.status == 5
+    again = evg.Ring.from_workload(w, **over)
+    again.import_state(ring.export_state())   # the blob carries the device's iteration along
+    for r in (ref, ring, again):
+        r.step(9)                             # a gap in the numbering
+    same(ref, ring)
+    same(ref, again)
+    ref.step(10)
+    ring.step_next()
+    again.step_next()
+    same(ref, ring)
+    same(ref, again)
