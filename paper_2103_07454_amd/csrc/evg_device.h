@@ -138,10 +138,11 @@ __device__ __forceinline__ void copy_chunk(const Tables& T, uint32_t r, const Ch
 // gives the same bits on any IEEE machine.  The chains run on the ranges the generator feeds them
 // (uniforms are odd multiples of 2^-24), which lets quotients and roots do without the scaling and
 // special cases of the general operators: a hardware estimate and one correction by fused
-// multiply-adds already rounds correctly for every input that occurs.  An input is 23 random bits:
-// radius and angle have been compared with the general operators over all 2^23 of them, no
-// difference.  Cycles per wavefront for four variates, Philox included: normal 779 -> 530,
-// Student-t 1737 -> 1265.
+// multiply-adds rounds as they do.  An input is 23 random bits: over all 2^23 of them a correctly rounded
+// estimate never leaves a difference, and one that is off by its last bit (the estimates' accuracy) does at
+// 7 of them for the normal's radius, 9 for the Student-t's (tests/test_generator_estimates.py, which also draws
+// those on the GPU).  Angle and uniform take no estimate.  Cycles per wavefront for four variates, Philox
+// included: normal 779 -> 530, Student-t 1737 -> 1265.
 struct Rand4 { uint32_t w[4]; };
 
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
