@@ -205,7 +205,8 @@ def main():
     rho = w.topk_ppm / 1e6
     f_full = float((st["events_full_rl"].astype(np.float64) * numel[None, :]).sum() / (elems * args.steps))
     f_topk = float((st["events_topk_rl"].astype(np.float64) * numel[None, :]).sum() / (elems * args.steps))
-    # rings that stream from memory, with ordinary delivery: the update pass walks the ring
+    # rings that stream from memory, with ordinary delivery: the update pass walks the ring (where xhat is reset at events it
+    # reads the mailboxes too, as the pass of the other rings does)
     walks = 20 * w.P * evg.padded_numel(w.layer_numel) > (128 << 20) and not args.delivery_delay and not args.xhat_reset
     if walks:
         step_bytes_per_elem = (20 if w.momentum != 0.0 else 12) + 8 * f_full + 8 * f_topk + 20 * rho * f_topk
@@ -266,7 +267,8 @@ def main():
                                                      or args.topk_ppm is not None) else None
         upd_counters = (counters or {}).get("kernels", {}).get("k_update", {})
         traffic = upd_counters.get("traffic_bytes")
-        out["roofline"] = {"kernel": "k_update", "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
+        kernel = "k_update_walk" if walks else "k_update"
+        out["roofline"] = {"kernel": kernel, "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
                            "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                            "traffic": traffic,
                            "traffic_measured_at": None if traffic is None else {
@@ -283,7 +285,7 @@ def main():
         if valu is not None and w.dist == 1:
             # Student-t gradients: the generator, not memory, bounds the pass
             ops = valu * elems / (avg_ms * 1e-3) / 1e12
-            out["roofline"] = {"kernel": "k_update", "bound": "alu", "achieved": ops, "peak": ALU_PEAK_TLANEOPS,
+            out["roofline"] = {"kernel": kernel, "bound": "alu", "achieved": ops, "peak": ALU_PEAK_TLANEOPS,
                                "unit": "T lane-instructions/s", "frac": ops / ALU_PEAK_TLANEOPS, "traffic": traffic,
                                "avg_launch_ms": avg_ms, "launches": n_upd,
                                "algorithmic_bytes_per_launch": upd_bytes,

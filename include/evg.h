@@ -171,8 +171,10 @@ typedef struct {
   uint64_t near_tie_flags;  /* tests with |norm - delta| < 1e-6 * delta          */
   uint64_t nonfinite_norms; /* tests whose norm was NaN or infinite              */
   uint64_t chunks_not_staged; /* Top-K work granules whose keys in the threshold's bin exceeded their
-                               staging slot and were selected straight from x and xhat instead (slower,
-                               same result): massive ties, or tensors shorter than 16 elements */
+                               staging slot (a quarter of the granule's length, rounded down to a
+                               multiple of 4; none below 16 elements) and were selected straight from
+                               x and xhat instead (slower, same result): massive ties, or tensors and
+                               ends of tensors of a few elements */
   uint64_t library_bytes;   /* device memory the library holds for this context besides the
                                caller's five arenas (tables, Top-K histograms,
                                staging and message buffers); for evg_init_static the part

@@ -401,10 +401,11 @@ __global__ __launch_bounds__(64) void k_topk_scan(Tables T, StepArgs A) {
   }
 }
 
-// Ahead of the update pass, one workgroup per sweep: writes the Top-K messages of this iteration and applies them
+// Ahead of the update pass, one workgroup per chunk: writes the Top-K messages of this iteration and applies them
 //   LEAD: to xhat, for the workers at the ends of the parts in which a ring is walked;
-//   else: to the neighbours' mailboxes (rings whose update pass cannot tell what a neighbour sent: its xhat is
-//   reset at events, or there is no room for the copies of x it would need).
+//   else: to the neighbours' mailboxes (rings whose update pass cannot tell what a neighbour sent: it does not walk,
+//   and there are no copies of x, for lack of room, or as those would be out of date or of no use: a norm pass of its own,
+//   xhat reset at events).
 template <int SWEEPS, bool LEAD>
 __global__ __launch_bounds__(kThreads) void k_topk_apply(Tables T, StepArgs A) {
   const WorkItem wi = work_item(T, blockIdx.y, blockIdx.x);

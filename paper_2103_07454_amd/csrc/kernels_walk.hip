@@ -8,9 +8,13 @@
 // there is nothing to wait for.  The next worker's loads are under way while one is updated.
 //
 // Bound by memory: 20 bytes per element (12 read), 8 more where a tensor is sent whole, messages and the 64-byte groups they
-// touch.  It moves them at 4.9 - 5.3 TB/s, where a large copy reaches 4.8 and reads alone 6.3.  Steps before (a pass
-// per worker that read the neighbours through the L2, and a copy kernel) -> now: 16 ResNet-18 workers with whole sends
-// 925 -> 868 us, 32 with plain SGD 1569 -> 1222, 7 of width 23 65.8 -> 54.0, 8 ResNet-50 workers of half width 343 -> 287.
+// touch.  It moves them at 4.9 - 5.3 TB/s.  On this card a large copy reaches 4.8, two reads to a write 5.9, reads alone
+// 6.3, and this pass writes about as much as it reads, or more.  Steps before (a pass per worker that read
+// the neighbours through the L2, and a copy kernel) -> now: 16 ResNet-18 workers with whole sends 925 -> 868 us, 32 with plain
+// SGD 1569 -> 1222, 7 of width 23 65.8 -> 54.0, 8 ResNet-50 workers of half width 343 -> 287.
+// Residency: whole sends 76 - 93 vector registers and 2 KB of LDS, 5 or 6 wavefronts a SIMD; Top-K 104 - 115 and 20 or 24 KB for
+// eight wavefronts, 4 a SIMD; with mailboxes read (RESET) 123 - 135, 4 or 3.  All use 106 scalar registers and spill
+// some tens of them to vector lanes: what more a Top-K walk keeps per worker costs 1 - 2 % at once.
 #include "message_device.h"
 #include "trigger_device.h"
 
