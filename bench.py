@@ -207,7 +207,8 @@ def main():
     f_topk = float((st["events_topk_rl"].astype(np.float64) * numel[None, :]).sum() / (elems * args.steps))
     # rings that stream from memory, with ordinary delivery: the update pass walks the ring (where xhat is reset at events it
     # reads the mailboxes too, as the pass of the other rings does)
-    walks = 20 * w.P * evg.padded_numel(w.layer_numel) > (128 << 20) and not args.delivery_delay and not args.xhat_reset
+    streams = 20 * w.P * evg.padded_numel(w.layer_numel) > (128 << 20) and not args.delivery_delay
+    walks = streams and not args.xhat_reset
     if walks:
         step_bytes_per_elem = (20 if w.momentum != 0.0 else 12) + 8 * f_full + 8 * f_topk + 20 * rho * f_topk
     else:
@@ -267,7 +268,7 @@ def main():
                                                      or args.topk_ppm is not None) else None
         upd_counters = (counters or {}).get("kernels", {}).get("k_update", {})
         traffic = upd_counters.get("traffic_bytes")
-        kernel = "k_update_walk" if walks else "k_update"
+        kernel = "k_update_walk" if streams else "k_update"
         out["roofline"] = {"kernel": kernel, "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
                            "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                            "traffic": traffic,
