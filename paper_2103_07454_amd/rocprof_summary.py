@@ -94,7 +94,7 @@ def main():
             per_step += float(r["AverageNs"]) / 1e6
     out += ["", f"Sum of the per-step kernels' averages: {per_step:.3f} ms per iteration.", "",
             f"The un-profiled `python bench.py --config {c}` run of the same session printed:", "",
-            f"    ms_per_step {b['ms_per_step']:.3f}, value {b['value']:.4e} elements/s, k_update avg launch "
+            f"    ms_per_step {b['ms_per_step']:.3f}, value {b['value']:.4e} elements/s, {rf['kernel']} avg launch "
             f"{rf['avg_launch_ms']:.3f} ms (HIP events on the library's stream),"]
     if rf["bound"] == "hbm":
         out.append(f"    roofline.achieved {rf['achieved']:.0f} GB/s = {rf['frac']:.3f} of 8 TB/s on "
@@ -148,7 +148,7 @@ def main():
                 fetch_bytes=af, write_bytes=aw, traffic_bytes=af + aw, launches=len(fv))
         upd = record["kernels"].get("k_update")
         if upd and rf["bound"] == "hbm":
-            out += ["", f"`k_update`: {upd['traffic_bytes'] / 1e9:.2f} GB per launch = {upd['traffic_bytes'] / elems:.1f} B per element, against "
+            out += ["", f"`{rf['kernel']}`: {upd['traffic_bytes'] / 1e9:.2f} GB per launch = {upd['traffic_bytes'] / elems:.1f} B per element, against "
                     f"{rf['algorithmic_bytes_per_launch'] / 1e9:.2f} GB algorithmic"
                     + (f" and a line-granular floor of {rf['line_granular_floor_bytes_per_launch'] / 1e9:.2f} GB "
                        f"(dense arrays + messages + write-back of every 64-byte group that holds a sent entry)."
