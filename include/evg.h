@@ -125,14 +125,15 @@ typedef struct {
                                    more than 256 MB.  In a cached ring
                                    without delivery delay each receiver fetches what its neighbours
                                    send inside the update pass, from a copy of x the library keeps
-                                   (two more arrays of the ring's size, library-owned); not where
+                                   (two more arrays of the ring's size, library-owned; not where one
+                                   workgroup has the whole ring of up to 8 workers at hand); not where
                                    Top-K messages are sent and xhat_reset or EVG_NORM_SEPARATE is
                                    set or seven arenas exceed 256 MB.  If such a ring sends whole tensors, its norms are
                                    accumulated by the update pass (norm_mode) and no tensor is
                                    longer than 131 072 elements, evg_step is then ONE kernel launch:
-                                   the update pass runs the trigger tests itself.  evg_step_next
-                                   keeps the trigger kernel (two launches), and so does evg_step on
-                                   a ring once evg_step_next has been called on it               */
+                                   the update pass runs the trigger tests itself, and so is
+                                   evg_step_next.  evg_step on a ring on which evg_step_next has been
+                                   called keeps the trigger kernel (two launches)                  */
   evg_synth synth;
   /* DEVICE arenas owned by the caller, each P * evg_padded_numel() floats,
    * 16-byte aligned, non-overlapping, alive until evg_destroy.  Worker r's
@@ -195,7 +196,7 @@ enum {
   EVG_PH_TRIGGER = 1,    /* norm finalisation, trigger test, thresholds
                             (no samples where the update pass runs the tests itself:
                             cache-resident rings that send whole tensors, norms fused,
-                            no tensor above 131 072 elements, evg_step only)          */
+                            no tensor above 131 072 elements)                         */
   EVG_PH_SEND_FULL = 2,  /* whole-tensor copies: only for the few workers whose values two
                             workgroups need, where a streaming ring of many workers and a
                             small network is walked in parts; elsewhere whole sends are part

@@ -8,7 +8,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libevg.so")
-SOURCES = ["evg_api.hip", "kernels_update.hip", "kernels_walk.hip", "kernels_trigger.hip", "kernels_topk.hip"]
+SOURCES = ["evg_api.hip", "kernels_update.hip", "kernels_walk.hip", "kernels_parts.hip", "kernels_trigger.hip", "kernels_topk.hip"]
 
 # -ffp-contract=off: every fused multiply-add in the kernels is written out, so
 #   results do not depend on what the compiler decides to contract.

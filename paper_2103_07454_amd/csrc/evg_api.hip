@@ -85,15 +85,11 @@ struct evg_ctx {
                                     // advance the device's iteration without the host seeing
                                     // it, so iters / last_iter are re-read whenever needed
   // Single-launch steps (cache-resident rings, whole-tensor sends, norms accumulated by the update
-  // pass, no tensor longer than 128 sweeps): the update pass runs the trigger tests itself.  What the
-  // tests read must then not be written in the same launch, so these arrays exist twice and a step
-  // writes the set it does not read; c->t always names the set that holds the current state.
-  struct SecondSet { double* partials; double* xhat_sq; float* delta; int32_t* last_event; };
-  // (the sums of squared xhat are not among them: such a ring's steps only read those)
-  SecondSet second{};
+  // pass, no tensor longer than 128 sweeps): the update pass goes through the ring in parts of `part` workers and runs the
+  // trigger tests itself.  c->t names the set of arrays that holds the current state (use_set).
+  PartTables parts{};
   bool one_launch = false;          // the ring qualifies
-  bool replayable_used = false;     // evg_step_next has been called: a captured graph may hold the pointers
-                                    // of c->t, so the sets must not change places any more
+  bool replayable_used = false;     // evg_step_next has been called: evg_step runs the tests in a kernel of their own from then on
   // evg_init_static: the tables are carved out of the device's static scratch block
   unsigned char* arena_base = nullptr;   // null = tables come from hipMalloc
   size_t arena_used = 0;
@@ -279,7 +275,7 @@ struct TableSum {
 
 // Bytes of library-owned device tables a configuration needs: the same list as the allocations of init_common.
 static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uint64_t hist_len, uint64_t Npad,
-                            uint64_t ktot, bool topk, bool norm_diff, bool pull, bool one_launch) {
+                            uint64_t ktot, bool topk, bool norm_diff, bool pull, bool one_launch, uint64_t windows, uint64_t parts) {
   const uint64_t S = P * L, PC = P * C;
   TableSum t;
   t.add(C, sizeof(ChunkDesc)); t.add(L, sizeof(LayerDesc));
@@ -294,7 +290,9 @@ static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uin
   if (one_launch) {                                              // the second set of what the trigger tests read
     t.add(PC * SW, 8); t.add(S, 4); t.add(S, 4);
     if (norm_diff) t.add(S, 8);
+    t.add(windows * parts, sizeof(PartClock));
   }
+  if (windows) t.add(windows, sizeof(WindowDesc));
   if (topk) {
     t.add(S * kHistBins, 4); t.add(S, 4); t.add(S, 4); t.add(S, 4); t.add(PC, 4);   // hist, selection, stage_n
     t.add(P * (Npad / 16 * 4), 4);                               // stage_key
@@ -466,8 +464,9 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   // carried from step to step: a caller may have written x since the copies were made, and the sender goes by x.
   bool pull = c->cached && !cfg->delivery_delay &&
               !(cfg->topk_ppm && (cfg->xhat_reset || cfg->norm_mode == EVG_NORM_SEPARATE || !copies_fit));
-  bool one_launch = false;
-  uint64_t need = 0;
+  bool in_parts = false, one_launch = false, may_be = true;
+  uint64_t need = 0, ring_windows = 0;
+  uint32_t ring_part = 0;
   auto cut_chunks = [&](bool on_lines) {
     chunks.clear();
     uint32_t most_sweeps = 0;
@@ -487,16 +486,30 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
       }
       most_sweeps = std::max(most_sweeps, d.nchunks * SW);
     }
-    // one launch per iteration: the ring's receivers fetch the sends (see `pull` below), the update pass
-    // accumulates the norms, and one wavefront sums a tensor's sweep partials with two loads per lane
-    one_launch = pull && !cfg->topk_ppm && cfg->norm_mode == EVG_NORM_FUSED && most_sweeps <= 128;
+    // Cached rings that send whole tensors and accumulate the norms in the update pass are updated in parts of the ring; in
+    // one launch per iteration where one wavefront sums a tensor's sweep partials with two loads per lane.
+    in_parts = may_be && pull && !cfg->topk_ppm && cfg->norm_mode == EVG_NORM_FUSED && arena_bytes < (1ull << 30);
+    one_launch = in_parts && most_sweeps <= 128;
+    ring_windows = 0;
+    for (const ChunkDesc& cd : chunks) ring_windows += (cd.len + kSweep - 1) / kSweep;
+    // Longer parts read less of other parts' workers and run fewer tests twice, shorter ones are more workgroups.  Parts
+    // of 2 / 4 / 8, us a step: 102 windows on 4 workers 5.8 / 6.8 / -, 120 on 8 7.2 / 7.7 / 11.2, on 24 12.7 / 12.5 / 15.6; 314 on
+    // 8 15.7 / 14.3 / 16.6, on 12 25.7 / 22.6 / 19.2, on 16 34.1 / 33.4 / 30.7; 438 on 8 24.9 / 21.8 / 18.4, on 16 53.3 / 48.9 / 49.0.
+    const uint64_t units = ring_windows * P;
+    ring_part = std::min<uint32_t>(P, units < 900 ? 2 : units < 3400 ? 4 : kPartMost);
+    if (in_parts && !one_launch) ring_part = std::min<uint32_t>(ring_part, 4);
     need = table_bytes(P, L, chunks.size(), SW, hist_len, Npad, ktot, cfg->topk_ppm != 0,
-                       cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF, pull, one_launch);
+                       cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF, pull && !(in_parts && ring_part == P), one_launch,
+                       in_parts ? ring_windows : 0, (P + ring_part - 1) / ring_part);
     return (uint64_t)P * chunks.size() * (SW + 1) <= 0xFFFFFFF0ull && (uint64_t)P * ktot <= 0xFFFFFFF0ull &&
            !(use_scratch && need > kScratchBytes);
   };
   c->on_lines = !c->cached && cut_chunks(true);
   if (!c->on_lines) (void)cut_chunks(false);
+  if (use_scratch && need > kScratchBytes && in_parts) {        // thousands of short tensors: no room for what the parts take
+    may_be = false;
+    (void)cut_chunks(false);
+  }
   if (use_scratch && need > kScratchBytes && pull && cfg->topk_ppm) {   // no room for the copies of x: messages are applied
     pull = false;                                                        // by a kernel of their own
     (void)cut_chunks(false);
@@ -641,12 +654,31 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   }
   // cache-resident ring, whole tensors, same-iteration delivery: the update pass fetches the sends
   // itself from a copy of x it keeps (one more array of the ring's size, library-owned)
-  if (pull) TRY_OR_FREE(c->dalloc(&t.xsnap, 2 * (uint64_t)P * Npad, false));
+  if (pull && !(in_parts && ring_part == P)) TRY_OR_FREE(c->dalloc(&t.xsnap, 2 * (uint64_t)P * Npad, false));
+  std::vector<WindowDesc> ring;
+  if (in_parts) {
+    for (size_t i = 0; i < chunks.size(); ++i)
+      for (uint32_t u = 0; u * kSweep < chunks[i].len; ++u) {
+        const ChunkDesc& cd = chunks[i];
+        const LayerDesc& d = layers[cd.layer];
+        ring.push_back({cd.off + u * kSweep, std::min<uint32_t>(kSweep, cd.len - u * kSweep), cd.layer, cd.j0 + u * kSweep,
+                        (uint32_t)i * SW + u, d.chunk0 * SW, d.nchunks * SW, i == d.chunk0 && u == 0 ? 1u : 0u, d.sig_base});
+      }
+    WindowDesc* d_ring = nullptr;
+    TRY_OR_FREE(c->dalloc(&d_ring, ring.size(), false));
+    HIP_OR_FREE(hipMemcpyAsync(d_ring, ring.data(), ring.size() * sizeof(WindowDesc), hipMemcpyHostToDevice, c->stream));
+    c->parts.windows = d_ring;
+    c->parts.count = (uint32_t)ring.size();
+    c->part = ring_part;
+    c->parts.set[0] = c->parts.set[1] = {t.partials, t.xhat_sq, t.delta, t.last_event};
+  }
   if (one_launch) {
-    TRY_OR_FREE(c->dalloc(&c->second.partials, P * C * t.SW, true));
-    TRY_OR_FREE(c->dalloc(&c->second.delta, S, true));
-    TRY_OR_FREE(c->dalloc(&c->second.last_event, S, true));
-    if (cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF) TRY_OR_FREE(c->dalloc(&c->second.xhat_sq, S, true));
+    TRY_OR_FREE(c->dalloc(&c->parts.clocks, ring.size() * ((P + ring_part - 1) / ring_part), true));
+    PartTables::Set& other = c->parts.set[1];
+    TRY_OR_FREE(c->dalloc(&other.partials, P * C * t.SW, true));
+    TRY_OR_FREE(c->dalloc(&other.delta, S, true));
+    TRY_OR_FREE(c->dalloc(&other.last_event, S, true));
+    if (cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF) TRY_OR_FREE(c->dalloc(&other.xhat_sq, S, true));
     c->one_launch = true;
   }
   // a step writes where it reads, unless it is a single-launch step (enqueue_step)
@@ -694,6 +726,17 @@ evg_status evg_init_static(evg_ctx** out, const evg_config* cfg, void* hip_strea
   return init_common(out, cfg, hip_stream, true);
 }
 
+// Single-launch rings: c->t names the set that the next step reads.
+static void use_set(evg_ctx* c) {
+  if (!c->one_launch) return;
+  Tables& t = c->t;
+  const PartTables::Set& now = c->parts.set[c->iters & 1];
+  t.partials = t.partials_out = now.partials;
+  t.xhat_sq = t.xhat_sq_out = now.xhat_sq;
+  t.delta = t.delta_out = now.delta;
+  t.last_event = t.last_event_out = now.last_event;
+}
+
 // Brings iters / last_iter up to date with the device after replayable steps.
 static evg_status refresh_iteration(evg_ctx* c) {
   if (!c->device_ahead) return EVG_OK;
@@ -704,6 +747,7 @@ static evg_status refresh_iteration(evg_ctx* c) {
     return fail(EVG_ERR_STATE, "evg_step_next ran past iteration %u, the end of its decay table", kDecayTable - 1);
   c->iters = it.iters;
   c->last_iter = (int64_t)it.k_next - 1;
+  use_set(c);
   return EVG_OK;
 }
 
@@ -718,15 +762,14 @@ static evg_status enqueue_step(evg_ctx* c, const StepArgs& args, bool timed) {
   c->timing = was_timing && timed;
   struct Restore { evg_ctx* c; bool v; ~Restore() { c->timing = v; } } restore{c, was_timing};
   evg_status st;
-  // single launch: the update pass runs the trigger tests on the current set of arrays and writes
-  // the other set, which is the current one from then on.  Not once evg_step_next has been used:
-  // a captured graph holds c->t's pointers.
-  const bool single = c->one_launch && !c->replayable_used && !a.from_device;
-  if (single) {
-    a.one_launch = 1;
-    a.step_no = (uint32_t)c->iters;
-    t.partials_out = c->second.partials;
-    t.xhat_sq_out = c->second.xhat_sq; t.delta_out = c->second.delta; t.last_event_out = c->second.last_event;
+  // single launch: the update pass runs the trigger tests
+  const bool single = c->one_launch && (a.from_device || !c->replayable_used);
+  a.one_launch = single;
+  a.step_no = (uint32_t)c->iters;
+  if (c->one_launch) {
+    const PartTables::Set& next = c->parts.set[(c->iters + 1) & 1];
+    t.partials_out = next.partials;
+    t.xhat_sq_out = next.xhat_sq; t.delta_out = next.delta; t.last_event_out = next.last_event;
   }
   if (!fused) {
     Phase ph(c, EVG_PH_NORM);
@@ -761,17 +804,10 @@ static evg_status enqueue_step(evg_ctx* c, const StepArgs& args, bool timed) {
   {
     Phase ph(c, EVG_PH_UPDATE);
     const int norm = !fused ? 0 : !norm_diff ? 1 : g.topk_ppm ? 3 : 2;
-    HIP_TRY(a.walk ? launch_walk(t, a, g.synth.dist, g.grad_mode, norm, c->stream)
-                   : launch_update(t, a, g.synth.dist, g.grad_mode, norm, c->stream));
+    HIP_TRY(a.walk          ? launch_walk(t, a, g.synth.dist, g.grad_mode, norm, c->stream)
+            : c->parts.count ? launch_part(t, a, c->parts, g.synth.dist, g.grad_mode, norm, c->stream)
+                            : launch_update(t, a, g.synth.dist, g.grad_mode, norm, c->stream));
     if ((st = ph.end()) != EVG_OK) return st;
-  }
-  if (single) {
-    Tables& ct = c->t;
-    std::swap(ct.partials, c->second.partials);
-    std::swap(ct.xhat_sq, c->second.xhat_sq); std::swap(ct.delta, c->second.delta);
-    std::swap(ct.last_event, c->second.last_event);
-    ct.partials_out = ct.partials; ct.partials_hat_out = ct.partials_hat; ct.xhat_sq_out = ct.xhat_sq;
-    ct.delta_out = ct.delta; ct.last_event_out = ct.last_event;
   }
   if (a.delay) {
     Phase ph(c, EVG_PH_DELIVER);
@@ -835,6 +871,7 @@ evg_status evg_step(evg_ctx* c, uint64_t iter, const float* grad) {
   if ((st = enqueue_step(c, a, true)) != EVG_OK) return st;
   c->last_iter = (int64_t)iter;
   c->iters += 1;
+  use_set(c);
   return EVG_OK;
 }
 
@@ -1059,7 +1096,8 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
     off += pad_to(c->numel[l], 4);
   }
   const uint64_t here = (uint64_t)t.C * t.SW, there = (uint64_t)got.C * got.SW;
-  const bool same_cut = got.C == t.C && got.SW == t.SW, from_lines = there != plain;
+  // (a pass in parts writes no sum where a chunk has no window, so what another ring has there is moved in any case)
+  const bool same_cut = got.C == t.C && got.SW == t.SW && !c->parts.count, from_lines = there != plain;
   const bool maybe_lines = got.version == 4 || (flags & kCutOnLines);     // (version 4 does not say)
   if (there != plain && !(maybe_lines && there == lines))
     return fail(EVG_ERR_INVALID, "blob was exported from a different configuration or version");
@@ -1079,6 +1117,13 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
   const size_t sum_count = (size_t)t.P * here;
   std::unique_ptr<double[]> moved(same_cut ? nullptr : new (std::nothrow) double[sum_count]);
   if (!same_cut && !moved) return fail(EVG_ERR_OOM, "host allocation failed");
+  const size_t clock_count = c->one_launch ? (size_t)c->parts.count * ((t.P + c->part - 1) / c->part) : 0;
+  std::unique_ptr<PartClock[]> clocks(new (std::nothrow) PartClock[clock_count + 1]);
+  if (!clocks) return fail(EVG_ERR_OOM, "host allocation failed");
+  std::fill_n(clocks.get(), clock_count, PartClock{(uint32_t)(got.last_iter + 1), (uint32_t)got.iters});
+  c->iters = got.iters;
+  c->last_iter = got.last_iter;
+  use_set(c);
   // Everything goes through the context's stream, and is waited for: steps on a non-blocking stream do not wait for copies
   // on the default stream, and a copy from device to device does not make the host wait.
   const char* in = static_cast<const char*>(blob) + sizeof got;
@@ -1111,6 +1156,8 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
     HIP_TRY(hipMemcpyAsync(p.dev, in, p.bytes, hipMemcpyHostToDevice, c->stream));
     in += p.bytes;
   }
+  if (clock_count)
+    HIP_TRY(hipMemcpyAsync(c->parts.clocks, clocks.get(), clock_count * sizeof(PartClock), hipMemcpyHostToDevice, c->stream));
   // the library's copy of x follows the caller's arena, which holds the saved parameters again
   if (c->t.xsnap) {
     const size_t arena = (size_t)c->t.P * c->t.Npad;
@@ -1118,8 +1165,6 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
     HIP_TRY(hipMemcpyAsync(c->t.xsnap + arena, c->t.x, arena * 4, hipMemcpyDeviceToDevice, c->stream));
   }
   HIP_TRY(hipStreamSynchronize(c->stream));
-  c->iters = got.iters;
-  c->last_iter = got.last_iter;
   c->messages_live = false;         // message buffers are scratch and are not part of the blob
   return EVG_OK;
 }

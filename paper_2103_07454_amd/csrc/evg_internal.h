@@ -38,6 +38,24 @@ struct LayerDesc {
   double sig_base;   // sigma0 [/ sqrt(fan_in)]
 };
 
+// A window of kernels_parts.hip: up to 1024 elements of one tensor.
+struct WindowDesc {
+  uint32_t off, len;   // start inside a worker's slice (multiple of 4), elements
+  uint32_t layer, j0;  // tensor, start inside it
+  uint32_t slot;       // where the window's sum goes among a worker's partials
+  uint32_t sum0, sums; // the tensor's partials
+  uint32_t books;      // the tensor's first window
+  double sig_base;     // sigma0 [/ sqrt(fan_in)]
+};
+constexpr uint32_t kPartMost = 8;      // workers of a part of the ring there
+struct PartClock { uint32_t k, steps; };       // the next iteration, and the steps completed
+struct PartTables {
+  const WindowDesc* windows; uint32_t count;
+  PartClock* clocks;       // [count * parts]
+  // What the trigger tests read and an event writes exists twice: step n (from 0) reads set n & 1 and writes the other.
+  struct Set { double* partials; double* xhat_sq; float* delta; int32_t* last_event; } set[2];
+};
+
 // The iteration as the device knows it.  evg_step passes the iteration by value; a step
 // that must be replayable from a captured graph (evg_step_next) reads it from here instead.
 struct IterState {
@@ -66,7 +84,7 @@ struct Tables {
   int32_t* last_event;
   // Where a step WRITES the sweep sums, and an event the threshold, its iteration and the squared
   // norm of what was sent.  The same arrays as partials, partials_hat, delta, last_event, xhat_sq
-  // (which a step reads), except in a single-launch step, whose workgroups must all still see the
+  // (which a step reads), except in rings whose steps can be a single launch, whose workgroups must all still see the
   // values from before the step: there the two sets alternate from step to step.
   double* partials_out; double* partials_hat_out; double* xhat_sq_out;
   float* delta_out; int32_t* last_event_out;
@@ -120,7 +138,7 @@ struct StepArgs {
   uint32_t pull;           // sends are fetched by the receivers inside the update pass
   uint32_t applied;        // Top-K messages are written and put into the mailboxes ahead of the update pass
   uint32_t one_launch;     // ... and the update pass also runs the trigger tests (no other kernel in the step)
-  uint32_t step_no;        // one_launch: steps completed before this one (picks the copy of x to read)
+  uint32_t step_no;        // steps completed before this one, where the host counts them (kernels_parts.hip)
   uint32_t key0, key1;
   double decay_pow;        // decay^k
   float spike_prob, spike_gain;
@@ -134,6 +152,8 @@ hipError_t launch_update(const Tables& t, const StepArgs& a, uint32_t dist, uint
                          int norm, hipStream_t s);
 // norm as above; rings for which the host sets StepArgs::walk
 hipError_t launch_walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t grad_mode, int norm, hipStream_t s);
+// norm: 1 or 2
+hipError_t launch_part(const Tables& t, const StepArgs& a, const PartTables& p, uint32_t dist, uint32_t grad_mode, int norm, hipStream_t s);
 hipError_t launch_trigger(const Tables& t, const StepArgs& a, hipStream_t s);
 hipError_t launch_copy(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
 hipError_t launch_deliver(const Tables& t, uint32_t chunk_elems, hipStream_t s);

@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_decide(Tables T, StepArgs A) 
     double acc, acc_hat;
     bool hat_sums;
     segment_sums(T, A, seg, &acc, &acc_hat, &hat_sums);
-    if (lane_id() == 0) code = segment_test<true, true>(T, A, seg, acc, acc_hat, hat_sums, tested_k(T, A));
+    if (lane_id() == 0) code = segment_test(T, A, seg, acc, acc_hat, hat_sums, tested_k(T, A));
   }
   __syncthreads();
   pick_bin<0>(T, seg, code, ws);

@@ -17,7 +17,7 @@ __device__ __forceinline__ void trigger_segment(const Tables& T, const StepArgs&
   double acc, acc_hat;
   bool hat_sums;
   segment_sums(T, A, seg, &acc, &acc_hat, &hat_sums);
-  if (lane_id() == 0) (void)segment_test<true, true>(T, A, seg, acc, acc_hat, hat_sums, tested_k(T, A));
+  if (lane_id() == 0) (void)segment_test(T, A, seg, acc, acc_hat, hat_sums, tested_k(T, A));
 }
 
 __global__ __launch_bounds__(kThreads) void k_trigger(Tables T, StepArgs A) {

@@ -3,8 +3,8 @@
 // of Section 4), which also accumulates the squared drift || x - xhat ||^2 that the
 // next iteration's trigger test needs, and a stand-alone drift-norm pass.
 //
-// Streaming rings with ordinary delivery are updated by kernels_walk.hip; k_update here serves the others:
-// rings that live in the cache, delayed delivery, xhat reset at events.  One workgroup (256 threads, one
+// Streaming rings with ordinary delivery are updated by kernels_walk.hip, cached rings with whole-tensor sends by kernels_parts.hip;
+// k_update here serves the others: cached Top-K rings, norm passes of their own, delayed delivery, xhat reset at events.  One workgroup (256 threads, one
 // float4 per thread) owns one 1024-element sweep of one chunk of one worker; where the pass also builds
 // the histogram of a Top-K ring, two.
 #include "message_device.h"
@@ -71,67 +71,29 @@ __device__ __forceinline__ void block_sums(const double v[SPW], double* ws, doub
 // mailbox here; and the new x is also written to the other of the two copies for the next
 // iteration (two copies in turn: the one read now is written by nobody in this launch).  Fewer
 // launches per iteration for rings that live in the cache, where launches are what costs.
-// TESTS (with PULL): no kernel has run the trigger tests of this iteration.  Every workgroup
-// runs the three it depends on itself (its own tensor's and that tensor's of the two
-// neighbours: three wavefronts, one each, from the sweep sums the previous pass left), and the
-// first workgroup of each tensor books its tensor's outcome.  What the tests read is not
-// written by this launch (Tables: the _out arrays), so every workgroup decides alike.  One
-// launch per iteration.
-template <int DIST, bool GRADBUF, int NORM, bool TOPK, bool HISTA, int SPW, bool STREAM, bool PULL = false,
-          bool TESTS = false>
+template <int DIST, bool GRADBUF, int NORM, bool TOPK, bool HISTA, int SPW, bool STREAM, bool PULL = false>
 __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
-  static_assert(!TESTS || (PULL && !TOPK && SPW == 1), "the tests ride in the pass of rings whose receivers fetch the sends");
   __shared__ double ws[4 * SPW];
-  __shared__ uint32_t outcome[3];
   __shared__ uint32_t hA[HISTA ? kHistBins : 1];
   const uint32_t groups = T.SW / SPW;      // workgroups per chunk (SW is a multiple of SPW)
   const uint32_t c = blockIdx.x / groups, sub0 = (blockIdx.x % groups) * SPW, r = blockIdx.y;
   const ChunkDesc cd = T.chunks[c];
   const uint32_t seg = r * T.L + cd.layer;
-  bool vl = T.valid_l[seg] != 0, vr = T.valid_r[seg] != 0;
+  const bool vl = T.valid_l[seg] != 0, vr = T.valid_r[seg] != 0;
   const uint32_t lw = (r + T.P - 1) % T.P, rw = (r + 1) % T.P;
-  uint32_t my_event;
-  bool from_l = false, from_r = false, some_l = false, some_r = false;   // the neighbours sent all / some of their tensor
-  if (TESTS) {
-    const uint32_t segs[3] = {seg, lw * T.L + cd.layer, rw * T.L + cd.layer};
-    const bool books = blockIdx.x == T.layers[cd.layer].chunk0 * groups;    // the tensor's first workgroup
-    if (wave_id() < 3) {
-      const uint32_t sg = segs[wave_id()];
-      double acc, acc_hat;
-      bool hat_sums;
-      segment_sums(T, A, sg, &acc, &acc_hat, &hat_sums);
-      if (lane_id() == 0)
-        outcome[wave_id()] = (books && wave_id() == 0) ? segment_test<true, false>(T, A, sg, acc, acc_hat, hat_sums, A.k)
-                                                       : segment_test<false, false>(T, A, sg, acc, acc_hat, hat_sums, A.k);
-    }
-    __syncthreads();
-    my_event = outcome[0];
-    from_l = outcome[1] == 1;
-    from_r = outcome[2] == 1;
-    // a neighbour's send fills my mailbox slot for good (the flags only ever go from 0 to 1, so
-    // a workgroup that reads one after the booking below sees what it would have computed)
-    vl = vl || from_l;
-    vr = vr || from_r;
-    if (books && threadIdx.x == 0) {
-      if (from_l) T.valid_l[seg] = 1;
-      if (from_r) T.valid_r[seg] = 1;
-    }
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) close_step(T, A);
-  } else {
-    my_event = T.fired[seg];
-    // what did my neighbours send of this tensor in this iteration? (then vl / vr are set)
-    if (PULL) {
-      const uint32_t fl = T.fired[lw * T.L + cd.layer], fr = T.fired[rw * T.L + cd.layer];
-      from_l = fl == 1;
-      from_r = fr == 1;
-      some_l = TOPK && fl == 2;
-      some_r = TOPK && fr == 2;
-    }
+  const uint32_t my_event = T.fired[seg];
+  // what did my neighbours send of this tensor in this iteration? (then vl / vr are set)
+  bool from_l = false, from_r = false, some_l = false, some_r = false;   // all / some of their tensor
+  if (PULL) {
+    const uint32_t fl = T.fired[lw * T.L + cd.layer], fr = T.fired[rw * T.L + cd.layer];
+    from_l = fl == 1;
+    from_r = fr == 1;
+    some_l = TOPK && fl == 2;
+    some_r = TOPK && fr == 2;
   }
-  // step n reads copy (n-1) & 1 of x and writes copy n & 1; where a kernel ahead of this one ran
-  // the tests it has counted this step already
+  // step n reads copy (n-1) & 1 of x and writes copy n & 1; the kernel that ran the tests has counted this step already
   const size_t arena = (size_t)T.P * T.Npad;
-  const uint64_t step_no = !PULL ? 0 : TESTS ? (uint64_t)A.step_no + 1 : T.it->iters;
+  const uint64_t step_no = PULL ? T.it->iters : 0;
   const float* snap_in = PULL ? T.xsnap + ((step_no + 1) & 1) * arena : nullptr;
   float* snap_out = PULL ? T.xsnap + (step_no & 1) * arena : nullptr;
   // xhat := x for the whole tensor: after a whole send, or after any event when a Top-K
@@ -322,14 +284,6 @@ static void launch_update_w(const Tables& t, const StepArgs& a, uint32_t dist, u
                             hipStream_t s) {
   const dim3 grid(t.C * (t.SW / SPW), t.P), block(kThreads);
   if (a.pull) {              // the host sets pull only for cache-resident rings
-    if (!TOPK && a.one_launch) {      // ... and one_launch only where the pass accumulates the norms (NORM != 0)
-      constexpr bool TS = !TOPK && NORM != 0;
-      constexpr int S1 = TOPK ? SPW : 1;
-      if (grad_mode == 1) k_update<0, true, NORM, TOPK, HISTA, S1, false, true, TS><<<grid, block, 0, s>>>(t, a);
-      else if (dist == 0) k_update<0, false, NORM, TOPK, HISTA, S1, false, true, TS><<<grid, block, 0, s>>>(t, a);
-      else k_update<1, false, NORM, TOPK, HISTA, S1, false, true, TS><<<grid, block, 0, s>>>(t, a);
-      return;
-    }
     if (grad_mode == 1) k_update<0, true, NORM, TOPK, HISTA, SPW, false, true><<<grid, block, 0, s>>>(t, a);
     else if (dist == 0) k_update<0, false, NORM, TOPK, HISTA, SPW, false, true><<<grid, block, 0, s>>>(t, a);
     else k_update<1, false, NORM, TOPK, HISTA, SPW, false, true><<<grid, block, 0, s>>>(t, a);

@@ -16,29 +16,13 @@
 // eight wavefronts, 4 a SIMD; with mailboxes read (RESET) 123 - 135, 4 or 3.  All use 106 scalar registers and spill
 // some tens of them to vector lanes: what more a Top-K walk keeps per worker costs 1 - 2 % at once.
 #include "message_device.h"
+#include "quad_device.h"
 #include "trigger_device.h"
 
 namespace evg {
 
-constexpr int kNt = 2;                        // non-temporal: every line is touched once (ordinary stores: 1100 -> 1360 us
-                                              // with Top-K 10 % of 16 workers, ordinary loads: 2 .. 9 % slower)
-constexpr uint32_t kNowhere = 0xFFFFFFF0u;    // an offset past every window
-
-struct Quad { float v[4]; };
-
-__device__ __forceinline__ Quad load_quad(const float* at, uint32_t bytes, uint32_t byte) {
-  const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(window(at, bytes), (int)byte, 0, kNt);
-  Quad q;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) q.v[i] = __uint_as_float(t[i]);
-  return q;
-}
-__device__ __forceinline__ void store_quad(float* at, uint32_t bytes, uint32_t byte, const Quad& q) {
-  u32x4 t;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) t[i] = __float_as_uint(q.v[i]);
-  __builtin_amdgcn_raw_buffer_store_b128(t, window(at, bytes), (int)byte, 0, kNt);
-}
+// Accesses are non-temporal: every line is touched once (ordinary stores: 1100 -> 1360 us with Top-K 10 % of 16 workers,
+// ordinary loads: 2 .. 9 % slower).
 
 // A copy that stays where it is written: the registers of the original are free for the next load from
 // here on (left to itself the compiler loads elsewhere and moves the values at the loop's end, which
@@ -48,34 +32,6 @@ __device__ __forceinline__ Quad taken(const Quad& q) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) asm volatile("v_mov_b32 %0, %1" : "=v"(c.v[i]) : "v"(q.v[i]));
   return c;
-}
-
-// The sum of wave_sum, in its order of additions, without LDS: halves and rows change places for the
-// first two steps; from then on a row's values repeat with the step's period, so that a rotation
-// brings the same value as the exchange.
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const uint64_t b = (uint64_t)__double_as_longlong(v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xF, 0xF, true);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
-  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-__device__ __forceinline__ double wave_sum_dpp(double v) {
-  uint64_t b = (uint64_t)__double_as_longlong(v);
-  const auto l32 = __builtin_amdgcn_permlane32_swap((uint32_t)b, (uint32_t)b, false, false);
-  const auto h32 = __builtin_amdgcn_permlane32_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
-  v = __longlong_as_double((long long)(((uint64_t)h32[0] << 32) | l32[0])) +
-      __longlong_as_double((long long)(((uint64_t)h32[1] << 32) | l32[1]));
-  b = (uint64_t)__double_as_longlong(v);
-  const auto l16 = __builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false);
-  const auto h16 = __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
-  v = __longlong_as_double((long long)(((uint64_t)h16[0] << 32) | l16[0])) +
-      __longlong_as_double((long long)(((uint64_t)h16[1] << 32) | l16[1]));
-  v += dpp_f64<0x128>(v);   // row_ror:8
-  v += dpp_f64<0x124>(v);   // row_ror:4
-  v += dpp_f64<0x122>(v);   // row_ror:2
-  v += dpp_f64<0x121>(v);   // row_ror:1
-  return v;
 }
 
 // What the walk has to know of a worker; lane i of a wavefront holds the i-th worker's.
@@ -159,7 +115,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
       const bool sends = (f & kCode) != 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) q.v[i] = sends ? x.v[i] : h.v[i];
-      store_quad(at(T.xhat, s), sends ? to_hat : 0u, byte, q);
+      store_quad<true>(at(T.xhat, s), sends ? to_hat : 0u, byte, q);
       sent = (f & kCode) == 1 ? (1u << nv) - 1u : win;
       return q;
     }
@@ -176,9 +132,9 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
       for (int i = 0; i < 4; ++i) q.v[i] = whole ? x.v[i] : h.v[i];
     }
     const bool sends = (f & kCode) != 0;
-    store_quad(at(T.xhat, s), sends && !led ? to_hat : 0u, where, q);
-    store_quad(at(T.mbox_l, s + 1 == P ? 0u : s + 1), sends ? to_right : 0u, where, q);
-    store_quad(at(T.mbox_r, s == 0 ? P - 1 : s - 1), sends ? to_left : 0u, where, q);
+    store_quad<true>(at(T.xhat, s), sends && !led ? to_hat : 0u, where, q);
+    store_quad<true>(at(T.mbox_l, s + 1 == P ? 0u : s + 1), sends ? to_right : 0u, where, q);
+    store_quad<true>(at(T.mbox_r, s == 0 ? P - 1 : s - 1), sends ? to_left : 0u, where, q);
     return q;
   };
   // does the walk need xhat from memory?  (not where the whole tensor has just been sent)
@@ -201,18 +157,18 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
   // RESET: the next worker's mailboxes; x before its update, and what it sent, of the worker before, the first and the last
   Quad ml1{}, mr1{}, xl{}, x_first{};
   uint32_t sent_l = 0, sent_c = 0, sent_first = 0, sent_last = 0;
-  auto mailbox = [&](float* m, uint32_t s, uint32_t f, uint32_t filled) { return load_quad(at(m, s), f & filled ? nb : 0u, byte); };
+  auto mailbox = [&](float* m, uint32_t s, uint32_t f, uint32_t filled) { return load_quad<true>(at(m, s), f & filled ? nb : 0u, byte); };
   auto receive = [&](float* m, uint32_t s, uint32_t sent, const Quad& from, Quad& held) {
     take_winners(sent, from.v, held.v);
-    store_quad(at(m, s), nb, any_of_line_part(sent) ? byte : kNowhere, held);
+    store_quad<true>(at(m, s), nb, any_of_line_part(sent) ? byte : kNowhere, held);
   };
   if (!dead) {
     const uint32_t before = r0 == 0 ? P - 1 : r0 - 1;
-    x_last = load_quad(at(T.x, before), closed ? nb : 0u, byte);
-    xc = load_quad(at(T.x, r0), nb, byte);
-    x1 = load_quad(at(T.x, worker(1)), 1 <= last_x ? nb : 0u, byte);
-    v1 = load_quad(at(T.vel, r0), nb_vel, byte);
-    if (GRADBUF) g1 = load_quad(A.grad + (size_t)r0 * T.Npad + off, nb, byte);
+    x_last = load_quad<true>(at(T.x, before), closed ? nb : 0u, byte);
+    xc = load_quad<true>(at(T.x, r0), nb, byte);
+    x1 = load_quad<true>(at(T.x, worker(1)), 1 <= last_x ? nb : 0u, byte);
+    v1 = load_quad<true>(at(T.vel, r0), nb_vel, byte);
+    if (GRADBUF) g1 = load_quad<true>(A.grad + (size_t)r0 * T.Npad + off, nb, byte);
     const uint32_t seg_b = before * T.L + layer;
     uint32_t f_b = __builtin_amdgcn_readfirstlane((int)T.fired[seg_b]);
     if (is_led(T, A, before)) f_b |= kLed;
@@ -223,9 +179,9 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
       place_b = message_place(T, before * T.C + c, sub0 * 4 + wave_id(), T.sel_krem[seg_b]);
     }
     const uint32_t f0 = read_mark(cur.f, nxt.f, 0);
-    const Quad h_last = load_quad(at(T.xhat, before), reads_hat(f_b) ? nb : 0u, byte);
-    const Quad h0 = load_quad(at(T.xhat, r0), reads_hat(f0) ? nb : 0u, byte);
-    h1 = load_quad(at(T.xhat, worker(1)), 1 <= last_h && reads_hat(read_mark(cur.f, nxt.f, 1)) ? nb : 0u, byte);
+    const Quad h_last = load_quad<true>(at(T.xhat, before), reads_hat(f_b) ? nb : 0u, byte);
+    const Quad h0 = load_quad<true>(at(T.xhat, r0), reads_hat(f0) ? nb : 0u, byte);
+    h1 = load_quad<true>(at(T.xhat, worker(1)), 1 <= last_h && reads_hat(read_mark(cur.f, nxt.f, 1)) ? nb : 0u, byte);
     if (RESET) {
       ml1 = mailbox(T.mbox_l, r0, f0, kLeftFilled);
       mr1 = mailbox(T.mbox_r, r0, f0, kRightFilled);
@@ -259,10 +215,10 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
       const uint32_t f2 = read_mark(cur.f, nxt.f, i + 2);
       const uint32_t s1 = worker(i + 1), s2 = i + 2 <= n ? worker(i + 2) : 0u;
       const bool another = i + 1 < n;
-      x1 = load_quad(at(T.x, s2), i + 2 <= last_x ? nb : 0u, byte);
-      h1 = load_quad(at(T.xhat, s2), i + 2 <= last_h && reads_hat(f2) ? nb : 0u, byte);
-      v1 = load_quad(at(T.vel, another ? r + 1 : 0), another ? nb_vel : 0u, byte);
-      if (GRADBUF) g1 = load_quad(A.grad + (size_t)(another ? r + 1 : 0) * T.Npad + off, another ? nb : 0u, byte);
+      x1 = load_quad<true>(at(T.x, s2), i + 2 <= last_x ? nb : 0u, byte);
+      h1 = load_quad<true>(at(T.xhat, s2), i + 2 <= last_h && reads_hat(f2) ? nb : 0u, byte);
+      v1 = load_quad<true>(at(T.vel, another ? r + 1 : 0), another ? nb_vel : 0u, byte);
+      if (GRADBUF) g1 = load_quad<true>(A.grad + (size_t)(another ? r + 1 : 0) * T.Npad + off, another ? nb : 0u, byte);
       if (RESET) {
         ml1 = mailbox(T.mbox_l, another ? r + 1 : 0, another ? fn : 0u, kLeftFilled);
         mr1 = mailbox(T.mbox_r, another ? r + 1 : 0, another ? fn : 0u, kRightFilled);
@@ -295,8 +251,8 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
         xc.v[i] = in ? xnew : xc.v[i];
         vel.v[i] = in ? vn : vel.v[i];
       }
-      store_quad(at(T.x, r), nb, byte, xc);
-      store_quad(at(T.vel, r), nb_vel, byte, vel);
+      store_quad<true>(at(T.x, r), nb, byte, xc);
+      store_quad<true>(at(T.vel, r), nb_vel, byte, vel);
       if (NORM) {
         double acc = 0.0, acc_hat = 0.0;
 #pragma unroll

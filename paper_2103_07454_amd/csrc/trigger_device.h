@@ -2,6 +2,7 @@
 // run it: k_trigger / k_topk_decide (one wavefront per tensor, ahead of the update pass) and the
 // update pass of rings that take a single launch per iteration (every workgroup repeats the
 // tests it depends on; the tensor's first workgroup records the outcome).
+// There the wavefronts sum several tensors at a time (kernels_parts.hip); test and booking are the same.
 //
 // What a test READS (sweep sums, delta, last_event, xhat_sq) and what an event WRITES of the
 // same (delta, last_event, xhat_sq; the sweep sums are written by the update pass) go through
@@ -48,36 +49,33 @@ __device__ __forceinline__ void segment_sums(const Tables& T, const StepArgs& A,
   *hat_sums_out = hat_sums;
 }
 
-// The event condition || xhat - x || >= delta (Section 4) on those sums, for ONE lane.  Returns
+// The tested quantity, from the tensor's sums.
+__device__ __forceinline__ float tested_norm(const StepArgs& A, double acc, double acc_hat) {
+  return A.norm_src == 0 ? (float)sqrt(acc) : __builtin_fabsf((float)sqrt(acc) - (float)sqrt(acc_hat));
+}
+
+// The event condition || xhat - x || >= delta (Section 4).  dl: threshold, khat: iteration of the last event.  Returns
 // 0 silent, 1 the whole tensor is sent, 2 a Top-K message is sent.
-// k: the iteration.
-// RECORD: also book the outcome: norm, threshold before, near-tie flag, counters, and at an
-// event the adaptive threshold (Eq. 3), the event's iteration and the event counters.
-// MARK: at an event also mark the two neighbours' mailbox slots as filled.
-template <bool RECORD, bool MARK>
-__device__ __forceinline__ uint8_t segment_test(const Tables& T, const StepArgs& A, uint32_t seg, double acc,
-                                                double acc_hat, bool hat_sums, uint32_t k) {
-  const uint32_t r = seg / T.L, l = seg % T.L;
-  float d;
-  if (A.norm_src == 0) {
-    d = (float)sqrt(acc);
-  } else {
-    if (!hat_sums) acc_hat = T.xhat_sq[seg];
-    d = __builtin_fabsf((float)sqrt(acc) - (float)sqrt(acc_hat));
-  }
-  const float dl = T.delta[seg];
-  const int32_t khat = T.last_event[seg];
+__device__ __forceinline__ uint8_t event_code(const StepArgs& A, float d, float dl, int32_t khat, uint32_t k) {
   const bool fire = (A.force_first && k == 0) || (d >= dl);   // NaN never fires
   // a tensor's first message has nothing to patch on the receiving side: send it whole
-  const uint8_t code = !fire ? 0 : (!A.topk_on || khat < 0) ? 1 : 2;
-  if (!RECORD) return code;
+  return !fire ? 0 : (!A.topk_on || khat < 0) ? 1 : 2;
+}
 
+// Books the outcome of a test, by ONE lane: norm, threshold before, near-tie flag, counters, and at an event the adaptive
+// threshold (Eq. 3), the event's iteration and the event counters.
+// MARK: at an event also mark the two neighbours' mailbox slots as filled.
+template <bool MARK>
+__device__ __forceinline__ void book_test(const Tables& T, const StepArgs& A, uint32_t seg, float d, float dl, int32_t khat,
+                                          uint8_t code, double acc, uint32_t k) {
+  const bool fire = code != 0;
   T.last_norm[seg] = d;
   T.delta_before[seg] = dl;
-  if (!(__builtin_fabsf(d) <= 3.402823466e+38f)) T.nonfinite_cnt[seg] += 1;   // NaN or inf
+  // (additions that return nothing: nobody waits for them)
+  if (!(__builtin_fabsf(d) <= 3.402823466e+38f)) atomicAdd(&T.nonfinite_cnt[seg], 1u);   // NaN or inf
   const bool near = __builtin_fabsf(d - dl) < 1e-6f * dl;
   T.near_tie[seg] = near ? 1 : 0;
-  if (near) T.near_cnt[seg] += 1;
+  if (near) atomicAdd(&T.near_cnt[seg], 1u);
   float dl_new = dl;
   if (fire) {
     if (A.thr_mode == 1) {
@@ -99,9 +97,9 @@ __device__ __forceinline__ uint8_t segment_test(const Tables& T, const StepArgs&
         dl_new = A.horizon * (sum / (float)cnt);
       }
     }
-    if (code == 1) T.ev_full[seg] += 1;
-    else T.ev_topk[seg] += 1;
+    atomicAdd(code == 1 ? &T.ev_full[seg] : &T.ev_topk[seg], 1u);
     if (MARK && !A.delay) {             // with delayed delivery: set when the put lands (k_deliver)
+      const uint32_t r = seg / T.L, l = seg % T.L;
       const uint32_t left = (r + T.P - 1) % T.P, right = (r + 1) % T.P;
       T.valid_r[left * T.L + l] = 1;    // I am my left neighbour's right-hand source
       T.valid_l[right * T.L + l] = 1;
@@ -112,6 +110,16 @@ __device__ __forceinline__ uint8_t segment_test(const Tables& T, const StepArgs&
   // the whole tensor is sent: xhat becomes x, and so does its squared norm
   if (A.norm_src == 1) T.xhat_sq_out[seg] = fire ? acc : T.xhat_sq[seg];
   T.fired[seg] = code;
+}
+
+// Test and booking of a tensor whose sums are at hand, by ONE lane; k: the iteration.
+__device__ __forceinline__ uint8_t segment_test(const Tables& T, const StepArgs& A, uint32_t seg, double acc, double acc_hat,
+                                                bool hat_sums, uint32_t k) {
+  if (A.norm_src != 0 && !hat_sums) acc_hat = T.xhat_sq[seg];
+  const float d = tested_norm(A, acc, acc_hat), dl = T.delta[seg];
+  const int32_t khat = T.last_event[seg];
+  const uint8_t code = event_code(A, d, dl, khat, k);
+  book_test<true>(T, A, seg, d, dl, khat, code, acc, k);
   return code;
 }
 
@@ -131,7 +139,7 @@ __device__ __forceinline__ void close_step(const Tables& T, const StepArgs& A) {
   } else {
     T.it->k_next = k + 1;
   }
-  T.it->iters += 1;
+  atomicAdd(reinterpret_cast<unsigned long long*>(&T.it->iters), 1ull);     // (returns nothing: nobody waits for it)
 }
 // By the first workgroup of the update pass.
 __device__ __forceinline__ void end_replayable(const Tables& T, const StepArgs& A) {
