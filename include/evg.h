@@ -146,8 +146,8 @@ typedef struct {
    * evg_average's out).  Between evg_init and evg_destroy xhat and the mailboxes are the
    * library's to write: a mailbox that has received equals its sender's xhat (unless
    * delivery is delayed or xhat_reset moves xhat without a message), and evg_step reads
-   * whichever copy is nearer.  So is x, of which the update pass carries norms, histograms and
-   * copies on to the next step (a Top-K tensor whose histogram no longer fits it sends nothing);
+   * whichever copy is nearer.  So is x, of which the update pass carries norms, histograms, key codes and
+   * copies on to the next step (a Top-K tensor whose keys are seen not to fit them sends nothing);
    * with EVG_NORM_SEPARATE nothing but a cached whole-tensor ring's copies is carried, and
    * in every other ring the caller may write x between two steps. */
   float* x;      /* current parameters                                   */

@@ -275,7 +275,7 @@ struct TableSum {
 
 // Bytes of library-owned device tables a configuration needs: the same list as the allocations of init_common.
 static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uint64_t hist_len, uint64_t Npad,
-                            uint64_t ktot, bool topk, bool norm_diff, bool pull, bool one_launch, uint64_t windows, uint64_t parts) {
+                            uint64_t ktot, bool topk, bool norm_diff, bool pull, bool one_launch, uint64_t windows, uint64_t parts, bool codes) {
   const uint64_t S = P * L, PC = P * C;
   TableSum t;
   t.add(C, sizeof(ChunkDesc)); t.add(L, sizeof(LayerDesc));
@@ -298,6 +298,8 @@ static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uin
     t.add(P * (Npad / 16 * 4), 4);                               // stage_key
     t.add(PC * SW * 4, 4); t.add(PC, 8); t.add(PC, 8);           // group, chunk_cnt, chunk_before
     t.add(P * ktot, 4); t.add(P * ktot, 4); t.add(S, 8); t.add(S, 8);
+    t.add(S, 4); t.add(S, 4);                                     // anchor, sel_left
+    if (codes) t.add(P * Npad, 1);
   }
   return t.total;
 }
@@ -465,6 +467,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   bool pull = c->cached && !cfg->delivery_delay &&
               !(cfg->topk_ppm && (cfg->xhat_reset || cfg->norm_mode == EVG_NORM_SEPARATE || !copies_fit));
   bool in_parts = false, one_launch = false, may_be = true;
+  bool codes = cfg->topk_ppm && cfg->norm_mode == EVG_NORM_FUSED && !c->cached;     // (from the cache x and xhat are read as fast)
   uint64_t need = 0, ring_windows = 0;
   uint32_t ring_part = 0;
   auto cut_chunks = [&](bool on_lines) {
@@ -500,7 +503,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     if (in_parts && !one_launch) ring_part = std::min<uint32_t>(ring_part, 4);
     need = table_bytes(P, L, chunks.size(), SW, hist_len, Npad, ktot, cfg->topk_ppm != 0,
                        cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF, pull && !(in_parts && ring_part == P), one_launch,
-                       in_parts ? ring_windows : 0, (P + ring_part - 1) / ring_part);
+                       in_parts ? ring_windows : 0, (P + ring_part - 1) / ring_part, codes);
     return (uint64_t)P * chunks.size() * (SW + 1) <= 0xFFFFFFF0ull && (uint64_t)P * ktot <= 0xFFFFFFF0ull &&
            !(use_scratch && need > kScratchBytes);
   };
@@ -509,6 +512,10 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   if (use_scratch && need > kScratchBytes && in_parts) {        // thousands of short tensors: no room for what the parts take
     may_be = false;
     (void)cut_chunks(false);
+  }
+  if (use_scratch && need > kScratchBytes && codes) {           // no room for key codes: x and xhat are read instead
+    codes = false;
+    (void)cut_chunks(c->on_lines);
   }
   if (use_scratch && need > kScratchBytes && pull && cfg->topk_ppm) {   // no room for the copies of x: messages are applied
     pull = false;                                                        // by a kernel of their own
@@ -696,6 +703,12 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     TRY_OR_FREE(c->dalloc(&t.chunk_before, P * C, true));
     TRY_OR_FREE(c->dalloc(&t.msg_idx, (uint64_t)P * ktot, true));
     TRY_OR_FREE(c->dalloc(&t.msg_val, (uint64_t)P * ktot, true));
+    TRY_OR_FREE(c->dalloc(&t.sel_left, S, true));
+    if (cfg->norm_mode == EVG_NORM_FUSED) {
+      TRY_OR_FREE(c->dalloc(&t.anchor, S, false));
+      HIP_OR_FREE(hipMemsetAsync(t.anchor, 0xFF, S * 4, c->stream));      // kNoAnchor
+    }
+    if (codes) TRY_OR_FREE(c->dalloc(&t.codes, (uint64_t)P * Npad, true));
     TRY_OR_FREE(c->dalloc(&t.idx_hash, S, true));
     TRY_OR_FREE(c->dalloc(&t.msg_hash, S, true));
   }
@@ -1028,7 +1041,7 @@ std::vector<Piece> state_pieces(evg_ctx* c) {
 StateHeader state_header(evg_ctx* c) {
   StateHeader h{};
   std::memcpy(h.magic, "EVGSTATE", 8);
-  h.version = 5;
+  h.version = 6;
   h.P = c->t.P; h.L = c->t.L; h.C = c->t.C; h.SW = c->t.SW; h.S = c->t.S;
   h.hist_len = c->t.hist_len;
   h.topk_ppm = c->cfg.topk_ppm;
@@ -1070,6 +1083,13 @@ evg_status evg_state_export(evg_ctx* c, void* blob, uint64_t capacity) {
     HIP_TRY(hipMemcpy(out, p.dev, p.bytes, hipMemcpyDeviceToHost));
     out += p.bytes;
   }
+  if (c->t.anchor) {       // (see evg_state_import)
+    std::unique_ptr<uint32_t[]> anchors(new (std::nothrow) uint32_t[c->t.S]);
+    if (!anchors) return fail(EVG_ERR_OOM, "host allocation failed");
+    HIP_TRY(hipMemcpy(anchors.get(), c->t.anchor, (size_t)c->t.S * 4, hipMemcpyDeviceToHost));
+    char* hists = out - (size_t)c->t.S * kHistBins * 4;
+    for (size_t i = 0; i < c->t.S; ++i) std::memcpy(hists + (i * kHistBins + kHistBins - 1) * 4, &anchors[i], 4);
+  }
   return EVG_OK;
 }
 
@@ -1108,7 +1128,7 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
   StateHeader want = state_header(c);
   want.C = got.C;
   want.SW = got.SW;
-  if (got.version == 3 || got.version == 4) want.version = got.version;
+  if (got.version >= 3 && got.version < 6) want.version = got.version;
   want.pad = (want.pad & ~(kCutOnLines | kCutFiner)) | flags;
   want.iters = got.iters;
   want.last_iter = got.last_iter;
@@ -1120,6 +1140,14 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
   const size_t clock_count = c->one_launch ? (size_t)c->parts.count * ((t.P + c->part - 1) / c->part) : 0;
   std::unique_ptr<PartClock[]> clocks(new (std::nothrow) PartClock[clock_count + 1]);
   if (!clocks) return fail(EVG_ERR_OOM, "host allocation failed");
+  // anchors of key codes: in the last word of a tensor's saved histogram, which the bins do not reach, from version 6 on
+  std::unique_ptr<uint32_t[]> anchors(new (std::nothrow) uint32_t[t.S]);
+  if (!anchors) return fail(EVG_ERR_OOM, "host allocation failed");
+  const char* hists = static_cast<const char*>(blob) + size - (size_t)t.S * kHistBins * 4;      // (the last piece, if there is one)
+  for (size_t i = 0; t.anchor && i < t.S; ++i) {
+    anchors[i] = kNoAnchor;
+    if (got.version >= 6) std::memcpy(&anchors[i], hists + (i * kHistBins + kHistBins - 1) * 4, 4);
+  }
   std::fill_n(clocks.get(), clock_count, PartClock{(uint32_t)(got.last_iter + 1), (uint32_t)got.iters});
   c->iters = got.iters;
   c->last_iter = got.last_iter;
@@ -1158,6 +1186,14 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
   }
   if (clock_count)
     HIP_TRY(hipMemcpyAsync(c->parts.clocks, clocks.get(), clock_count * sizeof(PartClock), hipMemcpyHostToDevice, c->stream));
+  if (t.anchor) {
+    // Histograms and key codes are counted again, from the arenas: the saved ones go by eighths of an octave in versions before 6.
+    StepArgs a{};
+    a.topk_key = c->cfg.topk_key;
+    HIP_TRY(hipMemcpyAsync(t.anchor, anchors.get(), (size_t)t.S * 4, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(hipMemsetAsync(t.hist, 0, (size_t)t.S * kHistBins * 4, c->stream));
+    HIP_TRY(launch_topk_count_all(t, a, c->chunk_elems, c->stream));
+  }
   // the library's copy of x follows the caller's arena, which holds the saved parameters again
   if (c->t.xsnap) {
     const size_t arena = (size_t)c->t.P * c->t.Npad;

@@ -9,12 +9,18 @@ constexpr int kThreads = 256;          // 4 wavefronts of 64 lanes
 constexpr int kLaneElems = 4;          // one float4 per lane and sweep
 constexpr int kSweep = kThreads * kLaneElems;   // elements one workgroup covers per sweep
 constexpr uint32_t kLineElems = 32;    // floats of a 128-byte cache line
-constexpr int kHistBins = 2048;        // 11 key bits per selection pass (passes A, B); pass C uses 512
+constexpr int kHistBins = 2048;        // histogram of a selection pass: the second takes 11 bits of a key
+constexpr int kFirstBins = 1280;       // the first (see first_bins)
+constexpr uint32_t kCoarseBits = 21, kFineBits = 17;                  // bits of a key below its coarse and fine bins
+constexpr uint32_t kPerCoarse = 1u << (kCoarseBits - kFineBits);      // fine bins of a coarse one
+constexpr uint32_t kFineBins = 128;                                   // fine bins
+constexpr int kLastBins = 1024;        // the last takes what is left, 6 or 10 bits
 constexpr uint32_t kStageCap = 2048;   // staged keys of a chunk at most
 // Threshold key that no key reaches (they have 31 bits).  A selection ends with it where it would not find exactly K
 // winners: the histogram that the last update pass left does not fit x and xhat, which the caller has written since.
 // Nothing is sent then; the update passes write a message's winners without a look at its length.
 constexpr uint32_t kNoThreshold = 0xFFFFFFFFu;
+constexpr uint32_t kNoAnchor = 0xFFFFFFFFu;
 
 // A chunk is a run of one tensor's elements that one workgroup handles; it never
 // straddles tensors, starts at a multiple of 4 elements and is at most chunk_elems long.
@@ -97,8 +103,12 @@ struct Tables {
   uint32_t* sel_cut;       // [S] the last element of the tensor that wins with a key equal to the threshold
   uint32_t* stage_n;       // [P*C] staged keys of a chunk: those in the threshold bin; 0xFFFFFFFF: more than the
                            // chunk's slot holds, nothing staged (they are then read from the arenas)
-  uint32_t* stage_key;     // [P*stage_stride] their low 20 bits, and the group in the chunk they belong to
+  uint32_t* stage_key;     // [P*stage_stride] their bits below the bin (at most 21), and from bit 21 on the group of the chunk they belong to
   uint64_t stage_stride;   // staging entries per worker
+  uint8_t* codes;          // [P*Npad] or null: rank keys of x and xhat as the last update pass left them, in a byte: bits 30..17
+                           // counted from the tensor's anchor; 0 and 255 also stand for all that is further off
+  uint32_t* anchor;        // [S] or null: where the fine bins of the first pass's histogram begin; kNoAnchor: there are none
+  uint32_t* sel_left;      // [S] bits of a key below the first pass's bin, and from bit 8 on the code of that bin's keys (0: none)
   uint32_t* group;         // [P*C*SW*4] per 256 elements: keys above the threshold bin; in the end, over the chunk's
                            // earlier groups, keys above (low half) and equal to (high half) the threshold
   uint2* chunk_cnt;        // [P*C] keys above and equal to the threshold per chunk
@@ -159,6 +169,8 @@ hipError_t launch_copy(const Tables& t, const StepArgs& a, uint32_t chunk_elems,
 hipError_t launch_deliver(const Tables& t, uint32_t chunk_elems, hipStream_t s);
 hipError_t launch_topk_decide(const Tables& t, const StepArgs& a, hipStream_t s);
 hipError_t launch_topk_select(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
+// pass A's histograms and the key codes of all tensors, as an update pass leaves them; added to the histograms that are there
+hipError_t launch_topk_count_all(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
 hipError_t launch_topk_apply(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
 hipError_t launch_average(const Tables& t, float* out, hipStream_t s);
 hipError_t launch_message_hashes(const Tables& t, hipStream_t s);

@@ -8,19 +8,22 @@
 // registers afterwards -- the update pass -- can tell the winners by itself, and where they belong
 // in the message from the number of winners before its group of 256 elements.
 //
-//   k_topk_hist     pass A where the previous update pass has not done it: histogram of key bits 30..20 per tensor
+//   k_topk_hist     pass A where the previous update pass has not done it: histogram of the keys per tensor, in the bins of first_bins
 //   k_topk_decide   trigger test, and the bin b that holds the K-th largest key (k_topk_pick: the latter alone)
 //   k_topk_stage    the one pass over the fired tensors: per group of 256 elements how many keys lie above
-//                   bin b, and the keys IN bin b (a 9 .. 12 % wide slice of the key range, some per cent of the
-//                   tensor), whose bits 19..9 it counts
-//   k_topk_low      bits 8..0 of the in-bin keys under the 22-bit prefix -> threshold key
+//                   bin b, and the keys IN bin b (a sixty-fourth of an octave where the threshold was expected, some 0.4 % of the
+//                   tensor), whose next 11 bits it counts.  From the key codes of the last update pass, 1 byte an element
+//                   instead of 8, where bin b has a code: only the keys in it are fetched then
+//   k_topk_low      the last bits of the in-bin keys under the prefix found so far -> threshold key
 //   k_topk_count    keys above and equal to the threshold per group, as running totals over a chunk
 //   k_topk_scan     the same over a tensor's chunks, and the cut
 //   k_topk_apply    messages written and applied ahead of the update pass, where that pass cannot
+// Codes and fine bins, steps before -> now: 16 ResNet-18 workers with given gradients, 10 % 1371 -> 1277 us (k_topk_stage 184 -> 61, the
+// walk, which writes the codes, 1156 -> 1173), 64 4903 -> 4538, 8 ResNet-50 workers, 1 %, Student-t 1269 -> 1199.  Of the keys' bins
+// 128 are fine: with 256 the walk merges more counts (ResNet-50 1220), with a thirty-second of an octave each the stage fetches
+// more (64 workers 4647); bins of an eighth and codes that divide them cost a launch more and 1317 where 1277 is now.
 // (The selection used to stage every possible winner as (index, value) and to compact the messages from there;
-// the update passes then scattered three messages each into LDS.  One kernel per tensor for all that follows
-// the staging was slower than the five launches: 89 instead of 30 us for 16 ResNet-18 workers, whose largest
-// tensors have 72 000 in-bin keys.)
+// the update passes then scattered three messages each into LDS.)
 #include "trigger_device.h"
 #include "message_device.h"
 
@@ -65,12 +68,14 @@ __device__ __forceinline__ void flush_hist(const uint32_t* h, uint32_t* gh) {
   }
 }
 
-template <int SWEEPS>
+// ALL: of all tensors, not only of those that send a Top-K message now, by their anchors, and their key codes: what an update pass
+// leaves.
+template <int SWEEPS, bool ALL>
 __global__ __launch_bounds__(kThreads) void k_topk_hist(Tables T, StepArgs A) {
-  __shared__ uint32_t h[kHistBins];
+  __shared__ uint32_t h[kFirstBins];
   const WorkItem wi = work_item(T, blockIdx.y, blockIdx.x);
-  if (T.fired[wi.seg] != 2) return;          // uniform
-  for (uint32_t b = threadIdx.x; b < (uint32_t)kHistBins; b += kThreads) h[b] = 0;
+  if (!ALL && T.fired[wi.seg] != 2) return;          // uniform
+  for (uint32_t b = threadIdx.x; b < (uint32_t)kFirstBins; b += kThreads) h[b] = 0;
   __syncthreads();
 #pragma unroll
   for (int it = 0; it < SWEEPS; ++it) {
@@ -81,28 +86,30 @@ __global__ __launch_bounds__(kThreads) void k_topk_hist(Tables T, StepArgs A) {
       if (!A.topk_key) h4 = ld4s(T.xhat + wi.base + e);
       const float xa[4] = {x4.x, x4.y, x4.z, x4.w}, ha[4] = {h4.x, h4.y, h4.z, h4.w};
       const uint32_t nv = wi.cd.len - e < 4u ? wi.cd.len - e : 4u;
+      const Bins bins = first_bins(xa, ha, A.topk_key, ALL ? T.anchor[wi.seg] : kNoAnchor);
+      if (ALL && T.codes) store_codes(T, wi.base, (wi.cd.len + 3) / 4 * 16, e * 4, bins.codes);
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        if ((uint32_t)q < nv) atomicAdd(&h[rank_key(xa[q], ha[q], A.topk_key) >> 20], 1u);
+        if ((uint32_t)q < nv) atomicAdd(&h[bins.bin[q]], 1u);
     }
   }
   __syncthreads();
-  flush_hist<kHistBins>(h, T.hist + (size_t)wi.seg * kHistBins);
+  flush_hist<kFirstBins>(h, T.hist + (size_t)wi.seg * kHistBins);
 }
 
 // One workgroup per tensor that sends a Top-K message: find the bin that holds the krem-th largest key, append it to the
 // prefix, keep what is still to be taken inside that bin, and clear the histogram for the next pass.
-// PASS 0: bits 30..20, PASS 1: bits 19..9, PASS 2: bits 8..0.
+// PASS 0: the bins of first_bin, PASS 1: the next 11 bits, PASS 2: the rest.
 template <int PASS>
 __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t code, uint32_t* ws) {
-  constexpr int NB = PASS == 2 ? 512 : kHistBins;
+  constexpr int NB = PASS == 0 ? kFirstBins : PASS == 1 ? kHistBins : kLastBins;
   constexpr int PER = NB / kThreads;
   uint32_t* gh = T.hist + (size_t)seg * kHistBins;
   if (code != 2) {          // uniform for the workgroup
     // pass A histograms are built for every tensor when the update pass makes them:
     // those of tensors that stay silent are simply dropped
     if (PASS == 0)
-      for (uint32_t b = threadIdx.x; b < (uint32_t)kHistBins; b += kThreads) gh[b] = 0;
+      for (uint32_t b = threadIdx.x; b < (uint32_t)kFirstBins; b += kThreads) gh[b] = 0;
     return;
   }
   const uint32_t krem = PASS == 0 ? T.layers[seg % T.L].K : T.sel_krem[seg];
@@ -116,7 +123,10 @@ __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t
   }
   uint32_t total;
   const uint32_t above = block_excl_scan<4>(local, ws, &total);   // keys in higher bins
-  if (total < krem && threadIdx.x == 0) T.sel_prefix[seg] = kNoThreshold;   // (no later pass finds krem keys under this prefix either)
+  if (total < krem && threadIdx.x == 0) {
+    T.sel_prefix[seg] = kNoThreshold;
+    if (PASS == 0) T.sel_left[seg] = kCoarseBits;
+  }
   if (above < krem && krem <= above + local) {    // exactly one thread
     uint32_t run = above, bin = top, rem = krem - above;
 #pragma unroll
@@ -124,9 +134,22 @@ __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t
       if (run < krem && krem <= run + cnt[j]) { bin = top - j; rem = krem - run; }
       run += cnt[j];
     }
-    const uint32_t prefix = PASS == 0 ? 0u : T.sel_prefix[seg];
-    T.sel_prefix[seg] = PASS == 0 ? bin : PASS == 1 ? ((prefix << 11) | bin) : ((prefix << 9) | bin);
     T.sel_krem[seg] = rem;
+    if (PASS == 0) {
+      const uint32_t anchor = T.anchor ? T.anchor[seg] : kNoAnchor;
+      uint32_t left, next;
+      const uint32_t begin = bin_begin(bin, anchor, &left);
+      T.sel_prefix[seg] = begin;
+      const uint32_t fine = (begin >> kFineBits) - anchor;
+      T.sel_left[seg] = left | (T.codes && left == kFineBits && fine > 0u && fine < 255u ? fine << 8 : 0u);
+      if (T.anchor) {            // of the histogram and codes that the update pass will leave: this bin in the middle
+        next = (begin >> kFineBits) + kPerCoarse / 2;
+        T.anchor[seg] = next > kFineBins / 2 ? (next - kFineBins / 2) / kPerCoarse * kPerCoarse : 0u;
+      }
+    } else {
+      const uint32_t prefix = T.sel_prefix[seg];           // (a selection that has ended stays so)
+      if (prefix != kNoThreshold) T.sel_prefix[seg] = prefix + (PASS == 1 ? bin << ((T.sel_left[seg] & 255u) - 11u) : bin);
+    }
   }
 }
 
@@ -152,9 +175,69 @@ __global__ __launch_bounds__(kThreads) void k_topk_decide(Tables T, StepArgs A) 
   if (seg == 0 && threadIdx.x == 0) close_step(T, A);
 }
 
+// Staging from the key codes, 1 byte an element instead of 8: what has the code of the threshold bin is listed by its
+// position in the chunk, and only those keys are fetched.  A key that is not what its code says (the caller has written x
+// since) ends the selection.
+template <int SWEEPS>
+__device__ __forceinline__ void stage_by_codes(const Tables& T, const StepArgs& A, const WorkItem& wi, uint32_t begin, uint32_t code,
+                                               uint32_t* list, uint32_t* listed) {
+  const __amdgpu_buffer_rsrc_t codes = window(T.codes + wi.base, (wi.cd.len + 3) / 4 * 4);
+  uint32_t four[SWEEPS];
+#pragma unroll
+  for (int it = 0; it < SWEEPS; ++it) {
+    const uint32_t e = it * kSweep + threadIdx.x * kLaneElems - wi.cd.lead;   // positions before the lead wrap around
+    four[it] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(codes, (int)(e < wi.cd.len ? e : 0xFFFFFFF0u), 0, 2);
+    // what is past the tensor's end gets code 0, which no bin has that is told by codes
+    if (e < wi.cd.len && wi.cd.len - e < 4u) four[it] &= (1u << 8 * (wi.cd.len - e)) - 1u;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < SWEEPS; ++it) {
+    // bytes 0 and 2, 1 and 3, in halves of a register: adding 255 - code sets bit 8 of those above the code, 256 - code of
+    // those that have it too
+    const uint32_t p = four[it] & 0x00FF00FFu, q = (four[it] >> 8) & 0x00FF00FFu, more = (255u - code) * 0x10001u;
+    const uint32_t gp = (p + more) & 0x01000100u, gq = (q + more) & 0x01000100u;
+    const uint32_t ip = ((p + more + 0x10001u) & 0x01000100u) ^ gp, iq = ((q + more + 0x10001u) & 0x01000100u) ^ gq;
+    const uint32_t g = (gp >> 8) + (gq >> 8), above = (g + (g >> 16)) & 7u;    // 0 .. 4
+    const uint32_t n = __popcll(__ballot(above & 1u)) + 2 * __popcll(__ballot(above & 2u)) + 4 * __popcll(__ballot(above & 4u));
+    if (lane_id() == 0) T.group[(size_t)wi.w * (T.SW * 4) + it * 4 + wave_id()] = n;
+    if (ip | iq) {                                     // few lanes
+      const uint32_t pos = it * kSweep + threadIdx.x * kLaneElems;
+      const bool in[4] = {(ip & 0x100u) != 0, (iq & 0x100u) != 0, (ip >> 16) != 0, (iq >> 16) != 0};
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        if (in[b]) {
+          const uint32_t at = atomicAdd(listed, 1u);
+          if (at < kStageCap) list[at] = pos + b;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  const uint32_t n = *listed;
+  uint32_t* gh = T.hist + (size_t)wi.seg * kHistBins;
+  const __amdgpu_buffer_rsrc_t x = window(T.x + wi.base, wi.cd.len * 4), h = window(T.xhat + wi.base, A.topk_key ? 0u : wi.cd.len * 4);
+  auto low = [&](uint32_t pos) {
+    const uint32_t at = (pos - wi.cd.lead) * 4;
+    const float xv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(x, (int)at, 0, 0));
+    const float hv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(h, (int)at, 0, 0));
+    const uint32_t l = rank_key(xv, hv, A.topk_key) - begin;
+    if (l >> kFineBits) T.sel_prefix[wi.seg] = kNoThreshold;
+    atomicAdd(&gh[(l >> (kFineBits - 11)) & 2047u], 1u);
+    return l & ((1u << kFineBits) - 1u);
+  };
+  if (n <= kStageCap) {
+    for (uint32_t i = threadIdx.x; i < n; i += kThreads) list[i] = low(list[i]) | (list[i] >> 8) << 21;
+  } else {
+    for (uint32_t pos = wi.cd.lead + threadIdx.x; pos < wi.cd.lead + wi.cd.len; pos += kThreads)
+      if (T.codes[wi.base + pos - wi.cd.lead] == code) (void)low(pos);
+  }
+  __syncthreads();
+}
+
 // One workgroup per chunk; a wavefront's part of a sweep is a group of 256 elements.  Ballots give the
 // counts; the keys in the threshold bin are gathered in LDS, in no particular order (each carries its
-// group, in the bits above its low 20), and leave as one run.  Bound by reading x and xhat.
+// group, in the bits from the 21st on), and leave as one run.  Bound by reading x and xhat, or by instructions where it goes by codes.
 // COPY: 0 nothing to do for a tensor sent whole (it lands later, or the update pass sends it), 1 its chunk goes into
 // the two mailboxes, 2 into xhat, if its worker is at the end of a part of the ring (see copy_chunk): a
 // Top-K tensor's first send takes no launch of its own.
@@ -167,8 +250,11 @@ __global__ __launch_bounds__(kThreads) void k_topk_stage(Tables T, StepArgs A) {
   const uint32_t code = T.fired[wi.seg];      // uniform
   if (COPY && code == 1 && (COPY == 1 || is_led(T, A, wi.r))) copy_chunk<SWEEPS, STREAM, COPY == 2>(T, wi.r, wi.cd);
   if (code != 2) return;
-  const uint32_t bin = T.sel_prefix[wi.seg];
+  const uint32_t begin = T.sel_prefix[wi.seg], left = T.sel_left[wi.seg] & 255u, of_bin = T.sel_left[wi.seg] >> 8;
   if (threadIdx.x == 0) listed = 0;
+  if (of_bin) {                                        // uniform
+    stage_by_codes<SWEEPS>(T, A, wi, begin, of_bin, list, &listed);
+  } else {
   for (uint32_t b = threadIdx.x; b < (uint32_t)kHistBins; b += kThreads) h[b] = 0;
   __syncthreads();
 #pragma unroll
@@ -197,9 +283,12 @@ __global__ __launch_bounds__(kThreads) void k_topk_stage(Tables T, StepArgs A) {
       for (int q = 0; q < 4; ++q) {
         key[u][q] = rank_key(xa[q], ha[q], A.topk_key);
         const bool valid = (uint32_t)q < nv;
-        in[u][q] = __ballot(valid && (key[u][q] >> 20) == bin);
-        above += __popcll(__ballot(valid && (key[u][q] >> 20) > bin));
-        if (valid && (key[u][q] >> 20) == bin) atomicAdd(&h[(key[u][q] >> 9) & 2047u], 1u);
+        const int32_t low = (int32_t)(key[u][q] - begin);          // (both have 31 bits)
+        const bool is_in = valid && (uint32_t)low >> left == 0;
+        key[u][q] = (uint32_t)low;
+        in[u][q] = __ballot(is_in);
+        above += __popcll(__ballot(valid && low >> left > 0));
+        if (is_in) atomicAdd(&h[(uint32_t)low >> (left - 11u)], 1u);
         n_in[u] += __popcll(in[u][q]);
       }
       if (lane_id() == 0) T.group[(size_t)wi.w * (T.SW * 4) + (it + u) * 4 + wave_id()] = above;
@@ -216,13 +305,14 @@ __global__ __launch_bounds__(kThreads) void k_topk_stage(Tables T, StepArgs A) {
       for (int q = 0; q < 4; ++q) {
         const uint32_t pos = at + lanes_below(in[u][q]);
         if (((in[u][q] >> lane_id()) & 1ull) && pos < kStageCap)
-          list[pos] = (key[u][q] & 0xFFFFFu) | (((it + u) * 4 + wave_id()) << 20);
+          list[pos] = key[u][q] | (((it + u) * 4 + wave_id()) << 21);
         at += __popcll(in[u][q]);
       }
     }
   }
   __syncthreads();
   flush_hist<kHistBins>(h, T.hist + (size_t)wi.seg * kHistBins);
+  }
   const uint32_t n = listed;
   const bool over = n > stage_cap(wi.cd.len);        // uniform
   if (threadIdx.x == 0) {
@@ -293,8 +383,8 @@ __device__ __forceinline__ void in_bin_keys(const Tables& T, const StepArgs& A, 
   }
 }
 
-// Bits 8..0 of the in-bin keys that carry the 22-bit prefix found so far.  Matches are
-// rare (a 2^-22 slice of the key range), so they go straight to the tensor's histogram,
+// The last 6 or 10 bits of the in-bin keys that carry the prefix found so far.  Matches are
+// rare (a 2^-25 or 2^-21 slice of the key range), so they go straight to the tensor's histogram,
 // one atomic per distinct value per 64 entries.
 __global__ __launch_bounds__(kThreads) void k_topk_low(Tables T, StepArgs A) {
   WorkItem wi;
@@ -312,8 +402,9 @@ __global__ __launch_bounds__(kThreads) void k_topk_low(Tables T, StepArgs A) {
       todo &= ~same;
     }
   };
-  in_bin_keys(T, A, wi, [&](uint32_t e, bool in) { add(e & 511u, in && ((e >> 9) & 2047u) == (prefix & 2047u)); },
-              [&](uint32_t key, uint32_t, bool in) { add(key & 511u, in && (key >> 9) == prefix); });
+  const uint32_t bits = T.sel_left[wi.seg] & 255u, left = bits - 11u, mask = (1u << bits) - 1u, last = (1u << left) - 1u;
+  in_bin_keys(T, A, wi, [&](uint32_t e, bool in) { add(e & last, in && (e & mask) >> left == (prefix & mask) >> left); },
+              [&](uint32_t key, uint32_t, bool in) { add(key & last, in && key >> left == prefix >> left); });
 }
 
 // Keys above (low half) and equal to (high half) the threshold: per group the sum over the chunk's earlier groups, and
@@ -323,7 +414,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_count(Tables T, StepArgs A) {
   WorkItem wi;
   if (!wave_item(T, &wi)) return;
   uint32_t* cnt = counts[wave_id()];
-  const uint32_t t = T.sel_prefix[wi.seg], lane = lane_id(), G = T.SW * 4;
+  const uint32_t t = T.sel_prefix[wi.seg], mask = (1u << (T.sel_left[wi.seg] & 255u)) - 1u, lane = lane_id(), G = T.SW * 4;
   uint32_t* group = T.group + (size_t)wi.w * G;
   const uint32_t above = lane < G ? group[lane] : 0u;
   cnt[lane] = 0;
@@ -331,8 +422,8 @@ __global__ __launch_bounds__(kThreads) void k_topk_count(Tables T, StepArgs A) {
   bool staged = true;
   in_bin_keys(T, A, wi,
               [&](uint32_t e, bool in) {
-                const uint32_t k = e & 0xFFFFFu, t20 = t & 0xFFFFFu;
-                if (in && k >= t20) atomicAdd(&cnt[e >> 20], k == t20 ? 0x10000u : 1u);
+                const uint32_t k = e & mask;
+                if (in && k >= (t & mask)) atomicAdd(&cnt[e >> 21], k == (t & mask) ? 0x10000u : 1u);
               },
               [&](uint32_t key, uint32_t g, bool in) {
                 staged = false;
@@ -423,7 +514,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_apply(Tables T, StepArgs A) {
     float ha[4] = {h4.x, h4.y, h4.z, h4.w};
     const uint32_t nv = !live ? 0u : wi.cd.len - e < 4u ? wi.cd.len - e : 4u;
     const uint32_t win = winners4(xa, ha, A.topk_key, t, cut, wi.cd.j0 + e, nv);
-    put_message(T, wi.r, ld.msg_off, message_place(T, wi.w, it * 4 + wave_id(), T.sel_krem[wi.seg]), win, xa, wi.cd.j0 + e);
+    put_message(T, wi.r, ld.msg_off, message_place(T, wi.w, it * 4 + wave_id(), T.sel_krem[wi.seg]), in_vector(ld.K), win, xa, wi.cd.j0 + e);
     const bool changes = any_of_line_part(win) && live;
     if (LEAD) {
       take_winners(win, xa, ha);
@@ -501,7 +592,7 @@ template <int SWEEPS>
 static void select_s(const Tables& t, const StepArgs& a, hipStream_t s) {
   const dim3 g(t.C, t.P), gw((t.C + 3) / 4, t.P), b(kThreads), segs(t.S);
   if (!a.hist_fused) {
-    k_topk_hist<SWEEPS><<<g, b, 0, s>>>(t, a);
+    k_topk_hist<SWEEPS, false><<<g, b, 0, s>>>(t, a);
     k_topk_pick<0><<<segs, b, 0, s>>>(t);
   }
   if (a.delay || a.pull || (a.walk && a.part == t.P)) {
@@ -530,6 +621,22 @@ hipError_t launch_topk_select(const Tables& t, const StepArgs& a, uint32_t chunk
     case 2: select_s<2>(t, a, s); break;
     case 4: select_s<4>(t, a, s); break;
     case 8: select_s<8>(t, a, s); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+template <int SWEEPS>
+static void count_s(const Tables& t, const StepArgs& a, hipStream_t s) {
+  k_topk_hist<SWEEPS, true><<<dim3(t.C, t.P), dim3(kThreads), 0, s>>>(t, a);
+}
+
+hipError_t launch_topk_count_all(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s) {
+  switch (chunk_elems / kSweep) {
+    case 1: count_s<1>(t, a, s); break;
+    case 2: count_s<2>(t, a, s); break;
+    case 4: count_s<4>(t, a, s); break;
+    case 8: count_s<8>(t, a, s); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -60,7 +60,8 @@ __device__ __forceinline__ void block_sums(const double v[SPW], double* ws, doub
 // drift, 2 its squared x (xhat is then not read at all), 3 its squared x and squared xhat.
 // TOPK: Top-K messages of this iteration: my own is told from x and xhat as they pass through the registers, written to
 // the message buffers and applied to xhat; a neighbour's (PULL) from the copy of its x and from my mailbox.
-// HISTA: also histogram the top 11 bits of the new rank keys per tensor, the first
+// (TOPK with NORM also leaves the codes of the new rank keys, if the ring keeps any.)
+// HISTA: also histogram the new rank keys per tensor, the first
 // radix pass of the next iteration's Top-K selection, while the values are in registers.
 // SPW: consecutive sweeps of a chunk per workgroup (one float4 per thread and sweep).  Two halve the cost of
 // clearing and merging the histogram.
@@ -74,7 +75,7 @@ __device__ __forceinline__ void block_sums(const double v[SPW], double* ws, doub
 template <int DIST, bool GRADBUF, int NORM, bool TOPK, bool HISTA, int SPW, bool STREAM, bool PULL = false>
 __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
   __shared__ double ws[4 * SPW];
-  __shared__ uint32_t hA[HISTA ? kHistBins : 1];
+  __shared__ uint32_t hA[HISTA ? kFirstBins : 1];
   const uint32_t groups = T.SW / SPW;      // workgroups per chunk (SW is a multiple of SPW)
   const uint32_t c = blockIdx.x / groups, sub0 = (blockIdx.x % groups) * SPW, r = blockIdx.y;
   const ChunkDesc cd = T.chunks[c];
@@ -119,12 +120,14 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
     uint32_t nv[SPW];
     float lx[TOPK && PULL ? SPW : 1][4], rx[TOPK && PULL ? SPW : 1][4];   // the neighbours' x before this iteration's update
     // selections of mine and the neighbours' tensors, asked for early: nobody waits for them until the arenas are there
-    uint32_t thr[3], cut[3], moff = 0, place[SPW];
+    uint32_t thr[3], cut[3], moff = 0, K = 0, place[SPW];
+    const uint32_t anchor = TOPK && NORM ? T.anchor[seg] : kNoAnchor;
     if (TOPK) {
       const uint32_t segs[3] = {seg, PULL ? lw * T.L + cd.layer : seg, PULL ? rw * T.L + cd.layer : seg};
 #pragma unroll
       for (int i = 0; i < 3; ++i) { thr[i] = T.sel_prefix[segs[i]]; cut[i] = T.sel_cut[segs[i]]; }
       moff = T.layers[cd.layer].msg_off;
+      K = in_vector(T.layers[cd.layer].K);
 #pragma unroll
       for (int u = 0; u < SPW; ++u) place[u] = message_place(T, r * T.C + c, (sub0 + u) * 4 + wave_id(), T.sel_krem[seg]);
     }
@@ -185,7 +188,7 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
 #pragma unroll
         for (int u = 0; u < SPW; ++u) {
           const uint32_t win = winners4(xa[u], hat_was[u], A.topk_key, thr[0], cut[0], cd.j0 + e[u], nv[u]);
-          if (!A.applied) put_message(T, r, moff, place[u], win, xa[u], cd.j0 + e[u]);
+          if (!A.applied) put_message(T, r, moff, place[u], K, win, xa[u], cd.j0 + e[u]);
           if (!sent_whole) {
             take_winners(win, xa[u], ha[u]);
             if (any_of_line_part(win) && live[u]) st4t<STREAM>(T.xhat + base + e[u], make_float4(ha[u][0], ha[u][1], ha[u][2], ha[u][3]));
@@ -197,7 +200,7 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
       if (PULL && some_r) receive(thr[2], cut[2], rx, T.mbox_r, ra);
     }
     if (HISTA) {
-      for (uint32_t b = threadIdx.x; b < (uint32_t)kHistBins; b += kThreads) hA[b] = 0;
+      for (uint32_t b = threadIdx.x; b < (uint32_t)kFirstBins; b += kThreads) hA[b] = 0;
       __syncthreads();
     }
 #pragma unroll
@@ -225,10 +228,12 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
         if (NORM == 1) drift_acc(acc[u], xa[u], ha[u], nv[u]);
         if (NORM >= 2) square_acc(acc[u], xa[u], nv[u]);
         if (NORM == 3) square_acc(acc_hat[u], ha[u], nv[u]);
-        if (HISTA) {
+        if (TOPK && NORM) {
+          const Bins bins = first_bins(xa[u], ha[u], A.topk_key, anchor);
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            if ((uint32_t)i < nv[u]) atomicAdd(&hA[rank_key(xa[u][i], ha[u][i], A.topk_key) >> 20], 1u);
+            if (HISTA && (uint32_t)i < nv[u]) atomicAdd(&hA[bins.bin[i]], 1u);
+          if (T.codes) store_codes(T, base, (cd.len + 3) / 4 * 16, e[u] * 4, bins.codes);
         }
       }
     }
@@ -236,7 +241,7 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
   if (HISTA && sub0 * kSweep < cd.len + cd.lead) {     // uniform
     __syncthreads();
     uint32_t* gh = T.hist + (size_t)seg * kHistBins;
-    for (uint32_t b = threadIdx.x; b < (uint32_t)kHistBins; b += kThreads) {
+    for (uint32_t b = threadIdx.x; b < (uint32_t)kFirstBins; b += kThreads) {
       const uint32_t v = hA[b];
       if (v) atomicAdd(&gh[b], v);
     }

@@ -35,8 +35,8 @@ __device__ __forceinline__ Quad taken(const Quad& q) {
 }
 
 // What the walk has to know of a worker; lane i of a wavefront holds the i-th worker's.
-struct Marks { uint32_t f, thr, cut, place; };   // f: see below; Top-K: threshold key, last element that wins a tie, place in
-                                                 // the message of the first winner of this wavefront's group
+struct Marks { uint32_t f, thr, cut, place, anchor; };   // f: see below; Top-K: threshold key, last element that wins a tie, place in
+                                                 // the message of the first winner of this wavefront's group, anchor of its key codes
 constexpr uint32_t kCode = 3u, kLeftFilled = 4u, kRightFilled = 8u, kSpike = 16u, kLed = 32u;
 
 // RESET (with TOPK; the whole ring in one part): an event resets the sender's xhat to x while the mailboxes take the sent
@@ -47,7 +47,7 @@ template <int DIST, bool GRADBUF, int NORM, bool TOPK, bool HISTA, int W, bool R
 __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
   constexpr uint32_t kElems = 256 * W, SPW = W / 4;
   __shared__ double ws[NORM ? 64 * W : 1], ws_hat[NORM == 3 ? 64 * W : 1];
-  __shared__ __attribute__((aligned(16))) uint32_t hist[HISTA ? 2 * kHistBins + 4 : 4];
+  __shared__ __attribute__((aligned(16))) uint32_t hist[HISTA ? 2 * kFirstBins + 4 : 4];
   const uint32_t groups = T.SW / SPW;
   // Workgroups go to the eight XCDs in turn by their number.  Where the pass counts keys, each XCD takes a contiguous
   // eighth of the windows, so that the counts of a tensor are added in one L2 (8 ResNet-50 workers 1019 -> 944 us;
@@ -74,17 +74,18 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
   const float third = 0.333333343f;   // (float)(1/3): the ring's mixing weight
   const float sg = GRADBUF ? 0.0f : (float)(T.layers[layer].sig_base * step_decay(T, A));
   const uint32_t nb_vel = A.plain_sgd ? 0u : nb;
-  const uint32_t msg_off = TOPK ? T.layers[layer].msg_off : 0u;
+  const uint32_t msg_off = TOPK ? T.layers[layer].msg_off : 0u, K = TOPK ? in_vector(T.layers[layer].K) : 0u;
   auto at = [&](float* arena, uint32_t s) { return arena + (size_t)s * T.Npad + off; };
   auto worker = [&](uint32_t i) { return r0 + i < P ? r0 + i : r0 + i - P; };   // i <= n
 
   // the i-th worker of the part, i = n: the one after it
   auto marks_of = [&](uint32_t i) {
-    Marks m{0u, kNoThreshold, 0u, 0u};
+    Marks m{0u, kNoThreshold, 0u, 0u, kNoAnchor};
     if (i <= n) {
       const uint32_t s = worker(i), seg = s * T.L + layer, code = T.fired[seg];
       m.f = code | (T.valid_l[seg] ? kLeftFilled : 0u) | (T.valid_r[seg] ? kRightFilled : 0u);
       if (!GRADBUF && has_spike(A, k_iter, s)) m.f |= kSpike;
+      if (HISTA) m.anchor = T.anchor[seg];
       if (is_led(T, A, s)) m.f |= kLed;
       else if (TOPK && code == 2) {
         m.thr = T.sel_prefix[seg];
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
     uint32_t where = byte;
     if (RESET) {
       const uint32_t win = winners4(x.v, h.v, A.topk_key, thr, cut, j, nv);
-      if (to_hat) put_message(T, s, msg_off, place, win, x.v, j);
+      if (to_hat) put_message(T, s, msg_off, place, K, win, x.v, j);
       const bool sends = (f & kCode) != 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) q.v[i] = sends ? x.v[i] : h.v[i];
@@ -123,7 +124,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
     if (TOPK) {
       // (workers at the ends of parts: k_topk_apply has done all this but the mailboxes)
       const uint32_t win = winners4(x.v, h.v, A.topk_key, thr, cut, j, nv);
-      if (to_hat) put_message(T, s, msg_off, place, win, x.v, j);
+      if (to_hat) put_message(T, s, msg_off, place, K, win, x.v, j);
 #pragma unroll
       for (int i = 0; i < 4; ++i) q.v[i] = whole || ((win >> i) & 1u) ? x.v[i] : h.v[i];
       if (!whole && !led && !any_of_line_part(win)) where = kNowhere;
@@ -141,7 +142,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
   auto reads_hat = [](uint32_t f) { return (f & kCode) != 1 || (f & kLed) != 0; };
 
   if (HISTA) {
-    for (uint32_t b = threadIdx.x; b < 2 * kHistBins + 4; b += 64 * W) hist[b] = 0;
+    for (uint32_t b = threadIdx.x; b < 2 * kFirstBins + 4; b += 64 * W) hist[b] = 0;
     __syncthreads();
   }
   const bool dead = !HISTA && wave_id() * 256u >= here + skip;      // wave-uniform
@@ -270,11 +271,12 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
         }
       }
       if (HISTA) {
+        const uint32_t anchor = read_mark(cur.anchor, nxt.anchor, i);
+        const Bins bins = first_bins(xc.v, ec.v, A.topk_key, anchor);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const uint32_t bin = rank_key(xc.v[q], ec.v[q], A.topk_key) >> 20;
-          atomicAdd(&hist[(uint32_t)q < nv ? (i & 1u) * kHistBins + bin : 2 * kHistBins], 1u);
-        }
+        for (int q = 0; q < 4; ++q)
+          atomicAdd(&hist[(uint32_t)q < nv ? (i & 1u) * kFirstBins + bins.bin[q] : 2 * kFirstBins], 1u);
+        if (T.codes) store_codes(T, (size_t)r * T.Npad + off, nb, byte, bins.codes);
       }
       if (!RESET) el = ec;
       ec = en;
@@ -286,8 +288,8 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
       // two histograms in turn: this barrier ends worker r's counting, and the clearing of the other one
       __syncthreads();
       uint32_t* gh = T.hist + (size_t)(r * T.L + layer) * kHistBins;
-      for (uint32_t b = threadIdx.x * 4; b < (uint32_t)kHistBins; b += 256 * W) {
-        u32x4* p = reinterpret_cast<u32x4*>(hist + (i & 1u) * kHistBins + b);
+      for (uint32_t b = threadIdx.x * 4; b < (uint32_t)kFirstBins; b += 256 * W) {
+        u32x4* p = reinterpret_cast<u32x4*>(hist + (i & 1u) * kFirstBins + b);
         const u32x4 n = *p;
         if (n.x | n.y | n.z | n.w) {
 #pragma unroll
