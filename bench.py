@@ -208,9 +208,13 @@ def main():
     # rings that stream from memory, with ordinary delivery: the update pass walks the ring (where xhat is reset at events it
     # reads the mailboxes too, as the pass of the other rings does)
     streams = 20 * w.P * evg.padded_numel(w.layer_numel) > (128 << 20) and not args.delivery_delay
-    walks = streams and not args.xhat_reset
+    # ... and so do the parts of the ring in which cached rings are updated; both leave a key code for each element of a Top-K
+    # ring, a byte, from which the selection is made
+    parts = not streams and not args.delivery_delay and not (args.xhat_reset and w.topk_ppm)
+    walks = (streams and not args.xhat_reset) or parts
+    codes = 1 if w.topk_ppm else 0
     if walks:
-        step_bytes_per_elem = (20 if w.momentum != 0.0 else 12) + 8 * f_full + 8 * f_topk + 20 * rho * f_topk
+        step_bytes_per_elem = (20 if w.momentum != 0.0 else 12) + 8 * f_full + codes + f_topk + 20 * rho * f_topk
     else:
         step_bytes_per_elem = (28 if w.momentum != 0.0 else 20) + 16 * f_full + 8 * f_topk + 28 * rho * f_topk
     out = {
@@ -243,7 +247,7 @@ def main():
     if phases:
         ms_upd, n_upd = phases["update"]
         avg_ms = ms_upd / max(1, n_upd)
-        per_elem = (UPDATE_BYTES_PER_ELEM_WALK + 8 * f_full if walks else UPDATE_BYTES_PER_ELEM) \
+        per_elem = (UPDATE_BYTES_PER_ELEM_WALK + 8 * f_full + codes if walks else UPDATE_BYTES_PER_ELEM) \
             + UPDATE_TOPK_BYTES_PER_FIRED_ELEM_PER_RHO * rho * f_topk
         if w.momentum == 0.0:
             per_elem -= 8          # plain SGD: no velocity read or write
@@ -268,7 +272,7 @@ def main():
                                                      or args.topk_ppm is not None) else None
         upd_counters = (counters or {}).get("kernels", {}).get("k_update", {})
         traffic = upd_counters.get("traffic_bytes")
-        kernel = "k_update_walk" if streams else "k_update"
+        kernel = "k_update_walk" if streams else "k_update_part" if parts else "k_update"
         out["roofline"] = {"kernel": kernel, "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
                            "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                            "traffic": traffic,
@@ -296,8 +300,8 @@ def main():
                                "hbm_achieved_GBps": achieved, "hbm_frac": achieved / HBM_PEAK_GBS}
         out["phase_ms_per_step"] = {p: ms / max(1, args.steps) for p, (ms, n) in phases.items()}
         # the other HBM-bound phases against the same peak, on their share of the lower-bound bytes:
-        # the Top-K selection makes one key pass over x and xhat (8 B)
-        alg = {"topk_select": 8 * f_topk}
+        # the Top-K selection makes one pass over the key codes of fired tensors (1 B; 8, over x and xhat, where there are none)
+        alg = {"topk_select": (1 if walks else 8) * f_topk}
         out["phase_frac_of_hbm_peak"] = {
             p: b * elems / (phases[p][0] / max(1, args.steps) * 1e-3) / 1e9 / HBM_PEAK_GBS
             for p, b in alg.items() if phases[p][0] > 0 and b > 0}

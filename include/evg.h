@@ -175,7 +175,10 @@ typedef struct {
                                staging slot (a quarter of the granule's length, rounded down to a
                                multiple of 4; none below 16 elements) and were selected straight from
                                x and xhat instead (slower, same result): massive ties, or tensors and
-                               ends of tensors of a few elements */
+                               ends of tensors of a few elements.  In cached rings with ordinary delivery
+                               and tensors of at most 327 680 elements: those of tensors of more than 256
+                               whose selection went by x and xhat as a whole (a first Top-K message, massive
+                               ties, a threshold that has moved by more than an octave) */
   uint64_t library_bytes;   /* device memory the library holds for this context besides the
                                caller's five arenas (tables, Top-K histograms,
                                staging and message buffers); for evg_init_static the part
@@ -193,7 +196,8 @@ typedef struct {
 /* Phases reported by evg_timing_read. */
 enum {
   EVG_PH_NORM = 0,       /* separate drift-norm pass (EVG_NORM_SEPARATE only)        */
-  EVG_PH_TRIGGER = 1,    /* norm finalisation, trigger test, thresholds
+  EVG_PH_TRIGGER = 1,    /* norm finalisation, trigger test, thresholds; the whole Top-K selection
+                            of cached rings where one launch makes it
                             (no samples where the update pass runs the tests itself:
                             cache-resident rings that send whole tensors, norms fused,
                             no tensor above 131 072 elements)                         */

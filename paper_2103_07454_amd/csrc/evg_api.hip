@@ -80,6 +80,7 @@ struct evg_ctx {
   bool on_lines = false;            // sweeps begin on cache lines (streaming rings)
   bool walk = false;                // the update pass walks the ring
   uint32_t part = 0;                // workers of the ring that one workgroup of a walking pass goes through
+  ChooseTables choose{};            // longest = 0: selections are made in many launches
   bool cached = false;              // the five arenas together fit the last-level cache
   bool device_ahead = false;        // evg_step_next has been used: replays of a captured graph
                                     // advance the device's iteration without the host seeing
@@ -299,7 +300,8 @@ static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uin
     t.add(PC * SW * 4, 4); t.add(PC, 8); t.add(PC, 8);           // group, chunk_cnt, chunk_before
     t.add(P * ktot, 4); t.add(P * ktot, 4); t.add(S, 8); t.add(S, 8);
     t.add(S, 4); t.add(S, 4);                                     // anchor, sel_left
-    if (codes) t.add(P * Npad, 1);
+    if (codes) t.add(P * Npad + 16, 1);
+    t.add(L, 4);                                                   // order
   }
   return t.total;
 }
@@ -467,9 +469,11 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   bool pull = c->cached && !cfg->delivery_delay &&
               !(cfg->topk_ppm && (cfg->xhat_reset || cfg->norm_mode == EVG_NORM_SEPARATE || !copies_fit));
   bool in_parts = false, one_launch = false, may_be = true;
-  bool codes = cfg->topk_ppm && cfg->norm_mode == EVG_NORM_FUSED && !c->cached;     // (from the cache x and xhat are read as fast)
+  bool codes = cfg->topk_ppm && cfg->norm_mode == EVG_NORM_FUSED, choose = false;
   uint64_t need = 0, ring_windows = 0;
   uint32_t ring_part = 0;
+  uint32_t longest = 0;
+  for (const LayerDesc& d : layers) longest = std::max(longest, d.numel);
   auto cut_chunks = [&](bool on_lines) {
     chunks.clear();
     uint32_t most_sweeps = 0;
@@ -491,8 +495,9 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     }
     // Cached rings that send whole tensors and accumulate the norms in the update pass are updated in parts of the ring; in
     // one launch per iteration where one wavefront sums a tensor's sweep partials with two loads per lane.
-    in_parts = may_be && pull && !cfg->topk_ppm && cfg->norm_mode == EVG_NORM_FUSED && arena_bytes < (1ull << 30);
-    one_launch = in_parts && most_sweeps <= 128;
+    in_parts = may_be && pull && cfg->norm_mode == EVG_NORM_FUSED && arena_bytes < (1ull << 30) && (!cfg->topk_ppm || (codes && longest <= kChooseMost));
+    one_launch = in_parts && !cfg->topk_ppm && most_sweeps <= 128;
+    choose = in_parts && cfg->topk_ppm;
     ring_windows = 0;
     for (const ChunkDesc& cd : chunks) ring_windows += (cd.len + kSweep - 1) / kSweep;
     // Longer parts read less of other parts' workers and run fewer tests twice, shorter ones are more workgroups.  Parts
@@ -500,16 +505,19 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     // 8 15.7 / 14.3 / 16.6, on 12 25.7 / 22.6 / 19.2, on 16 34.1 / 33.4 / 30.7; 438 on 8 24.9 / 21.8 / 18.4, on 16 53.3 / 48.9 / 49.0.
     const uint64_t units = ring_windows * P;
     ring_part = std::min<uint32_t>(P, units < 900 ? 2 : units < 3400 ? 4 : kPartMost);
-    if (in_parts && !one_launch) ring_part = std::min<uint32_t>(ring_part, 4);
+    // Top-K, parts of 1 / 2 / 4: 28 windows on 8 workers 19.9 / 21.2 / 23.9, 120 on 5 20.8 / 21.3 / 24.0, 160 on 12 38.2 / 36.8 / 37.0, 314 on
+    // 8 35.2 / 32.8 / 32.6, on 24 106 / 103 / 98, 438 on 12 78 / 78 / 69.
+    if (cfg->topk_ppm) ring_part = std::min<uint32_t>(P, units < 900 ? 1 : units < 1600 ? 2 : 4);
+    else if (in_parts && !one_launch) ring_part = std::min<uint32_t>(ring_part, 4);
     need = table_bytes(P, L, chunks.size(), SW, hist_len, Npad, ktot, cfg->topk_ppm != 0,
                        cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF, pull && !(in_parts && ring_part == P), one_launch,
-                       in_parts ? ring_windows : 0, (P + ring_part - 1) / ring_part, codes);
+                       in_parts ? ring_windows : 0, (P + ring_part - 1) / ring_part, codes && (choose || !c->cached));
     return (uint64_t)P * chunks.size() * (SW + 1) <= 0xFFFFFFF0ull && (uint64_t)P * ktot <= 0xFFFFFFF0ull &&
            !(use_scratch && need > kScratchBytes);
   };
   c->on_lines = !c->cached && cut_chunks(true);
   if (!c->on_lines) (void)cut_chunks(false);
-  if (use_scratch && need > kScratchBytes && in_parts) {        // thousands of short tensors: no room for what the parts take
+  if (use_scratch && need > kScratchBytes && in_parts && !cfg->topk_ppm) {        // thousands of short tensors: no room for what the parts take
     may_be = false;
     (void)cut_chunks(false);
   }
@@ -663,6 +671,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   // itself from a copy of x it keeps (one more array of the ring's size, library-owned)
   if (pull && !(in_parts && ring_part == P)) TRY_OR_FREE(c->dalloc(&t.xsnap, 2 * (uint64_t)P * Npad, false));
   std::vector<WindowDesc> ring;
+  std::vector<uint32_t> order;
   if (in_parts) {
     for (size_t i = 0; i < chunks.size(); ++i)
       for (uint32_t u = 0; u * kSweep < chunks[i].len; ++u) {
@@ -708,7 +717,19 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
       TRY_OR_FREE(c->dalloc(&t.anchor, S, false));
       HIP_OR_FREE(hipMemsetAsync(t.anchor, 0xFF, S * 4, c->stream));      // kNoAnchor
     }
-    if (codes) TRY_OR_FREE(c->dalloc(&t.codes, (uint64_t)P * Npad, true));
+    // (cached rings that make their selections in many launches read x and xhat as fast)
+    if (codes && (choose || !c->cached)) TRY_OR_FREE(c->dalloc(&t.codes, (uint64_t)P * Npad + 16, true));
+    if (choose) {
+      order.resize(L);
+      for (uint32_t l = 0; l < L; ++l) order[l] = l;
+      std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return layers[a].numel > layers[b].numel; });
+      uint32_t* d_order = nullptr;
+      TRY_OR_FREE(c->dalloc(&d_order, L, false));
+      HIP_OR_FREE(hipMemcpyAsync(d_order, order.data(), L * 4, hipMemcpyHostToDevice, c->stream));
+      c->choose.order = d_order;
+      c->choose.longest = longest;
+      for (const LayerDesc& d : layers) c->choose.longer += d.numel > 256;
+    }
     TRY_OR_FREE(c->dalloc(&t.idx_hash, S, true));
     TRY_OR_FREE(c->dalloc(&t.msg_hash, S, true));
   }
@@ -791,7 +812,9 @@ static evg_status enqueue_step(evg_ctx* c, const StepArgs& args, bool timed) {
   }
   if (!single) {
     Phase ph(c, EVG_PH_TRIGGER);
-    HIP_TRY(a.hist_fused ? launch_topk_decide(t, a, c->stream) : launch_trigger(t, a, c->stream));
+    HIP_TRY(a.choose       ? launch_topk_choose(t, a, c->choose, c->stream)
+            : a.hist_fused ? launch_topk_decide(t, a, c->stream)
+                           : launch_trigger(t, a, c->stream));
     if ((st = ph.end()) != EVG_OK) return st;
   }
   // Whole sends: with delayed delivery the mailboxes are written after the update, a cache-resident ring's receivers
@@ -802,7 +825,7 @@ static evg_status enqueue_step(evg_ctx* c, const StepArgs& args, bool timed) {
     HIP_TRY(launch_copy(t, a, c->chunk_elems, c->stream));
     if ((st = ph.end()) != EVG_OK) return st;
   }
-  if (a.topk_on) {
+  if (a.topk_on && !a.choose) {
     {
       Phase ph(c, EVG_PH_TOPK_SELECT);
       HIP_TRY(launch_topk_select(t, a, c->chunk_elems, c->stream));
@@ -851,6 +874,7 @@ static evg_status fixed_args(evg_ctx* c, const float* grad, StepArgs* out) {
   a.topk_key = g.topk_key;
   a.delay = g.delivery_delay;
   a.hist_fused = (g.topk_ppm && g.norm_mode == EVG_NORM_FUSED) ? 1u : 0u;
+  a.choose = c->choose.longest ? 1u : 0u;
   a.cached = c->cached ? 1u : 0u;
   a.pull = c->t.xsnap ? 1u : 0u;
   a.walk = c->walk ? 1u : 0u;
@@ -1190,6 +1214,7 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
     // Histograms and key codes are counted again, from the arenas: the saved ones go by eighths of an octave in versions before 6.
     StepArgs a{};
     a.topk_key = c->cfg.topk_key;
+    a.choose = c->choose.longest ? 1u : 0u;
     HIP_TRY(hipMemcpyAsync(t.anchor, anchors.get(), (size_t)t.S * 4, hipMemcpyHostToDevice, c->stream));
     HIP_TRY(hipMemsetAsync(t.hist, 0, (size_t)t.S * kHistBins * 4, c->stream));
     HIP_TRY(launch_topk_count_all(t, a, c->chunk_elems, c->stream));

@@ -14,6 +14,8 @@ constexpr int kFirstBins = 1280;       // the first (see first_bins)
 constexpr uint32_t kCoarseBits = 21, kFineBits = 17;                  // bits of a key below its coarse and fine bins
 constexpr uint32_t kPerCoarse = 1u << (kCoarseBits - kFineBits);      // fine bins of a coarse one
 constexpr uint32_t kFineBins = 128;                                   // fine bins
+constexpr uint32_t kCodeStride = 256;                                 // ... in eight copies, each of those codes and of all above
+constexpr uint32_t kFirstCode = 64, kCodeBins = 128;                  // key codes that are counted where there are no such histograms
 constexpr int kLastBins = 1024;        // the last takes what is left, 6 or 10 bits
 constexpr uint32_t kStageCap = 2048;   // staged keys of a chunk at most
 // Threshold key that no key reaches (they have 31 bits).  A selection ends with it where it would not find exactly K
@@ -139,6 +141,7 @@ struct StepArgs {
                            // and squared xhat in partials / partials_hat
   uint32_t delay;          // messages of this iteration land after its updates
   uint32_t hist_fused;     // the update pass of the previous iteration already built pass A's histograms
+  uint32_t choose;         // one workgroup per tensor makes the whole selection, from key codes (k_topk_choose)
   uint32_t plain_sgd;      // momentum == 0: the velocity arena is not touched
   uint32_t from_device;    // take k and decay^k from IterState instead of the two fields here
   uint32_t xhat_reset;     // a Top-K event resets the whole tensor's xhat to x
@@ -171,6 +174,12 @@ hipError_t launch_topk_decide(const Tables& t, const StepArgs& a, hipStream_t s)
 hipError_t launch_topk_select(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
 // pass A's histograms and the key codes of all tensors, as an update pass leaves them; added to the histograms that are there
 hipError_t launch_topk_count_all(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
+// The tensors by size, the `longer` of more than 256 elements first; the longest's elements, at most kChooseMost.
+struct ChooseTables { const uint32_t* order; uint32_t longer, longest; };
+// Longer ones are too much for one workgroup (us a step, in many launches / one workgroup a tensor, 3 and 8 workers): perceptrons
+// of 102 000 elements 45 / 25 and 45 / 29, 251 000 47 / 39 and 57 / 47, 401 000 50 / 55 and 72 / 69, 627 000 59 / 76 and 105 / 112.
+constexpr uint32_t kChooseMost = 327680;
+hipError_t launch_topk_choose(const Tables& t, const StepArgs& a, const ChooseTables& c, hipStream_t s);
 hipError_t launch_topk_apply(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
 hipError_t launch_average(const Tables& t, float* out, hipStream_t s);
 hipError_t launch_message_hashes(const Tables& t, hipStream_t s);

@@ -24,6 +24,7 @@
 // more (64 workers 4647); bins of an eighth and codes that divide them cost a launch more and 1317 where 1277 is now.
 // (The selection used to stage every possible winner as (index, value) and to compact the messages from there;
 // the update passes then scattered three messages each into LDS.)
+// Cached rings whose tensors are not too long make the whole selection in one launch, kernels_choose.hip.
 #include "trigger_device.h"
 #include "message_device.h"
 
@@ -89,8 +90,14 @@ __global__ __launch_bounds__(kThreads) void k_topk_hist(Tables T, StepArgs A) {
       const Bins bins = first_bins(xa, ha, A.topk_key, ALL ? T.anchor[wi.seg] : kNoAnchor);
       if (ALL && T.codes) store_codes(T, wi.base, (wi.cd.len + 3) / 4 * 16, e * 4, bins.codes);
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if ((uint32_t)q < nv) atomicAdd(&h[bins.bin[q]], 1u);
+      for (int q = 0; q < 4; ++q) {
+        uint32_t b = bins.bin[q];
+        if (ALL && A.choose) {                             // what k_update_part counts
+          const uint32_t c = (bins.codes >> (8 * q) & 255u) - kFirstCode;
+          b = (int)c < 0 ? kFirstBins - 1 : c < kCodeBins ? c : kCodeBins;
+        }
+        if ((uint32_t)q < nv && !(ALL && A.choose && b == kFirstBins - 1)) atomicAdd(&h[b], 1u);
+      }
     }
   }
   __syncthreads();

@@ -1,0 +1,112 @@
+"""Cached Top-K rings whose tensors are not too long: one workgroup per tensor makes the whole selection, from the key codes and
+counts that the update pass leaves (a pass in parts of the ring).  Checked against the oracle, message by message, at the
+sizes where it can go wrong: tensors of a wavefront (up to 256 elements) and one more, ends of groups of 256, of the codes that a
+workgroup holds at once (163 840) and the longest it takes (327 680); parts of 1, 2 and 4 workers, closed rings and last parts of
+one; thresholds that leave the counted codes (spikes, decay), ties, and blobs that move to and from streaming rings."""
+import numpy as np
+import pytest
+
+from paper_2103_07454_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+ARENAS = ("x", "xhat", "vel", "mbox_l", "mbox_r")
+
+
+@pytest.fixture(scope="module")
+def evg():
+    from paper_2103_07454_amd import evg as m
+    m.lib()
+    return m
+
+
+def _workload(P, sizes, iters, **kw):
+    tensors = [inputs.TensorSpec(f"t{i}", (n,), 16 + i, "weight") for i, n in enumerate(sizes)]
+    base = dict(sigma0=0.05, decay=0.95, seed=P, topk_ppm=100_000)
+    base.update(kw)
+    return inputs.Workload("choose", P, tensors, iters, **base)
+
+
+def _run(evg, oracle_mod, w, **both):
+    from helpers import lockstep
+    x0 = inputs.replicate(w.x0(), w.P)
+    ring = evg.Ring.from_workload(w, x0, mailbox_fill=float("nan"), **both)
+    orc = oracle_mod.Oracle.from_workload(w, x0, **both)
+    differ = "trigger_kind" in both
+    rep = lockstep(ring, orc, w.iters, sample_messages=8, norm_rtol=None if differ else 2e-7, norm_abs_of_x=2.5e-7 if differ else None)
+    assert rep["rel"]["x"] <= 1e-5 and (differ or all(rep["bitwise"].values())), rep
+
+
+@pytest.mark.parametrize("sizes", [[1, 2, 3, 5, 255, 256, 257, 258], [1023, 1024, 1025, 2047, 2049], [16_383, 16_385], [163_839, 4],
+                                   [163_841], [327_680, 7], [327_681, 260]], ids=lambda s: "_".join(map(str, s)))
+@pytest.mark.parametrize("kw", [dict(), dict(topk_ppm=7_000, dist=1, topk_key=1)], ids=["drift", "value"])
+def test_sizes(evg, oracle_mod, sizes, kw):
+    kw = dict(kw)
+    both = dict(topk_key=kw.pop("topk_key")) if "topk_key" in kw else {}
+    _run(evg, oracle_mod, _workload(3, sizes, 6, **kw), **both)
+
+
+# few windows: parts of one worker; some 1000 of a window and worker: of two; more: of four
+@pytest.mark.parametrize("P,sizes", [(3, [700] * 3), (5, [300] * 4), (3, [1021] * 310), (11, [259] * 90), (4, [300] * 401),
+                                     (9, [261] * 200), (12, [1027] * 150)])
+@pytest.mark.parametrize("kw", [dict(spike_prob=0.3, spike_gain=9.0), dict(momentum=0.0, decay=0.3), dict(trigger_kind=1), dict(gradients=True)],
+                         ids=["spikes", "decay_plain", "norms", "given"])
+def test_parts(evg, oracle_mod, P, sizes, kw):
+    import torch
+    from helpers import lockstep
+    kw = dict(kw)
+    if kw.pop("gradients", False):
+        w = _workload(P, sizes, 6)
+        x0 = inputs.replicate(w.x0(), P)
+        ring = evg.Ring.from_workload(w, x0, mailbox_fill=float("nan"), grad_mode=1)
+        orc = oracle_mod.Oracle.from_workload(w, x0, grad_mode=1)
+        given = {k: inputs.random_grads(P, w.N, 900 + k, 0.02) for k in range(w.iters)}
+        on_gpu = {k: torch.from_numpy(ring.layout.pad(g)).cuda() for k, g in given.items()}
+        rep = lockstep(ring, orc, w.iters, grads=given.get, gpu_grads=on_gpu.get, sample_messages=8)
+        assert all(rep["bitwise"].values()), rep
+        return
+    both = dict(trigger_kind=kw.pop("trigger_kind")) if "trigger_kind" in kw else {}
+    _run(evg, oracle_mod, _workload(P, sizes, 7, **kw), **both)
+
+
+@pytest.mark.parametrize("sizes", [[100, 3000, 20_000], [20_480]])
+def test_ties_that_do_not_all_win(evg, oracle_mod, sizes):
+    """Gradients of a few values: from some tens to thousands of keys equal the threshold."""
+    import torch
+    from helpers import lockstep
+    w = _workload(4, sizes, 10, thr_mode=inputs.THR_FIXED, thr_fixed=0.0)
+    x0 = inputs.replicate(w.x0(), w.P)
+    ring = evg.Ring.from_workload(w, x0, grad_mode=1, lr=0.5, momentum=0.0)
+    orc = oracle_mod.Oracle.from_workload(w, x0, grad_mode=1, lr=0.5, momentum=0.0)
+    given = {}
+    for k in range(w.iters):
+        g = np.round(inputs.random_grads(w.P, w.N, 40 + k) * (200.0 if k % 2 else 2.0)) * np.float32(0.25)
+        given[k] = g.astype(np.float32)
+    on_gpu = {k: torch.from_numpy(ring.layout.pad(g)).cuda() for k, g in given.items()}
+    rep = lockstep(ring, orc, w.iters, grads=given.get, gpu_grads=on_gpu.get, sample_messages=12)
+    assert all(rep["bitwise"].values()), rep
+
+
+@pytest.mark.parametrize("written_by", ["stream", "cached"])
+def test_blobs_between_streaming_and_cached_rings(evg, written_by):
+    w = _workload(5, [40_000, 300, 7, 2049], 12, spike_prob=0.2, spike_gain=3.0)
+    modes = dict(stream=evg.ACCESS_STREAM, cached=evg.ACCESS_CACHED)
+    a = evg.Ring.from_workload(w, mailbox_fill=0.0, access_mode=modes[written_by])
+    for k in range(5):
+        a.step(k)
+    ck = a.export_state()
+    rings = [evg.Ring.from_workload(w, mailbox_fill=0.0, access_mode=m) for m in modes.values()]
+    for r in rings:
+        r.import_state(ck)
+    again = evg.Ring.from_workload(w, mailbox_fill=0.0, access_mode=modes[written_by])
+    again.import_state(rings[0].export_state())
+    for k in range(5, 12):
+        for r in [a, again] + rings:
+            r.step(k)
+        for r in [again] + rings:
+            assert np.array_equal(a.decisions()["fired"], r.decisions()["fired"]), k
+            for mine, its in zip(a.message_hashes(), r.message_hashes()):
+                assert np.array_equal(mine, its), k
+    for r in [again] + rings:
+        for name in ARENAS:
+            assert np.array_equal(a.state(name), r.state(name)), name
