@@ -184,40 +184,59 @@ __global__ __launch_bounds__(kThreads) void k_topk_decide(Tables T, StepArgs A) 
 
 // Staging from the key codes, 1 byte an element instead of 8: what has the code of the threshold bin is listed by its
 // position in the chunk, and only those keys are fetched.  A key that is not what its code says (the caller has written x
-// since) ends the selection.
+// since) ends the selection.  Sixteen codes a lane in one load, sums by rotations and one place a wavefront: four codes a
+// lane with ballots and a place for each took 10 us more for 16 ResNet-18 workers (a step 1272 -> 1262 us; 8 ResNet-50 1199 -> 1195, 64
+// ResNet-18 workers the same).  Bound by the chain descriptor, decision, codes, keys, slot.
 template <int SWEEPS>
 __device__ __forceinline__ void stage_by_codes(const Tables& T, const StepArgs& A, const WorkItem& wi, uint32_t begin, uint32_t code,
                                                uint32_t* list, uint32_t* listed) {
-  const __amdgpu_buffer_rsrc_t codes = window(T.codes + wi.base, (wi.cd.len + 3) / 4 * 4);
-  uint32_t four[SWEEPS];
+  constexpr int LOADS = (SWEEPS + 3) / 4;                  // of 4096 positions
+  const uint32_t positions = wi.cd.lead + wi.cd.len;       // (positions before the lead are codes of the tensor before)
+  const __amdgpu_buffer_rsrc_t codes = window(T.codes + wi.base - wi.cd.lead, (positions + 15) / 16 * 16);
+  u32x4 sixteen[LOADS];
 #pragma unroll
-  for (int it = 0; it < SWEEPS; ++it) {
-    const uint32_t e = it * kSweep + threadIdx.x * kLaneElems - wi.cd.lead;   // positions before the lead wrap around
-    four[it] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(codes, (int)(e < wi.cd.len ? e : 0xFFFFFFF0u), 0, 2);
-    // what is past the tensor's end gets code 0, which no bin has that is told by codes
-    if (e < wi.cd.len && wi.cd.len - e < 4u) four[it] &= (1u << 8 * (wi.cd.len - e)) - 1u;
+  for (int u = 0; u < LOADS; ++u) {
+    const uint32_t p = (u * kThreads + threadIdx.x) * 16;
+    sixteen[u] = __builtin_amdgcn_raw_buffer_load_b128(codes, (int)(p < positions ? p : 0xFFFFFFF0u), 0, 2);
   }
   __syncthreads();
+  uint32_t in[LOADS], mine = 0;                            // which of a lane's sixteen have the code
 #pragma unroll
-  for (int it = 0; it < SWEEPS; ++it) {
-    // bytes 0 and 2, 1 and 3, in halves of a register: adding 255 - code sets bit 8 of those above the code, 256 - code of
-    // those that have it too
-    const uint32_t p = four[it] & 0x00FF00FFu, q = (four[it] >> 8) & 0x00FF00FFu, more = (255u - code) * 0x10001u;
-    const uint32_t gp = (p + more) & 0x01000100u, gq = (q + more) & 0x01000100u;
-    const uint32_t ip = ((p + more + 0x10001u) & 0x01000100u) ^ gp, iq = ((q + more + 0x10001u) & 0x01000100u) ^ gq;
-    const uint32_t g = (gp >> 8) + (gq >> 8), above = (g + (g >> 16)) & 7u;    // 0 .. 4
-    const uint32_t n = __popcll(__ballot(above & 1u)) + 2 * __popcll(__ballot(above & 2u)) + 4 * __popcll(__ballot(above & 4u));
-    if (lane_id() == 0) T.group[(size_t)wi.w * (T.SW * 4) + it * 4 + wave_id()] = n;
-    if (ip | iq) {                                     // few lanes
-      const uint32_t pos = it * kSweep + threadIdx.x * kLaneElems;
-      const bool in[4] = {(ip & 0x100u) != 0, (iq & 0x100u) != 0, (ip >> 16) != 0, (iq >> 16) != 0};
+  for (int u = 0; u < LOADS; ++u) {
+    const uint32_t p = (u * kThreads + threadIdx.x) * 16;
+    uint32_t above = 0;
+    in[u] = 0;
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        if (in[b]) {
-          const uint32_t at = atomicAdd(listed, 1u);
-          if (at < kStageCap) list[at] = pos + b;
-        }
-      }
+    for (uint32_t w = 0; w < 4; ++w) {
+      // what is no element of the chunk gets code 0, which no bin has that is told by codes
+      const uint32_t at = p + 4 * w, left = at < wi.cd.lead || at >= positions ? 0u : positions - at;
+      const uint32_t four = left < 4u ? sixteen[u][w] & ((1u << 8 * left) - 1u) : sixteen[u][w], more = (255u - code) * 0x10001u;
+      // bytes 0 and 2, 1 and 3, in halves of a register: adding 255 - code sets bit 8 of those above the code, 256 - code of
+      // those that have it too
+      const uint32_t a = (four & 0x00FF00FFu) + more, b = ((four >> 8) & 0x00FF00FFu) + more;
+      above += (a & 0x01000100u) + (b & 0x01000100u);
+      const uint32_t ia = ((a + 0x10001u) ^ a) & 0x01000100u, ib = ((b + 0x10001u) ^ b) & 0x01000100u;
+      in[u] |= (ia >> 8 | ib >> 7) << 2 * w;               // element 4 w + i: bit 2 w + (i & 1) + 16 (i >> 1)
+    }
+    mine += (uint32_t)__popc(in[u]);
+    above = (above >> 8 & 0xFu) + (above >> 24);           // sixteen lanes have a group of 256 positions
+    above += (uint32_t)__builtin_amdgcn_mov_dpp((int)above, 0x128, 0xF, 0xF, true);   // row_ror:8, 4, 2, 1
+    above += (uint32_t)__builtin_amdgcn_mov_dpp((int)above, 0x124, 0xF, 0xF, true);
+    above += (uint32_t)__builtin_amdgcn_mov_dpp((int)above, 0x122, 0xF, 0xF, true);
+    above += (uint32_t)__builtin_amdgcn_mov_dpp((int)above, 0x121, 0xF, 0xF, true);
+    if ((lane_id() & 15u) == 0 && p < SWEEPS * (uint32_t)kSweep) T.group[(size_t)wi.w * (T.SW * 4) + (p >> 8)] = above;
+  }
+  const uint32_t upto = wave_incl_scan(mine);
+  uint32_t next = 0;
+  if (lane_id() == 63) next = atomicAdd(listed, upto);
+  next = (uint32_t)__builtin_amdgcn_readlane((int)next, 63) + upto - mine;
+#pragma unroll
+  for (int u = 0; u < LOADS; ++u) {
+    while (in[u]) {
+      const uint32_t b = (uint32_t)__ffs((int)in[u]) - 1u;
+      in[u] &= in[u] - 1u;
+      if (next < kStageCap) list[next] = (u * kThreads + threadIdx.x) * 16 + (b >> 1 & 7u) * 4 + (b & 1u) + (b >> 4) * 2;
+      ++next;
     }
   }
   __syncthreads();
@@ -244,7 +263,7 @@ __device__ __forceinline__ void stage_by_codes(const Tables& T, const StepArgs& 
 
 // One workgroup per chunk; a wavefront's part of a sweep is a group of 256 elements.  Ballots give the
 // counts; the keys in the threshold bin are gathered in LDS, in no particular order (each carries its
-// group, in the bits from the 21st on), and leave as one run.  Bound by reading x and xhat, or by instructions where it goes by codes.
+// group, in the bits from the 21st on), and leave as one run.  Bound by reading x and xhat, or by latency where it goes by codes.
 // COPY: 0 nothing to do for a tensor sent whole (it lands later, or the update pass sends it), 1 its chunk goes into
 // the two mailboxes, 2 into xhat, if its worker is at the end of a part of the ring (see copy_chunk): a
 // Top-K tensor's first send takes no launch of its own.

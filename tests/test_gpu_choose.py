@@ -46,6 +46,21 @@ def test_sizes(evg, oracle_mod, sizes, kw):
     _run(evg, oracle_mod, _workload(3, sizes, 6, **kw), **both)
 
 
+# streaming rings stage by codes, sixteen to a lane: ends of those, of their words, of groups of 256 and of chunks; tensors begin anywhere
+# on their cache line (every other tensor is of odd length)
+@pytest.mark.parametrize("chunk", [1024, 2048, 4096, 8192])
+@pytest.mark.parametrize("topk_key", [0, 1])
+def test_streamed_sizes(evg, oracle_mod, chunk, topk_key):
+    from helpers import lockstep
+    sizes = [15, 16, 17, 31, 33, 1, 241, 255, 257, 1009, 1024, 1039, 4095, 4097, 8175, 8191, 8209, 16_385, 24_575]
+    w = _workload(3, sizes, 6, topk_ppm=20_000)
+    x0 = inputs.replicate(w.x0(), w.P)
+    ring = evg.Ring.from_workload(w, x0, mailbox_fill=float("nan"), topk_key=topk_key, access_mode=evg.ACCESS_STREAM, chunk_elems=chunk)
+    orc = oracle_mod.Oracle.from_workload(w, x0, topk_key=topk_key)
+    rep = lockstep(ring, orc, w.iters, sample_messages=8)
+    assert all(rep["bitwise"].values()), rep
+
+
 # few windows: parts of one worker; some 1000 of a window and worker: of two; more: of four
 @pytest.mark.parametrize("P,sizes", [(3, [700] * 3), (5, [300] * 4), (3, [1021] * 310), (11, [259] * 90), (4, [300] * 401),
                                      (9, [261] * 200), (12, [1027] * 150)])
