@@ -120,6 +120,9 @@ __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t
     return;
   }
   const uint32_t krem = PASS == 0 ? T.layers[seg % T.L].K : T.sel_krem[seg];
+  // asked for along with the counts, not by the thread that finds the bin: a load less in the chain of launches
+  const uint32_t anchor = PASS == 0 && T.anchor ? T.anchor[seg] : kNoAnchor;
+  const uint32_t prefix = PASS ? T.sel_prefix[seg] : 0u, bits = PASS == 1 ? T.sel_left[seg] & 255u : 0u;
   const uint32_t top = NB - 1 - threadIdx.x * PER;   // this thread's highest bin
   uint32_t cnt[PER], local = 0;
 #pragma unroll
@@ -143,7 +146,6 @@ __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t
     }
     T.sel_krem[seg] = rem;
     if (PASS == 0) {
-      const uint32_t anchor = T.anchor ? T.anchor[seg] : kNoAnchor;
       uint32_t left, next;
       const uint32_t begin = bin_begin(bin, anchor, &left);
       T.sel_prefix[seg] = begin;
@@ -154,8 +156,8 @@ __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t
         T.anchor[seg] = next > kFineBins / 2 ? (next - kFineBins / 2) / kPerCoarse * kPerCoarse : 0u;
       }
     } else {
-      const uint32_t prefix = T.sel_prefix[seg];           // (a selection that has ended stays so)
-      if (prefix != kNoThreshold) T.sel_prefix[seg] = prefix + (PASS == 1 ? bin << ((T.sel_left[seg] & 255u) - 11u) : bin);
+      // (a selection that has ended stays so)
+      if (prefix != kNoThreshold) T.sel_prefix[seg] = prefix + (PASS == 1 ? bin << (bits - 11u) : bin);
     }
   }
 }

@@ -60,7 +60,7 @@ __device__ __forceinline__ void block_sums(const double v[SPW], double* ws, doub
 // drift, 2 its squared x (xhat is then not read at all), 3 its squared x and squared xhat.
 // TOPK: Top-K messages of this iteration: my own is told from x and xhat as they pass through the registers, written to
 // the message buffers and applied to xhat; a neighbour's (PULL) from the copy of its x and from my mailbox.
-// (TOPK with NORM also leaves the codes of the new rank keys, if the ring keeps any.)
+// (TOPK with NORM also leaves the codes of the new rank keys, if the ring keeps any: one that streams.)
 // HISTA: also histogram the new rank keys per tensor, the first
 // radix pass of the next iteration's Top-K selection, while the values are in registers.
 // SPW: consecutive sweeps of a chunk per workgroup (one float4 per thread and sweep).  Two halve the cost of
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
 #pragma unroll
           for (int i = 0; i < 4; ++i)
             if (HISTA && (uint32_t)i < nv[u]) atomicAdd(&hA[bins.bin[i]], 1u);
-          if (T.codes) store_codes(T, base, (cd.len + 3) / 4 * 16, e[u] * 4, bins.codes);
+          if (!PULL && T.codes) store_codes(T, base, (cd.len + 3) / 4 * 16, e[u] * 4, bins.codes);
         }
       }
     }
