@@ -137,6 +137,8 @@ __global__ __launch_bounds__(kThreads) void k_update_part(PartArgs R, StepArgs A
       }
     }
   }
+  // (all wavefronts have cleared their share of the counts before one adds to them; the arenas are still on their way)
+  if (TOPK) __syncthreads();
 
   // ---- the trigger tests ----
   uint32_t code = was;
