@@ -104,7 +104,10 @@ def test_configuration_beyond_the_block_is_rejected(evg):
 @pytest.mark.parametrize("P,most,more,kw,over", [
     (8, [2_178_496], [2_178_560], dict(topk_ppm=100_000), dict(chunk_elems=8192)),
     (3, [4] * 2630, [4] * 2631, dict(topk_ppm=100_000), dict(chunk_elems=8192)),
-    (16, [4] * 62_112, [4] * 62_113, dict(), dict(chunk_elems=1024, access_mode=1))], ids=["long", "tiny", "whole"])
+    (16, [4] * 62_112, [4] * 62_113, dict(), dict(chunk_elems=1024, access_mode=1)),
+    # (a cached ring, and one with so many tensors that what its update in parts takes has no room)
+    (16, [15] * 18_332, [15] * 18_333, dict(), dict(access_mode=2)),
+    (16, [15] * 18_332, [15] * 20_166, dict(), dict(access_mode=2))], ids=["long", "tiny", "whole", "cached", "cached_no_parts"])
 def test_the_largest_configurations_admitted(evg, P, most, more, kw, over):
     with pytest.raises(evg.EvgError) as ei:
         evg.Ring.from_workload(workload(P, more, **kw), static_tables=True, **over)
