@@ -147,7 +147,9 @@ typedef struct {
    * library's to write: a mailbox that has received equals its sender's xhat (unless
    * delivery is delayed or xhat_reset moves xhat without a message), and evg_step reads
    * whichever copy is nearer.  So is x, of which the update pass carries norms, histograms, key codes and
-   * copies on to the next step (a Top-K tensor whose keys are seen not to fit them sends nothing);
+   * copies on to the next step (a Top-K tensor whose keys are seen not to fit them sends nothing, and where keys are counted
+   * by their codes -- streaming rings, cached ones with tensors of at most 327 680 elements -- neither do any of its groups of
+   * 256 elements in which another number wins than was counted; neighbours in a cached ring go by the copies);
    * with EVG_NORM_SEPARATE nothing but a cached whole-tensor ring's copies is carried, and
    * in every other ring the caller may write x between two steps. */
   float* x;      /* current parameters                                   */
@@ -283,7 +285,8 @@ evg_status evg_last_decisions(evg_ctx* c, uint8_t* fired, uint8_t* near_tie, flo
 
 /* The Top-K message worker r sent for tensor l in the most recent step: ascending
  * element indices within the tensor and their values (Section 7: values + indices
- * = 2K words).  *count = K, or 0 if (r, l) sent no Top-K message (or no step has run
+ * = 2K words).  *count = K (fewer if the caller has written x since the step before: see evg_config::x),
+ * or 0 if (r, l) sent no Top-K message (or no step has run
  * in this context since evg_init / evg_state_import); at most cap
  * entries are copied to the HOST arrays idx / val (either may be NULL). */
 evg_status evg_message(evg_ctx* c, uint32_t r, uint32_t l, uint32_t* idx, float* val,

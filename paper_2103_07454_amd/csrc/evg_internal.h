@@ -18,11 +18,12 @@ constexpr uint32_t kCodeStride = 256;                                 // ... in 
 constexpr uint32_t kFirstCode = 64, kCodeBins = 128;                  // key codes that are counted where there are no such histograms
 constexpr int kLastBins = 1024;        // the last takes what is left, 6 or 10 bits
 constexpr uint32_t kStageCap = 2048;   // staged keys of a chunk at most
-// Threshold key that no key reaches (they have 31 bits).  A selection ends with it where it would not find exactly K
-// winners: the histogram that the last update pass left does not fit x and xhat, which the caller has written since.
-// Nothing is sent then; the update passes write a message's winners without a look at its length.
+// Threshold key that no key reaches (they have 31 bits).  A selection ends with it where it sees that it would not find exactly K
+// winners: the histogram and the key codes that the last update pass left do not fit x and xhat, which the caller has written since.
+// Nothing is sent then.  Where keys are counted by their codes, the update passes compare each 256 elements' winners with the count.
 constexpr uint32_t kNoThreshold = 0xFFFFFFFFu;
 constexpr uint32_t kNoAnchor = 0xFFFFFFFFu;
+constexpr uint32_t kNoEntry = 0xFFFFFFFFu;       // index in a message's place that nothing was sent for
 
 // A chunk is a run of one tensor's elements that one workgroup handles; it never
 // straddles tensors, starts at a multiple of 4 elements and is at most chunk_elems long.

@@ -80,17 +80,22 @@ __global__ __launch_bounds__(kThreads) void k_update_part(PartArgs R, StepArgs A
   }
   // lane t holds member t's threshold, last event, mailbox flags and decision (lanes past the members: the last one's)
   const uint32_t mseg = worker(lane) * R.L + layer;
-  uint32_t thr = 0, cut = 0, ties = 0, in_chunk = 0, anchor = 0;
-  uint2 so_far = make_uint2(0, 0);
+  uint32_t thr = 0, cut = 0, ties = 0, in_chunk = 0, in_chunk2 = 0, anchor = 0;
+  uint2 so_far = make_uint2(0, 0), so_far2 = so_far;
   if (TOPK) {
-    // member t's selection, and where the winners of this wavefront's group of 256 elements belong in its message
+    // member t's selection, and where the winners of this wavefront's group of 256 elements, and of the next, belong in its message
+    // (chunks have no leads here, so that a tensor's groups lie one behind the other)
     thr = T.sel_prefix[mseg];
     cut = T.sel_cut[mseg];
     anchor = T.anchor[mseg];
-    const uint32_t w = worker(lane) * T.C;
     ties = T.sel_krem[mseg];
-    so_far = T.chunk_before[w + (wd.slot >> (31 - __builtin_clz(T.SW)))];       // (a power of two)
-    in_chunk = T.group[((size_t)w * T.SW + wd.slot) * 4 + wave];
+    const int shift = 33 - __builtin_clz(T.SW);            // groups of a chunk (a power of two)
+    const uint32_t first_group = worker(lane) * T.C << shift, groups = P * T.C << shift;
+    const uint32_t group = first_group + wd.slot * 4 + wave, next = group + 1 < groups ? group + 1 : group;
+    so_far = T.chunk_before[group >> shift];
+    in_chunk = T.group[group];
+    so_far2 = T.chunk_before[next >> shift];
+    in_chunk2 = T.group[next];
     for (uint32_t b = threadIdx.x; b < N * (kCodeBins + 1); b += kThreads) counts[b] = 0;
   }
   const uint32_t fl = R.valid_l[mseg], fr = R.valid_r[mseg], was = TESTS ? 0u : (uint32_t)R.fired[mseg];
@@ -166,12 +171,14 @@ __global__ __launch_bounds__(kThreads) void k_update_part(PartArgs R, StepArgs A
   }
   const uint64_t sent = __ballot(code == 1);               // bit t: member t
   const uint64_t some = TOPK ? __ballot(code == 2) : 0;
-  uint32_t place = 0, K = 0, msg_off = 0;
+  uint32_t place = 0, count = 0, msg_off = 0;
   if (TOPK) {
-    const uint32_t equal = so_far.y + (in_chunk >> 16);
+    const uint32_t equal = so_far.y + (in_chunk >> 16), equal2 = so_far2.y + (in_chunk2 >> 16);
     place = so_far.x + (in_chunk & 0xFFFFu) + (equal < ties ? equal : ties);
-    K = in_vector(T.layers[layer].K);
-    msg_off = T.layers[layer].msg_off;
+    const uint32_t end = so_far2.x + (in_chunk2 & 0xFFFFu) + (equal2 < ties ? equal2 : ties);
+    const LayerDesc& ld = T.layers[layer];
+    count = thr == kNoThreshold ? 0u : (wd.j0 + (wave + 1) * 256 < ld.numel ? end : ld.K) - place;
+    msg_off = ld.msg_off;
   }
   // a neighbour's send fills a mailbox for good (a workgroup that reads a flag after it has been booked sees what it
   // would have computed)
@@ -188,7 +195,7 @@ __global__ __launch_bounds__(kThreads) void k_update_part(PartArgs R, StepArgs A
     h = either(bit(sent, t), x, h);
     uint32_t win = 0;
     if (TOPK && bit(some, t)) {                            // uniform
-      win = winners4(x.v, h.v, A.topk_key, mark(thr, t), mark(cut, t), wd.j0 + e, nv);
+      win = counted_winners(winners4(x.v, h.v, A.topk_key, mark(thr, t), mark(cut, t), wd.j0 + e, nv), mark(count, t));
       take_winners(win, x.v, h.v);
     }
     if (TOPK) touched |= bit(sent, t) || any_of_line_part(win) ? 1u << t : 0u;
@@ -222,12 +229,12 @@ __global__ __launch_bounds__(kThreads) void k_update_part(PartArgs R, StepArgs A
     acc[i] = 0.0;
     if (NORM == 3) acc_hat[i] = 0.0;
     // (lanes' values are read where all lanes have them: not below, where some are switched off)
-    const uint32_t my_place = TOPK ? mark(place, i + 1) : 0u, my_anchor = TOPK ? mark(anchor, i + 1) : 0u;
+    const uint32_t my_place = TOPK ? mark(place, i + 1) : 0u, my_count = TOPK ? mark(count, i + 1) : 0u, my_anchor = TOPK ? mark(anchor, i + 1) : 0u;
     if ((uint32_t)i < n && e < wd.len) {
       const uint32_t at = first + i * row;
       const Quad& er = i + 1 < N ? h[i + 1 < N ? i + 1 : 0] : right;
       if (TOPK) {
-        if (bit(some, i + 1)) put_message(T, r0 + i, msg_off, my_place, K, wins[i], x[i].v, wd.j0 + e);
+        if (bit(some, i + 1)) (void)put_message<true>(T, r0 + i, msg_off, my_place, my_count, wins[i], x[i].v, wd.j0 + e);
         if (touched >> (i + 1) & 1u) store_at(R.xhat, at, h[i]);
         if (touched >> i & 1u) store_at(R.mbox_l, at, left);
         if (touched >> (i + 2) & 1u) store_at(R.mbox_r, at, er);

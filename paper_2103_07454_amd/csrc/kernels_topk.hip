@@ -541,8 +541,9 @@ __global__ __launch_bounds__(kThreads) void k_topk_apply(Tables T, StepArgs A) {
     const float xa[4] = {x4.x, x4.y, x4.z, x4.w};
     float ha[4] = {h4.x, h4.y, h4.z, h4.w};
     const uint32_t nv = !live ? 0u : wi.cd.len - e < 4u ? wi.cd.len - e : 4u;
-    const uint32_t win = winners4(xa, ha, A.topk_key, t, cut, wi.cd.j0 + e, nv);
-    put_message(T, wi.r, ld.msg_off, message_place(T, wi.w, it * 4 + wave_id(), T.sel_krem[wi.seg]), in_vector(ld.K), win, xa, wi.cd.j0 + e);
+    const Place place = message_place(T, wi.w, wi.cd, ld, it * 4 + wave_id(), T.sel_krem[wi.seg]);
+    const uint32_t win = put_message<true>(T, wi.r, ld.msg_off, place.first, t == kNoThreshold ? 0u : place.count,
+                                           winners4(xa, ha, A.topk_key, t, cut, wi.cd.j0 + e, nv), xa, wi.cd.j0 + e);
     const bool changes = any_of_line_part(win) && live;
     if (LEAD) {
       take_winners(win, xa, ha);
@@ -590,6 +591,7 @@ __global__ __launch_bounds__(kThreads) void k_message_hashes(Tables T) {
     const size_t mbase = (size_t)(seg / T.L) * T.Ktot + ld.msg_off;
     for (uint32_t q = threadIdx.x; q < ld.K; q += kThreads) {
       const unsigned long long j = T.msg_idx[mbase + q];
+      if (j == kNoEntry) continue;
       hi += mix64(j);
       hm += mix64(((unsigned long long)__float_as_uint(T.msg_val[mbase + q]) << 32) | j);
     }

@@ -121,16 +121,17 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
     uint32_t nv[SPW];
     float lx[TOPK && PULL ? SPW : 1][4], rx[TOPK && PULL ? SPW : 1][4];   // the neighbours' x before this iteration's update
     // selections of mine and the neighbours' tensors, asked for early: nobody waits for them until the arenas are there
-    uint32_t thr[3], cut[3], moff = 0, K = 0, place[SPW];
+    uint32_t thr[3], cut[3], moff = 0;
+    Place place[SPW];
     const uint32_t anchor = TOPK && NORM ? T.anchor[seg] : kNoAnchor;
     if (TOPK) {
       const uint32_t segs[3] = {seg, PULL ? lw * T.L + cd.layer : seg, PULL ? rw * T.L + cd.layer : seg};
 #pragma unroll
       for (int i = 0; i < 3; ++i) { thr[i] = T.sel_prefix[segs[i]]; cut[i] = T.sel_cut[segs[i]]; }
-      moff = T.layers[cd.layer].msg_off;
-      K = in_vector(T.layers[cd.layer].K);
+      const LayerDesc ld = T.layers[cd.layer];
+      moff = ld.msg_off;
 #pragma unroll
-      for (int u = 0; u < SPW; ++u) place[u] = message_place(T, r * T.C + c, (sub0 + u) * 4 + wave_id(), T.sel_krem[seg]);
+      for (int u = 0; u < SPW; ++u) place[u] = message_place(T, r * T.C + c, cd, ld, (sub0 + u) * 4 + wave_id(), T.sel_krem[seg]);
     }
     auto receive = [&](uint32_t thr, uint32_t cut, const float (*sx)[4], float* mbox, float (*a)[4]) {
 #pragma unroll
@@ -188,8 +189,11 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
       if (my_event == 2) {                   // uniform
 #pragma unroll
         for (int u = 0; u < SPW; ++u) {
-          const uint32_t win = winners4(xa[u], hat_was[u], A.topk_key, thr[0], cut[0], cd.j0 + e[u], nv[u]);
-          if (!A.applied) put_message(T, r, moff, place[u], K, win, xa[u], cd.j0 + e[u]);
+          constexpr bool CHECK = STREAM && NORM;         // (other rings have no key codes)
+          uint32_t win = winners4(xa[u], hat_was[u], A.topk_key, thr[0], cut[0], cd.j0 + e[u], nv[u]);
+          const uint32_t count = thr[0] == kNoThreshold ? 0u : place[u].count;
+          if (!A.applied) win = put_message<CHECK>(T, r, moff, place[u].first, count, win, xa[u], cd.j0 + e[u]);
+          else if (CHECK) win = counted_winners(win, count);
           if (!sent_whole) {
             take_winners(win, xa[u], ha[u]);
             if (any_of_line_part(win) && live[u]) st4t<STREAM>(T.xhat + base + e[u], make_float4(ha[u][0], ha[u][1], ha[u][2], ha[u][3]));

@@ -38,6 +38,7 @@ __device__ __forceinline__ Quad taken(const Quad& q) {
 struct Marks { uint32_t f, thr, cut, place, anchor; };   // f: see below; Top-K: threshold key, last element that wins a tie, place in
                                                  // the message of the first winner of this wavefront's group, anchor of its key codes
 constexpr uint32_t kCode = 3u, kLeftFilled = 4u, kRightFilled = 8u, kSpike = 16u, kLed = 32u;
+constexpr int kCountShift = 8;                   // and from bit 8 on the winners in the group
 
 // RESET (with TOPK; the whole ring in one part): an event resets the sender's xhat to x while the mailboxes take the sent
 // entries only, so a mailbox is not its sender's xhat and is read, 8 bytes more per element: its winners are taken from the
@@ -74,7 +75,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
   const float third = 0.333333343f;   // (float)(1/3): the ring's mixing weight
   const float sg = GRADBUF ? 0.0f : (float)(T.layers[layer].sig_base * step_decay(T, A));
   const uint32_t nb_vel = A.plain_sgd ? 0u : nb;
-  const uint32_t msg_off = TOPK ? T.layers[layer].msg_off : 0u, K = TOPK ? in_vector(T.layers[layer].K) : 0u;
+  const uint32_t msg_off = TOPK ? T.layers[layer].msg_off : 0u;
   auto at = [&](float* arena, uint32_t s) { return arena + (size_t)s * T.Npad + off; };
   auto worker = [&](uint32_t i) { return r0 + i < P ? r0 + i : r0 + i - P; };   // i <= n
 
@@ -90,7 +91,9 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
       else if (TOPK && code == 2) {
         m.thr = T.sel_prefix[seg];
         m.cut = T.sel_cut[seg];
-        m.place = message_place(T, s * T.C + c, sub0 * 4 + wave_id(), T.sel_krem[seg]);
+        const Place p = message_place(T, s * T.C + c, cd, T.layers[layer], sub0 * 4 + wave_id(), T.sel_krem[seg]);
+        m.place = p.first;
+        if (HISTA && m.thr != kNoThreshold) m.f |= p.count << kCountShift;
       }
     }
     return m;
@@ -111,8 +114,8 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
     Quad q;
     uint32_t where = byte;
     if (RESET) {
-      const uint32_t win = winners4(x.v, h.v, A.topk_key, thr, cut, j, nv);
-      if (to_hat) put_message(T, s, msg_off, place, K, win, x.v, j);
+      uint32_t win = winners4(x.v, h.v, A.topk_key, thr, cut, j, nv);
+      if (to_hat) win = put_message<HISTA>(T, s, msg_off, place, f >> kCountShift, win, x.v, j);
       const bool sends = (f & kCode) != 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) q.v[i] = sends ? x.v[i] : h.v[i];
@@ -123,8 +126,8 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
     const bool led = (f & kLed) != 0, whole = (f & kCode) == 1 && !led;
     if (TOPK) {
       // (workers at the ends of parts: k_topk_apply has done all this but the mailboxes)
-      const uint32_t win = winners4(x.v, h.v, A.topk_key, thr, cut, j, nv);
-      if (to_hat) put_message(T, s, msg_off, place, K, win, x.v, j);
+      uint32_t win = winners4(x.v, h.v, A.topk_key, thr, cut, j, nv);
+      if (to_hat) win = put_message<HISTA>(T, s, msg_off, place, f >> kCountShift, win, x.v, j);
 #pragma unroll
       for (int i = 0; i < 4; ++i) q.v[i] = whole || ((win >> i) & 1u) ? x.v[i] : h.v[i];
       if (!whole && !led && !any_of_line_part(win)) where = kNowhere;
@@ -177,7 +180,9 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
     if (TOPK && f_b == 2) {
       thr_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)T.sel_prefix[seg_b]);
       cut_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)T.sel_cut[seg_b]);
-      place_b = message_place(T, before * T.C + c, sub0 * 4 + wave_id(), T.sel_krem[seg_b]);
+      const Place p = message_place(T, before * T.C + c, cd, T.layers[layer], sub0 * 4 + wave_id(), T.sel_krem[seg_b]);
+      place_b = p.first;
+      if (HISTA && thr_b != kNoThreshold) f_b |= (uint32_t)__builtin_amdgcn_readfirstlane((int)p.count) << kCountShift;
     }
     const uint32_t f0 = read_mark(cur.f, nxt.f, 0);
     const Quad h_last = load_quad<true>(at(T.xhat, before), reads_hat(f_b) ? nb : 0u, byte);

@@ -72,46 +72,67 @@ __device__ __forceinline__ bool any_of_line_part(uint32_t any) {
   return any != 0;
 }
 
-// A uniform value that stays in a vector register.
-__device__ __forceinline__ uint32_t in_vector(uint32_t v) {
-  uint32_t r;
-  asm("v_mov_b32 %0, %1" : "=v"(r) : "s"(v));
-  return r;
+// Where a group of 256 elements has its entries in its tensor's message, and how many: the winners before it and in it.
+struct Place { uint32_t first, count; };
+
+// Chunk w of all workers' chunks, chunk c of its worker's, group g of the chunk; ties: how many keys equal to the threshold win.
+__device__ __forceinline__ Place message_place(const Tables& T, uint32_t w, const ChunkDesc& cd, const LayerDesc& ld, uint32_t g, uint32_t ties) {
+  const uint32_t G = T.SW * 4, beyond = cd.j0 + (g + 1) * 256 - cd.lead;        // the next group's first element
+  const bool same = g + 1 < G;                        // it is in this chunk
+  // (what is past the tensor's last chunk, and past its last group, is not read: the tensor ends with its K-th entry)
+  const uint32_t w2 = same || beyond >= ld.numel ? w : w + 1, g2 = same && beyond < ld.numel ? g + 1 : 0u;
+  const uint2 before = T.chunk_before[w], before2 = T.chunk_before[w2];
+  const uint32_t in_chunk = T.group[(size_t)w * G + g], in_chunk2 = T.group[(size_t)w2 * G + g2];
+  const uint32_t equal = before.y + (in_chunk >> 16), equal2 = before2.y + (in_chunk2 >> 16);
+  const uint32_t first = before.x + (in_chunk & 0xFFFFu) + (equal < ties ? equal : ties);
+  const uint32_t end = before2.x + (in_chunk2 & 0xFFFFu) + (equal2 < ties ? equal2 : ties);
+  return {first, beyond < ld.numel ? end - first : beyond < ld.numel + 256 ? ld.K - first : 0u};       // (past the tensor's end: none)
 }
 
-// Winners of the tensor before a group of 256 elements (chunk w of all workers' chunks, group g of the chunk; ties: how
-// many keys equal to the threshold win).
-__device__ __forceinline__ uint32_t message_place(const Tables& T, uint32_t w, uint32_t g, uint32_t ties) {
-  const uint2 before = T.chunk_before[w];
-  const uint32_t in_chunk = T.group[(size_t)w * (T.SW * 4) + g], equal = before.y + (in_chunk >> 16);
-  return before.x + (in_chunk & 0xFFFFu) + (equal < ties ? equal : ties);
-}
-
-// Writes the winners of a wavefront's group to their places in worker r's message, ascending indices: `place` is the first
-// one's (the same in all lanes).  The stretch that they fill is a buffer of just their number, past which the
-// other lanes' stores fall.  K: entries of the message, in a vector register (the passes are short of scalar ones): what is
-// past them, where the caller has written x since the keys were counted, goes nowhere.
-__device__ __forceinline__ void put_message(const Tables& T, uint32_t r, uint32_t msg_off, uint32_t place, uint32_t K, uint32_t win,
-                                            const float x[4], uint32_t j) {
-  uint32_t n = 0, rank = 0;
+// How many winners a wavefront's group has, and how many come before a lane's first.
+__device__ __forceinline__ uint32_t count_winners(uint32_t win, uint32_t* rank) {
+  uint32_t n = 0;
+  *rank = 0;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const uint64_t m = __ballot((win >> i) & 1u);
     n += (uint32_t)__popcll(m);
-    rank += lanes_below(m);
+    *rank += lanes_below(m);
   }
-  if (n == 0) return;                                 // wave-uniform
-  const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)place);
-  const size_t at = (size_t)r * T.Ktot + msg_off + first;
-  const __amdgpu_buffer_rsrc_t idx = window(T.msg_idx + at, n * 4), val = window(T.msg_val + at, n * 4);
+  return n;
+}
+
+// The winners of a wavefront's group, none if there are not as many as the selection has counted in it: the selection goes by key
+// codes, and the caller has written x since the last update pass left them.
+__device__ __forceinline__ uint32_t counted_winners(uint32_t win, uint32_t count) {
+  uint32_t rank;
+  return count_winners(win, &rank) == count ? win : 0u;
+}
+
+// Writes the winners of a wavefront's group to their places in worker r's message, ascending indices; `first` is the
+// first one's, `count` how many the selection has counted in the group (the same in all lanes).  CHECK: where there is another number
+// (see above) all of these places are marked as empty instead.  Returns who is sent.  The stretch of the group is a buffer of just its
+// entries, past which the other lanes' stores fall.
+template <bool CHECK>
+__device__ __forceinline__ uint32_t put_message(const Tables& T, uint32_t r, uint32_t msg_off, uint32_t first, uint32_t count, uint32_t win,
+                                                const float x[4], uint32_t j) {
+  uint32_t rank;
+  const uint32_t n = count_winners(win, &rank);
+  if (!CHECK) count = n;
+  if ((n | count) == 0) return 0;                     // wave-uniform
+  const bool fits = n == count;
+  win = fits ? win : 0u;
+  const size_t at = (size_t)r * T.Ktot + msg_off + (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
+  const __amdgpu_buffer_rsrc_t idx = window(T.msg_idx + at, count * 4), val = window(T.msg_val + at, count * 4);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const bool w = (win >> i) & 1u;
-    const int byte = (int)(w && first + rank < K ? rank * 4 : 0xFFFFFFF0u);
-    __builtin_amdgcn_raw_buffer_store_b32(j + i, idx, byte, 0, 0);
+    const int byte = (int)(!fits ? lane_id() * 16 + 4 * i : w ? rank * 4 : 0xFFFFFFF0u);
+    __builtin_amdgcn_raw_buffer_store_b32(fits ? j + i : kNoEntry, idx, byte, 0, 0);
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[i]), val, byte, 0, 0);
     rank += w ? 1u : 0u;
   }
+  return win;
 }
 
 }  // namespace evg

@@ -53,3 +53,68 @@ def test_other_tensors_messages_stay(evg, P, over):
         sa, sb = a.state(name), b.state(name)
         for l, (n, o) in enumerate(zip([3000, 40, 9001, 700], [0, 3000, 3040, 12041])):
             assert l == written or np.array_equal(sa[:, o:o + n], sb[:, o:o + n]), (name, l)
+
+
+# A write that moves a few keys from below the threshold to above it, or the other way round, leaves all counts of keys with K winners.  What
+# is sent all the same is what the message says: the groups of 256 elements in which another number wins send nothing.
+@pytest.mark.parametrize("up", [True, False], ids=["to_above", "to_below"])
+@pytest.mark.parametrize("P,over", [(4, dict(access_mode=1)), (17, dict(access_mode=1)), (4, dict(access_mode=1, xhat_reset=1)),
+                                    (17, dict(access_mode=1, xhat_reset=1)), (4, dict(access_mode=1, delivery_delay=1)),
+                                    (4, dict(access_mode=2)), (12, dict(access_mode=2))],
+                         ids=["stream", "parts", "reset", "reset_ahead", "delay", "cached", "cached_parts"])
+def test_a_message_is_what_its_sender_and_its_receivers_take(evg, P, over, up):
+    import torch
+    sizes = [3000, 40, 9001, 700] + ([1024 * 24] * 5 if over["access_mode"] == 2 and P > 4 else [])
+    tensors = [inputs.TensorSpec(f"t{i}", (n,), 16, "weight") for i, n in enumerate(sizes)]
+    w = inputs.Workload("room", P, tensors, 8, thr_mode=inputs.THR_FIXED, thr_fixed=0.0, sigma0=0.05, decay=0.9, seed=6, topk_ppm=100_000)
+    ring = evg.Ring.from_workload(w, mailbox_fill=0.0, **over)
+    starts = np.concatenate([[0], np.cumsum(sizes)])
+    for k in range(4):
+        ring.step(k)
+    for k in range(4, 7):
+        x, before = ring.state("x"), {name: ring.state(name) for name in ("xhat", "mbox_l", "mbox_r")}
+        moved = np.zeros((P, w.N), bool)
+        if k == 4:
+            for l in (0, 2):
+                part = slice(int(starts[l]), int(starts[l + 1]))
+                order = np.argsort(np.abs(x[:, part] - before["xhat"][:, part]), axis=1, kind="stable")
+                some = (order[:, :5] if up else order[:, -5:]) + starts[l]
+                np.put_along_axis(x, some, np.take_along_axis(before["xhat"], some, axis=1) + np.float32(50.0 if up else 0.0), axis=1)
+                np.put_along_axis(moved, some, True, axis=1)
+            ring.x.copy_(torch.from_numpy(ring.layout.pad(x)))
+            torch.cuda.synchronize()
+        ring.step(k)
+        assert (ring.decisions()["fired"] == 2).all()
+        after = {name: ring.state(name) for name in ("xhat", "mbox_l", "mbox_r")}
+        hashes = ring.message_hashes()[0]
+        for r in range(P):
+            sent = np.zeros(w.N, bool)
+            for l, n in enumerate(sizes):
+                idx, val = ring.message(r, l)
+                K, lead = -(-n // 10), int(ring.layout.offsets[l]) % 32 if over["access_mode"] == 1 else 0
+                if k == 4 and l in (0, 2):
+                    groups = set((np.nonzero(moved[r, starts[l]:starts[l + 1]])[0] + lead) // 256)
+                    assert 0 < idx.size < K and not groups & set((idx + lead) // 256), (k, r, l)
+                else:
+                    assert idx.size == K, (k, r, l)
+                assert (np.diff(idx.astype(np.int64)) > 0).all() and idx[-1] < n, (k, r, l)
+                assert np.array_equal(val, x[r, starts[l] + idx]) and hashes[r, l] == _index_hash(idx), (k, r, l)
+                sent[starts[l] + idx] = True
+            for name, whose in (("xhat", r), ("mbox_l", (r + 1) % P), ("mbox_r", (r - 1) % P)):
+                # (cached rings: in the step after the write a neighbour takes what the copies of x held for it)
+                if over["access_mode"] == 2 and name != "xhat":
+                    continue
+                want = before[name][whose].copy()
+                want[sent] = x[r, sent]
+                if name == "xhat" and over.get("xhat_reset"):
+                    want = x[r]
+                assert np.array_equal(after[name][whose], want), (k, r, name)
+
+
+def _index_hash(idx):
+    """The index half of evg_message_hashes: the sum of SplitMix64's finaliser over the indices."""
+    with np.errstate(over="ignore"):
+        z = idx.astype(np.uint64) + np.uint64(0x9E3779B97F4A7C15)
+        z = (z ^ z >> np.uint64(30)) * np.uint64(0xBF58476D1CE4E5B9)
+        z = (z ^ z >> np.uint64(27)) * np.uint64(0x94D049BB133111EB)
+        return (z ^ z >> np.uint64(31)).sum(dtype=np.uint64)
