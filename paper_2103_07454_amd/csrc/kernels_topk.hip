@@ -525,7 +525,8 @@ __global__ __launch_bounds__(64) void k_topk_scan(Tables T, StepArgs A) {
 //   else: to the neighbours' mailboxes (rings whose update pass cannot tell what a neighbour sent: it does not walk,
 //   and there are no copies of x, for lack of room, or as those would be out of date or of no use: a norm pass of its own,
 //   xhat reset at events).
-template <int SWEEPS, bool LEAD>
+// CODES: the ring keeps key codes.
+template <int SWEEPS, bool LEAD, bool CODES>
 __global__ __launch_bounds__(kThreads) void k_topk_apply(Tables T, StepArgs A) {
   const WorkItem wi = work_item(T, blockIdx.y, blockIdx.x);
   if (T.fired[wi.seg] != 2 || (LEAD && !is_led(T, A, wi.r))) return;           // uniform
@@ -542,7 +543,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_apply(Tables T, StepArgs A) {
     float ha[4] = {h4.x, h4.y, h4.z, h4.w};
     const uint32_t nv = !live ? 0u : wi.cd.len - e < 4u ? wi.cd.len - e : 4u;
     const Place place = message_place(T, wi.w, wi.cd, ld, it * 4 + wave_id(), T.sel_krem[wi.seg]);
-    const uint32_t win = put_message<true>(T, wi.r, ld.msg_off, place.first, t == kNoThreshold ? 0u : place.count,
+    const uint32_t win = put_message<CODES>(T, wi.r, ld.msg_off, place.first, t == kNoThreshold ? 0u : place.count,
                                            winners4(xa, ha, A.topk_key, t, cut, wi.cd.j0 + e, nv), xa, wi.cd.j0 + e);
     const bool changes = any_of_line_part(win) && live;
     if (LEAD) {
@@ -641,8 +642,10 @@ static void select_s(const Tables& t, const StepArgs& a, hipStream_t s) {
 template <int SWEEPS>
 static void apply_s(const Tables& t, const StepArgs& a, hipStream_t s) {
   const dim3 g(t.C, t.P), b(kThreads);
-  if (a.walk) k_topk_apply<SWEEPS, true><<<g, b, 0, s>>>(t, a);
-  else k_topk_apply<SWEEPS, false><<<g, b, 0, s>>>(t, a);
+  if (a.walk && t.codes) k_topk_apply<SWEEPS, true, true><<<g, b, 0, s>>>(t, a);
+  else if (a.walk) k_topk_apply<SWEEPS, true, false><<<g, b, 0, s>>>(t, a);
+  else if (t.codes) k_topk_apply<SWEEPS, false, true><<<g, b, 0, s>>>(t, a);
+  else k_topk_apply<SWEEPS, false, false><<<g, b, 0, s>>>(t, a);
 }
 
 hipError_t launch_topk_select(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s) {
