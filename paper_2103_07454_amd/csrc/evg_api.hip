@@ -103,6 +103,11 @@ struct evg_ctx {
   double ms[EVG_PH_COUNT] = {0};
   uint64_t samples[EVG_PH_COUNT] = {0};
 
+  uint64_t hists() const {           // first histograms: one a worker and tensor, and the long tensors' further copies
+    const uint64_t longs = (t.long_layer[0] != kNoLayer) + (t.long_layer[1] != kNoLayer);
+    return (uint64_t)t.S + (kHistCopies - 1) * longs * t.P;
+  }
+
   template <typename T>
   evg_status dalloc(T** p, size_t count, bool zero) {
     void* d = nullptr;
@@ -276,7 +281,7 @@ struct TableSum {
 
 // Bytes of library-owned device tables a configuration needs: the same list as the allocations of init_common.
 static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uint64_t hist_len, uint64_t Npad,
-                            uint64_t ktot, bool topk, bool norm_diff, bool pull, bool one_launch, uint64_t windows, uint64_t parts, bool codes) {
+                            uint64_t ktot, bool topk, bool norm_diff, bool pull, bool one_launch, uint64_t windows, uint64_t parts, bool codes, uint64_t hists) {
   const uint64_t S = P * L, PC = P * C;
   TableSum t;
   t.add(C, sizeof(ChunkDesc)); t.add(L, sizeof(LayerDesc));
@@ -295,7 +300,7 @@ static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uin
   }
   if (windows) t.add(windows, sizeof(WindowDesc));
   if (topk) {
-    t.add(S * kHistBins, 4); t.add(S, 4); t.add(S, 4); t.add(S, 4); t.add(PC, 4);   // hist, selection, stage_n
+    t.add(hists * kHistBins, 4); t.add(S, 4); t.add(S, 4); t.add(S, 4); t.add(PC, 4);   // hist, selection, stage_n
     t.add(P * (Npad / 16 * 4), 4);                               // stage_key
     t.add(PC * SW * 4, 4); t.add(PC, 8); t.add(PC, 8);           // group, chunk_cnt, chunk_before
     t.add(P * ktot, 4); t.add(P * ktot, 4); t.add(S, 8); t.add(S, 8);
@@ -469,8 +474,14 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   bool pull = c->cached && !cfg->delivery_delay &&
               !(cfg->topk_ppm && (cfg->xhat_reset || cfg->norm_mode == EVG_NORM_SEPARATE || !copies_fit));
   bool in_parts = false, one_launch = false, may_be = true, sets_counted = false;
-  bool codes = cfg->topk_ppm && cfg->norm_mode == EVG_NORM_FUSED, choose = false;
+  bool codes = cfg->topk_ppm && cfg->norm_mode == EVG_NORM_FUSED, choose = false, hist_copies = codes;
   uint64_t need = 0, ring_windows = 0;
+  // A tensor that is most of a ring has all workgroups of an update pass add their counts to one histogram, on all XCDs, at some 30 ns for each
+  // addition to an address; of other rings each XCD has tensors of its own (kernels_walk.hip).  One histogram -> one for each XCD, us a
+  // step: 9 perceptrons of 813 000 elements, given gradients, 152 -> 83, 30 of 556 000 225 -> 172, 3 of 461 000 (cached) 48 -> 45; streamed, 24 of 198 000
+  // 89 -> 78, 64 of 135 000 115 -> 109, 64 of 79 000 79 -> 78, 24 of 119 000 68.4 -> 68.7 (with copies from 16 384 elements on).  Tensors of more than an
+  // eighth of a ring, ResNet-18 of width 16 to 64 on 8 and 16 workers, the two longest: within 0.5 %.
+  std::vector<uint32_t> long_layers;
   uint32_t ring_part = 0;
   uint32_t longest = 0;
   for (const LayerDesc& d : layers) longest = std::max(longest, d.numel);
@@ -500,6 +511,9 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     // (admission counts the second set of what the tests read also where the parts find no room, as it always has)
     sets_counted = pull && !cfg->topk_ppm && cfg->norm_mode == EVG_NORM_FUSED && most_sweeps <= 128;
     choose = in_parts && cfg->topk_ppm;
+    long_layers.clear();
+    for (uint32_t l = 0; l < L && hist_copies && !choose; ++l)
+      if (layers[l].numel >= kHistCopiesFrom && 8ull * layers[l].numel > 3 * c->N) long_layers.push_back(l);
     ring_windows = 0;
     for (const ChunkDesc& cd : chunks) ring_windows += (cd.len + kSweep - 1) / kSweep;
     // Longer parts read less of other parts' workers and run fewer tests twice, shorter ones are more workgroups.  Parts
@@ -513,7 +527,8 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     else if (in_parts && !one_launch) ring_part = std::min<uint32_t>(ring_part, 4);
     need = table_bytes(P, L, chunks.size(), SW, hist_len, Npad, ktot, cfg->topk_ppm != 0,
                        cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF, pull && !(in_parts && ring_part == P), one_launch,
-                       in_parts ? ring_windows : 0, (P + ring_part - 1) / ring_part, codes && (choose || !c->cached));
+                       in_parts ? ring_windows : 0, (P + ring_part - 1) / ring_part, codes && (choose || !c->cached),
+                       (uint64_t)P * L + (kHistCopies - 1) * P * long_layers.size());
     return (uint64_t)P * chunks.size() * (SW + 1) <= 0xFFFFFFF0ull && (uint64_t)P * ktot <= 0xFFFFFFF0ull &&
            !(use_scratch && need > kScratchBytes);
   };
@@ -522,6 +537,10 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   if (use_scratch && need > kScratchBytes && in_parts && !cfg->topk_ppm) {        // thousands of short tensors: no room for what the parts take
     may_be = false;
     (void)cut_chunks(false);
+  }
+  if (use_scratch && need > kScratchBytes && hist_copies) {     // no room for a long tensor's histograms
+    hist_copies = false;
+    (void)cut_chunks(c->on_lines);
   }
   if (use_scratch && need > kScratchBytes && codes) {           // no room for key codes: x and xhat are read instead
     codes = false;
@@ -577,6 +596,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   t.Ktot = (uint32_t)ktot;
   t.Npad = Npad;
   t.stage_stride = Npad / 16 * 4;
+  for (size_t i = 0; i < 2; ++i) t.long_layer[i] = i < long_layers.size() ? long_layers[i] : kNoLayer;
   t.x = cfg->x; t.xhat = cfg->xhat; t.mbox_l = cfg->mbox_l; t.mbox_r = cfg->mbox_r; t.vel = cfg->vel;
   int dev = 0;
   ChunkDesc* d_chunks = nullptr;
@@ -703,7 +723,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   t.partials_out = t.partials; t.partials_hat_out = t.partials_hat; t.xhat_sq_out = t.xhat_sq;
   t.delta_out = t.delta; t.last_event_out = t.last_event;
   if (cfg->topk_ppm) {
-    TRY_OR_FREE(c->dalloc(&t.hist, S * kHistBins, true));
+    TRY_OR_FREE(c->dalloc(&t.hist, c->hists() * kHistBins, true));
     TRY_OR_FREE(c->dalloc(&t.sel_prefix, S, true));
     TRY_OR_FREE(c->dalloc(&t.sel_krem, S, true));
     TRY_OR_FREE(c->dalloc(&t.sel_cut, S, true));
@@ -1229,7 +1249,7 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
     a.topk_key = c->cfg.topk_key;
     a.choose = c->choose.longest ? 1u : 0u;
     HIP_TRY(hipMemcpyAsync(t.anchor, anchors.get(), (size_t)t.S * 4, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipMemsetAsync(t.hist, 0, (size_t)t.S * kHistBins * 4, c->stream));
+    HIP_TRY(hipMemsetAsync(t.hist, 0, c->hists() * kHistBins * 4, c->stream));
     HIP_TRY(launch_topk_count_all(t, a, c->chunk_elems, c->stream));
   }
   // the library's copy of x follows the caller's arena, which holds the saved parameters again

@@ -15,6 +15,9 @@ constexpr uint32_t kCoarseBits = 21, kFineBits = 17;                  // bits of
 constexpr uint32_t kPerCoarse = 1u << (kCoarseBits - kFineBits);      // fine bins of a coarse one
 constexpr uint32_t kFineBins = 128;                                   // fine bins
 constexpr uint32_t kCodeStride = 256;                                 // ... in eight copies, each of those codes and of all above
+constexpr uint32_t kHistCopies = 8;    // of the first histogram of a tensor that is most of a ring (Tables::long_layer)
+constexpr uint32_t kHistCopiesFrom = 131072;      // elements of such a tensor at least
+constexpr uint32_t kNoLayer = 0xFFFFFFFFu;
 constexpr uint32_t kFirstCode = 64, kCodeBins = 128;                  // key codes that are counted where there are no such histograms
 constexpr int kLastBins = 1024;        // the last takes what is left, 6 or 10 bits
 constexpr uint32_t kStageCap = 2048;   // staged keys of a chunk at most
@@ -101,7 +104,10 @@ struct Tables {
   uint32_t* ev_full; uint32_t* ev_topk; uint32_t* near_cnt; uint32_t* nonfinite_cnt;
   float* slope_hist; uint32_t* slope_cnt;   // [S*hist_len], [S]
   uint32_t* not_staged;    // [1] chunks so far whose possible winners did not fit their staging slot
-  uint32_t* hist;          // [S*kHistBins]
+  uint32_t* hist;          // [S*kHistBins], and behind it the further copies of the long tensors' (first_hist)
+  // Tensors whose first histogram, which an update pass leaves, is the sum of kHistCopies: all workgroups of a pass would add to one
+  // (up to two tensors, the first, or both, may be kNoLayer).
+  uint32_t long_layer[2];
   uint32_t* sel_prefix; uint32_t* sel_krem;   // [S] in the end the threshold key (or kNoThreshold), and how many of the keys equal to it win
   uint32_t* sel_cut;       // [S] the last element of the tensor that wins with a key equal to the threshold
   uint32_t* stage_n;       // [P*C] staged keys of a chunk: those in the threshold bin; 0xFFFFFFFF: more than the

@@ -106,16 +106,16 @@ __global__ __launch_bounds__(kThreads) void k_topk_hist(Tables T, StepArgs A) {
 
 // One workgroup per tensor that sends a Top-K message: find the bin that holds the krem-th largest key, append it to the
 // prefix, keep what is still to be taken inside that bin, and clear the histogram for the next pass.
-// PASS 0: the bins of first_bin, PASS 1: the next 11 bits, PASS 2: the rest.
+// PASS 0: the bins of first_bin, PASS 1: the next 11 bits, PASS 2: the rest.  `counted`: the histogram, if it has been taken from T.hist.
 template <int PASS>
-__device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t code, uint32_t* ws) {
+__device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t code, uint32_t* ws, const uint32_t* counted) {
   constexpr int NB = PASS == 0 ? kFirstBins : PASS == 1 ? kHistBins : kLastBins;
   constexpr int PER = NB / kThreads;
   uint32_t* gh = T.hist + (size_t)seg * kHistBins;
   if (code != 2) {          // uniform for the workgroup
     // pass A histograms are built for every tensor when the update pass makes them:
     // those of tensors that stay silent are simply dropped
-    if (PASS == 0)
+    if (PASS == 0 && !counted)
       for (uint32_t b = threadIdx.x; b < (uint32_t)kFirstBins; b += kThreads) gh[b] = 0;
     return;
   }
@@ -125,11 +125,19 @@ __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t
   const uint32_t prefix = PASS ? T.sel_prefix[seg] : 0u, bits = PASS == 1 ? T.sel_left[seg] & 255u : 0u;
   const uint32_t top = NB - 1 - threadIdx.x * PER;   // this thread's highest bin
   uint32_t cnt[PER], local = 0;
+  if (PASS == 0 && counted) {
 #pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    cnt[j] = gh[top - j];
-    gh[top - j] = 0;
-    local += cnt[j];
+    for (int j = 0; j < PER; ++j) {
+      cnt[j] = counted[top - j];
+      local += cnt[j];
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      cnt[j] = gh[top - j];
+      gh[top - j] = 0;
+      local += cnt[j];
+    }
   }
   uint32_t total;
   const uint32_t above = block_excl_scan<4>(local, ws, &total);   // keys in higher bins
@@ -165,22 +173,46 @@ __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t
 template <int PASS>
 __global__ __launch_bounds__(kThreads) void k_topk_pick(Tables T) {
   __shared__ uint32_t ws[4];
-  pick_bin<PASS>(T, blockIdx.x, T.fired[blockIdx.x], ws);
+  pick_bin<PASS>(T, blockIdx.x, T.fired[blockIdx.x], ws, nullptr);
 }
 
 // Rings whose update pass has built pass A's histograms: trigger test and pass A's bin in one
 // launch, one workgroup per tensor (the first wavefront runs the test).
 __global__ __launch_bounds__(kThreads) void k_topk_decide(Tables T, StepArgs A) {
-  __shared__ uint32_t ws[4], code;
-  const uint32_t seg = blockIdx.x;
+  __shared__ uint32_t ws[4], code, counted[kFirstBins];
+  const uint32_t seg = blockIdx.x, layer = seg % T.L;
+  const bool copies = layer == T.long_layer[0] || layer == T.long_layer[1];        // uniform
   if (wave_id() == 0) {
     double acc, acc_hat;
     bool hat_sums;
     segment_sums(T, A, seg, &acc, &acc_hat, &hat_sums);
     if (lane_id() == 0) code = segment_test(T, A, seg, acc, acc_hat, hat_sums, tested_k(T, A));
+  } else if (copies) {
+    // a long tensor's histograms, added up while it is tested (one after the other behind the test, which the bins need too: 8.7 us
+    // instead of 5.0 with 64 perceptrons of 159 000 elements)
+    uint32_t* from[kHistCopies];
+#pragma unroll
+    for (uint32_t i = 0; i < kHistCopies; ++i) {
+      const HistAt at = first_hist(T, layer, i);
+      from[i] = T.hist + (size_t)(at.first + seg / T.L * at.step) * kHistBins;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < (kFirstBins + kThreads - 65) / (kThreads - 64); ++u) {
+      const uint32_t b = u * (kThreads - 64) + threadIdx.x - 64;
+      if (b < (uint32_t)kFirstBins) {
+        uint32_t n = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < kHistCopies; ++i) n += from[i][b];
+        counted[b] = n;
+        if (n) {
+#pragma unroll
+          for (uint32_t i = 0; i < kHistCopies; ++i) from[i][b] = 0;
+        }
+      }
+    }
   }
   __syncthreads();
-  pick_bin<0>(T, seg, code, ws);
+  pick_bin<0>(T, seg, code, ws, copies ? counted : nullptr);
   if (seg == 0 && threadIdx.x == 0) close_step(T, A);
 }
 

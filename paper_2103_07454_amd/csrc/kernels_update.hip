@@ -245,7 +245,8 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
   }
   if (HISTA && sub0 * kSweep < cd.len + cd.lead) {     // uniform
     __syncthreads();
-    uint32_t* gh = T.hist + (size_t)seg * kHistBins;
+    const HistAt counts = first_hist(T, cd.layer, blockIdx.x & 7u);
+    uint32_t* gh = T.hist + (size_t)(counts.first + r * counts.step) * kHistBins;
     for (uint32_t b = threadIdx.x; b < (uint32_t)kFirstBins; b += kThreads) {
       const uint32_t v = hA[b];
       if (v) atomicAdd(&gh[b], v);

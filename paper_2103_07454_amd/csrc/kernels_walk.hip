@@ -144,6 +144,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
   // does the walk need xhat from memory?  (not where the whole tensor has just been sent)
   auto reads_hat = [](uint32_t f) { return (f & kCode) != 1 || (f & kLed) != 0; };
 
+  const HistAt counts = HISTA ? first_hist(T, layer, blockIdx.x & 7u) : HistAt{0, 0};
   if (HISTA) {
     for (uint32_t b = threadIdx.x; b < 2 * kFirstBins + 4; b += 64 * W) hist[b] = 0;
     __syncthreads();
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
     if (HISTA) {
       // two histograms in turn: this barrier ends worker r's counting, and the clearing of the other one
       __syncthreads();
-      uint32_t* gh = T.hist + (size_t)(r * T.L + layer) * kHistBins;
+      uint32_t* gh = T.hist + (size_t)(counts.first + r * counts.step) * kHistBins;
       for (uint32_t b = threadIdx.x * 4; b < (uint32_t)kFirstBins; b += 256 * W) {
         u32x4* p = reinterpret_cast<u32x4*>(hist + (i & 1u) * kFirstBins + b);
         const u32x4 n = *p;

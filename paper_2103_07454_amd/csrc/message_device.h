@@ -33,6 +33,13 @@ __device__ __forceinline__ Bins first_bins(const float x[4], const float h[4], u
   b.codes = __builtin_amdgcn_perm(codes[1], codes[0], 0x06040200u);
   return b;
 }
+// Where an update pass counts the keys of a tensor: worker r's histogram is number first + r * step of those in T.hist.
+struct HistAt { uint32_t first, step; };
+__device__ __forceinline__ HistAt first_hist(const Tables& T, uint32_t layer, uint32_t copy) {
+  const uint32_t which = layer == T.long_layer[0] ? 0u : layer == T.long_layer[1] ? 1u : 2u;
+  if (copy == 0 || which == 2) return {layer, T.L};
+  return {T.S + (which * (kHistCopies - 1) + copy - 1) * T.P, 1u};
+}
 // The smallest key of a bin, and how many bits its keys have below it.
 __device__ __forceinline__ uint32_t bin_begin(uint32_t bin, uint32_t anchor, uint32_t* left) {
   const uint32_t a = anchor / kPerCoarse;

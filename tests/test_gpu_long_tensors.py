@@ -1,0 +1,68 @@
+"""A tensor that is most of a Top-K ring has its keys counted in several histograms, which the selection adds up.  Checked against the
+oracle on both sides of the sizes where that begins (131 072 elements, three eighths of the ring), with one such tensor and two, streaming
+and cached, with delayed delivery and xhat reset, events and silent steps; and resumed from blobs of rings that count otherwise."""
+import numpy as np
+import pytest
+
+from paper_2103_07454_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+ARENAS = ("x", "xhat", "vel", "mbox_l", "mbox_r")
+
+
+@pytest.fixture(scope="module")
+def evg():
+    from paper_2103_07454_amd import evg as m
+    m.lib()
+    return m
+
+
+def _workload(P, sizes, iters, **kw):
+    tensors = [inputs.TensorSpec(f"t{i}", (n,), 16 + i, "weight") for i, n in enumerate(sizes)]
+    base = dict(sigma0=0.05, decay=0.97, seed=P, topk_ppm=30_000, spike_prob=0.2, spike_gain=3.0)
+    base.update(kw)
+    return inputs.Workload("long", P, tensors, iters, **base)
+
+
+# (the last two: a tensor of just under and of just over three eighths)
+@pytest.mark.parametrize("P,sizes", [(3, [131_071, 5]), (3, [131_072, 5]), (4, [140_003, 140_000, 9]), (3, [400_001]),
+                                     (3, [150_000, 125_000, 125_001]), (3, [150_004, 125_000, 125_001])], ids=lambda v: str(v).replace(" ", ""))
+@pytest.mark.parametrize("both", [dict(), dict(delivery_delay=1), dict(xhat_reset=1), dict(topk_key=1)], ids=["drift", "delay", "reset", "value"])
+@pytest.mark.parametrize("access", [1, 2], ids=["stream", "cached"])
+def test_selections(evg, oracle_mod, P, sizes, both, access):
+    from helpers import lockstep
+    w = _workload(P, sizes, 7)
+    x0 = inputs.replicate(w.x0(), P)
+    ring = evg.Ring.from_workload(w, x0, mailbox_fill=float("nan"), access_mode=access, **both)
+    orc = oracle_mod.Oracle.from_workload(w, x0, **both)
+    rep = lockstep(ring, orc, w.iters, sample_messages=4)
+    assert all(rep["bitwise"].values()), rep
+
+
+def test_blobs_and_silent_steps(evg):
+    sizes = [340_000, 3]
+    w = _workload(3, sizes, 14, sigma0=0.02, decay=0.9, spike_prob=0.0)
+    modes = (evg.ACCESS_STREAM, evg.ACCESS_CACHED)
+    rings = [evg.Ring.from_workload(w, mailbox_fill=0.0, access_mode=m) for m in modes]
+    fired = []
+    for k in range(7):
+        for r in rings:
+            r.step(k)
+        fired.append(rings[0].decisions()["fired"][:, 0])
+    blobs = [r.export_state() for r in rings]
+    rings += [evg.Ring.from_workload(w, mailbox_fill=0.0, access_mode=m) for m in modes for _ in blobs]
+    for r, b in zip(rings[2:], blobs * 2):
+        r.import_state(b)
+    for k in range(7, 14):
+        for r in rings:
+            r.step(k)
+        fired.append(rings[0].decisions()["fired"][:, 0])
+        for r in rings[1:]:
+            assert np.array_equal(rings[0].decisions()["fired"], r.decisions()["fired"]), k
+            for mine, its in zip(rings[0].message_hashes(), r.message_hashes()):
+                assert np.array_equal(mine, its), k
+    assert (np.array(fired) == 0).any() and (np.array(fired)[7:] == 2).any()
+    for r in rings[1:]:
+        for name in ARENAS:
+            assert np.array_equal(rings[0].state(name), r.state(name)), name
