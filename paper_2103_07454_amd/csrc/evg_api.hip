@@ -735,7 +735,10 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     TRY_OR_FREE(c->dalloc(&t.msg_idx, (uint64_t)P * ktot, true));
     TRY_OR_FREE(c->dalloc(&t.msg_val, (uint64_t)P * ktot, true));
     TRY_OR_FREE(c->dalloc(&t.sel_left, S, true));
-    if (cfg->norm_mode == EVG_NORM_FUSED) {
+    // Cached rings that put their messages ahead or late and have short tensors only count their keys by the upper 11 bits: finer bins about the
+    // threshold cost the update pass more than they save with a tensor's few keys (64 ResNet-18 workers of width 8 223 -> 213 us a step, given
+    // gradients 211 -> 208; of perceptrons of 159 000 elements 122 -> 129).
+    if (cfg->norm_mode == EVG_NORM_FUSED && (pull || !c->cached || !long_layers.empty())) {
       TRY_OR_FREE(c->dalloc(&t.anchor, S, false));
       HIP_OR_FREE(hipMemsetAsync(t.anchor, 0xFF, S * 4, c->stream));      // kNoAnchor
     }
@@ -1095,6 +1098,9 @@ std::vector<Piece> state_pieces(evg_ctx* c) {
   return v;
 }
 
+// Does the update pass count the keys of the next selection?
+bool carries_keys(const evg_ctx* c) { return c->cfg.topk_ppm && c->cfg.norm_mode == EVG_NORM_FUSED; }
+
 StateHeader state_header(evg_ctx* c) {
   StateHeader h{};
   std::memcpy(h.magic, "EVGSTATE", 8);
@@ -1140,10 +1146,11 @@ evg_status evg_state_export(evg_ctx* c, void* blob, uint64_t capacity) {
     HIP_TRY(hipMemcpy(out, p.dev, p.bytes, hipMemcpyDeviceToHost));
     out += p.bytes;
   }
-  if (c->t.anchor) {       // (see evg_state_import)
+  if (carries_keys(c)) {       // (see evg_state_import)
     std::unique_ptr<uint32_t[]> anchors(new (std::nothrow) uint32_t[c->t.S]);
     if (!anchors) return fail(EVG_ERR_OOM, "host allocation failed");
-    HIP_TRY(hipMemcpy(anchors.get(), c->t.anchor, (size_t)c->t.S * 4, hipMemcpyDeviceToHost));
+    std::fill_n(anchors.get(), c->t.S, kNoAnchor);
+    if (c->t.anchor) HIP_TRY(hipMemcpy(anchors.get(), c->t.anchor, (size_t)c->t.S * 4, hipMemcpyDeviceToHost));
     char* hists = out - (size_t)c->t.S * kHistBins * 4;
     for (size_t i = 0; i < c->t.S; ++i) std::memcpy(hists + (i * kHistBins + kHistBins - 1) * 4, &anchors[i], 4);
   }
@@ -1197,7 +1204,7 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
   const size_t clock_count = c->one_launch ? (size_t)c->parts.count * ((t.P + c->part - 1) / c->part) : 0;
   std::unique_ptr<PartClock[]> clocks(new (std::nothrow) PartClock[clock_count + 1]);
   if (!clocks) return fail(EVG_ERR_OOM, "host allocation failed");
-  // anchors of key codes: in the last word of a tensor's saved histogram, which the bins do not reach, from version 6 on
+  // anchors of key codes, if the exporter had any: in the last word of a tensor's saved histogram, from version 6 on
   std::unique_ptr<uint32_t[]> anchors(new (std::nothrow) uint32_t[t.S]);
   if (!anchors) return fail(EVG_ERR_OOM, "host allocation failed");
   const char* hists = static_cast<const char*>(blob) + size - (size_t)t.S * kHistBins * 4;      // (the last piece, if there is one)
@@ -1243,12 +1250,12 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
   }
   if (clock_count)
     HIP_TRY(hipMemcpyAsync(c->parts.clocks, clocks.get(), clock_count * sizeof(PartClock), hipMemcpyHostToDevice, c->stream));
-  if (t.anchor) {
-    // Histograms and key codes are counted again, from the arenas: the saved ones go by eighths of an octave in versions before 6.
+  if (carries_keys(c)) {
+    // Histograms and key codes are counted again, from the arenas: the saved ones have the exporter's bins.
     StepArgs a{};
     a.topk_key = c->cfg.topk_key;
     a.choose = c->choose.longest ? 1u : 0u;
-    HIP_TRY(hipMemcpyAsync(t.anchor, anchors.get(), (size_t)t.S * 4, hipMemcpyHostToDevice, c->stream));
+    if (t.anchor) HIP_TRY(hipMemcpyAsync(t.anchor, anchors.get(), (size_t)t.S * 4, hipMemcpyHostToDevice, c->stream));
     HIP_TRY(hipMemsetAsync(t.hist, 0, c->hists() * kHistBins * 4, c->stream));
     HIP_TRY(launch_topk_count_all(t, a, c->chunk_elems, c->stream));
   }

@@ -12,6 +12,7 @@ constexpr uint32_t kLineElems = 32;    // floats of a 128-byte cache line
 constexpr int kHistBins = 2048;        // histogram of a selection pass: the second takes 11 bits of a key
 constexpr int kFirstBins = 1280;       // the first (see first_bins)
 constexpr uint32_t kCoarseBits = 21, kFineBits = 17;                  // bits of a key below its coarse and fine bins
+constexpr uint32_t kPlainBits = 20;                                   // below the bins of rings without anchors
 constexpr uint32_t kPerCoarse = 1u << (kCoarseBits - kFineBits);      // fine bins of a coarse one
 constexpr uint32_t kFineBins = 128;                                   // fine bins
 constexpr uint32_t kCodeStride = 256;                                 // ... in eight copies, each of those codes and of all above

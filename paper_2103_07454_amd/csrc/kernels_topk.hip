@@ -73,10 +73,10 @@ __device__ __forceinline__ void flush_hist(const uint32_t* h, uint32_t* gh) {
 // leaves.
 template <int SWEEPS, bool ALL>
 __global__ __launch_bounds__(kThreads) void k_topk_hist(Tables T, StepArgs A) {
-  __shared__ uint32_t h[kFirstBins];
+  __shared__ uint32_t h[kHistBins];
   const WorkItem wi = work_item(T, blockIdx.y, blockIdx.x);
   if (!ALL && T.fired[wi.seg] != 2) return;          // uniform
-  for (uint32_t b = threadIdx.x; b < (uint32_t)kFirstBins; b += kThreads) h[b] = 0;
+  for (uint32_t b = threadIdx.x; b < (uint32_t)kHistBins; b += kThreads) h[b] = 0;
   __syncthreads();
 #pragma unroll
   for (int it = 0; it < SWEEPS; ++it) {
@@ -87,11 +87,11 @@ __global__ __launch_bounds__(kThreads) void k_topk_hist(Tables T, StepArgs A) {
       if (!A.topk_key) h4 = ld4s(T.xhat + wi.base + e);
       const float xa[4] = {x4.x, x4.y, x4.z, x4.w}, ha[4] = {h4.x, h4.y, h4.z, h4.w};
       const uint32_t nv = wi.cd.len - e < 4u ? wi.cd.len - e : 4u;
-      const Bins bins = first_bins(xa, ha, A.topk_key, ALL ? T.anchor[wi.seg] : kNoAnchor);
+      const Bins bins = first_bins(xa, ha, A.topk_key, T.anchor ? T.anchor[wi.seg] : kNoAnchor);
       if (ALL && T.codes) store_codes(T, wi.base, (wi.cd.len + 3) / 4 * 16, e * 4, bins.codes);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        uint32_t b = bins.bin[q];
+        uint32_t b = T.anchor ? bins.bin[q] : rank_key(xa[q], ha[q], A.topk_key) >> kPlainBits;
         if (ALL && A.choose) {                             // what k_update_part counts
           const uint32_t c = (bins.codes >> (8 * q) & 255u) - kFirstCode;
           b = (int)c < 0 ? kFirstBins - 1 : c < kCodeBins ? c : kCodeBins;
@@ -101,27 +101,28 @@ __global__ __launch_bounds__(kThreads) void k_topk_hist(Tables T, StepArgs A) {
     }
   }
   __syncthreads();
-  flush_hist<kFirstBins>(h, T.hist + (size_t)wi.seg * kHistBins);
+  flush_hist<kHistBins>(h, T.hist + (size_t)wi.seg * kHistBins);
 }
 
 // One workgroup per tensor that sends a Top-K message: find the bin that holds the krem-th largest key, append it to the
 // prefix, keep what is still to be taken inside that bin, and clear the histogram for the next pass.
-// PASS 0: the bins of first_bin, PASS 1: the next 11 bits, PASS 2: the rest.  `counted`: the histogram, if it has been taken from T.hist.
-template <int PASS>
+// PASS 0: the bins of first_bins (FINE: the ring has anchors) or a key's upper 11 bits, PASS 1: the next 11 bits, PASS 2: the rest.
+// `counted`: the histogram, if it has been taken from T.hist.
+template <int PASS, bool FINE = false>
 __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t code, uint32_t* ws, const uint32_t* counted) {
-  constexpr int NB = PASS == 0 ? kFirstBins : PASS == 1 ? kHistBins : kLastBins;
+  constexpr int NB = PASS == 0 ? FINE ? kFirstBins : kHistBins : PASS == 1 ? kHistBins : kLastBins;
   constexpr int PER = NB / kThreads;
   uint32_t* gh = T.hist + (size_t)seg * kHistBins;
   if (code != 2) {          // uniform for the workgroup
     // pass A histograms are built for every tensor when the update pass makes them:
     // those of tensors that stay silent are simply dropped
     if (PASS == 0 && !counted)
-      for (uint32_t b = threadIdx.x; b < (uint32_t)kFirstBins; b += kThreads) gh[b] = 0;
+      for (uint32_t b = threadIdx.x; b < (uint32_t)NB; b += kThreads) gh[b] = 0;
     return;
   }
   const uint32_t krem = PASS == 0 ? T.layers[seg % T.L].K : T.sel_krem[seg];
   // asked for along with the counts, not by the thread that finds the bin: a load less in the chain of launches
-  const uint32_t anchor = PASS == 0 && T.anchor ? T.anchor[seg] : kNoAnchor;
+  const uint32_t anchor = PASS == 0 && FINE ? T.anchor[seg] : kNoAnchor;
   const uint32_t prefix = PASS ? T.sel_prefix[seg] : 0u, bits = PASS == 1 ? T.sel_left[seg] & 255u : 0u;
   const uint32_t top = NB - 1 - threadIdx.x * PER;   // this thread's highest bin
   uint32_t cnt[PER], local = 0;
@@ -143,7 +144,7 @@ __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t
   const uint32_t above = block_excl_scan<4>(local, ws, &total);   // keys in higher bins
   if (total < krem && threadIdx.x == 0) {
     T.sel_prefix[seg] = kNoThreshold;
-    if (PASS == 0) T.sel_left[seg] = kCoarseBits;
+    if (PASS == 0) T.sel_left[seg] = FINE ? kCoarseBits : kPlainBits;
   }
   if (above < krem && krem <= above + local) {    // exactly one thread
     uint32_t run = above, bin = top, rem = krem - above;
@@ -153,16 +154,18 @@ __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t
       run += cnt[j];
     }
     T.sel_krem[seg] = rem;
-    if (PASS == 0) {
-      uint32_t left, next;
+    if (PASS == 0 && FINE) {
+      uint32_t left;
       const uint32_t begin = bin_begin(bin, anchor, &left);
       T.sel_prefix[seg] = begin;
       const uint32_t fine = (begin >> kFineBits) - anchor;
       T.sel_left[seg] = left | (T.codes && left == kFineBits && fine > 0u && fine < 255u ? fine << 8 : 0u);
-      if (T.anchor) {            // of the histogram and codes that the update pass will leave: this bin in the middle
-        next = (begin >> kFineBits) + kPerCoarse / 2;
-        T.anchor[seg] = next > kFineBins / 2 ? (next - kFineBins / 2) / kPerCoarse * kPerCoarse : 0u;
-      }
+      // of the histogram and codes that the update pass will leave: this bin in the middle
+      const uint32_t next = (begin >> kFineBits) + kPerCoarse / 2;
+      T.anchor[seg] = next > kFineBins / 2 ? (next - kFineBins / 2) / kPerCoarse * kPerCoarse : 0u;
+    } else if (PASS == 0) {
+      T.sel_prefix[seg] = bin << kPlainBits;
+      T.sel_left[seg] = kPlainBits;
     } else {
       // (a selection that has ended stays so)
       if (prefix != kNoThreshold) T.sel_prefix[seg] = prefix + (PASS == 1 ? bin << (bits - 11u) : bin);
@@ -178,8 +181,10 @@ __global__ __launch_bounds__(kThreads) void k_topk_pick(Tables T) {
 
 // Rings whose update pass has built pass A's histograms: trigger test and pass A's bin in one
 // launch, one workgroup per tensor (the first wavefront runs the test).
+template <bool FINE>
 __global__ __launch_bounds__(kThreads) void k_topk_decide(Tables T, StepArgs A) {
-  __shared__ uint32_t ws[4], code, counted[kFirstBins];
+  constexpr uint32_t NB = FINE ? kFirstBins : kHistBins;
+  __shared__ uint32_t ws[4], code, counted[NB];
   const uint32_t seg = blockIdx.x, layer = seg % T.L;
   const bool copies = layer == T.long_layer[0] || layer == T.long_layer[1];        // uniform
   if (wave_id() == 0) {
@@ -197,9 +202,9 @@ __global__ __launch_bounds__(kThreads) void k_topk_decide(Tables T, StepArgs A) 
       from[i] = T.hist + (size_t)(at.first + seg / T.L * at.step) * kHistBins;
     }
 #pragma unroll
-    for (uint32_t u = 0; u < (kFirstBins + kThreads - 65) / (kThreads - 64); ++u) {
+    for (uint32_t u = 0; u < (NB + kThreads - 65) / (kThreads - 64); ++u) {
       const uint32_t b = u * (kThreads - 64) + threadIdx.x - 64;
-      if (b < (uint32_t)kFirstBins) {
+      if (b < NB) {
         uint32_t n = 0;
 #pragma unroll
         for (uint32_t i = 0; i < kHistCopies; ++i) n += from[i][b];
@@ -212,7 +217,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_decide(Tables T, StepArgs A) 
     }
   }
   __syncthreads();
-  pick_bin<0>(T, seg, code, ws, copies ? counted : nullptr);
+  pick_bin<0, FINE>(T, seg, code, ws, copies ? counted : nullptr);
   if (seg == 0 && threadIdx.x == 0) close_step(T, A);
 }
 
@@ -312,7 +317,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_stage(Tables T, StepArgs A) {
   if (code != 2) return;
   const uint32_t begin = T.sel_prefix[wi.seg], left = T.sel_left[wi.seg] & 255u, of_bin = T.sel_left[wi.seg] >> 8;
   if (threadIdx.x == 0) listed = 0;
-  if (of_bin) {                                        // uniform
+  if (STREAM && of_bin) {                              // uniform (cached rings whose selections are made here keep no codes)
     stage_by_codes<SWEEPS>(T, A, wi, begin, of_bin, list, &listed);
   } else {
   for (uint32_t b = threadIdx.x; b < (uint32_t)kHistBins; b += kThreads) h[b] = 0;
@@ -574,7 +579,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_apply(Tables T, StepArgs A) {
     const float xa[4] = {x4.x, x4.y, x4.z, x4.w};
     float ha[4] = {h4.x, h4.y, h4.z, h4.w};
     const uint32_t nv = !live ? 0u : wi.cd.len - e < 4u ? wi.cd.len - e : 4u;
-    const Place place = message_place(T, wi.w, wi.cd, ld, it * 4 + wave_id(), T.sel_krem[wi.seg]);
+    const Place place = message_place<CODES>(T, wi.w, wi.cd, ld, it * 4 + wave_id(), T.sel_krem[wi.seg]);
     const uint32_t win = put_message<CODES>(T, wi.r, ld.msg_off, place.first, t == kNoThreshold ? 0u : place.count,
                                            winners4(xa, ha, A.topk_key, t, cut, wi.cd.j0 + e, nv), xa, wi.cd.j0 + e);
     const bool changes = any_of_line_part(win) && live;
@@ -647,7 +652,8 @@ hipError_t launch_message_hashes(const Tables& t, hipStream_t s) {
 }
 
 hipError_t launch_topk_decide(const Tables& t, const StepArgs& a, hipStream_t s) {
-  k_topk_decide<<<dim3(t.S), dim3(kThreads), 0, s>>>(t, a);
+  if (t.anchor) k_topk_decide<true><<<dim3(t.S), dim3(kThreads), 0, s>>>(t, a);
+  else k_topk_decide<false><<<dim3(t.S), dim3(kThreads), 0, s>>>(t, a);
   return hipGetLastError();
 }
 

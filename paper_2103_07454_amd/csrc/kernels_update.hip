@@ -73,10 +73,12 @@ __device__ __forceinline__ void block_sums(const double v[SPW], double* ws, doub
 // mailbox here; and the new x is also written to the other of the two copies for the next
 // iteration (two copies in turn: the one read now is written by nobody in this launch).  Fewer
 // launches per iteration for rings that live in the cache, where launches are what costs.
-template <int DIST, bool GRADBUF, int NORM, bool TOPK, bool HISTA, int SPW, bool STREAM, bool PULL = false>
+// FINE: it goes by the bins of first_bins, else by the upper 11 bits of a key (cached rings without anchors).
+template <int DIST, bool GRADBUF, int NORM, bool TOPK, bool HISTA, int SPW, bool STREAM, bool PULL = false, bool FINE = true>
 __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
   __shared__ double ws[4 * SPW];
-  __shared__ uint32_t hA[HISTA ? kFirstBins : 1];
+  constexpr uint32_t BINS = FINE ? kFirstBins : kHistBins;
+  __shared__ uint32_t hA[HISTA ? BINS : 1];
   const uint32_t groups = T.SW / SPW;      // workgroups per chunk (SW is a multiple of SPW)
   const uint32_t c = blockIdx.x / groups, sub0 = (blockIdx.x % groups) * SPW, r = blockIdx.y;
   const ChunkDesc cd = T.chunks[c];
@@ -123,15 +125,14 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
     // selections of mine and the neighbours' tensors, asked for early: nobody waits for them until the arenas are there
     uint32_t thr[3], cut[3], moff = 0;
     Place place[SPW];
-    const uint32_t anchor = TOPK && NORM ? T.anchor[seg] : kNoAnchor;
+    const uint32_t anchor = TOPK && NORM && FINE ? T.anchor[seg] : kNoAnchor;
     if (TOPK) {
       const uint32_t segs[3] = {seg, PULL ? lw * T.L + cd.layer : seg, PULL ? rw * T.L + cd.layer : seg};
 #pragma unroll
       for (int i = 0; i < 3; ++i) { thr[i] = T.sel_prefix[segs[i]]; cut[i] = T.sel_cut[segs[i]]; }
-      const LayerDesc ld = T.layers[cd.layer];
-      moff = ld.msg_off;
+      moff = T.layers[cd.layer].msg_off;
 #pragma unroll
-      for (int u = 0; u < SPW; ++u) place[u] = message_place(T, r * T.C + c, cd, ld, (sub0 + u) * 4 + wave_id(), T.sel_krem[seg]);
+      for (int u = 0; u < SPW; ++u) place[u] = message_place<STREAM && NORM != 0>(T, r * T.C + c, cd, T.layers[cd.layer], (sub0 + u) * 4 + wave_id(), T.sel_krem[seg]);
     }
     auto receive = [&](uint32_t thr, uint32_t cut, const float (*sx)[4], float* mbox, float (*a)[4]) {
 #pragma unroll
@@ -205,7 +206,7 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
       if (PULL && some_r) receive(thr[2], cut[2], rx, T.mbox_r, ra);
     }
     if (HISTA) {
-      for (uint32_t b = threadIdx.x; b < (uint32_t)kFirstBins; b += kThreads) hA[b] = 0;
+      for (uint32_t b = threadIdx.x; b < BINS; b += kThreads) hA[b] = 0;
       __syncthreads();
     }
 #pragma unroll
@@ -233,21 +234,26 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
         if (NORM == 1) drift_acc(acc[u], xa[u], ha[u], nv[u]);
         if (NORM >= 2) square_acc(acc[u], xa[u], nv[u]);
         if (NORM == 3) square_acc(acc_hat[u], ha[u], nv[u]);
-        if (TOPK && NORM) {
+        if (TOPK && NORM && !FINE) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (HISTA && (uint32_t)i < nv[u]) atomicAdd(&hA[rank_key(xa[u][i], ha[u][i], A.topk_key) >> kPlainBits], 1u);
+        }
+        if (TOPK && NORM && FINE) {
           const Bins bins = first_bins(xa[u], ha[u], A.topk_key, anchor);
 #pragma unroll
           for (int i = 0; i < 4; ++i)
             if (HISTA && (uint32_t)i < nv[u]) atomicAdd(&hA[bins.bin[i]], 1u);
-          if (!PULL && T.codes) store_codes(T, base, (cd.len + 3) / 4 * 16, e[u] * 4, bins.codes);
+          if (STREAM && T.codes) store_codes(T, base, (cd.len + 3) / 4 * 16, e[u] * 4, bins.codes);
         }
       }
     }
   }
   if (HISTA && sub0 * kSweep < cd.len + cd.lead) {     // uniform
     __syncthreads();
-    const HistAt counts = first_hist(T, cd.layer, blockIdx.x & 7u);
+    const HistAt counts = first_hist(T, cd.layer, FINE ? blockIdx.x & 7u : 0u);
     uint32_t* gh = T.hist + (size_t)(counts.first + r * counts.step) * kHistBins;
-    for (uint32_t b = threadIdx.x; b < (uint32_t)kFirstBins; b += kThreads) {
+    for (uint32_t b = threadIdx.x; b < BINS; b += kThreads) {
       const uint32_t v = hA[b];
       if (v) atomicAdd(&gh[b], v);
     }
@@ -298,6 +304,13 @@ static void launch_update_w(const Tables& t, const StepArgs& a, uint32_t dist, u
     if (grad_mode == 1) k_update<0, true, NORM, TOPK, HISTA, SPW, false, true><<<grid, block, 0, s>>>(t, a);
     else if (dist == 0) k_update<0, false, NORM, TOPK, HISTA, SPW, false, true><<<grid, block, 0, s>>>(t, a);
     else k_update<1, false, NORM, TOPK, HISTA, SPW, false, true><<<grid, block, 0, s>>>(t, a);
+    return;
+  }
+  if (a.cached && HISTA && !t.anchor) {
+    constexpr bool F = !HISTA;
+    if (grad_mode == 1) k_update<0, true, NORM, TOPK, HISTA, SPW, false, false, F><<<grid, block, 0, s>>>(t, a);
+    else if (dist == 0) k_update<0, false, NORM, TOPK, HISTA, SPW, false, false, F><<<grid, block, 0, s>>>(t, a);
+    else k_update<1, false, NORM, TOPK, HISTA, SPW, false, false, F><<<grid, block, 0, s>>>(t, a);
     return;
   }
   if (a.cached) {

@@ -91,7 +91,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
       else if (TOPK && code == 2) {
         m.thr = T.sel_prefix[seg];
         m.cut = T.sel_cut[seg];
-        const Place p = message_place(T, s * T.C + c, cd, T.layers[layer], sub0 * 4 + wave_id(), T.sel_krem[seg]);
+        const Place p = message_place<HISTA>(T, s * T.C + c, cd, T.layers[layer], sub0 * 4 + wave_id(), T.sel_krem[seg]);
         m.place = p.first;
         if (HISTA && m.thr != kNoThreshold) m.f |= p.count << kCountShift;
       }
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
     if (TOPK && f_b == 2) {
       thr_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)T.sel_prefix[seg_b]);
       cut_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)T.sel_cut[seg_b]);
-      const Place p = message_place(T, before * T.C + c, cd, T.layers[layer], sub0 * 4 + wave_id(), T.sel_krem[seg_b]);
+      const Place p = message_place<HISTA>(T, before * T.C + c, cd, T.layers[layer], sub0 * 4 + wave_id(), T.sel_krem[seg_b]);
       place_b = p.first;
       if (HISTA && thr_b != kNoThreshold) f_b |= (uint32_t)__builtin_amdgcn_readfirstlane((int)p.count) << kCountShift;
     }

@@ -79,20 +79,27 @@ __device__ __forceinline__ bool any_of_line_part(uint32_t any) {
   return any != 0;
 }
 
-// Where a group of 256 elements has its entries in its tensor's message, and how many: the winners before it and in it.
+// Winners of the tensor before a group of 256 elements (chunk w of all workers' chunks, group g of the chunk; ties: how
+// many keys equal to the threshold win).
+__device__ __forceinline__ uint32_t winners_before(const Tables& T, uint32_t w, uint32_t g, uint32_t ties) {
+  const uint2 before = T.chunk_before[w];
+  const uint32_t in_chunk = T.group[(size_t)w * (T.SW * 4) + g], equal = before.y + (in_chunk >> 16);
+  return before.x + (in_chunk & 0xFFFFu) + (equal < ties ? equal : ties);
+}
+
+// Where a group has its entries in its tensor's message, and (CHECK, see put_message) how many.
 struct Place { uint32_t first, count; };
 
-// Chunk w of all workers' chunks, chunk c of its worker's, group g of the chunk; ties: how many keys equal to the threshold win.
+// w, cd: the chunk.
+template <bool CHECK>
 __device__ __forceinline__ Place message_place(const Tables& T, uint32_t w, const ChunkDesc& cd, const LayerDesc& ld, uint32_t g, uint32_t ties) {
+  const uint32_t first = winners_before(T, w, g, ties);
+  if (!CHECK) return {first, 0u};
   const uint32_t G = T.SW * 4, beyond = cd.j0 + (g + 1) * 256 - cd.lead;        // the next group's first element
   const bool same = g + 1 < G;                        // it is in this chunk
   // (what is past the tensor's last chunk, and past its last group, is not read: the tensor ends with its K-th entry)
   const uint32_t w2 = same || beyond >= ld.numel ? w : w + 1, g2 = same && beyond < ld.numel ? g + 1 : 0u;
-  const uint2 before = T.chunk_before[w], before2 = T.chunk_before[w2];
-  const uint32_t in_chunk = T.group[(size_t)w * G + g], in_chunk2 = T.group[(size_t)w2 * G + g2];
-  const uint32_t equal = before.y + (in_chunk >> 16), equal2 = before2.y + (in_chunk2 >> 16);
-  const uint32_t first = before.x + (in_chunk & 0xFFFFu) + (equal < ties ? equal : ties);
-  const uint32_t end = before2.x + (in_chunk2 & 0xFFFFu) + (equal2 < ties ? equal2 : ties);
+  const uint32_t end = winners_before(T, w2, g2, ties);
   return {first, beyond < ld.numel ? end - first : beyond < ld.numel + 256 ? ld.K - first : 0u};       // (past the tensor's end: none)
 }
 

@@ -40,18 +40,20 @@ def test_selections(evg, oracle_mod, P, sizes, both, access):
     assert all(rep["bitwise"].values()), rep
 
 
-def test_blobs_and_silent_steps(evg):
-    sizes = [340_000, 3]
+# (cached rings without a long tensor, whose messages are put ahead or late, count their keys in other bins than streaming ones)
+@pytest.mark.parametrize("sizes,both", [([340_000, 3], dict()), ([100_000, 3], dict(xhat_reset=1)), ([100_000, 90_001], dict(delivery_delay=1))],
+                         ids=["drift", "reset", "delay"])
+def test_blobs_and_silent_steps(evg, sizes, both):
     w = _workload(3, sizes, 14, sigma0=0.02, decay=0.9, spike_prob=0.0)
     modes = (evg.ACCESS_STREAM, evg.ACCESS_CACHED)
-    rings = [evg.Ring.from_workload(w, mailbox_fill=0.0, access_mode=m) for m in modes]
+    rings = [evg.Ring.from_workload(w, mailbox_fill=0.0, access_mode=m, **both) for m in modes]
     fired = []
     for k in range(7):
         for r in rings:
             r.step(k)
         fired.append(rings[0].decisions()["fired"][:, 0])
     blobs = [r.export_state() for r in rings]
-    rings += [evg.Ring.from_workload(w, mailbox_fill=0.0, access_mode=m) for m in modes for _ in blobs]
+    rings += [evg.Ring.from_workload(w, mailbox_fill=0.0, access_mode=m, **both) for m in modes for _ in blobs]
     for r, b in zip(rings[2:], blobs * 2):
         r.import_state(b)
     for k in range(7, 14):
