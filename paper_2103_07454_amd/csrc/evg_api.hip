@@ -1152,6 +1152,7 @@ evg_status evg_state_export(evg_ctx* c, void* blob, uint64_t capacity) {
     std::fill_n(anchors.get(), c->t.S, kNoAnchor);
     if (c->t.anchor) HIP_TRY(hipMemcpy(anchors.get(), c->t.anchor, (size_t)c->t.S * 4, hipMemcpyDeviceToHost));
     char* hists = out - (size_t)c->t.S * kHistBins * 4;
+    for (size_t i = 0; i < c->t.S; ++i) if (anchors[i] != kNoAnchor) anchors[i] &= kAnchorBits;      // (an import makes the codes)
     for (size_t i = 0; i < c->t.S; ++i) std::memcpy(hists + (i * kHistBins + kHistBins - 1) * 4, &anchors[i], 4);
   }
   return EVG_OK;

@@ -27,6 +27,10 @@ constexpr uint32_t kStageCap = 2048;   // staged keys of a chunk at most
 // Nothing is sent then.  Where keys are counted by their codes, the update passes compare each 256 elements' winners with the count.
 constexpr uint32_t kNoThreshold = 0xFFFFFFFFu;
 constexpr uint32_t kNoAnchor = 0xFFFFFFFFu;
+// Anchors are multiples of 16.  Bit 0 of one (and of kNoAnchor): the update pass leaves no key codes, as the tensor has been silent
+// for more than kCodedFor iterations (streaming rings): its next selection reads x and xhat.
+constexpr uint32_t kUncoded = 1u, kAnchorBits = ~15u;
+constexpr uint32_t kCodedFor = 4;        // (some five bytes written cost what seven that need not be read save)
 constexpr uint32_t kNoEntry = 0xFFFFFFFFu;       // index in a message's place that nothing was sent for
 
 // A chunk is a run of one tensor's elements that one workgroup handles; it never
@@ -116,7 +120,7 @@ struct Tables {
   uint32_t* stage_key;     // [P*stage_stride] their bits below the bin (at most 21), and from bit 21 on the group of the chunk they belong to
   uint64_t stage_stride;   // staging entries per worker
   uint8_t* codes;          // [P*Npad] or null: rank keys of x and xhat as the last update pass left them, in a byte: bits 30..17
-                           // counted from the tensor's anchor; 0 and 255 also stand for all that is further off
+                           // counted from the tensor's anchor; 0 and 255 also stand for all that is further off (see kUncoded)
   uint32_t* anchor;        // [S] or null: where the fine bins of the first pass's histogram begin; kNoAnchor: there are none
   uint32_t* sel_left;      // [S] bits of a key below the first pass's bin, and from bit 8 on the code of that bin's keys (0: none)
   uint32_t* group;         // [P*C*SW*4] per 256 elements: keys above the threshold bin; in the end, over the chunk's

@@ -240,11 +240,11 @@ __global__ __launch_bounds__(kThreads) void k_update(Tables T, StepArgs A) {
             if (HISTA && (uint32_t)i < nv[u]) atomicAdd(&hA[rank_key(xa[u][i], ha[u][i], A.topk_key) >> kPlainBits], 1u);
         }
         if (TOPK && NORM && FINE) {
-          const Bins bins = first_bins(xa[u], ha[u], A.topk_key, anchor);
+          const Bins bins = first_bins(xa[u], ha[u], A.topk_key, anchor & kAnchorBits);
 #pragma unroll
           for (int i = 0; i < 4; ++i)
             if (HISTA && (uint32_t)i < nv[u]) atomicAdd(&hA[bins.bin[i]], 1u);
-          if (STREAM && T.codes) store_codes(T, base, (cd.len + 3) / 4 * 16, e[u] * 4, bins.codes);
+          if (STREAM && T.codes && !(anchor & kUncoded)) store_codes(T, base, (cd.len + 3) / 4 * 16, e[u] * 4, bins.codes);
         }
       }
     }

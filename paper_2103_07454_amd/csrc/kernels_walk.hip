@@ -37,7 +37,7 @@ __device__ __forceinline__ Quad taken(const Quad& q) {
 // What the walk has to know of a worker; lane i of a wavefront holds the i-th worker's.
 struct Marks { uint32_t f, thr, cut, place, anchor; };   // f: see below; Top-K: threshold key, last element that wins a tie, place in
                                                  // the message of the first winner of this wavefront's group, anchor of its key codes
-constexpr uint32_t kCode = 3u, kLeftFilled = 4u, kRightFilled = 8u, kSpike = 16u, kLed = 32u;
+constexpr uint32_t kCode = 3u, kLeftFilled = 4u, kRightFilled = 8u, kSpike = 16u, kLed = 32u, kCoded = 64u;
 constexpr int kCountShift = 8;                   // and from bit 8 on the winners in the group
 
 // RESET (with TOPK; the whole ring in one part): an event resets the sender's xhat to x while the mailboxes take the sent
@@ -86,7 +86,11 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
       const uint32_t s = worker(i), seg = s * T.L + layer, code = T.fired[seg];
       m.f = code | (T.valid_l[seg] ? kLeftFilled : 0u) | (T.valid_r[seg] ? kRightFilled : 0u);
       if (!GRADBUF && has_spike(A, k_iter, s)) m.f |= kSpike;
-      if (HISTA) m.anchor = T.anchor[seg];
+      if (HISTA) {
+        m.anchor = T.anchor[seg];
+        if (T.codes && !(m.anchor & kUncoded)) m.f |= kCoded;
+        m.anchor &= kAnchorBits;
+      }
       if (is_led(T, A, s)) m.f |= kLed;
       else if (TOPK && code == 2) {
         m.thr = T.sel_prefix[seg];
@@ -282,7 +286,7 @@ __global__ __launch_bounds__(64 * W) void k_update_walk(Tables T, StepArgs A) {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
           atomicAdd(&hist[(uint32_t)q < nv ? (i & 1u) * kFirstBins + bins.bin[q] : 2 * kFirstBins], 1u);
-        if (T.codes) store_codes(T, (size_t)r * T.Npad + off, nb, byte, bins.codes);
+        if (f & kCoded) store_codes(T, (size_t)r * T.Npad + off, nb, byte, bins.codes);
       }
       if (!RESET) el = ec;
       ec = en;

@@ -44,7 +44,7 @@ __device__ __forceinline__ HistAt first_hist(const Tables& T, uint32_t layer, ui
 __device__ __forceinline__ uint32_t bin_begin(uint32_t bin, uint32_t anchor, uint32_t* left) {
   const uint32_t a = anchor / kPerCoarse;
   *left = bin >= a && bin < a + kFineBins ? kFineBits : kCoarseBits;
-  return bin < a ? bin << kCoarseBits : bin < a + kFineBins ? (bin - a + anchor) << kFineBits
+  return bin < a ? bin << kCoarseBits : bin < a + kFineBins ? (bin - a + (anchor & kAnchorBits)) << kFineBits
                                                           : (bin - (kFineBins - kFineBins / kPerCoarse)) << kCoarseBits;
 }
 // Codes of four elements at bytes `byte` .. of a window of `bytes` bytes of an arena that starts at element `first` of it.
