@@ -207,16 +207,18 @@ def main():
     f_topk = float((st["events_topk_rl"].astype(np.float64) * numel[None, :]).sum() / (elems * args.steps))
     # rings that stream from memory, with ordinary delivery: the update pass walks the ring (where xhat is reset at events it
     # reads the mailboxes too, as the pass of the other rings does)
-    streams = 20 * w.P * evg.padded_numel(w.layer_numel) > (128 << 20) and not args.delivery_delay
-    # ... and so do the parts of the ring in which cached rings are updated; both leave a key code for each element of a Top-K
-    # ring, a byte, from which the selection is made
-    parts = not streams and not args.delivery_delay and not (args.xhat_reset and w.topk_ppm)
+    beyond_cache = 20 * w.P * evg.padded_numel(w.layer_numel) > (128 << 20)
+    streams = beyond_cache and not args.delivery_delay
+    # ... and so do the parts of the ring in which cached rings are updated (Top-K: with tensors of at most 327 680 elements)
+    parts = not beyond_cache and not args.delivery_delay and not (w.topk_ppm and (args.xhat_reset or max(w.layer_numel) > 327_680))
     walks = (streams and not args.xhat_reset) or parts
-    codes = 1 if w.topk_ppm else 0
+    # a streaming Top-K ring, and those parts, leave a key code for each element, a byte, from which the selection is made
+    codes = 1 if w.topk_ppm and (beyond_cache or parts) else 0
     if walks:
         step_bytes_per_elem = (20 if w.momentum != 0.0 else 12) + 8 * f_full + codes + f_topk + 20 * rho * f_topk
     else:
-        step_bytes_per_elem = (28 if w.momentum != 0.0 else 20) + 16 * f_full + 8 * f_topk + 28 * rho * f_topk
+        step_bytes_per_elem = (28 if w.momentum != 0.0 else 20) + 16 * f_full + (codes + f_topk if codes else 8 * f_topk) \
+            + 28 * rho * f_topk
     out = {
         "metric": "param_elements_per_s_fused_trigger_consensus_update",
         "value": elems * args.steps / dt,
@@ -247,7 +249,7 @@ def main():
     if phases:
         ms_upd, n_upd = phases["update"]
         avg_ms = ms_upd / max(1, n_upd)
-        per_elem = (UPDATE_BYTES_PER_ELEM_WALK + 8 * f_full + codes if walks else UPDATE_BYTES_PER_ELEM) \
+        per_elem = (UPDATE_BYTES_PER_ELEM_WALK + 8 * f_full if walks else UPDATE_BYTES_PER_ELEM) + codes \
             + UPDATE_TOPK_BYTES_PER_FIRED_ELEM_PER_RHO * rho * f_topk
         if w.momentum == 0.0:
             per_elem -= 8          # plain SGD: no velocity read or write
@@ -301,7 +303,7 @@ def main():
         out["phase_ms_per_step"] = {p: ms / max(1, args.steps) for p, (ms, n) in phases.items()}
         # the other HBM-bound phases against the same peak, on their share of the lower-bound bytes:
         # the Top-K selection makes one pass over the key codes of fired tensors (1 B; 8, over x and xhat, where there are none)
-        alg = {"topk_select": (1 if walks else 8) * f_topk}
+        alg = {"topk_select": (1 if codes else 8) * f_topk}
         out["phase_frac_of_hbm_peak"] = {
             p: b * elems / (phases[p][0] / max(1, args.steps) * 1e-3) / 1e9 / HBM_PEAK_GBS
             for p, b in alg.items() if phases[p][0] > 0 and b > 0}

@@ -125,3 +125,48 @@ def test_blobs_between_streaming_and_cached_rings(evg, written_by):
     for r in [again] + rings:
         for name in ARENAS:
             assert np.array_equal(a.state(name), r.state(name)), name
+
+
+def _not_staged(evg, oracle_mod, sizes, P, iters, given=None, **kw):
+    """What evg_stats counts in each iteration of a run that agrees with the oracle: chunks of tensors of more than 256 elements whose
+    selection read all keys instead of going by codes."""
+    import torch
+    w = _workload(P, sizes, iters, decay=1.0, thr_mode=inputs.THR_FIXED, thr_fixed=0.0, **kw)
+    x0 = inputs.replicate(w.x0(), P)
+    more = dict(grad_mode=1, lr=0.5, momentum=0.0) if given is not None else {}
+    ring = evg.Ring.from_workload(w, x0, mailbox_fill=0.0, **more)
+    orc = oracle_mod.Oracle.from_workload(w, x0, **more)
+    counts = [0]
+    for k in range(iters):
+        g = None if given is None else given(k, w.N)
+        ring.step(k, None if g is None else torch.from_numpy(ring.layout.pad(g)).cuda())
+        orc.step(k, grad=g)
+        counts.append(ring.stats()["chunks_not_staged"])
+        for mine, its in zip(ring.message_hashes(), orc.message_hashes()):
+            assert np.array_equal(mine, its), k
+    for name in ("x", "xhat"):
+        assert np.array_equal(ring.state(name), orc.state(name)), name
+    return np.diff(counts)
+
+
+@pytest.mark.parametrize("sizes,kw", [([300, 4000, 20_000, 100_000], dict(momentum=0.0)), ([257, 320_000], dict(topk_ppm=10_000)),
+                                      ([256, 17], dict())], ids=["small", "longest", "wavefront"])
+def test_selections_go_by_codes(evg, oracle_mod, sizes, kw):
+    """Only a tensor's first Top-K message is told from all of its keys; later ones go by the codes and counts of the update pass."""
+    n = _not_staged(evg, oracle_mod, sizes, 3, 10, **kw)
+    chunks = 3 * sum(-(-s // 2048) for s in sizes if s > 256)
+    assert n.tolist() == [0, chunks] + [0] * 8
+
+
+# Drifts of one size: in half of the elements, more keys than the list holds have the threshold's code, and all keys are read; in a
+# twentieth, and with a share below that, more ties than a wavefront sorts out, from the codes all the same
+@pytest.mark.parametrize("every,ppm,lists", [(2, 100_000, False), (20, 20_000, True)])
+def test_more_keys_of_a_code_than_the_list_holds(evg, oracle_mod, every, ppm, lists):
+    sizes = [30_000]
+
+    def given(k, N):
+        g = inputs.random_grads(3, N, 70 + k, 1e-3)
+        g[:, (7 * k) % every::every] = 64.0
+        return g
+    n = _not_staged(evg, oracle_mod, sizes, 3, 8, given, topk_ppm=ppm)
+    assert n[:2].tolist() == [0, 45] and ((n[3:] == 0).all() if lists else (n[3:] > 0).any()), n
