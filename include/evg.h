@@ -180,7 +180,8 @@ typedef struct {
                                ends of tensors of a few elements.  In cached rings with ordinary delivery
                                and tensors of at most 327 680 elements: those of tensors of more than 256
                                whose selection went by x and xhat as a whole (a first Top-K message, massive
-                               ties, a threshold that has moved by more than an octave) */
+                               ties, a threshold that has moved by more than an octave down or
+                               three quarters of one up) */
   uint64_t library_bytes;   /* device memory the library holds for this context besides the
                                caller's five arenas (tables, Top-K histograms,
                                staging and message buffers); for evg_init_static the part

@@ -14,12 +14,12 @@ constexpr int kFirstBins = 1280;       // the first (see first_bins)
 constexpr uint32_t kCoarseBits = 21, kFineBits = 17;                  // bits of a key below its coarse and fine bins
 constexpr uint32_t kPlainBits = 20;                                   // below the bins of rings without anchors
 constexpr uint32_t kPerCoarse = 1u << (kCoarseBits - kFineBits);      // fine bins of a coarse one
-constexpr uint32_t kFineBins = 128;                                   // fine bins
-constexpr uint32_t kCodeStride = 256;                                 // ... in eight copies, each of those codes and of all above
+constexpr uint32_t kFineBins = 128;
 constexpr uint32_t kHistCopies = 8;    // of the first histogram of a tensor that is most of a ring (Tables::long_layer)
 constexpr uint32_t kHistCopiesFrom = 131072;      // elements of such a tensor at least
 constexpr uint32_t kNoLayer = 0xFFFFFFFFu;
-constexpr uint32_t kFirstCode = 64, kCodeBins = 128;                  // key codes that are counted where there are no such histograms
+constexpr uint32_t kFirstCode = 64, kCodeBins = 128;                  // key codes that are counted where there are no such histograms,
+constexpr uint32_t kCodeStride = 256;                                 // in eight copies, each of those codes and of all above
 constexpr int kLastBins = 1024;        // the last takes what is left, 6 or 10 bits
 constexpr uint32_t kStageCap = 2048;   // staged keys of a chunk at most
 // Threshold key that no key reaches (they have 31 bits).  A selection ends with it where it sees that it would not find exactly K
@@ -177,7 +177,7 @@ hipError_t launch_update(const Tables& t, const StepArgs& a, uint32_t dist, uint
                          int norm, hipStream_t s);
 // norm as above; rings for which the host sets StepArgs::walk
 hipError_t launch_walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t grad_mode, int norm, hipStream_t s);
-// norm: 1 or 2
+// norm: 1, 2 or, with Top-K, 1 or 3
 hipError_t launch_part(const Tables& t, const StepArgs& a, const PartTables& p, uint32_t dist, uint32_t grad_mode, int norm, hipStream_t s);
 hipError_t launch_trigger(const Tables& t, const StepArgs& a, hipStream_t s);
 hipError_t launch_copy(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
@@ -188,8 +188,10 @@ hipError_t launch_topk_select(const Tables& t, const StepArgs& a, uint32_t chunk
 hipError_t launch_topk_count_all(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
 // The tensors by size, the `longer` of more than 256 elements first; the longest's elements, at most kChooseMost.
 struct ChooseTables { const uint32_t* order; uint32_t longer, longest; };
-// Longer ones are too much for one workgroup (us a step, in many launches / one workgroup a tensor, 3 and 8 workers): perceptrons
-// of 102 000 elements 45 / 25 and 45 / 29, 251 000 47 / 39 and 57 / 47, 401 000 50 / 55 and 72 / 69, 627 000 59 / 76 and 105 / 112.
+// Longer ones are too much for one workgroup.  Steps in us, in many launches / one workgroup a tensor, rings of 3, 5 and 8 perceptrons whose
+// longest tensor has 141 000 elements 35.2 / 26.5, 37.5 / 28.9, 39.6 / 30.6; 251 000 37.9 / 38.1, 41.7 / 40.2, 47.0 / 44.1; 327 000 39.0 /
+// 44.2, 45.0 / 48.8, 53.5 / 52.0; 408 000 41.9 / 52.3, 47.4 / 56.8, 58.5 / 62.1; with given gradients 251 000 35.9 / 30.4, 39.4 / 33.1, 45.1 /
+// 38.4; 327 000 37.0 / 34.2, 43.1 / 40.1, 50.9 / 44.1; 408 000 40.2 / 40.5, 45.0 / 46.0, 56.7 / 53.6.  A compromise of these.
 constexpr uint32_t kChooseMost = 327680;
 hipError_t launch_topk_choose(const Tables& t, const StepArgs& a, const ChooseTables& c, hipStream_t s);
 hipError_t launch_topk_apply(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);

@@ -6,7 +6,7 @@
 // expected (one addition a lane and workgroup, where the histogram of all keys took a pass of its own through LDS).  The counts
 // name the code of the K-th largest key; the workgroup goes through the codes once, lists what has that one (some 0.4 % of the
 // tensor), fetches those keys alone and finds the threshold among them.  Where the counts do not reach it (a tensor's first
-// message; it has moved by more than an octave) the keys are read from the arenas, in four passes.
+// message; it has moved by more than an octave down or three quarters of one up) the keys are read from the arenas, in four passes.
 // Tensors of at most 256 elements are a wavefront's work.
 //
 // Bound by latency: some ten dependent steps of a workgroup (8 ResNet-20 workers 15 us, its longest tensors 36 864 elements; 24 000
@@ -63,7 +63,7 @@ __device__ __forceinline__ bool pick(Chosen& s, uint32_t rem) {
 // What the selection leaves of a tensor for the update pass.
 struct Threshold { uint32_t key, ties; bool ok; };
 
-// Running totals of winners before every group of 256 elements, for message_place; s.list[g] holds group g's keys above (low half)
+// Running totals of winners before every group of 256 elements, for message_place; groups[g] holds group g's keys above (low half)
 // and equal to (high half) the threshold.  Returns the tensor's totals.
 __device__ __forceinline__ uint2 place_groups(const Tables& T, Chosen& s, uint32_t r, const LayerDesc& ld, const uint32_t* groups) {
   const uint32_t G = T.SW * 4, ngroups = (ld.numel + 255) / 256, first = r * T.C + ld.chunk0;

@@ -6,8 +6,8 @@
 // Streaming rings with ordinary delivery are updated by kernels_walk.hip, cached rings by kernels_parts.hip; k_update here serves
 // the others: cached Top-K rings with tensors too long for k_topk_choose, norm passes of their own, delayed delivery, xhat
 // reset at events.  One workgroup (256 threads, one float4 per thread) owns one 1024-element sweep of one chunk of one
-// worker; where the pass also builds the histogram of a Top-K ring, two.  With given gradients and copies of x it has 96 vector
-// registers, the most for five wavefronts a SIMD (one more: 5 perceptrons of 479 000 elements 53.5 -> 56.7 us a step).
+// worker; where the pass also builds the histogram of a Top-K ring, two.  With given gradients and copies of x it has 95 vector
+// registers; more than 96 are too many for five wavefronts a SIMD (97: 5 perceptrons of 479 000 elements 53.5 -> 56.7 us a step).
 #include "message_device.h"
 #include "trigger_device.h"
 

@@ -12,9 +12,10 @@
 // 6.3, and this pass writes about as much as it reads, or more.  Steps before (a pass per worker that read
 // the neighbours through the L2, and a copy kernel) -> now: 16 ResNet-18 workers with whole sends 925 -> 868 us, 32 with plain
 // SGD 1569 -> 1222, 7 of width 23 65.8 -> 54.0, 8 ResNet-50 workers of half width 343 -> 287.
-// Residency: whole sends 76 - 93 vector registers and 2 KB of LDS, 5 or 6 wavefronts a SIMD; Top-K 104 - 115 and 20 or 24 KB for
-// eight wavefronts, 4 a SIMD; with mailboxes read (RESET) 123 - 135, 4 or 3.  All use 106 scalar registers and spill
-// some tens of them to vector lanes: what more a Top-K walk keeps per worker costs 1 - 2 % at once.
+// Residency: whole sends 76 - 93 vector registers and 2 KB of LDS, 5 or 6 wavefronts a SIMD; Top-K 106 - 126 and 20 or 24 KB for
+// eight wavefronts, 4 a SIMD; with mailboxes read (RESET) 130 - 146, 3.  Most use 106 scalar registers and spill
+// some tens of them to vector lanes: what more a Top-K walk keeps per worker costs 1 - 5 % at once, so that the number of winners in a
+// group and whether codes are wanted ride with the other marks.
 #include "message_device.h"
 #include "quad_device.h"
 #include "trigger_device.h"

@@ -9,9 +9,9 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// The first pass's bins, by ascending keys: a quarter of an octave each (bits 30..21), but a sixty-fourth (bits 30..17) in the four
+// The first pass's bins, by ascending keys: a quarter of an octave each (bits 30..21), but a sixty-fourth (bits 30..17) in the two
 // octaves from the anchor on, bits 30..17 of a key (a multiple of 16), in whose middle the threshold is expected.  A bin holds some
-// 0.4 % of a tensor's keys there; with an eighth of an octave everywhere, as it was before, 3 to 12 %.
+// 0.4 % of a tensor's keys there; with an eighth of an octave everywhere (rings without anchors) 3 to 12 %.
 // (Four keys at a time, two in a register, in 16-bit arithmetic: 25 instructions instead of 40.)
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 struct Bins { uint32_t bin[4], codes; };     // codes: see Tables::codes
