@@ -1025,18 +1025,29 @@ evg_status evg_message(evg_ctx* c, uint32_t r, uint32_t l, uint32_t* idx, float*
   }
   const uint64_t K = c->K[l];
   const size_t base = (size_t)r * t.Ktot + c->msg_off[l];
-  // (places of a message that nothing was sent for are left out)
-  std::unique_ptr<uint32_t[]> at(new (std::nothrow) uint32_t[K]);
-  std::unique_ptr<float[]> values(val ? new (std::nothrow) float[K] : nullptr);
-  if (!at || (val && !values)) return fail(EVG_ERR_OOM, "host allocation failed");
-  HIP_TRY(hipMemcpy(at.get(), t.msg_idx + base, K * 4, hipMemcpyDeviceToHost));
-  if (val) HIP_TRY(hipMemcpy(values.get(), t.msg_val + base, K * 4, hipMemcpyDeviceToHost));
+  if (!t.codes) {
+    const uint64_t n = K < cap ? K : cap;
+    if (idx && n) HIP_TRY(hipMemcpy(idx, t.msg_idx + base, n * 4, hipMemcpyDeviceToHost));
+    if (val && n) HIP_TRY(hipMemcpy(val, t.msg_val + base, n * 4, hipMemcpyDeviceToHost));
+    *count = K;
+    return EVG_OK;
+  }
+  // where keys are counted by their codes, places of a message that nothing was sent for are left out
+  constexpr uint64_t kBlock = 1 << 16;
+  std::unique_ptr<uint32_t[]> at(new (std::nothrow) uint32_t[kBlock]);
+  std::unique_ptr<float[]> values(new (std::nothrow) float[kBlock]);
+  if (!at || !values) return fail(EVG_ERR_OOM, "host allocation failed");
   uint64_t n = 0;
-  for (uint64_t i = 0; i < K; ++i) {
-    if (at[i] == kNoEntry) continue;
-    if (idx && n < cap) idx[n] = at[i];
-    if (val && n < cap) val[n] = values[i];
-    ++n;
+  for (uint64_t i0 = 0; i0 < K; i0 += kBlock) {
+    const uint64_t m = std::min(kBlock, K - i0);
+    HIP_TRY(hipMemcpy(at.get(), t.msg_idx + base + i0, m * 4, hipMemcpyDeviceToHost));
+    if (val && n < cap) HIP_TRY(hipMemcpy(values.get(), t.msg_val + base + i0, m * 4, hipMemcpyDeviceToHost));
+    for (uint64_t i = 0; i < m; ++i) {
+      if (at[i] == kNoEntry) continue;
+      if (idx && n < cap) idx[n] = at[i];
+      if (val && n < cap) val[n] = values[i];
+      ++n;
+    }
   }
   *count = n;
   return EVG_OK;
