@@ -4,6 +4,7 @@ barrier and additions is read; on the GPU the counts are compared with those of 
 have nothing to do and reach their end early), of some and of all, with drawn and given gradients and parts of 1, 2 and 4 workers."""
 import os
 import re
+import shutil
 import subprocess
 
 import numpy as np
@@ -14,6 +15,7 @@ from paper_2103_07454_amd import build, inputs
 HIST_BINS, COPY, BINS, FIRST_CODE, FINE_BITS = 2048, 256, 128, 64, 17      # of evg_internal.h
 
 
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="reads what hipcc compiles")
 def test_counts_are_cleared_behind_a_barrier(tmp_path):
     asm = tmp_path / "parts.s"
     subprocess.run(["hipcc", *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, "kernels_parts.hip"), "-o", asm],
