@@ -8,7 +8,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libevg.so")
-SOURCES = ["evg_api.hip", "kernels_update.hip", "kernels_walk.hip", "kernels_parts.hip", "kernels_trigger.hip", "kernels_topk.hip", "kernels_choose.hip"]
+SOURCES = ["evg_api.hip", "kernels_update.hip", "kernels_walk.hip", "kernels_parts.hip", "kernels_ring.hip", "kernels_trigger.hip", "kernels_topk.hip", "kernels_choose.hip"]
 
 # -ffp-contract=off: every fused multiply-add in the kernels is written out, so
 #   results do not depend on what the compiler decides to contract.
@@ -31,7 +31,7 @@ def build_library(verbose: bool = False) -> str:
         subprocess.run(cmd, check=True)
         return obj
 
-    with ThreadPoolExecutor(max_workers=7) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
         objs = list(ex.map(compile_one, SOURCES))
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     if verbose:

@@ -281,12 +281,12 @@ struct TableSum {
 
 // Bytes of library-owned device tables a configuration needs: the same list as the allocations of init_common.
 static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uint64_t hist_len, uint64_t Npad,
-                            uint64_t ktot, bool topk, bool norm_diff, bool pull, bool one_launch, uint64_t windows, uint64_t parts, bool codes, uint64_t hists) {
+                            uint64_t ktot, bool topk, bool norm_diff, bool pull, bool one_launch, uint64_t windows, uint64_t parts, bool codes, uint64_t hists, uint64_t fine) {
   const uint64_t S = P * L, PC = P * C;
   TableSum t;
   t.add(C, sizeof(ChunkDesc)); t.add(L, sizeof(LayerDesc));
-  t.add(PC * SW, 8);
-  if (norm_diff) { t.add(PC * SW, 8); t.add(S, 8); }
+  t.add(PC * SW * fine, 8);
+  if (norm_diff) { t.add(PC * SW * fine, 8); t.add(S, 8); }
   t.add(S, 4); t.add(S, 4); t.add(S, 4); t.add(S, 4);            // delta, last_norm, delta_before, last_event
   t.add(S, 1); t.add(S, 1); t.add(S, 1); t.add(S, 1);            // valid_l, valid_r, fired, near_tie
   t.add(S, 4); t.add(S, 4); t.add(S, 4); t.add(S, 4);            // ev_full, ev_topk, near_cnt, nonfinite_cnt
@@ -294,7 +294,7 @@ static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uin
   t.add(1, 4); t.add(1, sizeof(IterState)); t.add(kDecayTable, 8);
   if (pull) t.add(2 * P * Npad, 4);                              // xsnap
   if (one_launch) {                                              // the second set of what the trigger tests read
-    t.add(PC * SW, 8); t.add(S, 4); t.add(S, 4);
+    t.add(PC * SW * fine, 8); t.add(S, 4); t.add(S, 4);
     if (norm_diff) t.add(S, 8);
     t.add(windows * parts, sizeof(PartClock));
   }
@@ -345,6 +345,35 @@ static uint64_t admitted_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, 
     t.add(P * ktot, 4); t.add(P * ktot, 4); t.add(S, 8); t.add(S, 8);
   }
   return t.total;
+}
+
+// The shape of the workgroups of kernels_ring.hip for a ring that is cached by its size (`windows` of 1024 elements), groups = 0: it goes by
+// kernels_parts.hip, like the larger ones that are cached because that is asked for.
+// With few float4s in the ring a thread has one of them and windows are short, so that there are workgroups; with more, two, as
+// the sums that the tests read and the threads get many.  Four workers or fewer with long networks: whole sweeps.  A workgroup of more than twelve wavefronts leaves
+// a CU too few of them beside it unless it has much to load.  Kernels_parts.hip / groups and quads 1 1 / 2 1 / 2 2 / 4 2, us a step, normal
+// gradients: perceptrons of 102 windows on 4 workers 6.2 / 5.7 / 5.4 / 5.6 / 6.2, 39 on 4 5.1 / 4.5 / 4.7 / 4.9 / 5.4, 506 on 6 22.0 / 20.6 / 20.2 / 17.3 /
+// 17.9; ResNet-20 of 314 on 3 8.8 / 7.4 / 7.9 / 7.8 / 8.5, on 8 14.5 / 13.6 / 16.5 / 12.6 / 15.6, on 16 30.1 / 27.2 / - / 26.5 / -, of 186 on 15 13.7 / 16.3 / - / 15.3 / -;
+// ResNet-18 of 729 on 4 16.9 / 18.2 / 18.6 / 17.8 / 16.8; more workers have one float4 each of several: 120 windows on 24 12.7 and 15.4.  Top-K, kernels_parts.hip / 1 2 / 2 2:
+// ResNet-20 of 314 windows on 8 33.6 / 32.4 / 32.3, on 16 67.3 / 60.1 / 63.9, of 426 on 15 86 / 76 / 83; perceptrons of 129 on 11 32.4 / - / 34.9, of
+// 237 on 10 44.0 / 49.2 / 45.8; ResNet-18 of 729 on 4 39.7 / - / 41.4, ResNet-20 of 509 on 4 with given gradients 27.8 / - / 25.8.
+static void ring_shape(uint32_t P, uint64_t windows, uint32_t longest, bool topk, bool tests, bool given, uint32_t* groups, uint32_t* quads) {
+  *groups = *quads = 0;
+  const uint64_t units = windows * P;
+  if (P > kRingMost || (P > 12 && units < (given && !topk ? 800 : 4000))) return;
+  if (topk) {
+    if (units < 1700 || (longest > 200000 && P > 8) || (P <= 4 && !given)) return;
+    *groups = P > 12 ? 1 : 2;
+    *quads = 2;
+  } else if (P <= 4 && windows >= 400) {
+    *groups = 4;
+    *quads = 2;
+  } else if (units >= 1300) {
+    *groups = *quads = 2;
+  } else {
+    *groups = tests && longest > 65536 && P <= 8 ? 2 : 1;
+    *quads = 1;
+  }
 }
 
 static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_stream, bool use_scratch) {
@@ -483,7 +512,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   // eighth of a ring, ResNet-18 of width 16 to 64 on 8 and 16 workers, the two longest: within 0.5 %.
   std::vector<uint32_t> long_layers;
   uint32_t ring_part = 0;
-  uint32_t longest = 0;
+  uint32_t longest = 0, groups = 0, quads = 0, fine = 1;
   for (const LayerDesc& d : layers) longest = std::max(longest, d.numel);
   auto cut_chunks = [&](bool on_lines) {
     chunks.clear();
@@ -519,16 +548,25 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     // Longer parts read less of other parts' workers and run fewer tests twice, shorter ones are more workgroups.  Parts
     // of 2 / 4 / 8, us a step: 102 windows on 4 workers 5.8 / 6.8 / -, 120 on 8 7.2 / 7.7 / 11.2, on 24 12.7 / 12.5 / 15.6; 314 on
     // 8 15.7 / 14.3 / 16.6, on 12 25.7 / 22.6 / 19.2, on 16 34.1 / 33.4 / 30.7; 438 on 8 24.9 / 21.8 / 18.4, on 16 53.3 / 48.9 / 49.0.
+    groups = quads = 0;
+    fine = 1;                      // (a window's sum is one of its sweep's)
+    if (in_parts && small_ring) ring_shape(P, windows, longest, cfg->topk_ppm != 0, one_launch, cfg->grad_mode == EVG_GRAD_BUFFER, &groups, &quads);
+    if (groups) {
+      fine = 4 / groups;
+      ring_windows = 0;
+      for (const ChunkDesc& cd : chunks) ring_windows += (cd.len + 256 * groups - 1) / (256 * groups);
+    }
     const uint64_t units = ring_windows * P;
     ring_part = std::min<uint32_t>(P, units < 900 ? 2 : units < 3400 ? 4 : kPartMost);
     // Top-K, parts of 1 / 2 / 4: 28 windows on 8 workers 19.9 / 21.2 / 23.9, 120 on 5 20.8 / 21.3 / 24.0, 160 on 12 38.2 / 36.8 / 37.0, 314 on
     // 8 35.2 / 32.8 / 32.6, on 24 106 / 103 / 98, 438 on 12 78 / 78 / 69.
     if (cfg->topk_ppm) ring_part = std::min<uint32_t>(P, units < 900 ? 1 : units < 1600 ? 2 : 4);
     else if (in_parts && !one_launch) ring_part = std::min<uint32_t>(ring_part, 4);
+    if (groups) ring_part = P;
     need = table_bytes(P, L, chunks.size(), SW, hist_len, Npad, ktot, cfg->topk_ppm != 0,
                        cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF, pull && !(in_parts && ring_part == P), one_launch,
                        in_parts ? ring_windows : 0, (P + ring_part - 1) / ring_part, codes && (choose || !c->cached),
-                       (uint64_t)P * L + (kHistCopies - 1) * P * long_layers.size());
+                       (uint64_t)P * L + (kHistCopies - 1) * P * long_layers.size(), fine);
     return (uint64_t)P * chunks.size() * (SW + 1) <= 0xFFFFFFF0ull && (uint64_t)P * ktot <= 0xFFFFFFF0ull &&
            !(use_scratch && need > kScratchBytes);
   };
@@ -592,6 +630,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   Tables& t = c->t;
   t.P = P; t.L = L; t.C = (uint32_t)C; t.S = (uint32_t)S;
   t.SW = SW;
+  t.fine = fine;
   t.hist_len = hist_len;
   t.Ktot = (uint32_t)ktot;
   t.Npad = Npad;
@@ -658,9 +697,9 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   HIP_OR_FREE(hipMemcpyAsync(d_layers, layers.data(), L * sizeof(LayerDesc), hipMemcpyHostToDevice, c->stream));
   t.chunks = d_chunks;
   t.layers = d_layers;
-  TRY_OR_FREE(c->dalloc(&t.partials, P * C * t.SW, true));
+  TRY_OR_FREE(c->dalloc(&t.partials, P * C * t.SW * fine, true));
   if (cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF) {
-    TRY_OR_FREE(c->dalloc(&t.partials_hat, P * C * t.SW, true));
+    TRY_OR_FREE(c->dalloc(&t.partials_hat, P * C * t.SW * fine, true));
     TRY_OR_FREE(c->dalloc(&t.xhat_sq, S, true));
   }
   TRY_OR_FREE(c->dalloc(&t.delta, S, false));
@@ -695,25 +734,29 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   std::vector<WindowDesc> ring;
   std::vector<uint32_t> order;
   if (in_parts) {
+    const uint32_t length = kSweep / fine, sums = SW * fine;
     for (size_t i = 0; i < chunks.size(); ++i)
-      for (uint32_t u = 0; u * kSweep < chunks[i].len; ++u) {
+      for (uint32_t u = 0; u * length < chunks[i].len; ++u) {
         const ChunkDesc& cd = chunks[i];
         const LayerDesc& d = layers[cd.layer];
-        ring.push_back({cd.off + u * kSweep, std::min<uint32_t>(kSweep, cd.len - u * kSweep), cd.layer, cd.j0 + u * kSweep,
-                        (uint32_t)i * SW + u, d.chunk0 * SW, d.nchunks * SW, i == d.chunk0 && u == 0 ? 1u : 0u, d.sig_base});
+        ring.push_back({cd.off + u * length, std::min<uint32_t>(length, cd.len - u * length), cd.layer, cd.j0 + u * length,
+                        (uint32_t)i * sums + u, d.chunk0 * sums, d.nchunks * sums, i == d.chunk0 && u == 0 ? 1u : 0u, d.sig_base,
+                        d.numel, d.K, d.msg_off, 0u});
       }
     WindowDesc* d_ring = nullptr;
     TRY_OR_FREE(c->dalloc(&d_ring, ring.size(), false));
     HIP_OR_FREE(hipMemcpyAsync(d_ring, ring.data(), ring.size() * sizeof(WindowDesc), hipMemcpyHostToDevice, c->stream));
     c->parts.windows = d_ring;
     c->parts.count = (uint32_t)ring.size();
+    c->parts.groups = groups;
+    c->parts.quads = quads;
     c->part = ring_part;
     c->parts.set[0] = c->parts.set[1] = {t.partials, t.xhat_sq, t.delta, t.last_event};
   }
   if (one_launch) {
     TRY_OR_FREE(c->dalloc(&c->parts.clocks, ring.size() * ((P + ring_part - 1) / ring_part), true));
     PartTables::Set& other = c->parts.set[1];
-    TRY_OR_FREE(c->dalloc(&other.partials, P * C * t.SW, true));
+    TRY_OR_FREE(c->dalloc(&other.partials, P * C * t.SW * fine, true));
     TRY_OR_FREE(c->dalloc(&other.delta, S, true));
     TRY_OR_FREE(c->dalloc(&other.last_event, S, true));
     if (cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF) TRY_OR_FREE(c->dalloc(&other.xhat_sq, S, true));
@@ -866,6 +909,7 @@ static evg_status enqueue_step(evg_ctx* c, const StepArgs& args, bool timed) {
     Phase ph(c, EVG_PH_UPDATE);
     const int norm = !fused ? 0 : !norm_diff ? 1 : g.topk_ppm ? 3 : 2;
     HIP_TRY(a.walk          ? launch_walk(t, a, g.synth.dist, g.grad_mode, norm, c->stream)
+            : c->parts.groups ? launch_ring(t, a, c->parts, g.synth.dist, g.grad_mode, norm, c->stream)
             : c->parts.count ? launch_part(t, a, c->parts, g.synth.dist, g.grad_mode, norm, c->stream)
                             : launch_update(t, a, g.synth.dist, g.grad_mode, norm, c->stream));
     if ((st = ph.end()) != EVG_OK) return st;
@@ -1153,7 +1197,20 @@ evg_status evg_state_export(evg_ctx* c, void* blob, uint64_t capacity) {
   char* out = static_cast<char*>(blob);
   std::memcpy(out, &h, sizeof h);
   out += sizeof h;
+  const Tables& t = c->t;
   for (const Piece& p : state_pieces(c)) {
+    if (t.fine > 1 && (p.dev == t.partials || p.dev == t.partials_hat)) {      // blobs hold a sum a sweep
+      const size_t sweeps = p.bytes / 8;
+      std::unique_ptr<double[]> parts(new (std::nothrow) double[sweeps * t.fine]);
+      if (!parts) return fail(EVG_ERR_OOM, "host allocation failed");
+      HIP_TRY(hipMemcpy(parts.get(), p.dev, p.bytes * t.fine, hipMemcpyDeviceToHost));
+      for (size_t i = 0; i < sweeps; ++i, out += 8) {
+        double sum = 0.0;
+        for (uint32_t u = 0; u < t.fine; ++u) sum += parts[i * t.fine + u];
+        std::memcpy(out, &sum, 8);
+      }
+      continue;
+    }
     HIP_TRY(hipMemcpy(out, p.dev, p.bytes, hipMemcpyDeviceToHost));
     out += p.bytes;
   }
@@ -1210,7 +1267,7 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
   want.last_iter = got.last_iter;
   if (std::memcmp(&got, &want, sizeof got) != 0)
     return fail(EVG_ERR_INVALID, "blob was exported from a different configuration or version");
-  const size_t sum_count = (size_t)t.P * here;
+  const size_t sum_count = (size_t)t.P * here * t.fine;
   std::unique_ptr<double[]> moved(same_cut ? nullptr : new (std::nothrow) double[sum_count]);
   if (!same_cut && !moved) return fail(EVG_ERR_OOM, "host allocation failed");
   const size_t clock_count = c->one_launch ? (size_t)c->parts.count * ((t.P + c->part - 1) / c->part) : 0;
@@ -1247,13 +1304,13 @@ evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size) {
             double v;
             std::memcpy(&v, in, 8);
             in += 8;
-            to[std::min(i, used - 1)] += v;
+            to[std::min(i, used - 1) * t.fine] += v;
           }
-          to += sums_of(l, off, t.SW, c->on_lines);
+          to += sums_of(l, off, t.SW, c->on_lines) * t.fine;
           off += pad_to(c->numel[l], 4);
         }
       }
-      HIP_TRY(hipMemcpyAsync(p.dev, moved.get(), p.bytes, hipMemcpyHostToDevice, c->stream));
+      HIP_TRY(hipMemcpyAsync(p.dev, moved.get(), sum_count * 8, hipMemcpyHostToDevice, c->stream));
       HIP_TRY(hipStreamSynchronize(c->stream));        // `moved` is filled again
       continue;
     }

@@ -55,7 +55,7 @@ struct LayerDesc {
   double sig_base;   // sigma0 [/ sqrt(fan_in)]
 };
 
-// A window of kernels_parts.hip: up to 1024 elements of one tensor.
+// A window of kernels_ring.hip or kernels_parts.hip: up to 1024 elements of one tensor.
 struct WindowDesc {
   uint32_t off, len;   // start inside a worker's slice (multiple of 4), elements
   uint32_t layer, j0;  // tensor, start inside it
@@ -63,11 +63,14 @@ struct WindowDesc {
   uint32_t sum0, sums; // the tensor's partials
   uint32_t books;      // the tensor's first window
   double sig_base;     // sigma0 [/ sqrt(fan_in)]
+  uint32_t numel, K, msg_off, pad;     // of the tensor; its Top-K message (see LayerDesc)
 };
 constexpr uint32_t kPartMost = 8;      // workers of a part of the ring there
+constexpr uint32_t kRingMost = 16;     // workers of a ring whose windows are one workgroup's
 struct PartClock { uint32_t k, steps; };       // the next iteration, and the steps completed
 struct PartTables {
   const WindowDesc* windows; uint32_t count;
+  uint32_t groups, quads;  // kernels_ring.hip: groups of 256 elements in a window, float4s of a thread; 0: the ring goes by kernels_parts.hip
   PartClock* clocks;       // [count * parts]
   // What the trigger tests read and an event writes exists twice: step n (from 0) reads set n & 1 and writes the other.
   struct Set { double* partials; double* xhat_sq; float* delta; int32_t* last_event; } set[2];
@@ -92,9 +95,9 @@ struct Tables {
   float* xsnap;            // [2][P*Npad] or null: copies of x that the update pass of one iteration leaves
                            // for the next one, two in turn (cache-resident rings with ordinary
                            // delivery: the receivers then fetch what a neighbour sends, no copy kernel)
-  double* partials;        // [P*C*SW] per 1024-element sweep of a chunk: sum of squared drift, or
+  double* partials;        // [P*C*SW*fine] per 1024-element sweep of a chunk, or per part of it: sum of squared drift, or
                            // of squared x when the trigger compares norms
-  double* partials_hat;    // [P*C*SW] sum of squared xhat (norm-difference trigger only)
+  double* partials_hat;    // [P*C*SW*fine] sum of squared xhat (norm-difference trigger only)
   double* xhat_sq;         // [S] squared norm of what was last sent, kept as a scalar when whole
                            // tensors are sent (norm-difference trigger only)
   float* delta; float* last_norm; float* delta_before;
@@ -135,6 +138,7 @@ struct Tables {
   uint32_t decay_len;
   uint32_t P, L, C, S;
   uint32_t SW;             // 1024-element sweeps per chunk
+  uint32_t fine;           // sums of a sweep: 1, or where windows are shorter than sweeps (kernels_ring.hip) 2 or 4
   uint32_t hist_len;
   uint32_t Ktot;           // sum of K over tensors
   uint64_t Npad;
@@ -179,6 +183,8 @@ hipError_t launch_update(const Tables& t, const StepArgs& a, uint32_t dist, uint
 hipError_t launch_walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32_t grad_mode, int norm, hipStream_t s);
 // norm: 1, 2 or, with Top-K, 1 or 3
 hipError_t launch_part(const Tables& t, const StepArgs& a, const PartTables& p, uint32_t dist, uint32_t grad_mode, int norm, hipStream_t s);
+// the same, a workgroup to a window of the whole ring
+hipError_t launch_ring(const Tables& t, const StepArgs& a, const PartTables& p, uint32_t dist, uint32_t grad_mode, int norm, hipStream_t s);
 hipError_t launch_trigger(const Tables& t, const StepArgs& a, hipStream_t s);
 hipError_t launch_copy(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
 hipError_t launch_deliver(const Tables& t, uint32_t chunk_elems, hipStream_t s);

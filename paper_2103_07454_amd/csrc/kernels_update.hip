@@ -31,7 +31,7 @@ __global__ __launch_bounds__(kThreads) void k_norm(Tables T) {
     if (NORMDIFF) { square_acc(acc, xa, nv); square_acc(acc_hat, ha, nv); }
     else drift_acc(acc, xa, ha, nv);
   }
-  const size_t slot = ((size_t)r * T.C + c) * T.SW + sub;
+  const size_t slot = (((size_t)r * T.C + c) * T.SW + sub) * T.fine;
   const double total = block_sum(acc, ws);
   if (threadIdx.x == 0) T.partials_out[slot] = total;
   if (NORMDIFF) {

@@ -35,13 +35,13 @@ __device__ __forceinline__ void segment_sums(const Tables& T, const StepArgs& A,
                                              double* acc_hat_out, bool* hat_sums_out) {
   const uint32_t r = seg / T.L, l = seg % T.L;
   const LayerDesc ld = T.layers[l];
-  const double* part = T.partials + ((size_t)r * T.C + ld.chunk0) * T.SW;
-  const uint32_t np = ld.nchunks * T.SW;
+  const uint32_t sums = T.SW * T.fine, np = ld.nchunks * sums;
+  const double* part = T.partials + ((size_t)r * T.C + ld.chunk0) * sums;
   double acc_hat = 0.0;
   const double acc = wave_sum(ordered_lane_sum(part, np));
   const bool hat_sums = A.norm_src == 2 || (A.norm_src == 1 && T.last_event[seg] < 0);
   if (hat_sums) {
-    const double* ph = T.partials_hat + ((size_t)r * T.C + ld.chunk0) * T.SW;
+    const double* ph = T.partials_hat + ((size_t)r * T.C + ld.chunk0) * sums;
     acc_hat = wave_sum(ordered_lane_sum(ph, np));
   }
   *acc_out = acc;

@@ -1,0 +1,96 @@
+"""Cached rings of at most 16 workers are updated by one workgroup for each window of the whole ring; windows are of 256, 512
+or 1024 elements, and a thread has one float4 or two.  Checked against the oracle at the edges of groups, windows and chunks,
+for rings of 3 to 16 workers, by sizes that lead to each shape of a workgroup (evg_api.hip: ring_shape)."""
+import numpy as np
+import pytest
+
+from paper_2103_07454_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [255, 256, 257, 511, 513, 1023, 1025, 2047, 2049, 1, 4]
+
+
+@pytest.fixture(scope="module")
+def evg():
+    from paper_2103_07454_amd import evg as m
+    m.lib()
+    return m
+
+
+def _workload(P, sizes, **kw):
+    tensors = [inputs.TensorSpec(f"t{i}", (n,), 16 + i % 40, "weight") for i, n in enumerate(sizes)]
+    return inputs.Workload("ring", P, tensors, 7, sigma0=0.05, decay=0.9, seed=P, **kw)
+
+
+def _check(evg, oracle_mod, w, both=None, given=False):
+    import torch
+    from helpers import lockstep
+    both = both or {}
+    x0 = inputs.replicate(w.x0(), w.P)
+    ring = evg.Ring.from_workload(w, x0, mailbox_fill=float("nan"), grad_mode=int(given), **both)
+    orc = oracle_mod.Oracle.from_workload(w, x0, grad_mode=int(given), **both)
+    host = dev = None
+    if given:
+        def host(k):
+            return inputs.random_grads(w.P, w.N, 40 + k, 0.02)
+
+        def dev(k):
+            return torch.from_numpy(ring.layout.pad(host(k))).cuda()
+    norms = both.get("trigger_kind", 0)
+    rep = lockstep(ring, orc, w.iters, grads=host, gpu_grads=dev, sample_messages=3,
+                   norm_rtol=None if norms else 2e-7, norm_abs_of_x=2.5e-7 if norms else None)
+    assert rep["rel"]["x"] <= 1e-5 and (norms or all(rep["bitwise"].values())), rep
+
+
+# one float4 a thread (short windows; with a tensor of more than 65 536 elements longer ones), two, whole sweeps
+WHOLE = [(3, EDGES), (13, EDGES * 6), (5, EDGES + [65537, 131072]), (8, EDGES * 10), (12, EDGES * 8), (16, [1023] * 200 + EDGES * 4),
+         (3, EDGES * 25), (4, EDGES * 25), (6, EDGES * 10 + [131073])]
+
+
+@pytest.mark.parametrize("P,sizes", WHOLE, ids=[f"{P}x{len(s)}" for P, s in WHOLE])
+@pytest.mark.parametrize("kw", [dict(spike_prob=0.3, spike_gain=4.0), dict(momentum=0.0, dist=1), dict(trigger_kind=1), dict(given=True)],
+                         ids=["normal", "student_plain", "norms", "given"])
+def test_whole_sends(evg, oracle_mod, P, sizes, kw):
+    kw = dict(kw)
+    both = {k: kw.pop(k) for k in ("trigger_kind",) if k in kw}
+    given = kw.pop("given", False)
+    _check(evg, oracle_mod, _workload(P, sizes, **kw), both, given)
+
+
+TOPK = [(5, EDGES * 24), (12, EDGES * 10 + [5000]), (16, [700] * 200 + EDGES * 4), (13, [257] * 300 + EDGES)]
+
+
+@pytest.mark.parametrize("P,sizes", TOPK, ids=[f"{P}x{len(s)}" for P, s in TOPK])
+@pytest.mark.parametrize("kw", [dict(topk_ppm=100_000), dict(topk_ppm=3_000, momentum=0.0, dist=1), dict(topk_ppm=400_000, trigger_kind=1),
+                                dict(topk_ppm=100_000, given=True)], ids=["normal", "student_plain", "norms", "given"])
+def test_messages(evg, oracle_mod, P, sizes, kw):
+    kw = dict(kw)
+    both = {k: kw.pop(k) for k in ("trigger_kind",) if k in kw}
+    given = kw.pop("given", False)
+    _check(evg, oracle_mod, _workload(P, sizes, **kw), both, given)
+
+
+# a blob holds a sum for every 1024 elements, however many windows a ring has there
+@pytest.mark.parametrize("sizes", [EDGES, EDGES * 12, EDGES * 25], ids=len)
+@pytest.mark.parametrize("kw", [dict(), dict(trigger_kind=1), dict(topk_ppm=100_000)], ids=["whole", "norms", "topk"])
+def test_checkpoints_with_short_windows(evg, sizes, kw):
+    kw = dict(kw)
+    both = {k: kw.pop(k) for k in ("trigger_kind",) if k in kw}
+    w = _workload(4, sizes, **kw)
+    rings = [evg.Ring.from_workload(w, mailbox_fill=0.0, access_mode=m, **both) for m in (evg.ACCESS_CACHED, evg.ACCESS_STREAM)]
+    for k in range(5):
+        for r in rings:
+            r.step(k)
+    blobs = [r.export_state() for r in rings]
+    others = [evg.Ring.from_workload(w, mailbox_fill=0.0, access_mode=m, **both) for m in (evg.ACCESS_STREAM, evg.ACCESS_CACHED)]
+    for r, b in zip(others, blobs):
+        r.import_state(b)
+    for k in range(5, 9):
+        for r in rings + others:
+            r.step(k)
+        for r in rings[1:] + others:
+            assert np.array_equal(r.decisions()["fired"], rings[0].decisions()["fired"]), k
+    for r in rings[1:] + others:
+        for name in ("x", "xhat", "vel", "mbox_l", "mbox_r"):
+            assert np.array_equal(r.state(name), rings[0].state(name)), name
