@@ -306,7 +306,7 @@ static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uin
     t.add(P * ktot, 4); t.add(P * ktot, 4); t.add(S, 8); t.add(S, 8);
     t.add(S, 4); t.add(S, 4);                                     // anchor, sel_left
     if (codes) t.add(P * Npad + 16, 1);
-    t.add(L, 4);                                                   // order
+    t.add(L, sizeof(ChooseDesc));                                  // tensors by size
   }
   return t.total;
 }
@@ -535,7 +535,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     }
     // Cached rings that send whole tensors and accumulate the norms in the update pass are updated in parts of the ring; in
     // one launch per iteration where one wavefront sums a tensor's sweep partials with two loads per lane.
-    in_parts = may_be && pull && cfg->norm_mode == EVG_NORM_FUSED && arena_bytes < (1ull << 30) && (!cfg->topk_ppm || (codes && longest <= kChooseMost));
+    in_parts = may_be && pull && cfg->norm_mode == EVG_NORM_FUSED && arena_bytes < (1ull << 30) && (!cfg->topk_ppm || (codes && longest <= (P > 3 || cfg->grad_mode == EVG_GRAD_BUFFER ? kChooseMost : kChooseMostOf3)));
     one_launch = in_parts && !cfg->topk_ppm && most_sweeps <= 128;
     // (admission counts the second set of what the tests read also where the parts find no room, as it always has)
     sets_counted = pull && !cfg->topk_ppm && cfg->norm_mode == EVG_NORM_FUSED && most_sweeps <= 128;
@@ -732,7 +732,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   // itself from a copy of x it keeps (one more array of the ring's size, library-owned)
   if (pull && !(in_parts && ring_part == P)) TRY_OR_FREE(c->dalloc(&t.xsnap, 2 * (uint64_t)P * Npad, false));
   std::vector<WindowDesc> ring;
-  std::vector<uint32_t> order;
+  std::vector<ChooseDesc> by_size;
   if (in_parts) {
     const uint32_t length = kSweep / fine, sums = SW * fine;
     for (size_t i = 0; i < chunks.size(); ++i)
@@ -788,13 +788,15 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     // (cached rings that make their selections in many launches read x and xhat as fast)
     if (codes && (choose || !c->cached)) TRY_OR_FREE(c->dalloc(&t.codes, (uint64_t)P * Npad + 16, true));
     if (choose) {
-      order.resize(L);
-      for (uint32_t l = 0; l < L; ++l) order[l] = l;
-      std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return layers[a].numel > layers[b].numel; });
-      uint32_t* d_order = nullptr;
-      TRY_OR_FREE(c->dalloc(&d_order, L, false));
-      HIP_OR_FREE(hipMemcpyAsync(d_order, order.data(), L * 4, hipMemcpyHostToDevice, c->stream));
-      c->choose.order = d_order;
+      for (uint32_t l = 0; l < L; ++l) {
+        const LayerDesc& d = layers[l];
+        by_size.push_back({l, d.off, d.numel, d.K, d.chunk0, d.nchunks, d.chunk0 * SW * fine, d.nchunks * SW * fine});
+      }
+      std::stable_sort(by_size.begin(), by_size.end(), [&](const ChooseDesc& a, const ChooseDesc& b) { return a.numel > b.numel; });
+      ChooseDesc* d_by_size = nullptr;
+      TRY_OR_FREE(c->dalloc(&d_by_size, L, false));
+      HIP_OR_FREE(hipMemcpyAsync(d_by_size, by_size.data(), L * sizeof(ChooseDesc), hipMemcpyHostToDevice, c->stream));
+      c->choose.tensors = d_by_size;
       c->choose.longest = longest;
       for (const LayerDesc& d : layers) c->choose.longer += d.numel > 256;
     }

@@ -192,13 +192,15 @@ hipError_t launch_topk_decide(const Tables& t, const StepArgs& a, hipStream_t s)
 hipError_t launch_topk_select(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
 // pass A's histograms and the key codes of all tensors, as an update pass leaves them; added to the histograms that are there
 hipError_t launch_topk_count_all(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
+// What k_topk_choose has to know of a tensor (LayerDesc; sum0, sums: its partials in a worker's).
+struct ChooseDesc { uint32_t layer, off, numel, K, chunk0, nchunks, sum0, sums; };
 // The tensors by size, the `longer` of more than 256 elements first; the longest's elements, at most kChooseMost.
-struct ChooseTables { const uint32_t* order; uint32_t longer, longest; };
-// Longer ones are too much for one workgroup.  Steps in us, in many launches / one workgroup a tensor, rings of 3, 5 and 8 perceptrons whose
-// longest tensor has 141 000 elements 35.2 / 26.5, 37.5 / 28.9, 39.6 / 30.6; 251 000 37.9 / 38.1, 41.7 / 40.2, 47.0 / 44.1; 327 000 39.0 /
-// 44.2, 45.0 / 48.8, 53.5 / 52.0; 408 000 41.9 / 52.3, 47.4 / 56.8, 58.5 / 62.1; with given gradients 251 000 35.9 / 30.4, 39.4 / 33.1, 45.1 /
-// 38.4; 327 000 37.0 / 34.2, 43.1 / 40.1, 50.9 / 44.1; 408 000 40.2 / 40.5, 45.0 / 46.0, 56.7 / 53.6.  A compromise of these.
-constexpr uint32_t kChooseMost = 327680;
+struct ChooseTables { const ChooseDesc* tensors; uint32_t longer, longest; };
+// Longer ones are too much for one workgroup.  Steps in us, in many launches / one workgroup a tensor, rings of 3, 5 (4) and 8 (9) perceptrons whose
+// longest tensor has 329 000 elements 41.6 / 32.2, (43.8 / 33.6), (62.3 / 41.5); 502 000 44.6 / 38.7, 51.4 / 44.8, 75.2 / 53.0; 706 000 49.8 / 50.7, (59.5 /
+// 53.4), (105.6 / 97.4); 784 000 51.7 / 54.4, 74.2 / 66.3, 104.1 / 87.2; with given gradients 329 000 39.6 / 25.9, (42.4 / 27.8), (63.4 / 43.0); 706 000
+// 52.5 / 41.3, (60.7 / 47.7), (104.7 / 89.9); 784 000 55.2 / 44.5, 76.7 / 56.5, 104.2 / 79.6.  Three workers that draw their gradients: kChooseMostOf3.
+constexpr uint32_t kChooseMost = 819200, kChooseMostOf3 = 655360;
 hipError_t launch_topk_choose(const Tables& t, const StepArgs& a, const ChooseTables& c, hipStream_t s);
 hipError_t launch_topk_apply(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
 hipError_t launch_average(const Tables& t, float* out, hipStream_t s);

@@ -5,29 +5,37 @@
 // The update pass has left a key code for each element, a byte, and has counted the 128 codes in whose middle the threshold is
 // expected (one addition a lane and workgroup, where the histogram of all keys took a pass of its own through LDS).  The counts
 // name the code of the K-th largest key; the workgroup goes through the codes once, lists what has that one (some 0.4 % of the
-// tensor), fetches those keys alone and finds the threshold among them.  Where the counts do not reach it (a tensor's first
+// tensor), fetches those keys alone and finds the threshold among them: a histogram of their upper ten bits leaves a key or a few, which
+// every wavefront ranks for itself.  Where the counts do not reach it (a tensor's first
 // message; it has moved by more than an octave down or three quarters of one up) the keys are read from the arenas, in four passes.
 // Tensors of at most 256 elements are a wavefront's work.
 //
-// Bound by latency: some ten dependent steps of a workgroup (8 ResNet-20 workers 15 us, its longest tensors 36 864 elements; 24 000
-// cycles: descriptors 4000, trigger test 5100, the pass over the codes 3500, fetching 2500, finding the threshold 4700, the groups' places
-// 3600).  Steps, before -> now, with the update pass in parts of the ring: 8 ResNet-20 workers, 10 % 52.7 -> 32.7 us, 5 perceptrons of
-// 160 000 elements, 5 % 36.9 -> 25.8, 3 to 12 rings of other small networks 40 - 57 -> 19 - 39.
+// Bound by latency, and by the vector ALUs where a tensor is long.  A workgroup of a ResNet-20 ring of 8 workers (its longest tensors 36 864 elements) takes
+// 6.7 us: its descriptor and everything asked for 0.7, sums, counts and codes there 1.1, the codes gone through 1.4 (160 000 elements:
+// 4.6), keys fetched 1.7, the histogram 0.5, ranked and added to the groups 0.8, the groups' places 0.6.  The tests' outcome is booked while the keys are on
+// their way.  Before, with descriptors in two tables, the test's threshold asked for behind its sums, bytes compared in halves of registers and two
+// histograms with three barriers each, 24 000 cycles.  The launch 15.8 -> 10.2 us, 160 000 elements 21.5 -> 14.4; steps: 8 ResNet-20 workers, 10 % 32.3 -> 26.8 us,
+// 5 perceptrons of 160 000 elements, 5 % 27.5 -> 20.8 (in many launches 52.7 and 36.9).
 #include "message_device.h"
+#include "quad_device.h"
 #include "trigger_device.h"
 
 namespace evg {
 
 constexpr uint32_t kWide = 1024;           // threads of a workgroup
-constexpr uint32_t kListCap = 4096;        // listed keys at most
 constexpr uint32_t kBlock = 4;             // loads of x and of xhat that a thread has in flight
+constexpr uint32_t kNearBits = 7;          // lower bits of the keys of a code that are looked at last
 constexpr uint32_t kHeld = 10;             // sixteen codes each that a thread holds
 
+// The trigger test of a tensor (test_tensor).
+struct Tested { double acc; float d, dl; int32_t khat; uint32_t code, k; };
+
 struct Chosen {                            // LDS
+  Tested test;
   uint32_t hist[kHistBins];
-  uint32_t list[kListCap], key[kListCap];
   uint32_t wave[kWide / 64 * 2];
-  uint32_t bin, rem, listed, code, cut;
+  uint32_t near_key[64], near_at[64];
+  uint32_t bin, rem, listed, near, code, cut;
 };
 
 // The bin, from the highest down, in which the rem-th key lies, and its rank there; NB bins, a multiple of 1024 or
@@ -60,37 +68,72 @@ __device__ __forceinline__ bool pick(Chosen& s, uint32_t rem) {
   return rem <= total;
 }
 
+// The sum of the earlier wavefronts' totals, and of all sixteen.
+__device__ __forceinline__ uint32_t earlier_waves(const uint32_t* totals, uint32_t* all) {
+  static_assert(kWide / 64 == 16, "a row of lanes holds a workgroup's totals");
+  uint32_t v = totals[lane_id() & 15u];
+  const uint32_t own = v;
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);   // row_shr:1, 2, 4, 8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+  *all = (uint32_t)__builtin_amdgcn_readlane((int)v, 15);
+  const int w = __builtin_amdgcn_readfirstlane((int)wave_id());
+  return (uint32_t)__builtin_amdgcn_readlane((int)(v - own), w);
+}
+
+// The same where the workgroup has just passed a barrier and each thread has one bin.
+__device__ __forceinline__ bool pick_at_once(Chosen& s, uint32_t rem) {
+  const uint32_t bin = kWide - 1 - threadIdx.x, cnt = s.hist[bin];
+  s.hist[bin] = 0;
+  const uint32_t upto = wave_incl_scan(cnt);
+  if (lane_id() == 63) s.wave[wave_id()] = upto;
+  __syncthreads();
+  uint32_t total;
+  const uint32_t above = earlier_waves(s.wave, &total) + upto - cnt;
+  if (above < rem && rem <= above + cnt) {                 // at most one thread
+    s.bin = bin;
+    s.rem = rem - above;
+  }
+  __syncthreads();
+  return rem <= total;
+}
+
 // What the selection leaves of a tensor for the update pass.
 struct Threshold { uint32_t key, ties; bool ok; };
 
 // Running totals of winners before every group of 256 elements, for message_place; groups[g] holds group g's keys above (low half)
 // and equal to (high half) the threshold.  Returns the tensor's totals.
-__device__ __forceinline__ uint2 place_groups(const Tables& T, Chosen& s, uint32_t r, const LayerDesc& ld, const uint32_t* groups) {
+__device__ __forceinline__ uint2 place_groups(const Tables& T, Chosen& s, uint32_t r, const ChooseDesc& ld, const uint32_t* groups) {
   const uint32_t G = T.SW * 4, ngroups = (ld.numel + 255) / 256, first = r * T.C + ld.chunk0;
+  constexpr uint32_t W = kWide / 64;
   uint32_t carry_a = 0, carry_e = 0;
   for (uint32_t g0 = 0; g0 < ngroups; g0 += kWide) {       // uniform
     const uint32_t g = g0 + threadIdx.x, n = g < ngroups ? groups[g] : 0u;
-    uint32_t all_a, all_e;
-    const uint32_t a = carry_a + block_excl_scan<kWide / 64>(n & 0xFFFFu, s.wave, &all_a);
-    const uint32_t e = carry_e + block_excl_scan<kWide / 64>(n >> 16, s.wave, &all_e);
-    // a chunk's first group (1024 is a multiple of a chunk's groups): its running totals are the chunk's
-    const uint32_t lead = threadIdx.x / G * G;
-    s.hist[threadIdx.x] = a;
-    s.hist[kWide + threadIdx.x] = e;
-    __syncthreads();
-    if (g < ngroups) {
-      T.group[(size_t)first * G + g] = (a - s.hist[lead]) | (e - s.hist[kWide + lead]) << 16;
-      if (lead == threadIdx.x) T.chunk_before[first + g / G] = make_uint2(a, e);
+    const uint32_t upto_a = wave_incl_scan(n & 0xFFFFu), upto_e = wave_incl_scan(n >> 16);
+    if (g0) __syncthreads();                               // (the totals of the round before have been read)
+    if (lane_id() == 63) {
+      s.wave[wave_id()] = upto_a;
+      s.wave[W + wave_id()] = upto_e;
     }
     __syncthreads();
+    uint32_t all_a, all_e;
+    const uint32_t a = carry_a + earlier_waves(s.wave, &all_a) + upto_a - (n & 0xFFFFu), e = carry_e + earlier_waves(s.wave + W, &all_e) + upto_e - (n >> 16);
     carry_a += all_a;
     carry_e += all_e;
+    // a chunk's first group (64 is a multiple of a chunk's groups): its running totals are the chunk's
+    const uint32_t lead = lane_id() / G * G;
+    const uint32_t lead_a = (uint32_t)__shfl((int)a, (int)lead, 64), lead_e = (uint32_t)__shfl((int)e, (int)lead, 64);
+    if (g < ngroups) {
+      T.group[(size_t)first * G + g] = (a - lead_a) | (e - lead_e) << 16;
+      if (lead == lane_id()) T.chunk_before[first + g / G] = make_uint2(a, e);
+    }
   }
   return make_uint2(carry_a, carry_e);
 }
 
 // Of the keys equal to the threshold only the first `ties` win: the last of them.
-__device__ __forceinline__ void cut_by_groups(const Tables& T, const StepArgs& A, Chosen& s, uint32_t r, const LayerDesc& ld, uint32_t t,
+__device__ __forceinline__ void cut_by_groups(const Tables& T, const StepArgs& A, Chosen& s, uint32_t r, const ChooseDesc& ld, uint32_t t,
                                               uint32_t ties, const uint32_t* groups) {
   uint32_t carry = 0;
   for (uint32_t g0 = 0; g0 < (ld.numel + 255) / 256; g0 += kWide) {       // uniform
@@ -119,7 +162,7 @@ __device__ __forceinline__ void cut_by_groups(const Tables& T, const StepArgs& A
 // f(first element, its four keys, how many of them are elements) for all float4s of a tensor, in order: a wavefront has a
 // group of 256 at a time.
 template <typename F>
-__device__ __forceinline__ void for_keys(const Tables& T, const StepArgs& A, uint32_t r, const LayerDesc& ld, F&& f) {
+__device__ __forceinline__ void for_keys(const Tables& T, const StepArgs& A, uint32_t r, const ChooseDesc& ld, F&& f) {
   const size_t base = (size_t)r * T.Npad + ld.off;
   const uint32_t bytes = (ld.numel + 3) / 4 * 16;
   const __amdgpu_buffer_rsrc_t x = window(T.x + base, bytes), h = window(T.xhat + base, A.topk_key ? 0u : bytes);
@@ -150,16 +193,11 @@ __device__ __forceinline__ void load_codes(const Tables& T, size_t base, uint32_
   for (uint32_t u = 0; u < kHeld; ++u) {
     const uint32_t j = j0 + (u * kWide + threadIdx.x) * 16;
     held[u] = __builtin_amdgcn_raw_buffer_load_b128(codes, (int)(j < numel ? j : 0xFFFFFFF0u), 0, 0);
-#pragma unroll
-    for (uint32_t w = 0; w < 4; ++w) {                     // what is past the end has code 0
-      const uint32_t left = j < numel && numel - j > 4 * w ? numel - j - 4 * w : 0u;
-      if (left < 4u) held[u][w] &= (1u << 8 * left) - 1u;
-    }
   }
 }
 
 // Keys from the arenas: bits 30..20, 19..9 and 8..0 in turn, then the groups.
-__device__ __forceinline__ Threshold choose_by_keys(const Tables& T, const StepArgs& A, Chosen& s, uint32_t r, const LayerDesc& ld,
+__device__ __forceinline__ Threshold choose_by_keys(const Tables& T, const StepArgs& A, Chosen& s, uint32_t r, const ChooseDesc& ld,
                                                     uint32_t* groups) {
   auto count = [&](uint32_t shift, uint32_t left, uint32_t prefix, uint32_t mask) {
     for_keys(T, A, r, ld, [&](uint32_t, const uint32_t key[4], uint32_t nv) {
@@ -195,35 +233,33 @@ __device__ __forceinline__ Threshold choose_by_keys(const Tables& T, const StepA
   return {t, ties, all.x + ties == ld.K && all.y >= ties};
 }
 
-// From the codes, `code` that of the K-th largest key and `rem` its rank among those; false: too many keys have it.
-__device__ __forceinline__ bool choose_by_codes(const Tables& T, const StepArgs& A, Chosen& s, uint32_t r, const LayerDesc& ld,
-                                                uint32_t anchor, uint32_t code, uint32_t rem, u32x4 held[kHeld], uint32_t* groups,
-                                                Threshold* out) {
+// From the codes, `code` that of the K-th largest key and `rem` its rank among those; false: too many keys have it.  `meanwhile` is done while
+// the keys are on their way.
+template <typename F>
+__device__ __forceinline__ bool choose_by_codes(const Tables& T, const StepArgs& A, Chosen& s, uint32_t r, const ChooseDesc& ld,
+                                                uint32_t anchor, uint32_t code, uint32_t rem, u32x4 held[kHeld], uint32_t* groups, uint32_t* list, uint32_t cap,
+                                                Threshold* out, F&& meanwhile) {
   const size_t base = (size_t)r * T.Npad + ld.off;
-  const uint32_t more = (255u - code) * 0x10001u;          // (as in stage_by_codes)
+  uint32_t* const key = list + cap;
   for (uint32_t j0 = 0; j0 < ld.numel; j0 += kHeld * kWide * 16) {          // uniform
     if (j0) load_codes(T, base, ld.numel, j0, held);
     uint32_t in[kHeld], mine = 0;                          // which of a thread's sixteen have the code
 #pragma unroll
     for (uint32_t u = 0; u < kHeld; ++u) {
       in[u] = 0;
-      const uint32_t j = j0 + (u * kWide + threadIdx.x) * 16;
-      if (j0 + u * kWide * 16 >= ld.numel) continue;       // uniform
-      uint32_t above = 0;
+      const uint32_t first = j0 + u * kWide * 16, j = first + threadIdx.x * 16;
+      if (first >= ld.numel) continue;                     // uniform
+      if (ld.numel - first < kWide * 16) {                 // uniform: what is past the end has code 0
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const uint32_t four = held[u][w], p = (four & 0x00FF00FFu) + more, q = ((four >> 8) & 0x00FF00FFu) + more;
-        above += (p & 0x01000100u) + (q & 0x01000100u);
-        const uint32_t ip = ((p + 0x10001u) ^ p) & 0x01000100u, iq = ((q + 0x10001u) ^ q) & 0x01000100u;
-        in[u] |= (ip >> 8 | iq >> 7) << 2 * w;             // element 4 w + b: bit 2 w + (b & 1) + 16 (b >> 1)
+        for (uint32_t w = 0; w < 4; ++w) {
+          const uint32_t left = j < ld.numel && ld.numel - j > 4 * w ? ld.numel - j - 4 * w : 0u;
+          if (left < 4u) held[u][w] &= (1u << 8 * left) - 1u;
+        }
       }
-      mine += (uint32_t)__popc(in[u]);
-      // sixteen lanes have a group of 256 elements
-      above = (above >> 8 & 0xFu) + (above >> 24);
-      above += (uint32_t)__builtin_amdgcn_mov_dpp((int)above, 0x128, 0xF, 0xF, true);   // row_ror:8, 4, 2, 1
-      above += (uint32_t)__builtin_amdgcn_mov_dpp((int)above, 0x124, 0xF, 0xF, true);
-      above += (uint32_t)__builtin_amdgcn_mov_dpp((int)above, 0x122, 0xF, 0xF, true);
-      above += (uint32_t)__builtin_amdgcn_mov_dpp((int)above, 0x121, 0xF, 0xF, true);
+      const Compared c = compare_codes(held[u], code);
+      in[u] = c.in;
+      mine += (uint32_t)__popc(c.in);
+      const uint32_t above = row_sum(c.above);             // sixteen lanes have a group of 256 elements
       if ((lane_id() & 15u) == 0 && j < ld.numel) groups[j >> 8] = above;
     }
     const uint32_t upto = wave_incl_scan(mine);
@@ -235,54 +271,91 @@ __device__ __forceinline__ bool choose_by_codes(const Tables& T, const StepArgs&
       while (in[u]) {
         const uint32_t b = (uint32_t)__ffs((int)in[u]) - 1u;
         in[u] &= in[u] - 1u;
-        if (at < kListCap) s.list[at] = j0 + (u * kWide + threadIdx.x) * 16 + (b >> 1 & 7u) * 4 + (b & 1u) + (b >> 4) * 2;
+        if (at < cap) list[at] = j0 + (u * kWide + threadIdx.x) * 16 + (b & 7u) * 4 + (b >> 3);
         ++at;
       }
     }
   }
   __syncthreads();
   const uint32_t n = s.listed;
-  if (n > kListCap) return false;                          // uniform
+  if (n > cap) return false;                          // uniform
+  meanwhile();
   const uint32_t begin = (code + anchor) << kFineBits;
   const __amdgpu_buffer_rsrc_t x = window(T.x + base, ld.numel * 4), h = window(T.xhat + base, A.topk_key ? 0u : ld.numel * 4);
   bool moved = false;                                      // a key is not what its code says: the caller has written x since
   for (uint32_t i = threadIdx.x; i < n; i += kWide) {
-    const float xv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(x, (int)(s.list[i] * 4), 0, 0));
-    const float hv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(h, (int)(s.list[i] * 4), 0, 0));
+    const float xv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(x, (int)(list[i] * 4), 0, 0));
+    const float hv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(h, (int)(list[i] * 4), 0, 0));
     const uint32_t low = rank_key(xv, hv, A.topk_key) - begin;
     moved |= low >> kFineBits != 0;
-    s.key[i] = low & ((1u << kFineBits) - 1u);
-    atomicAdd(&s.hist[s.key[i] >> (kFineBits - 11)], 1u);
+    key[i] = low & ((1u << kFineBits) - 1u);
+    atomicAdd(&s.hist[key[i] >> kNearBits], 1u);
   }
   moved = __syncthreads_or(moved);
-  bool ok = pick<kHistBins>(s, rem) && !moved;
+  static_assert(1u << (kFineBits - kNearBits) == kWide, "one bin a thread");
+  bool ok = pick_at_once(s, rem) && !moved;
+  // what shares the upper ten of their bits with the threshold: a key or a few, unless many are equal
   const uint32_t upper = s.bin, rem2 = s.rem;
   for (uint32_t i = threadIdx.x; i < n; i += kWide)
-    if (s.key[i] >> (kFineBits - 11) == upper) atomicAdd(&s.hist[s.key[i] & ((1u << (kFineBits - 11)) - 1u)], 1u);
+    if (key[i] >> kNearBits == upper) {
+      const uint32_t at = atomicAdd(&s.near, 1u);
+      if (at < 64) {
+        s.near_key[at] = key[i];
+        s.near_at[at] = list[i];
+      }
+    }
   __syncthreads();
-  const uint32_t last = threadIdx.x < 64 ? s.hist[threadIdx.x] : 0u;        // (6 bits)
+  const uint32_t near = s.near;
+  uint32_t t, ties;
+  if (near <= 64) {                                        // uniform: ranked by every wavefront for itself, larger keys first, then earlier elements
+    const uint32_t l = lane_id(), k = s.near_key[l], at = s.near_at[l];
+    uint32_t greater = 0, before = 0;
+    for (uint32_t q = 0; q < near; ++q) {
+      const uint32_t kq = (uint32_t)__builtin_amdgcn_readlane((int)k, (int)q), jq = (uint32_t)__builtin_amdgcn_readlane((int)at, (int)q);
+      greater += kq > k ? 1u : 0u;
+      before += kq == k && jq < at ? 1u : 0u;
+    }
+    const uint64_t is = __ballot(l < near && greater + before + 1 == rem2);          // (no lane: the counts do not fit, `ok` says so)
+    const int who = is ? __ffsll((unsigned long long)is) - 1 : 0;
+    t = (uint32_t)__builtin_amdgcn_readlane((int)k, who);
+    ties = rem2 - (uint32_t)__builtin_amdgcn_readlane((int)greater, who);
+    ok &= is != 0;
+    if (threadIdx.x == 0) s.cut = (uint32_t)__builtin_amdgcn_readlane((int)at, who);
+    for (uint32_t i = threadIdx.x; i < n; i += kWide)
+      if (key[i] >= t) atomicAdd(&groups[list[i] >> 8], key[i] == t ? 0x10000u : 1u);
+    __syncthreads();
+    const uint2 all = place_groups(T, s, r, ld, groups);
+    *out = {begin + t, ties, ok && all.x + ties == ld.K && all.y >= ties};
+    return true;
+  }
+  for (uint32_t i = threadIdx.x; i < n; i += kWide)
+    if (key[i] >> kNearBits == upper) atomicAdd(&s.hist[key[i] & ((1u << kNearBits) - 1u)], 1u);
   __syncthreads();
-  ok &= pick<1u << (kFineBits - 11)>(s, rem2);
-  const uint32_t t = upper << (kFineBits - 11) | s.bin, ties = s.rem;
+  const uint32_t last = threadIdx.x < 1u << kNearBits ? s.hist[threadIdx.x] : 0u;
+  __syncthreads();
+  ok &= pick<1u << kNearBits>(s, rem2);
+  t = upper << kNearBits | s.bin;
+  ties = s.rem;
   if (threadIdx.x == s.bin) s.code = last;                 // keys equal to the threshold
-  if (threadIdx.x == 0) s.cut = ld.numel - 1;
+  if (threadIdx.x == 0) {
+    s.cut = ld.numel - 1;
+    s.near = 0;
+  }
   __syncthreads();
   const uint32_t equal = s.code;
-  if (threadIdx.x == 0) s.listed = 0;
-  __syncthreads();
   for (uint32_t i = threadIdx.x; i < n; i += kWide) {
-    const uint32_t k = s.key[i], j = s.list[i];
+    const uint32_t k = key[i], j = list[i];
     if (k >= t) atomicAdd(&groups[j >> 8], k == t ? 0x10000u : 1u);
     if (k == t && equal != ties) {                         // not all of them win (common: drifts are multiples of x's spacing)
-      const uint32_t at = atomicAdd(&s.listed, 1u);
-      if (at < kWide) s.hist[at] = j;
+      const uint32_t at = atomicAdd(&s.near, 1u);
+      if (at < 64) s.near_at[at] = j;
     }
   }
   __syncthreads();
   if (equal != ties && equal <= 64 && threadIdx.x < equal) {
     uint32_t before = 0;                                   // the last winner has ties - 1 before it
-    for (uint32_t q = 0; q < equal; ++q) before += s.hist[q] < s.hist[threadIdx.x] ? 1u : 0u;
-    if (before + 1 == ties) s.cut = s.hist[threadIdx.x];
+    for (uint32_t q = 0; q < equal; ++q) before += s.near_at[q] < s.near_at[threadIdx.x] ? 1u : 0u;
+    if (before + 1 == ties) s.cut = s.near_at[threadIdx.x];
   }
   __syncthreads();
   const uint2 all = place_groups(T, s, r, ld, groups);
@@ -291,20 +364,33 @@ __device__ __forceinline__ bool choose_by_codes(const Tables& T, const StepArgs&
   return true;
 }
 
+// The trigger test of a tensor, by a wavefront.  Threshold and last event are asked for with the sums.
+__device__ __forceinline__ Tested test_tensor(const Tables& T, const StepArgs& A, uint32_t r, const ChooseDesc& ld) {
+  const uint32_t seg = r * T.L + ld.layer;
+  Tested t;
+  t.dl = T.delta[seg];
+  t.khat = T.last_event[seg];
+  t.k = tested_k(T, A);
+  const size_t at = (size_t)r * T.C * (T.SW * T.fine) + ld.sum0;
+  const double sum = ordered_lane_sum(T.partials + at, ld.sums);
+  t.acc = wave_sum_dpp(sum);
+  double acc_hat = 0.0;
+  if (A.norm_src == 2) acc_hat = wave_sum_dpp(ordered_lane_sum(T.partials_hat + at, ld.sums));
+  t.d = tested_norm(A, t.acc, acc_hat);
+  t.code = (uint32_t)__builtin_amdgcn_readfirstlane((int)event_code(A, t.d, t.dl, t.khat, t.k));
+  return t;
+}
+
 // A tensor of at most 256 elements, by a wavefront: four keys a lane, the threshold bit by bit.
-__device__ __forceinline__ void choose_small(const Tables& T, const StepArgs& A, uint32_t seg) {
-  const uint32_t r = seg / T.L, lane = lane_id();
-  const LayerDesc ld = T.layers[seg % T.L];
+__device__ __forceinline__ void choose_small(const Tables& T, const StepArgs& A, uint32_t r, const ChooseDesc& ld) {
+  const uint32_t seg = r * T.L + ld.layer, lane = lane_id();
   const size_t base = (size_t)r * T.Npad + ld.off;
   const uint32_t bytes = (ld.numel + 3) / 4 * 16;
   const u32x4 xv = __builtin_amdgcn_raw_buffer_load_b128(window(T.x + base, bytes), (int)(lane * 16), 0, 0);
   const u32x4 hv = __builtin_amdgcn_raw_buffer_load_b128(window(T.xhat + base, bytes), (int)(lane * 16), 0, 0);
-  double acc, acc_hat;
-  bool hat_sums;
-  segment_sums(T, A, seg, &acc, &acc_hat, &hat_sums);
-  uint32_t code = 0;
-  if (lane == 0) code = segment_test(T, A, seg, acc, acc_hat, hat_sums, tested_k(T, A));
-  if ((uint32_t)__builtin_amdgcn_readfirstlane((int)code) != 2) return;
+  const Tested test = test_tensor(T, A, r, ld);
+  if (lane == 0) book_test<true>(T, A, seg, test.d, test.dl, test.khat, (uint8_t)test.code, test.acc, test.k);
+  if (test.code != 2) return;
   uint32_t key[4];
   uint64_t valid[4];
 #pragma unroll
@@ -345,30 +431,29 @@ __device__ __forceinline__ void choose_small(const Tables& T, const StepArgs& A,
   }
 }
 
-// order: the tensors by size, the `longer` of more than 256 elements first.  A workgroup has one of them, or sixteen others.
-__global__ __launch_bounds__(kWide) void k_topk_choose(Tables T, StepArgs A, const uint32_t* order, uint32_t longer) {
+// tensors: by size, the `longer` of more than 256 elements first.  A workgroup has one of them, or sixteen others.
+__global__ __launch_bounds__(kWide) void k_topk_choose(const ChooseDesc* tensors, uint32_t longer, uint32_t lists, uint32_t cap, StepArgs A, Tables T) {
   __shared__ Chosen s;
-  extern __shared__ uint32_t groups[];                     // one a group of the longest tensor
+  extern __shared__ uint32_t groups[];                     // one a group of the longest tensor; from `lists` on `cap` listed elements and their keys
   const uint32_t r = blockIdx.y, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_id());
-  if (blockIdx.x == 0 && r == 0 && threadIdx.x == 0) close_step(T, A);
   if (blockIdx.x >= longer) {
     const uint32_t i = longer + (blockIdx.x - longer) * (kWide / 64) + wave;
-    if (i < T.L) choose_small(T, A, r * T.L + order[i]);
+    if (i < T.L) choose_small(T, A, r, tensors[i]);
+    if (longer == 0 && blockIdx.x == 0 && r == 0 && threadIdx.x == 0) close_step(T, A);
     return;
   }
-  const uint32_t layer = order[blockIdx.x], seg = r * T.L + layer;
-  const LayerDesc ld = T.layers[layer];
-  const uint32_t anchor = T.anchor[seg];
+  const ChooseDesc ld = tensors[blockIdx.x];
+  const uint32_t seg = r * T.L + ld.layer;
   u32x4 held[kHeld];
   load_codes(T, (size_t)r * T.Npad + ld.off, ld.numel, 0, held);
-  for (uint32_t b = threadIdx.x; b < (uint32_t)kHistBins; b += kWide) s.hist[b] = 0;
+  const uint32_t anchor = T.anchor[seg];
+  s.hist[threadIdx.x] = 0;
+  s.hist[kWide + threadIdx.x] = 0;
   if (wave == 0) {
-    double acc, acc_hat;
-    bool hat_sums;
-    segment_sums(T, A, seg, &acc, &acc_hat, &hat_sums);
+    const Tested test = test_tensor(T, A, r, ld);
     if (lane_id() == 0) {
-      s.code = segment_test(T, A, seg, acc, acc_hat, hat_sums, tested_k(T, A));
-      s.listed = 0;
+      s.test = test;
+      s.listed = s.near = 0;
     }
   } else if (wave == 1) {
     // the counts of codes kFirstCode + 127 .. kFirstCode, from the highest down, two a lane; those above are in the last word
@@ -395,13 +480,22 @@ __global__ __launch_bounds__(kWide) void k_topk_choose(Tables T, StepArgs A, con
     }
   }
   __syncthreads();
-  if (s.code != 2) return;                                 // uniform
+  auto book = [&] {
+    if (threadIdx.x != kWide - 1) return;
+    book_test<true>(T, A, seg, s.test.d, s.test.dl, s.test.khat, (uint8_t)s.test.code, s.test.acc, s.test.k);
+    if (blockIdx.x == 0 && r == 0) close_step(T, A);
+  };
+  if (s.test.code != 2) {                                  // uniform
+    book();
+    return;
+  }
   const uint32_t code = s.bin, rem = s.rem;
-  __syncthreads();                                         // (s.code and s.bin are written again further down)
+  __syncthreads();                                         // (s.bin is written again further down)
   Threshold found;
-  if (anchor == kNoAnchor || code == 0 || !choose_by_codes(T, A, s, r, ld, anchor, code, rem, held, groups, &found)) {
+  if (anchor == kNoAnchor || code == 0 || !choose_by_codes(T, A, s, r, ld, anchor, code, rem, held, groups, groups + lists, cap, &found, book)) {
     __syncthreads();
     if (threadIdx.x == 0) atomicAdd(T.not_staged, ld.nchunks);
+    book();
     found = choose_by_keys(T, A, s, r, ld, groups);
   }
   if (threadIdx.x == 0) {
@@ -415,7 +509,9 @@ __global__ __launch_bounds__(kWide) void k_topk_choose(Tables T, StepArgs A, con
 
 hipError_t launch_topk_choose(const Tables& t, const StepArgs& a, const ChooseTables& c, hipStream_t s) {
   const dim3 grid(c.longer + (t.L - c.longer + kWide / 64 - 1) / (kWide / 64), t.P);
-  k_topk_choose<<<grid, dim3(kWide), (c.longest + 255) / 256 * 4, s>>>(t, a, c.order, c.longer);
+  // (a list of 12 288 takes 1.2 us more where one of 4096 will do: no other workgroup is on the CU meanwhile)
+  const uint32_t groups = (c.longest + 255) / 256, cap = c.longest <= 327680 ? 4096u : 12288u;
+  k_topk_choose<<<grid, dim3(kWide), (groups + 2 * cap) * 4, s>>>(c.tensors, c.longer, groups, cap, a, t);
   return hipGetLastError();
 }
 

@@ -52,6 +52,34 @@ __device__ __forceinline__ void store_codes(const Tables& T, size_t first, uint3
   __builtin_amdgcn_raw_buffer_store_b32(four, window(T.codes + first, bytes >> 2), (int)(byte >> 2), 0, 2);     // non-temporal
 }
 
+// Sixteen codes against one (1 .. 254): how many are above it, and which are equal, bit 8 b + w for the b-th of the w-th four.
+// Four bytes at a time: with bit 7 set, a byte less the lower seven bits of k keeps that bit where its own seven are no less.  (44 instructions;
+// taking bytes apart into halves of registers 70.)
+struct Compared { uint32_t above, in; };
+__device__ __forceinline__ Compared compare_codes(const u32x4& sixteen, uint32_t code) {
+  const uint32_t k = code * 0x01010101u, k1 = k + 0x01010101u, m = 0x80808080u;
+  Compared c{0u, 0u};
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const uint32_t four = sixteen[w], with = four | m;
+    // (a & ~b) | (~(a ^ b) & c): bit 7 of each byte says whether it is at least the code, or above it
+    const uint32_t ge = __builtin_amdgcn_bitop3_b32(four, k, with - (k & ~m), 0xB2);
+    const uint32_t gt = __builtin_amdgcn_bitop3_b32(four, k1, with - (k1 & ~m), 0xB2);
+    c.above += (uint32_t)__popc(gt & m);
+    const uint32_t eq = __builtin_amdgcn_bitop3_b32(ge, gt, m, 0x20);                 // a & ~b & c
+    c.in |= eq >> (7 - w);
+  }
+  return c;
+}
+// Sum over the lane's sixteen lanes.
+__device__ __forceinline__ uint32_t row_sum(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xF, 0xF, true);   // row_ror:8, 4, 2, 1
+  v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x124, 0xF, 0xF, true);
+  v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x122, 0xF, 0xF, true);
+  v += (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x121, 0xF, 0xF, true);
+  return v;
+}
+
 // One bit per element of a float4, the first of them element j of the tensor.  thr = kNoThreshold: none.
 // nv: how many of the four are elements of the tensor.
 __device__ __forceinline__ uint32_t winners4(const float x[4], const float h[4], uint32_t by_value, uint32_t thr,

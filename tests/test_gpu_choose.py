@@ -170,3 +170,8 @@ def test_more_keys_of_a_code_than_the_list_holds(evg, oracle_mod, every, ppm, li
         return g
     n = _not_staged(evg, oracle_mod, sizes, 3, 8, given, topk_ppm=ppm)
     assert n[:2].tolist() == [0, 45] and ((n[3:] == 0).all() if lists else (n[3:] > 0).any()), n
+
+
+@pytest.mark.parametrize("P,n", [(3, 655_360), (3, 655_361), (4, 819_200), (4, 819_201)])
+def test_the_longest_tensors_of_a_workgroup(evg, oracle_mod, P, n):
+    _run(evg, oracle_mod, _workload(P, [n, 9], 4, topk_ppm=30_000))
