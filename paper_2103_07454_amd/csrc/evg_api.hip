@@ -288,7 +288,7 @@ static uint64_t table_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, uin
   t.add(PC * SW * fine, 8);
   if (norm_diff) { t.add(PC * SW * fine, 8); t.add(S, 8); }
   t.add(S, 4); t.add(S, 4); t.add(S, 4); t.add(S, 4);            // delta, last_norm, delta_before, last_event
-  t.add(S, 1); t.add(S, 1); t.add(S, 1); t.add(S, 1);            // valid_l, valid_r, fired, near_tie
+  for (int i = 0; i < 4; ++i) t.add((S + 3) / 4 * 4, 1);         // valid_l, valid_r, fired (whole words are read), near_tie
   t.add(S, 4); t.add(S, 4); t.add(S, 4); t.add(S, 4);            // ev_full, ev_topk, near_cnt, nonfinite_cnt
   t.add(S * hist_len, 4); t.add(S, 4);                           // slope_hist, slope_cnt
   t.add(1, 4); t.add(1, sizeof(IterState)); t.add(kDecayTable, 8);
@@ -354,17 +354,19 @@ static uint64_t admitted_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, 
 // a CU too few of them beside it unless it has much to load.  Kernels_parts.hip / groups and quads 1 1 / 2 1 / 2 2 / 4 2, us a step, normal
 // gradients: perceptrons of 102 windows on 4 workers 6.2 / 5.7 / 5.4 / 5.6 / 6.2, 39 on 4 5.1 / 4.5 / 4.7 / 4.9 / 5.4, 506 on 6 22.0 / 20.6 / 20.2 / 17.3 /
 // 17.9; ResNet-20 of 314 on 3 8.8 / 7.4 / 7.9 / 7.8 / 8.5, on 8 14.5 / 13.6 / 16.5 / 12.6 / 15.6, on 16 30.1 / 27.2 / - / 26.5 / -, of 186 on 15 13.7 / 16.3 / - / 15.3 / -;
-// ResNet-18 of 729 on 4 16.9 / 18.2 / 18.6 / 17.8 / 16.8; more workers have one float4 each of several: 120 windows on 24 12.7 and 15.4.  Top-K, kernels_parts.hip / 1 2 / 2 2:
+// ResNet-18 of 729 on 4 16.9 / 18.2 / 18.6 / 17.8 / 16.8, ResNet-20 of 923 on 4 17.2 / - / - / - / 17.8; more workers have one float4 each of several: 120 windows on 24 12.7 and 15.4.  Top-K, kernels_parts.hip / 1 2 / 2 2:
 // ResNet-20 of 314 windows on 8 33.6 / 32.4 / 32.3, on 16 67.3 / 60.1 / 63.9, of 426 on 15 86 / 76 / 83; perceptrons of 129 on 11 32.4 / - / 34.9, of
 // 237 on 10 44.0 / 49.2 / 45.8; ResNet-18 of 729 on 4 39.7 / - / 41.4, ResNet-20 of 509 on 4 with given gradients 27.8 / - / 25.8.
 static void ring_shape(uint32_t P, uint64_t windows, uint32_t longest, bool topk, bool tests, bool given, uint32_t* groups, uint32_t* quads) {
   *groups = *quads = 0;
   const uint64_t units = windows * P;
-  if (P > kRingMost || (P > 12 && units < (given && !topk ? 800 : 4000))) return;
+  if (P > 16 || (P > 12 && units < (given && !topk ? 800 : 4000))) return;
   if (topk) {
     if (units < 1700 || (longest > 200000 && P > 8) || (P <= 4 && !given)) return;
     *groups = P > 12 ? 1 : 2;
     *quads = 2;
+  } else if (P <= 4 && windows >= 700 && !given) {
+    return;
   } else if (P <= 4 && windows >= 400) {
     *groups = 4;
     *quads = 2;
@@ -374,6 +376,25 @@ static void ring_shape(uint32_t P, uint64_t windows, uint32_t longest, bool topk
     *groups = tests && longest > 65536 && P <= 8 ? 2 : 1;
     *quads = 1;
   }
+}
+
+// The same for a ring that streams from memory and sends whole tensors; groups = 0: it is walked.  `row`: bytes of a worker's slice.
+// Short windows put a CU's wavefronts to different tasks, but each has a sum that the tests read; workgroups have no more than sixteen wavefronts.
+// Walked / groups and quads 1 1 / 2 1 / 1 2 / 1 4, us a step: ResNet-18 of width 23 on 7 workers 64.7 / 55.0 / 53.6 / 55.2 / 58.0, with given
+// gradients and plain SGD 54.0 / 48.5 / 47.5 / 48.6 / 49.8, of width 60 on 6 275 / 271 / 267 / 272 / 286, of width 64 on 16 873 / 817 / - / 846 / 844,
+// with given gradients 1035 / 1022 / - / 1025 / 1010; ResNet-50 of width 30 on 15 496 / 450 / - / 482 / 472; ResNet-20 of width 24 on 13 49.6 / 37.5 / - /
+// 36.2 / 36.8, of width 21 on 23 80.0 / - / - / 47.3 / 51.0; perceptrons of 471 000 elements on 18 45.2 / - / - / 38.0 / 38.6; ResNet-50 of width 48 on 29 1584 / - /
+// - / 1601 / 1500, of width 39 on 19 943 / - / - / 917 / 902; ResNet-20 of width 24 on 47 205 / - / - / - / 140, ResNet-18 of width 20 on 57 (1.2 GB) 403 / - / - / - / 367, of width 26 on 47
+// (1.7 GB) 539 / - / - / - / 571, of width 42 on 35 (3.2 GB) 631 / - / - / - / 685.
+// All workers' stretches of a window are read and written at once.  Where they lie multiples of 8 KB apart, or nearly, those of more than eight workers get in each
+// other's way in the memory: ResNet-18 of width 39 with workers 8192 n + 0, 256, 1024, 2048 and 4096 bytes apart on 20 workers 0.83 .. 0.93, 0.95, 0.98, 0.97 and 0.97
+// times as fast as walked, on 12 0.86 .. 0.91, 0.95, 1.01, 1.01 and 0.99, on 7 1.00 .. 1.08, 1.05, 1.08, 1.09 and 1.10.
+static void stream_shape(uint32_t P, uint64_t row, uint32_t* groups, uint32_t* quads) {
+  *groups = *quads = 0;
+  const uint64_t bytes = 5 * P * row, apart = (row + 256) % 8192;      // (rows are multiples of 256 bytes)
+  if (P > kRingMost || (P > 32 && bytes > (1ull << 30)) || (P > 8 && apart <= 512)) return;
+  *groups = P <= 8 ? 2 : 1;
+  *quads = P <= 16 ? 1 : P <= 32 && bytes < (600ull << 20) ? 2 : 4;
 }
 
 static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_stream, bool use_scratch) {
@@ -502,7 +523,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   // carried from step to step: a caller may have written x since the copies were made, and the sender goes by x.
   bool pull = c->cached && !cfg->delivery_delay &&
               !(cfg->topk_ppm && (cfg->xhat_reset || cfg->norm_mode == EVG_NORM_SEPARATE || !copies_fit));
-  bool in_parts = false, one_launch = false, may_be = true, sets_counted = false;
+  bool in_parts = false, one_launch = false, one_shot = false, may_be = true, sets_counted = false;
   bool codes = cfg->topk_ppm && cfg->norm_mode == EVG_NORM_FUSED, choose = false, hist_copies = codes;
   uint64_t need = 0, ring_windows = 0;
   // A tensor that is most of a ring has all workgroups of an update pass add their counts to one histogram, on all XCDs, at some 30 ns for each
@@ -551,10 +572,12 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     groups = quads = 0;
     fine = 1;                      // (a window's sum is one of its sweep's)
     if (in_parts && small_ring) ring_shape(P, windows, longest, cfg->topk_ppm != 0, one_launch, cfg->grad_mode == EVG_GRAD_BUFFER, &groups, &quads);
+    if (may_be && !c->cached && !cfg->topk_ppm && !cfg->delivery_delay && cfg->norm_mode == EVG_NORM_FUSED) stream_shape(P, Npad * 4, &groups, &quads);
+    one_shot = groups && !in_parts;
     if (groups) {
       fine = 4 / groups;
       ring_windows = 0;
-      for (const ChunkDesc& cd : chunks) ring_windows += (cd.len + 256 * groups - 1) / (256 * groups);
+      for (const ChunkDesc& cd : chunks) ring_windows += (cd.lead + cd.len + 256 * groups - 1) / (256 * groups);
     }
     const uint64_t units = ring_windows * P;
     ring_part = std::min<uint32_t>(P, units < 900 ? 2 : units < 3400 ? 4 : kPartMost);
@@ -565,12 +588,16 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     if (groups) ring_part = P;
     need = table_bytes(P, L, chunks.size(), SW, hist_len, Npad, ktot, cfg->topk_ppm != 0,
                        cfg->trigger_kind == EVG_TRIGGER_NORM_DIFF, pull && !(in_parts && ring_part == P), one_launch,
-                       in_parts ? ring_windows : 0, (P + ring_part - 1) / ring_part, codes && (choose || !c->cached),
+                       in_parts || one_shot ? ring_windows : 0, (P + ring_part - 1) / ring_part, codes && (choose || !c->cached),
                        (uint64_t)P * L + (kHistCopies - 1) * P * long_layers.size(), fine);
     return (uint64_t)P * chunks.size() * (SW + 1) <= 0xFFFFFFF0ull && (uint64_t)P * ktot <= 0xFFFFFFF0ull &&
            !(use_scratch && need > kScratchBytes);
   };
   c->on_lines = !c->cached && cut_chunks(true);
+  if (!c->cached && !c->on_lines && one_shot) {                 // no room for a descriptor a window
+    may_be = false;
+    c->on_lines = cut_chunks(true);
+  }
   if (!c->on_lines) (void)cut_chunks(false);
   if (use_scratch && need > kScratchBytes && in_parts && !cfg->topk_ppm) {        // thousands of short tensors: no room for what the parts take
     may_be = false;
@@ -615,10 +642,10 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   }
   one_part |= cfg->topk_ppm ? windows >= 390 && 16ull * P <= windows : windows >= 110 && P < 16;
   const uint64_t parts = one_part ? 1 : std::min((aim + windows - 1) / windows, std::max<uint64_t>(1, P / std::max<uint64_t>(1, fewest)));
-  c->part = (uint32_t)((P + parts - 1) / parts);
+  c->part = one_shot ? P : (uint32_t)((P + parts - 1) / parts);
   // A mailbox equals its sender's xhat wherever a message has arrived, unless messages are under way (delay).  Where xhat is
   // reset at events the walk reads the mailboxes, and does not know of messages applied ahead at the ends of parts.
-  c->walk = !c->cached && !cfg->delivery_delay && !(cfg->xhat_reset && cfg->topk_ppm && parts > 1);
+  c->walk = !c->cached && !one_shot && !cfg->delivery_delay && !(cfg->xhat_reset && cfg->topk_ppm && parts > 1);
   const uint64_t C = chunks.size();
   if ((uint64_t)P * C * (SW + 1) > 0xFFFFFFF0ull || (uint64_t)P * ktot > 0xFFFFFFF0ull) {
     delete c;
@@ -706,9 +733,9 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   TRY_OR_FREE(c->dalloc(&t.last_norm, S, true));
   TRY_OR_FREE(c->dalloc(&t.delta_before, S, true));
   TRY_OR_FREE(c->dalloc(&t.last_event, S, false));
-  TRY_OR_FREE(c->dalloc(&t.valid_l, S, true));
-  TRY_OR_FREE(c->dalloc(&t.valid_r, S, true));
-  TRY_OR_FREE(c->dalloc(&t.fired, S, true));
+  TRY_OR_FREE(c->dalloc(&t.valid_l, (S + 3) / 4 * 4, true));
+  TRY_OR_FREE(c->dalloc(&t.valid_r, (S + 3) / 4 * 4, true));
+  TRY_OR_FREE(c->dalloc(&t.fired, (S + 3) / 4 * 4, true));
   TRY_OR_FREE(c->dalloc(&t.near_tie, S, true));
   TRY_OR_FREE(c->dalloc(&t.ev_full, S, true));
   TRY_OR_FREE(c->dalloc(&t.ev_topk, S, true));
@@ -733,13 +760,14 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   if (pull && !(in_parts && ring_part == P)) TRY_OR_FREE(c->dalloc(&t.xsnap, 2 * (uint64_t)P * Npad, false));
   std::vector<WindowDesc> ring;
   std::vector<ChooseDesc> by_size;
-  if (in_parts) {
+  if (in_parts || one_shot) {
     const uint32_t length = kSweep / fine, sums = SW * fine;
     for (size_t i = 0; i < chunks.size(); ++i)
-      for (uint32_t u = 0; u * length < chunks[i].len; ++u) {
+      for (uint32_t u = 0; u * length < chunks[i].lead + chunks[i].len; ++u) {
         const ChunkDesc& cd = chunks[i];
         const LayerDesc& d = layers[cd.layer];
-        ring.push_back({cd.off + u * length, std::min<uint32_t>(length, cd.len - u * length), cd.layer, cd.j0 + u * length,
+        const uint32_t first = u ? u * length - cd.lead : 0u, end = std::min<uint32_t>(cd.len, (u + 1) * length - cd.lead);
+        ring.push_back({cd.off + first, end - first, cd.layer, cd.j0 + first,
                         (uint32_t)i * sums + u, d.chunk0 * sums, d.nchunks * sums, i == d.chunk0 && u == 0 ? 1u : 0u, d.sig_base,
                         d.numel, d.K, d.msg_off, 0u});
       }
@@ -750,7 +778,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     c->parts.count = (uint32_t)ring.size();
     c->parts.groups = groups;
     c->parts.quads = quads;
-    c->part = ring_part;
+    if (in_parts) c->part = ring_part;
     c->parts.set[0] = c->parts.set[1] = {t.partials, t.xhat_sq, t.delta, t.last_event};
   }
   if (one_launch) {

@@ -66,7 +66,7 @@ struct WindowDesc {
   uint32_t numel, K, msg_off, pad;     // of the tensor; its Top-K message (see LayerDesc)
 };
 constexpr uint32_t kPartMost = 8;      // workers of a part of the ring there
-constexpr uint32_t kRingMost = 16;     // workers of a ring whose windows are one workgroup's
+constexpr uint32_t kRingMost = 64;     // workers of a ring whose windows are one workgroup's: 64 KB of LDS
 struct PartClock { uint32_t k, steps; };       // the next iteration, and the steps completed
 struct PartTables {
   const WindowDesc* windows; uint32_t count;

@@ -1,6 +1,6 @@
-// The update pass of cached rings of at most kRingMost workers (same work and results as k_update): one workgroup owns a window of one
-// tensor in ALL workers, a wavefront has one worker's stretch of it (or two workers'), and what a worker's neighbours hold of it passes
-// between the wavefronts through LDS.
+// The update pass of cached rings of few workers, and of streaming ones that send whole tensors, of at most kRingMost (same work and results as
+// k_update): one workgroup owns a window of one tensor in ALL workers, a wavefront has one worker's stretch of it (or some workers'), and what a
+// worker's neighbours hold of it passes between the wavefronts through LDS.
 //
 // As in the walk of kernels_walk.hip, what a worker last received from a neighbour is that neighbour's xhat.  A ring cut into parts
 // (kernels_parts.hip) reads what lies beyond a part's ends from xhat, and from copies of x that its passes leave; here a third of the reads
@@ -13,6 +13,12 @@
 // wavefronts a SIMD (they spill: 12.6 -> 13 and more), and kernel arguments that are there with the wavefront gain 0.1 us at most.
 // Steps, kernels_parts.hip -> here: the smallest perceptron on 4 workers 6.2 -> 5.4 us, 8 ResNet-20 workers 14.5 -> 12.6, replayed 19.4 -> 18.0,
 // 16 30.1 -> 26.4, 9 of width 24 39.5 -> 34.3, 12 ResNet-18 workers of width 8 14.2 -> 12.6 (the rule: ring_shape).
+//
+// Streaming rings (STREAM): memory, at 5.1 to 5.5 TB/s, where workgroups that go around the ring (kernels_walk.hip) reach 4.8 to 5.1: these take one window
+// after the other, all at once, in the order of their addresses, and a ring of few windows has as many wavefronts as workers.  The
+// trigger tests are a launch of their own, so that xhat is not read where the whole tensor is sent.  Walked -> here: 16 ResNet-18 workers 873 -> 817 .. 845 us,
+// with given gradients 1035 -> 1010 .. 1022, 7 of width 23 with given gradients and plain SGD 54.0 -> 47.5, 13 ResNet-20 of width 24 49.6 -> 37.5 (the rule:
+// stream_shape).  Runs of neighbouring windows for an XCD: no faster (2 or 4), 3 % slower (8 and more).
 #include "message_device.h"
 #include "quad_device.h"
 #include "trigger_device.h"
@@ -42,15 +48,17 @@ struct RingArgs {
 // (message_device.h).  The pass leaves the codes of the new rank keys and counts those about the anchor.
 // G: groups of 256 elements in a window.  Q: float4s of a thread.
 // R and A come first, as all workgroups wait for them; T is for the bookings.
-template <int DIST, bool GRADBUF, int NORM, bool TESTS, bool TOPK, int G, int Q>
+template <int DIST, bool GRADBUF, int NORM, bool TESTS, bool TOPK, int G, int Q, bool STREAM>
 __global__ __launch_bounds__(1024) void k_update_ring(RingArgs R, StepArgs A, Tables T) {
   static_assert(!(TESTS && TOPK), "selections follow the tests");
+  static_assert(!(STREAM && (TESTS || TOPK)), "cached rings only");
   constexpr int WQ = Q > G ? Q / G : 1;                    // workers of a wavefront
   constexpr int GQ = Q > G ? G : Q;                        // groups of each that it has
   constexpr int SPLIT = G / GQ;                            // wavefronts of a worker
   constexpr int FIRST = G == 4 ? 2 : 4;                    // sums of a test that a lane asks for at once
   extern __shared__ float4 held[];                         // [P][G][64] what the neighbours hold from this iteration on
   __shared__ uint32_t codes[TESTS ? kRingMost : 1];
+  __shared__ uint64_t spiky;
   __shared__ double ws[SPLIT > 1 ? kRingMost * SPLIT : 1], ws_hat[SPLIT > 1 && NORM == 3 ? kRingMost * SPLIT : 1];
   const WindowDesc wd = R.windows[blockIdx.x];
   const uint32_t P = R.P, layer = wd.layer, lane = lane_id();
@@ -79,20 +87,11 @@ __global__ __launch_bounds__(1024) void k_update_ring(RingArgs R, StepArgs A, Ta
       for (int q = 0; q < FIRST; ++q)
         p[i][q] = load_f64((turn ? R.partials[1] : R.partials[0]) + (size_t)some(i) * R.sums_row + wd.sum0, wd.sums * 8, lane * 8 + q * 512);
   }
-  // (two scalar registers an array; lanes past the window ask for its first element.  Tensors are padded to 4 elements)
-  auto at = [&](float* arena, uint32_t r) { return arena + (size_t)r * R.row + wd.off; };
-  auto elem = [&](int q) { return (g0 + q % GQ) * 256u + lane * 4; };
-  auto byte = [&](int q) { return elem(q) < wd.len ? elem(q) * 4 : 0u; };
-  Quad x[Q], v[Q], h[Q], g[Q];
-#pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    const uint32_t r = some(q / GQ);
-    x[q] = load_at(at(R.x, r), byte(q));
-    h[q] = load_at(at(R.xhat, r), byte(q));
-    v[q] = load_at(at(A.plain_sgd ? R.x : R.vel, r), byte(q));
-    if (GRADBUF) g[q] = load_at(at(const_cast<float*>(A.grad), r), byte(q));
-  }
-  // its workers' state, the same in all lanes
+  // its workers' state, the same in all lanes.  Where xhat is only asked for once a flag is known it comes by scalar loads of the word it is in, as
+  // loads of lanes are waited for in their order
+  auto flag = [](const uint8_t* flags, uint32_t i) {
+    return STREAM ? reinterpret_cast<const uint32_t*>(flags)[i >> 2] >> (8 * (i & 3u)) & 255u : (uint32_t)flags[i];
+  };
   uint32_t code[WQ], from_l[WQ], from_r[WQ];
   float d[WQ], dl[WQ];
   int32_t khat[WQ];
@@ -101,16 +100,37 @@ __global__ __launch_bounds__(1024) void k_update_ring(RingArgs R, StepArgs A, Ta
   for (int i = 0; i < WQ; ++i) {
     const uint32_t seg = some(i) * R.L + layer;
     const uint32_t left = some(i) == 0 ? P - 1 : some(i) - 1, right = some(i) + 1 == P ? 0u : some(i) + 1;
-    from_l[i] = R.valid_l[seg];
-    from_r[i] = R.valid_r[seg];
+    from_l[i] = flag(R.valid_l, seg);
+    from_r[i] = flag(R.valid_r, seg);
     if (TESTS) {
       dl[i] = (turn ? R.delta[1] : R.delta[0])[seg];
       khat[i] = (turn ? R.last_event[1] : R.last_event[0])[seg];
       if (NORM == 2) hat_sq[i] = (turn ? R.xhat_sq[1] : R.xhat_sq[0])[seg];
     } else {
-      code[i] = R.fired[seg];
-      from_l[i] |= R.fired[left * R.L + layer] == 1 ? 1u : 0u;
-      from_r[i] |= R.fired[right * R.L + layer] == 1 ? 1u : 0u;
+      code[i] = flag(R.fired, seg);
+      from_l[i] |= flag(R.fired, left * R.L + layer) == 1 ? 1u : 0u;
+      from_r[i] |= flag(R.fired, right * R.L + layer) == 1 ? 1u : 0u;
+    }
+  }
+  // (two scalar registers an array; lanes past the window ask for its first element.  Tensors are padded to 4 elements)
+  auto at = [&](float* arena, uint32_t r) { return arena + (size_t)r * R.row + wd.off; };
+  auto elem = [&](int q) { return (g0 + q % GQ) * 256u + lane * 4; };
+  auto byte = [&](int q) { return elem(q) < wd.len ? elem(q) * 4 : 0u; };
+  Quad x[Q], v[Q], h[Q], g[Q];
+  auto load = [](const float* a, uint32_t b) { return STREAM ? load_nt_at(a, b) : load_at(a, b); };
+  auto store = [](float* a, uint32_t b, const Quad& q) { STREAM ? store_nt_at(a, b, q) : store_at(a, b, q); };
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const uint32_t r = some(q / GQ);
+    x[q] = load(at(R.x, r), byte(q));
+    if (!STREAM) h[q] = load(at(R.xhat, r), byte(q));
+    if (!STREAM || !A.plain_sgd) v[q] = load(at(A.plain_sgd ? R.x : R.vel, r), byte(q));
+    if (GRADBUF) g[q] = load(at(const_cast<float*>(A.grad), r), byte(q));
+  }
+  if (STREAM) {                                            // xhat is not read where the whole tensor is sent: lanes past the end, all of them, get zeros
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      h[q] = load_quad<true>(at(R.xhat, some(q / GQ)), code[q / GQ] == 1 ? 0u : (wd.len + 3) / 4 * 16, elem(q) * 4);
     }
   }
   // The selections: lane q holds what float4 q of the wavefront's threads goes by, its worker's threshold and the places of its group's winners
@@ -139,11 +159,19 @@ __global__ __launch_bounds__(1024) void k_update_ring(RingArgs R, StepArgs A, Ta
   if (!GRADBUF) {
     const double decay_pow = A.from_device ? T.decay_tab[now.k < T.decay_len ? now.k : T.decay_len - 1] : A.decay_pow;
     const float sg = (float)(wd.sig_base * decay_pow);
+    uint64_t spikes = 0;                                   // bit r: worker r
+    if (A.spike_prob > 0.0f) {                             // uniform; one wavefront draws for all workers (each for its own: as much again as its gradients take)
+      if (wave == 0) {
+        const uint64_t all = __ballot(has_spike(A, now.k, lane));
+        if (lane == 0) spiky = all;
+      }
+      __syncthreads();
+      spikes = spiky;
+    }
 #pragma unroll
     for (int q = 0; q < Q; ++q)
       if (exists(q / GQ) && (g0 + q % GQ) * 256u < wd.len)             // uniform
-        draw_gradient<DIST>(A, wd.j0 + elem(q), layer, now.k, worker(q / GQ), sg,
-                            A.spike_prob > 0.0f && has_spike(A, now.k, worker(q / GQ)), g[q].v);
+        draw_gradient<DIST>(A, wd.j0 + elem(q), layer, now.k, worker(q / GQ), sg, ((spikes >> worker(q / GQ)) & 1u) != 0, g[q].v);
   }
 
   // ---- the trigger tests ----
@@ -234,9 +262,9 @@ __global__ __launch_bounds__(1024) void k_update_ring(RingArgs R, StepArgs A, Ta
       if (code[i] != 0) {                                  // uniform
         if (TOPK && code[i] == 2) (void)put_message<true>(T, r, wd.msg_off, mark(place, q), mark(count, q), win[q], x[q].v, wd.j0 + e);
         if (puts[q] && e < wd.len) {
-          store_at(at(R.xhat, r), e * 4, h[q]);
-          store_at(at(R.mbox_l, right), e * 4, h[q]);
-          store_at(at(R.mbox_r, left), e * 4, h[q]);
+          store(at(R.xhat, r), e * 4, h[q]);
+          store(at(R.mbox_l, right), e * 4, h[q]);
+          store(at(R.mbox_r, left), e * 4, h[q]);
         }
       }
       double s = 0.0, s2 = 0.0;
@@ -257,8 +285,8 @@ __global__ __launch_bounds__(1024) void k_update_ring(RingArgs R, StepArgs A, Ta
         }
       }
       if (e < wd.len) {
-        store_at(at(R.x, r), e * 4, x[q]);
-        if (!A.plain_sgd) store_at(at(R.vel, r), e * 4, v[q]);
+        store(at(R.x, r), e * 4, x[q]);
+        if (!A.plain_sgd) store(at(R.vel, r), e * 4, v[q]);
       }
       sum += wave_sum_dpp(s);
       if (NORM == 3) sum_hat += wave_sum_dpp(s2);
@@ -313,21 +341,30 @@ __global__ __launch_bounds__(1024) void k_update_ring(RingArgs R, StepArgs A, Ta
 namespace {
 struct Launch { const Tables& t; const StepArgs& a; RingArgs r; uint32_t windows, dist, grad_mode; hipStream_t s; };
 
-template <int NORM, bool TESTS, bool TOPK, int G, int Q>
+template <int NORM, bool TESTS, bool TOPK, int G, int Q, bool STREAM = false>
 hipError_t ring_kernel(Launch l) {
   const uint32_t per = Q > G ? Q / G : 1, split = Q > G ? 1 : G / Q;
   const dim3 grid(l.windows), block((l.t.P + per - 1) / per * split * 64);
   const size_t lds = (size_t)l.t.P * (G * 1024 + (TOPK ? (kCodeBins + 1) * 4 : 0));
   if (block.x > 1024 || l.t.P > kRingMost) return hipErrorInvalidValue;
   l.r.threads = block.x;
-  if (l.grad_mode == 1) k_update_ring<0, true, NORM, TESTS, TOPK, G, Q><<<grid, block, lds, l.s>>>(l.r, l.a, l.t);
-  else if (l.dist == 0) k_update_ring<0, false, NORM, TESTS, TOPK, G, Q><<<grid, block, lds, l.s>>>(l.r, l.a, l.t);
-  else k_update_ring<1, false, NORM, TESTS, TOPK, G, Q><<<grid, block, lds, l.s>>>(l.r, l.a, l.t);
+  if (l.grad_mode == 1) k_update_ring<0, true, NORM, TESTS, TOPK, G, Q, STREAM><<<grid, block, lds, l.s>>>(l.r, l.a, l.t);
+  else if (l.dist == 0) k_update_ring<0, false, NORM, TESTS, TOPK, G, Q, STREAM><<<grid, block, lds, l.s>>>(l.r, l.a, l.t);
+  else k_update_ring<1, false, NORM, TESTS, TOPK, G, Q, STREAM><<<grid, block, lds, l.s>>>(l.r, l.a, l.t);
   return hipGetLastError();
 }
 
 template <int NORM, bool TESTS, bool TOPK>
 hipError_t ring_of(const Launch& l, uint32_t groups, uint32_t quads) {
+  if constexpr (!TESTS && !TOPK) {
+    if (!l.a.cached) {
+      if (groups == 2 && quads == 1) return ring_kernel<NORM, false, false, 2, 1, true>(l);
+      if (groups == 1 && quads == 1) return ring_kernel<NORM, false, false, 1, 1, true>(l);
+      if (groups == 1 && quads == 2) return ring_kernel<NORM, false, false, 1, 2, true>(l);
+      if (groups == 1 && quads == 4) return ring_kernel<NORM, false, false, 1, 4, true>(l);
+      return hipErrorInvalidValue;
+    }
+  }
   if (groups == 2 && quads == 2) return ring_kernel<NORM, TESTS, TOPK, 2, 2>(l);
   if constexpr (TOPK) {
     if (groups == 1 && quads == 2) return ring_kernel<NORM, TESTS, TOPK, 1, 2>(l);

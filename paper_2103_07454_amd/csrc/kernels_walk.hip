@@ -1,4 +1,4 @@
-// The update pass of rings that stream from memory (same work and results as k_update): one
+// The update pass of rings that stream from memory and send Top-K messages, or are too large for kernels_ring.hip (same work and results as k_update): one
 // workgroup owns a window of one tensor and walks it around the ring, worker by worker.
 //
 // What a worker last received from a neighbour IS that neighbour's xhat (same-iteration delivery, only sent entries count as

@@ -40,6 +40,20 @@ __device__ __forceinline__ void store_at(float* a, uint32_t byte, const Quad& q)
   for (int i = 0; i < 4; ++i) t[i] = q.v[i];
   *reinterpret_cast<f32x4*>(reinterpret_cast<char*>(a) + byte) = t;
 }
+// ... and non-temporal.
+__device__ __forceinline__ Quad load_nt_at(const float* a, uint32_t byte) {
+  const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(a) + byte));
+  Quad q;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) q.v[i] = t[i];
+  return q;
+}
+__device__ __forceinline__ void store_nt_at(float* a, uint32_t byte, const Quad& q) {
+  f32x4 t;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) t[i] = q.v[i];
+  __builtin_nontemporal_store(t, reinterpret_cast<f32x4*>(reinterpret_cast<char*>(a) + byte));
+}
 __device__ __forceinline__ double load_f64(const double* at, uint32_t bytes, uint32_t byte) {
   const auto t = __builtin_amdgcn_raw_buffer_load_b64(window(at, bytes), (int)byte, 0, 0);
   return __longlong_as_double((long long)(((uint64_t)t[1] << 32) | t[0]));

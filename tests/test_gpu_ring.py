@@ -1,6 +1,6 @@
-"""Cached rings of at most 16 workers are updated by one workgroup for each window of the whole ring; windows are of 256, 512
-or 1024 elements, and a thread has one float4 or two.  Checked against the oracle at the edges of groups, windows and chunks,
-for rings of 3 to 16 workers, by sizes that lead to each shape of a workgroup (evg_api.hip: ring_shape)."""
+"""Cached rings of at most 16 workers, and streaming ones with whole sends, are updated by one workgroup for each window of the whole
+ring; windows are of 256, 512 or 1024 elements, and a thread has one float4 or a few.  Checked against the oracle at the edges of groups, windows and chunks,
+by sizes that lead to each shape of a workgroup (evg_api.hip: ring_shape, stream_shape)."""
 import numpy as np
 import pytest
 
@@ -23,12 +23,12 @@ def _workload(P, sizes, **kw):
     return inputs.Workload("ring", P, tensors, 7, sigma0=0.05, decay=0.9, seed=P, **kw)
 
 
-def _check(evg, oracle_mod, w, both=None, given=False):
+def _check(evg, oracle_mod, w, both=None, given=False, **gpu):
     import torch
     from helpers import lockstep
     both = both or {}
     x0 = inputs.replicate(w.x0(), w.P)
-    ring = evg.Ring.from_workload(w, x0, mailbox_fill=float("nan"), grad_mode=int(given), **both)
+    ring = evg.Ring.from_workload(w, x0, mailbox_fill=float("nan"), grad_mode=int(given), **both, **gpu)
     orc = oracle_mod.Oracle.from_workload(w, x0, grad_mode=int(given), **both)
     host = dev = None
     if given:
@@ -94,3 +94,39 @@ def test_checkpoints_with_short_windows(evg, sizes, kw):
     for r in rings[1:] + others:
         for name in ("x", "xhat", "vel", "mbox_l", "mbox_r"):
             assert np.array_equal(r.state(name), rings[0].state(name)), name
+
+
+# streaming rings: windows that begin on cache lines, workgroups of every shape (8, 16, 32 workers and more), tensors shorter than their lead
+STREAMED = [(3, EDGES), (8, EDGES * 3 + [8191, 8193, 20_001]), (9, EDGES * 2), (16, [5, 31, 33] + EDGES), (17, EDGES), (32, [1000, 3, 8192]), (33, [1021, 7]),
+            (64, [257, 2, 513])]
+
+
+@pytest.mark.parametrize("P,sizes", STREAMED, ids=[f"{P}x{len(s)}" for P, s in STREAMED])
+@pytest.mark.parametrize("kw", [dict(spike_prob=0.3, spike_gain=4.0), dict(momentum=0.0, dist=1), dict(trigger_kind=1), dict(given=True)],
+                         ids=["normal", "student_plain", "norms", "given"])
+def test_streamed_whole_sends(evg, oracle_mod, P, sizes, kw):
+    kw = dict(kw)
+    both = {k: kw.pop(k) for k in ("trigger_kind",) if k in kw}
+    given = kw.pop("given", False)
+    _check(evg, oracle_mod, _workload(P, sizes, **kw), both, given, access_mode=evg.ACCESS_STREAM)
+
+
+@pytest.mark.parametrize("P", [5, 16, 40])
+def test_replays_of_streamed_steps(evg, P):
+    import torch
+    w = _workload(P, EDGES, spike_prob=0.3, spike_gain=4.0)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        a = evg.Ring.from_workload(w, mailbox_fill=0.0, stream=stream, access_mode=evg.ACCESS_STREAM)
+    b = evg.Ring.from_workload(w, mailbox_fill=0.0, access_mode=evg.ACCESS_STREAM)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        a.step_next()
+    for k in range(6):
+        g.replay()
+        b.step(k)
+        torch.cuda.synchronize()
+        assert np.array_equal(a.decisions()["fired"], b.decisions()["fired"]), k
+    for name in ("x", "xhat", "vel", "mbox_l", "mbox_r"):
+        assert np.array_equal(a.state(name), b.state(name)), name
