@@ -9,7 +9,7 @@ constexpr int kThreads = 256;          // 4 wavefronts of 64 lanes
 constexpr int kLaneElems = 4;          // one float4 per lane and sweep
 constexpr int kSweep = kThreads * kLaneElems;   // elements one workgroup covers per sweep
 constexpr uint32_t kLineElems = 32;    // floats of a 128-byte cache line
-constexpr int kHistBins = 2048;        // histogram of a selection pass: the second takes 11 bits of a key
+constexpr int kHistBins = 2048;        // histogram of a selection pass: the second takes 11 bits of a key, the last what is left, 6, 9 or 10
 constexpr int kFirstBins = 1280;       // the first (see first_bins)
 constexpr uint32_t kCoarseBits = 21, kFineBits = 17;                  // bits of a key below its coarse and fine bins
 constexpr uint32_t kPlainBits = 20;                                   // below the bins of rings without anchors
@@ -20,7 +20,6 @@ constexpr uint32_t kHistCopiesFrom = 131072;      // elements of such a tensor a
 constexpr uint32_t kNoLayer = 0xFFFFFFFFu;
 constexpr uint32_t kFirstCode = 64, kCodeBins = 128;                  // key codes that are counted where there are no such histograms,
 constexpr uint32_t kCodeStride = 256;                                 // in eight copies, each of those codes and of all above
-constexpr int kLastBins = 1024;        // the last takes what is left, 6 or 10 bits
 constexpr uint32_t kStageCap = 2048;   // staged keys of a chunk at most
 // Threshold key that no key reaches (they have 31 bits).  A selection ends with it where it sees that it would not find exactly K
 // winners: the histogram and the key codes that the last update pass left do not fit x and xhat, which the caller has written since.

@@ -14,7 +14,7 @@
 //                   bin b, and the keys IN bin b (a sixty-fourth of an octave where the threshold was expected, some 0.4 % of the
 //                   tensor), whose next 11 bits it counts.  From the key codes of the last update pass, 1 byte an element
 //                   instead of 8, where bin b has a code: only the keys in it are fetched then
-//   k_topk_low      the last bits of the in-bin keys under the prefix found so far -> threshold key
+//   k_topk_low      the last bits of the in-bin keys under the prefix found so far -> threshold key (last_bin)
 //   k_topk_count    keys above and equal to the threshold per group, as running totals over a chunk
 //   k_topk_scan     the same over a tensor's chunks, and the cut
 //   k_topk_apply    messages written and applied ahead of the update pass, where that pass cannot
@@ -22,6 +22,11 @@
 // walk, which writes the codes, 1156 -> 1173), 64 4903 -> 4538, 8 ResNet-50 workers, 1 %, Student-t 1269 -> 1199.  Of the keys' bins
 // 128 are fine: with 256 the walk merges more counts (ResNet-50 1220), with a thirty-second of an octave each the stage fetches
 // more (64 workers 4647); bins of an eighth and codes that divide them cost a launch more and 1317 where 1277 is now.
+// The many launches are bound by their chains of dependent reads, which go together where they can, and by vector instructions in k_topk_stage.
+// 64 ResNet-18 workers, 10 %, and 8 ResNet-50 workers, 1 %, us a launch, before -> now: k_topk_decide 28 -> 22 and 10 -> 9 (bins asked for ahead of the
+// test), k_topk_stage 360 -> 349 and 70 -> 60 (compare_codes, one list of a lane's two loads), k_topk_low 27 -> 21 and 9 -> 7.5, and a launch
+// of 6 and 5 less (last_bin).  Steps: 16 ResNet-18 workers with given gradients, 10 % 1269 -> 1259, 8 ResNet-50 1160 -> 1150, 64 ResNet-18
+// 4547 -> 4538, 42 ResNet-20 of width 18, 14 % 210 -> 204, 31 ResNet-50 of width 46 with spikes, 0.5 % 2232 -> 2208.
 // (The selection used to stage every possible winner as (index, value) and to compact the messages from there;
 // the update passes then scattered three messages each into LDS.)
 // Cached rings whose tensors are not too long make the whole selection in one launch, kernels_choose.hip.
@@ -106,12 +111,31 @@ __global__ __launch_bounds__(kThreads) void k_topk_hist(Tables T, StepArgs A) {
 
 // One workgroup per tensor that sends a Top-K message: find the bin that holds the krem-th largest key, append it to the
 // prefix, keep what is still to be taken inside that bin, and clear the histogram for the next pass.
-// PASS 0: the bins of first_bins (FINE: the ring has anchors) or a key's upper 11 bits, PASS 1: the next 11 bits, PASS 2: the rest.
-// `counted`: the histogram, if it has been taken from T.hist.
+// PASS 0: the bins of first_bins (FINE: the ring has anchors) or a key's upper 11 bits, PASS 1: the next 11 bits.  (The rest: last_bin.)
+// `counted`: the histogram, if it has been taken from T.hist.  What else it goes by is asked for by look_at, ahead of the test where there is one.
+template <int PASS, bool FINE>
+struct Bounds {
+  static constexpr int NB = PASS == 0 && FINE ? kFirstBins : kHistBins, PER = NB / kThreads;
+  uint32_t cnt[PER], krem, anchor, prefix, bits;           // (cnt: from this thread's highest bin downwards)
+};
 template <int PASS, bool FINE = false>
-__device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t code, uint32_t* ws, const uint32_t* counted) {
-  constexpr int NB = PASS == 0 ? FINE ? kFirstBins : kHistBins : PASS == 1 ? kHistBins : kLastBins;
-  constexpr int PER = NB / kThreads;
+__device__ __forceinline__ Bounds<PASS, FINE> look_at(const Tables& T, uint32_t seg, bool counted) {
+  Bounds<PASS, FINE> b;
+  const uint32_t* gh = T.hist + (size_t)seg * kHistBins;
+  if (!counted) {                                          // uniform
+#pragma unroll
+    for (int j = 0; j < b.PER; ++j) b.cnt[j] = gh[b.NB - 1 - threadIdx.x * b.PER - j];
+  }
+  b.krem = PASS == 0 ? T.layers[seg % T.L].K : T.sel_krem[seg];
+  b.anchor = PASS == 0 && FINE ? T.anchor[seg] : kNoAnchor;
+  b.prefix = PASS ? T.sel_prefix[seg] : 0u;
+  b.bits = PASS ? T.sel_left[seg] & 255u : 0u;
+  return b;
+}
+template <int PASS, bool FINE>
+__device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t code, uint32_t* ws, const uint32_t* counted,
+                                         Bounds<PASS, FINE> b) {
+  constexpr int NB = Bounds<PASS, FINE>::NB, PER = Bounds<PASS, FINE>::PER;
   uint32_t* gh = T.hist + (size_t)seg * kHistBins;
   if (code != 2) {          // uniform for the workgroup
     // pass A histograms are built for every tensor when the update pass makes them:
@@ -120,25 +144,15 @@ __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t
       for (uint32_t b = threadIdx.x; b < (uint32_t)NB; b += kThreads) gh[b] = 0;
     return;
   }
-  const uint32_t krem = PASS == 0 ? T.layers[seg % T.L].K : T.sel_krem[seg];
-  // asked for along with the counts, not by the thread that finds the bin: a load less in the chain of launches
-  const uint32_t anchor = PASS == 0 && FINE ? T.anchor[seg] : kNoAnchor;
-  const uint32_t prefix = PASS ? T.sel_prefix[seg] : 0u, bits = PASS == 1 ? T.sel_left[seg] & 255u : 0u;
+  const uint32_t krem = b.krem, anchor = b.anchor, prefix = b.prefix, bits = b.bits;
   const uint32_t top = NB - 1 - threadIdx.x * PER;   // this thread's highest bin
-  uint32_t cnt[PER], local = 0;
-  if (PASS == 0 && counted) {
+  uint32_t* const cnt = b.cnt;
+  uint32_t local = 0;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      cnt[j] = counted[top - j];
-      local += cnt[j];
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      cnt[j] = gh[top - j];
-      gh[top - j] = 0;
-      local += cnt[j];
-    }
+  for (int j = 0; j < PER; ++j) {
+    if (PASS == 0 && counted) cnt[j] = counted[top - j];
+    else gh[top - j] = 0;
+    local += cnt[j];
   }
   uint32_t total;
   const uint32_t above = block_excl_scan<4>(local, ws, &total);   // keys in higher bins
@@ -168,7 +182,7 @@ __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t
       T.sel_left[seg] = kPlainBits;
     } else {
       // (a selection that has ended stays so)
-      if (prefix != kNoThreshold) T.sel_prefix[seg] = prefix + (PASS == 1 ? bin << (bits - 11u) : bin);
+      if (prefix != kNoThreshold) T.sel_prefix[seg] = prefix + (bin << (bits - 11u));
     }
   }
 }
@@ -176,7 +190,7 @@ __device__ __forceinline__ void pick_bin(const Tables& T, uint32_t seg, uint32_t
 template <int PASS>
 __global__ __launch_bounds__(kThreads) void k_topk_pick(Tables T) {
   __shared__ uint32_t ws[4];
-  pick_bin<PASS>(T, blockIdx.x, T.fired[blockIdx.x], ws, nullptr);
+  pick_bin<PASS, false>(T, blockIdx.x, T.fired[blockIdx.x], ws, nullptr, look_at<PASS>(T, blockIdx.x, false));
 }
 
 // Rings whose update pass has built pass A's histograms: trigger test and pass A's bin in one
@@ -187,10 +201,11 @@ __global__ __launch_bounds__(kThreads) void k_topk_decide(Tables T, StepArgs A) 
   __shared__ uint32_t ws[4], code, counted[NB];
   const uint32_t seg = blockIdx.x, layer = seg % T.L;
   const bool copies = layer == T.long_layer[0] || layer == T.long_layer[1];        // uniform
+  const Bounds<0, FINE> bounds = look_at<0, FINE>(T, seg, copies);
   if (wave_id() == 0) {
     double acc, acc_hat;
     bool hat_sums;
-    const uint32_t anchor = FINE ? T.anchor[seg] : kNoAnchor, k = tested_k(T, A);
+    const uint32_t anchor = bounds.anchor, k = tested_k(T, A);
     const int32_t khat = T.last_event[seg];
     segment_sums(T, A, seg, &acc, &acc_hat, &hat_sums);
     if (lane_id() == 0) {
@@ -225,15 +240,15 @@ __global__ __launch_bounds__(kThreads) void k_topk_decide(Tables T, StepArgs A) 
     }
   }
   __syncthreads();
-  pick_bin<0, FINE>(T, seg, code, ws, copies ? counted : nullptr);
+  pick_bin<0, FINE>(T, seg, code, ws, copies ? counted : nullptr, bounds);
   if (seg == 0 && threadIdx.x == 0) close_step(T, A);
 }
 
 // Staging from the key codes, 1 byte an element instead of 8: what has the code of the threshold bin is listed by its
 // position in the chunk, and only those keys are fetched.  A key that is not what its code says (the caller has written x
 // since) ends the selection.  Sixteen codes a lane in one load, sums by rotations and one place a wavefront: four codes a
-// lane with ballots and a place for each took 10 us more for 16 ResNet-18 workers (a step 1272 -> 1262 us; 8 ResNet-50 1199 -> 1195, 64
-// ResNet-18 workers the same).  Bound by the chain descriptor, decision, codes, keys, slot.
+// lane with ballots and a place for each took 10 us more for 16 ResNet-18 workers.  Bound by vector instructions and the chain descriptor,
+// decision, codes, keys, slot; with 10 % sent by the lines of x and xhat that hold the keys.
 template <int SWEEPS>
 __device__ __forceinline__ void stage_by_codes(const Tables& T, const StepArgs& A, const WorkItem& wi, uint32_t begin, uint32_t code,
                                                uint32_t* list, uint32_t* listed) {
@@ -247,44 +262,37 @@ __device__ __forceinline__ void stage_by_codes(const Tables& T, const StepArgs& 
     sixteen[u] = __builtin_amdgcn_raw_buffer_load_b128(codes, (int)(p < positions ? p : 0xFFFFFFF0u), 0, 2);
   }
   __syncthreads();
-  uint32_t in[LOADS], mine = 0;                            // which of a lane's sixteen have the code
+  static_assert(LOADS <= 2, "two loads share a register's bits");
+  const bool ends = wi.cd.lead != 0 || positions < SWEEPS * (uint32_t)kSweep;      // uniform: not all positions are elements of the chunk
+  uint32_t in = 0, above = 0;                              // which of a lane's have the code: bit 8 b + 4 u + w for the b-th of the w-th four
+#pragma unroll
+  for (int u = 0; u < LOADS; ++u) {
+    if (ends) {                                            // what is no element gets code 0, which no bin has that is told by codes
+#pragma unroll
+      for (uint32_t w = 0; w < 4; ++w) {
+        const uint32_t at = (u * kThreads + threadIdx.x) * 16 + 4 * w, left = at < wi.cd.lead || at >= positions ? 0u : positions - at;
+        if (left < 4u) sixteen[u][w] &= (1u << 8 * left) - 1u;
+      }
+    }
+    const Compared c = compare_codes(sixteen[u], code);
+    in |= c.in << 4 * u;
+    above |= c.above << 16 * u;
+  }
+  above = row_sum(above);                                  // sixteen lanes have a group of 256 positions
 #pragma unroll
   for (int u = 0; u < LOADS; ++u) {
     const uint32_t p = (u * kThreads + threadIdx.x) * 16;
-    uint32_t above = 0;
-    in[u] = 0;
-#pragma unroll
-    for (uint32_t w = 0; w < 4; ++w) {
-      // what is no element of the chunk gets code 0, which no bin has that is told by codes
-      const uint32_t at = p + 4 * w, left = at < wi.cd.lead || at >= positions ? 0u : positions - at;
-      const uint32_t four = left < 4u ? sixteen[u][w] & ((1u << 8 * left) - 1u) : sixteen[u][w], more = (255u - code) * 0x10001u;
-      // bytes 0 and 2, 1 and 3, in halves of a register: adding 255 - code sets bit 8 of those above the code, 256 - code of
-      // those that have it too
-      const uint32_t a = (four & 0x00FF00FFu) + more, b = ((four >> 8) & 0x00FF00FFu) + more;
-      above += (a & 0x01000100u) + (b & 0x01000100u);
-      const uint32_t ia = ((a + 0x10001u) ^ a) & 0x01000100u, ib = ((b + 0x10001u) ^ b) & 0x01000100u;
-      in[u] |= (ia >> 8 | ib >> 7) << 2 * w;               // element 4 w + i: bit 2 w + (i & 1) + 16 (i >> 1)
-    }
-    mine += (uint32_t)__popc(in[u]);
-    above = (above >> 8 & 0xFu) + (above >> 24);           // sixteen lanes have a group of 256 positions
-    above += (uint32_t)__builtin_amdgcn_mov_dpp((int)above, 0x128, 0xF, 0xF, true);   // row_ror:8, 4, 2, 1
-    above += (uint32_t)__builtin_amdgcn_mov_dpp((int)above, 0x124, 0xF, 0xF, true);
-    above += (uint32_t)__builtin_amdgcn_mov_dpp((int)above, 0x122, 0xF, 0xF, true);
-    above += (uint32_t)__builtin_amdgcn_mov_dpp((int)above, 0x121, 0xF, 0xF, true);
-    if ((lane_id() & 15u) == 0 && p < SWEEPS * (uint32_t)kSweep) T.group[(size_t)wi.w * (T.SW * 4) + (p >> 8)] = above;
+    if ((lane_id() & 15u) == 0 && p < SWEEPS * (uint32_t)kSweep) T.group[(size_t)wi.w * (T.SW * 4) + (p >> 8)] = above >> 16 * u & 0xFFFFu;
   }
-  const uint32_t upto = wave_incl_scan(mine);
+  const uint32_t mine = (uint32_t)__popc(in), upto = wave_incl_scan(mine);
   uint32_t next = 0;
   if (lane_id() == 63) next = atomicAdd(listed, upto);
   next = (uint32_t)__builtin_amdgcn_readlane((int)next, 63) + upto - mine;
-#pragma unroll
-  for (int u = 0; u < LOADS; ++u) {
-    while (in[u]) {
-      const uint32_t b = (uint32_t)__ffs((int)in[u]) - 1u;
-      in[u] &= in[u] - 1u;
-      if (next < kStageCap) list[next] = (u * kThreads + threadIdx.x) * 16 + (b >> 1 & 7u) * 4 + (b & 1u) + (b >> 4) * 2;
-      ++next;
-    }
+  while (in) {
+    const uint32_t b = (uint32_t)__ffs((int)in) - 1u;
+    in &= in - 1u;
+    if (next < kStageCap) list[next] = (b >> 2 & 1u) * (kThreads * 16) + threadIdx.x * 16 + (b & 3u) * 4 + (b >> 3);
+    ++next;
   }
   __syncthreads();
   const uint32_t n = *listed;
@@ -419,30 +427,46 @@ __device__ __forceinline__ void keys_at(const Tables& T, const StepArgs& A, uint
 // The kernels below walk a chunk's staged keys, a few hundred, so one wavefront per chunk does it without
 // workgroup barriers.  Four independent wavefronts share a workgroup.
 
-// The chunk of this wavefront (blockIdx.y = worker); false: none, or its tensor sends no Top-K message.
-__device__ __forceinline__ bool wave_item(const Tables& T, WorkItem* wi) {
+// A wavefront's chunk (blockIdx.y = worker) and its first 512 keys in the threshold bin, which are asked for before it is known
+// that its tensor sends a Top-K message, and so is what too(seg) does: bound by descriptor, then keys, decision and the rest at once
+// instead of one behind the other.
+struct Staged { WorkItem wi; uint32_t n; u32x4 e[2]; bool sends; };
+__device__ __forceinline__ u32x4 four_staged(const Tables& T, const WorkItem& wi, uint32_t n, uint32_t q) {
+  return __builtin_amdgcn_raw_buffer_load_b128(window(T.stage_key + stage_slot(T, wi.r, wi.cd.off), (n + 3) / 4 * 16), (int)(q * 4), 0, 0);
+}
+template <typename F>
+__device__ __forceinline__ bool wave_item(const Tables& T, Staged* s, F&& too) {
   const uint32_t c = blockIdx.x * (kThreads / 64) + (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_id());
   if (c >= T.C) return false;
-  *wi = work_item(T, blockIdx.y, c);
-  return T.fired[wi->seg] == 2;
+  s->wi = work_item(T, blockIdx.y, c);
+  const uint32_t n = T.stage_n[s->wi.w], held = n <= stage_cap(s->wi.cd.len) ? n : 0u;      // (a silent tensor's is an earlier step's, or nobody's)
+#pragma unroll
+  for (uint32_t u = 0; u < 2; ++u) s->e[u] = four_staged(T, s->wi, held, 256 * u + 4 * lane_id());
+  const uint32_t code = T.fired[s->wi.seg];
+  too(s->wi);
+  s->sends = __builtin_amdgcn_readfirstlane((int)code) == 2;
+  s->n = s->sends ? n : 0u;
+  return true;
 }
 
 // f(low 20 bits and group) for every key of the chunk in the threshold bin; all(key, group) instead, for every key, where
 // nothing is staged.
 template <typename F, typename G>
-__device__ __forceinline__ void in_bin_keys(const Tables& T, const StepArgs& A, const WorkItem& wi, F&& f, G&& all) {
-  const uint32_t n = T.stage_n[wi.w];
-  if (n != kNotStaged) {                             // wave-uniform
-    const uint32_t* slot = T.stage_key + stage_slot(T, wi.r, wi.cd.off);
-    for (uint32_t q0 = 0; q0 < n; q0 += 512) {       // two loads of 4 entries per lane in flight
-      u32x4 e[2];
+__device__ __forceinline__ void in_bin_keys(const Tables& T, const StepArgs& A, const Staged& s, F&& f, G&& all) {
+  const WorkItem& wi = s.wi;
+  if (s.n != kNotStaged) {                           // wave-uniform
+    u32x4 e[2] = {s.e[0], s.e[1]};
+    for (uint32_t q0 = 0; q0 < s.n; q0 += 512) {     // two loads of 4 entries per lane in flight
+      if (q0) {
 #pragma unroll
-      for (uint32_t u = 0; u < 2; ++u)
-        e[u] = __builtin_amdgcn_raw_buffer_load_b128(window(slot, (n + 3) / 4 * 16), (int)((q0 + 256 * u + 4 * lane_id()) * 4), 0, 0);
+        for (uint32_t u = 0; u < 2; ++u) e[u] = four_staged(T, wi, s.n, q0 + 256 * u + 4 * lane_id());
+      }
 #pragma unroll
-      for (uint32_t u = 0; u < 2; ++u)
+      for (uint32_t u = 0; u < 2; ++u) {
+        if (q0 + 256 * u >= s.n) break;              // uniform
 #pragma unroll
-        for (uint32_t v = 0; v < 4; ++v) f(e[u][v], q0 + 256 * u + 4 * lane_id() + v < n);
+        for (uint32_t v = 0; v < 4; ++v) f(e[u][v], q0 + 256 * u + 4 * lane_id() + v < s.n);
+      }
     }
   } else {
 #pragma unroll 1
@@ -456,14 +480,48 @@ __device__ __forceinline__ void in_bin_keys(const Tables& T, const StepArgs& A, 
   }
 }
 
+// The bin that holds the krem-th largest of a tensor's last bins (6, 9 or 10 bits), and how many keys are to be taken of it, by one
+// wavefront.  Every wavefront that needs the threshold finds it for itself: a launch in between took 5 us.  n: bins[63 - lane].
+struct LastBin { uint32_t bin, rem; };               // rem = 0: there are not as many keys
+__device__ __forceinline__ LastBin last_bin(const uint32_t* bins, uint32_t n, uint32_t bits, uint32_t krem) {
+  const uint32_t lane = lane_id();
+  uint32_t top = 63;                                 // highest of 64 bins, or lanes' shares of them
+  auto find = [&](uint32_t n) {                      // which lane's it is in, lane 0 first; krem: left to be taken there
+    const uint32_t upto = wave_incl_scan(n);
+    const uint64_t m = __ballot(upto - n < krem && krem <= upto);
+    if (!m) return 64u;
+    const uint32_t l = (uint32_t)__ffsll((unsigned long long)m) - 1;
+    krem -= (uint32_t)__builtin_amdgcn_readlane((int)(upto - n), (int)l);
+    return l;
+  };
+  if (bits > 6) {                                    // uniform
+    const uint32_t per = 1u << (bits - 6);
+    n = 0;
+    for (uint32_t i = 0; i < per; i += 4) {
+      const u32x4 four = *reinterpret_cast<const u32x4*>(bins + (63 - lane) * per + i);
+      n += four.x + four.y + four.z + four.w;
+    }
+    const uint32_t l = find(n);
+    if (l == 64u) return {0u, 0u};
+    top = (64 - l) * per - 1;
+    n = lane < per ? bins[top - lane] : 0u;
+  }
+  const uint32_t l = find(n);
+  return {top - l, l == 64u ? 0u : krem};
+}
+
 // The last 6 or 10 bits of the in-bin keys that carry the prefix found so far.  Matches are
 // rare (a 2^-25 or 2^-21 slice of the key range), so they go straight to the tensor's histogram,
 // one atomic per distinct value per 64 entries.
 __global__ __launch_bounds__(kThreads) void k_topk_low(Tables T, StepArgs A) {
-  WorkItem wi;
-  if (!wave_item(T, &wi)) return;
-  const uint32_t prefix = T.sel_prefix[wi.seg];
-  uint32_t* gh = T.hist + (size_t)wi.seg * kHistBins;
+  Staged s;
+  uint32_t prefix = 0, bits = 0;
+  if (!wave_item(T, &s, [&](const WorkItem& wi) {
+        prefix = T.sel_prefix[wi.seg];
+        bits = T.sel_left[wi.seg] & 255u;
+        asm volatile("" : "+s"(prefix), "+s"(bits));       // (left to itself the compiler asks once the decision is known)
+      })) return;
+  uint32_t* gh = T.hist + (size_t)s.wi.seg * kHistBins;
   auto add = [&](uint32_t k9, bool pending) {
     uint64_t todo = __ballot(pending);
     while (todo) {                                  // uniform: every lane sees the same mask
@@ -475,8 +533,8 @@ __global__ __launch_bounds__(kThreads) void k_topk_low(Tables T, StepArgs A) {
       todo &= ~same;
     }
   };
-  const uint32_t bits = T.sel_left[wi.seg] & 255u, left = bits - 11u, mask = (1u << bits) - 1u, last = (1u << left) - 1u;
-  in_bin_keys(T, A, wi, [&](uint32_t e, bool in) { add(e & last, in && (e & mask) >> left == (prefix & mask) >> left); },
+  const uint32_t left = bits - 11u, mask = (1u << bits) - 1u, last = (1u << left) - 1u;
+  in_bin_keys(T, A, s, [&](uint32_t e, bool in) { add(e & last, in && (e & mask) >> left == (prefix & mask) >> left); },
               [&](uint32_t key, uint32_t, bool in) { add(key & last, in && key >> left == prefix >> left); });
 }
 
@@ -484,16 +542,26 @@ __global__ __launch_bounds__(kThreads) void k_topk_low(Tables T, StepArgs A) {
 // the chunk's totals.
 __global__ __launch_bounds__(kThreads) void k_topk_count(Tables T, StepArgs A) {
   __shared__ uint32_t counts[kThreads / 64][64];
-  WorkItem wi;
-  if (!wave_item(T, &wi)) return;
+  Staged s;
   uint32_t* cnt = counts[wave_id()];
-  const uint32_t t = T.sel_prefix[wi.seg], mask = (1u << (T.sel_left[wi.seg] & 255u)) - 1u, lane = lane_id(), G = T.SW * 4;
+  const uint32_t lane = lane_id(), G = T.SW * 4;
+  uint32_t above = 0, n = 0, bits = 0, prefix = 0, krem = 0;
+  if (!wave_item(T, &s, [&](const WorkItem& wi) {
+        above = T.group[(size_t)wi.w * G + (lane < G ? lane : 0u)];
+        n = T.hist[(size_t)wi.seg * kHistBins + 63 - lane];
+        bits = T.sel_left[wi.seg] & 255u;
+        prefix = T.sel_prefix[wi.seg];
+        krem = T.sel_krem[wi.seg];
+        asm volatile("" : "+v"(n), "+v"(above), "+s"(bits), "+s"(prefix), "+s"(krem));
+      }) || !s.sends) return;
+  const WorkItem& wi = s.wi;
   uint32_t* group = T.group + (size_t)wi.w * G;
-  const uint32_t above = lane < G ? group[lane] : 0u;
+  const uint32_t mask = (1u << bits) - 1u;
+  const uint32_t t = prefix + last_bin(T.hist + (size_t)wi.seg * kHistBins, n, bits - 11u, krem).bin;     // (no threshold: k_topk_scan ends it)
   cnt[lane] = 0;
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   bool staged = true;
-  in_bin_keys(T, A, wi,
+  in_bin_keys(T, A, s,
               [&](uint32_t e, bool in) {
                 const uint32_t k = e & mask;
                 if (in && k >= (t & mask)) atomicAdd(&cnt[e >> 21], k == (t & mask) ? 0x10000u : 1u);
@@ -503,28 +571,38 @@ __global__ __launch_bounds__(kThreads) void k_topk_count(Tables T, StepArgs A) {
                 if (in && key >= t) atomicAdd(&cnt[g], key == t ? 0x10000u : 1u);
               });
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  const uint32_t mine = cnt[lane] + (staged ? above : 0u), incl = wave_incl_scan(mine);
+  const uint32_t mine = cnt[lane] + (staged && lane < G ? above : 0u), incl = wave_incl_scan(mine);
   if (lane < G) group[lane] = incl - mine;
   if (lane == 63) T.chunk_cnt[wi.w] = make_uint2(incl & 0xFFFFu, incl >> 16);
 }
 
-// One wavefront per Top-K tensor: running totals over its chunks, in chunk order, and the last element that wins with a key
-// equal to the threshold (ties that do not all win are common: differences of parameters that have moved little
+// One wavefront per Top-K tensor: the threshold, clearing its bins; running totals over its chunks, in chunk order; and the last
+// element that wins with a key equal to the threshold (ties that do not all win are common: differences of parameters that have moved little
 // are multiples of the parameters' spacing).
 __global__ __launch_bounds__(64) void k_topk_scan(Tables T, StepArgs A) {
   const uint32_t seg = blockIdx.x, lane = threadIdx.x;
-  if (T.fired[seg] != 2) return;
-  const uint32_t r = seg / T.L, ties = T.sel_krem[seg], t = T.sel_prefix[seg], G = T.SW * 4;
+  const uint32_t code = T.fired[seg];
+  const uint32_t r = seg / T.L, prefix = T.sel_prefix[seg], last = (T.sel_left[seg] & 255u) - 11u, G = T.SW * 4;
   const LayerDesc ld = T.layers[seg % T.L];
   const uint32_t first = r * T.C + ld.chunk0;
-  uint32_t carry_g = 0, carry_e = 0, crossing = 0, need = 0;
-  for (uint32_t b = 0; b < ld.nchunks; b += 64 * 4) {
-    uint2 n[4];
+  uint32_t* bins = T.hist + (size_t)seg * kHistBins;
+  const uint32_t lowest = bins[63 - lane];
+  uint2 n[4];
+  auto ask = [&](uint32_t b) {
 #pragma unroll
     for (uint32_t u = 0; u < 4; ++u) {
       const uint32_t i = b + 64 * u + lane;
       n[u] = i < ld.nchunks ? T.chunk_cnt[first + i] : make_uint2(0, 0);
     }
+  };
+  ask(0);
+  if (code != 2) return;
+  const LastBin in = last_bin(bins, lowest, last, T.sel_krem[seg]);
+  for (uint32_t b = lane; b < 1u << last; b += 64) bins[b] = 0;
+  const uint32_t ties = in.rem, t = prefix == kNoThreshold || ties == 0 ? kNoThreshold : prefix + in.bin;
+  uint32_t carry_g = 0, carry_e = 0, crossing = 0, need = 0;
+  for (uint32_t b = 0; b < ld.nchunks; b += 64 * 4) {
+    if (b) ask(b);
 #pragma unroll
     for (uint32_t u = 0; u < 4; ++u) {
       const uint32_t i = b + 64 * u + lane;
@@ -544,6 +622,10 @@ __global__ __launch_bounds__(64) void k_topk_scan(Tables T, StepArgs A) {
   if (t == kNoThreshold || carry_g + ties != ld.K || carry_e < ties) {
     if (lane == 0) T.sel_prefix[seg] = kNoThreshold;
     return;
+  }
+  if (lane == 0) {
+    T.sel_prefix[seg] = t;
+    T.sel_krem[seg] = ties;
   }
   if (carry_e == ties) {                             // all of them win
     if (lane == 0) T.sel_cut[seg] = ld.numel - 1;
@@ -680,7 +762,6 @@ static void select_s(const Tables& t, const StepArgs& a, hipStream_t s) {
   else k_topk_stage<SWEEPS, 1, true><<<g, b, 0, s>>>(t, a);
   k_topk_pick<1><<<segs, b, 0, s>>>(t);
   k_topk_low<<<gw, b, 0, s>>>(t, a);
-  k_topk_pick<2><<<segs, b, 0, s>>>(t);
   k_topk_count<<<gw, b, 0, s>>>(t, a);
   k_topk_scan<<<segs, dim3(64), 0, s>>>(t, a);
 }

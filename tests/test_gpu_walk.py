@@ -53,6 +53,15 @@ def test_norms(evg, oracle_mod, P, topk, norm_mode, trigger_kind):
     _run(evg, oracle_mod, P, [9000, 33, 1024], topk_ppm=topk, norm_mode=norm_mode, **kw)
 
 
+# A selection's last bins are 64 where the threshold was expected, 1024 where it moved by octaves, 512 in rings whose norms are a pass of
+# their own; chunks that end with a load of sixteen codes, within one, and after the first of a lane's two
+@pytest.mark.parametrize("numels", [[8192, 4096, 4112, 15], [8208, 4097, 16, 12_289]], ids=["whole", "ragged"])
+@pytest.mark.parametrize("kw", [dict(), dict(spike_prob=0.5, spike_gain=50.0), dict(norm_mode=1), dict(topk_key=1)],
+                         ids=["expected", "moved", "plain", "value"])
+def test_last_bins_and_codes(evg, oracle_mod, numels, kw):
+    _run(evg, oracle_mod, 5, numels, topk_ppm=50_000, iters=9, **kw)
+
+
 # Tensors of one window each, and a longer one.  Of about 100 windows whole sends and Top-K go in parts of 3 workers (19 = 6 * 3 + 1),
 # 5 and 9 (65), 9 and 17 (130); of 200 in parts of 4 (16), 5 and 12 (23), 9 (66); of 330 in one part (15), of 9 (17), 10 (65).
 @pytest.mark.parametrize("windows,P", [(100, 19), (100, 65), (100, 130), (200, 16), (200, 23), (200, 66), (330, 15), (330, 17), (330, 65)])
