@@ -23,7 +23,7 @@
 // 128 are fine: with 256 the walk merges more counts (ResNet-50 1220), with a thirty-second of an octave each the stage fetches
 // more (64 workers 4647); bins of an eighth and codes that divide them cost a launch more and 1317 where 1277 is now.
 // The many launches are bound by their chains of dependent reads, which go together where they can, and by vector instructions in k_topk_stage.
-// 64 ResNet-18 workers, 10 %, and 8 ResNet-50 workers, 1 %, us a launch, before -> now: k_topk_decide 28 -> 22 and 10 -> 9 (bins asked for ahead of the
+// 64 ResNet-18 workers, 10 %, and 8 ResNet-50 workers, 1 %, us a launch, before -> now: k_topk_decide 28 -> 21 and 10 -> 8 (bins asked for ahead of the
 // test), k_topk_stage 360 -> 349 and 70 -> 60 (compare_codes, one list of a lane's two loads), k_topk_low 27 -> 21 and 9 -> 7.5, and a launch
 // of 6 and 5 less (last_bin).  Steps: 16 ResNet-18 workers with given gradients, 10 % 1269 -> 1259, 8 ResNet-50 1160 -> 1150, 64 ResNet-18
 // 4547 -> 4538, 42 ResNet-20 of width 18, 14 % 210 -> 204, 31 ResNet-50 of width 46 with spikes, 0.5 % 2232 -> 2208.
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_decide(Tables T, StepArgs A) 
     bool hat_sums;
     const uint32_t anchor = bounds.anchor, k = tested_k(T, A);
     const int32_t khat = T.last_event[seg];
-    segment_sums(T, A, seg, &acc, &acc_hat, &hat_sums);
+    segment_sums<16>(T, A, seg, &acc, &acc_hat, &hat_sums);
     if (lane_id() == 0) {
       code = segment_test(T, A, seg, acc, acc_hat, hat_sums, k);
       // Codes are a byte an element in every step, and save seven at an event: a tensor that is silent for longer leaves them out.  Steps while

@@ -16,12 +16,12 @@ namespace evg {
 __device__ __forceinline__ void trigger_segment(const Tables& T, const StepArgs& A, uint32_t seg) {
   double acc, acc_hat;
   bool hat_sums;
-  segment_sums(T, A, seg, &acc, &acc_hat, &hat_sums);
+  segment_sums<32>(T, A, seg, &acc, &acc_hat, &hat_sums);
   if (lane_id() == 0) (void)segment_test(T, A, seg, acc, acc_hat, hat_sums, tested_k(T, A));
 }
 
 __global__ __launch_bounds__(kThreads) void k_trigger(Tables T, StepArgs A) {
-  const uint32_t seg = blockIdx.x * (kThreads / 64) + wave_id();
+  const uint32_t seg = blockIdx.x * (kThreads / 64) + (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_id());
   if (seg >= T.S) return;           // whole wavefront leaves; no workgroup barrier below
   trigger_segment(T, A, seg);
   if (seg == 0 && lane_id() == 0) close_step(T, A);

@@ -11,12 +11,10 @@
 // launch still have to read the values from before the event.
 #pragma once
 #include "evg_device.h"
+#include "quad_device.h"
 
 namespace evg {
 
-// Sums of the tensor's sweep partials in a fixed order, by one whole wavefront; valid in every lane.
-// *hat_sums: the squared norm of xhat comes from the arena sums (norm-difference trigger with
-// Top-K, or before the tensor's first event) rather than from the scalar kept at its last event.
 // Eight loads are in flight at a time (the sums stay in order): a tensor of 2.4 M elements has 36 partials
 // per lane, and waiting for each of them made the kernel 13 us; batched, 5.
 __device__ __forceinline__ double ordered_lane_sum(const double* part, uint32_t np) {
@@ -31,6 +29,30 @@ __device__ __forceinline__ double ordered_lane_sum(const double* part, uint32_t 
   return acc;
 }
 
+// The same with MANY loads in flight where there are more than eight (part: the same in all lanes; past the end zeros): windows of 256 elements
+// leave a lane 144 partials of such a tensor.  k_trigger for 16 ResNet-18 workers 12.2 -> 7.4 us with 32 (a step with spikes 822 -> 817, with given
+// gradients 1005 -> 1001); k_topk_decide takes 16, as its registers cost workgroups beside it: 9 -> 8 and 22 -> 21 us for 8 ResNet-50 and 64 ResNet-18 workers.
+template <int N>
+__device__ __forceinline__ void add_in_order(const double* part, uint32_t np, uint32_t first, double* acc) {
+  double v[N];
+#pragma unroll
+  for (uint32_t u = 0; u < N; ++u) v[u] = load_f64(part, np * 8, (first + 64 * u + lane_id()) * 8);
+#pragma unroll
+  for (uint32_t u = 0; u < N; ++u) *acc += v[u];
+}
+template <int MANY>
+__device__ __forceinline__ double ordered_long_sum(const double* part, uint32_t np) {
+  double acc = 0.0;
+  uint32_t i = 0;
+  for (; i + 64 * 8 < np; i += 64 * MANY) add_in_order<MANY>(part, np, i, &acc);
+  if (i < np) add_in_order<8>(part, np, i, &acc);
+  return acc;
+}
+
+// Sums of the tensor's sweep partials in a fixed order, by one whole wavefront; valid in every lane.  seg: the same in all lanes.
+// *hat_sums: the squared norm of xhat comes from the arena sums (norm-difference trigger with
+// Top-K, or before the tensor's first event) rather than from the scalar kept at its last event.
+template <int MANY>
 __device__ __forceinline__ void segment_sums(const Tables& T, const StepArgs& A, uint32_t seg, double* acc_out,
                                              double* acc_hat_out, bool* hat_sums_out) {
   const uint32_t r = seg / T.L, l = seg % T.L;
@@ -38,11 +60,11 @@ __device__ __forceinline__ void segment_sums(const Tables& T, const StepArgs& A,
   const uint32_t sums = T.SW * T.fine, np = ld.nchunks * sums;
   const double* part = T.partials + ((size_t)r * T.C + ld.chunk0) * sums;
   double acc_hat = 0.0;
-  const double acc = wave_sum(ordered_lane_sum(part, np));
+  const double acc = wave_sum(ordered_long_sum<MANY>(part, np));
   const bool hat_sums = A.norm_src == 2 || (A.norm_src == 1 && T.last_event[seg] < 0);
   if (hat_sums) {
     const double* ph = T.partials_hat + ((size_t)r * T.C + ld.chunk0) * sums;
-    acc_hat = wave_sum(ordered_lane_sum(ph, np));
+    acc_hat = wave_sum(ordered_long_sum<MANY>(ph, np));
   }
   *acc_out = acc;
   *acc_hat_out = acc_hat;
