@@ -209,8 +209,8 @@ def main():
     # reads the mailboxes too, as the pass of the other rings does)
     beyond_cache = 20 * w.P * evg.padded_numel(w.layer_numel) > (128 << 20)
     streams = beyond_cache and not args.delivery_delay
-    # ... and so do the parts of the ring in which cached rings are updated (Top-K: with tensors of at most 327 680 elements)
-    parts = not beyond_cache and not args.delivery_delay and not (w.topk_ppm and (args.xhat_reset or max(w.layer_numel) > 327_680))
+    # ... and so do the parts of the ring in which cached rings are updated (Top-K: with tensors of at most 819 200 elements)
+    parts = not beyond_cache and not args.delivery_delay and not (w.topk_ppm and (args.xhat_reset or max(w.layer_numel) > 819_200))
     walks = (streams and not args.xhat_reset) or parts
     # a streaming Top-K ring, and those parts, leave a key code for each element, a byte, from which the selection is made
     codes = 1 if w.topk_ppm and (beyond_cache or parts) else 0
@@ -274,7 +274,9 @@ def main():
                                                      or args.topk_ppm is not None) else None
         upd_counters = (counters or {}).get("kernels", {}).get("k_update", {})
         traffic = upd_counters.get("traffic_bytes")
-        kernel = "k_update_walk" if streams else "k_update_part" if parts else "k_update"
+        # few workers have their stretches of a window in one workgroup
+        one_shot = w.P <= 16 and (parts if not streams else not w.topk_ppm)
+        kernel = "k_update_ring" if one_shot else "k_update_walk" if streams else "k_update_part" if parts else "k_update"
         out["roofline"] = {"kernel": kernel, "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
                            "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                            "traffic": traffic,

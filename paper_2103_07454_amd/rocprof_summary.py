@@ -26,6 +26,7 @@ import csv
 import glob
 import json
 import os
+import re
 
 from . import inputs
 
@@ -144,7 +145,7 @@ def main():
             af = sum(fv) / len(fv) * KIB * f_fetch
             aw = sum(wv) / len(wv) * KIB * f_write
             out.append(f"| {short(k)} | {len(fv)} | {af / 1e9:.3f} | {aw / 1e9:.3f} | {(af + aw) / 1e9:.3f} |")
-            record["kernels"].setdefault(short(k).replace("evg::", "").split("<")[0].replace("k_update_walk", "k_update"), {}).update(
+            record["kernels"].setdefault(re.sub("k_update_(walk|ring|part)", "k_update", short(k).replace("evg::", "").split("<")[0]), {}).update(
                 fetch_bytes=af, write_bytes=aw, traffic_bytes=af + aw, launches=len(fv))
         upd = record["kernels"].get("k_update")
         if upd and rf["bound"] == "hbm":

@@ -1,7 +1,7 @@
 """Cached Top-K rings whose tensors are not too long: one workgroup per tensor makes the whole selection, from the key codes and
 counts that the update pass leaves (a pass in parts of the ring).  Checked against the oracle, message by message, at the
 sizes where it can go wrong: tensors of a wavefront (up to 256 elements) and one more, ends of groups of 256, of the codes that a
-workgroup holds at once (163 840) and the longest it takes (327 680); parts of 1, 2 and 4 workers, closed rings and last parts of
+workgroup holds at once (163 840), twice as many and the longest it takes (819 200); parts of 1, 2 and 4 workers, closed rings and last parts of
 one; thresholds that leave the counted codes (spikes, decay), ties, and blobs that move to and from streaming rings."""
 import numpy as np
 import pytest
