@@ -136,6 +136,7 @@ __device__ __forceinline__ uint2 place_groups(const Tables& T, Chosen& s, uint32
 __device__ __forceinline__ void cut_by_groups(const Tables& T, const StepArgs& A, Chosen& s, uint32_t r, const ChooseDesc& ld, uint32_t t,
                                               uint32_t ties, const uint32_t* groups) {
   uint32_t carry = 0;
+  __syncthreads();                                         // (place_groups ends with reads of the totals that are written next)
   for (uint32_t g0 = 0; g0 < (ld.numel + 255) / 256; g0 += kWide) {       // uniform
     const uint32_t g = g0 + threadIdx.x, n = g < (ld.numel + 255) / 256 ? groups[g] >> 16 : 0u;
     uint32_t sum;
@@ -320,7 +321,8 @@ __device__ __forceinline__ bool choose_by_codes(const Tables& T, const StepArgs&
     t = (uint32_t)__builtin_amdgcn_readlane((int)k, who);
     ties = rem2 - (uint32_t)__builtin_amdgcn_readlane((int)greater, who);
     ok &= is != 0;
-    if (threadIdx.x == 0) s.cut = (uint32_t)__builtin_amdgcn_readlane((int)at, who);
+    const uint32_t last = (uint32_t)__builtin_amdgcn_readlane((int)at, who);
+    if (threadIdx.x == 0) s.cut = last;
     for (uint32_t i = threadIdx.x; i < n; i += kWide)
       if (key[i] >= t) atomicAdd(&groups[list[i] >> 8], key[i] == t ? 0x10000u : 1u);
     __syncthreads();
