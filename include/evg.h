@@ -316,7 +316,9 @@ evg_status evg_average(evg_ctx* c, float* out);
  * evg_state_import expects a context created with the same configuration (access_mode may
  * differ, and evg_init or evg_init_static) whose arenas already hold the saved contents; a blob from a different configuration is rejected with
  * EVG_ERR_INVALID.  After import, evg_step continues exactly (bit for bit) where the
- * exporting context stopped. */
+ * exporting context stopped.  (In another access mode, or where the static block has no room for
+ * what evg_init chose, tensors may be summed in other stretches: a tested norm can then
+ * differ in its last bit.) */
 uint64_t evg_state_size(evg_ctx* c); /* bytes needed for the blob; 0 if c is NULL */
 evg_status evg_state_export(evg_ctx* c, void* blob, uint64_t capacity);
 evg_status evg_state_import(evg_ctx* c, const void* blob, uint64_t size);

@@ -570,12 +570,12 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     // of 2 / 4 / 8, us a step: 102 windows on 4 workers 5.8 / 6.8 / -, 120 on 8 7.2 / 7.7 / 11.2, on 24 12.7 / 12.5 / 15.6; 314 on
     // 8 15.7 / 14.3 / 16.6, on 12 25.7 / 22.6 / 19.2, on 16 34.1 / 33.4 / 30.7; 438 on 8 24.9 / 21.8 / 18.4, on 16 53.3 / 48.9 / 49.0.
     groups = quads = 0;
-    fine = 1;                      // (a window's sum is one of its sweep's)
+    fine = 1;
     if (in_parts && small_ring) ring_shape(P, windows, longest, cfg->topk_ppm != 0, one_launch, cfg->grad_mode == EVG_GRAD_BUFFER, &groups, &quads);
     if (may_be && !c->cached && !cfg->topk_ppm && !cfg->delivery_delay && cfg->norm_mode == EVG_NORM_FUSED) stream_shape(P, Npad * 4, &groups, &quads);
     one_shot = groups && !in_parts;
     if (groups) {
-      fine = 4 / groups;
+      fine = one_shot && groups == 2 ? 2 : kGroupSums;
       ring_windows = 0;
       for (const ChunkDesc& cd : chunks) ring_windows += (cd.lead + cd.len + 256 * groups - 1) / (256 * groups);
     }
@@ -761,14 +761,14 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   std::vector<WindowDesc> ring;
   std::vector<ChooseDesc> by_size;
   if (in_parts || one_shot) {
-    const uint32_t length = kSweep / fine, sums = SW * fine;
+    const uint32_t length = groups ? 256 * groups : kSweep, sums = SW * fine, step = groups ? groups * fine / kGroupSums : 1;
     for (size_t i = 0; i < chunks.size(); ++i)
       for (uint32_t u = 0; u * length < chunks[i].lead + chunks[i].len; ++u) {
         const ChunkDesc& cd = chunks[i];
         const LayerDesc& d = layers[cd.layer];
         const uint32_t first = u ? u * length - cd.lead : 0u, end = std::min<uint32_t>(cd.len, (u + 1) * length - cd.lead);
         ring.push_back({cd.off + first, end - first, cd.layer, cd.j0 + first,
-                        (uint32_t)i * sums + u, d.chunk0 * sums, d.nchunks * sums, i == d.chunk0 && u == 0 ? 1u : 0u, d.sig_base,
+                        (uint32_t)i * sums + u * step, d.chunk0 * sums, d.nchunks * sums, i == d.chunk0 && u == 0 ? 1u : 0u, d.sig_base,
                         d.numel, d.K, d.msg_off, 0u});
       }
     WindowDesc* d_ring = nullptr;
@@ -1229,7 +1229,7 @@ evg_status evg_state_export(evg_ctx* c, void* blob, uint64_t capacity) {
   out += sizeof h;
   const Tables& t = c->t;
   for (const Piece& p : state_pieces(c)) {
-    if (t.fine > 1 && (p.dev == t.partials || p.dev == t.partials_hat)) {      // blobs hold a sum a sweep
+    if (t.fine > 1 && (p.dev == t.partials || p.dev == t.partials_hat)) {      // blobs hold a sum a sweep, added as every test adds it (SweepSums)
       const size_t sweeps = p.bytes / 8;
       std::unique_ptr<double[]> parts(new (std::nothrow) double[sweeps * t.fine]);
       if (!parts) return fail(EVG_ERR_OOM, "host allocation failed");

@@ -58,12 +58,13 @@ struct LayerDesc {
 struct WindowDesc {
   uint32_t off, len;   // start inside a worker's slice (multiple of 4), elements
   uint32_t layer, j0;  // tensor, start inside it
-  uint32_t slot;       // where the window's sum goes among a worker's partials
+  uint32_t slot;       // where the window's sum goes, or the first of its groups', among a worker's partials
   uint32_t sum0, sums; // the tensor's partials
   uint32_t books;      // the tensor's first window
   double sig_base;     // sigma0 [/ sqrt(fan_in)]
   uint32_t numel, K, msg_off, pad;     // of the tensor; its Top-K message (see LayerDesc)
 };
+constexpr uint32_t kGroupSums = 4;     // sums of a sweep where each group of 256 elements has one
 constexpr uint32_t kPartMost = 8;      // workers of a part of the ring there
 constexpr uint32_t kRingMost = 64;     // workers of a ring whose windows are one workgroup's: 64 KB of LDS
 struct PartClock { uint32_t k, steps; };       // the next iteration, and the steps completed
@@ -94,7 +95,7 @@ struct Tables {
   float* xsnap;            // [2][P*Npad] or null: copies of x that the update pass of one iteration leaves
                            // for the next one, two in turn (cache-resident rings with ordinary
                            // delivery: the receivers then fetch what a neighbour sends, no copy kernel)
-  double* partials;        // [P*C*SW*fine] per 1024-element sweep of a chunk, or per part of it: sum of squared drift, or
+  double* partials;        // [P*C*SW*fine] per 1024-element sweep of a chunk, or per part of it (fine): sum of squared drift, or
                            // of squared x when the trigger compares norms
   double* partials_hat;    // [P*C*SW*fine] sum of squared xhat (norm-difference trigger only)
   double* xhat_sq;         // [S] squared norm of what was last sent, kept as a scalar when whole
@@ -137,7 +138,7 @@ struct Tables {
   uint32_t decay_len;
   uint32_t P, L, C, S;
   uint32_t SW;             // 1024-element sweeps per chunk
-  uint32_t fine;           // sums of a sweep: 1, or where windows are shorter than sweeps (kernels_ring.hip) 2 or 4
+  uint32_t fine;           // sums of a sweep: 1, or of rings that go by kernels_ring.hip kGroupSums (streaming ones with windows of two groups: 2)
   uint32_t hist_len;
   uint32_t Ktot;           // sum of K over tensors
   uint64_t Npad;

@@ -374,10 +374,10 @@ __device__ __forceinline__ Tested test_tensor(const Tables& T, const StepArgs& A
   t.khat = T.last_event[seg];
   t.k = tested_k(T, A);
   const size_t at = (size_t)r * T.C * (T.SW * T.fine) + ld.sum0;
-  const double sum = ordered_lane_sum(T.partials + at, ld.sums);
-  t.acc = wave_sum_dpp(sum);
+  auto sum = [&](const double* part) { return T.fine == 1 ? ordered_lane_sum<8, 1>(part + at, ld.sums) : ordered_lane_sum<8, kGroupSums>(part + at, ld.sums); };
+  t.acc = wave_sum_dpp(sum(T.partials));
   double acc_hat = 0.0;
-  if (A.norm_src == 2) acc_hat = wave_sum_dpp(ordered_lane_sum(T.partials_hat + at, ld.sums));
+  if (A.norm_src == 2) acc_hat = wave_sum_dpp(sum(T.partials_hat));
   t.d = tested_norm(A, t.acc, acc_hat);
   t.code = (uint32_t)__builtin_amdgcn_readfirstlane((int)event_code(A, t.d, t.dl, t.khat, t.k));
   return t;

@@ -54,12 +54,16 @@ __global__ __launch_bounds__(1024) void k_update_ring(RingArgs R, StepArgs A, Ta
   static_assert(!(STREAM && (TESTS || TOPK)), "cached rings only");
   constexpr int WQ = Q > G ? Q / G : 1;                    // workers of a wavefront
   constexpr int GQ = Q > G ? G : Q;                        // groups of each that it has
+  static_assert(GQ <= 2, "half a wavefront sums a group");
   constexpr int SPLIT = G / GQ;                            // wavefronts of a worker
-  constexpr int FIRST = G == 4 ? 2 : 4;                    // sums of a test that a lane asks for at once
+  // sweeps of a test whose sums a lane asks for at once (Student-t gradients take the registers that a second one would)
+  constexpr int FIRST = G == 1 || (G == 2 && Q == 2 && DIST == 1) ? 1 : 2;
+  // Two wavefronts' sums of a worker are one: with one each streaming rings of 8 workers take 1.4 % longer (403 us, 397 together)
+  constexpr bool TOGETHER = STREAM && G == 2;
+  __shared__ double ws[TOGETHER ? kRingMost : 1][2], ws_hat[TOGETHER && NORM == 3 ? kRingMost : 1][2];
   extern __shared__ float4 held[];                         // [P][G][64] what the neighbours hold from this iteration on
   __shared__ uint32_t codes[TESTS ? kRingMost : 1];
   __shared__ uint64_t spiky;
-  __shared__ double ws[SPLIT > 1 ? kRingMost * SPLIT : 1], ws_hat[SPLIT > 1 && NORM == 3 ? kRingMost * SPLIT : 1];
   const WindowDesc wd = R.windows[blockIdx.x];
   const uint32_t P = R.P, layer = wd.layer, lane = lane_id();
   uint32_t* const counts = reinterpret_cast<uint32_t*>(held + P * G * 64);             // TOPK: [P][kCodeBins + 1]
@@ -79,13 +83,13 @@ __global__ __launch_bounds__(1024) void k_update_ring(RingArgs R, StepArgs A, Ta
   auto some = [&](int i) { return exists(i) ? worker(i) : P - 1; };    // (loads of workers that are not there)
 
   // ---- everything is asked for at once ----
-  double p[TESTS ? WQ : 1][FIRST];
+  SweepSums<kGroupSums> p[TESTS ? WQ : 1][FIRST];
   if (TESTS) {
 #pragma unroll
     for (int i = 0; i < WQ; ++i)
 #pragma unroll
       for (int q = 0; q < FIRST; ++q)
-        p[i][q] = load_f64((turn ? R.partials[1] : R.partials[0]) + (size_t)some(i) * R.sums_row + wd.sum0, wd.sums * 8, lane * 8 + q * 512);
+        p[i][q] = load_sweep<kGroupSums>((turn ? R.partials[1] : R.partials[0]) + (size_t)some(i) * R.sums_row + wd.sum0, wd.sums, lane + 64 * q);
   }
   // its workers' state, the same in all lanes.  Where xhat is only asked for once a flag is known it comes by scalar loads of the word it is in, as
   // loads of lanes are waited for in their order
@@ -148,7 +152,7 @@ __global__ __launch_bounds__(1024) void k_update_ring(RingArgs R, StepArgs A, Ta
     cut = R.cut[seg];
     ties = R.ties[seg];
     anchor = R.anchor[seg];
-    const uint32_t shift = R.chunk_groups, group = (r * R.C << shift) + wd.slot * G + my_group, next = more ? group + 1 : group;
+    const uint32_t shift = R.chunk_groups, group = (r * R.C << shift) + wd.slot + my_group, next = more ? group + 1 : group;
     in_chunk = R.group[group];
     so_far = R.chunk_before[group >> shift];
     in_chunk2 = R.group[next];
@@ -179,18 +183,18 @@ __global__ __launch_bounds__(1024) void k_update_ring(RingArgs R, StepArgs A, Ta
 #pragma unroll
     for (int i = 0; i < WQ; ++i) {
       const double* from = (turn ? R.partials[1] : R.partials[0]) + (size_t)some(i) * R.sums_row + wd.sum0;
-      double s = p[i][0];
+      double s = p[i][0].added();
 #pragma unroll
-      for (int q = 1; q < FIRST; ++q) s += p[i][q];
-      for (uint32_t q = FIRST * 64; q < wd.sums; q += 64) s += load_f64(from, wd.sums * 8, (q + lane) * 8);     // (long tensors)
+      for (int q = 1; q < FIRST; ++q) s += p[i][q].added();
+      for (uint32_t q = FIRST * 64; q < wd.sums / kGroupSums; q += 64) s += load_sweep<kGroupSums>(from, wd.sums, q + lane).added();     // (long tensors)
       acc[i] = wave_sum_dpp(s);
       double acc_hat = 0.0;
       if (NORM == 2) {
         acc_hat = hat_sq[i];
         if (khat[i] < 0) {               // before its first event a tensor's xhat has no norm of its own: the initial pass's sums
           double s2 = 0.0;
-          for (uint32_t q = 0; q < wd.sums; q += 64)
-            s2 += load_f64(T.partials_hat + (size_t)some(i) * R.sums_row + wd.sum0, wd.sums * 8, (q + lane) * 8);
+          for (uint32_t q = 0; q < wd.sums / kGroupSums; q += 64)
+            s2 += load_sweep<kGroupSums>(T.partials_hat + (size_t)some(i) * R.sums_row + wd.sum0, wd.sums, q + lane).added();
           acc_hat = wave_sum_dpp(s2);
         }
       }
@@ -252,7 +256,7 @@ __global__ __launch_bounds__(1024) void k_update_ring(RingArgs R, StepArgs A, Ta
       fl |= l;
       fr |= rr;
     }
-    double sum = 0.0, sum_hat = 0.0;
+    double sum[GQ], sum_hat[NORM == 3 ? GQ : 1];
 #pragma unroll
     for (int gq = 0; gq < GQ; ++gq) {
       const int q = i * GQ + gq;
@@ -288,8 +292,8 @@ __global__ __launch_bounds__(1024) void k_update_ring(RingArgs R, StepArgs A, Ta
         store(at(R.x, r), e * 4, x[q]);
         if (!A.plain_sgd) store(at(R.vel, r), e * 4, v[q]);
       }
-      sum += wave_sum_dpp(s);
-      if (NORM == 3) sum_hat += wave_sum_dpp(s2);
+      sum[gq] = s;
+      if (NORM == 3) sum_hat[gq] = s2;
       if (TOPK) {
         const Bins bins = first_bins(x[q].v, h[q].v, A.topk_key, mark(anchor, q));
         if (e < wd.len) *reinterpret_cast<uint32_t*>(T.codes + (size_t)r * R.row + wd.off + e) = bins.codes;
@@ -300,26 +304,25 @@ __global__ __launch_bounds__(1024) void k_update_ring(RingArgs R, StepArgs A, Ta
         }
       }
     }
-    const size_t slot = (size_t)r * R.sums_row + wd.slot;
-    if (SPLIT == 1 && lane == 0) {
-      (turn ? R.partials[0] : R.partials[1])[slot] = sum;
-      if (NORM == 3) T.partials_hat[slot] = sum_hat;
-    } else if (SPLIT > 1 && lane == 0) {
-      ws[r * SPLIT + wave % SPLIT] = sum;
-      if (NORM == 3) ws_hat[r * SPLIT + wave % SPLIT] = sum_hat;
+    // the groups' sums are in lanes 0 and 32 (a group past the window's end: zero)
+    const double total = GQ == 1 ? wave_sum_dpp(sum[0]) : wave_sums2(sum[0], sum[GQ - 1]);
+    const double total_hat = NORM != 3 ? 0.0 : GQ == 1 ? wave_sum_dpp(sum_hat[0]) : wave_sums2(sum_hat[0], sum_hat[NORM == 3 ? GQ - 1 : 0]);
+    if (TOGETHER) {
+      if (lane == 0) {
+        ws[r][g0] = total;
+        if (NORM == 3) ws_hat[r][g0] = total_hat;
+      }
+    } else if ((GQ == 1 ? lane : lane & 31u) == 0) {
+      const size_t slot = (size_t)r * R.sums_row + wd.slot + g0 + lane / 32;
+      (turn ? R.partials[0] : R.partials[1])[slot] = total;
+      if (NORM == 3) T.partials_hat[slot] = total_hat;
     }
   }
-  if (SPLIT > 1 || TOPK) __syncthreads();
-  if (SPLIT > 1 && threadIdx.x < P) {
+  if (TOGETHER || TOPK) __syncthreads();
+  if (TOGETHER && threadIdx.x < P) {
     const size_t slot = (size_t)threadIdx.x * R.sums_row + wd.slot;
-    double sum = 0.0, sum_hat = 0.0;
-#pragma unroll
-    for (int q = 0; q < SPLIT; ++q) {
-      sum += ws[threadIdx.x * SPLIT + q];
-      if (NORM == 3) sum_hat += ws_hat[threadIdx.x * SPLIT + q];
-    }
-    (turn ? R.partials[0] : R.partials[1])[slot] = sum;
-    if (NORM == 3) T.partials_hat[slot] = sum_hat;
+    (turn ? R.partials[0] : R.partials[1])[slot] = ws[threadIdx.x][0] + ws[threadIdx.x][1];
+    if (NORM == 3) T.partials_hat[slot] = ws_hat[threadIdx.x][0] + ws_hat[threadIdx.x][1];
   }
   if (TOPK) {
     for (uint32_t b = threadIdx.x; b < P * (kCodeBins + 1); b += R.threads) {

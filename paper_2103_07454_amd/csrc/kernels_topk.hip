@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kThreads) void k_topk_decide(Tables T, StepArgs A) 
     bool hat_sums;
     const uint32_t anchor = bounds.anchor, k = tested_k(T, A);
     const int32_t khat = T.last_event[seg];
-    segment_sums<16>(T, A, seg, &acc, &acc_hat, &hat_sums);
+    segment_sums<16, 1>(T, A, seg, &acc, &acc_hat, &hat_sums);     // (no rings with sums of groups)
     if (lane_id() == 0) {
       code = segment_test(T, A, seg, acc, acc_hat, hat_sums, k);
       // Codes are a byte an element in every step, and save seven at an event: a tensor that is silent for longer leaves them out.  Steps while

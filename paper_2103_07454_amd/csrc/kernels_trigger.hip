@@ -16,7 +16,9 @@ namespace evg {
 __device__ __forceinline__ void trigger_segment(const Tables& T, const StepArgs& A, uint32_t seg) {
   double acc, acc_hat;
   bool hat_sums;
-  segment_sums<32>(T, A, seg, &acc, &acc_hat, &hat_sums);
+  if (T.fine == 1) segment_sums<32, 1>(T, A, seg, &acc, &acc_hat, &hat_sums);       // uniform
+  else if (T.fine == 2) segment_sums<32, 2>(T, A, seg, &acc, &acc_hat, &hat_sums);
+  else segment_sums<32, kGroupSums>(T, A, seg, &acc, &acc_hat, &hat_sums);
   if (lane_id() == 0) (void)segment_test(T, A, seg, acc, acc_hat, hat_sums, tested_k(T, A));
 }
 

@@ -111,6 +111,10 @@ __device__ __forceinline__ double rows_added(double a, double b) {       // rows
   return __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0])) +
          __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
 }
+__device__ __forceinline__ double wave_sums2(double a, double b) {       // lanes 0 .. 31: a, 32 .. 63: b
+  const double v = halves_added(a, b);
+  return row_sum_dpp(rows_added(v, v));
+}
 __device__ __forceinline__ double wave_sums4(double a, double b, double c, double d) {     // rows 0, 1, 2, 3: a, b, c, d
   return row_sum_dpp(rows_added(halves_added(a, c), halves_added(b, d)));
 }

@@ -15,56 +15,74 @@
 
 namespace evg {
 
-// Eight loads are in flight at a time (the sums stay in order): a tensor of 2.4 M elements has 36 partials
-// per lane, and waiting for each of them made the kernel 13 us; batched, 5.
+// The sums of one sweep: one, or where windows are shorter (kernels_ring.hip) one for each group of 256 elements, or for two.  A sweep's are added up first,
+// as the passes that have a whole sweep in a workgroup add theirs (block_sum): a tensor's sum is the same bits also once its sweeps' have been made
+// one (evg_state_export), and, groups in their order, whichever pass has left them.
+template <int F> struct SweepSums {
+  double v[F];
+  __device__ __forceinline__ double added() const {
+    if constexpr (F == 1) return v[0];
+    else if constexpr (F == 2) return v[0] + v[1];
+    else return ((v[0] + v[1]) + v[2]) + v[3];
+  }
+};
+// part: the same in all lanes, a multiple of F; past its np sums zeros
+template <int F>
+__device__ __forceinline__ SweepSums<F> load_sweep(const double* part, uint32_t np, uint32_t sweep) {
+  static_assert(F == 1 || F == 2 || F == kGroupSums, "a sweep's, halves' or groups'");
+  SweepSums<F> s;
+  if constexpr (F == 1) {
+    s.v[0] = load_f64(part, np * 8, sweep * 8);
+  } else {
+#pragma unroll
+    for (int h = 0; h < F / 2; ++h) {
+      const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(window(part, np * 8), (int)(sweep * (F * 8) + h * 16), 0, 0);
+      s.v[2 * h] = __longlong_as_double((long long)(((uint64_t)t[1] << 32) | t[0]));
+      s.v[2 * h + 1] = __longlong_as_double((long long)(((uint64_t)t[3] << 32) | t[2]));
+    }
+  }
+  return s;
+}
+
+// A lane's sweeps in order, of np sums, MANY of which are in flight where there are more than eight: waiting for each of the 36 sweeps that a tensor
+// of 2.4 M elements leaves a lane made the kernel 13 us, eight at a time 5; of the 144 sums of its groups k_trigger for 16 ResNet-18 workers 12.2 us with
+// eight, 7.4 with 32 (a step with spikes 822 -> 817, with given gradients 1005 -> 1001).  k_topk_decide takes 16, as its registers cost workgroups
+// beside it: 9 -> 8 and 22 -> 21 us for 8 ResNet-50 and 64 ResNet-18 workers.
+template <int N, int F>
+__device__ __forceinline__ void add_in_order(const double* part, uint32_t np, uint32_t first, double* acc) {
+  SweepSums<F> s[N / F];
+#pragma unroll
+  for (uint32_t u = 0; u < N / F; ++u) s[u] = load_sweep<F>(part, np, first + 64 * u + lane_id());
+#pragma unroll
+  for (uint32_t u = 0; u < N / F; ++u) *acc += s[u].added();
+}
+template <int MANY, int F>
 __device__ __forceinline__ double ordered_lane_sum(const double* part, uint32_t np) {
   double acc = 0.0;
-  for (uint32_t i = lane_id(); i < np; i += 64 * 8) {
-    double v[8];
-#pragma unroll
-    for (uint32_t u = 0; u < 8; ++u) v[u] = i + 64 * u < np ? part[i + 64 * u] : 0.0;
-#pragma unroll
-    for (uint32_t u = 0; u < 8; ++u) acc += v[u];
-  }
-  return acc;
-}
-
-// The same with MANY loads in flight where there are more than eight (part: the same in all lanes; past the end zeros): windows of 256 elements
-// leave a lane 144 partials of such a tensor.  k_trigger for 16 ResNet-18 workers 12.2 -> 7.4 us with 32 (a step with spikes 822 -> 817, with given
-// gradients 1005 -> 1001); k_topk_decide takes 16, as its registers cost workgroups beside it: 9 -> 8 and 22 -> 21 us for 8 ResNet-50 and 64 ResNet-18 workers.
-template <int N>
-__device__ __forceinline__ void add_in_order(const double* part, uint32_t np, uint32_t first, double* acc) {
-  double v[N];
-#pragma unroll
-  for (uint32_t u = 0; u < N; ++u) v[u] = load_f64(part, np * 8, (first + 64 * u + lane_id()) * 8);
-#pragma unroll
-  for (uint32_t u = 0; u < N; ++u) *acc += v[u];
-}
-template <int MANY>
-__device__ __forceinline__ double ordered_long_sum(const double* part, uint32_t np) {
-  double acc = 0.0;
   uint32_t i = 0;
-  for (; i + 64 * 8 < np; i += 64 * MANY) add_in_order<MANY>(part, np, i, &acc);
-  if (i < np) add_in_order<8>(part, np, i, &acc);
+  const uint32_t sweeps = np / F;
+  if constexpr (MANY > 8)
+    for (; i + 64 * (8 / F) < sweeps; i += 64 * (MANY / F)) add_in_order<MANY, F>(part, np, i, &acc);
+  for (; i < sweeps; i += 64 * (8 / F)) add_in_order<8, F>(part, np, i, &acc);
   return acc;
 }
 
-// Sums of the tensor's sweep partials in a fixed order, by one whole wavefront; valid in every lane.  seg: the same in all lanes.
+// Sums of the tensor's sweep partials in a fixed order, by one whole wavefront; valid in every lane.  seg: the same in all lanes.  F: T.fine.
 // *hat_sums: the squared norm of xhat comes from the arena sums (norm-difference trigger with
 // Top-K, or before the tensor's first event) rather than from the scalar kept at its last event.
-template <int MANY>
+template <int MANY, int F>
 __device__ __forceinline__ void segment_sums(const Tables& T, const StepArgs& A, uint32_t seg, double* acc_out,
                                              double* acc_hat_out, bool* hat_sums_out) {
   const uint32_t r = seg / T.L, l = seg % T.L;
   const LayerDesc ld = T.layers[l];
-  const uint32_t sums = T.SW * T.fine, np = ld.nchunks * sums;
+  const uint32_t sums = T.SW * F, np = ld.nchunks * sums;
   const double* part = T.partials + ((size_t)r * T.C + ld.chunk0) * sums;
   double acc_hat = 0.0;
-  const double acc = wave_sum(ordered_long_sum<MANY>(part, np));
+  const double acc = wave_sum(ordered_lane_sum<MANY, F>(part, np));
   const bool hat_sums = A.norm_src == 2 || (A.norm_src == 1 && T.last_event[seg] < 0);
   if (hat_sums) {
     const double* ph = T.partials_hat + ((size_t)r * T.C + ld.chunk0) * sums;
-    acc_hat = wave_sum(ordered_long_sum<MANY>(ph, np));
+    acc_hat = wave_sum(ordered_lane_sum<MANY, F>(ph, np));
   }
   *acc_out = acc;
   *acc_hat_out = acc_hat;

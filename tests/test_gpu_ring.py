@@ -130,3 +130,29 @@ def test_replays_of_streamed_steps(evg, P):
         assert np.array_equal(a.decisions()["fired"], b.decisions()["fired"]), k
     for name in ("x", "xhat", "vel", "mbox_l", "mbox_r"):
         assert np.array_equal(a.state(name), b.state(name)), name
+
+
+# the sums that the next test reads come back as they were, and so does all that follows from them
+@pytest.mark.parametrize("P,sizes,stream", [(3, EDGES * 6, False), (5, EDGES * 4 + [65537], False), (8, EDGES * 10, False), (3, EDGES * 25, False),
+                                            (8, EDGES * 3 + [20_001], True), (16, EDGES * 3, True), (40, EDGES, True)])
+@pytest.mark.parametrize("kw", [dict(), dict(trigger_kind=1), dict(topk_ppm=100_000), dict(topk_ppm=100_000, trigger_kind=1)],
+                         ids=["whole", "norms", "topk", "norms_topk"])
+def test_a_resumed_ring_goes_on_bit_for_bit(evg, P, sizes, stream, kw):
+    kw = dict(kw)
+    over = {k: kw.pop(k) for k in ("trigger_kind",) if k in kw}
+    w = _workload(P, sizes, **kw)
+    a, b = (evg.Ring.from_workload(w, mailbox_fill=0.0, access_mode=evg.ACCESS_STREAM if stream else evg.ACCESS_CACHED, **over) for _ in range(2))
+    for k in range(4):
+        a.step(k)
+    b.import_state(a.export_state())
+    for k in range(4, 9):
+        a.step(k)
+        b.step(k)
+        da, db = a.decisions(), b.decisions()
+        for name in ("fired", "norm", "delta_before"):
+            assert np.array_equal(da[name].view(np.uint8), db[name].view(np.uint8)), (k, name)
+        ba, bb = a.export_state(), b.export_state()
+        end = len(ba["blob"]) - (P * len(sizes) * 2048 * 4 if "topk_ppm" in kw else 0)      # (behind it the counts of keys, whose cut into bins may differ)
+        assert np.array_equal(ba["blob"][:end], bb["blob"][:end]), k
+    for name in ("x", "xhat", "vel", "mbox_l", "mbox_r"):
+        assert np.array_equal(a.state(name), b.state(name)), name
