@@ -278,6 +278,16 @@ evg_status evg_step_next(evg_ctx* c, const float* grad);
 /* Waits for the stream, then fills *out (array members that are non-NULL too). */
 evg_status evg_stats(evg_ctx* c, evg_stats_t* out);
 
+/* The update pass that evg_init chose for this context, by its sizes, options and room: EVG_PASS_*, how many workers of the
+ * ring a workgroup has, and (EVG_PASS_PART, EVG_PASS_RING; else 0) of how many elements.  Any pointer may be NULL. */
+enum {
+  EVG_PASS_CHUNK = 0, /* a workgroup has a stretch of one worker's tensor                                  */
+  EVG_PASS_WALK = 1,  /* it goes around the ring, or a part of it, worker by worker (streaming rings)      */
+  EVG_PASS_PART = 2,  /* it has some neighbouring workers at once (cached rings)                           */
+  EVG_PASS_RING = 3   /* it has all workers at once                                                        */
+};
+evg_status evg_update_pass(evg_ctx* c, uint32_t* pass, uint32_t* workers, uint32_t* elements);
+
 /* Decisions of the most recent step, HOST arrays of P*L entries, any may be NULL:
  * fired (0 = silent, 1 = whole tensor, 2 = Top-K message), near_tie (the 1e-6
  * band), norm and the threshold the norm was compared with.  Waits for the stream. */

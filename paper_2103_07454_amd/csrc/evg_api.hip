@@ -1071,6 +1071,15 @@ evg_status evg_stats(evg_ctx* c, evg_stats_t* out) {
   return EVG_OK;
 }
 
+evg_status evg_update_pass(evg_ctx* c, uint32_t* pass, uint32_t* workers, uint32_t* elements) {
+  if (!c) return fail(EVG_ERR_INVALID, "context is NULL");
+  const uint32_t which = c->walk ? EVG_PASS_WALK : c->parts.groups ? EVG_PASS_RING : c->parts.count ? EVG_PASS_PART : EVG_PASS_CHUNK;
+  if (pass) *pass = which;
+  if (workers) *workers = which == EVG_PASS_CHUNK ? 1 : c->part;
+  if (elements) *elements = which == EVG_PASS_RING ? 256 * c->parts.groups : which == EVG_PASS_PART ? (uint32_t)kSweep : 0;
+  return EVG_OK;
+}
+
 evg_status evg_last_decisions(evg_ctx* c, uint8_t* fired, uint8_t* near_tie, float* norm, float* delta_before) {
   if (!c) return fail(EVG_ERR_INVALID, "context is NULL");
   const Tables& t = c->t;

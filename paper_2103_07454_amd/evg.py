@@ -26,7 +26,7 @@ TRIGGER_DRIFT_NORM, TRIGGER_NORM_DIFF = 0, 1
 PHASES = ("norm", "trigger", "send_full", "topk_select", "topk_send", "update", "deliver")
 
 EXPORTS = ("evg_padded_numel", "evg_layer_offsets", "evg_init", "evg_init_static", "evg_step", "evg_step_next", "evg_stats",
-           "evg_last_decisions", "evg_message", "evg_message_hashes", "evg_average", "evg_state_size", "evg_state_export",
+           "evg_update_pass", "evg_last_decisions", "evg_message", "evg_message_hashes", "evg_average", "evg_state_size", "evg_state_export",
            "evg_state_import", "evg_timing", "evg_timing_read",
            "evg_destroy", "evg_strerror", "evg_error_text")
 
@@ -91,6 +91,7 @@ def lib():
         l.evg_step.argtypes = [vp, C.c_uint64, vp]
         l.evg_step_next.argtypes = [vp, vp]
         l.evg_stats.argtypes = [vp, C.POINTER(Stats)]
+        l.evg_update_pass.argtypes = [vp, vp, vp, vp]
         l.evg_last_decisions.argtypes = [vp, vp, vp, vp, vp]
         l.evg_message.argtypes = [vp, C.c_uint32, C.c_uint32, vp, vp, C.c_uint64, u64p]
         l.evg_message_hashes.argtypes = [vp, vp, vp]
@@ -270,6 +271,12 @@ class Ring:
         return out
 
     # -- inspection ----------------------------------------------------------
+    def update_pass(self):
+        """The update pass's kernel, and the workers and (k_update_part, k_update_ring) elements that a workgroup has."""
+        v = [C.c_uint32() for _ in range(3)]
+        _check(lib().evg_update_pass(self._h, *map(C.byref, v)))
+        return ("k_update", "k_update_walk", "k_update_part", "k_update_ring")[v[0].value], v[1].value, v[2].value
+
     def decisions(self):
         S = self.P * self.L
         fired = np.zeros(S, np.uint8); near = np.zeros(S, np.uint8)

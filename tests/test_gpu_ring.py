@@ -156,3 +156,16 @@ def test_a_resumed_ring_goes_on_bit_for_bit(evg, P, sizes, stream, kw):
         assert np.array_equal(ba["blob"][:end], bb["blob"][:end]), k
     for name in ("x", "xhat", "vel", "mbox_l", "mbox_r"):
         assert np.array_equal(a.state(name), b.state(name)), name
+
+
+# the shapes that ring_shape and stream_shape choose for the rings above, and the other passes at their edges
+@pytest.mark.parametrize("P,sizes,kw,stream,given,want", [
+    (3, EDGES, {}, False, False, ("k_update_ring", 3, 256)), (5, EDGES + [65537], {}, False, False, ("k_update_ring", 5, 512)),
+    (3, EDGES * 25, {}, False, False, ("k_update_ring", 3, 1024)), (12, EDGES * 10 + [5000], dict(topk_ppm=100_000), False, False, ("k_update_ring", 12, 512)),
+    (16, [700] * 200 + EDGES * 4, dict(topk_ppm=100_000), False, False, ("k_update_ring", 16, 256)),
+    (17, EDGES, {}, False, False, ("k_update_part", 2, 1024)), (8, EDGES, {}, True, False, ("k_update_ring", 8, 512)),
+    (9, EDGES, {}, True, False, ("k_update_ring", 9, 256)), (65, EDGES, {}, True, False, ("k_update_walk", 1, 0)),
+    (5, EDGES, dict(topk_ppm=100_000), True, False, ("k_update_walk", 5, 0))], ids=str)
+def test_the_pass_chosen(evg, P, sizes, kw, stream, given, want):
+    ring = evg.Ring.from_workload(_workload(P, sizes, **kw), grad_mode=int(given), access_mode=evg.ACCESS_STREAM if stream else evg.ACCESS_AUTO)
+    assert ring.update_pass() == want
