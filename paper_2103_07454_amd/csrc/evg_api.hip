@@ -523,7 +523,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   // carried from step to step: a caller may have written x since the copies were made, and the sender goes by x.
   bool pull = c->cached && !cfg->delivery_delay &&
               !(cfg->topk_ppm && (cfg->xhat_reset || cfg->norm_mode == EVG_NORM_SEPARATE || !copies_fit));
-  bool in_parts = false, one_launch = false, one_shot = false, may_be = true, sets_counted = false;
+  bool in_parts = false, one_launch = false, one_shot = false, may_be = true, ring_may_be = true, sets_counted = false;
   bool codes = cfg->topk_ppm && cfg->norm_mode == EVG_NORM_FUSED, choose = false, hist_copies = codes;
   uint64_t need = 0, ring_windows = 0;
   // A tensor that is most of a ring has all workgroups of an update pass add their counts to one histogram, on all XCDs, at some 30 ns for each
@@ -571,7 +571,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     // 8 15.7 / 14.3 / 16.6, on 12 25.7 / 22.6 / 19.2, on 16 34.1 / 33.4 / 30.7; 438 on 8 24.9 / 21.8 / 18.4, on 16 53.3 / 48.9 / 49.0.
     groups = quads = 0;
     fine = 1;
-    if (in_parts && small_ring) ring_shape(P, windows, longest, cfg->topk_ppm != 0, one_launch, cfg->grad_mode == EVG_GRAD_BUFFER, &groups, &quads);
+    if (ring_may_be && in_parts && small_ring) ring_shape(P, windows, longest, cfg->topk_ppm != 0, one_launch, cfg->grad_mode == EVG_GRAD_BUFFER, &groups, &quads);
     if (may_be && !c->cached && !cfg->topk_ppm && !cfg->delivery_delay && cfg->norm_mode == EVG_NORM_FUSED) stream_shape(P, Npad * 4, &groups, &quads);
     one_shot = groups && !in_parts;
     if (groups) {
@@ -599,7 +599,11 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     c->on_lines = cut_chunks(true);
   }
   if (!c->on_lines) (void)cut_chunks(false);
-  if (use_scratch && need > kScratchBytes && in_parts && !cfg->topk_ppm) {        // thousands of short tensors: no room for what the parts take
+  if (use_scratch && need > kScratchBytes && in_parts && groups) {      // thousands of short tensors: no room for a sum a group, parts of the ring
+    ring_may_be = false;                                                // may have it
+    (void)cut_chunks(false);
+  }
+  if (use_scratch && need > kScratchBytes && in_parts && !cfg->topk_ppm) {        // ... nor for what the parts take
     may_be = false;
     (void)cut_chunks(false);
   }

@@ -165,7 +165,7 @@ def test_a_resumed_ring_goes_on_bit_for_bit(evg, P, sizes, stream, kw):
     (16, [700] * 200 + EDGES * 4, dict(topk_ppm=100_000), False, False, ("k_update_ring", 16, 256)),
     (17, EDGES, {}, False, False, ("k_update_part", 2, 1024)), (8, EDGES, {}, True, False, ("k_update_ring", 8, 512)),
     (9, EDGES, {}, True, False, ("k_update_ring", 9, 256)), (65, EDGES, {}, True, False, ("k_update_walk", 1, 0)),
-    (5, EDGES, dict(topk_ppm=100_000), True, False, ("k_update_walk", 5, 0))], ids=str)
+    (5, EDGES, dict(topk_ppm=100_000), True, False, ("k_update_walk", 5, 0))], ids=lambda v: f"{len(v)} tensors" if isinstance(v, list) else str(v))
 def test_the_pass_chosen(evg, P, sizes, kw, stream, given, want):
     ring = evg.Ring.from_workload(_workload(P, sizes, **kw), grad_mode=int(given), access_mode=evg.ACCESS_STREAM if stream else evg.ACCESS_AUTO)
     assert ring.update_pass() == want

@@ -128,3 +128,12 @@ def test_the_largest_configurations_admitted(evg, P, most, more, kw, over):
         assert np.array_equal(a.state(name), b.state(name)), name
     a.close()
     b.close()
+
+
+def test_where_a_sum_a_group_has_no_room_parts_of_the_ring_do(evg):
+    w = workload(12, [4] * 36_000)
+    a = run_pair(evg, w, 4, same_tables=False)
+    b = evg.Ring.from_workload(w)
+    assert a.update_pass() == ("k_update_part", 8, 1024) and b.update_pass()[0] == "k_update_ring"
+    a.close()
+    b.close()
