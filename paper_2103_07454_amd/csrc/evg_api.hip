@@ -81,6 +81,7 @@ struct evg_ctx {
   bool walk = false;                // the update pass walks the ring
   uint32_t part = 0;                // workers of the ring that one workgroup of a walking pass goes through
   ChooseTables choose{};            // longest = 0: selections are made in many launches
+  uint32_t most_sums = 0;           // partials of the longest tensor
   bool cached = false;              // the five arenas together fit the last-level cache
   bool device_ahead = false;        // evg_step_next has been used: replays of a captured graph
                                     // advance the device's iteration without the host seeing
@@ -662,6 +663,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   t.P = P; t.L = L; t.C = (uint32_t)C; t.S = (uint32_t)S;
   t.SW = SW;
   t.fine = fine;
+  for (const LayerDesc& d : layers) c->most_sums = std::max(c->most_sums, d.nchunks * SW * fine);
   t.hist_len = hist_len;
   t.Ktot = (uint32_t)ktot;
   t.Npad = Npad;
@@ -916,7 +918,7 @@ static evg_status enqueue_step(evg_ctx* c, const StepArgs& args, bool timed) {
     Phase ph(c, EVG_PH_TRIGGER);
     HIP_TRY(a.choose       ? launch_topk_choose(t, a, c->choose, c->stream)
             : a.hist_fused ? launch_topk_decide(t, a, c->stream)
-                           : launch_trigger(t, a, c->stream));
+                           : launch_trigger(t, a, c->most_sums, c->stream));
     if ((st = ph.end()) != EVG_OK) return st;
   }
   // Whole sends: with delayed delivery the mailboxes are written after the update, a cache-resident ring's receivers

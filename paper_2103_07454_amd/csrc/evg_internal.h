@@ -185,7 +185,8 @@ hipError_t launch_walk(const Tables& t, const StepArgs& a, uint32_t dist, uint32
 hipError_t launch_part(const Tables& t, const StepArgs& a, const PartTables& p, uint32_t dist, uint32_t grad_mode, int norm, hipStream_t s);
 // the same, a workgroup to a window of the whole ring
 hipError_t launch_ring(const Tables& t, const StepArgs& a, const PartTables& p, uint32_t dist, uint32_t grad_mode, int norm, hipStream_t s);
-hipError_t launch_trigger(const Tables& t, const StepArgs& a, hipStream_t s);
+// most_sums: the partials of the longest tensor
+hipError_t launch_trigger(const Tables& t, const StepArgs& a, uint32_t most_sums, hipStream_t s);
 hipError_t launch_copy(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
 hipError_t launch_deliver(const Tables& t, uint32_t chunk_elems, hipStream_t s);
 hipError_t launch_topk_decide(const Tables& t, const StepArgs& a, hipStream_t s);
