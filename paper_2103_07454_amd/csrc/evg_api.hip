@@ -387,13 +387,18 @@ static void ring_shape(uint32_t P, uint64_t windows, uint32_t longest, bool topk
 // 36.2 / 36.8, of width 21 on 23 80.0 / - / - / 47.3 / 51.0; perceptrons of 471 000 elements on 18 45.2 / - / - / 38.0 / 38.6; ResNet-50 of width 48 on 29 1584 / - /
 // - / 1601 / 1500, of width 39 on 19 943 / - / - / 917 / 902; ResNet-20 of width 24 on 47 205 / - / - / - / 140, ResNet-18 of width 20 on 57 (1.2 GB) 403 / - / - / - / 367, of width 26 on 47
 // (1.7 GB) 539 / - / - / - / 571, of width 42 on 35 (3.2 GB) 631 / - / - / - / 685.
-// All workers' stretches of a window are read and written at once.  Where they lie multiples of 8 KB apart, or nearly, those of more than eight workers get in each
+// A ring differs by up to a fifth between allocations of its arenas, so that a line takes many rings and some allocations of each (four): 98 drawn ones of 3 to
+// 32 workers are 0.91 to 1.64 times as fast as walked (1.07 in the middle; 52 of more than 1.5 GB 0.91 to 1.12, 1.04), 9 ResNets on 33 to 40 1.06 to
+// 1.61.  Of more than 32 workers whose network is mostly one long tensor, 28 perceptrons with a tensor of 280 000 elements and more are 0.87 to 1.10 times as
+// fast (0.99): walked; 9 shorter ones 1.03 to 1.37.
+// All workers' stretches of a window are read and written at once.  Where they lie multiples of 8 KB apart, or nearly, those of more than eight workers can get in each
 // other's way in the memory: ResNet-18 of width 39 with workers 8192 n + 0, 256, 1024, 2048 and 4096 bytes apart on 20 workers 0.83 .. 0.93, 0.95, 0.98, 0.97 and 0.97
-// times as fast as walked, on 12 0.86 .. 0.91, 0.95, 1.01, 1.01 and 0.99, on 7 1.00 .. 1.08, 1.05, 1.08, 1.09 and 1.10.
-static void stream_shape(uint32_t P, uint64_t row, uint32_t* groups, uint32_t* quads) {
+// times as fast as walked, on 12 0.86 .. 0.91, 0.95, 1.01, 1.01 and 0.99, on 7 1.00 .. 1.08, 1.05, 1.08, 1.09 and 1.10.  (Not always: ResNet-50s of width 17 to 44 on 10 to 29
+// workers, 8192 n + 0 and 256 apart, would be 1.04 to 1.18 times as fast.)
+static void stream_shape(uint32_t P, uint64_t row, uint64_t N, uint32_t longest, uint32_t* groups, uint32_t* quads) {
   *groups = *quads = 0;
   const uint64_t bytes = 5 * P * row, apart = (row + 256) % 8192;      // (rows are multiples of 256 bytes)
-  if (P > kRingMost || (P > 32 && bytes > (1ull << 30)) || (P > 8 && apart <= 512)) return;
+  if (P > kRingMost || (P > 32 && (bytes > (1ull << 30) || (longest > 262144 && 2ull * longest > N))) || (P > 8 && apart <= 512)) return;
   *groups = P <= 8 ? 2 : 1;
   *quads = P <= 16 ? 1 : P <= 32 && bytes < (600ull << 20) ? 2 : 4;
 }
@@ -573,7 +578,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     groups = quads = 0;
     fine = 1;
     if (ring_may_be && in_parts && small_ring) ring_shape(P, windows, longest, cfg->topk_ppm != 0, one_launch, cfg->grad_mode == EVG_GRAD_BUFFER, &groups, &quads);
-    if (may_be && !c->cached && !cfg->topk_ppm && !cfg->delivery_delay && cfg->norm_mode == EVG_NORM_FUSED) stream_shape(P, Npad * 4, &groups, &quads);
+    if (may_be && !c->cached && !cfg->topk_ppm && !cfg->delivery_delay && cfg->norm_mode == EVG_NORM_FUSED) stream_shape(P, Npad * 4, c->N, longest, &groups, &quads);
     one_shot = groups && !in_parts;
     if (groups) {
       fine = one_shot && groups == 2 ? 2 : kGroupSums;

@@ -169,3 +169,13 @@ def test_a_resumed_ring_goes_on_bit_for_bit(evg, P, sizes, stream, kw):
 def test_the_pass_chosen(evg, P, sizes, kw, stream, given, want):
     ring = evg.Ring.from_workload(_workload(P, sizes, **kw), grad_mode=int(given), access_mode=evg.ACCESS_STREAM if stream else evg.ACCESS_AUTO)
     assert ring.update_pass() == want
+
+
+# streaming whole sends: where the slices of more than eight workers lie multiples of 8 KB apart, or up to 256 bytes more or less, and where more than 32 workers have
+# mostly one long tensor, rings are walked; all others of up to 64 workers are not
+@pytest.mark.parametrize("P,sizes,walked", [(9, [16_384 + d], abs(d) < 128) for d in (-128, -64, 0, 64, 128)] + [
+    (8, [16_384], False), (64, [16_384 - 64], True), (64, [16_384 - 128], False), (33, [262_144, 1000], False), (33, [262_148, 1000], True),
+    (32, [262_148, 1000], False), (33, [262_148, 262_148, 1000], False)], ids=lambda v: str(v).replace(" ", ""))
+def test_the_streamed_rings_that_are_walked(evg, P, sizes, walked):
+    ring = evg.Ring.from_workload(_workload(P, sizes), access_mode=evg.ACCESS_STREAM)
+    assert (ring.update_pass()[0] == "k_update_walk") == walked
