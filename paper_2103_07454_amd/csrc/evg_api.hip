@@ -358,23 +358,45 @@ static uint64_t admitted_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, 
 // ResNet-18 of 729 on 4 16.9 / 18.2 / 18.6 / 17.8 / 16.8, ResNet-20 of 923 on 4 17.2 / - / - / - / 17.8; more workers have one float4 each of several: 120 windows on 24 12.7 and 15.4.  Top-K, kernels_parts.hip / 1 2 / 2 2:
 // ResNet-20 of 314 windows on 8 33.6 / 32.4 / 32.3, on 16 67.3 / 60.1 / 63.9, of 426 on 15 86 / 76 / 83; perceptrons of 129 on 11 32.4 / - / 34.9, of
 // 237 on 10 44.0 / 49.2 / 45.8; ResNet-18 of 729 on 4 39.7 / - / 41.4, ResNet-20 of 509 on 4 with given gradients 27.8 / - / 25.8.
-static void ring_shape(uint32_t P, uint64_t windows, uint32_t longest, bool topk, bool tests, bool given, uint32_t* groups, uint32_t* quads) {
+// One ring differs by up to a fifth between allocations of its arenas.  More rings, each in four of them, how many times as fast as with kernels_parts.hip:
+//   windows that are mostly empty, on 3 and 4 workers (tensors of 4, 30 and 200 elements): 4 2 0.82 .. 1.13, 1 1 1.4 .. 2.5
+//   a tensor of 131 000 elements on 8: 2 1 0.92, 1 1 1.21; of 112 000 to 128 000 on 5 to 7 2 1 1.13 .. 1.15, 1 1 1.13 .. 1.18
+//   7 and 8 workers, ResNets of 4000 units and more: normal gradients 0.90 .. 1.00 and 1.10 (7 rings), Student-t's and given ones 1.00 .. 1.23
+//   9 to 12, drawn gradients: where every CU has had two workgroups and a few are left (513 to 600) 0.89 .. 0.99, else 0.98 .. 1.24 (22 rings, 1.06 in the middle)
+//   13 to 16, drawn gradients: ResNets 0.78 .. 1.11 (45 rings, 0.99), perceptrons with normal ones 1.08 .. 1.20, with Student-t's 0.81 .. 0.99
+//   13 to 16, given ones, where a workgroup has a CU: 1 1 of up to 256 of them 1.19 .. 1.28, of more 0.81 .. 0.94 where 2 2 is 1.05 .. 1.17; 2 2 of
+//   264 (ResNet-20 of width 10) 0.86 .. 0.93, of 265 to 288 in a perceptron 1.09 .. 1.11, else 0.89 .. 1.31 (53 rings, 1.11)
+//   Top-K, 9 to 16, drawn gradients: of 2700 units and more 0.85 .. 1.07 (34 rings, 0.95), fewer 1.00 .. 1.13 (with a tensor of 155 000 elements 0.92)
+static void ring_shape(uint32_t P, uint64_t windows, const std::vector<LayerDesc>& layers, uint64_t N, bool topk, bool tests, bool given, bool normal,
+                       uint32_t* groups, uint32_t* quads) {
   *groups = *quads = 0;
   const uint64_t units = windows * P;
+  uint64_t longest = 0, of256 = 0, of512 = 0;              // elements of the longest tensor; workgroups
+  for (const LayerDesc& d : layers) {
+    longest = std::max<uint64_t>(longest, d.numel);
+    of256 += (d.numel + 255ull) / 256;
+    of512 += (d.numel + 511ull) / 512;
+  }
+  const bool one_long = 2 * longest > N;
   if (P > 16 || (P > 12 && units < (given && !topk ? 800 : 4000))) return;
   if (topk) {
-    if (units < 1700 || (longest > 200000 && P > 8) || (P <= 4 && !given)) return;
+    if (units < 1700 || (longest > 150000 && P > 8) || (P <= 4 && !given) || (P > 8 && !given && units >= 2700)) return;
     *groups = P > 12 ? 1 : 2;
     *quads = 2;
+  } else if (P > 12) {
+    if (given ? of256 > 256 && of512 > 256 && of512 <= 288 && !one_long : !(one_long && normal)) return;
+    *groups = *quads = given && of256 <= 256 ? 1 : 2;
   } else if (P <= 4 && windows >= 700 && !given) {
     return;
   } else if (P <= 4 && windows >= 400) {
-    *groups = 4;
-    *quads = 2;
+    const bool full = 5 * N >= 2 * 1024 * windows;
+    *groups = full ? 4 : 1;
+    *quads = full ? 2 : 1;
   } else if (units >= 1300) {
+    if (!given && !one_long && (P > 8 ? of512 > 512 && of512 <= 600 : P > 6 && normal && units >= 4000)) return;
     *groups = *quads = 2;
   } else {
-    *groups = tests && longest > 65536 && P <= 8 ? 2 : 1;
+    *groups = tests && longest > 65536 && P <= 6 ? 2 : 1;
     *quads = 1;
   }
 }
@@ -577,7 +599,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     // 8 15.7 / 14.3 / 16.6, on 12 25.7 / 22.6 / 19.2, on 16 34.1 / 33.4 / 30.7; 438 on 8 24.9 / 21.8 / 18.4, on 16 53.3 / 48.9 / 49.0.
     groups = quads = 0;
     fine = 1;
-    if (ring_may_be && in_parts && small_ring) ring_shape(P, windows, longest, cfg->topk_ppm != 0, one_launch, cfg->grad_mode == EVG_GRAD_BUFFER, &groups, &quads);
+    if (ring_may_be && in_parts && small_ring) ring_shape(P, windows, layers, c->N, cfg->topk_ppm != 0, one_launch, cfg->grad_mode == EVG_GRAD_BUFFER, cfg->synth.dist == EVG_DIST_NORMAL, &groups, &quads);
     if (may_be && !c->cached && !cfg->topk_ppm && !cfg->delivery_delay && cfg->norm_mode == EVG_NORM_FUSED) stream_shape(P, Npad * 4, c->N, longest, &groups, &quads);
     one_shot = groups && !in_parts;
     if (groups) {

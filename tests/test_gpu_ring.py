@@ -162,10 +162,18 @@ def test_a_resumed_ring_goes_on_bit_for_bit(evg, P, sizes, stream, kw):
 @pytest.mark.parametrize("P,sizes,kw,stream,given,want", [
     (3, EDGES, {}, False, False, ("k_update_ring", 3, 256)), (5, EDGES + [65537], {}, False, False, ("k_update_ring", 5, 512)),
     (3, EDGES * 25, {}, False, False, ("k_update_ring", 3, 1024)), (12, EDGES * 10 + [5000], dict(topk_ppm=100_000), False, False, ("k_update_ring", 12, 512)),
-    (16, [700] * 200 + EDGES * 4, dict(topk_ppm=100_000), False, False, ("k_update_ring", 16, 256)),
+    (16, [700] * 200 + EDGES * 4, dict(topk_ppm=100_000), False, True, ("k_update_ring", 16, 256)),
     (17, EDGES, {}, False, False, ("k_update_part", 2, 1024)), (8, EDGES, {}, True, False, ("k_update_ring", 8, 512)),
     (9, EDGES, {}, True, False, ("k_update_ring", 9, 256)), (65, EDGES, {}, True, False, ("k_update_walk", 1, 0)),
-    (5, EDGES, dict(topk_ppm=100_000), True, False, ("k_update_walk", 5, 0))], ids=lambda v: f"{len(v)} tensors" if isinstance(v, list) else str(v))
+    (5, EDGES, dict(topk_ppm=100_000), True, False, ("k_update_walk", 5, 0)),
+    (7, EDGES + [65537], {}, False, False, ("k_update_ring", 7, 256)), (4, [200] * 450, {}, False, True, ("k_update_ring", 4, 256)),
+    (8, [1100] * 260, {}, False, False, ("k_update_part", 8, 1024)), (8, [1100] * 260, dict(dist=1), False, False, ("k_update_ring", 8, 512)),
+    (10, [1000] * 260, {}, False, False, ("k_update_part", 4, 1024)), (10, [1000] * 260, {}, False, True, ("k_update_ring", 10, 512)),
+    (13, [600] * 320, {}, False, False, ("k_update_part", 8, 1024)), (13, [320_000, 9], {}, False, False, ("k_update_ring", 13, 512)),
+    (13, [320_000, 9], dict(dist=1), False, False, ("k_update_part", 8, 1024)),
+    (13, [64_000, 10], {}, False, True, ("k_update_ring", 13, 256)), (13, [2000] * 66, {}, False, True, ("k_update_part", 4, 1024)),
+    (13, [2000] * 150, {}, False, True, ("k_update_ring", 13, 512)), (10, [1000] * 280, dict(topk_ppm=100_000), False, False, ("k_update_part", 4, 1024)),
+    (10, [1000] * 280, dict(topk_ppm=100_000), False, True, ("k_update_ring", 10, 512))], ids=lambda v: f"{len(v)} tensors" if isinstance(v, list) else str(v))
 def test_the_pass_chosen(evg, P, sizes, kw, stream, given, want):
     ring = evg.Ring.from_workload(_workload(P, sizes, **kw), grad_mode=int(given), access_mode=evg.ACCESS_STREAM if stream else evg.ACCESS_AUTO)
     assert ring.update_pass() == want
