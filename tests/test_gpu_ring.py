@@ -170,7 +170,7 @@ def test_a_resumed_ring_goes_on_bit_for_bit(evg, P, sizes, stream, kw):
     (8, [1100] * 260, {}, False, False, ("k_update_part", 8, 1024)), (8, [1100] * 260, dict(dist=1), False, False, ("k_update_ring", 8, 512)),
     (10, [1000] * 260, {}, False, False, ("k_update_part", 4, 1024)), (10, [1000] * 260, {}, False, True, ("k_update_ring", 10, 512)),
     (13, [600] * 320, {}, False, False, ("k_update_part", 8, 1024)), (13, [320_000, 9], {}, False, False, ("k_update_ring", 13, 512)),
-    (13, [320_000, 9], dict(dist=1), False, False, ("k_update_part", 8, 1024)),
+    (13, [320_000, 9], dict(dist=1), False, False, ("k_update_part", 4, 1024)),
     (13, [64_000, 10], {}, False, True, ("k_update_ring", 13, 256)), (13, [2000] * 66, {}, False, True, ("k_update_part", 4, 1024)),
     (13, [2000] * 150, {}, False, True, ("k_update_ring", 13, 512)), (10, [1000] * 280, dict(topk_ppm=100_000), False, False, ("k_update_part", 4, 1024)),
     (10, [1000] * 280, dict(topk_ppm=100_000), False, True, ("k_update_ring", 10, 512))], ids=lambda v: f"{len(v)} tensors" if isinstance(v, list) else str(v))
