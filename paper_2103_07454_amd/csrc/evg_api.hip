@@ -563,6 +563,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   uint32_t ring_part = 0;
   uint32_t longest = 0, groups = 0, quads = 0, fine = 1;
   for (const LayerDesc& d : layers) longest = std::max(longest, d.numel);
+  const uint32_t most_chosen = cfg->grad_mode == EVG_GRAD_BUFFER ? kChooseMost : cfg->synth.spike_prob > 0.0f ? kChooseMostSpiky : P > 3 ? kChooseMost : kChooseMostOf3;
   auto cut_chunks = [&](bool on_lines) {
     chunks.clear();
     uint32_t most_sweeps = 0;
@@ -584,7 +585,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     }
     // Cached rings that send whole tensors and accumulate the norms in the update pass are updated in parts of the ring; in
     // one launch per iteration where one wavefront sums a tensor's sweep partials with two loads per lane.
-    in_parts = may_be && pull && cfg->norm_mode == EVG_NORM_FUSED && arena_bytes < (1ull << 30) && (!cfg->topk_ppm || (codes && longest <= (P > 3 || cfg->grad_mode == EVG_GRAD_BUFFER ? kChooseMost : kChooseMostOf3)));
+    in_parts = may_be && pull && cfg->norm_mode == EVG_NORM_FUSED && arena_bytes < (1ull << 30) && (!cfg->topk_ppm || (codes && longest <= most_chosen));
     one_launch = in_parts && !cfg->topk_ppm && most_sweeps <= 128;
     // (admission counts the second set of what the tests read also where the parts find no room, as it always has)
     sets_counted = pull && !cfg->topk_ppm && cfg->norm_mode == EVG_NORM_FUSED && most_sweeps <= 128;

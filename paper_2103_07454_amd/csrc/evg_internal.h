@@ -200,8 +200,10 @@ struct ChooseTables { const ChooseDesc* tensors; uint32_t longer, longest; };
 // Longer ones are too much for one workgroup.  Steps in us, in many launches / one workgroup a tensor, rings of 3, 5 (4) and 8 (9) perceptrons whose
 // longest tensor has 329 000 elements 41.6 / 32.2, (43.8 / 33.6), (62.3 / 41.5); 502 000 44.6 / 38.7, 51.4 / 44.8, 75.2 / 53.0; 706 000 49.8 / 50.7, (59.5 /
 // 53.4), (105.6 / 97.4); 784 000 51.7 / 54.4, 74.2 / 66.3, 104.1 / 87.2; with given gradients 329 000 39.6 / 25.9, (42.4 / 27.8), (63.4 / 43.0); 706 000
-// 52.5 / 41.3, (60.7 / 47.7), (104.7 / 89.9); 784 000 55.2 / 44.5, 76.7 / 56.5, 104.2 / 79.6.  Three workers that draw their gradients: kChooseMostOf3.
-constexpr uint32_t kChooseMost = 819200, kChooseMostOf3 = 655360;
+// 52.5 / 41.3, (60.7 / 47.7), (104.7 / 89.9); 784 000 55.2 / 44.5, 76.7 / 56.5, 104.2 / 79.6.  Three workers that draw their gradients: kChooseMostOf3.  With
+// spikes kChooseMostSpiky: after one a tensor's threshold has left the codes, and one workgroup reads all its keys four times; 15 of 60 rings with 329 000 to
+// 811 000 elements were 0.45 to 0.98 times as fast as in many launches, the others 1.02 to 1.85 (6 workers of 675 000 65 / 137 us, 9 of 461 000 63 / 128).
+constexpr uint32_t kChooseMost = 819200, kChooseMostOf3 = 655360, kChooseMostSpiky = 327680;
 hipError_t launch_topk_choose(const Tables& t, const StepArgs& a, const ChooseTables& c, hipStream_t s);
 hipError_t launch_topk_apply(const Tables& t, const StepArgs& a, uint32_t chunk_elems, hipStream_t s);
 hipError_t launch_average(const Tables& t, float* out, hipStream_t s);

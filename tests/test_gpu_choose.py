@@ -175,3 +175,11 @@ def test_more_keys_of_a_code_than_the_list_holds(evg, oracle_mod, every, ppm, li
 @pytest.mark.parametrize("P,n", [(3, 655_360), (3, 655_361), (4, 819_200), (4, 819_201)])
 def test_the_longest_tensors_of_a_workgroup(evg, oracle_mod, P, n):
     _run(evg, oracle_mod, _workload(P, [n, 9], 4, topk_ppm=30_000))
+
+
+# a spike drives a long tensor's threshold out of its codes; with spikes only shorter ones are one workgroup's, and with those the ring's update pass
+@pytest.mark.parametrize("n,spikes,want", [(327_680, 0.1, "k_update_ring"), (327_681, 0.1, "k_update"), (327_681, 0.0, "k_update_ring")])
+def test_long_tensors_with_spikes_are_not_one_workgroups(evg, oracle_mod, n, spikes, want):
+    w = _workload(6, [n, 9], 4, topk_ppm=30_000, spike_prob=spikes, spike_gain=5.0)
+    assert evg.Ring.from_workload(w).update_pass()[0] == want
+    _run(evg, oracle_mod, w)
