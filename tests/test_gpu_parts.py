@@ -1,6 +1,6 @@
-"""Cached rings that send whole tensors are updated in parts of the ring, one workgroup to a window and a part.  Checked
-against the oracle at the rings where a part can go wrong (closed rings of 3 to 8 workers, last parts of one worker or a
-few, parts of 2, 4 and 8), with and without a tensor whose tests need a launch of their own, and replayed from a graph, in
+"""Cached rings that send whole tensors are updated in parts of the ring, one workgroup to a window and a part, or (most of those here
+of at most 16 workers) one to a window of the whole ring; test_gpu_passes.py says which and has the rings of the other pass.  Checked
+against the oracle at closed rings of 3 to 8 workers, last parts of one worker or a few, with and without a tensor whose tests need a launch of their own, and replayed from a graph, in
 whose launches every workgroup keeps count of the iterations by itself."""
 import numpy as np
 import pytest
@@ -25,7 +25,7 @@ def _workload(P, sizes, iters, **kw):
     return inputs.Workload("parts", P, tensors, iters, sigma0=0.05, decay=0.9, seed=P, **kw)
 
 
-# few windows: parts of 2; some 300: of 4; some 1000: of 8
+# 17 workers, 13 and 16 that draw, and 8 with 520 windows and normal gradients: parts, of 4 and 8; the others whole rings
 @pytest.mark.parametrize("P,sizes", [(3, [1300, 7, 2048]), (4, [1023, 1, 5]), (5, [1025, 3]), (9, [4097, 2]),
                                      (3, [1021] * 310), (4, [3] * 300), (9, [1027] * 90), (17, [5] * 100),
                                      (8, [2] * 520), (9, [3] * 430), (11, [1] * 400), (16, [1023] * 240),

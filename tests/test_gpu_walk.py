@@ -30,7 +30,8 @@ def _run(evg, oracle_mod, P, numels, *, norm_mode=0, iters=7, **kw):
     assert rep["rel"]["x"] <= 1e-5 and (differ or all(rep["bitwise"].values())), rep
 
 
-# so few windows: 3 and 4 workers in one part, more in parts of one worker
+# so few windows: 3 and 4 workers in one part, more in parts of one worker (whole sends of at most 64 workers are not walked, nor further down: those
+# that are, test_gpu_passes.py)
 @pytest.mark.parametrize("P", [3, 4, 15, 16, 17, 23, 63, 64, 65, 66, 130])
 @pytest.mark.parametrize("kw", [dict(), dict(momentum=0.0, spike_prob=0.3, spike_gain=4.0), dict(topk_ppm=100_000),
                                 dict(topk_ppm=20_000, dist=1, topk_key=1)], ids=["whole", "plain", "topk", "topk_value"])
@@ -62,8 +63,8 @@ def test_last_bins_and_codes(evg, oracle_mod, numels, kw):
     _run(evg, oracle_mod, 5, numels, topk_ppm=50_000, iters=9, **kw)
 
 
-# Tensors of one window each, and a longer one.  Of about 100 windows whole sends and Top-K go in parts of 3 workers (19 = 6 * 3 + 1),
-# 5 and 9 (65), 9 and 17 (130); of 200 in parts of 4 (16), 5 and 12 (23), 9 (66); of 330 in one part (15), of 9 (17), 10 (65).
+# Tensors of one window each, and a longer one.  Of about 100 windows Top-K goes in parts of 3 workers (19 = 6 * 3 + 1), 9 (65),
+# 17 (130), whole sends of 5 (65) and 9 (130); of 200 Top-K of 4 (16), 12 (23), both of 9 (66); of 330 Top-K in one part (15), of 9 (17), both of 10 (65).
 @pytest.mark.parametrize("windows,P", [(100, 19), (100, 65), (100, 130), (200, 16), (200, 23), (200, 66), (330, 15), (330, 17), (330, 65)])
 @pytest.mark.parametrize("kw", [dict(), dict(topk_ppm=100_000)], ids=["whole", "topk"])
 def test_parts(evg, oracle_mod, windows, P, kw):
