@@ -205,15 +205,13 @@ def main():
     rho = w.topk_ppm / 1e6
     f_full = float((st["events_full_rl"].astype(np.float64) * numel[None, :]).sum() / (elems * args.steps))
     f_topk = float((st["events_topk_rl"].astype(np.float64) * numel[None, :]).sum() / (elems * args.steps))
-    # rings that stream from memory, with ordinary delivery: the update pass walks the ring (where xhat is reset at events it
-    # reads the mailboxes too, as the pass of the other rings does)
+    # with ordinary delivery all passes but k_update go by xhat instead of the mailboxes (the walk not where xhat is reset at events)
+    kernel = ring.update_pass()[0]
+    whole = kernel in ("k_update_part", "k_update_ring")
+    walks = whole or (kernel == "k_update_walk" and not args.xhat_reset)
+    # a streaming Top-K ring, and a cached one with such a pass, leave a key code for each element, a byte, from which the selection is made
     beyond_cache = 20 * w.P * evg.padded_numel(w.layer_numel) > (128 << 20)
-    streams = beyond_cache and not args.delivery_delay
-    # ... and so do the parts of the ring in which cached rings are updated (Top-K: with tensors of at most 819 200 elements)
-    parts = not beyond_cache and not args.delivery_delay and not (w.topk_ppm and (args.xhat_reset or max(w.layer_numel) > 819_200))
-    walks = (streams and not args.xhat_reset) or parts
-    # a streaming Top-K ring, and those parts, leave a key code for each element, a byte, from which the selection is made
-    codes = 1 if w.topk_ppm and (beyond_cache or parts) else 0
+    codes = 1 if w.topk_ppm and (beyond_cache or whole) else 0
     if walks:
         step_bytes_per_elem = (20 if w.momentum != 0.0 else 12) + 8 * f_full + codes + f_topk + 20 * rho * f_topk
     else:
@@ -274,9 +272,6 @@ def main():
                                                      or args.topk_ppm is not None) else None
         upd_counters = (counters or {}).get("kernels", {}).get("k_update", {})
         traffic = upd_counters.get("traffic_bytes")
-        # few workers have their stretches of a window in one workgroup
-        one_shot = w.P <= 16 and (parts if not streams else not w.topk_ppm)
-        kernel = "k_update_ring" if one_shot else "k_update_walk" if streams else "k_update_part" if parts else "k_update"
         out["roofline"] = {"kernel": kernel, "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
                            "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                            "traffic": traffic,

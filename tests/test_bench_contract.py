@@ -68,3 +68,14 @@ def test_json_line_of_a_short_run(monkeypatch, capsys):
     # whole-tensor sends: nothing is patched, the line-granular floor is the algorithmic figure
     assert r["line_granular_floor_bytes_per_launch"] >= r["algorithmic_bytes_per_launch"]
     assert r["traffic"] is None and r["traffic_measured_at"] is None      # no counter run is recorded for configuration 2
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("config,more,kernel", [(1, ["--topk-ppm", "100000"], "k_update_part"), (1, [], "k_update_ring"),
+                                                (4, [], "k_update_walk"), (2, ["--delivery-delay", "1"], "k_update")])
+def test_the_kernel_named_is_the_one_that_runs(monkeypatch, capsys, config, more, kernel):
+    mod = load_bench()
+    monkeypatch.setattr(sys, "argv", ["bench.py", "--config", str(config), "--steps", "3", "--warmup", "1", "--no-cpu-baseline"] + more)
+    mod.main()
+    line = [l for l in capsys.readouterr().out.splitlines() if l.startswith("{")][-1]
+    assert json.loads(line)["roofline"]["kernel"] == kernel
