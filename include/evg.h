@@ -126,7 +126,7 @@ typedef struct {
                                    without delivery delay each receiver fetches what its neighbours
                                    send inside the update pass, from a copy of x the library keeps
                                    (two more arrays of the ring's size, library-owned; not where one
-                                   workgroup has the whole ring of up to 8 workers at hand); not where
+                                   workgroup has the whole ring, of up to 16 workers, at hand); not where
                                    Top-K messages are sent and xhat_reset or EVG_NORM_SEPARATE is
                                    set or seven arenas exceed 256 MB.  If such a ring sends whole tensors, its norms are
                                    accumulated by the update pass (norm_mode) and no tensor is

@@ -354,9 +354,9 @@ static uint64_t admitted_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, 
 // the sums that the tests read and the threads get many.  Four workers or fewer with long networks: whole sweeps.  A workgroup of more than twelve wavefronts leaves
 // a CU too few of them beside it unless it has much to load.  Kernels_parts.hip / groups and quads 1 1 / 2 1 / 2 2 / 4 2, us a step, normal
 // gradients: perceptrons of 102 windows on 4 workers 6.2 / 5.7 / 5.4 / 5.6 / 6.2, 39 on 4 5.1 / 4.5 / 4.7 / 4.9 / 5.4, 506 on 6 22.0 / 20.6 / 20.2 / 17.3 /
-// 17.9; ResNet-20 of 314 on 3 8.8 / 7.4 / 7.9 / 7.8 / 8.5, on 8 14.5 / 13.6 / 16.5 / 12.6 / 15.6, on 16 30.1 / 27.2 / - / 26.5 / -, of 186 on 15 13.7 / 16.3 / - / 15.3 / -;
+// 17.9; ResNet-20 of 314 on 3 8.8 / 7.4 / 7.9 / 7.8 / 8.5, on 8 14.5 / 13.6 / 16.5 / 12.6 / 15.6, of 186 on 15 13.7 / 16.3 / - / 15.3 / -;
 // ResNet-18 of 729 on 4 16.9 / 18.2 / 18.6 / 17.8 / 16.8, ResNet-20 of 923 on 4 17.2 / - / - / - / 17.8; more workers have one float4 each of several: 120 windows on 24 12.7 and 15.4.  Top-K, kernels_parts.hip / 1 2 / 2 2:
-// ResNet-20 of 314 windows on 8 33.6 / 32.4 / 32.3, on 16 67.3 / 60.1 / 63.9, of 426 on 15 86 / 76 / 83; perceptrons of 129 on 11 32.4 / - / 34.9, of
+// ResNet-20 of 314 windows on 8 33.6 / 32.4 / 32.3, on 16 45.1 / 43.9 / 49.6, of 426 on 10 36.5 / 37.1 / 38.6; perceptrons of 129 on 11 32.4 / - / 34.9, of
 // 237 on 10 44.0 / 49.2 / 45.8; ResNet-18 of 729 on 4 39.7 / - / 41.4, ResNet-20 of 509 on 4 with given gradients 27.8 / - / 25.8.
 // One ring differs by up to a fifth between allocations of its arenas.  More rings, each in four of them, how many times as fast as with kernels_parts.hip:
 //   windows that are mostly empty, on 3 and 4 workers (tensors of 4, 30 and 200 elements): 4 2 0.82 .. 1.13, 1 1 1.4 .. 2.5
@@ -655,7 +655,8 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
   }
   c->chunk_elems = ce;
   c->asked_SW = ce_asked / (uint32_t)kSweep;
-  // One workgroup per window and the whole ring, if that is enough of them for the 256 CUs; few windows are better walked in
+  // The parts in which a ring is walked (Top-K messages; whole sends of more than 64 workers, or as stream_shape leaves them; the figures of whole sends
+  // on fewer workers are from before that).  One workgroup per window and the whole ring, if that is enough of them for the 256 CUs; few windows are better walked in
   // parts, although the sends of the workers at their ends need a pass of their own.  What a part costs besides grows
   // with the windows, so a part has at least `fewest` workers, and there are no more than give `aim` workgroups (Top-K: of two
   // windows each).  Measured with parts of 1 to all workers, us a step, whole sends: perceptrons of 28 windows on 15 workers 16 in

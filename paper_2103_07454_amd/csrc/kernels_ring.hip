@@ -12,13 +12,13 @@
 // waits 1 for the other wavefronts.  A rolled draw (a third of the code) is slower (12.6 -> 13.8 us), so are 64 registers for eight
 // wavefronts a SIMD (they spill: 12.6 -> 13 and more), and kernel arguments that are there with the wavefront gain 0.1 us at most.
 // Steps, kernels_parts.hip -> here: the smallest perceptron on 4 workers 6.2 -> 5.4 us, 8 ResNet-20 workers 14.5 -> 12.6, replayed 19.4 -> 18.0,
-// 16 30.1 -> 26.4, 9 of width 24 39.5 -> 34.3, 12 ResNet-18 workers of width 8 14.2 -> 12.6 (the rule: ring_shape).
+// 9 of width 24 39.5 -> 34.3, 12 ResNet-18 workers of width 8 14.2 -> 12.6 (which rings: ring_shape).
 //
 // Streaming rings (STREAM): memory, at 5.1 to 5.5 TB/s, where workgroups that go around the ring (kernels_walk.hip) reach 4.8 to 5.1: these take one window
 // after the other, all at once, in the order of their addresses, and a ring of few windows has as many wavefronts as workers.  The
 // trigger tests are a launch of their own, so that xhat is not read where the whole tensor is sent.  Walked -> here: 16 ResNet-18 workers 873 -> 817 .. 845 us,
-// with given gradients 1035 -> 1010 .. 1022, 7 of width 23 with given gradients and plain SGD 54.0 -> 47.5, 13 ResNet-20 of width 24 49.6 -> 37.5 (the rule:
-// stream_shape).  Runs of neighbouring windows for an XCD: no faster (2 or 4), 3 % slower (8 and more).
+// with given gradients 1035 -> 1010 .. 1022, 7 of width 23 with given gradients and plain SGD 54.0 -> 47.5, 13 ResNet-20 of width 24 49.6 -> 37.5; 32
+// ResNet-18 workers with plain SGD 1242 and 1241 (which rings: stream_shape).  Runs of neighbouring windows for an XCD: no faster (2 or 4), 3 % slower (8 and more).
 #include "message_device.h"
 #include "quad_device.h"
 #include "trigger_device.h"

@@ -14,8 +14,8 @@
 //                   bin b, and the keys IN bin b (a sixty-fourth of an octave where the threshold was expected, some 0.4 % of the
 //                   tensor), whose next 11 bits it counts.  From the key codes of the last update pass, 1 byte an element
 //                   instead of 8, where bin b has a code: only the keys in it are fetched then
-//   k_topk_low      the last bits of the in-bin keys under the prefix found so far -> threshold key (last_bin)
-//   k_topk_count    keys above and equal to the threshold per group, as running totals over a chunk
+//   k_topk_low      counts the last bits of the in-bin keys under the prefix found so far
+//   k_topk_count    the threshold key from those counts (last_bin), and keys above and equal to it per group, as running totals over a chunk
 //   k_topk_scan     the same over a tensor's chunks, and the cut
 //   k_topk_apply    messages written and applied ahead of the update pass, where that pass cannot
 // Codes and fine bins, steps before -> now: 16 ResNet-18 workers with given gradients, 10 % 1371 -> 1277 us (k_topk_stage 184 -> 61, the
@@ -25,8 +25,8 @@
 // The many launches are bound by their chains of dependent reads, which go together where they can, and by vector instructions in k_topk_stage.
 // 64 ResNet-18 workers, 10 %, and 8 ResNet-50 workers, 1 %, us a launch, before -> now: k_topk_decide 28 -> 21 and 10 -> 8 (bins asked for ahead of the
 // test), k_topk_stage 360 -> 349 and 70 -> 60 (compare_codes, one list of a lane's two loads), k_topk_low 27 -> 21 and 9 -> 7.5, and a launch
-// of 6 and 5 less (last_bin).  Steps: 16 ResNet-18 workers with given gradients, 10 % 1269 -> 1259, 8 ResNet-50 1160 -> 1150, 64 ResNet-18
-// 4547 -> 4538, 42 ResNet-20 of width 18, 14 % 210 -> 204, 31 ResNet-50 of width 46 with spikes, 0.5 % 2232 -> 2208.
+// of 6 and 5 less (last_bin).  Steps of large rings hardly differ for it (16 ResNet-18 workers with given gradients, 10 % 1265 and 1259, 8 ResNet-50 1157 and
+// 1153, 64 ResNet-18 4528 and 4520: no more than two runs do), small ones do: 42 ResNet-20 of width 18, 14 % 210 -> 204.
 // (The selection used to stage every possible winner as (index, value) and to compact the messages from there;
 // the update passes then scattered three messages each into LDS.)
 // Cached rings whose tensors are not too long make the whole selection in one launch, kernels_choose.hip.
@@ -510,8 +510,8 @@ __device__ __forceinline__ LastBin last_bin(const uint32_t* bins, uint32_t n, ui
   return {top - l, l == 64u ? 0u : krem};
 }
 
-// The last 6 or 10 bits of the in-bin keys that carry the prefix found so far.  Matches are
-// rare (a 2^-25 or 2^-21 slice of the key range), so they go straight to the tensor's histogram,
+// The last 6, 9 or 10 bits of the in-bin keys that carry the prefix found so far.  Matches are
+// rare (a 2^-25 to 2^-21 slice of the key range), so they go straight to the tensor's histogram,
 // one atomic per distinct value per 64 entries.
 __global__ __launch_bounds__(kThreads) void k_topk_low(Tables T, StepArgs A) {
   Staged s;
