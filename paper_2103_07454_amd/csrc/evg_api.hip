@@ -364,7 +364,7 @@ static uint64_t admitted_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, 
 //   7 and 8 workers, ResNets of 4000 units and more: normal gradients 0.90 .. 1.00 and 1.10 (7 rings), Student-t's and given ones 1.00 .. 1.23
 //   9 to 12, drawn gradients: where every CU has had two workgroups and a few are left (513 to 600) 0.89 .. 0.99, else 0.98 .. 1.24 (22 rings, 1.06 in the middle)
 //   13 to 16, drawn gradients: ResNets 0.78 .. 1.11 (45 rings, 0.99), perceptrons with normal ones 1.08 .. 1.20, with Student-t's 0.81 .. 0.99
-//   13 to 16, given ones, where a workgroup has a CU: 1 1 of up to 256 of them 1.19 .. 1.28, of more 0.81 .. 0.94 where 2 2 is 1.05 .. 1.17; 2 2 of
+//   13 to 16, given ones, where a workgroup has a CU: 1 1 of up to 256 of them 1.19 .. 1.28 (below 800 units, where it is not taken, 1.15 .. 1.21 on four rings), of more 0.81 .. 0.94 where 2 2 is 1.05 .. 1.17; 2 2 of
 //   264 (ResNet-20 of width 10) 0.86 .. 0.93, of 265 to 288 in a perceptron 1.09 .. 1.11, else 0.89 .. 1.31 (53 rings, 1.11)
 //   Top-K, 9 to 16, drawn gradients: of 2700 units and more 0.85 .. 1.07 (34 rings, 0.95), fewer 1.00 .. 1.13 (with a tensor of 155 000 elements 0.92)
 static void ring_shape(uint32_t P, uint64_t windows, const std::vector<LayerDesc>& layers, uint64_t N, bool topk, bool tests, bool given, bool normal,
@@ -416,7 +416,8 @@ static void ring_shape(uint32_t P, uint64_t windows, const std::vector<LayerDesc
 // All workers' stretches of a window are read and written at once.  Where they lie multiples of 8 KB apart, or nearly, those of more than eight workers can get in each
 // other's way in the memory: ResNet-18 of width 39 with workers 8192 n + 0, 256, 1024, 2048 and 4096 bytes apart on 20 workers 0.83 .. 0.93, 0.95, 0.98, 0.97 and 0.97
 // times as fast as walked, on 12 0.86 .. 0.91, 0.95, 1.01, 1.01 and 0.99, on 7 1.00 .. 1.08, 1.05, 1.08, 1.09 and 1.10.  (Not always: ResNet-50s of width 17 to 44 on 10 to 29
-// workers, 8192 n + 0 and 256 apart, would be 1.04 to 1.18 times as fast.)
+// workers, 8192 n + 0 and 256 apart, would be 1.04 to 1.18 times as fast.)  From 512 bytes on: 22 rings with
+// workers 8192 n + 512 to 1280 bytes apart, or as much less, 0.94 to 1.64 times as fast (1.06 in the middle).
 static void stream_shape(uint32_t P, uint64_t row, uint64_t N, uint32_t longest, uint32_t* groups, uint32_t* quads) {
   *groups = *quads = 0;
   const uint64_t bytes = 5 * P * row, apart = (row + 256) % 8192;      // (rows are multiples of 256 bytes)
