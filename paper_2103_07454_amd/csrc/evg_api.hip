@@ -361,13 +361,17 @@ static uint64_t admitted_bytes(uint64_t P, uint64_t L, uint64_t C, uint64_t SW, 
 // One ring differs by up to a fifth between allocations of its arenas.  More rings, each in four of them, how many times as fast as with kernels_parts.hip:
 //   windows that are mostly empty, on 3 and 4 workers (tensors of 4, 30 and 200 elements): 4 2 0.82 .. 1.13, 1 1 1.4 .. 2.5
 //   a tensor of 131 000 elements on 8: 2 1 0.92, 1 1 1.21; of 112 000 to 128 000 on 5 to 7 2 1 1.13 .. 1.15, 1 1 1.13 .. 1.18
-//   7 and 8 workers, ResNets of 4000 units and more: normal gradients 0.90 .. 1.00 and 1.10 (7 rings), Student-t's and given ones 1.00 .. 1.23
-//   9 to 12, drawn gradients: where every CU has had two workgroups and a few are left (513 to 600) 0.89 .. 0.99, else 0.98 .. 1.24 (22 rings, 1.06 in the middle)
-//   13 to 16, drawn gradients: ResNets 0.78 .. 1.11 (45 rings, 0.99), perceptrons with normal ones 1.08 .. 1.20, with Student-t's 0.81 .. 0.99
+//   7 and 8 workers, ResNets of 4000 units and more in one part of the ring: normal gradients 0.90 .. 1.00 (6 rings), Student-t's and given ones 1.00 .. 1.23; with a
+//   tensor whose tests need a launch of their own, in parts of four, 1.1 and 1.2
+//   9 to 12, drawn gradients: where every CU has had two workgroups and a few are left (513 to 600) and parts are of four workers 0.89 .. 0.96 (3 rings), else
+//   0.98 .. 1.33 (24 rings, 1.06 in the middle)
+//   13 to 16, drawn gradients, of 512 elements: normal ones, ResNets 0.78 .. 1.02 (21 rings, 0.96), perceptrons 1.08 .. 1.20; Student-t's, up to 680 workgroups 0.98 .. 1.31
+//   (513 and more with spikes 0.89 .. 0.93), more 0.81 .. 1.07 (18 rings, 0.99).  Where windows are mostly empty (tensors of 4 to 1100 elements), 7 to 16 workers, 1.1 .. 1.7
 //   13 to 16, given ones, where a workgroup has a CU: 1 1 of up to 256 of them 1.19 .. 1.28 (below 800 units, where it is not taken, 1.15 .. 1.21 on four rings), of more 0.81 .. 0.94 where 2 2 is 1.05 .. 1.17; 2 2 of
 //   264 (ResNet-20 of width 10) 0.86 .. 0.93, of 265 to 288 in a perceptron 1.09 .. 1.11, else 0.89 .. 1.31 (53 rings, 1.11)
-//   Top-K, 9 to 16, drawn gradients: of 2700 units and more 0.85 .. 1.07 (34 rings, 0.95), fewer 1.00 .. 1.13 (with a tensor of 155 000 elements 0.92)
-static void ring_shape(uint32_t P, uint64_t windows, const std::vector<LayerDesc>& layers, uint64_t N, bool topk, bool tests, bool given, bool normal,
+//   Top-K, 9 to 16, drawn gradients: of 2700 units and more 0.85 .. 1.07 (34 rings, 0.95; where windows are mostly empty 1.0 .. 1.3), fewer 1.00 .. 1.13 (with a tensor
+//   of 155 000 elements 0.92)
+static void ring_shape(uint32_t P, uint64_t windows, const std::vector<LayerDesc>& layers, uint64_t N, bool topk, bool tests, bool given, bool normal, bool spikes,
                        uint32_t* groups, uint32_t* quads) {
   *groups = *quads = 0;
   const uint64_t units = windows * P;
@@ -377,14 +381,14 @@ static void ring_shape(uint32_t P, uint64_t windows, const std::vector<LayerDesc
     of256 += (d.numel + 255ull) / 256;
     of512 += (d.numel + 511ull) / 512;
   }
-  const bool one_long = 2 * longest > N;
+  const bool one_long = 2 * longest > N, thin = 10 * N < 6 * 1024 * windows;       // windows are mostly empty, or nearly so
   if (P > 16 || (P > 12 && units < (given && !topk ? 800 : 4000))) return;
   if (topk) {
-    if (units < 1700 || (longest > 150000 && P > 8) || (P <= 4 && !given) || (P > 8 && !given && units >= 2700)) return;
+    if (units < 1700 || (longest > 150000 && P > 8) || (P <= 4 && !given) || (P > 8 && !given && !thin && units >= 2700)) return;
     *groups = P > 12 ? 1 : 2;
     *quads = 2;
   } else if (P > 12) {
-    if (given ? of256 > 256 && of512 > 256 && of512 <= 288 && !one_long : !(one_long && normal)) return;
+    if (!thin && (given ? of256 > 256 && of512 > 256 && of512 <= 288 && !one_long : normal ? !one_long : of512 > (spikes ? 512 : 680))) return;
     *groups = *quads = given && of256 <= 256 ? 1 : 2;
   } else if (P <= 4 && windows >= 700 && !given) {
     return;
@@ -393,7 +397,7 @@ static void ring_shape(uint32_t P, uint64_t windows, const std::vector<LayerDesc
     *groups = full ? 4 : 1;
     *quads = full ? 2 : 1;
   } else if (units >= 1300) {
-    if (!given && !one_long && (P > 8 ? of512 > 512 && of512 <= 600 : P > 6 && normal && units >= 4000)) return;
+    if (!given && !one_long && !thin && (P > 8 ? of512 > 512 && of512 <= 600 && units < 3400 : P > 6 && tests && normal && units >= 4000)) return;
     *groups = *quads = 2;
   } else {
     *groups = tests && longest > 65536 && P <= 6 ? 2 : 1;
@@ -601,7 +605,7 @@ static evg_status init_common(evg_ctx** out, const evg_config* cfg, void* hip_st
     // 8 15.7 / 14.3 / 16.6, on 12 25.7 / 22.6 / 19.2, on 16 34.1 / 33.4 / 30.7; 438 on 8 24.9 / 21.8 / 18.4, on 16 53.3 / 48.9 / 49.0.
     groups = quads = 0;
     fine = 1;
-    if (ring_may_be && in_parts && small_ring) ring_shape(P, windows, layers, c->N, cfg->topk_ppm != 0, one_launch, cfg->grad_mode == EVG_GRAD_BUFFER, cfg->synth.dist == EVG_DIST_NORMAL, &groups, &quads);
+    if (ring_may_be && in_parts && small_ring) ring_shape(P, windows, layers, c->N, cfg->topk_ppm != 0, one_launch, cfg->grad_mode == EVG_GRAD_BUFFER, cfg->synth.dist == EVG_DIST_NORMAL, cfg->synth.spike_prob > 0.0f, &groups, &quads);
     if (may_be && !c->cached && !cfg->topk_ppm && !cfg->delivery_delay && cfg->norm_mode == EVG_NORM_FUSED) stream_shape(P, Npad * 4, c->N, longest, &groups, &quads);
     one_shot = groups && !in_parts;
     if (groups) {

@@ -25,7 +25,7 @@ def _workload(P, sizes, iters, **kw):
     return inputs.Workload("parts", P, tensors, iters, sigma0=0.05, decay=0.9, seed=P, **kw)
 
 
-# 17 workers, 13 and 16 that draw, and 8 with 520 windows and normal gradients: parts, of 4 and 8; the others whole rings
+# 17 workers, and 13 and 16 that draw: parts, of 4 and 8; the others whole rings
 @pytest.mark.parametrize("P,sizes", [(3, [1300, 7, 2048]), (4, [1023, 1, 5]), (5, [1025, 3]), (9, [4097, 2]),
                                      (3, [1021] * 310), (4, [3] * 300), (9, [1027] * 90), (17, [5] * 100),
                                      (8, [2] * 520), (9, [3] * 430), (11, [1] * 400), (16, [1023] * 240),

@@ -150,8 +150,9 @@ def test_replays_that_outlive_an_import(evg, P, sizes, part, which, streams, tri
         g.replay()
         b.step(k)
         same(k)
-    a.step(6)
+    a.step(6)                              # on its own stream, which the replays' does not wait for
     b.step(6)
+    same(6)
     g.replay()
     b.step(7)
     same(7)

@@ -167,13 +167,16 @@ def test_a_resumed_ring_goes_on_bit_for_bit(evg, P, sizes, stream, kw):
     (9, EDGES, {}, True, False, ("k_update_ring", 9, 256)), (65, EDGES, {}, True, False, ("k_update_walk", 1, 0)),
     (5, EDGES, dict(topk_ppm=100_000), True, False, ("k_update_walk", 5, 0)),
     (7, EDGES + [65537], {}, False, False, ("k_update_ring", 7, 256)), (4, [200] * 450, {}, False, True, ("k_update_ring", 4, 256)),
-    (8, [1100] * 260, {}, False, False, ("k_update_part", 8, 1024)), (8, [1100] * 260, dict(dist=1), False, False, ("k_update_ring", 8, 512)),
+    (8, [1000] * 505, {}, False, False, ("k_update_part", 8, 1024)), (8, [1000] * 505, dict(dist=1), False, False, ("k_update_ring", 8, 512)),
+    (8, [1100] * 260, {}, False, False, ("k_update_ring", 8, 512)), (8, [1000] * 370 + [140_000], {}, False, False, ("k_update_ring", 8, 512)),
     (10, [1000] * 260, {}, False, False, ("k_update_part", 4, 1024)), (10, [1000] * 260, {}, False, True, ("k_update_ring", 10, 512)),
-    (13, [600] * 320, {}, False, False, ("k_update_part", 8, 1024)), (13, [320_000, 9], {}, False, False, ("k_update_ring", 13, 512)),
-    (13, [320_000, 9], dict(dist=1), False, False, ("k_update_part", 4, 1024)),
+    (12, [1000] * 290, {}, False, False, ("k_update_ring", 12, 512)), (13, [1000] * 320, {}, False, False, ("k_update_part", 8, 1024)),
+    (13, [1000] * 320, dict(dist=1), False, False, ("k_update_ring", 13, 512)),
+    (13, [1000] * 320, dict(dist=1, spike_prob=0.1), False, False, ("k_update_part", 8, 1024)), (13, [300] * 320, {}, False, False, ("k_update_ring", 13, 512)), (13, [320_000, 9], {}, False, False, ("k_update_ring", 13, 512)),
+    (13, [360_000, 9], dict(dist=1), False, False, ("k_update_part", 4, 1024)),
     (13, [64_000, 10], {}, False, True, ("k_update_ring", 13, 256)), (13, [2000] * 66, {}, False, True, ("k_update_part", 4, 1024)),
     (13, [2000] * 150, {}, False, True, ("k_update_ring", 13, 512)), (10, [1000] * 280, dict(topk_ppm=100_000), False, False, ("k_update_part", 4, 1024)),
-    (10, [1000] * 280, dict(topk_ppm=100_000), False, True, ("k_update_ring", 10, 512))], ids=lambda v: f"{len(v)} tensors" if isinstance(v, list) else str(v))
+    (10, [300] * 280, dict(topk_ppm=100_000), False, False, ("k_update_ring", 10, 512)), (10, [1000] * 280, dict(topk_ppm=100_000), False, True, ("k_update_ring", 10, 512))], ids=lambda v: f"{len(v)} tensors" if isinstance(v, list) else str(v))
 def test_the_pass_chosen(evg, P, sizes, kw, stream, given, want):
     ring = evg.Ring.from_workload(_workload(P, sizes, **kw), grad_mode=int(given), access_mode=evg.ACCESS_STREAM if stream else evg.ACCESS_AUTO)
     assert ring.update_pass() == want
